@@ -62,7 +62,11 @@ enum { VCNN_PASS_FWD = 0, VCNN_PASS_BWD_FILTER = 1, VCNN_PASS_BWD_DATA = 2 };
  * gradient of fp32 layers with more than 4 maps and channels compute their products (Eq. 1 / Eq. 2) as sums of
  * bfloat16 products: every float operand is, exactly, a sum of three bfloat16 terms, and the six largest of the nine
  * term products, accumulated in float, carry the product to within float rounding.  The result stays within the
- * float tolerance; the matrix cores multiply bfloat16 sixteen times as fast as float.  AUTO never takes it. */
+ * float tolerance; the matrix cores multiply bfloat16 sixteen times as fast as float.  AUTO never takes it.
+ * AUTO (and the choices that are AUTO elsewhere) computes the products of larger fp32 layers from two half-precision
+ * terms per operand, scaled by powers of two: 24 significand bits, three products, float accumulation.  The result is at
+ * least as close to the exact sums as the float instruction's.  IMPLICIT keeps to the float instruction.  An element
+ * smaller than 2^-29 of its tensor's largest keeps an absolute error below 2^-50 of that largest element. */
 enum { VCNN_ALGO_AUTO = 0, VCNN_ALGO_EXPLICIT = 1, VCNN_ALGO_IMPLICIT = 2, VCNN_ALGO_FOLD = 3, VCNN_ALGO_FFT = 4,
        VCNN_ALGO_SPLIT = 5 };
 
@@ -92,7 +96,9 @@ vcnn_status vcnn_set_conv_algo(int32_t algo);
 
 /* Output size of the layer of Eq. 1: oh = (h + 2*pad_h - r)/stride_h + 1, likewise ow. */
 vcnn_status vcnn_conv_out_shape(const vcnn_conv_desc* d, int32_t* oh, int32_t* ow);
-/* Bytes of workspace the given pass needs for this descriptor (may be 0). */
+/* Bytes of workspace the given pass needs for this descriptor (may be 0).  A call that brings less may still run, by a
+ * slower route that needs less; a forward pass or input gradient that brings more than it asks for may use it to work
+ * on more of the batch at once. */
 vcnn_status vcnn_conv_workspace_bytes(const vcnn_conv_desc* d, int32_t pass, size_t* bytes);
 
 /* phi_c (Eq. 2; mini-batch form Eq. 4): col[(c*R+r)*S+s][(n*OH+oh)*OW+ow] = xpad[n][c][oh+r-pad_h][ow+s-pad_w].

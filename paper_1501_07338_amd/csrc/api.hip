@@ -1,6 +1,8 @@
 // C-ABI entry points: argument validation, shape algebra, workspace layout and kernel selection.
 // Validation never touches the HIP runtime, so error paths can be exercised on a host without a GPU.
+#include <algorithm>
 #include <atomic>
+#include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -102,7 +104,7 @@ static bool fold_beats_halo(const ConvGeom& g, const HaloPlan& hp, const FoldPla
 
 // Which realisation a pass uses for a given shape.  The same decision drives the workspace query and
 // the launch, so the two always agree.
-enum Path { PATH_EXPLICIT, PATH_POINTWISE, PATH_FEW_OUT, PATH_FEW_IN, PATH_DIRECT_FILTER, PATH_HALO, PATH_HALO_FILTER, PATH_HALO_BF16, PATH_FILTER_BF16, PATH_HALO_FILTER_BF16, PATH_FEW_COLS_FILTER, PATH_SMALL, PATH_SMALL_BWD, PATH_FOLD, PATH_FFT, PATH_TAPS, PATH_POINTWISE_BF16, PATH_SPLIT };
+enum Path { PATH_EXPLICIT, PATH_POINTWISE, PATH_FEW_OUT, PATH_FEW_IN, PATH_DIRECT_FILTER, PATH_HALO, PATH_HALO_FILTER, PATH_HALO_BF16, PATH_FILTER_BF16, PATH_HALO_FILTER_BF16, PATH_FEW_COLS_FILTER, PATH_SMALL, PATH_SMALL_BWD, PATH_FOLD, PATH_FFT, PATH_TAPS, PATH_POINTWISE_BF16, PATH_SPLIT, PATH_F16X2 };
 struct Plan {
   Path path;
   DirectGeom dg;
@@ -117,13 +119,90 @@ struct Plan {
   PointwiseBf16Plan pwb;
   PointwiseFilterBf16Plan pwf;
   SplitPlan sp;
+  F16x2Plan f2;
   int split;        // channel slices (few-out), output-map group size (few-in) or batch slices (filter gradient)
   size_t partial_bytes;
   size_t workspace_bytes;
   size_t bias_offset;  // filter-gradient pass: where the bias-gradient partial sums live in the workspace
 };
 
-static Plan make_plan(const ConvGeom& g, int pass, int dtype) {
+// Scratch memory of the allocation-free kernel gradient (vcnn_conv_bwd_filter_noalloc), per GPU.
+static constexpr size_t kScratchBytes = (size_t)32 << 20;
+// What a two-term pass may ask for beyond its float route's own workspace.  Larger layers ask for the float route's and
+// work through the batch in parts that fit what they are given.  The kernel gradient keeps to the scratch memory above,
+// so that the allocation-free entry point takes every layer it took, by the same route as the ordinary one.
+static size_t two_term_allowance(int pass, size_t own) {
+  if (pass != VCNN_PASS_BWD_FILTER) return (size_t)64 << 20;
+  return own <= kScratchBytes ? kScratchBytes : (size_t)384 << 20;
+}
+static constexpr size_t kAsk = ~(size_t)0;  // make_plan: plan for the workspace query, not for a given workspace
+
+// Estimated time of a float matrix-core kernel, in seconds: `blocks` blocks of four waves, each wave `tiles` accumulator
+// tiles over a contraction of `depth` (64 cycles per tile and two elements), shared by the 256 CUs; a block alone on its
+// CU does not keep the pipe busy.  Against 100 passes of drawn layers (15 us to 1.5 ms) the halo kernel takes 1.0 to 1.8
+// times this, the kernel gradient 0.8 to 1.2 times (1.3 to 1.5 with 32-row tiles); the factors below sit inside.
+static double f32_seconds(double blocks, double tiles, double depth) {
+  return std::max(std::ceil(blocks / 256.0), 1.6) * depth * 32.0 * tiles * 1.2 / 2.4e9;
+}
+
+// Replaces the implicit float kernels by the two-term ones (split_f16.h) where these are faster: three products at the
+// half-precision rate instead of one at the float rate, for a scan of both operands and a re-laid copy of each.  On 100
+// drawn layers the estimates hold to about 20 %; 8 % are kept as margin.  (n c h w -> k r s, float
+// kernel / two-term: 16 38 64 64 -> 512 16 16 forward 3.20 / 1.13 ms, kernel gradient 3.13 / 0.95 ms; 64 64 64 64 -> 32
+// 5 5 0.284 / 0.121 and 0.341 / 0.161 ms, input gradient 0.277 / 0.113 ms; 2 41 47 11 -> 137 3 3, 0.08 GFLOP: 11 /
+// 29 us, stays.)  The error against 64 bits is smaller than that of the kernel it replaces: the float instruction rounds
+// a sum once per two elements, the two-term one once per sixteen - 1.25e-8 sqrt(K) against 3.3e-9 sqrt(K) beside 7e-8
+// of the split itself; in the kernel gradient, whose sums are cut in slices, the count of roundings decides.
+//
+// `offered`: the workspace the call has (kAsk: the query).  A call whose workspace only holds the float route's partial
+// sums runs that route, as it always has.
+static void prefer_two_terms(const ConvGeom& g, int pass, size_t offered, Plan* p) {
+  if (g.c <= 4 || g.k <= 4) return;  // channel groups of eight, most of them padding
+  const size_t bias = pass == VCNN_PASS_BWD_FILTER ? align256(bias_grad_partial_bytes(g)) : 0;
+  const size_t own = p->workspace_bytes + bias;  // what the float route needs
+  double f32 = 12e-6;
+  if (p->path == PATH_HALO) {
+    const bool fwd = pass == VCNN_PASS_FWD;
+    const double rows = fwd ? (double)g.k : (double)g.c, depth = (double)(fwd ? g.c : g.k) * g.r * g.s;
+    const double blocks = std::ceil(rows / p->hp.bm) * (double)g.n * (double)p->hp.tiles_per_img;
+    f32 += 1.3 * f32_seconds(blocks, (double)p->hp.bm * p->hp.bn / 4096.0, depth);
+    if (depth < 64) return;
+  } else if (p->path == PATH_HALO_FILTER) {
+    const HaloFilterPlan& h = p->hfp;
+    const double blocks = std::ceil((double)g.M / h.bm) * std::ceil((double)g.K / h.bnk) * h.splits;
+    f32 += (h.bm <= 32 ? 1.3 : 0.95) * f32_seconds(blocks, (double)h.bm * h.bnk / 4096.0, (double)g.N / h.splits) + 2.0 * (double)h.partial_bytes / 4e12;
+  } else {
+    return;
+  }
+  F16x2Plan f2{};
+  // (the kernel gradient's parts add up to one sum: its budget, and with it the order of that sum, depends on the
+  // shape alone, not on how much more a caller has)
+  const size_t ask = std::max(own, two_term_allowance(pass, own));
+  if (!conv_f16x2_plan(g, pass, ask - bias, &f2)) return;
+  const bool whole = f2.parts == 1;
+  if (!whole && pass == VCNN_PASS_BWD_FILTER) {
+    if (!conv_f16x2_plan(g, pass, own - bias, &f2)) return;
+  } else if (!whole) {
+    if (offered == kAsk || !conv_f16x2_plan(g, pass, offered, &f2)) return;
+  }
+  const size_t need = align256(f2.workspace_bytes) + bias;
+  if (offered != kAsk && need > offered) return;
+  if (pass == VCNN_PASS_BWD_FILTER) {
+    // variance of the rounding, in units of one float accumulation's: per output, (sums in a slice) + (slices)
+    const HaloFilterPlan& h = p->hfp;
+    const double waves_k = 4 / (f2.filter.waves_m * f2.filter.waves_n), slices = (double)f2.filter.splits * f2.parts;
+    const double before = (double)g.N / h.splits / 2 + h.splits;
+    const double after = 16 + 0.56 * ((double)g.N / 16 / (slices * waves_k) + slices + waves_k);
+    if (after > before) return;
+  }
+  if (f2.est_seconds + 12e-6 > 0.92 * f32) return;
+  p->path = PATH_F16X2;
+  p->f2 = f2;
+  // (a kernel gradient in parts asks for what the float route does: a call with less takes neither)
+  p->workspace_bytes = whole ? need - bias : std::max(own - bias, need - bias);
+}
+
+static Plan make_plan(const ConvGeom& g, int pass, int dtype, size_t offered) {
   Plan p{};
   p.path = PATH_EXPLICIT;
   const int algo = g_conv_algo.load();
@@ -283,6 +362,7 @@ static Plan make_plan(const ConvGeom& g, int pass, int dtype) {
       p.workspace_bytes = col_bytes(g) + align256(bwd_filter_partial_bytes(g));
     }
   }
+  if (automatic && dtype == VCNN_F32) prefer_two_terms(g, pass, offered, &p);
   if (pass == VCNN_PASS_BWD_FILTER) {
     p.bias_offset = p.workspace_bytes;
     p.workspace_bytes += align256(bias_grad_partial_bytes(g));
@@ -290,7 +370,11 @@ static Plan make_plan(const ConvGeom& g, int pass, int dtype) {
   return p;
 }
 
-static size_t workspace_need(const ConvGeom& g, int pass, int dtype) { return make_plan(g, pass, dtype).workspace_bytes; }
+static size_t workspace_need(const ConvGeom& g, int pass, int dtype) { return make_plan(g, pass, dtype, kAsk).workspace_bytes; }
+// the workspace a call brings, as far as it can be used
+static size_t usable(const void* workspace, size_t bytes) {
+  return workspace && (reinterpret_cast<uintptr_t>(workspace) & 255) == 0 ? bytes : 0;
+}
 
 }  // namespace vcnn
 
@@ -369,7 +453,7 @@ vcnn_status vcnn_conv_fwd(const vcnn_conv_desc* d, const void* x, const void* w,
 
 static vcnn_status conv_fwd_linear(const vcnn_conv_desc* d, const ConvGeom& g, const void* x, const void* w,
                                    const float* bias, void* y, void* workspace, size_t workspace_bytes, void* stream) {
-  const Plan plan = make_plan(g, VCNN_PASS_FWD, d->dtype);
+  const Plan plan = make_plan(g, VCNN_PASS_FWD, d->dtype, usable(workspace, workspace_bytes));
   if (vcnn_status s = check_ws(workspace, workspace_bytes, plan.workspace_bytes, "conv_fwd")) return s;
   hipStream_t st = (hipStream_t)stream;
   const int relu = d->act == VCNN_ACT_RELU;
@@ -387,6 +471,8 @@ static vcnn_status conv_fwd_linear(const vcnn_conv_desc* d, const ConvGeom& g, c
                                  bias, y, relu, workspace, st);
   }
   if (plan.path == PATH_FFT) return launch_conv_fft(plan.fft, dt, g, x, w, bias, y, relu, workspace, st);
+  if (plan.path == PATH_F16X2)
+    return launch_conv_f16x2_fwd(plan.f2, g, (const float*)x, (const float*)w, bias, (float*)y, relu, workspace, st);
   if (plan.path == PATH_SPLIT)
     return launch_conv_split_fwd(plan.sp, g, (const float*)x, (const float*)w, bias, (float*)y, relu, workspace, st);
   // (its 16-byte reads of the kernel matrix need that alignment; a matrix placed otherwise takes the generic product)
@@ -417,7 +503,7 @@ vcnn_status vcnn_conv_bwd_filter(const vcnn_conv_desc* d, const void* x, const v
   ConvGeom g;
   if (vcnn_status s = make_geom(d, &g)) return s;
   if (!x || !dy || !dw) return fail(VCNN_ERR_NULL, "conv_bwd_filter: NULL tensor");
-  const Plan plan = make_plan(g, VCNN_PASS_BWD_FILTER, d->dtype);
+  const Plan plan = make_plan(g, VCNN_PASS_BWD_FILTER, d->dtype, usable(workspace, workspace_bytes));
   if (vcnn_status s = check_ws(workspace, workspace_bytes, plan.workspace_bytes, "conv_bwd_filter")) return s;
   hipStream_t st = (hipStream_t)stream;
   const int dt = d->dtype;
@@ -429,6 +515,8 @@ vcnn_status vcnn_conv_bwd_filter(const vcnn_conv_desc* d, const void* x, const v
   } else if (plan.path == PATH_FEW_COLS_FILTER) {
     if (vcnn_status s = launch_filter_grad_few_cols(plan.fcp, dt, g, x, dy, dw, dbias, (float*)workspace, st)) return s;
     if (plan.fcp.bias_column) return VCNN_OK;  // the bias gradient came out of the same product
+  } else if (plan.path == PATH_F16X2) {
+    if (vcnn_status s = launch_conv_f16x2_filter(plan.f2, g, (const float*)x, (const float*)dy, dw, workspace, st)) return s;
   } else if (plan.path == PATH_SPLIT) {
     if (vcnn_status s = launch_conv_split_filter(plan.sp, g, (const float*)x, (const float*)dy, dw, workspace, st)) return s;
   } else if (plan.path == PATH_POINTWISE_BF16) {
@@ -462,7 +550,7 @@ static vcnn_status conv_bwd_data_impl(const vcnn_conv_desc* d, int act_below, co
   if (vcnn_status s = make_geom(d, &g)) return s;
   if (act_below < VCNN_ACT_NONE || act_below > VCNN_ACT_SIGMOID) return fail(VCNN_ERR_UNSUPPORTED, "%s: unknown activation %d", who, act_below);
   if (!w || !dy || !dx || (act_below != VCNN_ACT_NONE && !x)) return fail(VCNN_ERR_NULL, "%s: NULL tensor", who);
-  const Plan plan = make_plan(g, VCNN_PASS_BWD_DATA, d->dtype);
+  const Plan plan = make_plan(g, VCNN_PASS_BWD_DATA, d->dtype, usable(workspace, workspace_bytes));
   if (vcnn_status s = check_ws(workspace, workspace_bytes, plan.workspace_bytes, who)) return s;
   hipStream_t st = (hipStream_t)stream;
   const int dt = d->dtype;
@@ -480,6 +568,8 @@ static vcnn_status conv_bwd_data_impl(const vcnn_conv_desc* d, int act_below, co
     return then_act(launch_conv_halo_bf16(plan.hb, g.n, g.k, g.oh, g.ow, g.c, g.r, g.s, g.r - 1 - g.ph, g.s - 1 - g.pw, dy,
                                           w, (int64_t)g.r * g.s, g.K, 1, nullptr, dx, 0, workspace, st));
   }
+  if (plan.path == PATH_F16X2)
+    return then_act(launch_conv_f16x2_bwd_data(plan.f2, g, (const float*)w, (const float*)dy, (float*)dx, workspace, st));
   if (plan.path == PATH_POINTWISE_BF16) {
     // dx[n][c][p] = sum_m w[m][c] * dy[n][m][p]: the forward product on the transposed kernel matrix
     if (vcnn_status s = launch_flip_transpose(dt, w, workspace, g.k, g.c, 1, st)) return s;
@@ -534,7 +624,6 @@ vcnn_status vcnn_conv_bwd_data_act(const vcnn_conv_desc* d, int32_t act_below, c
 // instead of a caller workspace.  Every GPU the library runs on holds its own copy of the array, at its own address,
 // until the process ends; host code never uses the array's name as an address, only what hipGetSymbolAddress
 // returned for the device that is current.
-static constexpr size_t kScratchBytes = (size_t)32 << 20;
 static constexpr int kMaxDevices = 64;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 static std::atomic<void*> g_scratch_ptr[kMaxDevices];

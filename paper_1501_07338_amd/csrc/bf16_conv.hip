@@ -24,11 +24,13 @@
 // padding; there a step contracts four pairs, lanes 16 k .. 16 k + 15 the k-th of them.  The input gradient is the same kernel
 // run on dy with the flipped, transposed kernels (the re-ordering pass does the flip).
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "bf16_core.h"
 #include "common.h"
 #include "elem.h"
+#include "split_f16.h"
 
 namespace vcnn {
 
@@ -125,10 +127,77 @@ __global__ __launch_bounds__(kThreads) void reorder_weights_frag8_kernel(const b
   }
 }
 
+// The two re-laying passes for float operands as two f16 terms each (split_f16.h): the same layouts, one plane per term,
+// `term` 16-byte words apart; block 0 leaves the operand's exponent for the product kernel.
+__global__ __launch_bounds__(kThreads) void interleave_channels_split_kernel(const float* __restrict__ x,
+                                                                             uint4* __restrict__ x8, int64_t term, int C,
+                                                                             int CG, int HW, int64_t total,
+                                                                             SplitScales* __restrict__ sc, int operand) {
+  const int e = split_exponent(sc->partial[operand]);
+  const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  if (i == 0) {
+    sc->exponent[operand] = e;
+    x8[total] = make_uint4(0u, 0u, 0u, 0u);
+  }
+  if (i >= total) return;
+  const int pos = (int)(i % HW);
+  const int64_t t = i / HW;
+  const int g = (int)(t % CG);
+  const int64_t n = t / CG;
+  const float* src = x + (n * C + g * 8) * HW + pos;
+  float f[8];
+#pragma unroll
+  for (int c8 = 0; c8 < 8; ++c8) f[c8] = src[g * 8 + c8 < C ? (int64_t)c8 * HW : 0];
+  uint32_t v[8];
+#pragma unroll
+  for (int c8 = 0; c8 < 8; ++c8) v[c8] = g * 8 + c8 < C ? split_f16(f[c8], e) : 0u;
+  uint4 hi, lo;
+  pack_terms(v, &hi, &lo);
+  x8[i] = hi;
+  x8[i + term] = lo;
+}
+
+// (a thread owns the eight channels of one (row, tap): 16-byte stores; the reads of a wave, one float per lane at the
+// stride of a kernel's taps, share cache lines over the steps of a chunk)
+__global__ __launch_bounds__(kThreads) void reorder_weights_split_kernel(const float* __restrict__ in,
+                                                                         uint4* __restrict__ out, int64_t term, int CO,
+                                                                         int CI, int RS, int64_t so, int64_t si, int flip,
+                                                                         int cgc, int nchunks, int steps, int m16,
+                                                                         int64_t total, SplitScales* __restrict__ sc,
+                                                                         int operand) {
+  const int e = split_exponent(sc->partial[operand]);
+  const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  if (i == 0) sc->exponent[operand] = e;
+  if (i >= total) return;
+  const int lane = (int)i & 63;
+  int64_t t = i >> 6;
+  const int jl = (int)(t % steps);
+  t /= steps;
+  const int ch = (int)(t % nchunks);
+  const int mt = (int)(t / nchunks);
+  const int row = m16 ? mt * 16 + (lane & 15) : mt * 32 + (lane & 31);
+  const int u = m16 ? 4 * jl + (lane >> 4) : 2 * jl + (lane >> 5);
+  const int gl = u / RS, q = u - gl * RS;
+  const int c0 = (ch * cgc + gl) * 8;
+  const bool ok = row < CO && gl < cgc;
+  const float* src = in + (ok ? (int64_t)row * so + (int64_t)c0 * si + (flip ? RS - 1 - q : q) : 0);
+  float f[8];
+#pragma unroll
+  for (int c8 = 0; c8 < 8; ++c8) f[c8] = ok && c0 + c8 < CI ? src[(int64_t)c8 * si] : 0.f;
+  uint32_t v[8];
+#pragma unroll
+  for (int c8 = 0; c8 < 8; ++c8) v[c8] = split_f16(f[c8], e);
+  uint4 hi, lo;
+  pack_terms(v, &hi, &lo);
+  out[i] = hi;
+  out[i + term] = lo;
+}
+
 struct HaloBf16Args {
   const uint4* x8;    // [n][cg][h][w] positions of 8 channels
   int64_t x8_term;    // TERMS > 1: distance between the terms of x8, and of wf, in 16-byte words
   int64_t wf_term;
+  const int32_t* exponent;  // TERMS = 2: the two operands' scales (result times 2^-(exponent[0] + exponent[1]))
   const uint4* zero;  // 16 zero bytes
   const uint4* wf;    // [mt][chunk][step][64 lanes] fragments
   const float* bias;  // [m] or null
@@ -143,16 +212,43 @@ struct HaloBf16Args {
   int hpos;           // positions per halo buffer (cgc*nr*wp rounded up to a multiple of 64)
   int nbuf;           // halo buffers: 2 = the next chunk is staged during the products of this one, 1 = between chunks
   int relu;
+  int flush;          // TWO_LEVEL: slabs between two flushes of a wave's accumulators
 };
 
-// TERMS = 3: both operands are given as three bfloat16 terms each (a float split exactly into three), and a step
+// The term pairs a step multiplies, smallest first: {term of the first operand, term of the second}, the order in which
+// the next step's terms are first used, and the accumulator of a pair (two f16 terms: the mixed products have their own).
+template <int TERMS>
+struct SplitTerms {  // three bfloat16 terms (and, with PAIRS = 1, plain operands)
+  static constexpr int PAIRS = TERMS == 1 ? 1 : 6;
+  static constexpr int kA[6] = {2, 0, 1, 1, 0, 0}, kB[6] = {0, 2, 1, 0, 1, 0};
+  static constexpr int kOrderA[3] = {2, 0, 1}, kOrderB[3] = {0, 2, 1};
+  static constexpr bool kMixed[6] = {};
+};
+template <>
+struct SplitTerms<2> {
+  static constexpr int PAIRS = 3;
+  static constexpr int kA[3] = {1, 0, 0}, kB[3] = {0, 1, 0};
+  static constexpr int kOrderA[2] = {1, 0}, kOrderB[2] = {0, 1};
+  static constexpr bool kMixed[3] = {true, true, false};
+};
+template <int TERMS, typename Acc>
+__device__ __forceinline__ Acc mfma_term(uint4 a, uint4 b, Acc c) {
+  if constexpr (TERMS == 2) return mfma_f16(a, b, c);
+  else return mfma_bf16(a, b, c);
+}
+
+// TERMS = 2: floats as two f16 terms each (split_f16.h), three products per step, the mixed ones in an accumulator set
+// of their own.  TERMS = 3: both operands are given as three bfloat16 terms each (a float split exactly into three), and a step
 // multiplies the six largest of the nine term pairs - smallest first - into the same accumulators: the float product
 // to within float rounding, with every staged word and every fragment used for two or three MFMAs instead of one.
-template <int WAVES_M, int WAVES_K, int TM, int TN, bool M16 = false, int WAVES_N = 1, int TERMS = 1>
+// TWO_LEVEL (two terms): every a.flush slabs a wave adds its accumulators to a second set and starts them again from
+// zero.  A sum of s rounded additions becomes sums of about sqrt(s): the long contractions of an input gradient
+// (every map x every tap) then round less than the fold route, which adds them tap by tap.
+template <int WAVES_M, int WAVES_K, int TM, int TN, bool M16 = false, int WAVES_N = 1, int TERMS = 1, bool TWO_LEVEL = false>
 __global__ __launch_bounds__(kThreads, 2) void conv_halo_bf16_kernel(HaloBf16Args a) {
-  static_assert(TERMS == 1 || TERMS == 3, "plain bfloat16 operands, or floats as three terms");
-  constexpr int PAIRS = TERMS == 1 ? 1 : 6;
-  constexpr int kTermA[6] = {2, 0, 1, 1, 0, 0}, kTermB[6] = {0, 2, 1, 0, 1, 0};  // kernel-matrix term, input term
+  static_assert(TERMS >= 1 && TERMS <= 3, "plain bfloat16 operands, or floats as two f16 or three bfloat16 terms");
+  using Split = SplitTerms<TERMS>;
+  constexpr int PAIRS = Split::PAIRS;
   static_assert(WAVES_M * WAVES_K * WAVES_N * 64 == kThreads, "four waves per block");
   static_assert(!M16 || WAVES_M == 1, "16-row tiles: every wave holds all rows");
   constexpr int TILE = M16 ? 16 : 32;     // rows and pixels of one accumulator tile
@@ -231,6 +327,26 @@ __global__ __launch_bounds__(kThreads, 2) void conv_halo_bf16_kernel(HaloBf16Arg
     for (int ni = 0; ni < TN; ++ni)
 #pragma unroll
       for (int q = 0; q < AQ; ++q) acc[mi][ni][q] = 0.f;
+  Acc mixed[TERMS == 2 ? TM : 1][TERMS == 2 ? TN : 1];  // two terms: the sums of hi*lo and lo*hi, 2^11 times too large
+  if constexpr (TERMS == 2) {
+#pragma unroll
+    for (int mi = 0; mi < TM; ++mi)
+#pragma unroll
+      for (int ni = 0; ni < TN; ++ni)
+#pragma unroll
+        for (int q = 0; q < AQ; ++q) mixed[mi][ni][q] = 0.f;
+  }
+
+  Acc total[TWO_LEVEL ? TM : 1][TWO_LEVEL ? TN : 1];
+  int until_flush = a.flush;
+  if constexpr (TWO_LEVEL) {
+#pragma unroll
+    for (int mi = 0; mi < TM; ++mi)
+#pragma unroll
+      for (int ni = 0; ni < TN; ++ni)
+#pragma unroll
+        for (int q = 0; q < AQ; ++q) total[mi][ni][q] = 0.f;
+  }
 
   const uint4* x8n = a.x8 + (int64_t)n * a.cg * a.h * a.w;
   const int steps = a.uch / 8 * SPS;                         // fragment steps per chunk
@@ -241,7 +357,7 @@ __global__ __launch_bounds__(kThreads, 2) void conv_halo_bf16_kernel(HaloBf16Arg
   // A fragments of the slab this wave works on next: af[step in slab][row tile]
   // (three terms: one step ahead instead of one slab - a step is 6 * TM * TN MFMAs long - which leaves the registers
   // for reading the halo words a step ahead as well)
-  constexpr int AHEAD = TERMS == 3 ? 1 : SPS;
+  constexpr int AHEAD = TERMS > 1 ? 1 : SPS;
   uint4 af[TERMS][AHEAD][TM];
   auto load_a = [&](int ch, int sl) {
     const uint4* src = wf0 + ((int64_t)ch * steps + sl * SPS) * 64;
@@ -293,13 +409,18 @@ __global__ __launch_bounds__(kThreads, 2) void conv_halo_bf16_kernel(HaloBf16Arg
     __syncthreads();
     if (a.nbuf == 2 && ch + 1 < a.nchunks) stage(ch + 1, hbuf + ((ch + 1) & 1) * kBuf * a.hpos);
 
-    if constexpr (TERMS == 3) {
+    if constexpr (TERMS > 1) {
       // Both operands of a step are requested a step ahead: the halo words of step i + 1 (LDS) and the fragments of
       // step i + 1 (second-level cache) are on their way while the 6 * TM * TN MFMAs of step i run, so that the two
       // waves of a SIMD never wait for LDS at the same time.  Only the first step of a chunk waits for its words.
       auto read_offsets = [&](int sl, int (&dst)[4]) {
-        const int4 o4 = *reinterpret_cast<const int4*>(tbl + sl * 8 + half * 4);
-        dst[0] = o4.x, dst[1] = o4.y, dst[2] = o4.z, dst[3] = o4.w;
+        if (M16) {
+          const int2 o2 = *reinterpret_cast<const int2*>(tbl + sl * 8 + half * 2);
+          dst[0] = o2.x, dst[1] = o2.y, dst[2] = 0, dst[3] = 0;
+        } else {
+          const int4 o4 = *reinterpret_cast<const int4*>(tbl + sl * 8 + half * 4);
+          dst[0] = o4.x, dst[1] = o4.y, dst[2] = o4.z, dst[3] = o4.w;
+        }
       };
       int o[4] = {0, 0, 0, 0};
       uint4 bfr[TERMS][TN];
@@ -330,12 +451,11 @@ __global__ __launch_bounds__(kThreads, 2) void conv_halo_bf16_kernel(HaloBf16Arg
           const int onext = i + 1 < SPS ? o[(i + 1) & 3] : on[0];
           // (requested in the order the next step's MFMAs first use them, so that its first MFMA waits for the
           // oldest request only, not for all of them)
-          constexpr int kOrderA[3] = {2, 0, 1}, kOrderB[3] = {0, 2, 1};
 #pragma unroll
           for (int k = 0; k < TERMS; ++k)
 #pragma unroll
             for (int mi = 0; mi < TM; ++mi) {
-              const int t = kOrderA[k];
+              const int t = Split::kOrderA[k];
               cur[t][mi] = af[t][0][mi];
               af[t][0][mi] = nptr[t * a.wf_term + mi * mstride];
             }
@@ -343,7 +463,7 @@ __global__ __launch_bounds__(kThreads, 2) void conv_halo_bf16_kernel(HaloBf16Arg
           for (int k = 0; k < TERMS; ++k)
 #pragma unroll
             for (int ni = 0; ni < TN; ++ni) {
-              const int t = kOrderB[k];
+              const int t = Split::kOrderB[k];
               bnext[t][ni] = halo[t * a.hpos + lane_base[ni] + onext];
             }
 #pragma unroll
@@ -351,14 +471,18 @@ __global__ __launch_bounds__(kThreads, 2) void conv_halo_bf16_kernel(HaloBf16Arg
 #pragma unroll
             for (int mi = 0; mi < TM; ++mi)
 #pragma unroll
-              for (int ni = 0; ni < TN; ++ni) acc[mi][ni] = mfma_bf16(cur[kTermA[pr]][mi], bfr[kTermB[pr]][ni], acc[mi][ni]);
-          // issue order of the step: the requests of the next step go out between this step's MFMAs, one fragment
-          // load and one halo read after every TM * TN of them, in the shadow of the matrix pipe
+              for (int ni = 0; ni < TN; ++ni) {
+                Acc& to = Split::kMixed[pr] ? mixed[TERMS == 2 ? mi : 0][TERMS == 2 ? ni : 0] : acc[mi][ni];
+                to = mfma_term<TERMS>(cur[Split::kA[pr]][mi], bfr[Split::kB[pr]][ni], to);
+              }
+          // issue order of the step: the requests of the next step go out between this step's MFMAs, a fragment
+          // load and a halo read (while there are any) after every few of them, in the shadow of the matrix pipe
+          constexpr int GROUPS = TERMS * (TM > TN ? TM : TN);
 #pragma unroll
-          for (int k = 0; k < TERMS * TM; ++k) {
-            __builtin_amdgcn_sched_group_barrier(0x008, PAIRS * TN / TERMS, 0);  // MFMA
-            __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);                   // global read
-            if (k < TERMS * TN) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // LDS read
+          for (int k = 0; k < GROUPS; ++k) {
+            __builtin_amdgcn_sched_group_barrier(0x008, PAIRS * TM * TN / GROUPS, 0);  // MFMA
+            if (k < TERMS * TM) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);     // global read
+            if (k < TERMS * TN) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);     // LDS read
           }
 #pragma unroll
           for (int t = 0; t < TERMS; ++t)
@@ -368,6 +492,20 @@ __global__ __launch_bounds__(kThreads, 2) void conv_halo_bf16_kernel(HaloBf16Arg
 #pragma unroll
         for (int i = 0; i < 4; ++i) o[i] = on[i];
         sl = after;
+        if constexpr (TWO_LEVEL) {
+          if (--until_flush == 0) {
+            until_flush = a.flush;
+#pragma unroll
+            for (int mi = 0; mi < TM; ++mi)
+#pragma unroll
+              for (int ni = 0; ni < TN; ++ni)
+#pragma unroll
+                for (int q = 0; q < AQ; ++q) {
+                  total[mi][ni][q] += join_f16(acc[mi][ni][q], mixed[mi][ni][q]);
+                  acc[mi][ni][q] = 0.f, mixed[mi][ni][q] = 0.f;
+                }
+          }
+        }
       }
     } else {
       // bfloat16 operands: the fragments are requested a slab ahead (a step is only TM * TN MFMAs long), the halo words
@@ -438,6 +576,17 @@ __global__ __launch_bounds__(kThreads, 2) void conv_halo_bf16_kernel(HaloBf16Arg
     }
   }
 
+  if constexpr (TERMS == 2) {
+#pragma unroll
+    for (int mi = 0; mi < TM; ++mi)
+#pragma unroll
+      for (int ni = 0; ni < TN; ++ni)
+#pragma unroll
+        for (int q = 0; q < AQ; ++q) {
+          acc[mi][ni][q] = join_f16(acc[mi][ni][q], mixed[mi][ni][q]);
+          if constexpr (TWO_LEVEL) acc[mi][ni][q] += total[mi][ni][q];
+        }
+  }
   // contraction split between waves: add the partial sums in wave order through LDS
   if (WAVES_K > 1) {
     float* red = reinterpret_cast<float*>(smem16);  // [TM*TN*AQ][64 lanes]
@@ -465,6 +614,7 @@ __global__ __launch_bounds__(kThreads, 2) void conv_halo_bf16_kernel(HaloBf16Arg
     if (wave_k != 0) return;
   }
 
+  const int descale = TERMS == 2 ? -(a.exponent[0] + a.exponent[1]) : 0;
 #pragma unroll
   for (int ni = 0; ni < TN; ++ni) {
     const int p = p0 + pw0 + ni * TILE + lcol;
@@ -477,6 +627,7 @@ __global__ __launch_bounds__(kThreads, 2) void conv_halo_bf16_kernel(HaloBf16Arg
         const int i = i0 + mi * TILE + (M16 ? 4 * half + q : 8 * (q >> 2) + 4 * half + (q & 3));
         if (i < a.m) {
           float v = acc[mi][ni][q];
+          if (TERMS == 2) v = ldexpf(v, descale);
           const int64_t at = ((int64_t)n * a.m + i) * a.P + p;
           if (a.y32 && a.accumulate) v += a.y32[at];
           if (a.bias) v += a.bias[i];
@@ -495,7 +646,7 @@ static constexpr int kTn16Choices[] = {4, 8, 10};  // 16-pixel tiles per wave (t
 // One arrangement of the four waves (waves_m along the maps, waves_n along the pixels, the rest along the contraction);
 // *cost_out is the estimated time in units of one 32-pixel wave tile.
 static bool plan_arrangement(int waves_m, int waves_n, int n, int c, int h, int w, int m, int r, int s, int ph, int pw,
-                             HaloBf16Plan* p, double* cost_out, int terms, int nbuf = 2) {
+                             HaloBf16Plan* p, double* cost_out, int terms, int nbuf = 2, int only_tn = -1) {
   const int oh = h + 2 * ph - r + 1, ow = w + 2 * pw - s + 1;
   if (oh <= 0 || ow <= 0) return false;
   const int rs = r * s;
@@ -516,6 +667,7 @@ static bool plan_arrangement(int waves_m, int waves_n, int n, int c, int h, int 
   // (three terms: the fragments and halo words of a step take three times the registers, which leaves room for the
   // accumulators of 64-pixel wave tiles only; their six products per step give those the reuse of wider tiles)
   for (int k = 0; k < (terms == 3 ? 1 : 3); ++k) {
+    if (only_tn >= 0 && k != only_tn) continue;
     const int tn = p->m16 ? kTn16Choices[k] : kTnChoices[k];
     const int bn = tile * tn * p->waves_n;
     int rows = (bn + ow - 2) / ow + 1;
@@ -559,7 +711,52 @@ static bool plan_arrangement(int waves_m, int waves_n, int n, int c, int h, int 
   return true;
 }
 
-bool conv_halo_bf16_plan(int n, int c, int h, int w, int m, int r, int s, int ph, int pw, HaloBf16Plan* p, int terms) {
+// Estimated time of the two-term kernel under plan p, in seconds: the matrix-pipe work of the busiest CU (at half the
+// nominal rate, what the kernel sustains with operands that change from step to step), padded pairs, rows and pixels
+// included, plus a block's start, its stages and its end.
+static double two_term_cost(const HaloBf16Plan& p, int n, int m, int r, int s, int64_t P) {
+  const int rs = r * s, tile = p.m16 ? 16 : 32;
+  const int waves_k = 4 / (p.waves_m * p.waves_n);
+  int64_t slabs = 0;
+  for (int ch = 0; ch < p.nchunks; ++ch)
+    slabs += ceil_div(ceil_div((int64_t)std::min(p.cgc, p.cg - ch * p.cgc) * rs, 8), waves_k);
+  const double mfma = (double)slabs * (p.m16 ? 2 * 16 : 4 * 32) * 3 * p.tm * p.tn;  // matrix-pipe cycles of a wave
+  const double blocks = (double)ceil_div(m, tile * p.tm * p.waves_m) * n * (double)ceil_div(P, tile * p.tn * p.waves_n);
+  const double per_cu = std::ceil(blocks / 256.0);
+  const double stage = (p.nbuf == 1 ? 2500.0 : 700.0) * p.nchunks;
+  return (std::max(per_cu, 1.5) * mfma * 1.9 + std::ceil(per_cu / 2) * (4000.0 + stage)) / 2.4e9;
+}
+
+// The two-term form: every arrangement of the waves that the kernel is built for, the cheapest by the estimate above.
+static bool two_term_plan(int n, int c, int h, int w, int m, int r, int s, int ph, int pw, HaloBf16Plan* p, bool two_level) {
+  if (two_level && m > 48) return false;  // three accumulator sets: 48 x 64 or 32 x 64 per wave
+  const int oh = h + 2 * ph - r + 1, ow = w + 2 * pw - s + 1;
+  bool found = false;
+  for (int arrangement = 0; arrangement < 4; ++arrangement) {
+    const int waves_m = arrangement == 2 ? 2 : (arrangement == 3 ? 4 : 1), waves_n = arrangement == 0 ? 4 : 1;
+    if (waves_m > 1 && m <= 64) continue;
+    for (int k = 0; k < 2; ++k) {           // accumulators: two sets, so 64 x 64 or 32 x 128 per wave (M16: 48 x 64)
+      if (k == 1 && (m > 32 || two_level)) continue;
+      for (int nbuf = 2; nbuf >= 1; --nbuf) {
+        HaloBf16Plan q{};
+        double unused = 0;
+        if (!plan_arrangement(waves_m, waves_n, n, c, h, w, m, r, s, ph, pw, &q, &unused, 2, nbuf, k)) continue;
+        q.est_seconds = two_term_cost(q, n, m, r, s, (int64_t)oh * ow);
+        if (!found || q.est_seconds < p->est_seconds) *p = q;
+        found = true;
+      }
+    }
+  }
+  if (found && two_level) {
+    const double slabs = (double)p->nchunks * (p->uch / 8) / (4 / (p->waves_m * p->waves_n));  // of one wave
+    p->flush = std::max(1, (int)std::lround(std::sqrt(slabs / (p->m16 ? 2 : 4))));
+  }
+  return found;
+}
+
+bool conv_halo_bf16_plan(int n, int c, int h, int w, int m, int r, int s, int ph, int pw, HaloBf16Plan* p, int terms,
+                         bool two_level) {
+  if (terms == 2) return two_term_plan(n, c, h, w, m, r, s, ph, pw, p, two_level);
   double cost = 0;
   if (terms != 1 && m <= 128) return false;  // the three-term form is built for the arrangements of many maps only
   if (m <= 128) return plan_arrangement(m > 64 ? 2 : 1, 1, n, c, h, w, m, r, s, ph, pw, p, &cost, terms);
@@ -581,10 +778,10 @@ bool conv_halo_bf16_plan(int n, int c, int h, int w, int m, int r, int s, int ph
   return maps_ok || wide_ok;
 }
 
-template <int WAVES_M, int WAVES_K, int TM, int TN, bool M16 = false, int WAVES_N = 1, int TERMS = 1>
+template <int WAVES_M, int WAVES_K, int TM, int TN, bool M16 = false, int WAVES_N = 1, int TERMS = 1, bool TWO_LEVEL = false>
 static void launch_one(const HaloBf16Args& a, size_t lds, hipStream_t st) {
   const dim3 grid((unsigned)((int64_t)a.tiles_m * a.n * a.tiles_per_img)), block(kThreads);
-  auto kernel = conv_halo_bf16_kernel<WAVES_M, WAVES_K, TM, TN, M16, WAVES_N, TERMS>;
+  auto kernel = conv_halo_bf16_kernel<WAVES_M, WAVES_K, TM, TN, M16, WAVES_N, TERMS, TWO_LEVEL>;
   static bool opted = false;  // one flag per instantiation, i.e. per kernel
   if (!opted) {
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -600,6 +797,18 @@ static void launch_tn(const HaloBf16Args& a, int waves_m, int waves_n, int tm, i
     if constexpr (TN == 2) {
       if (waves_n == 4) launch_one<1, 1, 2, TN, false, 4, 3>(a, lds, st);
       else launch_one<4, 1, 2, TN, false, 1, 3>(a, lds, st);
+    }
+  } else if (terms == 2) {  // (64 x 64 or 32 x 128 wave tiles)
+    if (TN <= 4 && tm == 1) {
+      if constexpr (TN <= 4) {
+        if (waves_n == 4) launch_one<1, 1, 1, TN, false, 4, 2>(a, lds, st);
+        else launch_one<1, 4, 1, TN, false, 1, 2>(a, lds, st);
+      }
+    } else if constexpr (TN == 2) {
+      if (waves_n == 4) launch_one<1, 1, 2, TN, false, 4, 2>(a, lds, st);
+      else if (waves_m == 4) launch_one<4, 1, 2, TN, false, 1, 2>(a, lds, st);
+      else if (waves_m == 2) launch_one<2, 2, 2, TN, false, 1, 2>(a, lds, st);
+      else launch_one<1, 4, 2, TN, false, 1, 2>(a, lds, st);
     }
   } else if (waves_n == 4) launch_one<1, 1, 2, TN, false, 4>(a, lds, st);
   else if (waves_m == 4) launch_one<4, 1, 2, TN>(a, lds, st);
@@ -643,14 +852,15 @@ static vcnn_status relay_kernels(const HaloBf16Plan& p, int c, int m, int rs, co
 
 static vcnn_status launch_product(const HaloBf16Plan& p, int n, int h, int w, int m, int r, int s, int ph, int pw,
                                   const float* bias, void* y, int relu, const void* x8_buf, const void* wf_buf,
-                                  hipStream_t st, float* y32, int accumulate) {
+                                  hipStream_t st, float* y32, int accumulate, const SplitScales* sc = nullptr) {
   const uint4* x8 = (const uint4*)x8_buf;
   const int tile = p.m16 ? 16 : 32;
   const int bm = tile * p.tm * p.waves_m;
   HaloBf16Args a{};
   a.x8 = x8, a.zero = x8 + (int64_t)n * p.cg * h * w, a.wf = (const uint4*)wf_buf, a.bias = bias, a.y = (bf16*)y;
-  a.x8_term = (int64_t)(p.x8_bytes / 16), a.wf_term = (int64_t)(p.wf_bytes / 16);  // (read by the three-term form only)
+  a.x8_term = (int64_t)(p.x8_bytes / 16), a.wf_term = (int64_t)(p.wf_bytes / 16);  // (read by the split forms only)
   a.y32 = y32, a.accumulate = accumulate;
+  a.exponent = sc ? sc->exponent : nullptr;
   a.n = n, a.h = h, a.w = w, a.m = m, a.r = r, a.s = s, a.ph = ph, a.pw = pw;
   a.oh = h + 2 * ph - r + 1, a.ow = w + 2 * pw - s + 1;
   a.P = a.oh * a.ow;
@@ -658,7 +868,16 @@ static vcnn_status launch_product(const HaloBf16Plan& p, int n, int h, int w, in
   a.tiles_per_img = (int)ceil_div(a.P, tile * p.tn * p.waves_n);
   a.cg = p.cg, a.cgc = p.cgc, a.nchunks = p.nchunks, a.nr = p.nr, a.wp = p.wp, a.uch = p.uch, a.hpos = p.hpos, a.relu = relu;
   a.nbuf = p.nbuf;
-  if (p.m16) {
+  a.flush = p.flush;
+  if (p.flush) {  // (planned for at most 48 maps)
+    if (p.m16 && p.waves_n == 4) launch_one<1, 1, 3, 4, true, 4, 2, true>(a, p.lds_bytes, st);
+    else if (p.m16) launch_one<1, 4, 3, 4, true, 1, 2, true>(a, p.lds_bytes, st);
+    else if (p.waves_n == 4) launch_one<1, 1, 1, 2, false, 4, 2, true>(a, p.lds_bytes, st);
+    else launch_one<1, 4, 1, 2, false, 1, 2, true>(a, p.lds_bytes, st);
+  } else if (p.m16 && p.terms == 2) {
+    if (p.waves_n == 4) launch_one<1, 1, 3, 4, true, 4, 2>(a, p.lds_bytes, st);
+    else launch_one<1, 4, 3, 4, true, 1, 2>(a, p.lds_bytes, st);
+  } else if (p.m16) {
     if (p.tn == 4) launch_one<1, 4, 3, 4, true>(a, p.lds_bytes, st);
     else if (p.tn == 8) launch_one<1, 4, 3, 8, true>(a, p.lds_bytes, st);
     else launch_one<1, 4, 3, 10, true>(a, p.lds_bytes, st);
@@ -694,6 +913,27 @@ vcnn_status launch_conv_halo_bf16_terms(const HaloBf16Plan& p, int n, int c, int
       return e;
   }
   return launch_product(p, n, h, w, m, r, s, ph, pw, bias, nullptr, relu, x8_bufs, wf_bufs, st, y32, 0);
+}
+
+// Two-term form (p planned with terms = 2) of a float layer: x and wgt are float; x8_bufs / wf_bufs take the two re-laid
+// terms of each (2 x p.x8_bytes, 2 x p.wf_bytes), `sc` their scales (partial maxima of x in slot 0, of wgt in slot 1).
+vcnn_status launch_conv_halo_f16x2(const HaloBf16Plan& p, int n, int c, int h, int w, int m, int r, int s, int ph, int pw,
+                                   const float* x, const float* wgt, int64_t w_so, int64_t w_si, int flip,
+                                   const float* bias, float* y32, int relu, SplitScales* sc, void* x8_bufs, void* wf_bufs,
+                                   hipStream_t st) {
+  const int64_t total = (int64_t)n * p.cg * h * w;
+  hipLaunchKernelGGL(interleave_channels_split_kernel, dim3((unsigned)ceil_div(total, kThreads)), dim3(kThreads), 0, st, x,
+                     (uint4*)x8_bufs, (int64_t)(p.x8_bytes / 16), c, p.cg, h * w, total, sc, 0);
+  if (vcnn_status e = check_launch("interleave_channels_split")) return e;
+  const int tile = p.m16 ? 16 : 32;
+  const int bm = tile * p.tm * p.waves_m;
+  const int steps = p.uch / 8 * (p.m16 ? 2 : 4);
+  const int64_t wtotal = ceil_div(m, bm) * (bm / tile) * p.nchunks * steps * 64;
+  hipLaunchKernelGGL(reorder_weights_split_kernel, dim3((unsigned)ceil_div(wtotal, kThreads)), dim3(kThreads), 0, st, wgt,
+                     (uint4*)wf_bufs, (int64_t)(p.wf_bytes / 16), m, c, r * s, w_so, w_si, flip, p.cgc, p.nchunks, steps,
+                     p.m16, wtotal, sc, 1);
+  if (vcnn_status e = check_launch("reorder_weights_split")) return e;
+  return launch_product(p, n, h, w, m, r, s, ph, pw, bias, nullptr, relu, x8_bufs, wf_bufs, st, y32, 0, sc);
 }
 
 // =========================================================================================================
@@ -810,12 +1050,94 @@ __global__ __launch_bounds__(kThreads) void dy_fragments_tile_kernel(const bf16*
   }
 }
 
+// The two re-laying passes of the kernel gradient for float operands as two f16 terms each (split_f16.h), in the layouts
+// above, one plane per term; block 0 leaves the operand's exponent for the product kernel.
+__global__ __launch_bounds__(kThreads) void interleave_images_split_kernel(const float* __restrict__ x,
+                                                                           uint4* __restrict__ x8n, int64_t term, int N,
+                                                                           int64_t CHW, int64_t total,
+                                                                           SplitScales* __restrict__ sc, int operand) {
+  const int e = split_exponent(sc->partial[operand]);
+  const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  if (i == 0) {
+    sc->exponent[operand] = e;
+    x8n[total] = make_uint4(0u, 0u, 0u, 0u);
+  }
+  if (i >= total) return;
+  const int64_t pos = i % CHW;
+  const int ng = (int)(i / CHW);
+  float f[8];
+#pragma unroll
+  for (int i8 = 0; i8 < 8; ++i8) f[i8] = x[ng * 8 + i8 < N ? (int64_t)(ng * 8 + i8) * CHW + pos : 0];
+  uint32_t v[8];
+#pragma unroll
+  for (int i8 = 0; i8 < 8; ++i8) v[i8] = ng * 8 + i8 < N ? split_f16(f[i8], e) : 0u;
+  uint4 hi, lo;
+  pack_terms(v, &hi, &lo);
+  x8n[i] = hi;
+  x8n[i + term] = lo;
+}
+
+// (as dy_fragments_tile_kernel, 32 pixels at a time: an element takes four bytes of the tile, its two terms.  The pitch
+// of 33 words keeps both sides on different banks: reads of one pixel column step a row per lane.)
+static constexpr int kSplitFragPixels = 32, kSplitFragPitch = 33;
+__global__ __launch_bounds__(kThreads) void dy_fragments_split_kernel(const float* __restrict__ dy, uint4* __restrict__ dyf,
+                                                                      int64_t term, int N, int M, int P, int MT, int runs,
+                                                                      int bp, int uch, int uchunks,
+                                                                      SplitScales* __restrict__ sc, int operand) {
+  __shared__ uint32_t tile[8 * 32 * kSplitFragPitch];
+  const int e = split_exponent(sc->partial[operand]);
+  const int tid = threadIdx.x;
+  if (blockIdx.x == 0 && tid == 0) sc->exponent[operand] = e;
+  int b = blockIdx.x;
+  const int uc = b % uchunks;
+  b /= uchunks;
+  const int run = b % runs;
+  b /= runs;
+  const int mt = b % MT, ng = b / MT;
+  const int u0 = uc * kSplitFragPixels;
+  {
+    const int u = u0 + (tid & 31), p = run * bp + u;
+    const bool pixel_ok = u < bp && p < P;
+    // (32 rows (image in group, map in tile) per thread, all loads in flight before the first is split)
+    float v[32];
+#pragma unroll
+    for (int k = 0; k < 32; ++k) {
+      const int row = (tid >> 5) + 8 * k;
+      const int img = min(ng * 8 + (row >> 5), N - 1), m = min(mt * 32 + (row & 31), M - 1);
+      v[k] = dy[((int64_t)img * M + m) * P + (pixel_ok ? p : 0)];
+    }
+#pragma unroll
+    for (int k = 0; k < 32; ++k) {
+      const int row = (tid >> 5) + 8 * k;
+      const bool ok = pixel_ok && ng * 8 + (row >> 5) < N && mt * 32 + (row & 31) < M;
+      tile[row * kSplitFragPitch + (tid & 31)] = ok ? split_f16(v[k], e) : 0u;
+    }
+  }
+  __syncthreads();
+  const int ml = tid & 31, ul = tid >> 5;
+  const int64_t frag0 = (((int64_t)ng * MT + mt) * runs + run) * (uch / 2);
+#pragma unroll
+  for (int j = 0; j < kSplitFragPixels / 8; ++j) {
+    const int ulocal = ul + 8 * j, u = u0 + ulocal;
+    if (u >= uch) break;
+    uint32_t v[8];
+#pragma unroll
+    for (int i8 = 0; i8 < 8; ++i8) v[i8] = tile[(i8 * 32 + ml) * kSplitFragPitch + ulocal];
+    uint4 hi, lo;
+    pack_terms(v, &hi, &lo);
+    const int64_t at = (frag0 + u / 2) * 64 + (u & 1) * 32 + ml;
+    dyf[at] = hi;
+    dyf[at + term] = lo;
+  }
+}
+
 struct FilterBf16Args {
   const uint4* x8n;   // [ng][c][h][w] positions of 8 images
   const uint4* zero;  // 16 zero bytes
   const uint4* dyf;   // [ng][mt][run][step][64 lanes] fragments
   int64_t x8n_term;   // TERMS > 1: distance between the terms of x8n, and of dyf, in 16-byte words
   int64_t dyf_term;
+  const int32_t* exponent;  // TERMS = 2: the two operands' scales
   float* out;         // [splits][m][K]
   int c, h, w, m, r, s, ph, pw, oh, ow;
   int K;              // c*r*s
@@ -833,9 +1155,9 @@ struct FilterBf16Args {
 template <int WAVES_M, int WAVES_K, int TM, int TN, int WAVES_N = 1, int TERMS = 1>
 __global__ __launch_bounds__(kThreads, 2) void filter_grad_bf16_kernel(FilterBf16Args a) {
   static_assert(WAVES_M * WAVES_K * WAVES_N * 64 == kThreads, "four waves per block");
-  static_assert(TERMS == 1 || TERMS == 3, "plain bfloat16 operands, or floats as three terms");
-  constexpr int PAIRS = TERMS == 1 ? 1 : 6;
-  constexpr int kTermA[6] = {2, 0, 1, 1, 0, 0}, kTermB[6] = {0, 2, 1, 0, 1, 0};  // dY term, input term
+  static_assert(TERMS >= 1 && TERMS <= 3, "plain bfloat16 operands, or floats as two f16 or three bfloat16 terms");
+  using Split = SplitTerms<TERMS>;
+  constexpr int PAIRS = Split::PAIRS;
   constexpr int BM = 32 * TM * WAVES_M, WN = 32 * TN, BN = WN * WAVES_N;
   extern __shared__ uint4 smem16[];
   int* const tbl = reinterpret_cast<int*>(smem16);  // [uch], per slab of 8 pixels: [half][4]
@@ -881,6 +1203,15 @@ __global__ __launch_bounds__(kThreads, 2) void filter_grad_bf16_kernel(FilterBf1
     for (int ni = 0; ni < TN; ++ni)
 #pragma unroll
       for (int q = 0; q < 16; ++q) acc[mi][ni][q] = 0.f;
+  f32x16 mixed[TERMS == 2 ? TM : 1][TERMS == 2 ? TN : 1];  // two terms: the sums of hi*lo and lo*hi, 2^11 times too large
+  if constexpr (TERMS == 2) {
+#pragma unroll
+    for (int mi = 0; mi < TM; ++mi)
+#pragma unroll
+      for (int ni = 0; ni < TN; ++ni)
+#pragma unroll
+        for (int q = 0; q < 16; ++q) mixed[mi][ni][q] = 0.f;
+  }
 
   const int id0 = blockIdx.y * a.chunks_per_split;
   const int id1 = min(a.chunks, id0 + a.chunks_per_split);
@@ -893,7 +1224,7 @@ __global__ __launch_bounds__(kThreads, 2) void filter_grad_bf16_kernel(FilterBf1
   };
 
   // fragments on their way: a slab ahead (bfloat16 operands: a step is TM * TN MFMAs long) or a step ahead (three terms)
-  constexpr int AHEAD = TERMS == 3 ? 1 : 4;
+  constexpr int AHEAD = TERMS > 1 ? 1 : 4;
   uint4 af[TERMS][AHEAD][TM];
   const int first_sl = min(wave_k, chunk_slabs - 1);
   {
@@ -938,7 +1269,7 @@ __global__ __launch_bounds__(kThreads, 2) void filter_grad_bf16_kernel(FilterBf1
     __syncthreads();
     if (a.nbuf == 2 && id + 1 < id1) stage(id + 1, hbuf + ((id + 1 - id0) & 1) * TERMS * a.hpos);
 
-    if constexpr (TERMS == 3) {
+    if constexpr (TERMS > 1) {
       auto read_offsets = [&](int sl, int (&dst)[4]) {
         const int4 o4 = *reinterpret_cast<const int4*>(tbl + sl * 8 + half * 4);
         dst[0] = o4.x, dst[1] = o4.y, dst[2] = o4.z, dst[3] = o4.w;
@@ -965,12 +1296,12 @@ __global__ __launch_bounds__(kThreads, 2) void filter_grad_bf16_kernel(FilterBf1
           uint4 cur[TERMS][TM], bnext[TERMS][TN];
           const uint4* nptr = i + 1 < 4 ? csrc + (i + 1) * 64 : nsrc;
           const int onext = i + 1 < 4 ? o[(i + 1) & 3] : on[0];
-          constexpr int kOrderA[3] = {2, 0, 1}, kOrderB[3] = {0, 2, 1};  // the order of first use in the next step
+          // (in the order of first use in the next step)
 #pragma unroll
           for (int k = 0; k < TERMS; ++k)
 #pragma unroll
             for (int mi = 0; mi < TM; ++mi) {
-              const int t = kOrderA[k];
+              const int t = Split::kOrderA[k];
               cur[t][mi] = af[t][0][mi];
               af[t][0][mi] = nptr[t * a.dyf_term + mi * mstride];
             }
@@ -978,7 +1309,7 @@ __global__ __launch_bounds__(kThreads, 2) void filter_grad_bf16_kernel(FilterBf1
           for (int k = 0; k < TERMS; ++k)
 #pragma unroll
             for (int ni = 0; ni < TN; ++ni) {
-              const int t = kOrderB[k];
+              const int t = Split::kOrderB[k];
               bnext[t][ni] = halo[t * a.hpos + tap_base[ni] + onext];
             }
 #pragma unroll
@@ -986,13 +1317,18 @@ __global__ __launch_bounds__(kThreads, 2) void filter_grad_bf16_kernel(FilterBf1
 #pragma unroll
             for (int mi = 0; mi < TM; ++mi)
 #pragma unroll
-              for (int ni = 0; ni < TN; ++ni) acc[mi][ni] = mfma_bf16(cur[kTermA[pr]][mi], bfr[kTermB[pr]][ni], acc[mi][ni]);
-          // issue order: one fragment load and one halo read after every TM * TN MFMAs, in the shadow of the matrix pipe
+              for (int ni = 0; ni < TN; ++ni) {
+                f32x16& to = Split::kMixed[pr] ? mixed[TERMS == 2 ? mi : 0][TERMS == 2 ? ni : 0] : acc[mi][ni];
+                to = mfma_term<TERMS>(cur[Split::kA[pr]][mi], bfr[Split::kB[pr]][ni], to);
+              }
+          // issue order: a fragment load and a halo read (while there are any) after every few MFMAs, in the shadow of
+          // the matrix pipe
+          constexpr int GROUPS = TERMS * (TM > TN ? TM : TN);
 #pragma unroll
-          for (int k = 0; k < TERMS * TM; ++k) {
-            __builtin_amdgcn_sched_group_barrier(0x008, PAIRS * TN / TERMS, 0);  // MFMA
-            __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);                   // global read
-            if (k < TERMS * TN) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // LDS read
+          for (int k = 0; k < GROUPS; ++k) {
+            __builtin_amdgcn_sched_group_barrier(0x008, PAIRS * TM * TN / GROUPS, 0);  // MFMA
+            if (k < TERMS * TM) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);     // global read
+            if (k < TERMS * TN) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);     // LDS read
           }
 #pragma unroll
           for (int t = 0; t < TERMS; ++t)
@@ -1027,12 +1363,30 @@ __global__ __launch_bounds__(kThreads, 2) void filter_grad_bf16_kernel(FilterBf1
         }
       }
     }
+    if (wave_k >= slabs && id + 1 < id1) {
+      // a short run left this wave without a slab: the fragments it holds are that run's, not the next one's
+      const uint4* src = frag_ptr(id + 1, first_sl);
+#pragma unroll
+      for (int t = 0; t < TERMS; ++t)
+#pragma unroll
+        for (int i = 0; i < AHEAD; ++i)
+#pragma unroll
+          for (int mi = 0; mi < TM; ++mi) af[t][i][mi] = src[t * a.dyf_term + mi * mstride + i * 64];
+    }
     if (a.nbuf == 1 && id + 1 < id1) {  // one buffer: every wave is done reading it, then it is refilled
       __syncthreads();
       stage(id + 1, hbuf);
     }
   }
 
+  if constexpr (TERMS == 2) {
+#pragma unroll
+    for (int mi = 0; mi < TM; ++mi)
+#pragma unroll
+      for (int ni = 0; ni < TN; ++ni)
+#pragma unroll
+        for (int q = 0; q < 16; ++q) acc[mi][ni][q] = join_f16(acc[mi][ni][q], mixed[mi][ni][q]);
+  }
   if (WAVES_K > 1) {  // contraction split between waves: add the partial sums in wave order through LDS
     float* red = reinterpret_cast<float*>(smem16);  // [TM*TN*16][64 lanes]
 #pragma unroll 1
@@ -1059,6 +1413,7 @@ __global__ __launch_bounds__(kThreads, 2) void filter_grad_bf16_kernel(FilterBf1
     if (wave_k != 0) return;
   }
 
+  const int descale = TERMS == 2 ? -(a.exponent[0] + a.exponent[1]) : 0;
   float* dst = a.out + (int64_t)blockIdx.y * a.m * a.K;
 #pragma unroll
   for (int ni = 0; ni < TN; ++ni) {
@@ -1069,7 +1424,7 @@ __global__ __launch_bounds__(kThreads, 2) void filter_grad_bf16_kernel(FilterBf1
 #pragma unroll
       for (int q = 0; q < 16; ++q) {
         const int m = i0 + mi * 32 + 8 * (q >> 2) + 4 * half + (q & 3);
-        if (m < a.m) dst[(int64_t)m * a.K + col] = acc[mi][ni][q];
+        if (m < a.m) dst[(int64_t)m * a.K + col] = TERMS == 2 ? ldexpf(acc[mi][ni][q], descale) : acc[mi][ni][q];
       }
   }
 }
@@ -1085,13 +1440,20 @@ static ConvGeom flatten_pointwise(const ConvGeom& g) {
   return f;
 }
 
-bool filter_grad_bf16_plan(const ConvGeom& g0, FilterGradBf16Plan* p, int terms) {
+static bool filter_plan_form(const ConvGeom& g0, FilterGradBf16Plan* p, int terms, bool prefer_split_k, bool wide_columns,
+                             int max_splits) {
   const ConvGeom g = flatten_pointwise(g0);
   const int rs = g.r * g.s;
   if ((int64_t)g.c * g.h * g.w > 0x7fffffffLL || g.K > 0x7fffffffLL) return false;
   p->terms = terms, p->waves_n = 1;
   int tn = 0;
-  if (terms == 3) {
+  if (terms == 2) {
+    // two accumulator sets: 64 x 64 wave tiles, 32 x 128 (or 32 x 64) for at most 32 maps.  The four waves take different
+    // columns of the same maps where the halo tile of that many columns fits LDS, else they split the contraction.
+    p->tm = g.M <= 32 ? 1 : 2;
+    p->waves_m = 1, p->waves_n = prefer_split_k ? 1 : 4;
+    tn = g.M <= 32 && wide_columns ? 4 : 2;
+  } else if (terms == 3) {
     // built for many maps: the four waves take 64 columns each of the same 64 maps (the registers of three terms
     // leave room for the accumulators of 64 x 64 wave tiles)
     if (g.M <= 128) return false;
@@ -1119,7 +1481,7 @@ bool filter_grad_bf16_plan(const ConvGeom& g0, FilterGradBf16Plan* p, int terms)
   // most output rows per run whose halo tile fits twice - or, three planes of a large kernel, once: then a chunk is
   // staged between the products of two chunks, not during them, and the other resident block covers the gap
   int bh = 0;
-  for (p->nbuf = 2; p->nbuf >= (terms == 3 ? 1 : 2) && bh == 0; --p->nbuf) {
+  for (p->nbuf = 2; p->nbuf >= (terms > 1 ? 1 : 2) && bh == 0; --p->nbuf) {
     for (int t = 1; t <= g.oh; ++t) {
       const int uch = (int)ceil_div((int64_t)t * g.ow, 8) * 8;
       const size_t hpos = ((size_t)p->ccs * (t + g.r - 1) * p->wp + 63) & ~(size_t)63;
@@ -1138,7 +1500,7 @@ bool filter_grad_bf16_plan(const ConvGeom& g0, FilterGradBf16Plan* p, int terms)
   p->chunks = p->ngroups * p->runs;
   const int64_t tiles = (int64_t)tiles_m * ceil_div(g.K, bn);
   int64_t want = ceil_div(512, tiles);
-  if (terms == 3) {
+  if (terms > 1) {
     // long blocks that keep the matrix pipe busy: the 256 CUs share them evenly when there are many per CU, or a
     // whole number; of the even splits of the chunks, the first that leaves the last CU at least 90 % of a share
     for (int64_t wn = want; wn <= p->chunks; ++wn) {
@@ -1150,6 +1512,7 @@ bool filter_grad_bf16_plan(const ConvGeom& g0, FilterGradBf16Plan* p, int terms)
       }
     }
   }
+  if (max_splits > 0 && want > max_splits) want = max_splits;
   if (want > p->chunks) want = p->chunks;
   if (want < 1) want = 1;
   p->chunks_per_split = (int)ceil_div(p->chunks, want);
@@ -1159,6 +1522,34 @@ bool filter_grad_bf16_plan(const ConvGeom& g0, FilterGradBf16Plan* p, int terms)
   p->dyf_bytes = ((size_t)p->ngroups * p->mt_total * p->runs * (p->uch / 2) * 64 * 16 + 255) & ~(size_t)255;
   p->partial_bytes = p->splits > 1 ? (size_t)p->splits * g.M * g.K * sizeof(float) : 0;
   return tiles <= 0x7fffffffLL && p->splits <= 65535;
+}
+
+// Estimated time of the two-term kernel under plan p, in seconds (as two_term_cost above).
+static double two_term_filter_cost(const FilterGradBf16Plan& p, const ConvGeom& g) {
+  const int waves_k = 4 / (p.waves_m * p.waves_n);
+  const double run_slabs = (double)ceil_div(ceil_div((int64_t)p.bp, 8), waves_k);
+  const double mfma = (double)p.chunks_per_split * run_slabs * 4 * 32 * 3 * p.tm * p.tn;
+  const double blocks = (double)ceil_div(g.M, 32 * p.tm * p.waves_m) * (double)ceil_div(g.K, 32 * p.tn * p.waves_n) * p.splits;
+  const double per_cu = std::ceil(blocks / 256.0);
+  // a chunk's halo tile comes from the second-level cache, 16 bytes a position and term at some 25 bytes per cycle and CU
+  const double fill = (double)p.hpos * 2 * 16 / 25.0;
+  const double stage = p.nbuf == 1 ? fill + 1500.0 : std::max(0.0, fill - run_slabs * 4 * 32 * 3 * p.tm * p.tn) + 500.0;
+  return (std::max(per_cu, 1.5) * mfma * 1.9 + std::ceil(per_cu / 2) * (4000.0 + stage * p.chunks_per_split)) / 2.4e9 +
+         (double)p.partial_bytes * 2 / 4e12;
+}
+
+bool filter_grad_bf16_plan(const ConvGeom& g, FilterGradBf16Plan* p, int terms, int max_splits) {
+  if (terms != 2) return filter_plan_form(g, p, terms, false, false, max_splits);
+  bool found = false;
+  for (int form = 0; form < 4; ++form) {
+    if ((form & 2) && g.M > 32) continue;
+    FilterGradBf16Plan q{};
+    if (!filter_plan_form(g, &q, 2, form & 1, form & 2, max_splits)) continue;
+    q.est_seconds = two_term_filter_cost(q, flatten_pointwise(g));
+    if (!found || q.est_seconds < p->est_seconds) *p = q;
+    found = true;
+  }
+  return found;
 }
 
 template <int WAVES_M, int WAVES_K, int TM, int TN, int WAVES_N = 1, int TERMS = 1>
@@ -1212,13 +1603,15 @@ static vcnn_status relay_dy(const FilterGradBf16Plan& p, const ConvGeom& g, cons
 
 // the product on re-laid operands (g flattened), slices summed into dw (added to its contents when `accumulate`)
 static vcnn_status launch_filter_product(const FilterGradBf16Plan& p, const ConvGeom& g, float* dw, const void* x8n_buf,
-                                         const void* dyf_buf, float* partial, hipStream_t st, int accumulate) {
+                                         const void* dyf_buf, float* partial, hipStream_t st, int accumulate,
+                                         const SplitScales* sc = nullptr) {
   const uint4* x8n = (const uint4*)x8n_buf;
   const int64_t chw = (int64_t)g.c * g.h * g.w;
   FilterBf16Args a{};
   // accumulate: dw += the product (the slice sum takes dw as its addend); the workspace then holds at least one slice
   a.x8n = x8n, a.zero = x8n + (int64_t)p.ngroups * chw, a.dyf = (const uint4*)dyf_buf;
-  a.x8n_term = (int64_t)(p.x8n_bytes / 16), a.dyf_term = (int64_t)(p.dyf_bytes / 16);  // (read by the three-term form only)
+  a.x8n_term = (int64_t)(p.x8n_bytes / 16), a.dyf_term = (int64_t)(p.dyf_bytes / 16);  // (read by the split forms only)
+  a.exponent = sc ? sc->exponent : nullptr;
   a.out = (p.splits > 1 || accumulate) ? partial : dw;
   a.c = g.c, a.h = g.h, a.w = g.w, a.m = g.k, a.r = g.r, a.s = g.s, a.ph = g.ph, a.pw = g.pw, a.oh = g.oh, a.ow = g.ow;
   a.K = (int)g.K;
@@ -1227,7 +1620,15 @@ static vcnn_status launch_filter_product(const FilterGradBf16Plan& p, const Conv
   a.uch = p.uch, a.hpos = p.hpos, a.ccs = p.ccs, a.nr = p.nr, a.wp = p.wp, a.nbuf = p.nbuf;
   a.chunks = p.chunks, a.chunks_per_split = p.chunks_per_split;
   const unsigned tiles = (unsigned)(a.tiles_m * ceil_div(g.K, 32 * p.tn * p.waves_n));
-  if (p.terms == 3) launch_filter_one<1, 1, 2, 2, 4, 3>(a, tiles, (unsigned)p.splits, p.lds_bytes, st);
+  const unsigned sp = (unsigned)p.splits;
+  if (p.terms == 2) {
+    if (p.tm == 2 && p.waves_n == 4) launch_filter_one<1, 1, 2, 2, 4, 2>(a, tiles, sp, p.lds_bytes, st);
+    else if (p.tm == 2) launch_filter_one<1, 4, 2, 2, 1, 2>(a, tiles, sp, p.lds_bytes, st);
+    else if (p.tn == 4 && p.waves_n == 4) launch_filter_one<1, 1, 1, 4, 4, 2>(a, tiles, sp, p.lds_bytes, st);
+    else if (p.tn == 4) launch_filter_one<1, 4, 1, 4, 1, 2>(a, tiles, sp, p.lds_bytes, st);
+    else if (p.waves_n == 4) launch_filter_one<1, 1, 1, 2, 4, 2>(a, tiles, sp, p.lds_bytes, st);
+    else launch_filter_one<1, 4, 1, 2, 1, 2>(a, tiles, sp, p.lds_bytes, st);
+  } else if (p.terms == 3) launch_filter_one<1, 1, 2, 2, 4, 3>(a, tiles, (unsigned)p.splits, p.lds_bytes, st);
   else if (p.tn == 2) launch_filter_tn<2>(a, p.waves_m, p.tm, tiles, (unsigned)p.splits, p.lds_bytes, st);
   else if (p.tn == 4) launch_filter_tn<4>(a, p.waves_m, p.tm, tiles, (unsigned)p.splits, p.lds_bytes, st);
   else launch_filter_tn<5>(a, p.waves_m, p.tm, tiles, (unsigned)p.splits, p.lds_bytes, st);
@@ -1261,6 +1662,26 @@ vcnn_status launch_filter_grad_bf16_terms(const FilterGradBf16Plan& p, const Con
     if (vcnn_status e = relay_dy(p, g, (const char*)dy_terms + t * dy_term_bytes, (char*)dyf_bufs + t * p.dyf_bytes, st)) return e;
   }
   return launch_filter_product(p, g, dw, x8n_bufs, dyf_bufs, partial, st, 0);
+}
+
+// Two-term form (p planned with terms = 2) of a float layer: x8n_bufs / dyf_bufs take the two re-laid terms of x and dy,
+// `sc` their scales (partial maxima of x in slot 0, of dy in slot 1), `partial` the slices (at least one with `accumulate`:
+// dw += the product).
+vcnn_status launch_filter_grad_f16x2(const FilterGradBf16Plan& p, const ConvGeom& g0, const float* x, const float* dy,
+                                     float* dw, SplitScales* sc, void* x8n_bufs, void* dyf_bufs, float* partial,
+                                     hipStream_t st, int accumulate) {
+  const ConvGeom g = flatten_pointwise(g0);
+  const int64_t chw = (int64_t)g.c * g.h * g.w;
+  const int64_t total = (int64_t)p.ngroups * chw;
+  hipLaunchKernelGGL(interleave_images_split_kernel, dim3((unsigned)ceil_div(total, kThreads)), dim3(kThreads), 0, st, x,
+                     (uint4*)x8n_bufs, (int64_t)(p.x8n_bytes / 16), g.n, chw, total, sc, 0);
+  if (vcnn_status e = check_launch("interleave_images_split")) return e;
+  const int uchunks = (int)ceil_div(p.uch, kSplitFragPixels);
+  const int64_t blocks = (int64_t)p.ngroups * p.mt_total * p.runs * uchunks;
+  hipLaunchKernelGGL(dy_fragments_split_kernel, dim3((unsigned)blocks), dim3(kThreads), 0, st, dy, (uint4*)dyf_bufs,
+                     (int64_t)(p.dyf_bytes / 16), g.n, (int)g.M, (int)g.P, p.mt_total, p.runs, p.bp, p.uch, uchunks, sc, 1);
+  if (vcnn_status e = check_launch("dy_fragments_split")) return e;
+  return launch_filter_product(p, g, dw, x8n_bufs, dyf_bufs, partial, st, accumulate, sc);
 }
 
 }  // namespace vcnn

@@ -163,7 +163,10 @@ struct HaloBf16Plan {
   int uch;           // (group, tap) pairs per chunk, padded to a multiple of 8
   int hpos;          // positions per halo buffer (per term)
   int nbuf;          // halo buffers in LDS (2, or 1 when three planes only fit once)
-  int terms;         // 1: bfloat16 operands; 3: float operands as three bfloat16 terms each, six products per step
+  int terms;         // 1: bfloat16 operands; 2: float operands as two f16 terms each, three products per step; 3: as
+                     // three bfloat16 terms each, six products per step
+  double est_seconds;  // terms = 2: estimated time of the product kernel
+  int flush;           // terms = 2, two-level sums: slabs between two flushes of the accumulators (0: one level)
   size_t lds_bytes;
   size_t x8_bytes, wf_bytes;  // workspace: channel-interleaved input, fragment-ordered kernel matrix
 };
@@ -187,7 +190,8 @@ vcnn_status launch_pointwise_bf16(const PointwiseBf16Plan& p, int n, int rows, i
 bool pointwise_filter_bf16_plan(const ConvGeom& g, PointwiseFilterBf16Plan* p);
 vcnn_status launch_pointwise_filter_bf16(const PointwiseFilterBf16Plan& p, const ConvGeom& g, const void* x, const void* dy,
                                          float* dw, float* partial, hipStream_t st);
-bool conv_halo_bf16_plan(int n, int c, int h, int w, int m, int r, int s, int ph, int pw, HaloBf16Plan* p, int terms = 1);
+bool conv_halo_bf16_plan(int n, int c, int h, int w, int m, int r, int s, int ph, int pw, HaloBf16Plan* p, int terms = 1,
+                         bool two_level = false);  // two_level: the two-term form that adds in two levels (m <= 48)
 // y = act(bias + W (*) x) with W(o, i, q) = wgt[o*w_so + i*w_si + (flip ? r*s-1-q : q)]; the workspace holds
 // x8_bytes + wf_bytes
 vcnn_status launch_conv_halo_bf16(const HaloBf16Plan& p, int n, int c, int h, int w, int m, int r, int s, int ph, int pw,
@@ -207,8 +211,9 @@ vcnn_status launch_conv_halo_bf16_terms(const HaloBf16Plan& p, int n, int c, int
 struct FilterGradBf16Plan {
   int waves_m, tm, tn;
   int waves_n;       // waves of a block along the kernel-matrix columns (same maps)
-  int terms;         // 1: bfloat16 operands; 3: float operands as three bfloat16 terms each, six products per step
-  int nbuf;          // halo buffers in LDS (2, or 1 when three planes only fit once)
+  int terms;         // as in HaloBf16Plan
+  double est_seconds;  // terms = 2: estimated time of the product kernel
+  int nbuf;          // halo buffers in LDS (2, or 1 when the planes only fit once)
   int ccs, nr, wp;   // channels, rows and row pitch of the halo tile
   int bh, bp, runs;  // output rows / pixels per run, runs per image
   int ngroups;       // image groups of 8
@@ -217,7 +222,8 @@ struct FilterGradBf16Plan {
   int mt_total;
   size_t lds_bytes, x8n_bytes, dyf_bytes, partial_bytes;
 };
-bool filter_grad_bf16_plan(const ConvGeom& g, FilterGradBf16Plan* p, int terms = 1);
+// max_splits: at most that many slices (0: as many as fill the chip)
+bool filter_grad_bf16_plan(const ConvGeom& g, FilterGradBf16Plan* p, int terms = 1, int max_splits = 0);
 // workspace: x8n_bytes + dyf_bytes + partial_bytes
 // accumulate: dw += the product; the workspace then needs max(partial_bytes, one slice of M*K floats) behind dyf
 vcnn_status launch_filter_grad_bf16(const FilterGradBf16Plan& p, const ConvGeom& g, const void* x, const void* dy,
@@ -230,6 +236,34 @@ vcnn_status launch_filter_grad_bf16_prepared(const FilterGradBf16Plan& p, const 
 vcnn_status launch_filter_grad_bf16_terms(const FilterGradBf16Plan& p, const ConvGeom& g, const void* x_terms,
                                           size_t x_term_bytes, const void* dy_terms, size_t dy_term_bytes, float* dw,
                                           void* x8n_bufs, void* dyf_bufs, float* partial, hipStream_t st);
+
+// ---- two f16 terms per float (split_f16.h): the float products of large layers, on the same kernels ------------------
+struct SplitScales;
+vcnn_status launch_conv_halo_f16x2(const HaloBf16Plan& p, int n, int c, int h, int w, int m, int r, int s, int ph, int pw,
+                                   const float* x, const float* wgt, int64_t w_so, int64_t w_si, int flip,
+                                   const float* bias, float* y32, int relu, SplitScales* sc, void* x8_bufs, void* wf_bufs,
+                                   hipStream_t st);
+vcnn_status launch_filter_grad_f16x2(const FilterGradBf16Plan& p, const ConvGeom& g, const float* x, const float* dy,
+                                     float* dw, SplitScales* sc, void* x8n_bufs, void* dyf_bufs, float* partial,
+                                     hipStream_t st, int accumulate);
+// ---- split_f16.hip: which float layers take them, and the scales -------------------------------------------------------
+struct F16x2Plan {
+  HaloBf16Plan fwd;           // forward pass, and the input gradient as a correlation, of `images` images
+  FilterGradBf16Plan filter;  // kernel gradient of `images` images
+  int parts, images;          // the batch is worked through in parts of at most `images` images
+  int max_splits;             // bound on the kernel gradient's slices (0: none)
+  size_t workspace_bytes;     // scales, re-laid terms, slices
+  double est_seconds;         // of the whole pass, re-laying included
+};
+// The fastest plan whose workspace holds in `budget` bytes: the batch in as few parts as that allows, and fewer slices of a
+// kernel gradient where they leave room for larger parts; false if there is none (or the layer does not fit the kernels).
+bool conv_f16x2_plan(const ConvGeom& g, int pass, size_t budget, F16x2Plan* p);
+vcnn_status launch_conv_f16x2_fwd(const F16x2Plan& p, const ConvGeom& g, const float* x, const float* w, const float* bias,
+                                  float* y, int relu, void* workspace, hipStream_t st);
+vcnn_status launch_conv_f16x2_bwd_data(const F16x2Plan& p, const ConvGeom& g, const float* w, const float* dy, float* dx,
+                                       void* workspace, hipStream_t st);
+vcnn_status launch_conv_f16x2_filter(const F16x2Plan& p, const ConvGeom& g, const float* x, const float* dy, float* dw,
+                                     void* workspace, hipStream_t st);
 
 // ---- split_bf16.hip: fp32 products of large layers as sums of bf16 products (on request only) ------------------------
 struct SplitPlan {

@@ -1,0 +1,182 @@
+// The float products of large layers on the half-precision matrix cores: which layers, the scales of the operands, and
+// the workspace.  The terms and their precision are described in split_f16.h; the kernels that multiply them are the
+// matrix-core kernels of the bfloat16 variant with two f16 terms per operand.
+#include <algorithm>
+
+#include "common.h"
+#include "split_f16.h"
+
+namespace vcnn {
+
+static constexpr int kThreads = 256;
+
+struct AbsMaxArgs {
+  const float* src[2];
+  int64_t count[2];
+  SplitScales* scales;
+};
+
+// Largest finite magnitude of each block's share of the two operands (blockIdx.y).  Bandwidth: read once, 16 bytes per
+// load and four loads in flight per thread.
+__global__ __launch_bounds__(kThreads) void absmax_kernel(AbsMaxArgs a) {
+  const int op = blockIdx.y;
+  const float* const p = a.src[op];
+  const int64_t count = a.count[op];
+  const int head = (int)min((int64_t)((16 - ((uintptr_t)p & 15)) & 15) / 4, count);  // floats before a 16-byte boundary
+  const uint4* const body = reinterpret_cast<const uint4*>(p + head);
+  const int64_t quads = (count - head) / 4;
+  uint32_t m = 0;
+  auto take = [&](uint32_t bits) {
+    bits &= 0x7fffffffu;
+    m = max(m, bits < 0x7f800000u ? bits : 0u);
+  };
+  constexpr int64_t kStep = (int64_t)kAbsMaxBlocks * kThreads;
+  int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  for (; i + 3 * kStep < quads; i += 4 * kStep) {
+    uint4 v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = body[i + k * kStep];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) take(v[k].x), take(v[k].y), take(v[k].z), take(v[k].w);
+  }
+  for (; i < quads; i += kStep) {
+    const uint4 v = body[i];
+    take(v.x), take(v.y), take(v.z), take(v.w);
+  }
+  if (blockIdx.x == 0 && threadIdx.x < 8) {  // the floats around the 16-byte words
+    const int64_t e = threadIdx.x < 4 ? (int64_t)threadIdx.x : head + quads * 4 + (threadIdx.x - 4);
+    if (threadIdx.x < 4 ? e < head : e < count) take(__float_as_uint(p[e]));
+  }
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, d));
+  __shared__ uint32_t wave_max[4];
+  if ((threadIdx.x & 63) == 0) wave_max[threadIdx.x >> 6] = m;
+  __syncthreads();
+  if (threadIdx.x == 0)
+    a.scales->partial[op][blockIdx.x] = max(max(wave_max[0], wave_max[1]), max(wave_max[2], wave_max[3]));
+}
+
+static vcnn_status launch_absmax(const float* a, int64_t na, const float* b, int64_t nb, SplitScales* sc, hipStream_t st) {
+  AbsMaxArgs args{{a, b}, {na, nb}, sc};
+  hipLaunchKernelGGL(absmax_kernel, dim3(kAbsMaxBlocks, 2), dim3(kThreads), 0, st, args);
+  return check_launch("absmax");
+}
+
+static inline size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
+
+// The scales read both operands, the re-laying passes read them again and write the terms: at some 3.5 TB/s, and three
+// launches.
+static double relay_seconds(double float_bytes, double term_bytes) { return (2 * float_bytes + term_bytes) / 3.5e12 + 10e-6; }
+
+// The plan for one part of n images.
+static bool part_plan(const ConvGeom& whole, int pass, int n, int max_splits, F16x2Plan* p) {
+  ConvGeom g = whole;
+  g.n = n, g.N = (int64_t)n * g.P;
+  const double x_bytes = 4.0 * g.n * g.c * g.h * g.w, w_bytes = 4.0 * (double)g.M * (double)g.K, y_bytes = 4.0 * (double)g.M * (double)g.N;
+  if (pass == VCNN_PASS_BWD_FILTER) {
+    if (!filter_grad_bf16_plan(g, &p->filter, 2, max_splits)) return false;
+    const size_t terms = 2 * (p->filter.x8n_bytes + p->filter.dyf_bytes);
+    // (later parts add to dw through the slice sum, which then needs one slice at least)
+    const size_t slices = std::max(p->filter.partial_bytes, n < whole.n ? (size_t)g.M * g.K * sizeof(float) : (size_t)0);
+    p->workspace_bytes = kSplitScalesBytes + terms + align256(slices);
+    p->est_seconds = p->filter.est_seconds + relay_seconds(x_bytes + y_bytes, (double)terms);
+    return true;
+  }
+  if (pass == VCNN_PASS_FWD) {
+    if (!conv_halo_bf16_plan(g.n, g.c, g.h, g.w, g.k, g.r, g.s, g.ph, g.pw, &p->fwd, 2)) return false;
+  } else {
+    // the input gradient as a correlation of dy (k channels) with the flipped kernels
+    const int ph = g.r - 1 - g.ph, pw = g.s - 1 - g.pw;
+    if (ph < 0 || pw < 0 || !conv_halo_bf16_plan(g.n, g.k, g.oh, g.ow, g.c, g.r, g.s, ph, pw, &p->fwd, 2)) return false;
+  }
+  const size_t terms = 2 * (p->fwd.x8_bytes + p->fwd.wf_bytes);
+  p->workspace_bytes = kSplitScalesBytes + terms;
+  p->est_seconds = p->fwd.est_seconds + relay_seconds((pass == VCNN_PASS_FWD ? x_bytes : y_bytes) + w_bytes, (double)terms);
+  return true;
+}
+
+bool conv_f16x2_plan(const ConvGeom& g, int pass, size_t budget, F16x2Plan* p) {
+  const bool filter = pass == VCNN_PASS_BWD_FILTER;
+  const int unit = filter ? 8 : 1;  // the kernel gradient takes images in groups of eight
+  bool found = false;
+  for (int max_splits = 0; max_splits <= 64; max_splits = max_splits ? 2 * max_splits : 4) {
+    for (int parts = 1, next; parts <= 16; parts = next) {
+      next = parts + 1;
+      const int images = (int)std::min<int64_t>(ceil_div(ceil_div(g.n, parts), unit) * unit, g.n);
+      if (parts > 1 && (int64_t)images * (parts - 1) >= g.n) continue;  // fewer parts of this size do
+      F16x2Plan q{};
+      if (!part_plan(g, pass, images, max_splits, &q)) return false;
+      if (q.workspace_bytes > budget) {  // (the room a part takes falls about as the parts rise)
+        next = std::max(next, (int)(0.8 * parts * (double)q.workspace_bytes / (double)std::max<size_t>(budget, 1)));
+        continue;
+      }
+      q.parts = parts, q.images = images, q.max_splits = max_splits;
+      q.est_seconds *= parts;
+      if (!found || q.est_seconds < p->est_seconds) *p = q;
+      found = true;
+      break;
+    }
+    if (!filter || (found && p->parts == 1 && p->max_splits == 0)) break;
+  }
+  return found;
+}
+
+// Runs `part(first image, its geometry, its plan)` over the parts of the batch.
+template <typename F>
+static vcnn_status each_part(const F16x2Plan& p, const ConvGeom& whole, int pass, F part) {
+  for (int n0 = 0; n0 < whole.n; n0 += p.images) {
+    ConvGeom g = whole;
+    g.n = std::min(p.images, whole.n - n0), g.N = (int64_t)g.n * g.P;
+    if (g.n == p.images) {
+      if (vcnn_status e = part(n0, g, p)) return e;
+      continue;
+    }
+    // a shorter last part: its own plan, which needs no more room (fewer images, at most as many slices)
+    F16x2Plan last{};
+    if (!part_plan(whole, pass, g.n, p.max_splits, &last) || last.workspace_bytes > p.workspace_bytes)
+      return fail(VCNN_ERR_UNSUPPORTED, "conv: no plan for the last %d images", g.n);
+    if (vcnn_status e = part(n0, g, last)) return e;
+  }
+  return VCNN_OK;
+}
+
+vcnn_status launch_conv_f16x2_fwd(const F16x2Plan& plan, const ConvGeom& whole, const float* x, const float* w,
+                                  const float* bias, float* y, int relu, void* workspace, hipStream_t st) {
+  SplitScales* const sc = (SplitScales*)workspace;
+  char* const x8 = (char*)workspace + kSplitScalesBytes;
+  return each_part(plan, whole, VCNN_PASS_FWD, [&](int n0, const ConvGeom& g, const F16x2Plan& p) {
+    const int64_t chw = (int64_t)g.c * g.h * g.w;
+    if (vcnn_status e = launch_absmax(x + n0 * chw, g.n * chw, w, g.M * g.K, sc, st)) return e;
+    return launch_conv_halo_f16x2(p.fwd, g.n, g.c, g.h, g.w, g.k, g.r, g.s, g.ph, g.pw, x + n0 * chw, w, g.K,
+                                  (int64_t)g.r * g.s, 0, bias, y + n0 * g.M * g.P, relu, sc, x8, x8 + 2 * p.fwd.x8_bytes, st);
+  });
+}
+
+vcnn_status launch_conv_f16x2_bwd_data(const F16x2Plan& plan, const ConvGeom& whole, const float* w, const float* dy,
+                                       float* dx, void* workspace, hipStream_t st) {
+  SplitScales* const sc = (SplitScales*)workspace;
+  char* const x8 = (char*)workspace + kSplitScalesBytes;
+  return each_part(plan, whole, VCNN_PASS_BWD_DATA, [&](int n0, const ConvGeom& g, const F16x2Plan& p) {
+    const float* const d = dy + n0 * g.M * g.P;
+    if (vcnn_status e = launch_absmax(d, g.M * g.N, w, g.M * g.K, sc, st)) return e;
+    return launch_conv_halo_f16x2(p.fwd, g.n, g.k, g.oh, g.ow, g.c, g.r, g.s, g.r - 1 - g.ph, g.s - 1 - g.pw, d, w,
+                                  (int64_t)g.r * g.s, g.K, 1, nullptr, dx + (int64_t)n0 * g.c * g.h * g.w, 0, sc, x8,
+                                  x8 + 2 * p.fwd.x8_bytes, st);
+  });
+}
+
+vcnn_status launch_conv_f16x2_filter(const F16x2Plan& plan, const ConvGeom& whole, const float* x, const float* dy, float* dw,
+                                     void* workspace, hipStream_t st) {
+  SplitScales* const sc = (SplitScales*)workspace;
+  char* const x8n = (char*)workspace + kSplitScalesBytes;
+  return each_part(plan, whole, VCNN_PASS_BWD_FILTER, [&](int n0, const ConvGeom& g, const F16x2Plan& p) {
+    char* const dyf = x8n + 2 * p.filter.x8n_bytes;
+    const int64_t chw = (int64_t)g.c * g.h * g.w;
+    const float* const d = dy + n0 * g.M * g.P;
+    if (vcnn_status e = launch_absmax(x + n0 * chw, g.n * chw, d, g.M * g.N, sc, st)) return e;
+    return launch_filter_grad_f16x2(p.filter, g, x + n0 * chw, d, dw, sc, x8n, dyf, (float*)(dyf + 2 * p.filter.dyf_bytes),
+                                    st, n0 > 0);
+  });
+}
+
+}  // namespace vcnn
