@@ -104,7 +104,7 @@ static bool fold_beats_halo(const ConvGeom& g, const HaloPlan& hp, const FoldPla
 
 // Which realisation a pass uses for a given shape.  The same decision drives the workspace query and
 // the launch, so the two always agree.
-enum Path { PATH_EXPLICIT, PATH_POINTWISE, PATH_FEW_OUT, PATH_FEW_IN, PATH_DIRECT_FILTER, PATH_HALO, PATH_HALO_FILTER, PATH_HALO_BF16, PATH_FILTER_BF16, PATH_HALO_FILTER_BF16, PATH_FEW_COLS_FILTER, PATH_SMALL, PATH_SMALL_BWD, PATH_FOLD, PATH_FFT, PATH_TAPS, PATH_POINTWISE_BF16, PATH_SPLIT, PATH_F16X2 };
+enum Path { PATH_EXPLICIT, PATH_POINTWISE, PATH_FEW_OUT, PATH_FEW_IN, PATH_DIRECT_FILTER, PATH_HALO, PATH_HALO_FILTER, PATH_HALO_BF16, PATH_FILTER_BF16, PATH_HALO_FILTER_BF16, PATH_FEW_COLS_FILTER, PATH_SMALL, PATH_SMALL_BWD, PATH_FOLD, PATH_FFT, PATH_TAPS, PATH_POINTWISE_BF16, PATH_SPLIT, PATH_F16X2, PATH_FOLD_FRAG };
 struct Plan {
   Path path;
   DirectGeom dg;
@@ -120,6 +120,7 @@ struct Plan {
   PointwiseFilterBf16Plan pwf;
   SplitPlan sp;
   F16x2Plan f2;
+  FoldFragPlan ff;
   int split;        // channel slices (few-out), output-map group size (few-in) or batch slices (filter gradient)
   size_t partial_bytes;
   size_t workspace_bytes;
@@ -167,6 +168,9 @@ static void prefer_two_terms(const ConvGeom& g, int pass, size_t offered, Plan* 
     const double blocks = std::ceil(rows / p->hp.bm) * (double)g.n * (double)p->hp.tiles_per_img;
     f32 += 1.3 * f32_seconds(blocks, (double)p->hp.bm * p->hp.bn / 4096.0, depth);
     if (depth < 64) return;
+  } else if (p->path == PATH_FOLD) {
+    // (as fold_beats_halo has it, per tile)
+    f32 += (double)g.n * p->fold.tiles_i * p->fold.tiles_j * (4.1e-6 * (double)ceil_div(g.M, 16) + 8e-6) / 1024.0;
   } else if (p->path == PATH_HALO_FILTER) {
     const HaloFilterPlan& h = p->hfp;
     const double blocks = std::ceil((double)g.M / h.bm) * std::ceil((double)g.K / h.bnk) * h.splits;
@@ -174,19 +178,37 @@ static void prefer_two_terms(const ConvGeom& g, int pass, size_t offered, Plan* 
   } else {
     return;
   }
+  // (what the launches, the scans and three products at the best rate take at least; the fold's launches alone 16 us:
+  // smaller layers are not worth planning for on every call)
+  const double operands = (double)g.n * g.c * g.h * g.w + (double)g.M * (double)g.K + (double)g.M * (double)g.N;
+  if (0.92 * f32 < (pass == VCNN_PASS_BWD_DATA ? 16e-6 : 22e-6 + 6.0 * operands / 3.5e12 + 6.0 * (double)g.M * (double)g.K * (double)g.N / 1.4e15)) return;
+  // The input gradient as the transposed product: the fold's own sums, so no more rounding than the float kernel's, and
+  // fewer than a correlation's.  It also serves layers whose correlation contracts for long over few tiles.
+  FoldFragPlan ff{};
+  double fold_s = 1e9;
+  if (pass == VCNN_PASS_BWD_DATA && bwd_data_fold_frag_plan(g, 2, std::max(own, two_term_allowance(pass, own)), &ff) &&
+      (offered == kAsk || ff.workspace_bytes <= offered))
+    fold_s = 1.05 * ff.est_seconds + 3e-6;
+  auto take_fold = [&] {
+    if (fold_s > 0.92 * f32) return;
+    p->path = PATH_FOLD_FRAG;
+    p->ff = ff;
+    p->workspace_bytes = align256(ff.workspace_bytes);
+  };
+  if (p->path == PATH_FOLD) return take_fold();
   F16x2Plan f2{};
   // (the kernel gradient's parts add up to one sum: its budget, and with it the order of that sum, depends on the
   // shape alone, not on how much more a caller has)
   const size_t ask = std::max(own, two_term_allowance(pass, own));
-  if (!conv_f16x2_plan(g, pass, ask - bias, &f2)) return;
+  if (!conv_f16x2_plan(g, pass, ask - bias, &f2)) return take_fold();
   const bool whole = f2.parts == 1;
   if (!whole && pass == VCNN_PASS_BWD_FILTER) {
     if (!conv_f16x2_plan(g, pass, own - bias, &f2)) return;
   } else if (!whole) {
-    if (offered == kAsk || !conv_f16x2_plan(g, pass, offered, &f2)) return;
+    if (offered == kAsk || !conv_f16x2_plan(g, pass, offered, &f2)) return take_fold();
   }
   const size_t need = align256(f2.workspace_bytes) + bias;
-  if (offered != kAsk && need > offered) return;
+  if (offered != kAsk && need > offered) return take_fold();
   if (pass == VCNN_PASS_BWD_FILTER) {
     // variance of the rounding, in units of one float accumulation's: per output, (sums in a slice) + (slices)
     const HaloFilterPlan& h = p->hfp;
@@ -195,6 +217,7 @@ static void prefer_two_terms(const ConvGeom& g, int pass, size_t offered, Plan* 
     const double after = 16 + 0.56 * ((double)g.N / 16 / (slices * waves_k) + slices + waves_k);
     if (after > before) return;
   }
+  if (fold_s < f2.est_seconds + 12e-6) return take_fold();
   if (f2.est_seconds + 12e-6 > 0.92 * f32) return;
   p->path = PATH_F16X2;
   p->f2 = f2;
@@ -258,6 +281,20 @@ static Plan make_plan(const ConvGeom& g, int pass, int dtype, size_t offered) {
       conv_halo_bf16_plan(g.n, g.k, g.oh, g.ow, g.c, g.r, g.s, g.r - 1 - g.ph, g.s - 1 - g.pw, &p.hb)) {
     p.path = PATH_HALO_BF16;
     p.workspace_bytes = p.hb.x8_bytes + p.hb.wf_bytes;
+    // Maps that contract for long over few tiles leave most of the chip idle in a correlation (one tile takes every map
+    // and tap); as the transposed product the taps are rows.  (9 160 8 8 -> 492 5 5: 150 -> 29 us, 6 283 14 10 -> 486 9 9:
+    // 472 -> 56 us; 16 38 64 64 -> 512 16 16 stays: 0.62 against 0.74 ms.)  The correlation takes 1.25 times its
+    // product's estimate and 15 us over drawn layers, and skips about half of the rows that only meet the zero border.
+    const double skip = 0.5 + 0.5 * (double)g.oh / g.h;
+    const double corr = 1.2 * skip * halo_bf16_seconds(p.hb, g.n, g.c, g.r, g.s, (int64_t)g.h * g.w) + 14e-6;
+    FoldFragPlan ff{};
+    const size_t own = p.workspace_bytes;
+    if (algo == VCNN_ALGO_AUTO && bwd_data_fold_frag_plan(g, 1, std::max(own, two_term_allowance(pass, own)), &ff) &&
+        (offered == kAsk || ff.workspace_bytes <= offered) && 1.05 * ff.est_seconds + 3e-6 < 0.9 * corr) {
+      p.path = PATH_FOLD_FRAG;
+      p.ff = ff;
+      p.workspace_bytes = align256(ff.workspace_bytes);
+    }
     return p;
   }
   // (a single map over many channels is faster as the taps-as-rows product below, as in the forward pass)
@@ -587,6 +624,7 @@ static vcnn_status conv_bwd_data_impl(const vcnn_conv_desc* d, int act_below, co
     return then_act(launch_conv_halo(plan.hp, dt, g.n, g.k, g.oh, g.ow, g.c, g.r, g.s, g.r - 1 - g.ph, g.s - 1 - g.pw, dy,
                                      workspace, nullptr, dx, 0, st));
   }
+  if (plan.path == PATH_FOLD_FRAG) return launch_bwd_data_fold_frag(plan.ff, g, w, dy, dx, workspace, st, da, ref);
   if (plan.path == PATH_FOLD) return launch_bwd_data_fold(plan.fold, dt, g, w, dy, dx, (float*)workspace, st, da, ref);
   // dcol[k][j] = sum_m W[m][k] * dY(m, j)
   GemmArgs a{};

@@ -212,7 +212,6 @@ struct HaloBf16Args {
   int hpos;           // positions per halo buffer (cgc*nr*wp rounded up to a multiple of 64)
   int nbuf;           // halo buffers: 2 = the next chunk is staged during the products of this one, 1 = between chunks
   int relu;
-  int flush;          // TWO_LEVEL: slabs between two flushes of a wave's accumulators
 };
 
 // The term pairs a step multiplies, smallest first: {term of the first operand, term of the second}, the order in which
@@ -241,10 +240,7 @@ __device__ __forceinline__ Acc mfma_term(uint4 a, uint4 b, Acc c) {
 // of their own.  TERMS = 3: both operands are given as three bfloat16 terms each (a float split exactly into three), and a step
 // multiplies the six largest of the nine term pairs - smallest first - into the same accumulators: the float product
 // to within float rounding, with every staged word and every fragment used for two or three MFMAs instead of one.
-// TWO_LEVEL (two terms): every a.flush slabs a wave adds its accumulators to a second set and starts them again from
-// zero.  A sum of s rounded additions becomes sums of about sqrt(s): the long contractions of an input gradient
-// (every map x every tap) then round less than the fold route, which adds them tap by tap.
-template <int WAVES_M, int WAVES_K, int TM, int TN, bool M16 = false, int WAVES_N = 1, int TERMS = 1, bool TWO_LEVEL = false>
+template <int WAVES_M, int WAVES_K, int TM, int TN, bool M16 = false, int WAVES_N = 1, int TERMS = 1>
 __global__ __launch_bounds__(kThreads, 2) void conv_halo_bf16_kernel(HaloBf16Args a) {
   static_assert(TERMS >= 1 && TERMS <= 3, "plain bfloat16 operands, or floats as two f16 or three bfloat16 terms");
   using Split = SplitTerms<TERMS>;
@@ -335,17 +331,6 @@ __global__ __launch_bounds__(kThreads, 2) void conv_halo_bf16_kernel(HaloBf16Arg
       for (int ni = 0; ni < TN; ++ni)
 #pragma unroll
         for (int q = 0; q < AQ; ++q) mixed[mi][ni][q] = 0.f;
-  }
-
-  Acc total[TWO_LEVEL ? TM : 1][TWO_LEVEL ? TN : 1];
-  int until_flush = a.flush;
-  if constexpr (TWO_LEVEL) {
-#pragma unroll
-    for (int mi = 0; mi < TM; ++mi)
-#pragma unroll
-      for (int ni = 0; ni < TN; ++ni)
-#pragma unroll
-        for (int q = 0; q < AQ; ++q) total[mi][ni][q] = 0.f;
   }
 
   const uint4* x8n = a.x8 + (int64_t)n * a.cg * a.h * a.w;
@@ -492,20 +477,6 @@ __global__ __launch_bounds__(kThreads, 2) void conv_halo_bf16_kernel(HaloBf16Arg
 #pragma unroll
         for (int i = 0; i < 4; ++i) o[i] = on[i];
         sl = after;
-        if constexpr (TWO_LEVEL) {
-          if (--until_flush == 0) {
-            until_flush = a.flush;
-#pragma unroll
-            for (int mi = 0; mi < TM; ++mi)
-#pragma unroll
-              for (int ni = 0; ni < TN; ++ni)
-#pragma unroll
-                for (int q = 0; q < AQ; ++q) {
-                  total[mi][ni][q] += join_f16(acc[mi][ni][q], mixed[mi][ni][q]);
-                  acc[mi][ni][q] = 0.f, mixed[mi][ni][q] = 0.f;
-                }
-          }
-        }
       }
     } else {
       // bfloat16 operands: the fragments are requested a slab ahead (a step is only TM * TN MFMAs long), the halo words
@@ -582,10 +553,7 @@ __global__ __launch_bounds__(kThreads, 2) void conv_halo_bf16_kernel(HaloBf16Arg
 #pragma unroll
       for (int ni = 0; ni < TN; ++ni)
 #pragma unroll
-        for (int q = 0; q < AQ; ++q) {
-          acc[mi][ni][q] = join_f16(acc[mi][ni][q], mixed[mi][ni][q]);
-          if constexpr (TWO_LEVEL) acc[mi][ni][q] += total[mi][ni][q];
-        }
+        for (int q = 0; q < AQ; ++q) acc[mi][ni][q] = join_f16(acc[mi][ni][q], mixed[mi][ni][q]);
   }
   // contraction split between waves: add the partial sums in wave order through LDS
   if (WAVES_K > 1) {
@@ -711,16 +679,16 @@ static bool plan_arrangement(int waves_m, int waves_n, int n, int c, int h, int 
   return true;
 }
 
-// Estimated time of the two-term kernel under plan p, in seconds: the matrix-pipe work of the busiest CU (at half the
+// Estimated time of the product kernel under plan p, in seconds: the matrix-pipe work of the busiest CU (at half the
 // nominal rate, what the kernel sustains with operands that change from step to step), padded pairs, rows and pixels
 // included, plus a block's start, its stages and its end.
-static double two_term_cost(const HaloBf16Plan& p, int n, int m, int r, int s, int64_t P) {
+static double halo_cost(const HaloBf16Plan& p, int n, int m, int r, int s, int64_t P) {
   const int rs = r * s, tile = p.m16 ? 16 : 32;
   const int waves_k = 4 / (p.waves_m * p.waves_n);
   int64_t slabs = 0;
   for (int ch = 0; ch < p.nchunks; ++ch)
     slabs += ceil_div(ceil_div((int64_t)std::min(p.cgc, p.cg - ch * p.cgc) * rs, 8), waves_k);
-  const double mfma = (double)slabs * (p.m16 ? 2 * 16 : 4 * 32) * 3 * p.tm * p.tn;  // matrix-pipe cycles of a wave
+  const double mfma = (double)slabs * (p.m16 ? 2 * 16 : 4 * 32) * (p.terms == 2 ? 3 : 1) * p.tm * p.tn;  // matrix-pipe cycles of a wave
   const double blocks = (double)ceil_div(m, tile * p.tm * p.waves_m) * n * (double)ceil_div(P, tile * p.tn * p.waves_n);
   const double per_cu = std::ceil(blocks / 256.0);
   const double stage = (p.nbuf == 1 ? 2500.0 : 700.0) * p.nchunks;
@@ -728,35 +696,31 @@ static double two_term_cost(const HaloBf16Plan& p, int n, int m, int r, int s, i
 }
 
 // The two-term form: every arrangement of the waves that the kernel is built for, the cheapest by the estimate above.
-static bool two_term_plan(int n, int c, int h, int w, int m, int r, int s, int ph, int pw, HaloBf16Plan* p, bool two_level) {
-  if (two_level && m > 48) return false;  // three accumulator sets: 48 x 64 or 32 x 64 per wave
+static bool two_term_plan(int n, int c, int h, int w, int m, int r, int s, int ph, int pw, HaloBf16Plan* p) {
   const int oh = h + 2 * ph - r + 1, ow = w + 2 * pw - s + 1;
   bool found = false;
   for (int arrangement = 0; arrangement < 4; ++arrangement) {
     const int waves_m = arrangement == 2 ? 2 : (arrangement == 3 ? 4 : 1), waves_n = arrangement == 0 ? 4 : 1;
     if (waves_m > 1 && m <= 64) continue;
     for (int k = 0; k < 2; ++k) {           // accumulators: two sets, so 64 x 64 or 32 x 128 per wave (M16: 48 x 64)
-      if (k == 1 && (m > 32 || two_level)) continue;
+      if (k == 1 && m > 32) continue;
       for (int nbuf = 2; nbuf >= 1; --nbuf) {
         HaloBf16Plan q{};
         double unused = 0;
         if (!plan_arrangement(waves_m, waves_n, n, c, h, w, m, r, s, ph, pw, &q, &unused, 2, nbuf, k)) continue;
-        q.est_seconds = two_term_cost(q, n, m, r, s, (int64_t)oh * ow);
+        q.est_seconds = halo_cost(q, n, m, r, s, (int64_t)oh * ow);
         if (!found || q.est_seconds < p->est_seconds) *p = q;
         found = true;
       }
     }
   }
-  if (found && two_level) {
-    const double slabs = (double)p->nchunks * (p->uch / 8) / (4 / (p->waves_m * p->waves_n));  // of one wave
-    p->flush = std::max(1, (int)std::lround(std::sqrt(slabs / (p->m16 ? 2 : 4))));
-  }
   return found;
 }
 
-bool conv_halo_bf16_plan(int n, int c, int h, int w, int m, int r, int s, int ph, int pw, HaloBf16Plan* p, int terms,
-                         bool two_level) {
-  if (terms == 2) return two_term_plan(n, c, h, w, m, r, s, ph, pw, p, two_level);
+double halo_bf16_seconds(const HaloBf16Plan& p, int n, int m, int r, int s, int64_t P) { return halo_cost(p, n, m, r, s, P); }
+
+bool conv_halo_bf16_plan(int n, int c, int h, int w, int m, int r, int s, int ph, int pw, HaloBf16Plan* p, int terms) {
+  if (terms == 2) return two_term_plan(n, c, h, w, m, r, s, ph, pw, p);
   double cost = 0;
   if (terms != 1 && m <= 128) return false;  // the three-term form is built for the arrangements of many maps only
   if (m <= 128) return plan_arrangement(m > 64 ? 2 : 1, 1, n, c, h, w, m, r, s, ph, pw, p, &cost, terms);
@@ -778,10 +742,10 @@ bool conv_halo_bf16_plan(int n, int c, int h, int w, int m, int r, int s, int ph
   return maps_ok || wide_ok;
 }
 
-template <int WAVES_M, int WAVES_K, int TM, int TN, bool M16 = false, int WAVES_N = 1, int TERMS = 1, bool TWO_LEVEL = false>
+template <int WAVES_M, int WAVES_K, int TM, int TN, bool M16 = false, int WAVES_N = 1, int TERMS = 1>
 static void launch_one(const HaloBf16Args& a, size_t lds, hipStream_t st) {
   const dim3 grid((unsigned)((int64_t)a.tiles_m * a.n * a.tiles_per_img)), block(kThreads);
-  auto kernel = conv_halo_bf16_kernel<WAVES_M, WAVES_K, TM, TN, M16, WAVES_N, TERMS, TWO_LEVEL>;
+  auto kernel = conv_halo_bf16_kernel<WAVES_M, WAVES_K, TM, TN, M16, WAVES_N, TERMS>;
   static bool opted = false;  // one flag per instantiation, i.e. per kernel
   if (!opted) {
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -868,13 +832,7 @@ static vcnn_status launch_product(const HaloBf16Plan& p, int n, int h, int w, in
   a.tiles_per_img = (int)ceil_div(a.P, tile * p.tn * p.waves_n);
   a.cg = p.cg, a.cgc = p.cgc, a.nchunks = p.nchunks, a.nr = p.nr, a.wp = p.wp, a.uch = p.uch, a.hpos = p.hpos, a.relu = relu;
   a.nbuf = p.nbuf;
-  a.flush = p.flush;
-  if (p.flush) {  // (planned for at most 48 maps)
-    if (p.m16 && p.waves_n == 4) launch_one<1, 1, 3, 4, true, 4, 2, true>(a, p.lds_bytes, st);
-    else if (p.m16) launch_one<1, 4, 3, 4, true, 1, 2, true>(a, p.lds_bytes, st);
-    else if (p.waves_n == 4) launch_one<1, 1, 1, 2, false, 4, 2, true>(a, p.lds_bytes, st);
-    else launch_one<1, 4, 1, 2, false, 1, 2, true>(a, p.lds_bytes, st);
-  } else if (p.m16 && p.terms == 2) {
+  if (p.m16 && p.terms == 2) {
     if (p.waves_n == 4) launch_one<1, 1, 3, 4, true, 4, 2>(a, p.lds_bytes, st);
     else launch_one<1, 4, 3, 4, true, 1, 2>(a, p.lds_bytes, st);
   } else if (p.m16) {
@@ -1524,7 +1482,7 @@ static bool filter_plan_form(const ConvGeom& g0, FilterGradBf16Plan* p, int term
   return tiles <= 0x7fffffffLL && p->splits <= 65535;
 }
 
-// Estimated time of the two-term kernel under plan p, in seconds (as two_term_cost above).
+// Estimated time of the two-term kernel under plan p, in seconds (as halo_cost above).
 static double two_term_filter_cost(const FilterGradBf16Plan& p, const ConvGeom& g) {
   const int waves_k = 4 / (p.waves_m * p.waves_n);
   const double run_slabs = (double)ceil_div(ceil_div((int64_t)p.bp, 8), waves_k);

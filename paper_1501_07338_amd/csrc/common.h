@@ -166,7 +166,6 @@ struct HaloBf16Plan {
   int terms;         // 1: bfloat16 operands; 2: float operands as two f16 terms each, three products per step; 3: as
                      // three bfloat16 terms each, six products per step
   double est_seconds;  // terms = 2: estimated time of the product kernel
-  int flush;           // terms = 2, two-level sums: slabs between two flushes of the accumulators (0: one level)
   size_t lds_bytes;
   size_t x8_bytes, wf_bytes;  // workspace: channel-interleaved input, fragment-ordered kernel matrix
 };
@@ -190,8 +189,9 @@ vcnn_status launch_pointwise_bf16(const PointwiseBf16Plan& p, int n, int rows, i
 bool pointwise_filter_bf16_plan(const ConvGeom& g, PointwiseFilterBf16Plan* p);
 vcnn_status launch_pointwise_filter_bf16(const PointwiseFilterBf16Plan& p, const ConvGeom& g, const void* x, const void* dy,
                                          float* dw, float* partial, hipStream_t st);
-bool conv_halo_bf16_plan(int n, int c, int h, int w, int m, int r, int s, int ph, int pw, HaloBf16Plan* p, int terms = 1,
-                         bool two_level = false);  // two_level: the two-term form that adds in two levels (m <= 48)
+bool conv_halo_bf16_plan(int n, int c, int h, int w, int m, int r, int s, int ph, int pw, HaloBf16Plan* p, int terms = 1);
+// estimated time of the product kernel under that plan, for m maps of P pixels from n images
+double halo_bf16_seconds(const HaloBf16Plan& p, int n, int m, int r, int s, int64_t P);
 // y = act(bias + W (*) x) with W(o, i, q) = wgt[o*w_so + i*w_si + (flip ? r*s-1-q : q)]; the workspace holds
 // x8_bytes + wf_bytes
 vcnn_status launch_conv_halo_bf16(const HaloBf16Plan& p, int n, int c, int h, int w, int m, int r, int s, int ph, int pw,
@@ -239,6 +239,8 @@ vcnn_status launch_filter_grad_bf16_terms(const FilterGradBf16Plan& p, const Con
 
 // ---- two f16 terms per float (split_f16.h): the float products of large layers, on the same kernels ------------------
 struct SplitScales;
+// partial maxima of the two operands (either may be empty: its exponent is then left alone)
+vcnn_status launch_absmax(const float* a, int64_t na, const float* b, int64_t nb, SplitScales* sc, hipStream_t st);
 vcnn_status launch_conv_halo_f16x2(const HaloBf16Plan& p, int n, int c, int h, int w, int m, int r, int s, int ph, int pw,
                                    const float* x, const float* wgt, int64_t w_so, int64_t w_si, int flip,
                                    const float* bias, float* y32, int relu, SplitScales* sc, void* x8_bufs, void* wf_bufs,
@@ -292,6 +294,18 @@ struct FoldPlan {
 bool bwd_data_fold_plan(const ConvGeom& g, FoldPlan* p);
 vcnn_status launch_bwd_data_fold(const FoldPlan& p, int dtype, const ConvGeom& g, const void* w, const void* dy, void* dx,
                                  float* partial, hipStream_t st, int dact = 0, const void* dact_ref = nullptr);
+
+// The same with the product on the half-precision matrix cores: float operands as two f16 terms each (terms = 2), or
+// bfloat16 ones (terms = 1); the batch in parts of `images` images whose workspace holds in `budget`.
+struct FoldFragPlan {
+  FoldPlan fold;
+  int terms, steps, images;
+  size_t lds_bytes, wf_bytes, df_bytes, partial_bytes, workspace_bytes;
+  double est_seconds;  // re-laying included, the gather not
+};
+bool bwd_data_fold_frag_plan(const ConvGeom& g, int terms, size_t budget, FoldFragPlan* p);
+vcnn_status launch_bwd_data_fold_frag(const FoldFragPlan& p, const ConvGeom& g, const void* w, const void* dy, void* dx,
+                                      void* workspace, hipStream_t st, int dact, const void* dact_ref);
 
 // ---- conv_taps.hip --------------------------------------------------------------------------------------
 // One-map layers over many channels with the kernel's taps as the rows of the product (see the file header).

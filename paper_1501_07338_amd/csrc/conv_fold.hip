@@ -18,7 +18,9 @@
 
 #include "common.h"
 #include "elem.h"
+#include "bf16_core.h"
 #include "mma_core.h"
+#include "split_f16.h"
 
 namespace vcnn {
 
@@ -61,6 +63,113 @@ __host__ __device__ inline FoldRegion fold_region(int it, int jt, int K, int P, 
   return g;
 }
 
+// Block order.  Consecutive block ids go round-robin to the 8 XCDs, each with its own L2: give every XCD a
+// contiguous run of the order below.  That order walks the tile grid (row tiles x all samples' column tiles) in
+// patches of kPatchI x PATCH_J tiles - about what one XCD holds resident at once -, so the blocks resident
+// together share kPatchI panels of the kernel matrix and PATCH_J panels of dy in L2 instead of sweeping one of the
+// operands whole.
+template <int PATCH_J>
+__device__ __forceinline__ void fold_block_tile(const FoldArgs& a, int* it_out, int* tj_out) {
+  const int total = gridDim.x;
+  const int per = total / 8;
+  const int t = (int)blockIdx.x < per * 8 ? ((int)blockIdx.x % 8) * per + (int)blockIdx.x / 8 : (int)blockIdx.x;
+  const int TI = a.tiles_i, TJ = a.n * a.tiles_j;
+  const int pj = t / (TI * PATCH_J);
+  const int rem = t - pj * (TI * PATCH_J);
+  const int wj = min(PATCH_J, TJ - pj * PATCH_J);
+  const int pi = rem / (kPatchI * wj);
+  const int rem2 = rem - pi * (kPatchI * wj);
+  const int hi = min(kPatchI, TI - pi * kPatchI);
+  const int jl = rem2 / hi;
+  *it_out = pi * kPatchI + (rem2 - jl * hi);
+  *tj_out = pj * PATCH_J + jl;
+}
+
+// phi_c^{-1} of a complete tile (it, jt) of sample n, on chip: folds the wave's accumulators into its half-waves' copies of
+// the region in `smem` (kCopies x rsz floats and the row table, over whatever the product kept there: every wave is past
+// its last read of it), adds the copies and writes the region, times 2^descale.
+template <bool MI_INDEP>
+__device__ __forceinline__ void fold_tile(const FoldArgs& a, int n, int it, int jt, const f32x16 (&acc)[2][2], float* smem,
+                                          int descale) {
+  constexpr int BM = kFoldBM, TM = 2, TN = 2;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int i0 = it * kFoldBM, j0 = jt * kFoldBN;
+  const int wm0 = (wave & 1) * 64, wn0 = (wave >> 1) * 64;
+  const int RS = a.r * a.s;
+  const FoldRegion g = fold_region(it, jt, a.K, a.P, RS, a.s, a.r, a.ow, a.ph);
+  float* const reg0 = smem;  // kCopies x rsz floats, over the operand slabs (all waves are past the last barrier)
+  int* const rowtab = reinterpret_cast<int*>(reg0 + kCopies * a.rsz);  // [BM] region offset of the tile's rows
+  for (int e = tid; e < kCopies / 4 * a.rsz; e += kThreads) reinterpret_cast<float4*>(reg0)[e] = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (tid < BM) {  // row i = (channel, kernel row, kernel column) -> offset of its tap inside the region; -1 beyond the matrix
+    const int i = i0 + tid;
+    const int ci = i / RS;
+    const int t = i - ci * RS;
+    const int r = t / a.s;
+    rowtab[tid] = i < a.K ? (ci - g.c_lo) * (g.nrows * a.wreg) + (r - g.r_lo) * a.wreg + (t - r * a.s) : -1;
+  }
+  __syncthreads();
+  const int l32 = lane & 31, half = lane >> 5;
+  float* const mine = reg0 + (wave * 2 + half) * a.rsz;
+  const int plane = g.nrows * a.wreg;
+  // region offset of this lane's two columns (pixels), relative to the tap (r_lo, s = 0) of channel c_lo
+  int col_off[TN];
+  bool col_ok[TN];
+#pragma unroll
+  for (int ni = 0; ni < TN; ++ni) {
+    const int p = j0 + wn0 + ni * 32 + l32;
+    col_ok[ni] = p < a.P;
+    const int pc = col_ok[ni] ? p : j0;
+    const int oh = pc / a.ow;
+    col_off[ni] = (oh - g.oh_first) * a.wreg + (pc - oh * a.ow);
+  }
+  // Neighbouring taps of one lane are neighbouring pixels of its neighbour lanes, so an add must see the adds of
+  // the steps before it: steps run strictly in program order (a wave's LDS accesses do).  Inside one step the
+  // addresses are provably distinct - a row's two column blocks are different pixels; rows 32 apart differ by a tap
+  // offset no pair of the wave's 64 pixels has (MI_INDEP, checked on the host) - so a step reads all its entries,
+  // adds, and writes them: one LDS round trip per step.
+  if (MI_INDEP) {
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      int off[TM];
+      float v[TM][TN];
+#pragma unroll
+      for (int mi = 0; mi < TM; ++mi) off[mi] = rowtab[wm0 + mi * 32 + acc_row(q, lane)];  // -1: row beyond the matrix
+#pragma unroll
+      for (int mi = 0; mi < TM; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < TN; ++ni) v[mi][ni] = mine[max(off[mi], 0) + col_off[ni]];
+#pragma unroll
+      for (int mi = 0; mi < TM; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < TN; ++ni)
+          if (off[mi] >= 0 && col_ok[ni]) mine[off[mi] + col_off[ni]] = v[mi][ni] + acc[mi][ni][q];
+    }
+  } else {
+#pragma unroll
+    for (int mi = 0; mi < TM; ++mi)
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        const int off = rowtab[wm0 + mi * 32 + acc_row(q, lane)];  // one row per half-wave and (mi, q)
+        if (off < 0) continue;
+        float v[TN];
+#pragma unroll
+        for (int ni = 0; ni < TN; ++ni) v[ni] = mine[off + col_off[ni]];
+#pragma unroll
+        for (int ni = 0; ni < TN; ++ni)
+          if (col_ok[ni]) mine[off + col_off[ni]] = v[ni] + acc[mi][ni][q];
+      }
+  }
+  __syncthreads();
+  float* out = a.partial + (((int64_t)n * a.tiles_i + it) * a.tiles_j + jt) * a.rsz;
+  const int used = g.nch * plane;
+  for (int e = tid; e < used; e += kThreads) {
+    float v = reg0[e];
+#pragma unroll
+    for (int k = 1; k < kCopies; ++k) v += reg0[k * a.rsz + e];
+    out[e] = ldexpf(v, descale);
+  }
+}
+
 template <bool A_VEC, bool B_VEC, bool MI_INDEP, typename T>
 __global__ __launch_bounds__(kThreads, 4) void bwd_data_fold_kernel(FoldArgs a) {
   constexpr int BM = kFoldBM, BN = kFoldBN, BK = kFoldBK, WM = 64, WN = 64, TM = 2, TN = 2;
@@ -75,27 +184,8 @@ __global__ __launch_bounds__(kThreads, 4) void bwd_data_fold_kernel(FoldArgs a) 
 
   const T* gA = static_cast<const T*>(a.w);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // Block order.  Consecutive block ids go round-robin to the 8 XCDs, each with its own L2: give every XCD a
-  // contiguous run of the order below.  That order walks the tile grid (row tiles x all samples' column tiles) in
-  // patches of kPatchI x kPatchJ tiles - about what one XCD holds resident at once -, so the blocks resident
-  // together share kPatchI panels of the kernel matrix and kPatchJ panels of dy in L2 instead of sweeping one of the
-  // operands whole.
   int it, tj;
-  {
-    const int total = gridDim.x;
-    const int per = total / 8;
-    const int t = (int)blockIdx.x < per * 8 ? ((int)blockIdx.x % 8) * per + (int)blockIdx.x / 8 : (int)blockIdx.x;
-    const int TI = a.tiles_i, TJ = a.n * a.tiles_j;
-    const int pj = t / (TI * kPatchJ);
-    const int rem = t - pj * (TI * kPatchJ);
-    const int wj = min(kPatchJ, TJ - pj * kPatchJ);
-    const int pi = rem / (kPatchI * wj);
-    const int rem2 = rem - pi * (kPatchI * wj);
-    const int hi = min(kPatchI, TI - pi * kPatchI);
-    const int jl = rem2 / hi;
-    it = pi * kPatchI + (rem2 - jl * hi);
-    tj = pj * kPatchJ + jl;
-  }
+  fold_block_tile<kPatchJ>(a, &it, &tj);
   const int n = tj / a.tiles_j, jt = tj - n * a.tiles_j;
   const int i0 = it * BM, j0 = jt * BN;
   const int wm0 = (wave & 1) * WM, wn0 = (wave >> 1) * WN;
@@ -177,79 +267,148 @@ __global__ __launch_bounds__(kThreads, 4) void bwd_data_fold_kernel(FoldArgs a) 
     __syncthreads();
   }
 
-  // ---- phi_c^{-1} of the tile, on chip ----------------------------------------------------------------------
-  const int RS = a.r * a.s;
-  const FoldRegion g = fold_region(it, jt, a.K, a.P, RS, a.s, a.r, a.ow, a.ph);
-  float* const reg0 = smem;  // kCopies x rsz floats, over the operand slabs (all waves are past the last barrier)
-  int* const rowtab = reinterpret_cast<int*>(reg0 + kCopies * a.rsz);  // [BM] region offset of the tile's rows
-  for (int e = tid; e < kCopies * a.rsz; e += kThreads) reg0[e] = 0.f;
-  if (tid < BM) {  // row i = (channel, kernel row, kernel column) -> offset of its tap inside the region; -1 beyond the matrix
-    const int i = i0 + tid;
-    const int ci = i / RS;
-    const int t = i - ci * RS;
-    const int r = t / a.s;
-    rowtab[tid] = i < a.K ? (ci - g.c_lo) * (g.nrows * a.wreg) + (r - g.r_lo) * a.wreg + (t - r * a.s) : -1;
-  }
-  __syncthreads();
-  const int l32 = lane & 31, half = lane >> 5;
-  float* const mine = reg0 + (wave * 2 + half) * a.rsz;
-  const int plane = g.nrows * a.wreg;
-  // region offset of this lane's two columns (pixels), relative to the tap (r_lo, s = 0) of channel c_lo
-  int col_off[TN];
-  bool col_ok[TN];
+  fold_tile<MI_INDEP>(a, n, it, jt, acc, smem, 0);
+}
+
+// ---- the same on the half-precision matrix cores -----------------------------------------------------------------------
+// TERMS = 2: float operands as two f16 terms each (split_f16.h), three products per step; TERMS = 1: bfloat16 operands.
+// Both operands are re-laid once into fragment order, frag[32-row tile][step of 16 maps][lane][8] (rows of the kernel
+// matrix's transpose, pixels of a sample's dy), one plane per term: a fragment is 1 KB that goes to LDS by direct
+// loads, a slab of kSlabSteps steps ahead, and is read back lane by lane without bank conflicts.  128 x 128 tiles, four
+// waves of 64 x 64, two blocks per CU (two accumulator sets): one block's fold runs under the other's products.
+struct FoldFragArgs {
+  FoldArgs f;
+  const uint4* wf;   // [4 tiles_i][steps][64]
+  const uint4* df;   // [n][4 tiles_j][steps][64]
+  int64_t wf_term, df_term;  // distance between the terms, in 16-byte words
+  int steps;         // of 16 output maps, a multiple of the slab's
+  const int32_t* exponent;   // TERMS = 2: the scales of dy and w
+};
+
+template <int TERMS>
+struct FoldSlab {
+  static constexpr int STEPS = TERMS == 2 ? 2 : 4;
+  static constexpr int WORDS = 4 * TERMS * STEPS * 64;  // 16-byte words of one operand's slab: four row tiles
+};
+
+template <int TERMS, bool MI_INDEP>
+__global__ __launch_bounds__(kThreads, 2) void bwd_data_fold_frag_kernel(FoldFragArgs a) {
+  using Slab = FoldSlab<TERMS>;
+  constexpr int TM = 2, TN = 2, STEPS = Slab::STEPS, WORDS = Slab::WORDS;
+  extern __shared__ float4 smem4[];
+  uint4* const lds = reinterpret_cast<uint4*>(smem4);  // two buffers of [w slab][dy slab], each [tile][term][step][64]
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int it, tj;
+  fold_block_tile<kPatchI>(a.f, &it, &tj);
+  const int n = tj / a.f.tiles_j, jt = tj - n * a.f.tiles_j;
+  // wave w stages row tile w of both operands: TERMS * STEPS fragments each, 1 KB a load
+  const uint4* const srcA = a.wf + ((int64_t)(4 * it + wave) * a.steps) * 64 + lane;
+  const uint4* const srcB = a.df + (((int64_t)n * a.f.tiles_j + jt) * 4 + wave) * a.steps * 64 + lane;
+  auto stage = [&](int sl, uint4* buf) {
+    uint4* const toA = buf + wave * (TERMS * STEPS * 64);
+    uint4* const toB = toA + WORDS;
 #pragma unroll
-  for (int ni = 0; ni < TN; ++ni) {
-    const int p = j0 + wn0 + ni * 32 + l32;
-    col_ok[ni] = p < a.P;
-    const int pc = col_ok[ni] ? p : j0;
-    const int oh = pc / a.ow;
-    col_off[ni] = (oh - g.oh_first) * a.wreg + (pc - oh * a.ow);
-  }
-  // Neighbouring taps of one lane are neighbouring pixels of its neighbour lanes, so an add must see the adds of
-  // the steps before it: steps run strictly in program order (a wave's LDS accesses do).  Inside one step the
-  // addresses are provably distinct - a row's two column blocks are different pixels; rows 32 apart differ by a tap
-  // offset no pair of the wave's 64 pixels has (MI_INDEP, checked on the host) - so a step reads all its entries,
-  // adds, and writes them: one LDS round trip per step.
-  if (MI_INDEP) {
+    for (int t = 0; t < TERMS; ++t)
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      int off[TM];
-      float v[TM][TN];
+      for (int i = 0; i < STEPS; ++i) {
+        load_to_lds16(srcA + t * a.wf_term + (sl * STEPS + i) * 64, toA + (t * STEPS + i) * 64);
+        load_to_lds16(srcB + t * a.df_term + (sl * STEPS + i) * 64, toB + (t * STEPS + i) * 64);
+      }
+  };
+  f32x16 acc[TM][TN], mixed[TERMS == 2 ? TM : 1][TERMS == 2 ? TN : 1];
+  zero_acc<TM, TN>(acc);
+  if constexpr (TERMS == 2) zero_acc<TM, TN>(mixed);
+  const int slabs = a.steps / STEPS;
+  const int ra = (wave & 1) * 2, rb = (wave >> 1) * 2;  // this wave's first row tile of either operand
+  stage(0, lds);
+  for (int sl = 0; sl < slabs; ++sl) {
+    const uint4* const A = lds + (sl & 1) * 2 * WORDS + lane;
+    const uint4* const B = A + WORDS;
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's share of the slab has landed
+    __syncthreads();                     // everyone's has, and the other buffer is free
+    if (sl + 1 < slabs) stage(sl + 1, lds + ((sl + 1) & 1) * 2 * WORDS);
 #pragma unroll
-      for (int mi = 0; mi < TM; ++mi) off[mi] = rowtab[wm0 + mi * 32 + acc_row(q, lane)];  // -1: row beyond the matrix
+    for (int i = 0; i < STEPS; ++i) {
+      uint4 fa[TERMS][TM], fb[TERMS][TN];
+#pragma unroll
+      for (int t = 0; t < TERMS; ++t) {
+#pragma unroll
+        for (int mi = 0; mi < TM; ++mi) fa[t][mi] = A[(((ra + mi) * TERMS + t) * STEPS + i) * 64];
+#pragma unroll
+        for (int ni = 0; ni < TN; ++ni) fb[t][ni] = B[(((rb + ni) * TERMS + t) * STEPS + i) * 64];
+      }
 #pragma unroll
       for (int mi = 0; mi < TM; ++mi)
 #pragma unroll
-        for (int ni = 0; ni < TN; ++ni) v[mi][ni] = mine[max(off[mi], 0) + col_off[ni]];
+        for (int ni = 0; ni < TN; ++ni) {
+          if constexpr (TERMS == 2) {
+            acc[mi][ni] = mfma_f16(fa[0][mi], fb[0][ni], acc[mi][ni]);
+            mixed[mi][ni] = mfma_f16(fa[0][mi], fb[1][ni], mixed[mi][ni]);
+          } else {
+            acc[mi][ni] = mfma_bf16(fa[0][mi], fb[0][ni], acc[mi][ni]);
+          }
+        }
+      if constexpr (TERMS == 2) {
 #pragma unroll
-      for (int mi = 0; mi < TM; ++mi)
+        for (int mi = 0; mi < TM; ++mi)
 #pragma unroll
-        for (int ni = 0; ni < TN; ++ni)
-          if (off[mi] >= 0 && col_ok[ni]) mine[off[mi] + col_off[ni]] = v[mi][ni] + acc[mi][ni][q];
+          for (int ni = 0; ni < TN; ++ni) mixed[mi][ni] = mfma_f16(fa[1][mi], fb[0][ni], mixed[mi][ni]);
+      }
     }
-  } else {
+  }
+  int descale = 0;
+  if constexpr (TERMS == 2) {
+    descale = -(a.exponent[0] + a.exponent[1]);
 #pragma unroll
     for (int mi = 0; mi < TM; ++mi)
 #pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const int off = rowtab[wm0 + mi * 32 + acc_row(q, lane)];  // one row per half-wave and (mi, q)
-        if (off < 0) continue;
-        float v[TN];
+      for (int ni = 0; ni < TN; ++ni)
 #pragma unroll
-        for (int ni = 0; ni < TN; ++ni) v[ni] = mine[off + col_off[ni]];
-#pragma unroll
-        for (int ni = 0; ni < TN; ++ni)
-          if (col_ok[ni]) mine[off + col_off[ni]] = v[ni] + acc[mi][ni][q];
-      }
+        for (int q = 0; q < 16; ++q) acc[mi][ni][q] = join_f16(acc[mi][ni][q], mixed[mi][ni][q]);
   }
-  __syncthreads();
-  float* out = a.partial + (((int64_t)n * a.tiles_i + it) * a.tiles_j + jt) * a.rsz;
-  const int used = g.nch * plane;
-  for (int e = tid; e < used; e += kThreads) {
-    float v = reg0[e];
+  __syncthreads();  // the slabs are read: the region takes their place
+  fold_tile<MI_INDEP>(a.f, n, it, jt, acc, reinterpret_cast<float*>(smem4), descale);
+}
+
+// Fragment order for an operand whose rows are contiguous and whose contraction index has stride s_k: word i of tile
+// (z, t) and step j holds row 32 t + lane % 32, contraction elements 16 j + 8 (lane / 32) + 0..7; zeros outside the
+// matrix.  blockIdx.y = tile, blockIdx.z = matrix (sample).  Loads of a wave: 128 contiguous bytes (float) per half-wave
+// and element, all eight in flight; stores 1 KB contiguous.
+template <int TERMS>
+__global__ __launch_bounds__(kThreads) void fold_fragments_kernel(const void* __restrict__ src, uint4* __restrict__ dst,
+                                                                  int64_t term, int rows, int depth, int64_t s_k,
+                                                                  int64_t s_z, int steps, SplitScales* __restrict__ sc,
+                                                                  int operand) {
+  int e = 0;
+  if constexpr (TERMS == 2) {
+    e = split_exponent(sc->partial[operand]);
+    if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x == 0) sc->exponent[operand] = e;
+  }
+  const int lane = threadIdx.x & 63, step = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
+  if (step >= steps) return;
+  const int row = blockIdx.y * 32 + (lane & 31), k0 = step * 16 + (lane >> 5) * 8;
+  const int64_t from = blockIdx.z * s_z + min(row, rows - 1);
+  const int64_t to = (((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * steps + step) * 64 + lane;
+  uint32_t v[8];
+  if constexpr (TERMS == 2) {
+    const float* const p = static_cast<const float*>(src) + from;
+    float f[8];
 #pragma unroll
-    for (int k = 1; k < kCopies; ++k) v += reg0[k * a.rsz + e];
-    out[e] = v;
+    for (int j = 0; j < 8; ++j) f[j] = p[min(k0 + j, depth - 1) * s_k];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = row < rows && k0 + j < depth ? split_f16(f[j], e) : 0u;
+    uint4 hi, lo;
+    pack_terms(v, &hi, &lo);
+    dst[to] = hi;
+    dst[to + term] = lo;
+  } else {
+    const bf16* const p = static_cast<const bf16*>(src) + from;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const uint32_t b = p[min(k0 + j, depth - 1) * s_k].bits;
+      v[j] = row < rows && k0 + j < depth ? b : 0u;
+    }
+    dst[to] = make_uint4(v[0] | v[1] << 16, v[2] | v[3] << 16, v[4] | v[5] << 16, v[6] | v[7] << 16);
   }
 }
 
@@ -330,6 +489,56 @@ bool bwd_data_fold_plan(const ConvGeom& g, FoldPlan* p) {
   return (int64_t)g.n * tiles_i * tiles_j <= 0x7fffffffLL;
 }
 
+// Rows i and i + 32 of one channel are taps (r1, s1), (r2, s2) with (r2 - r1) * s + (s2 - s1) = 32; their entries
+// for pixels p, p' land on one input pixel iff p' - p = (r2 - r1) * ow + (s2 - s1).  A wave's pixels span 64
+// consecutive ones, so beyond that distance the two rows' adds of one step cannot meet.
+static bool rows_independent(const ConvGeom& g) {
+  for (int dr = 32 / g.s; dr <= 32 / g.s + 1; ++dr) {
+    const int ds = 32 - dr * g.s;
+    if (ds > -g.s && ds < g.s && dr < g.r && std::abs(dr * g.ow + ds) < 64) return false;
+  }
+  return true;
+}
+
+static inline size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
+
+bool bwd_data_fold_frag_plan(const ConvGeom& whole, int terms, size_t budget, FoldFragPlan* p) {
+  if (!bwd_data_fold_plan(whole, &p->fold)) return false;
+  const int unit = terms == 2 ? FoldSlab<2>::STEPS : FoldSlab<1>::STEPS;
+  const size_t words = terms == 2 ? FoldSlab<2>::WORDS : FoldSlab<1>::WORDS;
+  p->terms = terms;
+  p->steps = (int)(ceil_div(ceil_div(whole.M, 16), unit) * unit);
+  const size_t frag = (size_t)p->steps * 64 * 16;  // bytes of one row tile and term
+  p->wf_bytes = align256(4 * (size_t)p->fold.tiles_i * frag);
+  p->lds_bytes = std::max(2 * 2 * words * 16, (size_t)p->fold.rsz * kCopies * sizeof(float) + kFoldBM * sizeof(int));
+  if (4 * (int64_t)std::max(p->fold.tiles_i, p->fold.tiles_j) > 65535) return false;  // tiles are a grid dimension
+  for (int parts = 1; parts <= whole.n; ++parts) {
+    const int images = (int)ceil_div(whole.n, parts);
+    if (images > 65535 || (parts > 1 && (int64_t)images * (parts - 1) >= whole.n)) continue;
+    p->images = images;
+    p->df_bytes = align256((size_t)images * 4 * p->fold.tiles_j * frag);
+    p->partial_bytes = align256((size_t)images * p->fold.tiles_i * p->fold.tiles_j * p->fold.rsz * sizeof(float));
+    p->workspace_bytes = kSplitScalesBytes + terms * (p->wf_bytes + p->df_bytes) + p->partial_bytes;
+    if (p->workspace_bytes > budget) continue;
+    // per CU: the tile's products at the rate the loop holds with operands that change (half the nominal one), and the
+    // part of the fold (LDS) that the other resident block's products do not cover
+    const double tiles = std::ceil((double)whole.n * p->fold.tiles_i * p->fold.tiles_j / 256.0);
+    const double mfma = (double)p->steps * (terms == 2 ? 12 : 4) * 32 * 1.9 / 2.4e9;
+    const double relay = (terms == 2 ? 12.0 : 4.0) * ((double)whole.M * whole.N + (double)whole.M * whole.K * parts) / 3.5e12;
+    p->est_seconds = tiles * (mfma + 3.5e-6) + relay + parts * 12e-6;
+    return true;
+  }
+  return false;
+}
+
+// dx from the regions, over `n` samples' worth of a.partial / a.dx
+template <typename T>
+static vcnn_status launch_fold_gather(const FoldArgs& a, hipStream_t st) {
+  const int64_t total = (int64_t)a.n * a.c * a.h * a.wd;
+  hipLaunchKernelGGL(fold_gather_kernel<T>, dim3((unsigned)ceil_div(total, kThreads)), dim3(kThreads), 0, st, a, 1.0f / (float)a.ow);
+  return check_launch("fold_gather");
+}
+
 vcnn_status launch_bwd_data_fold(const FoldPlan& p, int dtype, const ConvGeom& g, const void* w, const void* dy, void* dx,
                                  float* partial, hipStream_t st, int dact, const void* dact_ref) {
   FoldArgs a{};
@@ -341,14 +550,7 @@ vcnn_status launch_bwd_data_fold(const FoldPlan& p, int dtype, const ConvGeom& g
   const dim3 grid((unsigned)((int64_t)g.n * p.tiles_i * p.tiles_j)), block(kThreads);
   const bool bf = dtype == VCNN_BF16;
   const bool vec = bf ? g.K % 4 == 0 && group_aligned<bf16>(w) : g.K >= 4 && (reinterpret_cast<uintptr_t>(w) & 3) == 0;
-  // Rows i and i + 32 of one channel are taps (r1, s1), (r2, s2) with (r2 - r1) * s + (s2 - s1) = 32; their entries
-  // for pixels p, p' land on one input pixel iff p' - p = (r2 - r1) * ow + (s2 - s1).  A wave's pixels span 64
-  // consecutive ones, so beyond that distance the two rows' adds of one step cannot meet.
-  bool mi_indep = true;
-  for (int dr = 32 / g.s; dr <= 32 / g.s + 1; ++dr) {
-    const int ds = 32 - dr * g.s;
-    if (ds > -g.s && ds < g.s && dr < g.r && std::abs(dr * g.ow + ds) < 64) mi_indep = false;
-  }
+  const bool mi_indep = rows_independent(g);
   auto go = [&](auto kernel) {
     if (p.lds_bytes > 48 * 1024)  // opt in to more than the default dynamic LDS limit (idempotent, host-side only)
       (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024);
@@ -369,12 +571,57 @@ vcnn_status launch_bwd_data_fold(const FoldPlan& p, int dtype, const ConvGeom& g
     else go(bwd_data_fold_kernel<false, false, false, float>);
   }
   if (vcnn_status s = check_launch("bwd_data_fold")) return s;
-  const int64_t total = (int64_t)g.n * g.c * g.h * g.w;
-  const dim3 grid2((unsigned)ceil_div(total, kThreads));
-  const float inv_ow = 1.0f / (float)g.ow;
-  if (bf) hipLaunchKernelGGL(fold_gather_kernel<bf16>, grid2, block, 0, st, a, inv_ow);
-  else hipLaunchKernelGGL(fold_gather_kernel<float>, grid2, block, 0, st, a, inv_ow);
-  return check_launch("fold_gather");
+  return bf ? launch_fold_gather<bf16>(a, st) : launch_fold_gather<float>(a, st);
+}
+
+vcnn_status launch_bwd_data_fold_frag(const FoldFragPlan& p, const ConvGeom& g, const void* w, const void* dy, void* dx,
+                                      void* workspace, hipStream_t st, int dact, const void* dact_ref) {
+  SplitScales* const sc = (SplitScales*)workspace;
+  char* const wf = (char*)workspace + kSplitScalesBytes;
+  char* const df = wf + p.terms * p.wf_bytes;
+  FoldFragArgs a{};
+  a.f.partial = (float*)(df + p.terms * p.df_bytes);
+  a.f.dact = dact_ref ? dact : 0;
+  a.f.c = g.c, a.f.h = g.h, a.f.wd = g.w, a.f.m = (int)g.M, a.f.r = g.r, a.f.s = g.s, a.f.ph = g.ph, a.f.pw = g.pw;
+  a.f.oh = g.oh, a.f.ow = g.ow, a.f.P = (int)g.P, a.f.K = (int)g.K;
+  a.f.tiles_i = p.fold.tiles_i, a.f.tiles_j = p.fold.tiles_j, a.f.rsz = p.fold.rsz, a.f.wreg = p.fold.wreg;
+  a.wf = (const uint4*)wf, a.df = (const uint4*)df, a.wf_term = (int64_t)(p.wf_bytes / 16), a.df_term = (int64_t)(p.df_bytes / 16);
+  a.steps = p.steps, a.exponent = sc->exponent;
+  const size_t e = p.terms == 2 ? sizeof(float) : sizeof(bf16);
+  const bool indep = rows_independent(g);
+  const unsigned step_blocks = (unsigned)ceil_div(p.steps, kThreads / 64);
+  auto relay = [&](const void* src, void* dst, int64_t term, int rows, int tiles, int images, int64_t s_k, int64_t s_z, int operand) {
+    const dim3 grid(step_blocks, (unsigned)(4 * tiles), (unsigned)images);
+    if (p.terms == 2)
+      hipLaunchKernelGGL(fold_fragments_kernel<2>, grid, dim3(kThreads), 0, st, src, (uint4*)dst, term, rows, (int)g.M, s_k, s_z, p.steps, sc, operand);
+    else
+      hipLaunchKernelGGL(fold_fragments_kernel<1>, grid, dim3(kThreads), 0, st, src, (uint4*)dst, term, rows, (int)g.M, s_k, s_z, p.steps, sc, operand);
+    return check_launch("fold_fragments");
+  };
+  for (int n0 = 0; n0 < g.n; n0 += p.images) {
+    const int images = std::min(p.images, g.n - n0);
+    const char* const d = (const char*)dy + (size_t)n0 * g.M * g.P * e;
+    if (p.terms == 2)  // (the kernel matrix keeps its scale and its fragments from the first part)
+      if (vcnn_status s = launch_absmax((const float*)d, (int64_t)images * g.M * g.P, (const float*)w, n0 ? 0 : g.M * g.K, sc, st)) return s;
+    if (vcnn_status s = relay(d, df, a.df_term, (int)g.P, p.fold.tiles_j, images, g.P, g.M * g.P, 0)) return s;
+    if (n0 == 0)
+      if (vcnn_status s = relay(w, wf, a.wf_term, (int)g.K, p.fold.tiles_i, 1, g.K, 0, 1)) return s;
+    a.f.n = images;
+    a.f.dx = (char*)dx + (size_t)n0 * g.c * g.h * g.w * e;
+    a.f.dact_ref = dact_ref ? (const char*)dact_ref + (size_t)n0 * g.c * g.h * g.w * e : nullptr;
+    const dim3 grid((unsigned)((int64_t)images * p.fold.tiles_i * p.fold.tiles_j));
+    auto go = [&](auto kernel) {
+      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds_bytes);
+      hipLaunchKernelGGL(kernel, grid, dim3(kThreads), p.lds_bytes, st, a);
+    };
+    if (p.terms == 2 && indep) go(bwd_data_fold_frag_kernel<2, true>);
+    else if (p.terms == 2) go(bwd_data_fold_frag_kernel<2, false>);
+    else if (indep) go(bwd_data_fold_frag_kernel<1, true>);
+    else go(bwd_data_fold_frag_kernel<1, false>);
+    if (vcnn_status s = check_launch("bwd_data_fold_frag")) return s;
+    if (vcnn_status s = p.terms == 2 ? launch_fold_gather<float>(a.f, st) : launch_fold_gather<bf16>(a.f, st)) return s;
+  }
+  return VCNN_OK;
 }
 
 }  // namespace vcnn

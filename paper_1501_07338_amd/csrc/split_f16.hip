@@ -56,7 +56,7 @@ __global__ __launch_bounds__(kThreads) void absmax_kernel(AbsMaxArgs a) {
     a.scales->partial[op][blockIdx.x] = max(max(wave_max[0], wave_max[1]), max(wave_max[2], wave_max[3]));
 }
 
-static vcnn_status launch_absmax(const float* a, int64_t na, const float* b, int64_t nb, SplitScales* sc, hipStream_t st) {
+vcnn_status launch_absmax(const float* a, int64_t na, const float* b, int64_t nb, SplitScales* sc, hipStream_t st) {
   AbsMaxArgs args{{a, b}, {na, nb}, sc};
   hipLaunchKernelGGL(absmax_kernel, dim3(kAbsMaxBlocks, 2), dim3(kThreads), 0, st, args);
   return check_launch("absmax");
