@@ -104,7 +104,7 @@ static bool fold_beats_halo(const ConvGeom& g, const HaloPlan& hp, const FoldPla
 
 // Which realisation a pass uses for a given shape.  The same decision drives the workspace query and
 // the launch, so the two always agree.
-enum Path { PATH_EXPLICIT, PATH_POINTWISE, PATH_FEW_OUT, PATH_FEW_IN, PATH_DIRECT_FILTER, PATH_HALO, PATH_HALO_FILTER, PATH_HALO_BF16, PATH_FILTER_BF16, PATH_HALO_FILTER_BF16, PATH_FEW_COLS_FILTER, PATH_SMALL, PATH_SMALL_BWD, PATH_FOLD, PATH_FFT, PATH_TAPS, PATH_POINTWISE_BF16, PATH_SPLIT, PATH_F16X2, PATH_FOLD_FRAG };
+enum Path { PATH_EXPLICIT, PATH_POINTWISE, PATH_FEW_OUT, PATH_FEW_IN, PATH_DIRECT_FILTER, PATH_HALO, PATH_HALO_FILTER, PATH_HALO_BF16, PATH_FILTER_BF16, PATH_HALO_FILTER_BF16, PATH_FEW_COLS_FILTER, PATH_SMALL, PATH_SMALL_BWD, PATH_FOLD, PATH_FFT, PATH_TAPS, PATH_POINTWISE_BF16, PATH_SPLIT, PATH_F16X2, PATH_FOLD_FRAG, PATH_POINTWISE_F16 };
 struct Plan {
   Path path;
   DirectGeom dg;
@@ -121,6 +121,7 @@ struct Plan {
   SplitPlan sp;
   F16x2Plan f2;
   FoldFragPlan ff;
+  PointwiseF16Plan pw16;
   int split;        // channel slices (few-out), output-map group size (few-in) or batch slices (filter gradient)
   size_t partial_bytes;
   size_t workspace_bytes;
@@ -135,6 +136,10 @@ static constexpr size_t kScratchBytes = (size_t)32 << 20;
 static size_t two_term_allowance(int pass, size_t own) {
   if (pass != VCNN_PASS_BWD_FILTER) return (size_t)64 << 20;
   return own <= kScratchBytes ? kScratchBytes : (size_t)384 << 20;
+}
+// (1 x 1 layers are not cut into parts: their re-laid copies are as large as the activations)
+static size_t pointwise_allowance(int pass, size_t own) {
+  return pass == VCNN_PASS_BWD_FILTER && own <= kScratchBytes ? kScratchBytes : (size_t)384 << 20;
 }
 static constexpr size_t kAsk = ~(size_t)0;  // make_plan: plan for the workspace query, not for a given workspace
 
@@ -223,6 +228,31 @@ static void prefer_two_terms(const ConvGeom& g, int pass, size_t offered, Plan* 
   p->f2 = f2;
   // (a kernel gradient in parts asks for what the float route does: a call with less takes neither)
   p->workspace_bytes = whole ? need - bias : std::max(own - bias, need - bias);
+}
+
+// The same for the unpadded 1 x 1 layers (16 512 49 49 -> 512: see pointwise_f16.hip; 11 50 20 20 -> 455 input gradient 38 ->
+// 30 us, 11 296 56 12 -> 39 forward 28 against 31, stays).  The float product kernels take 1.0 to 1.3 times the estimate,
+// the two-term ones 0.9 to 1.1 times theirs.
+static void prefer_pointwise_f16(const ConvGeom& g, int pass, size_t offered, Plan* p) {
+  if (p->path != PATH_POINTWISE && !(p->path == PATH_HALO_FILTER && is_pointwise(g))) return;
+  const bool filter = pass == VCNN_PASS_BWD_FILTER;
+  const double rows = pass == VCNN_PASS_BWD_DATA ? (double)g.c : (double)g.k, cols = filter ? (double)g.c : (double)g.P;
+  const double depth = filter ? (double)g.N : (pass == VCNN_PASS_FWD ? (double)g.c : (double)g.k);
+  if (depth < 128 || cols < 128) return;  // (shorter sums round less in float than the split leaves; most of a tile padding)
+  double f32 = 8e-6;
+  if (filter) f32 += 2.0 * rows * cols * depth / 95e12;
+  else f32 += 1.3 * f32_seconds(std::ceil(rows / 64) * std::ceil(cols / 128) * g.n, 2, depth);
+  const double operands = filter ? (rows + cols) * depth : depth * cols * g.n;
+  if (0.92 * f32 < 12e-6 + 12.0 * operands / 4.5e12) return;  // not worth planning for
+  const size_t bias = filter ? align256(bias_grad_partial_bytes(g)) : 0, own = p->workspace_bytes + bias;
+  PointwiseF16Plan q{};
+  if (!pointwise_f16_plan(g, pass, &q)) return;
+  const size_t need = align256(q.workspace_bytes) + bias;
+  if (need > std::max(own, pointwise_allowance(pass, own)) || (offered != kAsk && need > offered)) return;
+  if (1.05 * q.est_seconds > 0.92 * f32) return;
+  p->path = PATH_POINTWISE_F16;
+  p->pw16 = q;
+  p->workspace_bytes = need - bias;
 }
 
 static Plan make_plan(const ConvGeom& g, int pass, int dtype, size_t offered) {
@@ -399,7 +429,10 @@ static Plan make_plan(const ConvGeom& g, int pass, int dtype, size_t offered) {
       p.workspace_bytes = col_bytes(g) + align256(bwd_filter_partial_bytes(g));
     }
   }
-  if (automatic && dtype == VCNN_F32) prefer_two_terms(g, pass, offered, &p);
+  if (automatic && dtype == VCNN_F32) {
+    prefer_pointwise_f16(g, pass, offered, &p);
+    prefer_two_terms(g, pass, offered, &p);
+  }
   if (pass == VCNN_PASS_BWD_FILTER) {
     p.bias_offset = p.workspace_bytes;
     p.workspace_bytes += align256(bias_grad_partial_bytes(g));
@@ -508,6 +541,8 @@ static vcnn_status conv_fwd_linear(const vcnn_conv_desc* d, const ConvGeom& g, c
                                  bias, y, relu, workspace, st);
   }
   if (plan.path == PATH_FFT) return launch_conv_fft(plan.fft, dt, g, x, w, bias, y, relu, workspace, st);
+  if (plan.path == PATH_POINTWISE_F16)
+    return launch_pointwise_f16(plan.pw16, g, VCNN_PASS_FWD, (const float*)w, (const float*)x, bias, (float*)y, relu, workspace, st);
   if (plan.path == PATH_F16X2)
     return launch_conv_f16x2_fwd(plan.f2, g, (const float*)x, (const float*)w, bias, (float*)y, relu, workspace, st);
   if (plan.path == PATH_SPLIT)
@@ -552,6 +587,8 @@ vcnn_status vcnn_conv_bwd_filter(const vcnn_conv_desc* d, const void* x, const v
   } else if (plan.path == PATH_FEW_COLS_FILTER) {
     if (vcnn_status s = launch_filter_grad_few_cols(plan.fcp, dt, g, x, dy, dw, dbias, (float*)workspace, st)) return s;
     if (plan.fcp.bias_column) return VCNN_OK;  // the bias gradient came out of the same product
+  } else if (plan.path == PATH_POINTWISE_F16) {
+    if (vcnn_status s = launch_pointwise_f16_filter(plan.pw16, g, (const float*)x, (const float*)dy, dw, workspace, st)) return s;
   } else if (plan.path == PATH_F16X2) {
     if (vcnn_status s = launch_conv_f16x2_filter(plan.f2, g, (const float*)x, (const float*)dy, dw, workspace, st)) return s;
   } else if (plan.path == PATH_SPLIT) {
@@ -605,6 +642,8 @@ static vcnn_status conv_bwd_data_impl(const vcnn_conv_desc* d, int act_below, co
     return then_act(launch_conv_halo_bf16(plan.hb, g.n, g.k, g.oh, g.ow, g.c, g.r, g.s, g.r - 1 - g.ph, g.s - 1 - g.pw, dy,
                                           w, (int64_t)g.r * g.s, g.K, 1, nullptr, dx, 0, workspace, st));
   }
+  if (plan.path == PATH_POINTWISE_F16)
+    return then_act(launch_pointwise_f16(plan.pw16, g, VCNN_PASS_BWD_DATA, (const float*)w, (const float*)dy, nullptr, (float*)dx, 0, workspace, st));
   if (plan.path == PATH_F16X2)
     return then_act(launch_conv_f16x2_bwd_data(plan.f2, g, (const float*)w, (const float*)dy, (float*)dx, workspace, st));
   if (plan.path == PATH_POINTWISE_BF16) {

@@ -249,6 +249,33 @@ vcnn_status launch_filter_grad_f16x2(const FilterGradBf16Plan& p, const ConvGeom
                                      float* dw, SplitScales* sc, void* x8n_bufs, void* dyf_bufs, float* partial,
                                      hipStream_t st, int accumulate);
 // ---- split_f16.hip: which float layers take them, and the scales -------------------------------------------------------
+// One operand into fragment order (frag_product.h): `images` matrices of `rows` x `depth` at distance s_z, strides s_row
+// and s_k (one of them 1), padded to `tiles` row tiles of 32 and `steps` steps of 16; terms `term` 16-byte words apart.
+// terms = 2: float, scaled by the exponent of its partial maxima; terms = 1: bfloat16.
+struct FragmentsArgs {
+  const void* src;
+  void* dst;
+  int64_t term;
+  int rows, depth;
+  int64_t s_row, s_k, s_z;
+  int tiles, images, steps, terms, operand;
+};
+vcnn_status launch_fragments(const FragmentsArgs& f, SplitScales* sc, hipStream_t st);
+// ---- pointwise_f16.hip: the unpadded 1 x 1 layers in float, both operands in fragment order ---------------------------------
+struct PointwiseF16Plan {
+  int tiles_i, tiles_j;  // 128-row tiles of the two operands (kernel gradient: maps, channels; else rows, pixels of a sample)
+  int steps;             // of 16 contraction elements (kernel gradient: pixels of a sample), whole slabs
+  int slabs_per_split, splits;  // kernel gradient: slabs (of any sample) per block
+  size_t a_bytes, b_bytes, partial_bytes, workspace_bytes;  // one term of either operand
+  double est_seconds;
+};
+bool pointwise_f16_plan(const ConvGeom& g, int pass, PointwiseF16Plan* p);
+// y[n][m][p] = act(bias + w x) (forward) or dx[n][c][p] = w^T dy (input gradient)
+vcnn_status launch_pointwise_f16(const PointwiseF16Plan& p, const ConvGeom& g, int pass, const float* w, const float* x,
+                                 const float* bias, float* y, int relu, void* workspace, hipStream_t st);
+vcnn_status launch_pointwise_f16_filter(const PointwiseF16Plan& p, const ConvGeom& g, const float* x, const float* dy, float* dw,
+                                        void* workspace, hipStream_t st);
+
 struct F16x2Plan {
   HaloBf16Plan fwd;           // forward pass, and the input gradient as a correlation, of `images` images
   FilterGradBf16Plan filter;  // kernel gradient of `images` images

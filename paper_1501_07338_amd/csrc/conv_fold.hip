@@ -18,9 +18,7 @@
 
 #include "common.h"
 #include "elem.h"
-#include "bf16_core.h"
-#include "mma_core.h"
-#include "split_f16.h"
+#include "frag_product.h"
 
 namespace vcnn {
 
@@ -272,10 +270,9 @@ __global__ __launch_bounds__(kThreads, 4) void bwd_data_fold_kernel(FoldArgs a) 
 
 // ---- the same on the half-precision matrix cores -----------------------------------------------------------------------
 // TERMS = 2: float operands as two f16 terms each (split_f16.h), three products per step; TERMS = 1: bfloat16 operands.
-// Both operands are re-laid once into fragment order, frag[32-row tile][step of 16 maps][lane][8] (rows of the kernel
-// matrix's transpose, pixels of a sample's dy), one plane per term: a fragment is 1 KB that goes to LDS by direct
-// loads, a slab of kSlabSteps steps ahead, and is read back lane by lane without bank conflicts.  128 x 128 tiles, four
-// waves of 64 x 64, two blocks per CU (two accumulator sets): one block's fold runs under the other's products.
+// Both operands are re-laid once into fragment order (rows of the kernel matrix's transpose, pixels of a sample's dy), and
+// the tile's product is frag_product's.  Two blocks per CU: one block's fold runs under the other's products.  16 38 64 64
+// -> 512 16 16: 3.17 (float kernel) -> 1.39 ms, matrix pipe 48 % busy at the 1.8 GHz the chip holds under it.
 struct FoldFragArgs {
   FoldArgs f;
   const uint4* wf;   // [4 tiles_i][steps][64]
@@ -285,100 +282,34 @@ struct FoldFragArgs {
   const int32_t* exponent;   // TERMS = 2: the scales of dy and w
 };
 
-template <int TERMS>
-struct FoldSlab {
-  static constexpr int STEPS = TERMS == 2 ? 2 : 4;
-  static constexpr int WORDS = 4 * TERMS * STEPS * 64;  // 16-byte words of one operand's slab: four row tiles
-};
-
 template <int TERMS, bool MI_INDEP>
 __global__ __launch_bounds__(kThreads, 2) void bwd_data_fold_frag_kernel(FoldFragArgs a) {
-  using Slab = FoldSlab<TERMS>;
-  constexpr int TM = 2, TN = 2, STEPS = Slab::STEPS, WORDS = Slab::WORDS;
   extern __shared__ float4 smem4[];
-  uint4* const lds = reinterpret_cast<uint4*>(smem4);  // two buffers of [w slab][dy slab], each [tile][term][step][64]
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   int it, tj;
   fold_block_tile<kPatchI>(a.f, &it, &tj);
   const int n = tj / a.f.tiles_j, jt = tj - n * a.f.tiles_j;
-  // wave w stages row tile w of both operands: TERMS * STEPS fragments each, 1 KB a load
-  const uint4* const srcA = a.wf + ((int64_t)(4 * it + wave) * a.steps) * 64 + lane;
-  const uint4* const srcB = a.df + (((int64_t)n * a.f.tiles_j + jt) * 4 + wave) * a.steps * 64 + lane;
-  auto stage = [&](int sl, uint4* buf) {
-    uint4* const toA = buf + wave * (TERMS * STEPS * 64);
-    uint4* const toB = toA + WORDS;
-#pragma unroll
-    for (int t = 0; t < TERMS; ++t)
-#pragma unroll
-      for (int i = 0; i < STEPS; ++i) {
-        load_to_lds16(srcA + t * a.wf_term + (sl * STEPS + i) * 64, toA + (t * STEPS + i) * 64);
-        load_to_lds16(srcB + t * a.df_term + (sl * STEPS + i) * 64, toB + (t * STEPS + i) * 64);
-      }
-  };
-  f32x16 acc[TM][TN], mixed[TERMS == 2 ? TM : 1][TERMS == 2 ? TN : 1];
-  zero_acc<TM, TN>(acc);
-  if constexpr (TERMS == 2) zero_acc<TM, TN>(mixed);
-  const int slabs = a.steps / STEPS;
-  const int ra = (wave & 1) * 2, rb = (wave >> 1) * 2;  // this wave's first row tile of either operand
-  stage(0, lds);
-  for (int sl = 0; sl < slabs; ++sl) {
-    const uint4* const A = lds + (sl & 1) * 2 * WORDS + lane;
-    const uint4* const B = A + WORDS;
-    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's share of the slab has landed
-    __syncthreads();                     // everyone's has, and the other buffer is free
-    if (sl + 1 < slabs) stage(sl + 1, lds + ((sl + 1) & 1) * 2 * WORDS);
-#pragma unroll
-    for (int i = 0; i < STEPS; ++i) {
-      uint4 fa[TERMS][TM], fb[TERMS][TN];
-#pragma unroll
-      for (int t = 0; t < TERMS; ++t) {
-#pragma unroll
-        for (int mi = 0; mi < TM; ++mi) fa[t][mi] = A[(((ra + mi) * TERMS + t) * STEPS + i) * 64];
-#pragma unroll
-        for (int ni = 0; ni < TN; ++ni) fb[t][ni] = B[(((rb + ni) * TERMS + t) * STEPS + i) * 64];
-      }
-#pragma unroll
-      for (int mi = 0; mi < TM; ++mi)
-#pragma unroll
-        for (int ni = 0; ni < TN; ++ni) {
-          if constexpr (TERMS == 2) {
-            acc[mi][ni] = mfma_f16(fa[0][mi], fb[0][ni], acc[mi][ni]);
-            mixed[mi][ni] = mfma_f16(fa[0][mi], fb[1][ni], mixed[mi][ni]);
-          } else {
-            acc[mi][ni] = mfma_bf16(fa[0][mi], fb[0][ni], acc[mi][ni]);
-          }
-        }
-      if constexpr (TERMS == 2) {
-#pragma unroll
-        for (int mi = 0; mi < TM; ++mi)
-#pragma unroll
-          for (int ni = 0; ni < TN; ++ni) mixed[mi][ni] = mfma_f16(fa[1][mi], fb[0][ni], mixed[mi][ni]);
-      }
-    }
-  }
-  int descale = 0;
-  if constexpr (TERMS == 2) {
-    descale = -(a.exponent[0] + a.exponent[1]);
-#pragma unroll
-    for (int mi = 0; mi < TM; ++mi)
-#pragma unroll
-      for (int ni = 0; ni < TN; ++ni)
-#pragma unroll
-        for (int q = 0; q < 16; ++q) acc[mi][ni][q] = join_f16(acc[mi][ni][q], mixed[mi][ni][q]);
-  }
-  __syncthreads();  // the slabs are read: the region takes their place
+  constexpr int STEPS = FragSlab<TERMS>::STEPS;
+  const uint4* const src_a = a.wf + ((int64_t)(4 * it + wave) * a.steps) * 64 + lane;
+  const uint4* const src_b = a.df + (((int64_t)n * a.f.tiles_j + jt) * 4 + wave) * a.steps * 64 + lane;
+  f32x16 acc[2][2];
+  frag_product<TERMS>(a.steps / STEPS, reinterpret_cast<uint4*>(smem4), a.wf_term, a.df_term,
+                      [&](int sl) { return src_a + sl * (STEPS * 64); }, [&](int sl) { return src_b + sl * (STEPS * 64); }, acc);
+  // the slabs are read: the region takes their place
+  const int descale = TERMS == 2 ? -(a.exponent[0] + a.exponent[1]) : 0;
   fold_tile<MI_INDEP>(a.f, n, it, jt, acc, reinterpret_cast<float*>(smem4), descale);
 }
 
-// Fragment order for an operand whose rows are contiguous and whose contraction index has stride s_k: word i of tile
-// (z, t) and step j holds row 32 t + lane % 32, contraction elements 16 j + 8 (lane / 32) + 0..7; zeros outside the
-// matrix.  blockIdx.y = tile, blockIdx.z = matrix (sample).  Loads of a wave: 128 contiguous bytes (float) per half-wave
-// and element, all eight in flight; stores 1 KB contiguous.
-template <int TERMS>
-__global__ __launch_bounds__(kThreads) void fold_fragments_kernel(const void* __restrict__ src, uint4* __restrict__ dst,
-                                                                  int64_t term, int rows, int depth, int64_t s_k,
-                                                                  int64_t s_z, int steps, SplitScales* __restrict__ sc,
-                                                                  int operand) {
+// Fragment order (frag_product.h) for an operand with rows at stride s_row and contraction elements at stride s_k, one of
+// them 1 (K_CONTIG: the elements); zeros outside the matrix.  blockIdx.y = row tile, blockIdx.z = matrix (sample).  Rows
+// contiguous: a half-wave reads 128 contiguous bytes (float) per element, all eight in flight; elements contiguous:
+// a lane reads its eight in two 16-byte loads at dword alignment.  Stores 1 KB contiguous per wave.
+template <int TERMS, bool K_CONTIG>
+__global__ __launch_bounds__(kThreads) void fragments_kernel(const void* __restrict__ src, uint4* __restrict__ dst,
+                                                             int64_t term, int rows, int depth, int64_t s_row, int64_t s_k,
+                                                             int64_t s_z, int steps, SplitScales* __restrict__ sc,
+                                                             int operand) {
+  static_assert(TERMS == 2 || !K_CONTIG, "bfloat16 operands: rows contiguous only");
   int e = 0;
   if constexpr (TERMS == 2) {
     e = split_exponent(sc->partial[operand]);
@@ -387,14 +318,19 @@ __global__ __launch_bounds__(kThreads) void fold_fragments_kernel(const void* __
   const int lane = threadIdx.x & 63, step = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
   if (step >= steps) return;
   const int row = blockIdx.y * 32 + (lane & 31), k0 = step * 16 + (lane >> 5) * 8;
-  const int64_t from = blockIdx.z * s_z + min(row, rows - 1);
+  const int64_t from = blockIdx.z * s_z + min(row, rows - 1) * s_row;
   const int64_t to = (((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * steps + step) * 64 + lane;
   uint32_t v[8];
   if constexpr (TERMS == 2) {
     const float* const p = static_cast<const float*>(src) + from;
     float f[8];
+    if (K_CONTIG && k0 + 8 <= depth) {
+      const float4 a = ld4_dword_aligned(p + k0), b = ld4_dword_aligned(p + k0 + 4);
+      f[0] = a.x, f[1] = a.y, f[2] = a.z, f[3] = a.w, f[4] = b.x, f[5] = b.y, f[6] = b.z, f[7] = b.w;
+    } else {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) f[j] = p[min(k0 + j, depth - 1) * s_k];
+      for (int j = 0; j < 8; ++j) f[j] = p[min(k0 + j, depth - 1) * s_k];
+    }
 #pragma unroll
     for (int j = 0; j < 8; ++j) v[j] = row < rows && k0 + j < depth ? split_f16(f[j], e) : 0u;
     uint4 hi, lo;
@@ -410,6 +346,18 @@ __global__ __launch_bounds__(kThreads) void fold_fragments_kernel(const void* __
     }
     dst[to] = make_uint4(v[0] | v[1] << 16, v[2] | v[3] << 16, v[4] | v[5] << 16, v[6] | v[7] << 16);
   }
+}
+
+vcnn_status launch_fragments(const FragmentsArgs& f, SplitScales* sc, hipStream_t st) {
+  const dim3 grid((unsigned)ceil_div(f.steps, kThreads / 64), (unsigned)f.tiles, (unsigned)f.images);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, st, f.src, (uint4*)f.dst, f.term, f.rows, f.depth, f.s_row, f.s_k,
+                       f.s_z, f.steps, sc, f.operand);
+  };
+  if (f.terms == 1) go(fragments_kernel<1, false>);
+  else if (f.s_k == 1) go(fragments_kernel<2, true>);
+  else go(fragments_kernel<2, false>);
+  return check_launch("fragments");
 }
 
 // p / d for 0 <= p < 2^23 and 0 < d: a float reciprocal and one correction step instead of an integer division
@@ -504,13 +452,13 @@ static inline size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 bool bwd_data_fold_frag_plan(const ConvGeom& whole, int terms, size_t budget, FoldFragPlan* p) {
   if (!bwd_data_fold_plan(whole, &p->fold)) return false;
-  const int unit = terms == 2 ? FoldSlab<2>::STEPS : FoldSlab<1>::STEPS;
-  const size_t words = terms == 2 ? FoldSlab<2>::WORDS : FoldSlab<1>::WORDS;
+  const int unit = terms == 2 ? FragSlab<2>::STEPS : FragSlab<1>::STEPS;
+  const size_t slabs = terms == 2 ? FragSlab<2>::LDS_BYTES : FragSlab<1>::LDS_BYTES;
   p->terms = terms;
   p->steps = (int)(ceil_div(ceil_div(whole.M, 16), unit) * unit);
   const size_t frag = (size_t)p->steps * 64 * 16;  // bytes of one row tile and term
   p->wf_bytes = align256(4 * (size_t)p->fold.tiles_i * frag);
-  p->lds_bytes = std::max(2 * 2 * words * 16, (size_t)p->fold.rsz * kCopies * sizeof(float) + kFoldBM * sizeof(int));
+  p->lds_bytes = std::max(slabs, (size_t)p->fold.rsz * kCopies * sizeof(float) + kFoldBM * sizeof(int));
   if (4 * (int64_t)std::max(p->fold.tiles_i, p->fold.tiles_j) > 65535) return false;  // tiles are a grid dimension
   for (int parts = 1; parts <= whole.n; ++parts) {
     const int images = (int)ceil_div(whole.n, parts);
@@ -589,23 +537,17 @@ vcnn_status launch_bwd_data_fold_frag(const FoldFragPlan& p, const ConvGeom& g, 
   a.steps = p.steps, a.exponent = sc->exponent;
   const size_t e = p.terms == 2 ? sizeof(float) : sizeof(bf16);
   const bool indep = rows_independent(g);
-  const unsigned step_blocks = (unsigned)ceil_div(p.steps, kThreads / 64);
-  auto relay = [&](const void* src, void* dst, int64_t term, int rows, int tiles, int images, int64_t s_k, int64_t s_z, int operand) {
-    const dim3 grid(step_blocks, (unsigned)(4 * tiles), (unsigned)images);
-    if (p.terms == 2)
-      hipLaunchKernelGGL(fold_fragments_kernel<2>, grid, dim3(kThreads), 0, st, src, (uint4*)dst, term, rows, (int)g.M, s_k, s_z, p.steps, sc, operand);
-    else
-      hipLaunchKernelGGL(fold_fragments_kernel<1>, grid, dim3(kThreads), 0, st, src, (uint4*)dst, term, rows, (int)g.M, s_k, s_z, p.steps, sc, operand);
-    return check_launch("fold_fragments");
-  };
+  FragmentsArgs of_dy{nullptr, df, a.df_term, (int)g.P, (int)g.M, 1, g.P, g.M * g.P, 4 * p.fold.tiles_j, 0, p.steps, p.terms, 0};
+  const FragmentsArgs of_w{w, wf, a.wf_term, (int)g.K, (int)g.M, 1, g.K, 0, 4 * p.fold.tiles_i, 1, p.steps, p.terms, 1};
   for (int n0 = 0; n0 < g.n; n0 += p.images) {
     const int images = std::min(p.images, g.n - n0);
     const char* const d = (const char*)dy + (size_t)n0 * g.M * g.P * e;
     if (p.terms == 2)  // (the kernel matrix keeps its scale and its fragments from the first part)
       if (vcnn_status s = launch_absmax((const float*)d, (int64_t)images * g.M * g.P, (const float*)w, n0 ? 0 : g.M * g.K, sc, st)) return s;
-    if (vcnn_status s = relay(d, df, a.df_term, (int)g.P, p.fold.tiles_j, images, g.P, g.M * g.P, 0)) return s;
+    of_dy.src = d, of_dy.images = images;
+    if (vcnn_status s = launch_fragments(of_dy, sc, st)) return s;
     if (n0 == 0)
-      if (vcnn_status s = relay(w, wf, a.wf_term, (int)g.K, p.fold.tiles_i, 1, g.K, 0, 1)) return s;
+      if (vcnn_status s = launch_fragments(of_w, sc, st)) return s;
     a.f.n = images;
     a.f.dx = (char*)dx + (size_t)n0 * g.c * g.h * g.w * e;
     a.f.dact_ref = dact_ref ? (const char*)dact_ref + (size_t)n0 * g.c * g.h * g.w * e : nullptr;

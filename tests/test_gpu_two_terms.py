@@ -179,3 +179,26 @@ def test_input_gradient_on_fragments(shape, dtype):
         assert_close(to_np(dx.float()), np.where(x > 0, want, 0), 4e-3 if bf else TOL, "dx, ReLU below")
     finally:
         vcnn.set_conv_algo(vcnn.ALGO_AUTO)
+
+
+# 1 x 1 layers on fragments: whole and ragged tiles, odd planes (rows at any dword), padded slabs, split and whole sums
+POINTWISE_SHAPES = [(16, 512, 49, 49, 512), (13, 389, 53, 51, 401), (11, 250, 33, 20, 455), (7, 260, 45, 45, 300)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", POINTWISE_SHAPES)
+def test_pointwise_layers_on_fragments(shape):
+    n, c, h, w, k = shape
+    d, x, wt, b, dy = tensors((n, c, h, w, k, 1, 1, 0, 0), 4700)
+    vcnn.set_conv_algo(vcnn.ALGO_AUTO)
+    assert vcnn.conv_workspace_bytes(d, vcnn.PASS_BWD_DATA) > 0  # (the float route needs none)
+    y, dw, db, dx = run(d, x, wt, b, dy)
+    xm, dm = x.astype(np.float64).reshape(n, c, -1), dy.astype(np.float64).reshape(n, k, -1)
+    wm = wt.astype(np.float64).reshape(k, c)
+    assert_close(y.reshape(n, k, -1), wm @ xm + b[:, None].astype(np.float64), TOL, "y")
+    assert_close(dx.reshape(n, c, -1), wm.T @ dm, TOL, "dx")
+    assert_close(dw.reshape(k, c), (dm @ xm.transpose(0, 2, 1)).sum(0), TOL, "dw")
+    assert_close(db, dm.sum((0, 2)), TOL, "db")
+    small = run(d, x, wt, b, dy, float_route_bytes(d))
+    for got, want in zip(small, (y, dw, db, dx)):
+        assert_close(got, want, 2 * TOL)
