@@ -73,8 +73,13 @@ class TrainStep:
                                                 L.stride, dtype=dtype)
             if getattr(L, "relu", False):  # gradient w.r.t. the pre-activation, read by both strands
                 self.dpre[li] = torch.empty(net.shapes[li], **act)
-            if isinstance(L, (Conv, FC)):
-                self.forked[li] = torch.cuda.Event()
+            if isinstance(L, Conv) and self.side is not None:
+                # a fork pays from about half a GFLOP of kernel gradient on: below, the events and the join cost the
+                # host and the chain more than the overlap returns (whole pass, two streams / one: cfg3 at batch 32,
+                # 0.37 GFLOP, 206 / 180 us; at batch 128, 1.5 GFLOP, 266 / 273 us; cfg2 at batch 16 129 / 91 us)
+                oshape = net.shapes[li]
+                if 2.0 * L.cout * ishape[1] * L.kh * L.kw * oshape[0] * oshape[2] * oshape[3] >= 5e8:
+                    self.forked[li] = torch.cuda.Event()
         self.workspace = torch.empty(max(ws_bytes, 256), dtype=torch.uint8, device=self.dev)
         self.workspace_side = torch.empty(max(ws_side_bytes, 256), dtype=torch.uint8, device=self.dev)
         if dtype == vcnn.BF16 and net.loss == "softmax":  # the cost works on float logits
@@ -127,6 +132,8 @@ class TrainStep:
     # ---- one pass each ---------------------------------------------------------------------------
     def forward(self, stream=None):
         net = self.net
+        # looked up once: each call of the binding would ask torch for the current stream again
+        stream = torch.cuda.current_stream() if stream is None else stream
         for li, L in enumerate(net.layers):
             a_in, a_out = self.acts[li], self.acts[li + 1]
             if isinstance(L, Conv):
@@ -142,6 +149,7 @@ class TrainStep:
 
     def cost(self, stream=None):
         net, out, dout = self.net, self.acts[-1], self.dacts[-1]
+        stream = torch.cuda.current_stream() if stream is None else stream
         if net.loss == "softmax" and self.dtype == vcnn.BF16:
             vcnn.bf16_to_f32(out.numel(), out, self.logits32, stream)
             vcnn.softmax_loss(out.shape[0], out.shape[1], self.logits32, self.labels, self.loss, self.dlogits32, stream)
@@ -162,6 +170,7 @@ class TrainStep:
         net = self.net
         main = stream if stream is not None else torch.cuda.current_stream()
         side = self.side if self.side is not None else main
+        joined = True   # nothing on the second stream yet
         folded = False  # the layer above already applied this layer's ReLU derivative and wrote dpre[li]
         for li in range(len(net.layers) - 1, -1, -1):
             L = net.layers[li]
@@ -190,15 +199,18 @@ class TrainStep:
             if not need_dx:  # nothing to overlap with
                 self._routed(li, lambda: vcnn.conv_bwd_filter(self.descs[li], a_in, d, dw, db, self.workspace, main))
                 continue
-            if side is not main:  # fork: the parameter-gradient strand starts once d is complete
+            fork = side is not main and li in self.forked
+            if fork:  # the parameter-gradient strand starts once d is complete
                 self.forked[li].record(main)
                 side.wait_event(self.forked[li])
+                joined = False
             # the input gradient first: the chain below waits for it, and a kernel-gradient block that is already
             # resident can leave no LDS for it
             self._routed(li, lambda: vcnn.conv_bwd_data_act(self.descs[li], act_below, a_in if folded else None, w, d,
                                                             dx_out, self.workspace, main))
-            self._routed(li, lambda: vcnn.conv_bwd_filter(self.descs[li], a_in, d, dw, db, self.workspace_side, side))
-        if side is not main:  # join before anything reads the parameter gradients
+            ws, st = (self.workspace_side, side) if fork else (self.workspace, main)
+            self._routed(li, lambda: vcnn.conv_bwd_filter(self.descs[li], a_in, d, dw, db, ws, st))
+        if not joined:  # before anything reads the parameter gradients
             main.wait_stream(side)
 
     def update(self, stream=None):
