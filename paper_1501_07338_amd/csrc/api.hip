@@ -313,7 +313,7 @@ static Plan make_plan(const ConvGeom& g, int pass, int dtype, size_t offered) {
     p.workspace_bytes = p.hb.x8_bytes + p.hb.wf_bytes;
     // Maps that contract for long over few tiles leave most of the chip idle in a correlation (one tile takes every map
     // and tap); as the transposed product the taps are rows.  (9 160 8 8 -> 492 5 5: 150 -> 29 us, 6 283 14 10 -> 486 9 9:
-    // 472 -> 56 us; 16 38 64 64 -> 512 16 16 stays: 0.62 against 0.74 ms.)  The correlation takes 1.25 times its
+    // 472 -> 56 us; 16 38 64 64 -> 512 16 16 stays: 0.60 against 0.68 ms.)  The correlation takes 1.25 times its
     // product's estimate and 15 us over drawn layers, and skips about half of the rows that only meet the zero border.
     const double skip = 0.5 + 0.5 * (double)g.oh / g.h;
     const double corr = 1.2 * skip * halo_bf16_seconds(p.hb, g.n, g.c, g.r, g.s, (int64_t)g.h * g.w) + 14e-6;

@@ -127,70 +127,80 @@ __global__ __launch_bounds__(kThreads) void reorder_weights_frag8_kernel(const b
   }
 }
 
-// The two re-laying passes for float operands as two f16 terms each (split_f16.h): the same layouts, one plane per term,
-// `term` 16-byte words apart; block 0 leaves the operand's exponent for the product kernel.
-__global__ __launch_bounds__(kThreads) void interleave_channels_split_kernel(const float* __restrict__ x,
-                                                                             uint4* __restrict__ x8, int64_t term, int C,
-                                                                             int CG, int HW, int64_t total,
-                                                                             SplitScales* __restrict__ sc, int operand) {
-  const int e = split_exponent(sc->partial[operand]);
-  const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+// The two re-laying passes for float operands as two f16 terms each (split_f16.h), in one launch: the same layouts, one plane
+// per term, `term` 16-byte words apart; each operand's first block leaves its exponent for the product kernel.  (Two
+// launches of some 5 us each on small layers, most of it their start: 128 32 15 15 -> 32 5 5 forward and input gradient,
+// 21 -> 14 us of re-laying together.)
+struct HaloSplitArgs {
+  const float* x;    // [n][c][HW]
+  uint4* x8;
+  int64_t x8_term, x_total;
+  int C, CG, HW;
+  const float* w;
+  uint4* wf;
+  int64_t wf_term, w_total, so, si;
+  int CO, RS, flip, cgc, nchunks, steps, m16;
+  int x_blocks;      // blocks of the input; the kernel matrix's follow
+  SplitScales* sc;   // slot 0: x, slot 1: w
+};
+
+__device__ __forceinline__ void interleave_channels_split(const HaloSplitArgs& a, int e, int64_t i) {
   if (i == 0) {
-    sc->exponent[operand] = e;
-    x8[total] = make_uint4(0u, 0u, 0u, 0u);
+    a.sc->exponent[0] = e;
+    a.x8[a.x_total] = make_uint4(0u, 0u, 0u, 0u);
   }
-  if (i >= total) return;
-  const int pos = (int)(i % HW);
-  const int64_t t = i / HW;
-  const int g = (int)(t % CG);
-  const int64_t n = t / CG;
-  const float* src = x + (n * C + g * 8) * HW + pos;
+  if (i >= a.x_total) return;
+  const int pos = (int)(i % a.HW);
+  const int64_t t = i / a.HW;
+  const int g = (int)(t % a.CG);
+  const int64_t n = t / a.CG;
+  const float* src = a.x + (n * a.C + g * 8) * a.HW + pos;
   float f[8];
 #pragma unroll
-  for (int c8 = 0; c8 < 8; ++c8) f[c8] = src[g * 8 + c8 < C ? (int64_t)c8 * HW : 0];
+  for (int c8 = 0; c8 < 8; ++c8) f[c8] = src[g * 8 + c8 < a.C ? (int64_t)c8 * a.HW : 0];
   uint32_t v[8];
 #pragma unroll
-  for (int c8 = 0; c8 < 8; ++c8) v[c8] = g * 8 + c8 < C ? split_f16(f[c8], e) : 0u;
+  for (int c8 = 0; c8 < 8; ++c8) v[c8] = g * 8 + c8 < a.C ? split_f16(f[c8], e) : 0u;
   uint4 hi, lo;
   pack_terms(v, &hi, &lo);
-  x8[i] = hi;
-  x8[i + term] = lo;
+  a.x8[i] = hi;
+  a.x8[i + a.x8_term] = lo;
 }
 
 // (a thread owns the eight channels of one (row, tap): 16-byte stores; the reads of a wave, one float per lane at the
 // stride of a kernel's taps, share cache lines over the steps of a chunk)
-__global__ __launch_bounds__(kThreads) void reorder_weights_split_kernel(const float* __restrict__ in,
-                                                                         uint4* __restrict__ out, int64_t term, int CO,
-                                                                         int CI, int RS, int64_t so, int64_t si, int flip,
-                                                                         int cgc, int nchunks, int steps, int m16,
-                                                                         int64_t total, SplitScales* __restrict__ sc,
-                                                                         int operand) {
-  const int e = split_exponent(sc->partial[operand]);
-  const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (i == 0) sc->exponent[operand] = e;
-  if (i >= total) return;
+__device__ __forceinline__ void reorder_weights_split(const HaloSplitArgs& a, int e, int64_t i) {
+  if (i == 0) a.sc->exponent[1] = e;
+  if (i >= a.w_total) return;
   const int lane = (int)i & 63;
   int64_t t = i >> 6;
-  const int jl = (int)(t % steps);
-  t /= steps;
-  const int ch = (int)(t % nchunks);
-  const int mt = (int)(t / nchunks);
-  const int row = m16 ? mt * 16 + (lane & 15) : mt * 32 + (lane & 31);
-  const int u = m16 ? 4 * jl + (lane >> 4) : 2 * jl + (lane >> 5);
-  const int gl = u / RS, q = u - gl * RS;
-  const int c0 = (ch * cgc + gl) * 8;
-  const bool ok = row < CO && gl < cgc;
-  const float* src = in + (ok ? (int64_t)row * so + (int64_t)c0 * si + (flip ? RS - 1 - q : q) : 0);
+  const int jl = (int)(t % a.steps);
+  t /= a.steps;
+  const int ch = (int)(t % a.nchunks);
+  const int mt = (int)(t / a.nchunks);
+  const int row = a.m16 ? mt * 16 + (lane & 15) : mt * 32 + (lane & 31);
+  const int u = a.m16 ? 4 * jl + (lane >> 4) : 2 * jl + (lane >> 5);
+  const int gl = u / a.RS, q = u - gl * a.RS;
+  const int c0 = (ch * a.cgc + gl) * 8;
+  const bool ok = row < a.CO && gl < a.cgc;
+  const float* src = a.w + (ok ? (int64_t)row * a.so + (int64_t)c0 * a.si + (a.flip ? a.RS - 1 - q : q) : 0);
   float f[8];
 #pragma unroll
-  for (int c8 = 0; c8 < 8; ++c8) f[c8] = ok && c0 + c8 < CI ? src[(int64_t)c8 * si] : 0.f;
+  for (int c8 = 0; c8 < 8; ++c8) f[c8] = ok && c0 + c8 < a.C ? src[(int64_t)c8 * a.si] : 0.f;
   uint32_t v[8];
 #pragma unroll
   for (int c8 = 0; c8 < 8; ++c8) v[c8] = split_f16(f[c8], e);
   uint4 hi, lo;
   pack_terms(v, &hi, &lo);
-  out[i] = hi;
-  out[i + term] = lo;
+  a.wf[i] = hi;
+  a.wf[i + a.wf_term] = lo;
+}
+
+__global__ __launch_bounds__(kThreads) void halo_split_kernel(HaloSplitArgs a) {
+  const bool weights = (int)blockIdx.x >= a.x_blocks;
+  const int e = split_exponent(a.sc->partial[weights]);
+  if (weights) reorder_weights_split(a, e, (int64_t)(blockIdx.x - a.x_blocks) * kThreads + threadIdx.x);
+  else interleave_channels_split(a, e, (int64_t)blockIdx.x * kThreads + threadIdx.x);
 }
 
 struct HaloBf16Args {
@@ -697,6 +707,7 @@ static double halo_cost(const HaloBf16Plan& p, int n, int m, int r, int s, int64
 
 // The two-term form: every arrangement of the waves that the kernel is built for, the cheapest by the estimate above.
 static bool two_term_plan(int n, int c, int h, int w, int m, int r, int s, int ph, int pw, HaloBf16Plan* p) {
+  if ((int64_t)n * ((c + 7) / 8) * h * w > (int64_t)kThreads << 30) return false;  // blocks of the re-laying pass
   const int oh = h + 2 * ph - r + 1, ow = w + 2 * pw - s + 1;
   bool found = false;
   for (int arrangement = 0; arrangement < 4; ++arrangement) {
@@ -879,18 +890,18 @@ vcnn_status launch_conv_halo_f16x2(const HaloBf16Plan& p, int n, int c, int h, i
                                    const float* x, const float* wgt, int64_t w_so, int64_t w_si, int flip,
                                    const float* bias, float* y32, int relu, SplitScales* sc, void* x8_bufs, void* wf_bufs,
                                    hipStream_t st) {
-  const int64_t total = (int64_t)n * p.cg * h * w;
-  hipLaunchKernelGGL(interleave_channels_split_kernel, dim3((unsigned)ceil_div(total, kThreads)), dim3(kThreads), 0, st, x,
-                     (uint4*)x8_bufs, (int64_t)(p.x8_bytes / 16), c, p.cg, h * w, total, sc, 0);
-  if (vcnn_status e = check_launch("interleave_channels_split")) return e;
   const int tile = p.m16 ? 16 : 32;
   const int bm = tile * p.tm * p.waves_m;
-  const int steps = p.uch / 8 * (p.m16 ? 2 : 4);
-  const int64_t wtotal = ceil_div(m, bm) * (bm / tile) * p.nchunks * steps * 64;
-  hipLaunchKernelGGL(reorder_weights_split_kernel, dim3((unsigned)ceil_div(wtotal, kThreads)), dim3(kThreads), 0, st, wgt,
-                     (uint4*)wf_bufs, (int64_t)(p.wf_bytes / 16), m, c, r * s, w_so, w_si, flip, p.cgc, p.nchunks, steps,
-                     p.m16, wtotal, sc, 1);
-  if (vcnn_status e = check_launch("reorder_weights_split")) return e;
+  HaloSplitArgs a{};
+  a.x = x, a.x8 = (uint4*)x8_bufs, a.x8_term = (int64_t)(p.x8_bytes / 16), a.x_total = (int64_t)n * p.cg * h * w;
+  a.C = c, a.CG = p.cg, a.HW = h * w;
+  a.w = wgt, a.wf = (uint4*)wf_bufs, a.wf_term = (int64_t)(p.wf_bytes / 16);
+  a.steps = p.uch / 8 * (p.m16 ? 2 : 4);
+  a.w_total = ceil_div(m, bm) * (bm / tile) * p.nchunks * a.steps * 64;
+  a.so = w_so, a.si = w_si, a.CO = m, a.RS = r * s, a.flip = flip, a.cgc = p.cgc, a.nchunks = p.nchunks, a.m16 = p.m16;
+  a.x_blocks = (int)ceil_div(a.x_total, kThreads), a.sc = sc;
+  hipLaunchKernelGGL(halo_split_kernel, dim3((unsigned)(a.x_blocks + ceil_div(a.w_total, kThreads))), dim3(kThreads), 0, st, a);
+  if (vcnn_status e = check_launch("halo_split")) return e;
   return launch_product(p, n, h, w, m, r, s, ph, pw, bias, nullptr, relu, x8_bufs, wf_bufs, st, y32, 0, sc);
 }
 

@@ -283,7 +283,7 @@ struct FoldFragArgs {
 };
 
 template <int TERMS, bool MI_INDEP>
-__global__ __launch_bounds__(kThreads, 2) void bwd_data_fold_frag_kernel(FoldFragArgs a) {
+__global__ __launch_bounds__(kThreads, TERMS == 2 ? 2 : 4) void bwd_data_fold_frag_kernel(FoldFragArgs a) {
   extern __shared__ float4 smem4[];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   int it, tj;
