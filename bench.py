@@ -4,8 +4,8 @@
 A "step" is one full training step (forward, cost, backward, SGD update) of a synthetic network whose
 inputs and weights are already resident in HBM; every arithmetic step runs in libvcnn's HIP kernels.
 The headline is the largest of the five workloads, the deconvolution CNN cfg5 in fp32 (1.29 TFLOP per
-step): images/s of the training step, GFLOP/s of its convolution passes against the fp32 matrix-core
-peak, and the roofline record of the pass that takes the most time.  cfg5 with bf16 storage and
+step): images/s of the training step, GFLOP/s of its convolution passes against the matrix-core
+peak for float products, and the roofline record of the pass that takes the most time.  cfg5 with bf16 storage and
 cfg1-cfg4 ride along as compact summaries; the long per-layer tables, the bandwidth-bound kernels and
 the mini-batch sweep go to a side file (--detail).
 
@@ -36,6 +36,9 @@ METRIC = "conv fwd+bwd GFLOP/s (% MFMA peak) and images/sec per training step, 1
 HBM_PEAK_GBS = 8000.0
 MFMA_F32_PEAK_TFLOPS = 157.3
 MFMA_BF16_PEAK_TFLOPS = 2500.0  # dense bf16 -> fp32 accumulate
+# A float product costs one multiply-add of the float instruction or three of the f16 one (two f16 terms per operand, the
+# route of the larger layers): the ceiling of the matrix cores for float products is the better of the two.
+MFMA_FLOAT_PRODUCT_PEAK_TFLOPS = max(MFMA_F32_PEAK_TFLOPS, MFMA_BF16_PEAK_TFLOPS / 3)
 WORKLOAD_TEXT = {
     "cfg1": "cfg1: single conv block 8x1x28x28 -> conv5x5x6 -> ReLU -> maxpool2, fwd + bwd from an upstream gradient",
     "cfg2": "cfg2: small recognition CNN, batch 128x1x28x28, conv5x5x20-pool-conv5x5x50-pool-fc500-fc10, "
@@ -201,7 +204,7 @@ def run_workload(name, steps, warmup, layer_iters=10, algos=None, phase_prefix=N
             mark(f"{phase_prefix or name}.conv{li}.{pname}")
             t = time_calls(fn, layer_iters, stream)
             mark("-")
-            peak = MFMA_BF16_PEAK_TFLOPS if bf16 else MFMA_F32_PEAK_TFLOPS
+            peak = MFMA_BF16_PEAK_TFLOPS if bf16 else MFMA_FLOAT_PRODUCT_PEAK_TFLOPS
             layers.append({"layer": f"conv{li}", "pass": pname, "M": g["M"], "K": g["K"], "N": g["N"], "ms": t,
                            "gflops": flops / (t * 1e6),
                            # the bf16 variant contracts on the bf16 matrix-core instructions: priced against their peak
@@ -214,7 +217,7 @@ def run_workload(name, steps, warmup, layer_iters=10, algos=None, phase_prefix=N
         del y_buf, dx_buf
     res["conv_layers"] = layers
     res["conv_gflops_fwd_bwd"] = conv_flops / (conv_ms * 1e6) if conv_ms else None
-    peak = MFMA_BF16_PEAK_TFLOPS if bf16 else MFMA_F32_PEAK_TFLOPS
+    peak = MFMA_BF16_PEAK_TFLOPS if bf16 else MFMA_FLOAT_PRODUCT_PEAK_TFLOPS
     res["conv_pct_mfma_peak"] = 100.0 * res["conv_gflops_fwd_bwd"] / (peak * 1e3) if conv_ms else None
     res["roofline"] = dominant_roofline(res)
     del graph, ts
@@ -239,14 +242,14 @@ def dominant_roofline(res):
     """Roofline record of the convolution pass that takes the most time inside the step.  A pass whose
     arithmetic intensity (flops over input + output + kernel bytes) is above the machine balance
     (matrix-core peak over 8 TB/s) is priced against the matrix-core peak of the instructions it contracts
-    on (fp32: 157.3 TFLOP/s; bf16 variant: 2.5 PFLOP/s), else against HBM."""
+    on (float products: 833 TFLOP/s, three f16 products each at 2.5 PFLOP/s; bf16 variant: 2.5 PFLOP/s), else against HBM."""
     layers = [l for l in res.get("conv_layers") or [] if l["in_step"]]
     if not layers:
         return None
     top = max(layers, key=lambda r: r["ms"])
     flops = 2.0 * top["M"] * top["K"] * top["N"]
     name = f"{res['workload']}.{top['layer']}.{top['pass']}"
-    peak = MFMA_BF16_PEAK_TFLOPS if res.get("storage_dtype") == "bf16" else MFMA_F32_PEAK_TFLOPS
+    peak = MFMA_BF16_PEAK_TFLOPS if res.get("storage_dtype") == "bf16" else MFMA_FLOAT_PRODUCT_PEAK_TFLOPS
     if flops / top["algorithmic_bytes"] >= peak * 1e3 / HBM_PEAK_GBS:
         ach = flops / (top["ms"] * 1e9)
         return {"kernel": name, "bound": "mfma", "achieved": ach, "peak": peak, "unit": "TFLOP/s",
@@ -344,8 +347,8 @@ def fourier_comparison(stream):
 def split_products_comparison(steps, warmup, default_res):
     """The same cfg5 training step with VCNN_ALGO_SPLIT: the float products of the forward pass and of the kernel
     gradient as sums of six bfloat16 products each (every float operand is exactly a sum of three bfloat16 terms; the
-    three smallest term products lie below float rounding).  On request only - the headline is the float
-    matrix-core path; this row shows what the chip's bfloat16 rate buys at float accuracy."""
+    three smallest term products lie below float rounding).  On request only: the headline's own route takes two f16
+    terms and three products on such layers (fewer products, and fewer roundings in its sums)."""
     from paper_1501_07338_amd import vcnn
     # the large layer only (c3: 383 GFLOP per pass, contraction 9728): on the smaller layers six passes of the bf16
     # kernels cost more than one of the float kernel
@@ -535,6 +538,8 @@ def main():
                    "ms_per_step_median": main_res["ms_per_step_median"],
                    "timing": "each step between its own event pair on the launch stream, mean of the K steps; the seeded "
                              "parameters are restored before every step outside the pair",
+                   "float_products": "larger layers: three f16 matrix-core products per float product (each operand two f16 terms "
+                                     "scaled by powers of two, 24 bits, fp32 accumulation); others: the float instruction",
                    "loss_first_step": main_res["loss_first_step"]},
         "conv_gflops_fwd_bwd": main_res["conv_gflops_fwd_bwd"],
         "conv_pct_mfma_peak": main_res["conv_pct_mfma_peak"],
