@@ -203,15 +203,16 @@ def main():
         out = [f"rocprofv3 matrix-core counters by benchmark phase: {args.name}, one MI355X (source tree at commit {head})", "",
                "command:",
                "  rocprofv3 --pmc SQ_VALU_MFMA_BUSY_CYCLES SQ_BUSY_CU_CYCLES SQ_INSTS_VALU_MFMA_MOPS_F32 SQ_INSTS_VALU_MFMA_MOPS_BF16 "
+               "SQ_INSTS_VALU_MFMA_MOPS_F16 "
                f"GRBM_GUI_ACTIVE --kernel-trace --output-format csv -d <dir> -o m -- python3 bench.py {args.cmd}",
-               "MfmaUtil = SQ_VALU_MFMA_BUSY_CYCLES / (4 SIMDs x SQ_BUSY_CU_CYCLES); executed MFMA flop = 512 x (MOPS_F32 + MOPS_BF16)",
+               "MfmaUtil = SQ_VALU_MFMA_BUSY_CYCLES / (4 SIMDs x SQ_BUSY_CU_CYCLES); executed MFMA flop = 512 x (MOPS_F32 + MOPS_BF16 + MOPS_F16)",
                "per dispatch (it includes tile padding and any zero border a kernel multiplies); durations under counter",
                "collection run a few % longer than in the timed runs.", ""]
         for phase, recs in m_ph.items():
             g = group(recs, "Kernel_Name", lambda r: int(r["Grid_Size"]))
             rows = []
             for k, v in g.items():
-                mops = statistics.mean(r["counters"].get("SQ_INSTS_VALU_MFMA_MOPS_F32", 0) + r["counters"].get("SQ_INSTS_VALU_MFMA_MOPS_BF16", 0) for r in v)
+                mops = statistics.mean(sum(r["counters"].get("SQ_INSTS_VALU_MFMA_MOPS_" + t, 0) for t in ("F32", "BF16", "F16")) for r in v)
                 if mops <= 0:
                     continue
                 busy = statistics.mean(r["counters"].get("SQ_VALU_MFMA_BUSY_CYCLES", 0) for r in v)

@@ -1332,7 +1332,7 @@ __global__ __launch_bounds__(kThreads, 2) void filter_grad_bf16_kernel(FilterBf1
         }
       }
     }
-    if (wave_k >= slabs && id + 1 < id1) {
+    if (WAVES_K > 1 && wave_k >= slabs && id + 1 < id1) {
       // a short run left this wave without a slab: the fragments it holds are that run's, not the next one's
       const uint4* src = frag_ptr(id + 1, first_sl);
 #pragma unroll

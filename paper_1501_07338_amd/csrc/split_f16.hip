@@ -106,6 +106,11 @@ bool conv_f16x2_plan(const ConvGeom& g, int pass, size_t budget, F16x2Plan* p) {
       if (parts > 1 && (int64_t)images * (parts - 1) >= g.n) continue;  // fewer parts of this size do
       F16x2Plan q{};
       if (!part_plan(g, pass, images, max_splits, &q)) return false;
+      if (const int rest = g.n % images) {  // the shorter last part has a plan of its own
+        F16x2Plan last{};
+        if (!part_plan(g, pass, rest, max_splits, &last)) return false;
+        q.workspace_bytes = std::max(q.workspace_bytes, last.workspace_bytes);
+      }
       if (q.workspace_bytes > budget) {  // (the room a part takes falls about as the parts rise)
         next = std::max(next, (int)(0.8 * parts * (double)q.workspace_bytes / (double)std::max<size_t>(budget, 1)));
         continue;
@@ -131,7 +136,7 @@ static vcnn_status each_part(const F16x2Plan& p, const ConvGeom& whole, int pass
       if (vcnn_status e = part(n0, g, p)) return e;
       continue;
     }
-    // a shorter last part: its own plan, which needs no more room (fewer images, at most as many slices)
+    // the shorter last part: its own plan, whose room the whole plan has counted in
     F16x2Plan last{};
     if (!part_plan(whole, pass, g.n, p.max_splits, &last) || last.workspace_bytes > p.workspace_bytes)
       return fail(VCNN_ERR_UNSUPPORTED, "conv: no plan for the last %d images", g.n);

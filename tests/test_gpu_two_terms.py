@@ -202,3 +202,21 @@ def test_pointwise_layers_on_fragments(shape):
     small = run(d, x, wt, b, dy, float_route_bytes(d))
     for got, want in zip(small, (y, dw, db, dx)):
         assert_close(got, want, 2 * TOL)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [vcnn.F32, vcnn.BF16])
+def test_kernel_gradient_with_a_run_shorter_than_the_waves_shares(dtype):
+    """A last run of output rows too short for every wave to get a slab, followed by the next image group in the same
+    block: the waves without a share must not carry that run's fragments into the next one."""
+    n, c, h, w, k, r, s = 16, 512, 57, 10, 20, 5, 5
+    d = vcnn.conv_desc(n, c, h, w, k, r, s, dtype=dtype)
+    x, dy = bf16_round(random_tensor(4801, (n, c, h, w))), bf16_round(random_tensor(4802, (n, k, h - 4, w - 4)))
+    t = torch.bfloat16 if dtype == vcnn.BF16 else torch.float32
+    xd, dyd = (torch.from_numpy(a).to(DEV).to(t) for a in (x, dy))
+    dw, db = torch.full((k, c, r, s), float("nan"), device=DEV), torch.full((k,), float("nan"), device=DEV)
+    ws = torch.empty(vcnn.conv_workspace_bytes(d, vcnn.PASS_BWD_FILTER), dtype=torch.uint8, device=DEV)
+    vcnn.conv_bwd_filter(d, xd, dyd, dw, db, ws)
+    rdw, rdb = O.conv_bwd_filter(x, dy, (r, s))
+    assert_close(to_np(dw), rdw, TOL, "dw")
+    assert_close(to_np(db), rdb, TOL, "db")
