@@ -32,7 +32,7 @@ ROOT = Path(__file__).resolve().parent
 if str(ROOT) not in sys.path:
     sys.path.insert(0, str(ROOT))
 
-METRIC = "conv fwd+bwd GFLOP/s (% MFMA peak) and images/sec per training step, 1 GPU"  # the benchmark's
+METRIC = "conv fwd+bwd GFLOP/s (% MFMA peak) and images/sec per training step, 1 GPU"
 HBM_PEAK_GBS = 8000.0
 MFMA_F32_PEAK_TFLOPS = 157.3
 MFMA_BF16_PEAK_TFLOPS = 2500.0  # dense bf16 -> fp32 accumulate

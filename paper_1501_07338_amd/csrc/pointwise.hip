@@ -560,8 +560,17 @@ __global__ __launch_bounds__(kThreads) void bias_grad_finish_kernel(int M, int s
                                                                     float* __restrict__ db) {
   const int m = blockIdx.x * kThreads + threadIdx.x;
   if (m >= M) return;
+  // (a serial chain of loads, one memory latency per slice, otherwise: 64 slices took 13 us)
   float acc = 0.f;
-  for (int s = 0; s < slices; ++s) acc += part[(int64_t)s * M + m];
+  int s = 0;
+  for (; s + 16 <= slices; s += 16) {
+    float v[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) v[u] = part[(int64_t)(s + u) * M + m];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) acc += v[u];
+  }
+  for (; s < slices; ++s) acc += part[(int64_t)s * M + m];
   db[m] = acc;
 }
 
