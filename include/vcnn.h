@@ -64,9 +64,13 @@ enum { VCNN_PASS_FWD = 0, VCNN_PASS_BWD_FILTER = 1, VCNN_PASS_BWD_DATA = 2 };
  * term products, accumulated in float, carry the product to within float rounding.  The result stays within the
  * float tolerance; the matrix cores multiply bfloat16 sixteen times as fast as float.  AUTO never takes it.
  * AUTO (and the choices that are AUTO elsewhere) computes the products of larger fp32 layers from two half-precision
- * terms per operand, scaled by powers of two: 24 significand bits, three products, float accumulation.  The result is at
- * least as close to the exact sums as the float instruction's.  IMPLICIT keeps to the float instruction.  An element
- * smaller than 2^-29 of its tensor's largest keeps an absolute error below 2^-50 of that largest element. */
+ * terms per operand, scaled by powers of two: 23 significand bits (an error of at most 2^-23 of each element), three of
+ * the four term products, float accumulation.  IMPLICIT keeps to the float instruction; on operands of ordinary range the
+ * two measure alike against the exact sums.  Activations, and dy in an input gradient, are scaled image by image, so that
+ * an image's result does not depend on the others.  The terms carry elements down to 2^-29 of the largest one under the
+ * same scale; an image (or kernel matrix, or operand of a kernel gradient) with more than one in 8192 of its elements
+ * below that, zeros aside, is computed by the float kernel instead, in its own time and that of the scan.  Nothing of this
+ * decision reaches the host. */
 enum { VCNN_ALGO_AUTO = 0, VCNN_ALGO_EXPLICIT = 1, VCNN_ALGO_IMPLICIT = 2, VCNN_ALGO_FOLD = 3, VCNN_ALGO_FFT = 4,
        VCNN_ALGO_SPLIT = 5 };
 
@@ -100,6 +104,11 @@ vcnn_status vcnn_conv_out_shape(const vcnn_conv_desc* d, int32_t* oh, int32_t* o
  * slower route that needs less; a forward pass or input gradient that brings more than it asks for may use it to work
  * on more of the batch at once. */
 vcnn_status vcnn_conv_workspace_bytes(const vcnn_conv_desc* d, int32_t pass, size_t* bytes);
+/* The route the given pass takes with that many bytes of aligned workspace, under the present VCNN_ALGO_* choice, as a
+ * short static string (for diagnostics and tests): "two_term", "two_term_fold" and "two_term_pointwise" are the fp32
+ * products from two half-precision terms, the others the names of their kernels.  VCNN_ERR_WORKSPACE if the pass cannot
+ * run with so little. */
+vcnn_status vcnn_conv_route(const vcnn_conv_desc* d, int32_t pass, size_t workspace_bytes, const char** name);
 
 /* phi_c (Eq. 2; mini-batch form Eq. 4): col[(c*R+r)*S+s][(n*OH+oh)*OW+ow] = xpad[n][c][oh+r-pad_h][ow+s-pad_w].
  * col is a dense [C*R*S][N*OH*OW] matrix of the descriptor's dtype.  Pure data movement. */

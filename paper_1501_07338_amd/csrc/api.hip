@@ -122,6 +122,8 @@ struct Plan {
   F16x2Plan f2;
   FoldFragPlan ff;
   PointwiseF16Plan pw16;
+  Path behind;       // PATH_F16X2, PATH_POINTWISE_F16: the float path enqueued behind for what the terms do not carry ...
+  size_t behind_at;  // ... and the offset of its workspace
   int split;        // channel slices (few-out), output-map group size (few-in) or batch slices (filter gradient)
   size_t partial_bytes;
   size_t workspace_bytes;
@@ -141,6 +143,9 @@ static size_t two_term_allowance(int pass, size_t own) {
 static size_t pointwise_allowance(int pass, size_t own) {
   return pass == VCNN_PASS_BWD_FILTER && own <= kScratchBytes ? kScratchBytes : (size_t)384 << 20;
 }
+// A launch of a float kernel behind a two-term product, whose blocks leave at once where nothing is left to them: it adds
+// 2 us (128 32 15 15 -> 32 5 5) to 4.5 us (16 512 49 49 -> 512 1 1) to a pass; it decides about the smaller layers.
+static constexpr double kLeaveSeconds = 2.5e-6;
 static constexpr size_t kAsk = ~(size_t)0;  // make_plan: plan for the workspace query, not for a given workspace
 
 // Estimated time of a float matrix-core kernel, in seconds: `blocks` blocks of four waves, each wave `tiles` accumulator
@@ -159,6 +164,8 @@ static double f32_seconds(double blocks, double tiles, double depth) {
 // 29 us, stays.)  The error against 64 bits is smaller than that of the kernel it replaces: the float instruction rounds
 // a sum once per two elements, the two-term one once per sixteen - 1.25e-8 sqrt(K) against 3.3e-9 sqrt(K) beside 7e-8
 // of the split itself; in the kernel gradient, whose sums are cut in slices, the count of roundings decides.
+//
+// The float kernel stays enqueued behind the product, for the images the terms do not carry (split_f16.h).
 //
 // `offered`: the workspace the call has (kAsk: the query).  A call whose workspace only holds the float route's partial
 // sums runs that route, as it always has.
@@ -194,6 +201,8 @@ static void prefer_two_terms(const ConvGeom& g, int pass, size_t offered, Plan* 
   if (pass == VCNN_PASS_BWD_DATA && bwd_data_fold_frag_plan(g, 2, std::max(own, two_term_allowance(pass, own)), &ff) &&
       (offered == kAsk || ff.workspace_bytes <= offered))
     fold_s = 1.05 * ff.est_seconds + 3e-6;
+  // (the float kernel behind the product leaves at once on ordinary data; one per part in the fold)
+  if (fold_s < 1e9) fold_s += kLeaveSeconds * (double)ceil_div(g.n, ff.images);
   auto take_fold = [&] {
     if (fold_s > 0.92 * f32) return;
     p->path = PATH_FOLD_FRAG;
@@ -205,15 +214,21 @@ static void prefer_two_terms(const ConvGeom& g, int pass, size_t offered, Plan* 
   // (the kernel gradient's parts add up to one sum: its budget, and with it the order of that sum, depends on the
   // shape alone, not on how much more a caller has)
   const size_t ask = std::max(own, two_term_allowance(pass, own));
-  if (!conv_f16x2_plan(g, pass, ask - bias, &f2)) return take_fold();
+  // (the float kernel's workspace: a kernel gradient's slices in the product's place, an input gradient's flipped kernel
+  // matrix beside it, where the product writes it)
+  const size_t beside = pass == VCNN_PASS_BWD_DATA ? p->workspace_bytes : 0;
+  if (ask < bias + beside || !conv_f16x2_plan(g, pass, ask - bias - beside, &f2)) return take_fold();
   const bool whole = f2.parts == 1;
   if (!whole && pass == VCNN_PASS_BWD_FILTER) {
     if (!conv_f16x2_plan(g, pass, own - bias, &f2)) return;
   } else if (!whole) {
-    if (offered == kAsk || !conv_f16x2_plan(g, pass, offered, &f2)) return take_fold();
+    if (offered == kAsk || offered < beside || !conv_f16x2_plan(g, pass, offered - beside, &f2)) return take_fold();
   }
-  const size_t need = align256(f2.workspace_bytes) + bias;
+  const size_t behind_at = pass == VCNN_PASS_BWD_FILTER ? split_scales_bytes(1) : align256(f2.workspace_bytes);
+  const size_t need = std::max(align256(f2.workspace_bytes), behind_at + p->workspace_bytes) + bias;
+  if (pass == VCNN_PASS_BWD_FILTER && need > ask) return;
   if (offered != kAsk && need > offered) return take_fold();
+  const double est = f2.est_seconds + 12e-6 + kLeaveSeconds;
   if (pass == VCNN_PASS_BWD_FILTER) {
     // variance of the rounding, in units of one float accumulation's: per output, (sums in a slice) + (slices)
     const HaloFilterPlan& h = p->hfp;
@@ -222,12 +237,12 @@ static void prefer_two_terms(const ConvGeom& g, int pass, size_t offered, Plan* 
     const double after = 16 + 0.56 * ((double)g.N / 16 / (slices * waves_k) + slices + waves_k);
     if (after > before) return;
   }
-  if (fold_s < f2.est_seconds + 12e-6) return take_fold();
-  if (f2.est_seconds + 12e-6 > 0.92 * f32) return;
+  if (fold_s < est) return take_fold();
+  if (est > 0.92 * f32) return;
+  p->behind = p->path, p->behind_at = behind_at;
   p->path = PATH_F16X2;
   p->f2 = f2;
-  // (a kernel gradient in parts asks for what the float route does: a call with less takes neither)
-  p->workspace_bytes = whole ? need - bias : std::max(own - bias, need - bias);
+  p->workspace_bytes = need - bias;
 }
 
 // The same for the unpadded 1 x 1 layers (16 512 49 49 -> 512: see pointwise_f16.hip; 11 50 20 20 -> 455 input gradient 38 ->
@@ -247,9 +262,11 @@ static void prefer_pointwise_f16(const ConvGeom& g, int pass, size_t offered, Pl
   const size_t bias = filter ? align256(bias_grad_partial_bytes(g)) : 0, own = p->workspace_bytes + bias;
   PointwiseF16Plan q{};
   if (!pointwise_f16_plan(g, pass, &q)) return;
-  const size_t need = align256(q.workspace_bytes) + bias;
+  const size_t behind_at = split_scales_bytes(filter ? 1 : g.n);
+  const size_t need = std::max(align256(q.workspace_bytes), behind_at + p->workspace_bytes) + bias;
   if (need > std::max(own, pointwise_allowance(pass, own)) || (offered != kAsk && need > offered)) return;
-  if (1.05 * q.est_seconds > 0.92 * f32) return;
+  if (1.05 * q.est_seconds + kLeaveSeconds > 0.92 * f32) return;
+  p->behind = p->path, p->behind_at = behind_at;
   p->path = PATH_POINTWISE_F16;
   p->pw16 = q;
   p->workspace_bytes = need - bias;
@@ -492,6 +509,37 @@ vcnn_status vcnn_conv_workspace_bytes(const vcnn_conv_desc* d, int32_t pass, siz
   return VCNN_OK;
 }
 
+vcnn_status vcnn_conv_route(const vcnn_conv_desc* d, int32_t pass, size_t workspace_bytes, const char** name) {
+  if (!name) return fail(VCNN_ERR_NULL, "conv_route: NULL out-parameter");
+  ConvGeom g;
+  if (vcnn_status s = make_geom(d, &g)) return s;
+  if (pass < VCNN_PASS_FWD || pass > VCNN_PASS_BWD_DATA) return fail(VCNN_ERR_UNSUPPORTED, "unknown pass %d", pass);
+  const Plan p = make_plan(g, pass, d->dtype, workspace_bytes);
+  if (p.workspace_bytes > workspace_bytes)
+    return fail(VCNN_ERR_WORKSPACE, "conv_route: %zu bytes of workspace, %zu needed", workspace_bytes, p.workspace_bytes);
+  switch (p.path) {
+    case PATH_EXPLICIT: *name = "explicit"; break;
+    case PATH_POINTWISE: *name = "pointwise"; break;
+    case PATH_FEW_OUT: *name = "few_out"; break;
+    case PATH_FEW_IN: *name = "few_in"; break;
+    case PATH_DIRECT_FILTER: *name = "direct_filter"; break;
+    case PATH_HALO: case PATH_HALO_FILTER: *name = "implicit"; break;
+    case PATH_HALO_BF16: case PATH_HALO_FILTER_BF16: *name = "implicit_bf16"; break;
+    case PATH_FILTER_BF16: *name = "explicit_bf16"; break;
+    case PATH_FEW_COLS_FILTER: *name = "few_cols"; break;
+    case PATH_SMALL: case PATH_SMALL_BWD: *name = "small"; break;
+    case PATH_FOLD: *name = "fold"; break;
+    case PATH_FFT: *name = "fft"; break;
+    case PATH_TAPS: *name = "taps"; break;
+    case PATH_POINTWISE_BF16: *name = "pointwise_bf16"; break;
+    case PATH_SPLIT: *name = "split"; break;
+    case PATH_F16X2: *name = "two_term"; break;
+    case PATH_FOLD_FRAG: *name = p.ff.terms == 2 ? "two_term_fold" : "fold_bf16"; break;
+    case PATH_POINTWISE_F16: *name = "two_term_pointwise"; break;
+  }
+  return VCNN_OK;
+}
+
 vcnn_status vcnn_im2col(const vcnn_conv_desc* d, const void* x, void* col, void* stream) {
   ConvGeom g;
   if (vcnn_status s = make_geom(d, &g)) return s;
@@ -534,17 +582,19 @@ static vcnn_status conv_fwd_linear(const vcnn_conv_desc* d, const ConvGeom& g, c
   if (plan.path == PATH_FEW_IN) return launch_direct_few_in(plan.dg, dt, plan.split, x, w, bias, y, relu, st);
   if (plan.path == PATH_SMALL)
     return launch_conv_small(dt, g.n, g.c, g.h, g.w, g.k, g.r, g.s, g.ph, g.pw, x, w, bias, y, relu, st);
-  if (plan.path == PATH_HALO)
-    return launch_conv_halo(plan.hp, dt, g.n, g.c, g.h, g.w, g.k, g.r, g.s, g.ph, g.pw, x, w, bias, y, relu, st);
+  auto float_halo = [&](const Declined& only) {
+    return launch_conv_halo(plan.hp, dt, g.n, g.c, g.h, g.w, g.k, g.r, g.s, g.ph, g.pw, x, w, bias, y, relu, st, only);
+  };
+  if (plan.path == PATH_HALO) return float_halo({});
   if (plan.path == PATH_HALO_BF16) {
     return launch_conv_halo_bf16(plan.hb, g.n, g.c, g.h, g.w, g.k, g.r, g.s, g.ph, g.pw, x, w, g.K, (int64_t)g.r * g.s, 0,
                                  bias, y, relu, workspace, st);
   }
   if (plan.path == PATH_FFT) return launch_conv_fft(plan.fft, dt, g, x, w, bias, y, relu, workspace, st);
-  if (plan.path == PATH_POINTWISE_F16)
-    return launch_pointwise_f16(plan.pw16, g, VCNN_PASS_FWD, (const float*)w, (const float*)x, bias, (float*)y, relu, workspace, st);
-  if (plan.path == PATH_F16X2)
-    return launch_conv_f16x2_fwd(plan.f2, g, (const float*)x, (const float*)w, bias, (float*)y, relu, workspace, st);
+  if (plan.path == PATH_F16X2) {
+    if (vcnn_status s = launch_conv_f16x2_fwd(plan.f2, g, (const float*)x, (const float*)w, bias, (float*)y, relu, workspace, st)) return s;
+    return float_halo(split_declined(workspace, g.n));
+  }
   if (plan.path == PATH_SPLIT)
     return launch_conv_split_fwd(plan.sp, g, (const float*)x, (const float*)w, bias, (float*)y, relu, workspace, st);
   // (its 16-byte reads of the kernel matrix need that alignment; a matrix placed otherwise takes the generic product)
@@ -558,7 +608,11 @@ static vcnn_status conv_fwd_linear(const vcnn_conv_desc* d, const ConvGeom& g, c
   a.a_si = g.K, a.a_sk = 1;
   a.c_si = g.P, a.c_sj = 1, a.c_P = (int)g.P, a.c_simg = g.M * g.P;
   a.relu = relu;
-  if (plan.path == PATH_POINTWISE || plan.path == PATH_POINTWISE_BF16) {
+  if (plan.path == PATH_POINTWISE_F16) {
+    if (vcnn_status s = launch_pointwise_f16(plan.pw16, g, VCNN_PASS_FWD, (const float*)w, (const float*)x, bias, (float*)y, relu, workspace, st)) return s;
+    a.only = split_declined(workspace, g.n);
+  }
+  if (plan.path == PATH_POINTWISE || plan.path == PATH_POINTWISE_F16 || plan.path == PATH_POINTWISE_BF16) {
     // patch matrix == input: B(k, j) = x[n][k][p]
     a.B = x;
     a.b_sk = g.P, a.b_sj = 1, a.b_P = (int)g.P, a.b_simg = g.K * g.P;
@@ -587,10 +641,12 @@ vcnn_status vcnn_conv_bwd_filter(const vcnn_conv_desc* d, const void* x, const v
   } else if (plan.path == PATH_FEW_COLS_FILTER) {
     if (vcnn_status s = launch_filter_grad_few_cols(plan.fcp, dt, g, x, dy, dw, dbias, (float*)workspace, st)) return s;
     if (plan.fcp.bias_column) return VCNN_OK;  // the bias gradient came out of the same product
-  } else if (plan.path == PATH_POINTWISE_F16) {
-    if (vcnn_status s = launch_pointwise_f16_filter(plan.pw16, g, (const float*)x, (const float*)dy, dw, workspace, st)) return s;
-  } else if (plan.path == PATH_F16X2) {
-    if (vcnn_status s = launch_conv_f16x2_filter(plan.f2, g, (const float*)x, (const float*)dy, dw, workspace, st)) return s;
+  } else if (plan.path == PATH_POINTWISE_F16 || plan.path == PATH_F16X2) {
+    const FilterBehind behind{&g, (const float*)x, (const float*)dy, plan.behind == PATH_HALO_FILTER ? &plan.hfp : nullptr,
+                              (float*)((char*)workspace + plan.behind_at)};
+    const vcnn_status s = plan.path == PATH_F16X2 ? launch_conv_f16x2_filter(plan.f2, g, behind.x, behind.dy, dw, workspace, behind, st)
+                                                  : launch_pointwise_f16_filter(plan.pw16, g, behind.x, behind.dy, dw, workspace, behind, st);
+    if (s != VCNN_OK) return s;
   } else if (plan.path == PATH_SPLIT) {
     if (vcnn_status s = launch_conv_split_filter(plan.sp, g, (const float*)x, (const float*)dy, dw, workspace, st)) return s;
   } else if (plan.path == PATH_POINTWISE_BF16) {
@@ -642,10 +698,15 @@ static vcnn_status conv_bwd_data_impl(const vcnn_conv_desc* d, int act_below, co
     return then_act(launch_conv_halo_bf16(plan.hb, g.n, g.k, g.oh, g.ow, g.c, g.r, g.s, g.r - 1 - g.ph, g.s - 1 - g.pw, dy,
                                           w, (int64_t)g.r * g.s, g.K, 1, nullptr, dx, 0, workspace, st));
   }
-  if (plan.path == PATH_POINTWISE_F16)
-    return then_act(launch_pointwise_f16(plan.pw16, g, VCNN_PASS_BWD_DATA, (const float*)w, (const float*)dy, nullptr, (float*)dx, 0, workspace, st));
-  if (plan.path == PATH_F16X2)
-    return then_act(launch_conv_f16x2_bwd_data(plan.f2, g, (const float*)w, (const float*)dy, (float*)dx, workspace, st));
+  auto float_halo = [&](void* flipped, const Declined& only) {
+    return launch_conv_halo(plan.hp, dt, g.n, g.k, g.oh, g.ow, g.c, g.r, g.s, g.r - 1 - g.ph, g.s - 1 - g.pw, dy, flipped,
+                            nullptr, dx, 0, st, only);
+  };
+  if (plan.path == PATH_F16X2) {
+    float* const flipped = (float*)((char*)workspace + plan.behind_at);
+    if (vcnn_status s = launch_conv_f16x2_bwd_data(plan.f2, g, (const float*)w, (const float*)dy, (float*)dx, flipped, workspace, st)) return s;
+    return then_act(float_halo(flipped, split_declined(workspace, g.n)));
+  }
   if (plan.path == PATH_POINTWISE_BF16) {
     // dx[n][c][p] = sum_m w[m][c] * dy[n][m][p]: the forward product on the transposed kernel matrix
     if (vcnn_status s = launch_flip_transpose(dt, w, workspace, g.k, g.c, 1, st)) return s;
@@ -660,8 +721,7 @@ static vcnn_status conv_bwd_data_impl(const vcnn_conv_desc* d, int act_below, co
   }
   if (plan.path == PATH_HALO) {
     if (vcnn_status s = launch_flip_transpose(dt, w, workspace, g.k, g.c, g.r * g.s, st)) return s;
-    return then_act(launch_conv_halo(plan.hp, dt, g.n, g.k, g.oh, g.ow, g.c, g.r, g.s, g.r - 1 - g.ph, g.s - 1 - g.pw, dy,
-                                     workspace, nullptr, dx, 0, st));
+    return then_act(float_halo(workspace, {}));
   }
   if (plan.path == PATH_FOLD_FRAG) return launch_bwd_data_fold_frag(plan.ff, g, w, dy, dx, workspace, st, da, ref);
   if (plan.path == PATH_FOLD) return launch_bwd_data_fold(plan.fold, dt, g, w, dy, dx, (float*)workspace, st, da, ref);
@@ -673,10 +733,15 @@ static vcnn_status conv_bwd_data_impl(const vcnn_conv_desc* d, int act_below, co
   a.a_si = 1, a.a_sk = g.K;
   a.b_sk = g.P, a.b_sj = 1, a.b_P = (int)g.P, a.b_simg = g.M * g.P;
   a.relu = 0;
-  if (plan.path == PATH_POINTWISE) {
+  if (plan.path == PATH_POINTWISE || plan.path == PATH_POINTWISE_F16) {
     // phi_c^{-1} is the identity per sample: store the product straight into dx[n][c][p].
     a.C = dx, a.out_dtype = dt;
     a.c_si = g.P, a.c_sj = 1, a.c_P = (int)g.P, a.c_simg = g.K * g.P;
+    if (plan.path == PATH_POINTWISE_F16) {
+      if (vcnn_status s = launch_pointwise_f16(plan.pw16, g, VCNN_PASS_BWD_DATA, (const float*)w, (const float*)dy, nullptr, (float*)dx, 0, workspace, st)) return s;
+      a.only = split_declined(workspace, g.n);
+      return then_act(launch_gemm_f32(a, st));
+    }
     a.dact = da, a.dact_ref = ref;
     return launch_gemm_f32(a, st);
   }

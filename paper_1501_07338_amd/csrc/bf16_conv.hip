@@ -128,7 +128,7 @@ __global__ __launch_bounds__(kThreads) void reorder_weights_frag8_kernel(const b
 }
 
 // The two re-laying passes for float operands as two f16 terms each (split_f16.h), in one launch: the same layouts, one plane
-// per term, `term` 16-byte words apart; each operand's first block leaves its exponent for the product kernel.  (Two
+// per term, `term` 16-byte words apart; the first block of a scale leaves it for the product kernel.  (Two
 // launches of some 5 us each on small layers, most of it their start: 128 32 15 15 -> 32 5 5 forward and input gradient,
 // 21 -> 14 us of re-laying together.)
 struct HaloSplitArgs {
@@ -136,42 +136,45 @@ struct HaloSplitArgs {
   uint4* x8;
   int64_t x8_term, x_total;
   int C, CG, HW;
+  int image_blocks;  // blocks of one image: a block never spans two, which have scales of their own
   const float* w;
   uint4* wf;
   int64_t wf_term, w_total, so, si;
   int CO, RS, flip, cgc, nchunks, steps, m16;
   int x_blocks;      // blocks of the input; the kernel matrix's follow
-  SplitScales* sc;   // slot 0: x, slot 1: w
+  SplitScales sc;    // slot 0: x, slot 1: w
 };
 
-__device__ __forceinline__ void interleave_channels_split(const HaloSplitArgs& a, int e, int64_t i) {
-  if (i == 0) {
-    a.sc->exponent[0] = e;
-    a.x8[a.x_total] = make_uint4(0u, 0u, 0u, 0u);
-  }
-  if (i >= a.x_total) return;
-  const int pos = (int)(i % a.HW);
-  const int64_t t = i / a.HW;
-  const int g = (int)(t % a.CG);
-  const int64_t n = t / a.CG;
-  const float* src = a.x + (n * a.C + g * 8) * a.HW + pos;
+// (both return the thread's count of small elements)
+__device__ __forceinline__ int interleave_channels_split(const HaloSplitArgs& a, int e, int image, int64_t local) {
+  if (image == 0 && local == 0) a.x8[a.x_total] = make_uint4(0u, 0u, 0u, 0u);
+  if (local >= (int64_t)a.CG * a.HW) return 0;
+  const int pos = (int)(local % a.HW);
+  const int g = (int)(local / a.HW);
+  const int64_t i = (int64_t)image * a.CG * a.HW + local;
+  const float* src = a.x + ((int64_t)image * a.C + g * 8) * a.HW + pos;
   float f[8];
 #pragma unroll
   for (int c8 = 0; c8 < 8; ++c8) f[c8] = src[g * 8 + c8 < a.C ? (int64_t)c8 * a.HW : 0];
   uint32_t v[8];
+  SmallElements small(e);
 #pragma unroll
-  for (int c8 = 0; c8 < 8; ++c8) v[c8] = g * 8 + c8 < a.C ? split_f16(f[c8], e) : 0u;
+  for (int c8 = 0; c8 < 8; ++c8) {
+    if (g * 8 + c8 >= a.C) f[c8] = 0.f;
+    v[c8] = split_f16(f[c8], e);
+    small.take(f[c8]);
+  }
   uint4 hi, lo;
   pack_terms(v, &hi, &lo);
   a.x8[i] = hi;
   a.x8[i + a.x8_term] = lo;
+  return small.count(f);
 }
 
 // (a thread owns the eight channels of one (row, tap): 16-byte stores; the reads of a wave, one float per lane at the
 // stride of a kernel's taps, share cache lines over the steps of a chunk)
-__device__ __forceinline__ void reorder_weights_split(const HaloSplitArgs& a, int e, int64_t i) {
-  if (i == 0) a.sc->exponent[1] = e;
-  if (i >= a.w_total) return;
+__device__ __forceinline__ int reorder_weights_split(const HaloSplitArgs& a, int e, int64_t i) {
+  if (i >= a.w_total) return 0;
   const int lane = (int)i & 63;
   int64_t t = i >> 6;
   const int jl = (int)(t % a.steps);
@@ -188,26 +191,39 @@ __device__ __forceinline__ void reorder_weights_split(const HaloSplitArgs& a, in
 #pragma unroll
   for (int c8 = 0; c8 < 8; ++c8) f[c8] = ok && c0 + c8 < a.C ? src[(int64_t)c8 * a.si] : 0.f;
   uint32_t v[8];
+  SmallElements small(e);
 #pragma unroll
-  for (int c8 = 0; c8 < 8; ++c8) v[c8] = split_f16(f[c8], e);
+  for (int c8 = 0; c8 < 8; ++c8) v[c8] = split_f16(f[c8], e), small.take(f[c8]);
   uint4 hi, lo;
   pack_terms(v, &hi, &lo);
   a.wf[i] = hi;
   a.wf[i + a.wf_term] = lo;
+  return small.count(f);
 }
 
 __global__ __launch_bounds__(kThreads) void halo_split_kernel(HaloSplitArgs a) {
-  const bool weights = (int)blockIdx.x >= a.x_blocks;
-  const int e = split_exponent(a.sc->partial[weights]);
-  if (weights) reorder_weights_split(a, e, (int64_t)(blockIdx.x - a.x_blocks) * kThreads + threadIdx.x);
-  else interleave_channels_split(a, e, (int64_t)blockIdx.x * kThreads + threadIdx.x);
+  const int op = (int)blockIdx.x >= a.x_blocks;
+  const int image = op ? 0 : (int)blockIdx.x / a.image_blocks;
+  const int block = op ? (int)blockIdx.x - a.x_blocks : (int)blockIdx.x - image * a.image_blocks;
+  const uint32_t largest = op ? split_max(a.sc.partial[1], kAbsMaxBlocks)
+                              : split_max(a.sc.partial[0] + (int64_t)image * a.sc.blocks, a.sc.blocks);
+  if (block == 0 && threadIdx.x == 0) note_scale(a.sc, op, image, largest);
+  const int e = split_exponent(largest);
+  const int64_t at = (int64_t)block * kThreads + threadIdx.x;
+  const int small = op ? reorder_weights_split(a, e, at) : interleave_channels_split(a, e, image, at);
+  note_small(a.sc, op, image, small);
 }
 
 struct HaloBf16Args {
   const uint4* x8;    // [n][cg][h][w] positions of 8 channels
   int64_t x8_term;    // TERMS > 1: distance between the terms of x8, and of wf, in 16-byte words
   int64_t wf_term;
-  const int32_t* exponent;  // TERMS = 2: the two operands' scales (result times 2^-(exponent[0] + exponent[1]))
+  const int32_t* image_exponent;  // TERMS = 2: the scales of the input's images ...
+  const int32_t* exponent;        // ... and of the kernel matrix (result times 2^-(image_exponent[n] + *exponent))
+  Declined declined;              // TERMS = 2: images left to the float kernel, which wants, for an input gradient, ...
+  const float* flip_w;            // ... this matrix [flip_m][m][r*s] ...
+  float* flipped;                 // ... flipped and transposed here
+  int flip_m;
   const uint4* zero;  // 16 zero bytes
   const uint4* wf;    // [mt][chunk][step][64 lanes] fragments
   const float* bias;  // [m] or null
@@ -223,6 +239,19 @@ struct HaloBf16Args {
   int nbuf;           // halo buffers: 2 = the next chunk is staged during the products of this one, 1 = between chunks
   int relu;
 };
+
+// This block's share of the kernel matrix flipped and transposed (as flip_transpose_kernel): w2[o][i][R S - 1 - q] =
+// w[i][o][q].  Only where an image is declined: the float kernel's own pass for it costs a launch on every call.
+__device__ __forceinline__ void flip_share(const HaloBf16Args& a) {
+  const int RS = a.r * a.s;
+  const int64_t count = (int64_t)a.flip_m * a.m * RS;
+  for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < count; i += (int64_t)gridDim.x * kThreads) {
+    const int q = (int)(i % RS);
+    const int64_t t = i / RS;
+    const int in = (int)(t % a.flip_m), out = (int)(t / a.flip_m);
+    a.flipped[i] = a.flip_w[((int64_t)in * a.m + out) * RS + (RS - 1 - q)];
+  }
+}
 
 // The term pairs a step multiplies, smallest first: {term of the first operand, term of the second}, the order in which
 // the next step's terms are first used, and the accumulator of a pair (two f16 terms: the mixed products have their own).
@@ -274,6 +303,10 @@ __global__ __launch_bounds__(kThreads, 2) void conv_halo_bf16_kernel(HaloBf16Arg
   const int tm = blockIdx.x % a.tiles_m;
   const int tj = blockIdx.x / a.tiles_m;
   const int n = tj / a.tiles_per_img;
+  if (TERMS == 2 && *a.declined.any) {
+    if (a.flipped) flip_share(a);
+    if (is_declined(a.declined, n)) return;
+  }
   const int p0 = (tj - n * a.tiles_per_img) * BN;
   const int i0 = tm * BM + wave_m * TILE * TM;  // first output map of this wave
   const int RS = a.r * a.s;
@@ -592,7 +625,7 @@ __global__ __launch_bounds__(kThreads, 2) void conv_halo_bf16_kernel(HaloBf16Arg
     if (wave_k != 0) return;
   }
 
-  const int descale = TERMS == 2 ? -(a.exponent[0] + a.exponent[1]) : 0;
+  const int descale = TERMS == 2 ? -(a.image_exponent[n] + *a.exponent) : 0;
 #pragma unroll
   for (int ni = 0; ni < TN; ++ni) {
     const int p = p0 + pw0 + ni * TILE + lcol;
@@ -707,7 +740,7 @@ static double halo_cost(const HaloBf16Plan& p, int n, int m, int r, int s, int64
 
 // The two-term form: every arrangement of the waves that the kernel is built for, the cheapest by the estimate above.
 static bool two_term_plan(int n, int c, int h, int w, int m, int r, int s, int ph, int pw, HaloBf16Plan* p) {
-  if ((int64_t)n * ((c + 7) / 8) * h * w > (int64_t)kThreads << 30) return false;  // blocks of the re-laying pass
+  if ((int64_t)n * ceil_div((int64_t)((c + 7) / 8) * h * w, kThreads) > 1 << 30) return false;  // blocks of the re-laying pass
   const int oh = h + 2 * ph - r + 1, ow = w + 2 * pw - s + 1;
   bool found = false;
   for (int arrangement = 0; arrangement < 4; ++arrangement) {
@@ -827,7 +860,8 @@ static vcnn_status relay_kernels(const HaloBf16Plan& p, int c, int m, int rs, co
 
 static vcnn_status launch_product(const HaloBf16Plan& p, int n, int h, int w, int m, int r, int s, int ph, int pw,
                                   const float* bias, void* y, int relu, const void* x8_buf, const void* wf_buf,
-                                  hipStream_t st, float* y32, int accumulate, const SplitScales* sc = nullptr) {
+                                  hipStream_t st, float* y32, int accumulate, const SplitScales* sc = nullptr,
+                                  const float* flip_w = nullptr, float* flipped = nullptr, int flip_m = 0) {
   const uint4* x8 = (const uint4*)x8_buf;
   const int tile = p.m16 ? 16 : 32;
   const int bm = tile * p.tm * p.waves_m;
@@ -835,7 +869,8 @@ static vcnn_status launch_product(const HaloBf16Plan& p, int n, int h, int w, in
   a.x8 = x8, a.zero = x8 + (int64_t)n * p.cg * h * w, a.wf = (const uint4*)wf_buf, a.bias = bias, a.y = (bf16*)y;
   a.x8_term = (int64_t)(p.x8_bytes / 16), a.wf_term = (int64_t)(p.wf_bytes / 16);  // (read by the split forms only)
   a.y32 = y32, a.accumulate = accumulate;
-  a.exponent = sc ? sc->exponent : nullptr;
+  if (sc) a.image_exponent = sc->exponent[0], a.exponent = sc->exponent[1], a.declined = sc->declined();
+  a.flip_w = flip_w, a.flipped = flipped, a.flip_m = flip_m;
   a.n = n, a.h = h, a.w = w, a.m = m, a.r = r, a.s = s, a.ph = ph, a.pw = pw;
   a.oh = h + 2 * ph - r + 1, a.ow = w + 2 * pw - s + 1;
   a.P = a.oh * a.ow;
@@ -885,11 +920,13 @@ vcnn_status launch_conv_halo_bf16_terms(const HaloBf16Plan& p, int n, int c, int
 }
 
 // Two-term form (p planned with terms = 2) of a float layer: x and wgt are float; x8_bufs / wf_bufs take the two re-laid
-// terms of each (2 x p.x8_bytes, 2 x p.wf_bytes), `sc` their scales (partial maxima of x in slot 0, of wgt in slot 1).
+// terms of each (2 x p.x8_bytes, 2 x p.wf_bytes), `sc` their scales (partial maxima of x's images in slot 0, of wgt in
+// slot 1).  Images that end up declined are not written; if there is one and `flipped` is given, it takes the kernel matrix
+// flipped and transposed for the float kernel.
 vcnn_status launch_conv_halo_f16x2(const HaloBf16Plan& p, int n, int c, int h, int w, int m, int r, int s, int ph, int pw,
                                    const float* x, const float* wgt, int64_t w_so, int64_t w_si, int flip,
-                                   const float* bias, float* y32, int relu, SplitScales* sc, void* x8_bufs, void* wf_bufs,
-                                   hipStream_t st) {
+                                   const float* bias, float* y32, int relu, const SplitScales& sc, void* x8_bufs, void* wf_bufs,
+                                   float* flipped, hipStream_t st) {
   const int tile = p.m16 ? 16 : 32;
   const int bm = tile * p.tm * p.waves_m;
   HaloSplitArgs a{};
@@ -899,10 +936,11 @@ vcnn_status launch_conv_halo_f16x2(const HaloBf16Plan& p, int n, int c, int h, i
   a.steps = p.uch / 8 * (p.m16 ? 2 : 4);
   a.w_total = ceil_div(m, bm) * (bm / tile) * p.nchunks * a.steps * 64;
   a.so = w_so, a.si = w_si, a.CO = m, a.RS = r * s, a.flip = flip, a.cgc = p.cgc, a.nchunks = p.nchunks, a.m16 = p.m16;
-  a.x_blocks = (int)ceil_div(a.x_total, kThreads), a.sc = sc;
+  a.image_blocks = (int)ceil_div((int64_t)p.cg * h * w, kThreads);
+  a.x_blocks = n * a.image_blocks, a.sc = sc;
   hipLaunchKernelGGL(halo_split_kernel, dim3((unsigned)(a.x_blocks + ceil_div(a.w_total, kThreads))), dim3(kThreads), 0, st, a);
   if (vcnn_status e = check_launch("halo_split")) return e;
-  return launch_product(p, n, h, w, m, r, s, ph, pw, bias, nullptr, relu, x8_bufs, wf_bufs, st, y32, 0, sc);
+  return launch_product(p, n, h, w, m, r, s, ph, pw, bias, nullptr, relu, x8_bufs, wf_bufs, st, y32, 0, &sc, wgt, flipped, c);
 }
 
 // =========================================================================================================
@@ -1020,30 +1058,40 @@ __global__ __launch_bounds__(kThreads) void dy_fragments_tile_kernel(const bf16*
 }
 
 // The two re-laying passes of the kernel gradient for float operands as two f16 terms each (split_f16.h), in the layouts
-// above, one plane per term; block 0 leaves the operand's exponent for the product kernel.
+// above, one plane per term; block 0 leaves the operand's scale for the product kernel.
 __global__ __launch_bounds__(kThreads) void interleave_images_split_kernel(const float* __restrict__ x,
                                                                            uint4* __restrict__ x8n, int64_t term, int N,
                                                                            int64_t CHW, int64_t total,
-                                                                           SplitScales* __restrict__ sc, int operand) {
-  const int e = split_exponent(sc->partial[operand]);
+                                                                           SplitScales sc) {
+  const uint32_t largest = split_max(sc.partial[0], sc.blocks);
+  const int e = split_exponent(largest);
   const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   if (i == 0) {
-    sc->exponent[operand] = e;
+    note_scale(sc, 0, 0, largest);
     x8n[total] = make_uint4(0u, 0u, 0u, 0u);
   }
-  if (i >= total) return;
-  const int64_t pos = i % CHW;
-  const int ng = (int)(i / CHW);
-  float f[8];
+  int small = 0;
+  if (i < total) {
+    const int64_t pos = i % CHW;
+    const int ng = (int)(i / CHW);
+    float f[8];
 #pragma unroll
-  for (int i8 = 0; i8 < 8; ++i8) f[i8] = x[ng * 8 + i8 < N ? (int64_t)(ng * 8 + i8) * CHW + pos : 0];
-  uint32_t v[8];
+    for (int i8 = 0; i8 < 8; ++i8) f[i8] = x[ng * 8 + i8 < N ? (int64_t)(ng * 8 + i8) * CHW + pos : 0];
+    uint32_t v[8];
+    SmallElements elements(e);
 #pragma unroll
-  for (int i8 = 0; i8 < 8; ++i8) v[i8] = ng * 8 + i8 < N ? split_f16(f[i8], e) : 0u;
-  uint4 hi, lo;
-  pack_terms(v, &hi, &lo);
-  x8n[i] = hi;
-  x8n[i + term] = lo;
+    for (int i8 = 0; i8 < 8; ++i8) {
+      if (ng * 8 + i8 >= N) f[i8] = 0.f;
+      v[i8] = split_f16(f[i8], e);
+      elements.take(f[i8]);
+    }
+    small = elements.count(f);
+    uint4 hi, lo;
+    pack_terms(v, &hi, &lo);
+    x8n[i] = hi;
+    x8n[i + term] = lo;
+  }
+  note_small(sc, 0, 0, small);
 }
 
 // (as dy_fragments_tile_kernel, 32 pixels at a time: an element takes four bytes of the tile, its two terms.  The pitch
@@ -1052,11 +1100,12 @@ static constexpr int kSplitFragPixels = 32, kSplitFragPitch = 33;
 __global__ __launch_bounds__(kThreads) void dy_fragments_split_kernel(const float* __restrict__ dy, uint4* __restrict__ dyf,
                                                                       int64_t term, int N, int M, int P, int MT, int runs,
                                                                       int bp, int uch, int uchunks,
-                                                                      SplitScales* __restrict__ sc, int operand) {
+                                                                      SplitScales sc) {
   __shared__ uint32_t tile[8 * 32 * kSplitFragPitch];
-  const int e = split_exponent(sc->partial[operand]);
+  const uint32_t largest = split_max(sc.partial[1], kAbsMaxBlocks);
+  const int e = split_exponent(largest);
   const int tid = threadIdx.x;
-  if (blockIdx.x == 0 && tid == 0) sc->exponent[operand] = e;
+  if (blockIdx.x == 0 && tid == 0) note_scale(sc, 1, 0, largest);
   int b = blockIdx.x;
   const int uc = b % uchunks;
   b /= uchunks;
@@ -1075,12 +1124,15 @@ __global__ __launch_bounds__(kThreads) void dy_fragments_split_kernel(const floa
       const int img = min(ng * 8 + (row >> 5), N - 1), m = min(mt * 32 + (row & 31), M - 1);
       v[k] = dy[((int64_t)img * M + m) * P + (pixel_ok ? p : 0)];
     }
+    SmallElements elements(e);
 #pragma unroll
     for (int k = 0; k < 32; ++k) {
       const int row = (tid >> 5) + 8 * k;
-      const bool ok = pixel_ok && ng * 8 + (row >> 5) < N && mt * 32 + (row & 31) < M;
-      tile[row * kSplitFragPitch + (tid & 31)] = ok ? split_f16(v[k], e) : 0u;
+      if (!(pixel_ok && ng * 8 + (row >> 5) < N && mt * 32 + (row & 31) < M)) v[k] = 0.f;
+      tile[row * kSplitFragPitch + (tid & 31)] = split_f16(v[k], e);
+      elements.take(v[k]);
     }
+    note_small(sc, 1, 0, elements.count(v));
   }
   __syncthreads();
   const int ml = tid & 31, ul = tid >> 5;
@@ -1106,7 +1158,8 @@ struct FilterBf16Args {
   const uint4* dyf;   // [ng][mt][run][step][64 lanes] fragments
   int64_t x8n_term;   // TERMS > 1: distance between the terms of x8n, and of dyf, in 16-byte words
   int64_t dyf_term;
-  const int32_t* exponent;  // TERMS = 2: the two operands' scales
+  const int32_t* exponent[2];  // TERMS = 2: the two operands' scales
+  const uint32_t* declined;    // TERMS = 2: nonzero: left to the float kernel
   float* out;         // [splits][m][K]
   int c, h, w, m, r, s, ph, pw, oh, ow;
   int K;              // c*r*s
@@ -1128,6 +1181,7 @@ __global__ __launch_bounds__(kThreads, 2) void filter_grad_bf16_kernel(FilterBf1
   using Split = SplitTerms<TERMS>;
   constexpr int PAIRS = Split::PAIRS;
   constexpr int BM = 32 * TM * WAVES_M, WN = 32 * TN, BN = WN * WAVES_N;
+  if (TERMS == 2 && *a.declined) return;
   extern __shared__ uint4 smem16[];
   int* const tbl = reinterpret_cast<int*>(smem16);  // [uch], per slab of 8 pixels: [half][4]
   uint4* const hbuf = smem16 + a.uch / 4;           // nbuf x TERMS x [ccs][nr][wp], each padded to hpos positions
@@ -1382,7 +1436,7 @@ __global__ __launch_bounds__(kThreads, 2) void filter_grad_bf16_kernel(FilterBf1
     if (wave_k != 0) return;
   }
 
-  const int descale = TERMS == 2 ? -(a.exponent[0] + a.exponent[1]) : 0;
+  const int descale = TERMS == 2 ? -(*a.exponent[0] + *a.exponent[1]) : 0;
   float* dst = a.out + (int64_t)blockIdx.y * a.m * a.K;
 #pragma unroll
   for (int ni = 0; ni < TN; ++ni) {
@@ -1573,14 +1627,14 @@ static vcnn_status relay_dy(const FilterGradBf16Plan& p, const ConvGeom& g, cons
 // the product on re-laid operands (g flattened), slices summed into dw (added to its contents when `accumulate`)
 static vcnn_status launch_filter_product(const FilterGradBf16Plan& p, const ConvGeom& g, float* dw, const void* x8n_buf,
                                          const void* dyf_buf, float* partial, hipStream_t st, int accumulate,
-                                         const SplitScales* sc = nullptr) {
+                                         const SplitScales* sc = nullptr, const OtherSlices& other = {}) {
   const uint4* x8n = (const uint4*)x8n_buf;
   const int64_t chw = (int64_t)g.c * g.h * g.w;
   FilterBf16Args a{};
   // accumulate: dw += the product (the slice sum takes dw as its addend); the workspace then holds at least one slice
   a.x8n = x8n, a.zero = x8n + (int64_t)p.ngroups * chw, a.dyf = (const uint4*)dyf_buf;
   a.x8n_term = (int64_t)(p.x8n_bytes / 16), a.dyf_term = (int64_t)(p.dyf_bytes / 16);  // (read by the split forms only)
-  a.exponent = sc ? sc->exponent : nullptr;
+  if (sc) a.exponent[0] = sc->exponent[0], a.exponent[1] = sc->exponent[1], a.declined = sc->any;
   a.out = (p.splits > 1 || accumulate) ? partial : dw;
   a.c = g.c, a.h = g.h, a.w = g.w, a.m = g.k, a.r = g.r, a.s = g.s, a.ph = g.ph, a.pw = g.pw, a.oh = g.oh, a.ow = g.ow;
   a.K = (int)g.K;
@@ -1602,10 +1656,10 @@ static vcnn_status launch_filter_product(const FilterGradBf16Plan& p, const Conv
   else if (p.tn == 4) launch_filter_tn<4>(a, p.waves_m, p.tm, tiles, (unsigned)p.splits, p.lds_bytes, st);
   else launch_filter_tn<5>(a, p.waves_m, p.tm, tiles, (unsigned)p.splits, p.lds_bytes, st);
   if (vcnn_status e = check_launch("filter_grad_bf16")) return e;
-  if (p.splits == 1 && !accumulate) return VCNN_OK;
   if (accumulate)  // "bias" of element i = dw[i]
-    return launch_sum_slices(partial, dw, dw, VCNN_F32, g.M * g.K, p.splits, 1, (int)(g.M * g.K), 0, st);
-  return launch_sum_slices(partial, nullptr, dw, VCNN_F32, g.M * g.K, p.splits, 1, 1, 0, st);
+    return launch_sum_slices(partial, dw, dw, VCNN_F32, g.M * g.K, p.splits, 1, (int)(g.M * g.K), 0, st, other);
+  if (p.splits == 1 && other.splits == 0) return VCNN_OK;
+  return launch_sum_slices(partial, nullptr, dw, VCNN_F32, g.M * g.K, p.splits > 1 ? p.splits : 0, 1, 1, 0, st, other);
 }
 
 vcnn_status launch_filter_grad_bf16_prepared(const FilterGradBf16Plan& p, const ConvGeom& g0, const void* x, const void* dy,
@@ -1635,22 +1689,26 @@ vcnn_status launch_filter_grad_bf16_terms(const FilterGradBf16Plan& p, const Con
 
 // Two-term form (p planned with terms = 2) of a float layer: x8n_bufs / dyf_bufs take the two re-laid terms of x and dy,
 // `sc` their scales (partial maxima of x in slot 0, of dy in slot 1), `partial` the slices (at least one with `accumulate`:
-// dw += the product).
+// dw += the product).  dw holds nothing of use once an operand is declined, until `behind`, the float kernel of the whole
+// gradient, has run: given with the last part, it goes in front of this product, and the slice sum takes either's slices.
 vcnn_status launch_filter_grad_f16x2(const FilterGradBf16Plan& p, const ConvGeom& g0, const float* x, const float* dy,
-                                     float* dw, SplitScales* sc, void* x8n_bufs, void* dyf_bufs, float* partial,
-                                     hipStream_t st, int accumulate) {
+                                     float* dw, const SplitScales& sc, void* x8n_bufs, void* dyf_bufs, float* partial,
+                                     hipStream_t st, int accumulate, const FilterBehind* behind) {
   const ConvGeom g = flatten_pointwise(g0);
   const int64_t chw = (int64_t)g.c * g.h * g.w;
   const int64_t total = (int64_t)p.ngroups * chw;
   hipLaunchKernelGGL(interleave_images_split_kernel, dim3((unsigned)ceil_div(total, kThreads)), dim3(kThreads), 0, st, x,
-                     (uint4*)x8n_bufs, (int64_t)(p.x8n_bytes / 16), g.n, chw, total, sc, 0);
+                     (uint4*)x8n_bufs, (int64_t)(p.x8n_bytes / 16), g.n, chw, total, sc);
   if (vcnn_status e = check_launch("interleave_images_split")) return e;
   const int uchunks = (int)ceil_div(p.uch, kSplitFragPixels);
   const int64_t blocks = (int64_t)p.ngroups * p.mt_total * p.runs * uchunks;
   hipLaunchKernelGGL(dy_fragments_split_kernel, dim3((unsigned)blocks), dim3(kThreads), 0, st, dy, (uint4*)dyf_bufs,
-                     (int64_t)(p.dyf_bytes / 16), g.n, (int)g.M, (int)g.P, p.mt_total, p.runs, p.bp, p.uch, uchunks, sc, 1);
+                     (int64_t)(p.dyf_bytes / 16), g.n, (int)g.M, (int)g.P, p.mt_total, p.runs, p.bp, p.uch, uchunks, sc);
   if (vcnn_status e = check_launch("dy_fragments_split")) return e;
-  return launch_filter_product(p, g, dw, x8n_bufs, dyf_bufs, partial, st, accumulate, sc);
+  OtherSlices other{};
+  if (behind)
+    if (vcnn_status e = launch_filter_behind(*behind, dw, sc.declined(), st, &other)) return e;
+  return launch_filter_product(p, g, dw, x8n_bufs, dyf_bufs, partial, st, accumulate, &sc, other);
 }
 
 }  // namespace vcnn

@@ -24,6 +24,24 @@ struct ConvGeom {
   int64_t M, K, N;
 };
 
+// The images a two-term product leaves to the float kernel behind it (split_f16.h): words the re-laying passes write on
+// the device.  A float kernel that is given them (any != null) computes only those images.
+struct Declined {
+  const uint32_t* any;    // nonzero: at least one image
+  const uint32_t* all;    // nonzero: every image
+  const uint32_t* image;  // [image] nonzero: that one
+};
+__device__ __forceinline__ bool is_declined(const Declined& d, int n) { return (*d.all | d.image[n]) != 0; }
+__device__ __forceinline__ bool leave_image(const Declined& only, int n) { return only.any && !is_declined(only, n); }
+__device__ __forceinline__ bool leave_all(const Declined& only) { return only.any && *only.any == 0; }
+
+// Slices a sum takes in place of its own if a product was declined (splits = 0: there is nothing left to add then).
+struct OtherSlices {
+  const uint32_t* declined;  // given: the word of Declined that decides
+  const float* partial;
+  int splits;
+};
+
 // ---- unroll.hip ---------------------------------------------------------------------------------
 // dtype = element type of x and of the patch matrix (im2col); of dx (col2im, whose patch matrix is float)
 vcnn_status launch_im2col(const ConvGeom& g, int dtype, const void* x, void* col, hipStream_t st);
@@ -66,6 +84,8 @@ struct GemmArgs {
   const void* dact_ref;
   // optional, small products only: the row sums of A, sum_k A(i,k), written to row_sums[i]
   float* row_sums;
+  // optional, tiled kernel only (c_P > 0: columns are images of c_P): only the images a two-term product left to this one
+  Declined only;
 };
 vcnn_status launch_gemm_f32(const GemmArgs& a, hipStream_t st);
 // true if launch_gemm_f32 takes the small-product kernel (one 32 x 32 tile per block, contraction split over waves)
@@ -79,7 +99,8 @@ int bwd_filter_splits(const ConvGeom& g);
 size_t bwd_filter_partial_bytes(const ConvGeom& g);
 // xin != nullptr (unpadded 1 x 1 layers only): the patch matrix is the input itself, read in place; col is unused
 vcnn_status launch_bwd_filter_gemm_f32(const ConvGeom& g, int dtype, const void* dy, const void* col, const void* xin,
-                                       float* dw, float* partial, hipStream_t st);
+                                       float* dw, float* partial, hipStream_t st, const Declined& only = {});
+// (with `only` the slices are left to the caller; so are those of launch_conv_halo_filter)
 
 // ---- direct.hip ---------------------------------------------------------------------------------
 // Generic correlation out[n][o][y][x] = sum_{i,r,s} wgt(o,i,r,s) * in[n][i][y+r-py][x+s-px] used by the
@@ -120,7 +141,7 @@ struct HaloPlan {
 bool conv_halo_plan(int n, int c, int h, int w, int m, int r, int s, int ph, int pw, HaloPlan* p);
 vcnn_status launch_conv_halo(const HaloPlan& p, int dtype, int n, int c, int h, int w, int m, int r, int s, int ph,
                              int pw, const void* x, const void* wgt, const float* bias, void* y, int relu,
-                             hipStream_t st);
+                             hipStream_t st, const Declined& only = {});
 struct HaloFilterPlan {
   int bm, bnk;       // block tile: output maps x kernel-matrix columns
   int bp;            // output pixels per staged run
@@ -134,7 +155,7 @@ struct HaloFilterPlan {
 bool conv_halo_filter_plan(const ConvGeom& g, HaloFilterPlan* p);
 // dbias may be null; with p.bias_column it is produced by the same launches, otherwise the caller computes it
 vcnn_status launch_conv_halo_filter(const HaloFilterPlan& p, int dtype, const ConvGeom& g, const void* x, const void* dy,
-                                    float* dw, float* dbias, float* partial, hipStream_t st);
+                                    float* dw, float* dbias, float* partial, hipStream_t st, const Declined& only = {});
 struct FewColsPlan {
   int tm, tn;        // 32-row / 32-column tiles of the whole M x K result
   int nr, wp;
@@ -239,15 +260,31 @@ vcnn_status launch_filter_grad_bf16_terms(const FilterGradBf16Plan& p, const Con
 
 // ---- two f16 terms per float (split_f16.h): the float products of large layers, on the same kernels ------------------
 struct SplitScales;
-// partial maxima of the two operands (either may be empty: its exponent is then left alone)
-vcnn_status launch_absmax(const float* a, int64_t na, const float* b, int64_t nb, SplitScales* sc, hipStream_t st);
+// The float kernel of a kernel gradient, behind the two-term product: of the whole batch, whatever parts that takes.
+struct FilterBehind {
+  const ConvGeom* g;
+  const float* x;
+  const float* dy;
+  const HaloFilterPlan* halo;  // null: the plain product of a 1 x 1 layer
+  float* workspace;
+};
+// Enqueues it; it runs if anything is declined, and leaves dw, or slices for the caller's sum.
+vcnn_status launch_filter_behind(const FilterBehind& b, float* dw, const Declined& only, hipStream_t st, OtherSlices* other);
+// Bytes of the scales of a product of `images` images, and their layout in the workspace for `images_at_once` of them (a
+// part of the batch); operand 0 has `per_image` floats per image and scale, operand 1 `others`.
+size_t split_scales_bytes(int images);
+SplitScales split_scales(void* workspace, int images, int images_at_once, int64_t per_image, int64_t others);
+Declined split_declined(const void* workspace, int images);
+// partial maxima of the images of a and of b (nb = 0: b's scale and words are left as they are); `first`: of the call
+vcnn_status launch_absmax(const float* a, int images, int64_t per_image, const float* b, int64_t nb, const SplitScales& sc,
+                          bool first, hipStream_t st);
 vcnn_status launch_conv_halo_f16x2(const HaloBf16Plan& p, int n, int c, int h, int w, int m, int r, int s, int ph, int pw,
                                    const float* x, const float* wgt, int64_t w_so, int64_t w_si, int flip,
-                                   const float* bias, float* y32, int relu, SplitScales* sc, void* x8_bufs, void* wf_bufs,
-                                   hipStream_t st);
+                                   const float* bias, float* y32, int relu, const SplitScales& sc, void* x8_bufs, void* wf_bufs,
+                                   float* flipped, hipStream_t st);
 vcnn_status launch_filter_grad_f16x2(const FilterGradBf16Plan& p, const ConvGeom& g, const float* x, const float* dy,
-                                     float* dw, SplitScales* sc, void* x8n_bufs, void* dyf_bufs, float* partial,
-                                     hipStream_t st, int accumulate);
+                                     float* dw, const SplitScales& sc, void* x8n_bufs, void* dyf_bufs, float* partial,
+                                     hipStream_t st, int accumulate, const FilterBehind* behind);
 // ---- split_f16.hip: which float layers take them, and the scales -------------------------------------------------------
 // One operand into fragment order (frag_product.h): `images` matrices of `rows` x `depth` at distance s_z, strides s_row
 // and s_k (one of them 1), padded to `tiles` row tiles of 32 and `steps` steps of 16; terms `term` 16-byte words apart.
@@ -259,8 +296,9 @@ struct FragmentsArgs {
   int rows, depth;
   int64_t s_row, s_k, s_z;
   int tiles, images, steps, terms, operand;
+  int per_image;  // the operand has a scale per image
 };
-vcnn_status launch_fragments(const FragmentsArgs& f, SplitScales* sc, hipStream_t st);
+vcnn_status launch_fragments(const FragmentsArgs& f, const SplitScales& sc, hipStream_t st);
 // ---- pointwise_f16.hip: the unpadded 1 x 1 layers in float, both operands in fragment order ---------------------------------
 struct PointwiseF16Plan {
   int tiles_i, tiles_j;  // 128-row tiles of the two operands (kernel gradient: maps, channels; else rows, pixels of a sample)
@@ -274,7 +312,7 @@ bool pointwise_f16_plan(const ConvGeom& g, int pass, PointwiseF16Plan* p);
 vcnn_status launch_pointwise_f16(const PointwiseF16Plan& p, const ConvGeom& g, int pass, const float* w, const float* x,
                                  const float* bias, float* y, int relu, void* workspace, hipStream_t st);
 vcnn_status launch_pointwise_f16_filter(const PointwiseF16Plan& p, const ConvGeom& g, const float* x, const float* dy, float* dw,
-                                        void* workspace, hipStream_t st);
+                                        void* workspace, const FilterBehind& behind, hipStream_t st);
 
 struct F16x2Plan {
   HaloBf16Plan fwd;           // forward pass, and the input gradient as a correlation, of `images` images
@@ -290,9 +328,9 @@ bool conv_f16x2_plan(const ConvGeom& g, int pass, size_t budget, F16x2Plan* p);
 vcnn_status launch_conv_f16x2_fwd(const F16x2Plan& p, const ConvGeom& g, const float* x, const float* w, const float* bias,
                                   float* y, int relu, void* workspace, hipStream_t st);
 vcnn_status launch_conv_f16x2_bwd_data(const F16x2Plan& p, const ConvGeom& g, const float* w, const float* dy, float* dx,
-                                       void* workspace, hipStream_t st);
+                                       float* flipped, void* workspace, hipStream_t st);
 vcnn_status launch_conv_f16x2_filter(const F16x2Plan& p, const ConvGeom& g, const float* x, const float* dy, float* dw,
-                                     void* workspace, hipStream_t st);
+                                     void* workspace, const FilterBehind& behind, hipStream_t st);
 
 // ---- split_bf16.hip: fp32 products of large layers as sums of bf16 products (on request only) ------------------------
 struct SplitPlan {
@@ -357,7 +395,7 @@ vcnn_status launch_conv_fft(const FftPlan& p, int dtype, const ConvGeom& g, cons
 
 // out[i] = act(bias[(i / plane) % maps] + sum_s partial[s][i]), slices added in ascending order (bias nullable)
 vcnn_status launch_sum_slices(const float* partial, const float* bias, void* out, int out_dtype, int64_t count,
-                              int splits, int64_t plane, int maps, int relu, hipStream_t st);
+                              int splits, int64_t plane, int maps, int relu, hipStream_t st, const OtherSlices& other = {});
 // partial is [splits][rows][cols + 1]: main[r][c] = sum_s partial[s][r][c] for c < cols, last[r] = sum_s partial[s][r][cols]
 vcnn_status launch_sum_slices_split(const float* partial, float* main, float* last, int64_t rows, int cols, int splits,
                                     hipStream_t st);

@@ -38,7 +38,12 @@ struct FoldArgs {
   int wreg;         // region row width = ow + s - 1 (input columns -pw .. ow + s - 2 - pw)
   int dact;         // second pass, VCNN_ACT_*: dx is multiplied by sigma'(.) evaluated from dact_ref (shape and type of dx)
   const void* dact_ref;
+  Declined declined;  // given (any != null): the images a two-term product leaves to the float kernel; ...
+  int redo;           // ... 1: this is that kernel and computes those alone, 0: this is the product and leaves them out
 };
+__device__ __forceinline__ bool fold_leaves(const FoldArgs& a, int n) {
+  return a.declined.any && is_declined(a.declined, n) != (a.redo != 0);
+}
 
 // Geometry of the region tile (it, jt) folds into: channels c_lo .. c_lo + nch - 1, region rows = input rows
 // h_lo .. h_lo + nrows - 1 (may stick out of the image; those rows are never read back).
@@ -185,6 +190,7 @@ __global__ __launch_bounds__(kThreads, 4) void bwd_data_fold_kernel(FoldArgs a) 
   int it, tj;
   fold_block_tile<kPatchJ>(a, &it, &tj);
   const int n = tj / a.tiles_j, jt = tj - n * a.tiles_j;
+  if (fold_leaves(a, n)) return;
   const int i0 = it * BM, j0 = jt * BN;
   const int wm0 = (wave & 1) * WM, wn0 = (wave >> 1) * WN;
   const T* gB = static_cast<const T*>(a.dy) + (int64_t)n * a.m * a.P;
@@ -279,7 +285,8 @@ struct FoldFragArgs {
   const uint4* df;   // [n][4 tiles_j][steps][64]
   int64_t wf_term, df_term;  // distance between the terms, in 16-byte words
   int steps;         // of 16 output maps, a multiple of the slab's
-  const int32_t* exponent;   // TERMS = 2: the scales of dy and w
+  const int32_t* image_exponent;  // TERMS = 2: the scales of dy's images ...
+  const int32_t* exponent;        // ... and of w
 };
 
 template <int TERMS, bool MI_INDEP>
@@ -289,6 +296,7 @@ __global__ __launch_bounds__(kThreads, TERMS == 2 ? 2 : 4) void bwd_data_fold_fr
   int it, tj;
   fold_block_tile<kPatchI>(a.f, &it, &tj);
   const int n = tj / a.f.tiles_j, jt = tj - n * a.f.tiles_j;
+  if (TERMS == 2 && fold_leaves(a.f, n)) return;
   constexpr int STEPS = FragSlab<TERMS>::STEPS;
   const uint4* const src_a = a.wf + ((int64_t)(4 * it + wave) * a.steps) * 64 + lane;
   const uint4* const src_b = a.df + (((int64_t)n * a.f.tiles_j + jt) * 4 + wave) * a.steps * 64 + lane;
@@ -296,7 +304,7 @@ __global__ __launch_bounds__(kThreads, TERMS == 2 ? 2 : 4) void bwd_data_fold_fr
   frag_product<TERMS>(a.steps / STEPS, reinterpret_cast<uint4*>(smem4), a.wf_term, a.df_term,
                       [&](int sl) { return src_a + sl * (STEPS * 64); }, [&](int sl) { return src_b + sl * (STEPS * 64); }, acc);
   // the slabs are read: the region takes their place
-  const int descale = TERMS == 2 ? -(a.exponent[0] + a.exponent[1]) : 0;
+  const int descale = TERMS == 2 ? -(a.image_exponent[n] + *a.exponent) : 0;
   fold_tile<MI_INDEP>(a.f, n, it, jt, acc, reinterpret_cast<float*>(smem4), descale);
 }
 
@@ -307,13 +315,16 @@ __global__ __launch_bounds__(kThreads, TERMS == 2 ? 2 : 4) void bwd_data_fold_fr
 template <int TERMS, bool K_CONTIG>
 __global__ __launch_bounds__(kThreads) void fragments_kernel(const void* __restrict__ src, uint4* __restrict__ dst,
                                                              int64_t term, int rows, int depth, int64_t s_row, int64_t s_k,
-                                                             int64_t s_z, int steps, SplitScales* __restrict__ sc,
-                                                             int operand) {
+                                                             int64_t s_z, int steps, SplitScales sc,
+                                                             int operand, int per_image) {
   static_assert(TERMS == 2 || !K_CONTIG, "bfloat16 operands: rows contiguous only");
   int e = 0;
+  const int image = per_image ? (int)blockIdx.z : 0;
   if constexpr (TERMS == 2) {
-    e = split_exponent(sc->partial[operand]);
-    if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x == 0) sc->exponent[operand] = e;
+    const uint32_t largest = operand ? split_max(sc.partial[1], kAbsMaxBlocks)
+                                     : split_max(sc.partial[0] + (int64_t)image * sc.blocks, sc.blocks);
+    e = split_exponent(largest);
+    if (blockIdx.x == 0 && blockIdx.y == 0 && (int)blockIdx.z == image && threadIdx.x == 0) note_scale(sc, operand, image, largest);
   }
   const int lane = threadIdx.x & 63, step = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
   if (step >= steps) return;
@@ -324,6 +335,7 @@ __global__ __launch_bounds__(kThreads) void fragments_kernel(const void* __restr
   if constexpr (TERMS == 2) {
     const float* const p = static_cast<const float*>(src) + from;
     float f[8];
+    SmallElements small(e);
     if (K_CONTIG && k0 + 8 <= depth) {
       const float4 a = ld4_dword_aligned(p + k0), b = ld4_dword_aligned(p + k0 + 4);
       f[0] = a.x, f[1] = a.y, f[2] = a.z, f[3] = a.w, f[4] = b.x, f[5] = b.y, f[6] = b.z, f[7] = b.w;
@@ -332,11 +344,16 @@ __global__ __launch_bounds__(kThreads) void fragments_kernel(const void* __restr
       for (int j = 0; j < 8; ++j) f[j] = p[min(k0 + j, depth - 1) * s_k];
     }
 #pragma unroll
-    for (int j = 0; j < 8; ++j) v[j] = row < rows && k0 + j < depth ? split_f16(f[j], e) : 0u;
+    for (int j = 0; j < 8; ++j) {
+      if (row >= rows || k0 + j >= depth) f[j] = 0.f;
+      v[j] = split_f16(f[j], e);
+      small.take(f[j]);
+    }
     uint4 hi, lo;
     pack_terms(v, &hi, &lo);
     dst[to] = hi;
     dst[to + term] = lo;
+    note_small(sc, operand, image, small.count(f));
   } else {
     const bf16* const p = static_cast<const bf16*>(src) + from;
 #pragma unroll
@@ -348,11 +365,11 @@ __global__ __launch_bounds__(kThreads) void fragments_kernel(const void* __restr
   }
 }
 
-vcnn_status launch_fragments(const FragmentsArgs& f, SplitScales* sc, hipStream_t st) {
+vcnn_status launch_fragments(const FragmentsArgs& f, const SplitScales& sc, hipStream_t st) {
   const dim3 grid((unsigned)ceil_div(f.steps, kThreads / 64), (unsigned)f.tiles, (unsigned)f.images);
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, st, f.src, (uint4*)f.dst, f.term, f.rows, f.depth, f.s_row, f.s_k,
-                       f.s_z, f.steps, sc, f.operand);
+                       f.s_z, f.steps, sc, f.operand, f.per_image);
   };
   if (f.terms == 1) go(fragments_kernel<1, false>);
   else if (f.s_k == 1) go(fragments_kernel<2, true>);
@@ -466,7 +483,7 @@ bool bwd_data_fold_frag_plan(const ConvGeom& whole, int terms, size_t budget, Fo
     p->images = images;
     p->df_bytes = align256((size_t)images * 4 * p->fold.tiles_j * frag);
     p->partial_bytes = align256((size_t)images * p->fold.tiles_i * p->fold.tiles_j * p->fold.rsz * sizeof(float));
-    p->workspace_bytes = kSplitScalesBytes + terms * (p->wf_bytes + p->df_bytes) + p->partial_bytes;
+    p->workspace_bytes = (terms == 2 ? split_scales_bytes(whole.n) : 0) + terms * (p->wf_bytes + p->df_bytes) + p->partial_bytes;
     if (p->workspace_bytes > budget) continue;
     // per CU: the tile's products at the rate the loop holds with operands that change (half the nominal one), and the
     // part of the fold (LDS) that the other resident block's products do not cover
@@ -487,24 +504,18 @@ static vcnn_status launch_fold_gather(const FoldArgs& a, hipStream_t st) {
   return check_launch("fold_gather");
 }
 
-vcnn_status launch_bwd_data_fold(const FoldPlan& p, int dtype, const ConvGeom& g, const void* w, const void* dy, void* dx,
-                                 float* partial, hipStream_t st, int dact, const void* dact_ref) {
-  FoldArgs a{};
-  a.w = w, a.dy = dy, a.partial = partial, a.dx = dx;
-  a.dact = dact_ref ? dact : 0, a.dact_ref = dact_ref;
-  a.n = g.n, a.c = g.c, a.h = g.h, a.wd = g.w, a.m = (int)g.M, a.r = g.r, a.s = g.s, a.ph = g.ph, a.pw = g.pw;
-  a.oh = g.oh, a.ow = g.ow, a.P = (int)g.P, a.K = (int)g.K;
-  a.tiles_i = p.tiles_i, a.tiles_j = p.tiles_j, a.rsz = p.rsz, a.wreg = p.wreg;
-  const dim3 grid((unsigned)((int64_t)g.n * p.tiles_i * p.tiles_j)), block(kThreads);
+// the tiles' products folded into their regions
+static vcnn_status launch_fold_product(const FoldPlan& p, int dtype, const FoldArgs& a, bool mi_indep, hipStream_t st) {
+  const void *const w = a.w, *const dy = a.dy;
+  const dim3 grid((unsigned)((int64_t)a.n * p.tiles_i * p.tiles_j)), block(kThreads);
   const bool bf = dtype == VCNN_BF16;
-  const bool vec = bf ? g.K % 4 == 0 && group_aligned<bf16>(w) : g.K >= 4 && (reinterpret_cast<uintptr_t>(w) & 3) == 0;
-  const bool mi_indep = rows_independent(g);
+  const bool vec = bf ? a.K % 4 == 0 && group_aligned<bf16>(w) : a.K >= 4 && (reinterpret_cast<uintptr_t>(w) & 3) == 0;
   auto go = [&](auto kernel) {
     if (p.lds_bytes > 48 * 1024)  // opt in to more than the default dynamic LDS limit (idempotent, host-side only)
       (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024);
     hipLaunchKernelGGL(kernel, grid, block, p.lds_bytes, st, a);
   };
-  const bool bvec = !bf && g.P >= 4 && (reinterpret_cast<uintptr_t>(dy) & 3) == 0;
+  const bool bvec = !bf && a.P >= 4 && (reinterpret_cast<uintptr_t>(dy) & 3) == 0;
   if (bf) {
     if (vec && mi_indep) go(bwd_data_fold_kernel<true, false, true, bf16>);
     else if (vec) go(bwd_data_fold_kernel<true, false, false, bf16>);
@@ -518,14 +529,25 @@ vcnn_status launch_bwd_data_fold(const FoldPlan& p, int dtype, const ConvGeom& g
     else if (vec) go(bwd_data_fold_kernel<true, false, false, float>);
     else go(bwd_data_fold_kernel<false, false, false, float>);
   }
-  if (vcnn_status s = check_launch("bwd_data_fold")) return s;
-  return bf ? launch_fold_gather<bf16>(a, st) : launch_fold_gather<float>(a, st);
+  return check_launch("bwd_data_fold");
+}
+
+vcnn_status launch_bwd_data_fold(const FoldPlan& p, int dtype, const ConvGeom& g, const void* w, const void* dy, void* dx,
+                                 float* partial, hipStream_t st, int dact, const void* dact_ref) {
+  FoldArgs a{};
+  a.w = w, a.dy = dy, a.partial = partial, a.dx = dx;
+  a.dact = dact_ref ? dact : 0, a.dact_ref = dact_ref;
+  a.n = g.n, a.c = g.c, a.h = g.h, a.wd = g.w, a.m = (int)g.M, a.r = g.r, a.s = g.s, a.ph = g.ph, a.pw = g.pw;
+  a.oh = g.oh, a.ow = g.ow, a.P = (int)g.P, a.K = (int)g.K;
+  a.tiles_i = p.tiles_i, a.tiles_j = p.tiles_j, a.rsz = p.rsz, a.wreg = p.wreg;
+  if (vcnn_status s = launch_fold_product(p, dtype, a, rows_independent(g), st)) return s;
+  return dtype == VCNN_BF16 ? launch_fold_gather<bf16>(a, st) : launch_fold_gather<float>(a, st);
 }
 
 vcnn_status launch_bwd_data_fold_frag(const FoldFragPlan& p, const ConvGeom& g, const void* w, const void* dy, void* dx,
                                       void* workspace, hipStream_t st, int dact, const void* dact_ref) {
-  SplitScales* const sc = (SplitScales*)workspace;
-  char* const wf = (char*)workspace + kSplitScalesBytes;
+  const bool split = p.terms == 2;
+  char* const wf = (char*)workspace + (split ? split_scales_bytes(g.n) : 0);
   char* const df = wf + p.terms * p.wf_bytes;
   FoldFragArgs a{};
   a.f.partial = (float*)(df + p.terms * p.df_bytes);
@@ -534,16 +556,20 @@ vcnn_status launch_bwd_data_fold_frag(const FoldFragPlan& p, const ConvGeom& g, 
   a.f.oh = g.oh, a.f.ow = g.ow, a.f.P = (int)g.P, a.f.K = (int)g.K;
   a.f.tiles_i = p.fold.tiles_i, a.f.tiles_j = p.fold.tiles_j, a.f.rsz = p.fold.rsz, a.f.wreg = p.fold.wreg;
   a.wf = (const uint4*)wf, a.df = (const uint4*)df, a.wf_term = (int64_t)(p.wf_bytes / 16), a.df_term = (int64_t)(p.df_bytes / 16);
-  a.steps = p.steps, a.exponent = sc->exponent;
-  const size_t e = p.terms == 2 ? sizeof(float) : sizeof(bf16);
+  a.steps = p.steps;
+  const size_t e = split ? sizeof(float) : sizeof(bf16);
   const bool indep = rows_independent(g);
-  FragmentsArgs of_dy{nullptr, df, a.df_term, (int)g.P, (int)g.M, 1, g.P, g.M * g.P, 4 * p.fold.tiles_j, 0, p.steps, p.terms, 0};
-  const FragmentsArgs of_w{w, wf, a.wf_term, (int)g.K, (int)g.M, 1, g.K, 0, 4 * p.fold.tiles_i, 1, p.steps, p.terms, 1};
+  FragmentsArgs of_dy{nullptr, df, a.df_term, (int)g.P, (int)g.M, 1, g.P, g.M * g.P, 4 * p.fold.tiles_j, 0, p.steps, p.terms, 0, 1};
+  const FragmentsArgs of_w{w, wf, a.wf_term, (int)g.K, (int)g.M, 1, g.K, 0, 4 * p.fold.tiles_i, 1, p.steps, p.terms, 1, 0};
   for (int n0 = 0; n0 < g.n; n0 += p.images) {
     const int images = std::min(p.images, g.n - n0);
     const char* const d = (const char*)dy + (size_t)n0 * g.M * g.P * e;
-    if (p.terms == 2)  // (the kernel matrix keeps its scale and its fragments from the first part)
-      if (vcnn_status s = launch_absmax((const float*)d, (int64_t)images * g.M * g.P, (const float*)w, n0 ? 0 : g.M * g.K, sc, st)) return s;
+    SplitScales sc{};
+    if (split) {  // (the kernel matrix keeps its scale and its fragments from the first part)
+      sc = split_scales(workspace, g.n, images, g.M * g.P, g.M * g.K).from(n0);
+      if (vcnn_status s = launch_absmax((const float*)d, images, g.M * g.P, (const float*)w, n0 ? 0 : g.M * g.K, sc, n0 == 0, st)) return s;
+      a.image_exponent = sc.exponent[0], a.exponent = sc.exponent[1], a.f.declined = sc.declined();
+    }
     of_dy.src = d, of_dy.images = images;
     if (vcnn_status s = launch_fragments(of_dy, sc, st)) return s;
     if (n0 == 0)
@@ -556,12 +582,17 @@ vcnn_status launch_bwd_data_fold_frag(const FoldFragPlan& p, const ConvGeom& g, 
       (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds_bytes);
       hipLaunchKernelGGL(kernel, grid, dim3(kThreads), p.lds_bytes, st, a);
     };
-    if (p.terms == 2 && indep) go(bwd_data_fold_frag_kernel<2, true>);
-    else if (p.terms == 2) go(bwd_data_fold_frag_kernel<2, false>);
+    if (split && indep) go(bwd_data_fold_frag_kernel<2, true>);
+    else if (split) go(bwd_data_fold_frag_kernel<2, false>);
     else if (indep) go(bwd_data_fold_frag_kernel<1, true>);
     else go(bwd_data_fold_frag_kernel<1, false>);
     if (vcnn_status s = check_launch("bwd_data_fold_frag")) return s;
-    if (vcnn_status s = p.terms == 2 ? launch_fold_gather<float>(a.f, st) : launch_fold_gather<bf16>(a.f, st)) return s;
+    if (split) {  // the regions of those images of the part that the terms do not carry: the float kernel's
+      FoldArgs behind = a.f;
+      behind.w = w, behind.dy = d, behind.redo = 1;
+      if (vcnn_status s = launch_fold_product(p.fold, VCNN_F32, behind, indep, st)) return s;
+    }
+    if (vcnn_status s = split ? launch_fold_gather<float>(a.f, st) : launch_fold_gather<bf16>(a.f, st)) return s;
   }
   return VCNN_OK;
 }

@@ -36,6 +36,7 @@ struct HaloArgs {
   int kch;            // taps per full chunk, padded to a multiple of BK
   int relu;
   int tw, tiles_x;    // tw > 0: a tile is a strip of BN / tw output rows x tw output columns (tiles_x strips side by side)
+  Declined only;      // given: only the images a two-term product left to this kernel
 };
 
 // Pixel q of a block's tile as a flat index into the sample's output plane (-1: outside it), and its position inside
@@ -102,6 +103,7 @@ __global__ __launch_bounds__(kThreads) void conv_halo_kernel(HaloArgs a) {
   const int tm = blockIdx.x % a.tiles_m;
   const int tj = blockIdx.x / a.tiles_m;
   const int n = tj / a.tiles_per_img;
+  if (leave_image(a.only, n)) return;
   const int tq = tj - n * a.tiles_per_img;
   const int p0 = a.tw ? 0 : tq * BN;
   const int oh_first = a.tw ? tq / a.tiles_x * (BN / a.tw) : p0 / a.ow;  // first output row and column of the tile
@@ -253,6 +255,7 @@ __global__ __launch_bounds__(kThreads) void conv_halo16_kernel(HaloArgs a) {
   const int tm = blockIdx.x % a.tiles_m;
   const int tj = blockIdx.x / a.tiles_m;
   const int n = tj / a.tiles_per_img;
+  if (leave_image(a.only, n)) return;
   const int tq = tj - n * a.tiles_per_img;
   const int p0 = a.tw ? 0 : tq * BN;
   const int oh_first = a.tw ? tq / a.tiles_x * (BN / a.tw) : p0 / a.ow;  // first output row and column of the tile
@@ -566,8 +569,9 @@ static void launch_halo16(const HaloArgs& a, const HaloPlan& p, bool vec, int dt
 
 vcnn_status launch_conv_halo(const HaloPlan& p, int dtype, int n, int c, int h, int w, int m, int r, int s, int ph,
                              int pw, const void* x, const void* wgt, const float* bias, void* y, int relu,
-                             hipStream_t st) {
+                             hipStream_t st, const Declined& only) {
   HaloArgs a{};
+  a.only = only;
   a.x = x, a.wgt = wgt, a.bias = bias, a.y = y;
   a.n = n, a.c = c, a.h = h, a.w = w, a.m = m, a.r = r, a.s = s, a.ph = ph, a.pw = pw;
   a.oh = h + 2 * ph - r + 1, a.ow = w + 2 * pw - s + 1;
@@ -625,6 +629,7 @@ struct HaloFilterArgs {
   int runs_per_split;
   int ccs;           // channels a block's column range can span
   int nr, wp;
+  Declined only;     // given: only if a two-term product left anything to this kernel
 };
 
 template <int BM, int BNK, int WM, int WN, int BK, bool VEC, typename T>
@@ -633,6 +638,7 @@ __global__ __launch_bounds__(kThreads) void conv_halo_filter_kernel(HaloFilterAr
   using LA = LdsTile<BM, BK, true>;
   using SA = Stager<BM, BK, kThreads, true, VEC>;
   constexpr int TM = WM / 32, TN = WN / 32;
+  if (leave_all(a.only)) return;
   extern __shared__ float4 smem4[];
   float* const As0 = reinterpret_cast<float*>(smem4);
   int* const pixoff = reinterpret_cast<int*>(As0 + 2 * LA::SIZE);  // [bp]
@@ -786,6 +792,7 @@ __global__ __launch_bounds__(kThreads) void conv_halo_filter16_kernel(HaloFilter
   using LA = LdsTile<BM, BK, true>;
   using SA = Stager<BM, BK, kThreads, true, VEC>;
   constexpr int TM = BM / 16, TN = WN / 16;
+  if (leave_all(a.only)) return;
   extern __shared__ float4 smem4[];
   float* const As0 = reinterpret_cast<float*>(smem4);
   int* const pixoff = reinterpret_cast<int*>(As0 + 2 * LA::SIZE);  // [bp]
@@ -1045,9 +1052,10 @@ static void launch_halo_filter16(const HaloFilterArgs& a, const HaloFilterPlan& 
 }
 
 vcnn_status launch_conv_halo_filter(const HaloFilterPlan& p, int dtype, const ConvGeom& g, const void* x, const void* dy,
-                                    float* dw, float* dbias, float* partial, hipStream_t st) {
+                                    float* dw, float* dbias, float* partial, hipStream_t st, const Declined& only) {
   const bool with_bias = p.bias_column && dbias;
   HaloFilterArgs a{};
+  a.only = only;
   a.x = x, a.dy = dy, a.out = (p.splits > 1 || with_bias) ? partial : dw;
   a.Kp = (int)g.K + (with_bias ? 1 : 0);
   a.n = g.n, a.c = g.c, a.h = g.h, a.w = g.w, a.m = g.k, a.r = g.r, a.s = g.s, a.ph = g.ph, a.pw = g.pw;
@@ -1068,7 +1076,7 @@ vcnn_status launch_conv_halo_filter(const HaloFilterPlan& p, int dtype, const Co
     launch_halo_filter<128, 128, 64, 64, 32>(a, p, vec, dtype, tiles, st);
   if (vcnn_status s = check_launch("conv_halo_filter")) return s;
   if (with_bias) return launch_sum_slices_split(partial, dw, dbias, g.M, (int)g.K, p.splits, st);
-  if (p.splits == 1) return VCNN_OK;
+  if (p.splits == 1 || only.any) return VCNN_OK;
   return launch_sum_slices(partial, nullptr, dw, VCNN_F32, g.M * g.K, p.splits, 1, 1, 0, st);
 }
 

@@ -259,13 +259,19 @@ __global__ __launch_bounds__(kThreads) void direct_few_out_kernel(DirectGeom g, 
   }
 }
 
+// The slices a sum takes: its own, or the float kernel's of a declined product (which has no addend); false: none.
+__device__ __forceinline__ bool choose_slices(const OtherSlices& other, const float** partial, int* splits, const float** bias) {
+  if (other.declined && *other.declined) *partial = other.partial, *splits = other.splits, *bias = nullptr;
+  return *splits > 0;
+}
+
 // out[idx] = act(bias[map(idx)] + sum_s partial[s][idx]), slices added in ascending order with four
 // independent loads in flight.
 template <typename TO>
-__global__ __launch_bounds__(kThreads) void sum_slices_kernel(const float* __restrict__ partial,
-                                                              const float* __restrict__ bias, TO* __restrict__ out,
+__global__ __launch_bounds__(kThreads) void sum_slices_kernel(const float* partial, const float* bias, TO* __restrict__ out,
                                                               int64_t count, int splits, int64_t plane, int maps,
-                                                              int relu) {
+                                                              int relu, OtherSlices other) {
+  if (!choose_slices(other, &partial, &splits, &bias)) return;
   const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   if (i >= count) return;
   float acc = 0.f;
@@ -312,10 +318,10 @@ __device__ __forceinline__ float sum_slices_lanes(const float* __restrict__ part
 }
 
 template <typename TO>
-__global__ __launch_bounds__(kThreads) void sum_slices_wide_kernel(const float* __restrict__ partial,
-                                                                   const float* __restrict__ bias,
+__global__ __launch_bounds__(kThreads) void sum_slices_wide_kernel(const float* partial, const float* bias,
                                                                    TO* __restrict__ out, int64_t count, int splits,
-                                                                   int64_t plane, int maps, int relu) {
+                                                                   int64_t plane, int maps, int relu, OtherSlices other) {
+  if (!choose_slices(other, &partial, &splits, &bias)) return;
   __shared__ float lanes[kSumLanes][kSumEl + 1];
   const int64_t i = (int64_t)blockIdx.x * kSumEl + (threadIdx.x & (kSumEl - 1));
   float total = sum_slices_lanes(partial, count, i, splits, lanes);
@@ -378,24 +384,24 @@ vcnn_status launch_sum_slices_split(const float* partial, float* main, float* la
 }
 
 vcnn_status launch_sum_slices(const float* partial, const float* bias, void* out, int out_dtype, int64_t count,
-                              int splits, int64_t plane, int maps, int relu, hipStream_t st) {
+                              int splits, int64_t plane, int maps, int relu, hipStream_t st, const OtherSlices& other) {
   if (splits >= 32 && count <= 65536) {  // few output elements, many slices: parallelise over the slices as well
     const dim3 grid((unsigned)ceil_div(count, kSumEl)), block(kThreads);
     if (out_dtype == VCNN_BF16)
       hipLaunchKernelGGL(sum_slices_wide_kernel<bf16>, grid, block, 0, st, partial, bias, (bf16*)out, count, splits, plane,
-                         maps, relu);
+                         maps, relu, other);
     else
       hipLaunchKernelGGL(sum_slices_wide_kernel<float>, grid, block, 0, st, partial, bias, (float*)out, count, splits,
-                         plane, maps, relu);
+                         plane, maps, relu, other);
     return check_launch("sum_slices_wide");
   }
   const dim3 grid((unsigned)ceil_div(count, kThreads)), block(kThreads);
   if (out_dtype == VCNN_BF16)
     hipLaunchKernelGGL(sum_slices_kernel<bf16>, grid, block, 0, st, partial, bias, (bf16*)out, count, splits, plane, maps,
-                       relu);
+                       relu, other);
   else
     hipLaunchKernelGGL(sum_slices_kernel<float>, grid, block, 0, st, partial, bias, (float*)out, count, splits, plane,
-                       maps, relu);
+                       maps, relu, other);
   return check_launch("sum_slices");
 }
 

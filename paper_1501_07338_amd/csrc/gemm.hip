@@ -60,6 +60,11 @@ __global__ __launch_bounds__(kThreads, BK == 16 ? 4 : 1) void gemm_f32_kernel(Ge
   const int tile = xcd_remap(blockIdx.x, tiles_total);
   const int i0 = (tile % tiles_m) * BM;
   const int j0 = (tile / tiles_m) * BN;
+  if (a.only.any) {
+    bool some = false;
+    for (int n = j0 / a.c_P; n <= (min(j0 + BN, a.N) - 1) / a.c_P; ++n) some |= is_declined(a.only, n);
+    if (!some) return;
+  }
   const int wm0 = (wave % (BM / WM)) * WM;
   const int wn0 = (wave / (BM / WM)) * WN;
 
@@ -162,7 +167,7 @@ __global__ __launch_bounds__(kThreads, BK == 16 ? 4 : 1) void gemm_f32_kernel(Ge
 #pragma unroll
   for (int ni = 0; ni < TN; ++ni) {
     const int j = j0 + wn0 + ni * 32 + l32;
-    if (j >= a.N) continue;
+    if (j >= a.N || (a.only.any && !is_declined(a.only, j / a.c_P))) continue;
     const int64_t cj = jmap(j, a.c_P, a.c_simg, a.c_sj);
 #pragma unroll
     for (int mi = 0; mi < TM; ++mi)
@@ -501,7 +506,9 @@ vcnn_status launch_gemm_f32(const GemmArgs& a, hipStream_t st) {
 template <int BM, int BN, int BK, int WM, int WN, bool VEC, typename T>
 __global__ __launch_bounds__(kThreads) void bwd_filter_f32_kernel(ConvGeom g, const T* __restrict__ dy,
                                                                   const T* __restrict__ col, const T* __restrict__ xin,
-                                                                  float* __restrict__ out, int tiles_m, int chunk) {
+                                                                  float* __restrict__ out, int tiles_m, int chunk,
+                                                                  Declined only) {
+  if (leave_all(only)) return;
   static_assert((BM / WM) * (BN / WN) * 64 == kThreads, "four waves per block");
   using LA = LdsTile<BM, BK, true>;
   using LB = LdsTile<BN, BK, true>;
@@ -673,29 +680,29 @@ size_t bwd_filter_partial_bytes(const ConvGeom& g) {
 
 template <int BM, int BN, int WM, int WN, bool VEC, typename T>
 static void launch_bf_one(const ConvGeom& g, const void* dy, const void* col, const void* xin, float* out, int tiles_m,
-                          int chunk, dim3 grid, hipStream_t st) {
+                          int chunk, dim3 grid, hipStream_t st, const Declined& only) {
   const size_t lds = gemm_lds_bytes<BM, BN, kBfBK, true, true>();
   auto kernel = bwd_filter_f32_kernel<BM, BN, kBfBK, WM, WN, VEC, T>;
   static bool opted_in = false;
   allow_lds(kernel, lds, opted_in);
   hipLaunchKernelGGL(kernel, grid, dim3(kThreads), lds, st, g, (const T*)dy, (const T*)col, (const T*)xin, out, tiles_m,
-                     chunk);
+                     chunk, only);
 }
 
 template <int BM, int BN, int WM, int WN>
 static void launch_bf(const ConvGeom& g, int dtype, const void* dy, const void* col, const void* xin, float* out,
-                      int tiles_m, int chunk, dim3 grid, bool vec, hipStream_t st) {
+                      int tiles_m, int chunk, dim3 grid, bool vec, hipStream_t st, const Declined& only) {
   if (dtype == VCNN_BF16) {
-    if (vec) launch_bf_one<BM, BN, WM, WN, true, bf16>(g, dy, col, xin, out, tiles_m, chunk, grid, st);
-    else launch_bf_one<BM, BN, WM, WN, false, bf16>(g, dy, col, xin, out, tiles_m, chunk, grid, st);
+    if (vec) launch_bf_one<BM, BN, WM, WN, true, bf16>(g, dy, col, xin, out, tiles_m, chunk, grid, st, only);
+    else launch_bf_one<BM, BN, WM, WN, false, bf16>(g, dy, col, xin, out, tiles_m, chunk, grid, st, only);
   } else {
-    if (vec) launch_bf_one<BM, BN, WM, WN, true, float>(g, dy, col, xin, out, tiles_m, chunk, grid, st);
-    else launch_bf_one<BM, BN, WM, WN, false, float>(g, dy, col, xin, out, tiles_m, chunk, grid, st);
+    if (vec) launch_bf_one<BM, BN, WM, WN, true, float>(g, dy, col, xin, out, tiles_m, chunk, grid, st, only);
+    else launch_bf_one<BM, BN, WM, WN, false, float>(g, dy, col, xin, out, tiles_m, chunk, grid, st, only);
   }
 }
 
 vcnn_status launch_bwd_filter_gemm_f32(const ConvGeom& g, int dtype, const void* dy, const void* col, const void* xin,
-                                       float* dw, float* partial, hipStream_t st) {
+                                       float* dw, float* partial, hipStream_t st, const Declined& only) {
   const int chunk = bwd_filter_chunk(g);
   const int splits = bwd_filter_splits(g);
   float* out = splits > 1 ? partial : dw;
@@ -709,15 +716,15 @@ vcnn_status launch_bwd_filter_gemm_f32(const ConvGeom& g, int dtype, const void*
   const bool vec = dtype == VCNN_BF16 ? g.P % 4 == 0 && g.N % 4 == 0 && in_aligned(dy, dtype) && in_aligned(b, dtype)
                                       : g.P >= 4 && ((reinterpret_cast<uintptr_t>(dy) | reinterpret_cast<uintptr_t>(b)) & 3) == 0;
   if (bm == 32)
-    launch_bf<32, 128, 32, 32>(g, dtype, dy, col, xin, out, tiles_m, chunk, grid, vec, st);
+    launch_bf<32, 128, 32, 32>(g, dtype, dy, col, xin, out, tiles_m, chunk, grid, vec, st, only);
   else if (bm == 64)
-    launch_bf<64, 128, 32, 64>(g, dtype, dy, col, xin, out, tiles_m, chunk, grid, vec, st);
+    launch_bf<64, 128, 32, 64>(g, dtype, dy, col, xin, out, tiles_m, chunk, grid, vec, st, only);
   else if (bwd_filter_bn(g) == 64)
-    launch_bf<128, 64, 64, 32>(g, dtype, dy, col, xin, out, tiles_m, chunk, grid, vec, st);
+    launch_bf<128, 64, 64, 32>(g, dtype, dy, col, xin, out, tiles_m, chunk, grid, vec, st, only);
   else
-    launch_bf<128, 128, 64, 64>(g, dtype, dy, col, xin, out, tiles_m, chunk, grid, vec, st);
+    launch_bf<128, 128, 64, 64>(g, dtype, dy, col, xin, out, tiles_m, chunk, grid, vec, st, only);
   vcnn_status s = check_launch("bwd_filter_f32");
-  if (s != VCNN_OK || splits == 1) return s;
+  if (s != VCNN_OK || splits == 1 || only.any) return s;
   return launch_sum_slices(partial, nullptr, dw, VCNN_F32, g.M * g.K, splits, 1, 1, 0, st);
 }
 

@@ -21,7 +21,9 @@ struct PointwiseF16Args {
   const uint4* a;  // rows of the result: [n or 1][4 tiles_i][steps][64]
   const uint4* b;  // columns: [n][4 tiles_j][steps][64]
   int64_t a_term, b_term;
-  const int32_t* exponent;
+  const int32_t* image_exponent;  // the scales of the activations' images (kernel gradient: of all of them) ...
+  const int32_t* exponent;        // ... and of the other operand
+  Declined declined;              // images left to the float kernel
   const float* bias;
   float* y;        // [n][rows][P], or slices [splits][rows][cols]
   int n, rows, cols, tiles_i, tiles_j, steps;
@@ -42,12 +44,13 @@ __global__ __launch_bounds__(kThreads, 2) void pointwise_f16_kernel(PointwiseF16
   const int item = xcd_item(blockIdx.x, gridDim.x);
   const int it = item % a.tiles_i, tj = item / a.tiles_i;  // tj = (sample, column tile)
   const int n = tj / a.tiles_j, jt = tj - n * a.tiles_j;
+  if (is_declined(a.declined, n)) return;
   const uint4* const src_a = a.a + (int64_t)(4 * it + wave) * a.steps * 64 + lane;
   const uint4* const src_b = a.b + ((int64_t)4 * tj + wave) * a.steps * 64 + lane;
   f32x16 acc[2][2];
   frag_product<2>(a.steps / kSteps, smem16, a.a_term, a.b_term, [&](int sl) { return src_a + sl * (kSteps * 64); },
                   [&](int sl) { return src_b + sl * (kSteps * 64); }, acc);
-  const int descale = -(a.exponent[0] + a.exponent[1]);
+  const int descale = -(a.image_exponent[n] + *a.exponent);
   const int i0 = it * kFragTile + (wave & 1) * 64, j0 = jt * kFragTile + (wave >> 1) * 64;
   float* const yn = a.y + (int64_t)n * a.rows * a.cols;
 #pragma unroll
@@ -71,6 +74,7 @@ __global__ __launch_bounds__(kThreads, 2) void pointwise_f16_kernel(PointwiseF16
 
 // (blockIdx.y: the split, a run of slabs across the samples)
 __global__ __launch_bounds__(kThreads, 2) void pointwise_f16_filter_kernel(PointwiseF16Args a) {
+  if (!leave_all(a.declined)) return;
   extern __shared__ uint4 smem16[];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int it = blockIdx.x % a.tiles_i, jt = blockIdx.x / a.tiles_i;
@@ -87,7 +91,7 @@ __global__ __launch_bounds__(kThreads, 2) void pointwise_f16_filter_kernel(Point
                     return a.b + (((int64_t)n * a.tiles_j + jt) * 4 + wave) * a.steps * 64 + s * (kSteps * 64) + lane;
                   },
                   acc);
-  const int descale = -(a.exponent[0] + a.exponent[1]);
+  const int descale = -(*a.image_exponent + *a.exponent);
   const int i0 = it * kFragTile + (wave & 1) * 64, j0 = jt * kFragTile + (wave >> 1) * 64;
   float* const out = a.y + (int64_t)blockIdx.y * a.rows * a.cols;
 #pragma unroll
@@ -131,7 +135,7 @@ bool pointwise_f16_plan(const ConvGeom& g, int pass, PointwiseF16Plan* p) {
     if (p->splits > 1) p->partial_bytes = align256((size_t)p->splits * g.M * g.K * sizeof(float));
     blocks = (double)tiles * p->splits, steps = (double)p->slabs_per_split * kSteps;
   }
-  p->workspace_bytes = kSplitScalesBytes + 2 * (p->a_bytes + p->b_bytes) + p->partial_bytes;
+  p->workspace_bytes = split_scales_bytes(filter ? 1 : g.n) + 2 * (p->a_bytes + p->b_bytes) + p->partial_bytes;
   // products at half the nominal rate on the busiest CU; the scan, the re-laying and the slices at 4.5 TB/s
   const double floats = 4.0 * (filter ? (double)g.M * g.N + (double)g.K * g.N : (double)g.M * g.K + (double)depth * g.N);
   p->est_seconds = std::max(std::ceil(blocks / 256.0), 1.5) * (steps * 12 * 32 * 1.9 / 2.4e9 + 1.5e-6) +
@@ -143,42 +147,47 @@ vcnn_status launch_pointwise_f16(const PointwiseF16Plan& p, const ConvGeom& g, i
                                  const float* bias, float* y, int relu, void* workspace, hipStream_t st) {
   const bool fwd = pass == VCNN_PASS_FWD;
   const int rows = fwd ? g.k : g.c, depth = fwd ? g.c : g.k, P = (int)g.P;
-  SplitScales* const sc = (SplitScales*)workspace;
-  char* const fa = (char*)workspace + kSplitScalesBytes;
+  const int64_t dp = (int64_t)depth * P;
+  const SplitScales sc = split_scales(workspace, g.n, g.n, dp, g.M * g.K);
+  char* const fa = (char*)workspace + split_scales_bytes(g.n);
   char* const fb = fa + 2 * p.a_bytes;
   PointwiseF16Args a{};
   a.a = (const uint4*)fa, a.b = (const uint4*)fb, a.a_term = (int64_t)(p.a_bytes / 16), a.b_term = (int64_t)(p.b_bytes / 16);
-  a.exponent = sc->exponent, a.bias = bias, a.y = y, a.relu = relu;
+  a.image_exponent = sc.exponent[0], a.exponent = sc.exponent[1], a.declined = sc.declined();
+  a.bias = bias, a.y = y, a.relu = relu;
   a.n = g.n, a.rows = rows, a.cols = P, a.tiles_i = p.tiles_i, a.tiles_j = p.tiles_j, a.steps = p.steps;
-  if (vcnn_status e = launch_absmax(x, (int64_t)g.n * depth * P, w, g.M * g.K, sc, st)) return e;
+  if (vcnn_status e = launch_absmax(x, g.n, dp, w, g.M * g.K, sc, true, st)) return e;
   // w is [k][c]: its rows (forward) or its columns (input gradient) are the rows of the result
-  if (vcnn_status e = launch_fragments({w, fa, a.a_term, rows, depth, fwd ? g.c : 1, fwd ? 1 : g.c, 0, 4 * p.tiles_i, 1, p.steps, 2, 1}, sc, st)) return e;
-  if (vcnn_status e = launch_fragments({x, fb, a.b_term, P, depth, 1, P, (int64_t)depth * P, 4 * p.tiles_j, g.n, p.steps, 2, 0}, sc, st)) return e;
+  if (vcnn_status e = launch_fragments({w, fa, a.a_term, rows, depth, fwd ? g.c : 1, fwd ? 1 : g.c, 0, 4 * p.tiles_i, 1, p.steps, 2, 1, 0}, sc, st)) return e;
+  if (vcnn_status e = launch_fragments({x, fb, a.b_term, P, depth, 1, P, dp, 4 * p.tiles_j, g.n, p.steps, 2, 0, 1}, sc, st)) return e;
   (void)hipFuncSetAttribute(reinterpret_cast<const void*>(pointwise_f16_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)FragSlab<2>::LDS_BYTES);
   hipLaunchKernelGGL(pointwise_f16_kernel, dim3((unsigned)((int64_t)g.n * p.tiles_i * p.tiles_j)), dim3(kThreads), FragSlab<2>::LDS_BYTES, st, a);
   return check_launch("pointwise_f16");
 }
 
 vcnn_status launch_pointwise_f16_filter(const PointwiseF16Plan& p, const ConvGeom& g, const float* x, const float* dy, float* dw,
-                                        void* workspace, hipStream_t st) {
+                                        void* workspace, const FilterBehind& behind, hipStream_t st) {
   const int P = (int)g.P;
-  SplitScales* const sc = (SplitScales*)workspace;
-  char* const fa = (char*)workspace + kSplitScalesBytes;
+  const SplitScales sc = split_scales(workspace, 1, 1, g.K * g.N, g.M * g.N);
+  char* const fa = (char*)workspace + split_scales_bytes(1);
   char* const fb = fa + 2 * p.a_bytes;
   float* const partial = (float*)(fb + 2 * p.b_bytes);
   PointwiseF16Args a{};
   a.a = (const uint4*)fa, a.b = (const uint4*)fb, a.a_term = (int64_t)(p.a_bytes / 16), a.b_term = (int64_t)(p.b_bytes / 16);
-  a.exponent = sc->exponent, a.y = p.splits > 1 ? partial : dw;
+  a.image_exponent = sc.exponent[0], a.exponent = sc.exponent[1], a.declined = sc.declined();
+  a.y = p.splits > 1 ? partial : dw;
   a.n = g.n, a.rows = (int)g.M, a.cols = (int)g.K, a.tiles_i = p.tiles_i, a.tiles_j = p.tiles_j, a.steps = p.steps;
   a.total_slabs = g.n * (p.steps / kSteps), a.slabs_per_split = p.slabs_per_split;
-  if (vcnn_status e = launch_absmax(x, g.K * g.N, dy, g.M * g.N, sc, st)) return e;
-  if (vcnn_status e = launch_fragments({dy, fa, a.a_term, (int)g.M, P, P, 1, g.M * P, 4 * p.tiles_i, g.n, p.steps, 2, 1}, sc, st)) return e;
-  if (vcnn_status e = launch_fragments({x, fb, a.b_term, (int)g.K, P, P, 1, g.K * P, 4 * p.tiles_j, g.n, p.steps, 2, 0}, sc, st)) return e;
+  if (vcnn_status e = launch_absmax(x, 1, g.K * g.N, dy, g.M * g.N, sc, true, st)) return e;
+  if (vcnn_status e = launch_fragments({dy, fa, a.a_term, (int)g.M, P, P, 1, g.M * P, 4 * p.tiles_i, g.n, p.steps, 2, 1, 0}, sc, st)) return e;
+  if (vcnn_status e = launch_fragments({x, fb, a.b_term, (int)g.K, P, P, 1, g.K * P, 4 * p.tiles_j, g.n, p.steps, 2, 0, 0}, sc, st)) return e;
   (void)hipFuncSetAttribute(reinterpret_cast<const void*>(pointwise_f16_filter_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)FragSlab<2>::LDS_BYTES);
   hipLaunchKernelGGL(pointwise_f16_filter_kernel, dim3((unsigned)(p.tiles_i * p.tiles_j), (unsigned)p.splits), dim3(kThreads), FragSlab<2>::LDS_BYTES, st, a);
   if (vcnn_status e = check_launch("pointwise_f16_filter")) return e;
-  if (p.splits == 1) return VCNN_OK;
-  return launch_sum_slices(partial, nullptr, dw, VCNN_F32, g.M * g.K, p.splits, 1, 1, 0, st);
+  OtherSlices other{};
+  if (vcnn_status e = launch_filter_behind(behind, dw, sc.declined(), st, &other)) return e;
+  if (p.splits == 1 && other.splits == 0) return VCNN_OK;
+  return launch_sum_slices(partial, nullptr, dw, VCNN_F32, g.M * g.K, p.splits > 1 ? p.splits : 0, 1, 1, 0, st, other);
 }
 
 }  // namespace vcnn

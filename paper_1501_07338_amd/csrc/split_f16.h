@@ -1,47 +1,113 @@
 // Floats as pairs of half-precision terms, for products of floats on the half-precision matrix cores.
 //
 // The matrix cores multiply f16 sixteen times as fast as float.  A float v, scaled by a power of two so that the
-// largest magnitude of its tensor lies in [2^14, 2^15), is hi + lo / 2^11 with hi = v rounded to f16 (11 significand
-// bits, and the sign of the remainder is a twelfth) and lo = the remainder times 2^11 rounded to f16: 24 bits, the
-// significand of a float, as long as |v| is above 2^-29 of the tensor's largest element; below that the remainder's
-// error stays under 2^-50 of the largest element.  Of the four term products hi*hi, hi*lo, lo*hi and lo*lo the last
-// lies below 2^-24 of the product - the rounding a float product has anyway - and is left out.  hi*hi is added in one
-// accumulator, the two mixed products in another, which joins the first with its factor 2^-11 at the end: the large
-// accumulator is rounded once per 16 contraction elements (v_mfma_f32_32x32x16_f16), where the float instruction
-// rounds it once per two, so the sums come out closer to the exact ones than the float instruction's.
+// largest magnitude under its scale lies in [2^14, 2^15), is hi + lo / 2^11 with hi = v rounded to f16 (11 significand
+// bits, and the sign of the remainder is a twelfth) and lo = the remainder times 2^11 rounded to f16: 23 bits, one short
+// of a float's significand (a quarter of all floats lose their last bit, an error of at most 2^-23 of the element).  Of the
+// four term products hi*hi, hi*lo, lo*hi and lo*lo the last, at most 2^-22 of the product and 2^-24.6 on average, is left
+// out.  hi*hi is added in one accumulator, the two mixed products in another, which joins the first with its factor 2^-11
+// at the end: the large accumulator is rounded once per 16 contraction elements (v_mfma_f32_32x32x16_f16), where the
+// float instruction rounds it once per two, so the sums of ordinary data come out no further from the exact ones.
 //
-// Infinities and NaN: hi carries them (lo = 0), and the joined sum is hi's alone when that is not finite, so a
-// non-finite element reaches exactly the sums it is part of.  The scale is taken from the finite elements.
+// Range.  One operand (the activations, or the gradient of them) has a scale per image, so that an image's results do not
+// depend on the images beside it; the kernel matrix has one, and so has either operand of the kernel gradient, whose sums
+// run over the images.  Under its scale an element keeps the 23 bits down to 2^-27 of the largest one and an absolute
+// error of 2^-36 (2^-50 of the largest) below that.  The re-laying passes count the elements they cannot keep to 21 bits
+// (below 2^-15 scaled); where they exceed one in 8192, the product is DECLINED: its
+// blocks leave at once and the float kernel, enqueued behind it and otherwise leaving at once itself, computes the
+// image (any declined element of the kernel matrix or of a kernel gradient: all of it).  The decision stays on the device.
+// So rare small elements - one in 10^8 of normally distributed ones - cost nothing, and an operand whose elements span
+// more than the terms hold gives what the float kernel gives.
+//
+// Infinities and NaN: hi carries them (lo = 0), and the joined sum is hi's alone when that is not finite.  The scale is
+// taken from the finite elements.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "common.h"
+
 namespace vcnn {
 
-static constexpr int kAbsMaxBlocks = 512;  // partial maxima per tensor
+static constexpr int kAbsMaxBlocks = 512;  // partial maxima of an operand with one scale
 
-// what a split product keeps about its two operands in the workspace
+// What a two-term product keeps about its two operands in the workspace (device pointers; the host lays them out).
 struct SplitScales {
-  uint32_t partial[2][kAbsMaxBlocks];  // largest finite magnitude of each block's share (float bits)
-  int32_t exponent[2];                 // operand t was scaled by 2^exponent[t]
-};
-static constexpr size_t kSplitScalesBytes = (sizeof(SplitScales) + 255) & ~(size_t)255;
+  uint32_t* partial[2];  // largest magnitude (float bits) of each scanning block's share
+  int32_t* exponent[2];  // scaled by 2^exponent: one per image, one
+  uint32_t* small[2];    // elements below 2^-15 when scaled: per image, one
+  uint32_t* any;         // the words of Declined
+  uint32_t* all;
+  uint32_t* image;
+  uint32_t limit[2];     // more small elements than this decline
+  int blocks;            // scanning blocks per image of operand 0
 
-// The exponent for a tensor from its partial maxima; called by all 256 threads of a block.
-__device__ __forceinline__ int split_exponent(const uint32_t* partial) {
+  Declined declined() const { return {any, all, image}; }
+  // The same for images n0 and on (a part of the batch).
+  SplitScales from(int n0) const {
+    SplitScales s = *this;
+    s.exponent[0] += n0, s.small[0] += n0, s.image += n0;
+    return s;
+  }
+};
+
+// The largest of `blocks` partial maxima; called by all 256 threads of a block.
+__device__ __forceinline__ uint32_t split_max(const uint32_t* partial, int blocks) {
   __shared__ uint32_t wave_max[4];
   const int tid = threadIdx.x;
   uint32_t m = 0;
-#pragma unroll
-  for (int i = 0; i < kAbsMaxBlocks / 256; ++i) m = max(m, partial[tid + 256 * i]);
+  for (int i = tid; i < blocks; i += 256) m = max(m, partial[i]);
 #pragma unroll
   for (int d = 32; d > 0; d >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, d));
   if ((tid & 63) == 0) wave_max[tid >> 6] = m;
   __syncthreads();
-  m = max(max(wave_max[0], wave_max[1]), max(wave_max[2], wave_max[3]));
-  // (a denormal largest element counts as 2^-126; an all-zero tensor needs no scale)
-  return m == 0 ? 0 : 14 - (max((int)(m >> 23), 1) - 127);
+  return max(max(wave_max[0], wave_max[1]), max(wave_max[2], wave_max[3]));
 }
+// The exponent for a largest magnitude (a denormal one counts as 2^-126; zeros need no scale).
+__device__ __forceinline__ int split_exponent(uint32_t largest) {
+  return largest == 0 ? 0 : 14 - (max((int)(largest >> 23), 1) - 127);
+}
+__device__ __forceinline__ void decline(const SplitScales& sc, int operand, int image) {
+  *sc.any = 1;
+  if (operand == 0) sc.image[image] = 1;
+  else *sc.all = 1;
+}
+// One thread per scale: leaves it for the product.
+__device__ __forceinline__ void note_scale(const SplitScales& sc, int operand, int image, uint32_t largest) {
+  sc.exponent[operand][operand == 0 ? image : 0] = split_exponent(largest);
+}
+// Adds a thread's count of small elements; called by whole waves.  (Waves that have none, all of them on ordinary data,
+// touch nothing; a counter past its limit is left alone.)
+__device__ __forceinline__ void note_small(const SplitScales& sc, int operand, int image, int count) {
+  if (__ballot(count != 0) == 0) return;
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) count += __shfl_xor(count, d);
+  uint32_t* const total = sc.small[operand] + (operand == 0 ? image : 0);
+  if ((threadIdx.x & 63) != 0 || __hip_atomic_load(total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > sc.limit[operand]) return;
+  if (atomicAdd(total, (uint32_t)count) + (uint32_t)count > sc.limit[operand]) decline(sc, operand, image);
+}
+
+// Finds the elements below 2^-15 when scaled.  key(): the magnitude's bits, zero (exact at any scale) above all others;
+// the splitting passes keep the least key of a thread's elements, two instructions for one, and count where it is below
+// the limit.
+struct SmallElements {
+  uint32_t limit, least;
+  __device__ __forceinline__ explicit SmallElements(int exponent) : least(~0u) {
+    const uint32_t bound = __float_as_uint(ldexpf(1.f, -15 - exponent));  // (0: no float is that small)
+    limit = bound ? 2 * bound - 1 : 0;
+  }
+  static __device__ __forceinline__ uint32_t key(float v) { return (__float_as_uint(v) << 1) - 1u; }
+  __device__ __forceinline__ void take(float v) { least = min(least, key(v)); }
+  template <int N>
+  __device__ __forceinline__ int count(const float (&v)[N]) const {
+    int c = 0;
+    if (least < limit) {
+#pragma unroll
+      for (int i = 0; i < N; ++i) c += key(v[i]) < limit;
+    }
+    return c;
+  }
+};
 
 // The two terms of v * 2^exponent as f16 bits: hi in the low half of the result, lo in the high half.
 __device__ __forceinline__ uint32_t split_f16(float v, int exponent) {

@@ -12,16 +12,28 @@ static constexpr int kThreads = 256;
 
 struct AbsMaxArgs {
   const float* src[2];
-  int64_t count[2];
-  SplitScales* scales;
+  int64_t count[2];  // floats per image, floats
+  int image_blocks;  // blocks of operand 0; operand 1's follow
+  int first;
+  SplitScales sc;
 };
 
-// Largest finite magnitude of each block's share of the two operands (blockIdx.y).  Bandwidth: read once, 16 bytes per
+// Largest finite magnitude of each block's share of the two operands, an image of
+// the first at a time; the first block of a scale clears its counter and its word.  Bandwidth: read once, 16 bytes per
 // load and four loads in flight per thread.
 __global__ __launch_bounds__(kThreads) void absmax_kernel(AbsMaxArgs a) {
-  const int op = blockIdx.y;
-  const float* const p = a.src[op];
+  const int op = (int)blockIdx.x >= a.image_blocks;
+  const int image = op ? 0 : (int)blockIdx.x / a.sc.blocks;
+  const int blocks = op ? kAbsMaxBlocks : a.sc.blocks;
+  const int block = op ? (int)blockIdx.x - a.image_blocks : (int)blockIdx.x - image * a.sc.blocks;
   const int64_t count = a.count[op];
+  const float* const p = a.src[op] + image * count;
+  if (block == 0 && threadIdx.x == 0) {
+    if (op == 0 && image == 0 && a.first) *a.sc.any = 0;
+    a.sc.small[op][image] = 0;
+    if (op) *a.sc.all = 0;
+    else a.sc.image[image] = 0;
+  }
   const int head = (int)min((int64_t)((16 - ((uintptr_t)p & 15)) & 15) / 4, count);  // floats before a 16-byte boundary
   const uint4* const body = reinterpret_cast<const uint4*>(p + head);
   const int64_t quads = (count - head) / 4;
@@ -30,20 +42,20 @@ __global__ __launch_bounds__(kThreads) void absmax_kernel(AbsMaxArgs a) {
     bits &= 0x7fffffffu;
     m = max(m, bits < 0x7f800000u ? bits : 0u);
   };
-  constexpr int64_t kStep = (int64_t)kAbsMaxBlocks * kThreads;
-  int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  for (; i + 3 * kStep < quads; i += 4 * kStep) {
+  const int64_t step = (int64_t)blocks * kThreads;
+  int64_t i = (int64_t)block * kThreads + threadIdx.x;
+  for (; i + 3 * step < quads; i += 4 * step) {
     uint4 v[4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) v[k] = body[i + k * kStep];
+    for (int k = 0; k < 4; ++k) v[k] = body[i + k * step];
 #pragma unroll
     for (int k = 0; k < 4; ++k) take(v[k].x), take(v[k].y), take(v[k].z), take(v[k].w);
   }
-  for (; i < quads; i += kStep) {
+  for (; i < quads; i += step) {
     const uint4 v = body[i];
     take(v.x), take(v.y), take(v.z), take(v.w);
   }
-  if (blockIdx.x == 0 && threadIdx.x < 8) {  // the floats around the 16-byte words
+  if (block == 0 && threadIdx.x < 8) {  // the floats around the 16-byte words
     const int64_t e = threadIdx.x < 4 ? (int64_t)threadIdx.x : head + quads * 4 + (threadIdx.x - 4);
     if (threadIdx.x < 4 ? e < head : e < count) take(__float_as_uint(p[e]));
   }
@@ -53,16 +65,54 @@ __global__ __launch_bounds__(kThreads) void absmax_kernel(AbsMaxArgs a) {
   if ((threadIdx.x & 63) == 0) wave_max[threadIdx.x >> 6] = m;
   __syncthreads();
   if (threadIdx.x == 0)
-    a.scales->partial[op][blockIdx.x] = max(max(wave_max[0], wave_max[1]), max(wave_max[2], wave_max[3]));
+    a.sc.partial[op][op ? block : (int)blockIdx.x] = max(max(wave_max[0], wave_max[1]), max(wave_max[2], wave_max[3]));
 }
 
-vcnn_status launch_absmax(const float* a, int64_t na, const float* b, int64_t nb, SplitScales* sc, hipStream_t st) {
-  AbsMaxArgs args{{a, b}, {na, nb}, sc};
-  hipLaunchKernelGGL(absmax_kernel, dim3(kAbsMaxBlocks, 2), dim3(kThreads), 0, st, args);
+vcnn_status launch_absmax(const float* a, int images, int64_t per_image, const float* b, int64_t nb, const SplitScales& sc,
+                          bool first, hipStream_t st) {
+  AbsMaxArgs args{{a, b}, {per_image, nb}, images * sc.blocks, first, sc};
+  hipLaunchKernelGGL(absmax_kernel, dim3((unsigned)(args.image_blocks + (nb ? kAbsMaxBlocks : 0))), dim3(kThreads), 0, st, args);
   return check_launch("absmax");
 }
 
 static inline size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
+
+// Blocks that scan one of `images` images (whatever part of the batch they are, images x blocks <= images + kAbsMaxBlocks).
+static int scan_blocks(int images) { return std::max(1, kAbsMaxBlocks / images); }
+
+size_t split_scales_bytes(int images) {
+  const size_t partial = (size_t)images + 2 * kAbsMaxBlocks, per_image = 3 * (size_t)images, others = 4;
+  return align256((partial + per_image + others) * sizeof(uint32_t));
+}
+
+SplitScales split_scales(void* workspace, int images, int images_at_once, int64_t per_image, int64_t others) {
+  uint32_t* w = (uint32_t*)workspace;
+  auto take = [&](size_t words) { uint32_t* const at = w; w += words; return at; };
+  SplitScales sc{};
+  sc.any = take(1), sc.all = take(1);
+  sc.exponent[1] = (int32_t*)take(1), sc.small[1] = take(1);
+  sc.exponent[0] = (int32_t*)take(images), sc.small[0] = take(images), sc.image = take(images);
+  sc.partial[1] = take(kAbsMaxBlocks), sc.partial[0] = take((size_t)images + kAbsMaxBlocks);
+  sc.blocks = scan_blocks(images_at_once);
+  auto limit = [](int64_t count) { return (uint32_t)std::min<int64_t>(count >> 13, 1 << 30); };
+  sc.limit[0] = limit(per_image), sc.limit[1] = limit(others);
+  return sc;
+}
+
+Declined split_declined(const void* workspace, int images) {
+  return split_scales(const_cast<void*>(workspace), images, images, 0, 0).declined();
+}
+
+vcnn_status launch_filter_behind(const FilterBehind& b, float* dw, const Declined& only, hipStream_t st, OtherSlices* other) {
+  other->declined = only.any, other->partial = b.workspace;
+  if (b.halo) {
+    other->splits = b.halo->splits > 1 ? b.halo->splits : 0;
+    return launch_conv_halo_filter(*b.halo, VCNN_F32, *b.g, b.x, b.dy, dw, nullptr, b.workspace, st, only);
+  }
+  const int splits = bwd_filter_splits(*b.g);
+  other->splits = splits > 1 ? splits : 0;
+  return launch_bwd_filter_gemm_f32(*b.g, VCNN_F32, b.dy, nullptr, b.x, dw, b.workspace, st, only);
+}
 
 // The scales read both operands, the re-laying passes read them again and write the terms: at some 3.5 TB/s, and three
 // launches.
@@ -78,7 +128,7 @@ static bool part_plan(const ConvGeom& whole, int pass, int n, int max_splits, F1
     const size_t terms = 2 * (p->filter.x8n_bytes + p->filter.dyf_bytes);
     // (later parts add to dw through the slice sum, which then needs one slice at least)
     const size_t slices = std::max(p->filter.partial_bytes, n < whole.n ? (size_t)g.M * g.K * sizeof(float) : (size_t)0);
-    p->workspace_bytes = kSplitScalesBytes + terms + align256(slices);
+    p->workspace_bytes = split_scales_bytes(1) + terms + align256(slices);
     p->est_seconds = p->filter.est_seconds + relay_seconds(x_bytes + y_bytes, (double)terms);
     return true;
   }
@@ -90,7 +140,7 @@ static bool part_plan(const ConvGeom& whole, int pass, int n, int max_splits, F1
     if (ph < 0 || pw < 0 || !conv_halo_bf16_plan(g.n, g.k, g.oh, g.ow, g.c, g.r, g.s, ph, pw, &p->fwd, 2)) return false;
   }
   const size_t terms = 2 * (p->fwd.x8_bytes + p->fwd.wf_bytes);
-  p->workspace_bytes = kSplitScalesBytes + terms;
+  p->workspace_bytes = split_scales_bytes(whole.n) + terms;
   p->est_seconds = p->fwd.est_seconds + relay_seconds((pass == VCNN_PASS_FWD ? x_bytes : y_bytes) + w_bytes, (double)terms);
   return true;
 }
@@ -147,40 +197,40 @@ static vcnn_status each_part(const F16x2Plan& p, const ConvGeom& whole, int pass
 
 vcnn_status launch_conv_f16x2_fwd(const F16x2Plan& plan, const ConvGeom& whole, const float* x, const float* w,
                                   const float* bias, float* y, int relu, void* workspace, hipStream_t st) {
-  SplitScales* const sc = (SplitScales*)workspace;
-  char* const x8 = (char*)workspace + kSplitScalesBytes;
+  const int64_t chw = (int64_t)whole.c * whole.h * whole.w;
+  char* const x8 = (char*)workspace + split_scales_bytes(whole.n);
   return each_part(plan, whole, VCNN_PASS_FWD, [&](int n0, const ConvGeom& g, const F16x2Plan& p) {
-    const int64_t chw = (int64_t)g.c * g.h * g.w;
-    if (vcnn_status e = launch_absmax(x + n0 * chw, g.n * chw, w, g.M * g.K, sc, st)) return e;
+    const SplitScales sc = split_scales(workspace, whole.n, g.n, chw, g.M * g.K).from(n0);
+    if (vcnn_status e = launch_absmax(x + n0 * chw, g.n, chw, w, g.M * g.K, sc, n0 == 0, st)) return e;
     return launch_conv_halo_f16x2(p.fwd, g.n, g.c, g.h, g.w, g.k, g.r, g.s, g.ph, g.pw, x + n0 * chw, w, g.K,
-                                  (int64_t)g.r * g.s, 0, bias, y + n0 * g.M * g.P, relu, sc, x8, x8 + 2 * p.fwd.x8_bytes, st);
+                                  (int64_t)g.r * g.s, 0, bias, y + n0 * g.M * g.P, relu, sc, x8, x8 + 2 * p.fwd.x8_bytes, nullptr,
+                                  st);
   });
 }
 
 vcnn_status launch_conv_f16x2_bwd_data(const F16x2Plan& plan, const ConvGeom& whole, const float* w, const float* dy,
-                                       float* dx, void* workspace, hipStream_t st) {
-  SplitScales* const sc = (SplitScales*)workspace;
-  char* const x8 = (char*)workspace + kSplitScalesBytes;
+                                       float* dx, float* flipped, void* workspace, hipStream_t st) {
+  const int64_t mp = whole.M * whole.P;
+  char* const x8 = (char*)workspace + split_scales_bytes(whole.n);
   return each_part(plan, whole, VCNN_PASS_BWD_DATA, [&](int n0, const ConvGeom& g, const F16x2Plan& p) {
-    const float* const d = dy + n0 * g.M * g.P;
-    if (vcnn_status e = launch_absmax(d, g.M * g.N, w, g.M * g.K, sc, st)) return e;
-    return launch_conv_halo_f16x2(p.fwd, g.n, g.k, g.oh, g.ow, g.c, g.r, g.s, g.r - 1 - g.ph, g.s - 1 - g.pw, d, w,
+    const SplitScales sc = split_scales(workspace, whole.n, g.n, mp, g.M * g.K).from(n0);
+    if (vcnn_status e = launch_absmax(dy + n0 * mp, g.n, mp, w, g.M * g.K, sc, n0 == 0, st)) return e;
+    return launch_conv_halo_f16x2(p.fwd, g.n, g.k, g.oh, g.ow, g.c, g.r, g.s, g.r - 1 - g.ph, g.s - 1 - g.pw, dy + n0 * mp, w,
                                   (int64_t)g.r * g.s, g.K, 1, nullptr, dx + (int64_t)n0 * g.c * g.h * g.w, 0, sc, x8,
-                                  x8 + 2 * p.fwd.x8_bytes, st);
+                                  x8 + 2 * p.fwd.x8_bytes, flipped, st);
   });
 }
 
 vcnn_status launch_conv_f16x2_filter(const F16x2Plan& plan, const ConvGeom& whole, const float* x, const float* dy, float* dw,
-                                     void* workspace, hipStream_t st) {
-  SplitScales* const sc = (SplitScales*)workspace;
-  char* const x8n = (char*)workspace + kSplitScalesBytes;
+                                     void* workspace, const FilterBehind& behind, hipStream_t st) {
+  const int64_t chw = (int64_t)whole.c * whole.h * whole.w, mp = whole.M * whole.P;
+  char* const x8n = (char*)workspace + split_scales_bytes(1);
   return each_part(plan, whole, VCNN_PASS_BWD_FILTER, [&](int n0, const ConvGeom& g, const F16x2Plan& p) {
+    const SplitScales sc = split_scales(workspace, 1, 1, g.n * chw, g.n * mp);
     char* const dyf = x8n + 2 * p.filter.x8n_bytes;
-    const int64_t chw = (int64_t)g.c * g.h * g.w;
-    const float* const d = dy + n0 * g.M * g.P;
-    if (vcnn_status e = launch_absmax(x + n0 * chw, g.n * chw, d, g.M * g.N, sc, st)) return e;
-    return launch_filter_grad_f16x2(p.filter, g, x + n0 * chw, d, dw, sc, x8n, dyf, (float*)(dyf + 2 * p.filter.dyf_bytes),
-                                    st, n0 > 0);
+    if (vcnn_status e = launch_absmax(x + n0 * chw, 1, g.n * chw, dy + n0 * mp, g.n * mp, sc, n0 == 0, st)) return e;
+    return launch_filter_grad_f16x2(p.filter, g, x + n0 * chw, dy + n0 * mp, dw, sc, x8n, dyf,
+                                    (float*)(dyf + 2 * p.filter.dyf_bytes), st, n0 > 0, n0 + g.n == whole.n ? &behind : nullptr);
   });
 }
 

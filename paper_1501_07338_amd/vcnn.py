@@ -43,6 +43,7 @@ _SIGNATURES = {
     "vcnn_set_conv_algo": (c_int32, [c_int32]),
     "vcnn_conv_out_shape": (c_int32, [POINTER(ConvDesc), POINTER(c_int32), POINTER(c_int32)]),
     "vcnn_conv_workspace_bytes": (c_int32, [POINTER(ConvDesc), c_int32, POINTER(c_size_t)]),
+    "vcnn_conv_route": (c_int32, [POINTER(ConvDesc), c_int32, c_size_t, POINTER(c_char_p)]),
     "vcnn_im2col": (c_int32, [POINTER(ConvDesc), c_void_p, c_void_p, c_void_p]),
     "vcnn_col2im": (c_int32, [POINTER(ConvDesc), c_void_p, c_void_p, c_void_p]),
     "vcnn_conv_fwd": (c_int32, [POINTER(ConvDesc), c_void_p, c_void_p, c_void_p, c_void_p, c_void_p, c_size_t, c_void_p]),
@@ -159,6 +160,12 @@ def conv_workspace_bytes(d: ConvDesc, which: int) -> int:
     b = c_size_t()
     _check(lib().vcnn_conv_workspace_bytes(byref(d), which, byref(b)))
     return b.value
+
+
+def conv_route(d: ConvDesc, which: int, workspace_bytes: int) -> str:
+    name = c_char_p()
+    _check(lib().vcnn_conv_route(byref(d), which, workspace_bytes, byref(name)))
+    return name.value.decode()
 
 
 def im2col(d, x, col, stream=None):

@@ -1,6 +1,6 @@
 """The float products of larger layers from two half-precision terms per operand (the AUTO route of such layers): parity
-with the oracle at the edges of its tiles and arrangements, the scales, non-finite inputs, parts of a batch, and the
-float route in its place where the workspace is too small."""
+with the oracle at the edges of its tiles and arrangements, the scales, operands the terms do not carry (magnitudes too far
+apart), non-finite inputs, parts of a batch, and the float route in its place where the workspace is too small."""
 import numpy as np
 import pytest
 import torch
@@ -13,19 +13,39 @@ from util import assert_close, to_np
 DEV = "cuda:0"
 # the split itself leaves about 1e-7 of the largest element, the float accumulation of these sums less than 2e-6
 TOL = 4e-6
+FWD, FILTER, DATA = vcnn.PASS_FWD, vcnn.PASS_BWD_FILTER, vcnn.PASS_BWD_DATA
+IMPLICIT, FOLD, POINTWISE = "two_term", "two_term_fold", "two_term_pointwise"
 
-# (n, c, h, w, k, r, s, pad_h, pad_w): at most 32 / 48 / 64 / more maps, ragged channels, planes and batches
+# (n, c, h, w, k, r, s, pad_h, pad_w) and the passes that take a two-term route, which the test asserts one by one: at most
+# 32 / 48 / 64 / 128 / more maps on the rows, ragged channels, planes and batches, either order of the fold's adds
 SHAPES = [
-    (3, 102, 29, 29, 8, 16, 1, 0, 0),      # at most 32 maps, few pixels
-    (10, 185, 22, 13, 23, 9, 9, 0, 0),     # 32-row tiles, long contraction
-    (11, 57, 33, 31, 38, 5, 7, 2, 3),      # 33..48 maps: 16-row tiles, padded
-    (17, 41, 40, 37, 49, 5, 5, 2, 2),      # one map more than the 16-row tiles take
-    (23, 130, 30, 30, 64, 5, 5, 2, 2),
-    (7, 29, 143, 11, 142, 12, 10, 0, 0),   # several row tiles, a short last one
-    (3, 26, 147, 147, 7, 1, 80, 0, 0),     # wide kernel
-    (2, 174, 27, 27, 300, 5, 5, 0, 0),     # four row groups side by side
-    (7, 19, 25, 42, 9, 7, 7, 3, 3),        # short runs of the kernel gradient: waves without a share of one
+    ((3, 102, 29, 29, 8, 16, 1, 0, 0), {FWD: IMPLICIT}),                 # at most 32 maps, few pixels
+    ((10, 185, 22, 13, 23, 9, 9, 0, 0), {FWD: IMPLICIT, DATA: IMPLICIT}),  # 32-row tiles; 185 maps of an input gradient
+    ((11, 57, 33, 31, 38, 5, 7, 2, 3), {FWD: IMPLICIT, DATA: IMPLICIT}),   # 33..48 maps: 16-row tiles, padded
+    ((17, 41, 40, 37, 49, 5, 5, 2, 2), {FWD: IMPLICIT, DATA: IMPLICIT}),   # one map more than the 16-row tiles take
+    ((23, 130, 30, 30, 64, 5, 5, 2, 2), {FWD: IMPLICIT, FILTER: IMPLICIT, DATA: IMPLICIT}),
+    ((2, 89, 12, 33, 61, 9, 2, 2, 0), {FWD: IMPLICIT, DATA: IMPLICIT}),    # 65..128 rows in the input gradient
+    ((7, 29, 143, 11, 142, 12, 10, 0, 0), {FWD: IMPLICIT, FILTER: IMPLICIT}),  # several row tiles, a short last one
+    ((3, 26, 147, 147, 7, 1, 80, 0, 0), {FWD: IMPLICIT}),                # wide kernel
+    ((2, 174, 27, 27, 300, 5, 5, 0, 0), {FWD: IMPLICIT}),                # four row groups side by side
+    ((7, 19, 25, 42, 9, 7, 7, 3, 3), {FILTER: IMPLICIT}),                # short runs: waves without a share of one
+    ((16, 512, 57, 10, 20, 5, 5, 0, 0), {FWD: IMPLICIT, FILTER: IMPLICIT}),  # a last run of rows shorter than the waves' shares
+    ((4, 6, 41, 51, 36, 3, 14, 0, 0), {FILTER: IMPLICIT}),               # six channels: most of a group padding
+    ((5, 5, 19, 47, 59, 10, 9, 0, 0), {FILTER: IMPLICIT}),
+    ((2, 46, 27, 27, 45, 9, 9, 2, 3), {FWD: IMPLICIT, FILTER: IMPLICIT, DATA: FOLD}),
+    ((2, 29, 30, 6, 100, 14, 4, 3, 2), {DATA: FOLD}),                    # rows 32 apart meet: added one after the other
+    ((3, 49, 10, 16, 140, 3, 14, 1, 7), {DATA: FOLD}),                   # ... several channels per tile, ragged maps
+    ((2, 62, 11, 24, 99, 4, 7, 2, 3), {DATA: FOLD}),
+    ((5, 339, 7, 9, 303, 2, 3, 1, 0), {DATA: FOLD}),
+    ((13, 389, 53, 51, 401, 1, 1, 0, 0), {FWD: POINTWISE, DATA: POINTWISE}),  # odd planes: rows at any dword; ragged tiles
+    ((11, 250, 33, 20, 455, 1, 1, 0, 0), {FWD: POINTWISE, DATA: POINTWISE}),
+    ((2, 395, 12, 33, 191, 1, 1, 0, 0), {FWD: POINTWISE}),
+    ((13, 512, 47, 51, 512, 1, 1, 0, 0), {FWD: POINTWISE, FILTER: POINTWISE, DATA: POINTWISE}),  # split sums, padded slabs
 ]
+# one small layer of every pair of route and pass
+ONE_EACH = [(SHAPES[2][0], FWD, IMPLICIT), (SHAPES[5][0], DATA, IMPLICIT), (SHAPES[9][0], FILTER, IMPLICIT),
+            (SHAPES[10][0], FILTER, IMPLICIT), (SHAPES[14][0], DATA, FOLD), (SHAPES[16][0], DATA, FOLD),
+            (SHAPES[20][0], FWD, POINTWISE), (SHAPES[19][0], DATA, POINTWISE), (SHAPES[21][0], FILTER, POINTWISE)]
 
 
 def tensors(shape, seed):
@@ -38,65 +58,194 @@ def tensors(shape, seed):
     return d, x, wt, b, random_tensor(seed + 3, (n, k, oh, ow))
 
 
-def run(d, x, wt, b, dy, ws_bytes=None):
-    """(y, dw, db, dx) under the current route choice, each with its own workspace of the size asked for."""
+def route(d, which):
+    return vcnn.conv_route(d, which, vcnn.conv_workspace_bytes(d, which))
+
+
+def run_pass(d, which, x, wt, b, dy, nbytes=None):
+    """The pass's result (kernel gradient: dw and db) with a workspace of exactly the size asked for, filled with NaN."""
     xd, wd, bd, dyd = (torch.from_numpy(np.ascontiguousarray(a)).to(DEV) for a in (x, wt, b, dy))
-    out = [torch.full(a.shape, float("nan"), device=DEV) for a in (dy, wt, b, x)]
+    nbytes = vcnn.conv_workspace_bytes(d, which) if nbytes is None else nbytes
+    ws = torch.full((nbytes,), 255, dtype=torch.uint8, device=DEV) if nbytes else None
+    out = torch.full({FWD: dy, FILTER: wt, DATA: x}[which].shape, float("nan"), device=DEV)
+    if which == FWD:
+        vcnn.conv_fwd(d, xd, wd, bd, out, ws)
+    elif which == DATA:
+        vcnn.conv_bwd_data(d, wd, dyd, out, ws)
+    else:
+        db = torch.full(b.shape, float("nan"), device=DEV)
+        vcnn.conv_bwd_filter(d, xd, dyd, out, db, ws)
+        return to_np(out), to_np(db)
+    return to_np(out)
 
-    def ws(which):
-        need = vcnn.conv_workspace_bytes(d, which) if ws_bytes is None else ws_bytes[which]
-        return torch.empty(need, dtype=torch.uint8, device=DEV) if need else None
-    vcnn.conv_fwd(d, xd, wd, bd, out[0], ws(vcnn.PASS_FWD))
-    vcnn.conv_bwd_filter(d, xd, dyd, out[1], out[2], ws(vcnn.PASS_BWD_FILTER))
-    vcnn.conv_bwd_data(d, wd, dyd, out[3], ws(vcnn.PASS_BWD_DATA))
-    return [to_np(t) for t in out]
+
+def product(d, which, x, wt, b, dy, nbytes=None):
+    got = run_pass(d, which, x, wt, b, dy, nbytes)
+    return got[0] if which == FILTER else got
 
 
-def float_route_bytes(d):
-    vcnn.set_conv_algo(vcnn.ALGO_IMPLICIT)
-    try:
-        return [vcnn.conv_workspace_bytes(d, p) for p in range(3)]
-    finally:
-        vcnn.set_conv_algo(vcnn.ALGO_AUTO)
+def expected(d, which, x, wt, b, dy):
+    pad = (d.pad_h, d.pad_w)
+    if d.r == d.s == 1:  # (a plain product, quicker without the oracle's loops)
+        xm, dm = x.astype(np.float64).reshape(d.n, d.c, -1), dy.astype(np.float64).reshape(d.n, d.k, -1)
+        wm = wt.astype(np.float64).reshape(d.k, d.c)
+        return {FWD: lambda: (wm @ xm + b[:, None].astype(np.float64)).reshape(dy.shape),
+                DATA: lambda: (wm.T @ dm).reshape(x.shape),
+                FILTER: lambda: sum(p @ q.T for p, q in zip(dm, xm)).reshape(wt.shape)}[which]()
+    if which == FWD:
+        return O.conv_fwd(x, wt, b, pad=pad)
+    return O.conv_bwd_data(wt, dy, (d.h, d.w), pad=pad) if which == DATA else O.conv_bwd_filter(x, dy, (d.r, d.s), pad=pad)[0]
+
+
+def float_bytes(d, which):
+    """What the float route of the pass needs: the least workspace it runs with."""
+    low, high = -1, vcnn.conv_workspace_bytes(d, which)
+    while high - low > 1:
+        mid = (low + high) // 2
+        try:
+            vcnn.conv_route(d, which, mid)
+            high = mid
+        except vcnn.VcnnError as e:
+            assert e.status == vcnn.ERR_WORKSPACE
+            low = mid
+    return high
+
+
+@pytest.mark.parametrize("shape,routes", SHAPES)
+def test_routes_of_the_tested_layers(shape, routes):
+    """No GPU needed: each pass below really is planned as a two-term product."""
+    d = vcnn.conv_desc(*shape)
+    for which, name in routes.items():
+        assert route(d, which) == name, (shape, which)
+    with pytest.raises(vcnn.VcnnError) as e:
+        vcnn.conv_route(d, 7, 0)
+    assert e.value.status == vcnn.ERR_UNSUPPORTED
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("shape", SHAPES)
-def test_two_term_products_against_the_oracle(shape):
-    n, c, h, w, k, r, s, ph, pw = shape
+@pytest.mark.parametrize("shape,routes", SHAPES)
+def test_two_term_products_against_the_oracle(shape, routes):
     d, x, wt, b, dy = tensors(shape, 4100)
-    assert [vcnn.conv_workspace_bytes(d, p) for p in range(3)] != float_route_bytes(d)  # the two-term route is taken
-    y, dw, db, dx = run(d, x, wt, b, dy)
-    assert_close(y, O.conv_fwd(x, wt, b, pad=(ph, pw)), TOL, "y")
-    rdw, rdb = O.conv_bwd_filter(x, dy, (r, s), pad=(ph, pw))
-    assert_close(dw, rdw, TOL, "dw")
-    assert_close(db, rdb, TOL, "db")
-    assert_close(dx, O.conv_bwd_data(wt, dy, (h, w), pad=(ph, pw)), TOL, "dx")
-    again = run(d, x, wt, b, dy)
-    assert all(np.array_equal(a, e) for a, e in zip((y, dw, db, dx), again))
+    for which, name in routes.items():
+        assert route(d, which) == name
+        got = run_pass(d, which, x, wt, b, dy)
+        want = expected(d, which, x, wt, b, dy)
+        if which == FILTER:
+            assert_close(got[0], want, TOL, "dw")
+            assert_close(got[1], dy.astype(np.float64).sum((0, 2, 3)), TOL, "db")
+        else:
+            assert_close(got, want, TOL, "y" if which == FWD else "dx")
+        again = run_pass(d, which, x, wt, b, dy)
+        assert all(np.array_equal(p, q) for p, q in zip(got, again))
 
 
 @pytest.mark.gpu
-def test_scales_are_exact():
+@pytest.mark.parametrize("shape,which,name", ONE_EACH)
+def test_scales_are_exact(shape, which, name):
     """The operands are scaled by powers of two, so inputs scaled by powers of two give the same bits, scaled."""
-    d, x, wt, b, dy = tensors(SHAPES[2], 4200)
+    d, x, wt, b, dy = tensors(shape, 4200)
+    assert route(d, which) == name
     zero = np.zeros_like(b)
-    base = run(d, x, wt, zero, dy)
-    e_x, e_w, e_d = 2.0 ** -80, 2.0 ** 60, 2.0 ** -30
+    base = product(d, which, x, wt, zero, dy).astype(np.float64)
     f = np.float32
-    got = run(d, x * f(e_x), wt * f(e_w), zero, dy * f(e_d))
-    for a, e, scale in zip(got, base, (e_x * e_w, e_x * e_d, e_d, e_w * e_d)):
-        assert np.array_equal(a.astype(np.float64), e.astype(np.float64) * scale)
-    assert not np.any(run(d, x * f(0), wt, zero, dy)[0])  # an operand of zeros has no scale
+    e_x, e_w, e_d = 2.0 ** -80, 2.0 ** 60, 2.0 ** -5
+    got = product(d, which, x * f(e_x), wt * f(e_w), zero, dy * f(e_d))
+    assert np.array_equal(got.astype(np.float64), base * {FWD: e_x * e_w, FILTER: e_x * e_d, DATA: e_w * e_d}[which])
+    # an operand of zeros has no scale
+    assert not np.any(product(d, which, x * f(0), wt, zero, dy * f(0)))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,which,name", ONE_EACH)
+def test_denormal_operand(shape, which, name):
+    """An operand whose largest element is a denormal (few bits each, but exactly what the terms hold)."""
+    d, x, wt, b, dy = tensors(shape, 4250)
+    assert route(d, which) == name
+    tiny, big = np.float32(2.0 ** -134), np.float32(2.0 ** 90)
+    x, wt = (x * tiny, wt * big) if which != DATA else (x, wt * tiny)
+    dy = dy * big if which != FWD else dy
+    b = np.zeros_like(b)
+    assert_close(product(d, which, x, wt, b, dy), expected(d, which, x, wt, b, dy), TOL)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,which,name", [t for t in ONE_EACH if t[1] != FILTER])
+def test_an_image_does_not_depend_on_its_neighbours(shape, which, name):
+    """Bit for bit, whatever the magnitudes of the other images."""
+    d, x, wt, b, dy = tensors(shape, 4300)
+    assert route(d, which) == name
+    base = product(d, which, x, wt, b, dy)
+    big = np.float32(2.0 ** 60)
+    x[1] *= big
+    dy[1] *= big
+    got = product(d, which, x, wt, b, dy)
+    others = np.arange(d.n) != 1
+    assert np.array_equal(got[others], base[others])
+    if which == DATA:
+        assert np.array_equal(got[1], base[1] * big)
+
+
+def spread(a, axis, at, factor):
+    """a, with its elements `at` along the axis multiplied."""
+    out = a.copy()
+    index = [slice(None)] * a.ndim
+    index[axis] = at
+    out[tuple(index)] *= np.float32(factor)
+    return out
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,which,name", ONE_EACH)
+@pytest.mark.parametrize("case", ["contraction", "outputs", "one", "images"])
+def test_magnitudes_the_terms_do_not_carry(shape, which, name, case):
+    """Elements 2^-45 of the largest one under the same scale that carry the result, or a part of it: the pass then gives
+    what the float kernel gives, every part of the result to the float tolerance of its own largest element."""
+    d, x, wt, b, dy = tensors(shape, 4400)
+    assert route(d, which) == name
+    b = np.zeros_like(b)
+    far, back = 2.0 ** 45, 2.0 ** -45
+    parts = 1  # axis of the result whose entries are held each to its own magnitude
+    if case == "contraction":  # a large channel (map) that meets small weights
+        if which == FWD:
+            x, wt = spread(x, 1, 0, far), spread(wt, 1, 0, back)
+        elif which == DATA:
+            dy, wt = spread(dy, 1, 0, far), spread(wt, 0, 0, back)
+        else:  # a large image whose gradient is small
+            x, dy = spread(x, 0, 0, far), spread(dy, 0, 0, back)
+    elif case == "outputs":    # maps (channels) of the result far apart
+        if which == FWD:
+            wt = spread(wt, 0, 0, far)
+        elif which == DATA:
+            wt = spread(wt, 1, 0, far)
+        else:
+            dy, parts = spread(dy, 1, 0, far), 0
+    elif case == "one":        # one large element, which meets zeros
+        if which == FWD:
+            x[:, 0, 0, 0] = far
+            wt[:, 0] = 0
+        elif which == DATA:
+            dy[:, 0, 0, 0] = far
+            wt[0] = 0
+        else:
+            x[0, 0, 0, 0] = far
+            dy[0] = 0
+    elif which == FILTER:      # images far apart: in both operands
+        x, dy = spread(x, 0, 0, back), spread(dy, 0, 1, back)
+    else:
+        x, dy, parts = spread(x, 0, 0, far), spread(dy, 0, 0, far), 0
+    got, want = product(d, which, x, wt, b, dy), expected(d, which, x, wt, b, dy)
+    got, want = np.moveaxis(got, parts, 0), np.moveaxis(want, parts, 0)
+    for i in range(got.shape[0]):
+        assert_close(got[i], want[i], 2 * TOL, f"{case}: part {i}")
 
 
 @pytest.mark.gpu
 def test_non_finite_elements_stay_in_their_sums():
-    n, c, h, w, k, r, s, ph, pw = shape = SHAPES[3]
-    d, x, wt, b, dy = tensors(shape, 4300)
-    base = run(d, x, wt, b, dy)[0]
+    n, c, h, w, k, r, s, ph, pw = shape = SHAPES[3][0]
+    d, x, wt, b, dy = tensors(shape, 4500)
+    base = product(d, FWD, x, wt, b, dy)
     x[1, 7, 20, 20], x[5, 0, 3, 30] = np.inf, np.nan
-    y = run(d, x, wt, b, dy)[0]
+    y = product(d, FWD, x, wt, b, dy)
     touched = np.zeros(y.shape, bool)
     touched[1, :, 18:23, 18:23] = touched[5, :, 1:6, 28:33] = True
     assert not np.any(np.isfinite(y[touched]))
@@ -104,104 +253,116 @@ def test_non_finite_elements_stay_in_their_sums():
 
 
 @pytest.mark.gpu
-def test_a_workspace_of_the_float_route_still_runs():
-    d, x, wt, b, dy = tensors(SHAPES[4], 4400)
-    small = float_route_bytes(d)
-    assert small[0] == 0 < vcnn.conv_workspace_bytes(d, vcnn.PASS_FWD)
-    for got, want in zip(run(d, x, wt, b, dy, small), run(d, x, wt, b, dy)):
-        assert_close(got, want, 2 * TOL)
+@pytest.mark.parametrize("act", [vcnn.ACT_RELU, vcnn.ACT_TANH, vcnn.ACT_SIGMOID])
+@pytest.mark.parametrize("shape,which,name", [t for t in ONE_EACH if t[1] == DATA])
+def test_activation_derivative_of_declined_images(shape, which, name, act):
+    """The derivative of the activation below is applied once, to the images the float kernel computes as to the others."""
+    d, x, wt, b, dy = tensors(shape, 4550)
+    assert route(d, which) == name
+    dy[1, 0, 0, 0] = 2.0 ** 45
+    wt[0] = 0
+    y = np.tanh(x) * np.float32(0.7)
+    ref = {vcnn.ACT_RELU: y > 0, vcnn.ACT_TANH: 1 - y.astype(np.float64) ** 2,
+           vcnn.ACT_SIGMOID: y * (1 - y.astype(np.float64))}[act]
+    want = expected(d, which, x, wt, b, dy) * ref
+    yd, wd, dyd = (torch.from_numpy(a).to(DEV) for a in (y, wt, dy))
+    ws = torch.full((vcnn.conv_workspace_bytes(d, which),), 255, dtype=torch.uint8, device=DEV)
+    dx = torch.full(x.shape, float("nan"), device=DEV)
+    vcnn.conv_bwd_data_act(d, act, yd, wd, dyd, dx, ws)
+    dx = to_np(dx)
+    for i in range(d.n):
+        assert_close(dx[i], want[i], TOL, f"image {i}")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,which,name", ONE_EACH)
+def test_a_workspace_of_the_float_route_still_runs(shape, which, name):
+    d, x, wt, b, dy = tensors(shape, 4600)
+    small = float_bytes(d, which)
+    assert route(d, which) == name and small < vcnn.conv_workspace_bytes(d, which)
+    assert not vcnn.conv_route(d, which, small).startswith("two_term")
+    got, want = (product(d, which, x, wt, b, dy, nbytes) for nbytes in (small, None))
+    assert_close(got, want, 2 * TOL)
 
 
 @pytest.mark.gpu
 def test_batch_in_parts():
-    """A layer whose re-laid copies exceed what a pass asks for goes through its batch in parts (a ragged last one)."""
+    """A layer whose re-laid copies exceed what a pass asks for goes through its batch in parts (a ragged last one), where
+    the call brings a workspace for them; by its own query the forward pass and the input gradient run in float."""
     shape = (67, 64, 64, 64, 32, 5, 5, 2, 2)
     n, c, h, w, k, r, s, ph, pw = shape
-    d, x, wt, b, dy = tensors(shape, 4500)
-    small = float_route_bytes(d)
+    d, x, wt, b, dy = tensors(shape, 4700)
     need = [vcnn.conv_workspace_bytes(d, p) for p in range(3)]
-    assert need[0] == 0 and need[1] == small[1] <= vcnn.conv_bwd_filter_noalloc_limit()
-    whole = run(d, x, wt, b, dy, [256 << 20] * 3)
-    parts = run(d, x, wt, b, dy, [20 << 20, need[1], 20 << 20])
-    for got, want in zip(parts, whole):
-        assert_close(got, want, 2 * TOL)
-    for img in (0, 66):  # first and last image, whole planes
-        assert_close(parts[0][img:img + 1], O.conv_fwd(x[img:img + 1], wt, b, pad=(ph, pw)), TOL, "y")
-        assert_close(parts[3][img:img + 1], O.conv_bwd_data(wt, dy[img:img + 1], (h, w), pad=(ph, pw)), TOL, "dx")
+    assert need[FWD] == 0 and need[FILTER] <= vcnn.conv_bwd_filter_noalloc_limit()
+    assert [route(d, p) for p in range(2)] == ["implicit", IMPLICIT]
+    sizes = ([256 << 20] * 3, [20 << 20, need[FILTER], 40 << 20])
+    assert all(vcnn.conv_route(d, p, z[p]) == IMPLICIT for z in sizes for p in range(3))
+    x[40, 0, 0, 0], dy[66, 0, 0, 0] = 2.0 ** 45, 2.0 ** 45  # declined: in a part of its own, in the ragged last one
+    wt[:, 0, :, :], wt[0] = 0, 0
+    whole, parts = ([run_pass(d, p, x, wt, b, dy, z[p]) for p in range(3)] for z in sizes)
+    for p in (FWD, DATA):
+        for img in range(n):
+            assert_close(parts[p][img], whole[p][img], 2 * TOL)
+    for img in (0, 40, 66):
+        assert_close(parts[FWD][img:img + 1], O.conv_fwd(x[img:img + 1], wt, b, pad=(ph, pw)), TOL, "y")
+        assert_close(parts[DATA][img:img + 1], O.conv_bwd_data(wt, dy[img:img + 1], (h, w), pad=(ph, pw)), TOL, "dx")
     # the kernel gradient's route depends on the shape alone: the same bits whatever more a caller has
-    assert np.array_equal(parts[1], whole[1]) and np.array_equal(parts[2], whole[2])
+    assert all(np.array_equal(p, q) for p, q in zip(parts[FILTER], whole[FILTER]))
+    x[40, 0, 0, 0], dy[66, 0, 0, 0] = 1, 1  # (the same with nothing declined, against the float kernel)
+    got = run_pass(d, FILTER, x, wt, b, dy)
+    want = run_pass(d, FILTER, x, wt, b, dy, float_bytes(d, FILTER))
+    assert_close(got[0], want[0], 2 * TOL, "dw")
+    assert_close(got[1], want[1], 2 * TOL, "db")
+
+
+@pytest.mark.gpu
+def test_fold_in_parts():
+    """The transposed product in two parts, the second one image shorter; declined images in both."""
+    shape = (331, 357, 6, 11, 161, 6, 3, 0, 0)
+    d, x, wt, b, dy = tensors(shape, 4800)
+    assert route(d, DATA) == FOLD
+    dy[3, 0, 0, 0] = dy[330, 0, 0, 0] = 2.0 ** 45
+    wt[0] = 0
+    got = product(d, DATA, x, wt, b, dy)
+    for img in (0, 3, 165, 166, 329, 330):
+        assert_close(got[img:img + 1], O.conv_bwd_data(wt, dy[img:img + 1], (d.h, d.w)), TOL, f"image {img}")
 
 
 def test_the_query_asks_for_no_more_than_its_allowance():
     """No GPU needed: the workspace query of layers whose re-laid copies are large."""
     for shape in ((64, 64, 64, 64, 32, 5, 5, 2, 2), (512, 64, 64, 64, 64, 3, 3, 1, 1), (16, 38, 64, 64, 512, 16, 16, 0, 0)):
-        d = vcnn.conv_desc(*shape)
-        assert vcnn.conv_workspace_bytes(d, vcnn.PASS_FWD) <= 64 << 20
-    d = vcnn.conv_desc(*SHAPES[2])
-    assert 0 < vcnn.conv_workspace_bytes(d, vcnn.PASS_BWD_FILTER) <= vcnn.conv_bwd_filter_noalloc_limit()
+        assert vcnn.conv_workspace_bytes(vcnn.conv_desc(*shape), FWD) <= 64 << 20
+    d = vcnn.conv_desc(*SHAPES[9][0])
+    assert 0 < vcnn.conv_workspace_bytes(d, FILTER) <= vcnn.conv_bwd_filter_noalloc_limit()
 
 
-# layers whose input gradient is the transposed product on fragments: ragged maps (padded steps), a kernel matrix and planes
-# that end inside a tile, one channel per tile and several, rows that may and may not be folded side by side
-FOLD_SHAPES = [
-    (2, 46, 27, 27, 45, 9, 9, 2, 3),
-    (6, 83, 14, 10, 286, 9, 9, 0, 0),
-    (3, 40, 31, 33, 130, 5, 4, 0, 1),
-    (4, 19, 8, 62, 262, 7, 7, 3, 3),
-    (9, 60, 8, 8, 192, 5, 5, 2, 2),
-]
+# bfloat16 layers whose input gradient is the transposed product on fragments (AUTO takes it where a correlation would
+# leave the chip idle): ragged maps (padded steps), a kernel matrix and planes that end inside a tile, either order of adds
+FOLD_BF16_SHAPES = [(6, 83, 14, 10, 286, 9, 9, 0, 0), (9, 60, 8, 8, 192, 5, 5, 2, 2), (7, 29, 143, 11, 142, 12, 10, 0, 0)]
+
+
+@pytest.mark.parametrize("shape", FOLD_BF16_SHAPES)
+def test_routes_of_the_bf16_layers(shape):
+    assert route(vcnn.conv_desc(*shape, dtype=vcnn.BF16), DATA) == "fold_bf16"
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("dtype", [vcnn.F32, vcnn.BF16])
-@pytest.mark.parametrize("shape", FOLD_SHAPES)
-def test_input_gradient_on_fragments(shape, dtype):
-    """The transposed product from fragments, folded on chip (FOLD asks for it in float; AUTO takes it in bfloat16 where a
-    correlation would leave the chip idle), with and without the derivative of the activation below."""
+@pytest.mark.parametrize("shape", FOLD_BF16_SHAPES)
+def test_bf16_input_gradient_on_fragments(shape):
     n, c, h, w, k, r, s, ph, pw = shape
-    bf = dtype == vcnn.BF16
-    d = vcnn.conv_desc(n, c, h, w, k, r, s, ph, pw, dtype=dtype)
+    d = vcnn.conv_desc(n, c, h, w, k, r, s, ph, pw, dtype=vcnn.BF16)
     oh, ow = vcnn.conv_out_shape(d)
-    wt = bf16_round(random_tensor(4601, (k, c, r, s), scale=(2.0 / (k * r * s)) ** 0.5))
-    dy, x = bf16_round(random_tensor(4602, (n, k, oh, ow))), bf16_round(random_tensor(4603, (n, c, h, w)))
-    t = torch.bfloat16 if bf else torch.float32
-    wd, dyd, xd = (torch.from_numpy(a).to(DEV).to(t) for a in (wt, dy, x))
+    wt = bf16_round(random_tensor(4901, (k, c, r, s), scale=(2.0 / (k * r * s)) ** 0.5))
+    dy, x = bf16_round(random_tensor(4902, (n, k, oh, ow))), bf16_round(random_tensor(4903, (n, c, h, w)))
+    wd, dyd, xd = (torch.from_numpy(a).to(DEV).bfloat16() for a in (wt, dy, x))
     want = O.conv_bwd_data(wt, dy, (h, w), pad=(ph, pw))
-    try:
-        vcnn.set_conv_algo(vcnn.ALGO_AUTO if bf else vcnn.ALGO_FOLD)
-        need = vcnn.conv_workspace_bytes(d, vcnn.PASS_BWD_DATA)
-        ws = torch.empty(max(need, 256), dtype=torch.uint8, device=DEV)
-        dx = torch.full((n, c, h, w), float("nan"), dtype=t, device=DEV)
-        vcnn.conv_bwd_data(d, wd, dyd, dx, ws)
-        # (bfloat16: one rounding of the result to eight bits)
-        assert_close(to_np(dx.float()), want, 4e-3 if bf else TOL, "dx")
-        vcnn.conv_bwd_data_act(d, vcnn.ACT_RELU, xd, wd, dyd, dx, ws)
-        assert_close(to_np(dx.float()), np.where(x > 0, want, 0), 4e-3 if bf else TOL, "dx, ReLU below")
-    finally:
-        vcnn.set_conv_algo(vcnn.ALGO_AUTO)
-
-
-# 1 x 1 layers on fragments: whole and ragged tiles, odd planes (rows at any dword), padded slabs, split and whole sums
-POINTWISE_SHAPES = [(16, 512, 49, 49, 512), (13, 389, 53, 51, 401), (11, 250, 33, 20, 455), (7, 260, 45, 45, 300)]
-
-
-@pytest.mark.gpu
-@pytest.mark.parametrize("shape", POINTWISE_SHAPES)
-def test_pointwise_layers_on_fragments(shape):
-    n, c, h, w, k = shape
-    d, x, wt, b, dy = tensors((n, c, h, w, k, 1, 1, 0, 0), 4700)
-    vcnn.set_conv_algo(vcnn.ALGO_AUTO)
-    assert vcnn.conv_workspace_bytes(d, vcnn.PASS_BWD_DATA) > 0  # (the float route needs none)
-    y, dw, db, dx = run(d, x, wt, b, dy)
-    xm, dm = x.astype(np.float64).reshape(n, c, -1), dy.astype(np.float64).reshape(n, k, -1)
-    wm = wt.astype(np.float64).reshape(k, c)
-    assert_close(y.reshape(n, k, -1), wm @ xm + b[:, None].astype(np.float64), TOL, "y")
-    assert_close(dx.reshape(n, c, -1), wm.T @ dm, TOL, "dx")
-    assert_close(dw.reshape(k, c), (dm @ xm.transpose(0, 2, 1)).sum(0), TOL, "dw")
-    assert_close(db, dm.sum((0, 2)), TOL, "db")
-    small = run(d, x, wt, b, dy, float_route_bytes(d))
-    for got, want in zip(small, (y, dw, db, dx)):
-        assert_close(got, want, 2 * TOL)
+    assert route(d, DATA) == "fold_bf16"
+    ws = torch.full((vcnn.conv_workspace_bytes(d, DATA),), 255, dtype=torch.uint8, device=DEV)
+    dx = torch.full((n, c, h, w), float("nan"), dtype=torch.bfloat16, device=DEV)
+    vcnn.conv_bwd_data(d, wd, dyd, dx, ws)
+    assert_close(to_np(dx.float()), want, 4e-3, "dx")  # one rounding of the result to eight bits
+    vcnn.conv_bwd_data_act(d, vcnn.ACT_RELU, xd, wd, dyd, dx, ws)
+    assert_close(to_np(dx.float()), np.where(x > 0, want, 0), 4e-3, "dx, ReLU below")
 
 
 @pytest.mark.gpu
