@@ -13,14 +13,12 @@
 // depend on the images beside it; the kernel matrix has one, and so has either operand of the kernel gradient, whose sums
 // run over the images.  Under its scale an element keeps the 23 bits down to 2^-27 of the largest one and an absolute
 // error of 2^-36 (2^-50 of the largest) below that.  The re-laying passes count the elements they cannot keep to 21 bits
-// (below 2^-15 scaled); where they exceed one in 8192, the product is DECLINED: its
+// (below 2^-15 scaled); where they exceed one in 8192, or where an element is not finite, the product is DECLINED: its
 // blocks leave at once and the float kernel, enqueued behind it and otherwise leaving at once itself, computes the
 // image (any declined element of the kernel matrix or of a kernel gradient: all of it).  The decision stays on the device.
 // So rare small elements - one in 10^8 of normally distributed ones - cost nothing, and an operand whose elements span
 // more than the terms hold gives what the float kernel gives.
-//
-// Infinities and NaN: hi carries them (lo = 0), and the joined sum is hi's alone when that is not finite.  The scale is
-// taken from the finite elements.
+// An infinity would meet terms that are zero where the float is not, and the zeros that pad a tile.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -63,18 +61,19 @@ __device__ __forceinline__ uint32_t split_max(const uint32_t* partial, int block
   __syncthreads();
   return max(max(wave_max[0], wave_max[1]), max(wave_max[2], wave_max[3]));
 }
-// The exponent for a largest magnitude (a denormal one counts as 2^-126; zeros need no scale).
+// The exponent for a largest magnitude (a denormal one counts as 2^-126; zeros, and what is not finite, need no scale).
 __device__ __forceinline__ int split_exponent(uint32_t largest) {
-  return largest == 0 ? 0 : 14 - (max((int)(largest >> 23), 1) - 127);
+  return largest == 0 || largest >= 0x7f800000u ? 0 : 14 - (max((int)(largest >> 23), 1) - 127);
 }
 __device__ __forceinline__ void decline(const SplitScales& sc, int operand, int image) {
   *sc.any = 1;
   if (operand == 0) sc.image[image] = 1;
   else *sc.all = 1;
 }
-// One thread per scale: leaves it for the product.
+// One thread per scale: leaves it for the product, and declines what holds an element that is not finite.
 __device__ __forceinline__ void note_scale(const SplitScales& sc, int operand, int image, uint32_t largest) {
   sc.exponent[operand][operand == 0 ? image : 0] = split_exponent(largest);
+  if (largest >= 0x7f800000u) decline(sc, operand, image);
 }
 // Adds a thread's count of small elements; called by whole waves.  (Waves that have none, all of them on ordinary data,
 // touch nothing; a counter past its limit is left alone.)
@@ -109,17 +108,16 @@ struct SmallElements {
   }
 };
 
-// The two terms of v * 2^exponent as f16 bits: hi in the low half of the result, lo in the high half.
+// The two terms of v * 2^exponent (v finite) as f16 bits: hi in the low half of the result, lo in the high half.
 __device__ __forceinline__ uint32_t split_f16(float v, int exponent) {
   const float t = ldexpf(v, exponent);
   const _Float16 hi = (_Float16)t;
-  const float rest = (t - (float)hi) * 2048.f;
-  const _Float16 lo = (_Float16)(fabsf(t) < __builtin_inff() ? rest : 0.f);
+  const _Float16 lo = (_Float16)((t - (float)hi) * 2048.f);
   return (uint32_t)__builtin_bit_cast(uint16_t, hi) | ((uint32_t)__builtin_bit_cast(uint16_t, lo) << 16);
 }
 // The joined sum, still scaled.
 __device__ __forceinline__ float join_f16(float hi, float lo) {
-  return fabsf(hi) < __builtin_inff() ? fmaf(lo, 1.f / 2048.f, hi) : hi;
+  return fmaf(lo, 1.f / 2048.f, hi);
 }
 // Eight split elements as one 16-byte word per term.
 __device__ __forceinline__ void pack_terms(const uint32_t (&v)[8], uint4* hi, uint4* lo) {

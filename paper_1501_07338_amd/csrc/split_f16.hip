@@ -18,7 +18,7 @@ struct AbsMaxArgs {
   SplitScales sc;
 };
 
-// Largest finite magnitude of each block's share of the two operands, an image of
+// Largest magnitude (infinities and NaN above every finite one) of each block's share of the two operands, an image of
 // the first at a time; the first block of a scale clears its counter and its word.  Bandwidth: read once, 16 bytes per
 // load and four loads in flight per thread.
 __global__ __launch_bounds__(kThreads) void absmax_kernel(AbsMaxArgs a) {
@@ -38,10 +38,7 @@ __global__ __launch_bounds__(kThreads) void absmax_kernel(AbsMaxArgs a) {
   const uint4* const body = reinterpret_cast<const uint4*>(p + head);
   const int64_t quads = (count - head) / 4;
   uint32_t m = 0;
-  auto take = [&](uint32_t bits) {
-    bits &= 0x7fffffffu;
-    m = max(m, bits < 0x7f800000u ? bits : 0u);
-  };
+  auto take = [&](uint32_t bits) { m = max(m, bits & 0x7fffffffu); };
   const int64_t step = (int64_t)blocks * kThreads;
   int64_t i = (int64_t)block * kThreads + threadIdx.x;
   for (; i + 3 * step < quads; i += 4 * step) {

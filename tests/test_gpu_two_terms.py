@@ -1,6 +1,6 @@
 """The float products of larger layers from two half-precision terms per operand (the AUTO route of such layers): parity
 with the oracle at the edges of its tiles and arrangements, the scales, operands the terms do not carry (magnitudes too far
-apart), non-finite inputs, parts of a batch, and the float route in its place where the workspace is too small."""
+apart, infinities and NaN), parts of a batch, and the float route in its place where the workspace is too small."""
 import numpy as np
 import pytest
 import torch
@@ -171,18 +171,21 @@ def test_denormal_operand(shape, which, name):
 @pytest.mark.gpu
 @pytest.mark.parametrize("shape,which,name", [t for t in ONE_EACH if t[1] != FILTER])
 def test_an_image_does_not_depend_on_its_neighbours(shape, which, name):
-    """Bit for bit, whatever the magnitudes of the other images."""
+    """Bit for bit, whatever the magnitudes of the other images, also where one of those is not finite."""
     d, x, wt, b, dy = tensors(shape, 4300)
     assert route(d, which) == name
     base = product(d, which, x, wt, b, dy)
-    big = np.float32(2.0 ** 60)
-    x[1] *= big
-    dy[1] *= big
-    got = product(d, which, x, wt, b, dy)
-    others = np.arange(d.n) != 1
-    assert np.array_equal(got[others], base[others])
-    if which == DATA:
-        assert np.array_equal(got[1], base[1] * big)
+    for big in (np.float32(2.0 ** 60), np.float32(np.inf)):
+        x2, dy2 = x.copy(), dy.copy()
+        x2[1] *= big
+        dy2[1] *= big
+        with np.errstate(invalid="ignore"):
+            got = product(d, which, x2, wt, b, dy2)
+        others = np.arange(d.n) != 1
+        assert np.array_equal(got[others], base[others])
+        if np.isfinite(big) and which == DATA:
+            assert np.array_equal(got[1], base[1] * big)
+        assert np.isfinite(big) or not np.all(np.isfinite(got[1]))
 
 
 def spread(a, axis, at, factor):
@@ -240,16 +243,35 @@ def test_magnitudes_the_terms_do_not_carry(shape, which, name, case):
 
 
 @pytest.mark.gpu
-def test_non_finite_elements_stay_in_their_sums():
-    n, c, h, w, k, r, s, ph, pw = shape = SHAPES[3][0]
+@pytest.mark.parametrize("shape,which,name", ONE_EACH)
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan])
+def test_non_finite_elements_stay_in_their_sums(shape, which, name, value):
+    """One element of either operand is not finite: the sums it is part of are not, all others are what they were."""
     d, x, wt, b, dy = tensors(shape, 4500)
-    base = product(d, FWD, x, wt, b, dy)
-    x[1, 7, 20, 20], x[5, 0, 3, 30] = np.inf, np.nan
-    y = product(d, FWD, x, wt, b, dy)
-    touched = np.zeros(y.shape, bool)
-    touched[1, :, 18:23, 18:23] = touched[5, :, 1:6, 28:33] = True
-    assert not np.any(np.isfinite(y[touched]))
-    assert np.max(np.abs(y - base)[~touched]) <= 2 * TOL * np.max(np.abs(base))
+    assert route(d, which) == name
+    base = product(d, which, x, wt, b, dy)
+    first, second = {FWD: ("x", "w"), FILTER: ("x", "dy"), DATA: ("dy", "w")}[which]
+    for operand in (first, second):
+        t = {"x": x, "w": wt, "dy": dy}[operand]
+        # the last row of the last image / map: where runs of rows and tiles end
+        for at in ((t.shape[0] - 1, 1, t.shape[2] - 1, 0), (0, t.shape[1] - 1, 0, t.shape[3] - 1)):
+            mark = {"x": np.ones_like(x), "w": np.ones_like(wt), "dy": np.ones_like(dy)}
+            mark[operand] = np.zeros_like(t)
+            mark[operand][at] = 1
+            touched = expected(d, which, mark["x"], mark["w"], np.zeros_like(b), mark["dy"]) != 0
+            spoilt = {"x": x, "w": wt, "dy": dy}
+            spoilt[operand] = t.copy()
+            spoilt[operand][at] = value
+            got = product(d, which, spoilt["x"], spoilt["w"], b, spoilt["dy"])
+            # (a sum of zeros counts: the unrolled product also multiplies the rectified zeros of x)
+            assert not np.any(np.isfinite(got[touched]) & (got[touched] != 0) & (base[touched] != 0))
+            if operand == second:  # the border's zeros as well: nothing is said of its map's other sums
+                axis = 0 if which == FILTER else 1
+                others = tuple(q for q in range(4) if q != axis)
+                touched = np.broadcast_to(touched.any(axis=others, keepdims=True), touched.shape)
+            rest = ~touched
+            assert np.all(np.isfinite(got[rest]))
+            assert np.max(np.abs(got - base)[rest], initial=0) <= 2 * TOL * np.max(np.abs(base))
 
 
 @pytest.mark.gpu
