@@ -156,6 +156,13 @@ static double f32_seconds(double blocks, double tiles, double depth) {
   return std::max(std::ceil(blocks / 256.0), 1.6) * depth * 32.0 * tiles * 1.2 / 2.4e9;
 }
 
+// Output rows whose tap lies inside an image of h rows, on average over r taps (likewise columns).
+static double inside(int h, int r, int pad, int oh) {
+  int64_t rows = 0;
+  for (int q = 0; q < r; ++q) rows += std::max(0, std::min(oh, h + pad - q) - std::max(0, pad - q));
+  return (double)rows / r;
+}
+
 // Replaces the implicit float kernels by the two-term ones (split_f16.h) where these are faster: three products at the
 // half-precision rate instead of one at the float rate, for a scan of both operands and a re-laid copy of each.  On 100
 // drawn layers the estimates hold to about 20 %; 8 % are kept as margin.  (n c h w -> k r s, float
@@ -230,12 +237,18 @@ static void prefer_two_terms(const ConvGeom& g, int pass, size_t offered, Plan* 
   if (offered != kAsk && need > offered) return take_fold();
   const double est = f2.est_seconds + 12e-6 + kLeaveSeconds;
   if (pass == VCNN_PASS_BWD_FILTER) {
-    // variance of the rounding, in units of one float accumulation's: per output, (sums in a slice) + (slices)
+    // Variance of the rounding per output, in units of one accumulation's: (sums in a slice, the zero border's apart) +
+    // (sums of slices).  A unit of the two-term kernel, with the split's own error in its products, measures 4.7 of the
+    // float kernel's (110 drawn layers against 64 bits: its error is 0.43 to 0.90 of the float kernel's where this line
+    // takes them, up to 1.15 of it beyond).
     const HaloFilterPlan& h = p->hfp;
-    const double waves_k = 4 / (f2.filter.waves_m * f2.filter.waves_n), slices = (double)f2.filter.splits * f2.parts;
-    const double before = (double)g.N / h.splits / 2 + h.splits;
-    const double after = 16 + 0.56 * ((double)g.N / 16 / (slices * waves_k) + slices + waves_k);
-    if (after > before) return;
+    const double waves_k = 4 / (f2.filter.waves_m * f2.filter.waves_n);
+    auto slice_sums = [&](double slices) { return sum_slices_depth(slices, (double)g.M * (double)g.K); };
+    const double pixels = (double)g.n * inside(g.h, g.r, g.ph, g.oh) * inside(g.w, g.s, g.pw, g.ow);
+    const double in_slice = pixels / ((double)f2.filter.splits * f2.parts * waves_k);
+    const double before = pixels / h.splits / 2 + slice_sums(h.splits);
+    const double after = 16 + 0.56 * (in_slice / 16 + slice_sums(f2.filter.splits) + f2.parts + waves_k);
+    if (4.7 * after > before) return;
   }
   if (fold_s < est) return take_fold();
   if (est > 0.92 * f32) return;

@@ -25,11 +25,12 @@ SHAPES = [
     ((17, 41, 40, 37, 49, 5, 5, 2, 2), {FWD: IMPLICIT, DATA: IMPLICIT}),   # one map more than the 16-row tiles take
     ((23, 130, 30, 30, 64, 5, 5, 2, 2), {FWD: IMPLICIT, FILTER: IMPLICIT, DATA: IMPLICIT}),
     ((2, 89, 12, 33, 61, 9, 2, 2, 0), {FWD: IMPLICIT, DATA: IMPLICIT}),    # 65..128 rows in the input gradient
-    ((7, 29, 143, 11, 142, 12, 10, 0, 0), {FWD: IMPLICIT, FILTER: IMPLICIT}),  # several row tiles, a short last one
+    ((7, 29, 143, 11, 142, 12, 10, 0, 0), {FWD: IMPLICIT}),              # several row tiles, a short last one
+    ((2, 6, 36, 46, 244, 3, 4, 0, 0), {FILTER: IMPLICIT}),
     ((3, 26, 147, 147, 7, 1, 80, 0, 0), {FWD: IMPLICIT}),                # wide kernel
     ((2, 174, 27, 27, 300, 5, 5, 0, 0), {FWD: IMPLICIT}),                # four row groups side by side
     ((7, 19, 25, 42, 9, 7, 7, 3, 3), {FILTER: IMPLICIT}),                # short runs: waves without a share of one
-    ((16, 512, 57, 10, 20, 5, 5, 0, 0), {FWD: IMPLICIT, FILTER: IMPLICIT}),  # a last run of rows shorter than the waves' shares
+    ((9, 120, 62, 23, 5, 10, 3, 0, 0), {FILTER: IMPLICIT}),              # a last run shorter than the waves' shares
     ((4, 6, 41, 51, 36, 3, 14, 0, 0), {FILTER: IMPLICIT}),               # six channels: most of a group padding
     ((5, 5, 19, 47, 59, 10, 9, 0, 0), {FILTER: IMPLICIT}),
     ((2, 46, 27, 27, 45, 9, 9, 2, 3), {FWD: IMPLICIT, FILTER: IMPLICIT, DATA: FOLD}),
@@ -43,9 +44,11 @@ SHAPES = [
     ((13, 512, 47, 51, 512, 1, 1, 0, 0), {FWD: POINTWISE, FILTER: POINTWISE, DATA: POINTWISE}),  # split sums, padded slabs
 ]
 # one small layer of every pair of route and pass
-ONE_EACH = [(SHAPES[2][0], FWD, IMPLICIT), (SHAPES[5][0], DATA, IMPLICIT), (SHAPES[9][0], FILTER, IMPLICIT),
-            (SHAPES[10][0], FILTER, IMPLICIT), (SHAPES[14][0], DATA, FOLD), (SHAPES[16][0], DATA, FOLD),
-            (SHAPES[20][0], FWD, POINTWISE), (SHAPES[19][0], DATA, POINTWISE), (SHAPES[21][0], FILTER, POINTWISE)]
+ONE_EACH = [((11, 57, 33, 31, 38, 5, 7, 2, 3), FWD, IMPLICIT), ((2, 89, 12, 33, 61, 9, 2, 2, 0), DATA, IMPLICIT),
+            ((7, 19, 25, 42, 9, 7, 7, 3, 3), FILTER, IMPLICIT), ((9, 120, 62, 23, 5, 10, 3, 0, 0), FILTER, IMPLICIT),
+            ((2, 29, 30, 6, 100, 14, 4, 3, 2), DATA, FOLD), ((2, 62, 11, 24, 99, 4, 7, 2, 3), DATA, FOLD),
+            ((2, 395, 12, 33, 191, 1, 1, 0, 0), FWD, POINTWISE), ((11, 250, 33, 20, 455, 1, 1, 0, 0), DATA, POINTWISE),
+            ((13, 512, 47, 51, 512, 1, 1, 0, 0), FILTER, POINTWISE)]
 
 
 def tensors(shape, seed):
@@ -109,6 +112,14 @@ def float_bytes(d, which):
             assert e.status == vcnn.ERR_WORKSPACE
             low = mid
     return high
+
+
+@pytest.mark.parametrize("shape", [(244, 9, 17, 17, 82, 7, 7, 0, 0), (6, 61, 27, 27, 461, 16, 16, 0, 0),
+                                   (15, 314, 8, 12, 15, 9, 9, 4, 4), (20, 233, 8, 8, 325, 9, 9, 4, 4)])
+def test_kernel_gradients_that_round_less_in_float_stay_there(shape):
+    """No GPU needed: short sums in many slices, and planes that are mostly border, where the two-term kernel measured up to
+    1.15 of the float kernel's error against 64 bits."""
+    assert route(vcnn.conv_desc(*shape), FILTER) == "implicit"
 
 
 @pytest.mark.parametrize("shape,routes", SHAPES)
@@ -354,7 +365,7 @@ def test_the_query_asks_for_no_more_than_its_allowance():
     """No GPU needed: the workspace query of layers whose re-laid copies are large."""
     for shape in ((64, 64, 64, 64, 32, 5, 5, 2, 2), (512, 64, 64, 64, 64, 3, 3, 1, 1), (16, 38, 64, 64, 512, 16, 16, 0, 0)):
         assert vcnn.conv_workspace_bytes(vcnn.conv_desc(*shape), FWD) <= 64 << 20
-    d = vcnn.conv_desc(*SHAPES[9][0])
+    d = vcnn.conv_desc(*ONE_EACH[2][0])
     assert 0 < vcnn.conv_workspace_bytes(d, FILTER) <= vcnn.conv_bwd_filter_noalloc_limit()
 
 
@@ -388,13 +399,16 @@ def test_bf16_input_gradient_on_fragments(shape):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("dtype", [vcnn.F32, vcnn.BF16])
-def test_kernel_gradient_with_a_run_shorter_than_the_waves_shares(dtype):
+@pytest.mark.parametrize("dtype,name,shape", [(vcnn.F32, IMPLICIT, (9, 120, 62, 23, 5, 10, 3)),
+                                              (vcnn.BF16, "implicit_bf16", (16, 512, 57, 10, 20, 5, 5))])
+def test_kernel_gradient_with_a_run_shorter_than_the_waves_shares(dtype, name, shape):
     """A last run of output rows too short for every wave to get a slab, followed by the next image group in the same
     block: the waves without a share must not carry that run's fragments into the next one."""
-    n, c, h, w, k, r, s = 16, 512, 57, 10, 20, 5, 5
+    n, c, h, w, k, r, s = shape
     d = vcnn.conv_desc(n, c, h, w, k, r, s, dtype=dtype)
-    x, dy = bf16_round(random_tensor(4801, (n, c, h, w))), bf16_round(random_tensor(4802, (n, k, h - 4, w - 4)))
+    assert route(d, FILTER) == name
+    x = bf16_round(random_tensor(4801, (n, c, h, w)))
+    dy = bf16_round(random_tensor(4802, (n, k, h - r + 1, w - s + 1)))
     t = torch.bfloat16 if dtype == vcnn.BF16 else torch.float32
     xd, dyd = (torch.from_numpy(a).to(DEV).to(t) for a in (x, dy))
     dw, db = torch.full((k, c, r, s), float("nan"), device=DEV), torch.full((k,), float("nan"), device=DEV)
