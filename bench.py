@@ -192,13 +192,13 @@ def run_workload(name, steps, warmup, layer_iters=10, algos=None, phase_prefix=N
         routed = lambda call, li=li: ts._routed(li, call)  # the layer's own route choice, if it has one
         passes = {
             "fwd": lambda: routed(lambda: vcnn.conv_fwd(d, a_in, w, b, y_buf, ts.workspace)),
-            "bwd_filter": lambda: routed(lambda: vcnn.conv_bwd_filter(d, a_in, dy, dw, db, ts.workspace_side)),
+            "bwd_filter": lambda: routed(lambda: vcnn.conv_bwd_filter(d, a_in, dy, dw, db, ts.workspace)),
             "bwd_data": lambda: routed(lambda: vcnn.conv_bwd_data(d, w, dy, dx_buf, ts.workspace)),
         }
         in_b = esize * g["n"] * g["c"] * g["h"] * g["w"]
         out_b = esize * g["M"] * g["N"]
         w_b = esize * g["M"] * g["K"]
-        ws_need = routed(lambda: max(vcnn.conv_workspace_bytes(d, p) for p in (vcnn.PASS_FWD, vcnn.PASS_BWD_DATA)))
+        ws_need = routed(lambda: max(vcnn.conv_workspace_bytes(d, p) for p in range(3)))
         assert ts.workspace.numel() >= ws_need
         for pname, fn in passes.items():
             mark(f"{phase_prefix or name}.conv{li}.{pname}")
@@ -539,7 +539,7 @@ def main():
                    "timing": "each step between its own event pair on the launch stream, mean of the K steps; the seeded "
                              "parameters are restored before every step outside the pair",
                    "float_products": "larger layers: three f16 matrix-core products per float product (each operand two f16 terms "
-                                     "scaled by powers of two, 24 bits, fp32 accumulation); others: the float instruction",
+                                     "scaled by powers of two, 23 bits, fp32 accumulation); others: the float instruction",
                    "loss_first_step": main_res["loss_first_step"]},
         "conv_gflops_fwd_bwd": main_res["conv_gflops_fwd_bwd"],
         "conv_pct_mfma_peak": main_res["conv_pct_mfma_peak"],

@@ -63,23 +63,23 @@ class TrainStep:
                 d = vcnn.conv_desc(ishape[0], ishape[1], ishape[2], ishape[3], L.cout, L.kh, L.kw, L.pad_h, L.pad_w,
                                    dtype=dtype, act=vcnn.ACT_RELU if L.relu else vcnn.ACT_NONE)
                 self.descs[li] = d
-                # (a first layer's filter gradient has no input gradient to overlap with and runs on the main stream)
                 need = self._routed(li, lambda: [vcnn.conv_workspace_bytes(d, p)
                                                  for p in (vcnn.PASS_FWD, vcnn.PASS_BWD_DATA, vcnn.PASS_BWD_FILTER)])
                 ws_bytes = max(ws_bytes, *need)
-                ws_side_bytes = max(ws_side_bytes, need[2])
             elif isinstance(L, Pool):
                 self.descs[li] = vcnn.pool_desc(ishape[0], ishape[1], ishape[2], ishape[3], L.win, L.win, L.stride,
                                                 L.stride, dtype=dtype)
             if getattr(L, "relu", False):  # gradient w.r.t. the pre-activation, read by both strands
                 self.dpre[li] = torch.empty(net.shapes[li], **act)
-            if isinstance(L, Conv) and self.side is not None:
+            # (a first layer's kernel gradient has no input gradient to overlap with and runs on the main stream)
+            if isinstance(L, Conv) and self.side is not None and (li > 0 or first_layer_dx):
                 # a fork pays from about half a GFLOP of kernel gradient on: below, the events and the join cost the
                 # host and the chain more than the overlap returns (whole pass, two streams / one: cfg3 at batch 32,
                 # 0.37 GFLOP, 206 / 180 us; at batch 128, 1.5 GFLOP, 266 / 273 us; cfg2 at batch 16 129 / 91 us)
                 oshape = net.shapes[li]
                 if 2.0 * L.cout * ishape[1] * L.kh * L.kw * oshape[0] * oshape[2] * oshape[3] >= 5e8:
                     self.forked[li] = torch.cuda.Event()
+                    ws_side_bytes = max(ws_side_bytes, need[2])
         self.workspace = torch.empty(max(ws_bytes, 256), dtype=torch.uint8, device=self.dev)
         self.workspace_side = torch.empty(max(ws_side_bytes, 256), dtype=torch.uint8, device=self.dev)
         if dtype == vcnn.BF16 and net.loss == "softmax":  # the cost works on float logits

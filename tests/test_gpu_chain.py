@@ -325,3 +325,12 @@ def test_step_with_split_products_on_the_large_layer():
     torch.cuda.synchronize()
     again = [t for pair in split.grads if pair is not None for t in pair] + [split.loss]
     assert all(torch.equal(a, b) for a, b in zip(eager, again))
+
+
+@pytest.mark.parametrize("name,batch,forks", [("cfg2", 16, False), ("cfg4", 8, True)])
+def test_second_workspace_is_sized_by_the_layers_that_use_it(name, batch, forks):
+    net = wl.make_net(name, batch)
+    ts = TrainStep(net, wl.make_params(net), wl.make_inputs(net), device=DEV)
+    need = [vcnn.conv_workspace_bytes(ts.descs[li], vcnn.PASS_BWD_FILTER) for li in ts.forked]
+    assert bool(need) == forks and 0 not in ts.forked
+    assert ts.workspace_side.numel() == max([256, *need])
