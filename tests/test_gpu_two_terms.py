@@ -309,6 +309,38 @@ def test_activation_derivative_of_declined_images(shape, which, name, act):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("shape,which,name", ONE_EACH)
+def test_recorded_call_decides_anew_on_every_replay(shape, which, name):
+    """A recorded pass on ordinary, far apart, non-finite and again ordinary data, with eager work between the replays."""
+    d, x, wt, b, dy = tensors(shape, 4570)
+    assert route(d, which) == name
+    xd, wd, bd, dyd = (torch.from_numpy(a).to(DEV) for a in (x, wt, b, dy))
+    ws = torch.empty(vcnn.conv_workspace_bytes(d, which), dtype=torch.uint8, device=DEV)
+    out = torch.empty({FWD: dy, FILTER: wt, DATA: x}[which].shape, device=DEV)
+    call = {FWD: lambda: vcnn.conv_fwd(d, xd, wd, bd, out, ws), DATA: lambda: vcnn.conv_bwd_data(d, wd, dyd, out, ws),
+            FILTER: lambda: vcnn.conv_bwd_filter(d, xd, dyd, out, None, ws)}[which]
+    call()
+    torch.cuda.synchronize()
+    stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        call()
+    moved = {FWD: xd, FILTER: xd, DATA: dyd}[which]
+    first = moved.clone()
+    for value in (None, 2.0 ** 45, None, np.inf, np.nan, None):
+        moved.copy_(first)
+        if value is not None:
+            moved[-1, -1, -1, -1] = value
+        ws.fill_(255)
+        graph.replay()
+        torch.cuda.synchronize()
+        got = out.clone()
+        assert np.isfinite(torch.randn(1 << 16, device=DEV).sum().item())  # unrelated eager work between replays
+        call()
+        torch.cuda.synchronize()
+        assert torch.equal(torch.nan_to_num(got, 7.0, 8.0, 9.0), torch.nan_to_num(out, 7.0, 8.0, 9.0))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,which,name", ONE_EACH)
 def test_a_workspace_of_the_float_route_still_runs(shape, which, name):
     d, x, wt, b, dy = tensors(shape, 4600)
     small = float_bytes(d, which)
