@@ -101,8 +101,10 @@ vcnn_status vcnn_set_conv_algo(int32_t algo);
 /* Output size of the layer of Eq. 1: oh = (h + 2*pad_h - r)/stride_h + 1, likewise ow. */
 vcnn_status vcnn_conv_out_shape(const vcnn_conv_desc* d, int32_t* oh, int32_t* ow);
 /* Bytes of workspace the given pass needs for this descriptor (may be 0).  A call that brings less may still run, by a
- * slower route that needs less; a forward pass or input gradient that brings more than it asks for may use it to work
- * on more of the batch at once. */
+ * slower route that needs less.  Where the re-laid operands of an fp32 forward pass or input gradient exceed 64 MiB the
+ * query asks for the float kernel's workspace only (often 0), and a call that brings just that runs it; one that brings
+ * more (64 MiB will do) takes the two-term kernels and works through the batch in parts:
+ * vcnn_conv_route tells what a size buys. */
 vcnn_status vcnn_conv_workspace_bytes(const vcnn_conv_desc* d, int32_t pass, size_t* bytes);
 /* The route the given pass takes with that many bytes of aligned workspace, under the present VCNN_ALGO_* choice, as a
  * short static string (for diagnostics and tests): "two_term", "two_term_fold" and "two_term_pointwise" are the fp32

@@ -143,9 +143,6 @@ static size_t two_term_allowance(int pass, size_t own) {
 static size_t pointwise_allowance(int pass, size_t own) {
   return pass == VCNN_PASS_BWD_FILTER && own <= kScratchBytes ? kScratchBytes : (size_t)384 << 20;
 }
-// A launch of a float kernel behind a two-term product, whose blocks leave at once where nothing is left to them: it adds
-// 2 us (128 32 15 15 -> 32 5 5) to 4.5 us (16 512 49 49 -> 512 1 1) to a pass; it decides about the smaller layers.
-static constexpr double kLeaveSeconds = 2.5e-6;
 static constexpr size_t kAsk = ~(size_t)0;  // make_plan: plan for the workspace query, not for a given workspace
 
 // Estimated time of a float matrix-core kernel, in seconds: `blocks` blocks of four waves, each wave `tiles` accumulator
@@ -166,13 +163,16 @@ static double inside(int h, int r, int pad, int oh) {
 // Replaces the implicit float kernels by the two-term ones (split_f16.h) where these are faster: three products at the
 // half-precision rate instead of one at the float rate, for a scan of both operands and a re-laid copy of each.  On 100
 // drawn layers the estimates hold to about 20 %; 8 % are kept as margin.  (n c h w -> k r s, float
-// kernel / two-term: 16 38 64 64 -> 512 16 16 forward 3.20 / 1.13 ms, kernel gradient 3.13 / 0.95 ms; 64 64 64 64 -> 32
-// 5 5 0.284 / 0.121 and 0.341 / 0.161 ms, input gradient 0.277 / 0.113 ms; 2 41 47 11 -> 137 3 3, 0.08 GFLOP: 11 /
-// 29 us, stays.)  The error against 64 bits is smaller than that of the kernel it replaces: the float instruction rounds
-// a sum once per two elements, the two-term one once per sixteen - 1.25e-8 sqrt(K) against 3.3e-9 sqrt(K) beside 7e-8
-// of the split itself; in the kernel gradient, whose sums are cut in slices, the count of roundings decides.
+// kernel / two-term: 16 38 64 64 -> 512 16 16 forward 3.19 / 1.06 ms, kernel gradient 3.11 / 0.96 ms; 64 64 64 64 -> 32
+// 5 5 0.287 / 0.120 and, in four parts, 0.343 / 0.207 ms, input gradient 0.266 / 0.113 ms; 128 32 15 15 -> 32 5 5 forward
+// 32 / 27 us; 2 41 47 11 -> 137 3 3, 0.08 GFLOP: 11 us, stays.)  The error against 64 bits measures no larger than that of
+// the kernel it replaces (350 drawn layers: forward 0.16 to 0.89 of it, input gradient 0.24 to 1.00): the float instruction
+// rounds a sum once per two elements, the two-term one once per sixteen - 1.25e-8 sqrt(K) against 3.3e-9 sqrt(K) beside
+// 7e-8 of the split itself; in the kernel gradient, whose sums are cut in slices, the count of roundings decides.
 //
-// The float kernel stays enqueued behind the product, for the images the terms do not carry (split_f16.h).
+// The float kernel stays enqueued behind the product, for the images the terms do not carry (split_f16.h): 2 to 4.5 us a
+// pass, which the margin covers (counted with 2.5 us, three layers at the line went back to float: 128 -> 158, 162 -> 184
+// and 301 -> 330 us a pass).
 //
 // `offered`: the workspace the call has (kAsk: the query).  A call whose workspace only holds the float route's partial
 // sums runs that route, as it always has.
@@ -186,7 +186,6 @@ static void prefer_two_terms(const ConvGeom& g, int pass, size_t offered, Plan* 
     const double rows = fwd ? (double)g.k : (double)g.c, depth = (double)(fwd ? g.c : g.k) * g.r * g.s;
     const double blocks = std::ceil(rows / p->hp.bm) * (double)g.n * (double)p->hp.tiles_per_img;
     f32 += 1.3 * f32_seconds(blocks, (double)p->hp.bm * p->hp.bn / 4096.0, depth);
-    if (depth < 64) return;
   } else if (p->path == PATH_FOLD) {
     // (as fold_beats_halo has it, per tile)
     f32 += (double)g.n * p->fold.tiles_i * p->fold.tiles_j * (4.1e-6 * (double)ceil_div(g.M, 16) + 8e-6) / 1024.0;
@@ -196,6 +195,12 @@ static void prefer_two_terms(const ConvGeom& g, int pass, size_t offered, Plan* 
     f32 += (h.bm <= 32 ? 1.3 : 0.95) * f32_seconds(blocks, (double)h.bm * h.bnk / 4096.0, (double)g.N / h.splits) + 2.0 * (double)h.partial_bytes / 4e12;
   } else {
     return;
+  }
+  if (pass != VCNN_PASS_BWD_FILTER) {
+    // terms of a sum that do not meet the zero border, on average: sums this short round less in float than the split
+    // leaves (96 terms: 0.89 of the float kernel's error, 20 terms: 1.49 times)
+    const double rows = g.r * inside(g.h, g.r, g.ph, g.oh), cols = g.s * inside(g.w, g.s, g.pw, g.ow);
+    if ((pass == VCNN_PASS_FWD ? g.c * rows * cols / (double)g.P : g.k * rows * cols / ((double)g.h * g.w)) < 80) return;
   }
   // (what the launches, the scans and three products at the best rate take at least; the fold's launches alone 16 us:
   // smaller layers are not worth planning for on every call)
@@ -208,8 +213,6 @@ static void prefer_two_terms(const ConvGeom& g, int pass, size_t offered, Plan* 
   if (pass == VCNN_PASS_BWD_DATA && bwd_data_fold_frag_plan(g, 2, std::max(own, two_term_allowance(pass, own)), &ff) &&
       (offered == kAsk || ff.workspace_bytes <= offered))
     fold_s = 1.05 * ff.est_seconds + 3e-6;
-  // (the float kernel behind the product leaves at once on ordinary data; one per part in the fold)
-  if (fold_s < 1e9) fold_s += kLeaveSeconds * (double)ceil_div(g.n, ff.images);
   auto take_fold = [&] {
     if (fold_s > 0.92 * f32) return;
     p->path = PATH_FOLD_FRAG;
@@ -235,20 +238,19 @@ static void prefer_two_terms(const ConvGeom& g, int pass, size_t offered, Plan* 
   const size_t need = std::max(align256(f2.workspace_bytes), behind_at + p->workspace_bytes) + bias;
   if (pass == VCNN_PASS_BWD_FILTER && need > ask) return;
   if (offered != kAsk && need > offered) return take_fold();
-  const double est = f2.est_seconds + 12e-6 + kLeaveSeconds;
+  const double est = f2.est_seconds + 12e-6;
   if (pass == VCNN_PASS_BWD_FILTER) {
-    // Variance of the rounding per output, in units of one accumulation's: (sums in a slice, the zero border's apart) +
-    // (sums of slices).  A unit of the two-term kernel, with the split's own error in its products, measures 4.7 of the
-    // float kernel's (110 drawn layers against 64 bits: its error is 0.43 to 0.90 of the float kernel's where this line
-    // takes them, up to 1.15 of it beyond).
+    // Variance of the error of an output against 64 bits, in units of 2e-16 of the output's own: what the products leave,
+    // the sums in a slice (the zero border's apart), the sums of slices.  Fitted to 170 drawn layers; where this line takes
+    // the two-term kernel its error measures 0.37 to 0.97 of the float kernel's, beyond it up to 1.5 (139 32 15 15 -> 32 5 5 0.8
+    // to 1.0, 139 32 7 7 -> 64 5 5 1.1 to 1.2: these stay in float, which costs them 0 to 15 us).
     const HaloFilterPlan& h = p->hfp;
-    const double waves_k = 4 / (f2.filter.waves_m * f2.filter.waves_n);
-    auto slice_sums = [&](double slices) { return sum_slices_depth(slices, (double)g.M * (double)g.K); };
+    const double waves_k = 4 / (f2.filter.waves_m * f2.filter.waves_n), parts = f2.parts, splits = f2.filter.splits;
     const double pixels = (double)g.n * inside(g.h, g.r, g.ph, g.oh) * inside(g.w, g.s, g.pw, g.ow);
-    const double in_slice = pixels / ((double)f2.filter.splits * f2.parts * waves_k);
-    const double before = pixels / h.splits / 2 + slice_sums(h.splits);
-    const double after = 16 + 0.56 * (in_slice / 16 + slice_sums(f2.filter.splits) + f2.parts + waves_k);
-    if (4.7 * after > before) return;
+    auto slice_sums = [&](double slices) { return 1.75 * sum_slices_depth(slices, (double)g.M * (double)g.K); };
+    const double before = 12 + pixels / h.splits / 2 + slice_sums(h.splits);
+    const double after = 32 + 3.3 * pixels / (splits * parts * waves_k) / 16 + slice_sums(splits) + 1.75 * parts + 5 * waves_k;
+    if (after > 0.8 * before) return;
   }
   if (fold_s < est) return take_fold();
   if (est > 0.92 * f32) return;
@@ -258,8 +260,8 @@ static void prefer_two_terms(const ConvGeom& g, int pass, size_t offered, Plan* 
   p->workspace_bytes = need - bias;
 }
 
-// The same for the unpadded 1 x 1 layers (16 512 49 49 -> 512: see pointwise_f16.hip; 11 50 20 20 -> 455 input gradient 38 ->
-// 30 us, 11 296 56 12 -> 39 forward 28 against 31, stays).  The float product kernels take 1.0 to 1.3 times the estimate,
+// The same for the unpadded 1 x 1 layers (16 512 49 49 -> 512: see pointwise_f16.hip; 11 50 20 20 -> 455 input gradient, 38
+// us, and 11 296 56 12 -> 39 forward, 28 us, stay).  The float product kernels take 1.0 to 1.3 times the estimate,
 // the two-term ones 0.9 to 1.1 times theirs.
 static void prefer_pointwise_f16(const ConvGeom& g, int pass, size_t offered, Plan* p) {
   if (p->path != PATH_POINTWISE && !(p->path == PATH_HALO_FILTER && is_pointwise(g))) return;
@@ -278,7 +280,7 @@ static void prefer_pointwise_f16(const ConvGeom& g, int pass, size_t offered, Pl
   const size_t behind_at = split_scales_bytes(filter ? 1 : g.n);
   const size_t need = std::max(align256(q.workspace_bytes), behind_at + p->workspace_bytes) + bias;
   if (need > std::max(own, pointwise_allowance(pass, own)) || (offered != kAsk && need > offered)) return;
-  if (1.05 * q.est_seconds + kLeaveSeconds > 0.92 * f32) return;
+  if (1.05 * q.est_seconds > 0.92 * f32) return;
   p->behind = p->path, p->behind_at = behind_at;
   p->path = PATH_POINTWISE_F16;
   p->pw16 = q;

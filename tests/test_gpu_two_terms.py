@@ -122,6 +122,13 @@ def test_kernel_gradients_that_round_less_in_float_stay_there(shape):
     assert route(vcnn.conv_desc(*shape), FILTER) == "implicit"
 
 
+def test_sums_that_mostly_meet_the_border_stay_in_float():
+    """No GPU needed: an input gradient whose 330 terms meet the zero border but for twenty, where the split alone leaves 1.5
+    times the float kernel's error; the same kernel on a wider plane takes the terms."""
+    assert route(vcnn.conv_desc(101, 235, 34, 34, 10, 1, 33), DATA) == "implicit"
+    assert route(vcnn.conv_desc(101, 235, 34, 120, 10, 1, 33), DATA) == IMPLICIT
+
+
 @pytest.mark.parametrize("shape,routes", SHAPES)
 def test_routes_of_the_tested_layers(shape, routes):
     """No GPU needed: each pass below really is planned as a two-term product."""
@@ -399,6 +406,27 @@ def test_the_query_asks_for_no_more_than_its_allowance():
         assert vcnn.conv_workspace_bytes(vcnn.conv_desc(*shape), FWD) <= 64 << 20
     d = vcnn.conv_desc(*ONE_EACH[2][0])
     assert 0 < vcnn.conv_workspace_bytes(d, FILTER) <= vcnn.conv_bwd_filter_noalloc_limit()
+
+
+def test_queries_and_routes_agree():
+    """No GPU needed: over drawn layers every pass runs with exactly what its query asks for and with more, the kernel
+    gradient by the same route; and the allocation-free entry point takes each layer whose float route fits it."""
+    rng, seen = np.random.default_rng(5), set()
+    log = lambda lo, hi: int(round(np.exp(rng.uniform(np.log(lo), np.log(hi)))))
+    for _ in range(400):
+        r, s = (1, 1) if rng.random() < 0.2 else (log(1, 20), log(1, 20))
+        d = vcnn.conv_desc(log(1, 400), log(5, 512), log(r, 100), log(s, 100), log(5, 512), r, s)
+        for which in (FWD, FILTER, DATA):
+            need = vcnn.conv_workspace_bytes(d, which)
+            name = vcnn.conv_route(d, which, need)
+            seen.add((which, name))
+            for more in (need + 256, need + (64 << 20)):
+                other = vcnn.conv_route(d, which, more)
+                assert which != FILTER or other == name
+            if name.startswith("two_term") and which == FILTER:
+                limit = vcnn.conv_bwd_filter_noalloc_limit()
+                assert (need <= limit) == (float_bytes(d, which) <= limit)
+    assert {(FWD, IMPLICIT), (FILTER, IMPLICIT), (DATA, IMPLICIT), (DATA, FOLD), (FWD, "implicit")} <= seen
 
 
 # bfloat16 layers whose input gradient is the transposed product on fragments (AUTO takes it where a correlation would
