@@ -108,7 +108,7 @@ def main():
         rows = load_trace(args.trace)
         ph = phases_of(rows, markers, "Kernel_Name", "grid")
         out = [f"rocprofv3 kernel trace by benchmark phase: {args.name}, one MI355X (source tree at commit {head})", "",
-               "command (from the repository root on the GPU box):",
+               "command (from the repository root):",
                f"  rocprofv3 --kernel-trace --stats --output-format csv -d <dir> -o p -- python3 bench.py {args.cmd}",
                "Each phase is one convolution pass called back to back (one untimed call, then the timed ones); durations in",
                "microseconds per dispatch.  'per call' = sum over the pass's kernels of their dispatches per call x average.", ""]
