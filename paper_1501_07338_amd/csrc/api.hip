@@ -625,7 +625,6 @@ static vcnn_status conv_fwd_linear(const vcnn_conv_desc* d, const ConvGeom& g, c
   a.relu = relu;
   if (plan.path == PATH_POINTWISE_F16) {
     if (vcnn_status s = launch_pointwise_f16(plan.pw16, g, VCNN_PASS_FWD, (const float*)w, (const float*)x, bias, (float*)y, relu, workspace, st)) return s;
-    a.only = split_declined(workspace, g.n);
   }
   if (plan.path == PATH_POINTWISE || plan.path == PATH_POINTWISE_F16 || plan.path == PATH_POINTWISE_BF16) {
     // patch matrix == input: B(k, j) = x[n][k][p]
@@ -636,7 +635,7 @@ static vcnn_status conv_fwd_linear(const vcnn_conv_desc* d, const ConvGeom& g, c
     a.B = workspace;
     a.b_sk = g.N, a.b_sj = 1, a.b_P = 0, a.b_simg = 0;
   }
-  return launch_gemm_f32(a, st);
+  return launch_gemm_f32(a, st, plan.path == PATH_POINTWISE_F16 ? split_declined(workspace, g.n) : Declined{});
 }
 
 vcnn_status vcnn_conv_bwd_filter(const vcnn_conv_desc* d, const void* x, const void* dy, float* dw, float* dbias,
@@ -754,8 +753,7 @@ static vcnn_status conv_bwd_data_impl(const vcnn_conv_desc* d, int act_below, co
     a.c_si = g.P, a.c_sj = 1, a.c_P = (int)g.P, a.c_simg = g.K * g.P;
     if (plan.path == PATH_POINTWISE_F16) {
       if (vcnn_status s = launch_pointwise_f16(plan.pw16, g, VCNN_PASS_BWD_DATA, (const float*)w, (const float*)dy, nullptr, (float*)dx, 0, workspace, st)) return s;
-      a.only = split_declined(workspace, g.n);
-      return then_act(launch_gemm_f32(a, st));
+      return then_act(launch_gemm_f32(a, st, split_declined(workspace, g.n)));
     }
     a.dact = da, a.dact_ref = ref;
     return launch_gemm_f32(a, st);

@@ -84,10 +84,9 @@ struct GemmArgs {
   const void* dact_ref;
   // optional, small products only: the row sums of A, sum_k A(i,k), written to row_sums[i]
   float* row_sums;
-  // optional, tiled kernel only (c_P > 0: columns are images of c_P): only the images a two-term product left to this one
-  Declined only;
 };
-vcnn_status launch_gemm_f32(const GemmArgs& a, hipStream_t st);
+// only (c_P > 0: columns are images of c_P): the images a two-term product left to this one
+vcnn_status launch_gemm_f32(const GemmArgs& a, hipStream_t st, const Declined& only = {});
 // true if launch_gemm_f32 takes the small-product kernel (one 32 x 32 tile per block, contraction split over waves)
 bool gemm_is_small(const GemmArgs& a);
 // The weight-gradient (gw) and input-gradient (gx) products of a fully connected layer in one launch; both small.

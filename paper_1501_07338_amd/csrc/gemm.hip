@@ -39,7 +39,7 @@ __device__ __forceinline__ int xcd_remap(int bid, int total) {
 
 // TI: element type of A and B in memory (float or bf16); TO: element type of C.  All arithmetic is fp32.
 template <int BM, int BN, int BK, int WM, int WN, bool A_KC, bool B_KC, bool A_VEC, bool B_VEC, typename TI, typename TO>
-__global__ __launch_bounds__(kThreads, BK == 16 ? 4 : 1) void gemm_f32_kernel(GemmArgs a, int tiles_m, int tiles_total) {
+__global__ __launch_bounds__(kThreads, BK == 16 ? 4 : 1) void gemm_f32_kernel(GemmArgs a, int tiles_m, int tiles_total, Declined only) {
   static_assert((BM / WM) * (BN / WN) * 64 == kThreads, "four waves per block");
   using LA = LdsTile<BM, BK, A_KC>;
   using LB = LdsTile<BN, BK, B_KC>;
@@ -60,9 +60,9 @@ __global__ __launch_bounds__(kThreads, BK == 16 ? 4 : 1) void gemm_f32_kernel(Ge
   const int tile = xcd_remap(blockIdx.x, tiles_total);
   const int i0 = (tile % tiles_m) * BM;
   const int j0 = (tile / tiles_m) * BN;
-  if (a.only.any) {
+  if (only.any) {
     bool some = false;
-    for (int n = j0 / a.c_P; n <= (min(j0 + BN, a.N) - 1) / a.c_P; ++n) some |= is_declined(a.only, n);
+    for (int n = j0 / a.c_P; n <= (min(j0 + BN, a.N) - 1) / a.c_P; ++n) some |= is_declined(only, n);
     if (!some) return;
   }
   const int wm0 = (wave % (BM / WM)) * WM;
@@ -167,7 +167,7 @@ __global__ __launch_bounds__(kThreads, BK == 16 ? 4 : 1) void gemm_f32_kernel(Ge
 #pragma unroll
   for (int ni = 0; ni < TN; ++ni) {
     const int j = j0 + wn0 + ni * 32 + l32;
-    if (j >= a.N || (a.only.any && !is_declined(a.only, j / a.c_P))) continue;
+    if (j >= a.N || (only.any && !is_declined(only, j / a.c_P))) continue;
     const int64_t cj = jmap(j, a.c_P, a.c_simg, a.c_sj);
 #pragma unroll
     for (int mi = 0; mi < TM; ++mi)
@@ -202,50 +202,50 @@ static void allow_lds(K kernel, size_t bytes, bool& done) {
 }
 
 template <int BM, int BN, int BK, int WM, int WN, bool A_KC, bool B_KC, bool A_VEC, bool B_VEC, typename TI, typename TO>
-static void launch_one(const GemmArgs& a, hipStream_t st) {
+static void launch_one(const GemmArgs& a, hipStream_t st, const Declined& only) {
   const int tiles_m = (int)ceil_div(a.M, BM);
   const int64_t blocks = (int64_t)tiles_m * ceil_div(a.N, BN);
   const size_t lds = gemm_lds_bytes<BM, BN, BK, A_KC, B_KC>();
   auto kernel = gemm_f32_kernel<BM, BN, BK, WM, WN, A_KC, B_KC, A_VEC, B_VEC, TI, TO>;
   static bool opted_in = false;  // one flag per instantiation of this launcher, i.e. per kernel
   allow_lds(kernel, lds, opted_in);
-  hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kThreads), lds, st, a, tiles_m, (int)blocks);
+  hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kThreads), lds, st, a, tiles_m, (int)blocks, only);
 }
 
 template <int BM, int BN, int BK, int WM, int WN, bool A_KC, bool B_KC, bool A_VEC, bool B_VEC>
-static void launch_typed(const GemmArgs& a, hipStream_t st) {
+static void launch_typed(const GemmArgs& a, hipStream_t st, const Declined& only) {
   if (a.in_dtype == VCNN_BF16) {
     if (a.out_dtype == VCNN_BF16)
-      launch_one<BM, BN, BK, WM, WN, A_KC, B_KC, A_VEC, B_VEC, bf16, bf16>(a, st);
+      launch_one<BM, BN, BK, WM, WN, A_KC, B_KC, A_VEC, B_VEC, bf16, bf16>(a, st, only);
     else
-      launch_one<BM, BN, BK, WM, WN, A_KC, B_KC, A_VEC, B_VEC, bf16, float>(a, st);
+      launch_one<BM, BN, BK, WM, WN, A_KC, B_KC, A_VEC, B_VEC, bf16, float>(a, st, only);
   } else {
-    launch_one<BM, BN, BK, WM, WN, A_KC, B_KC, A_VEC, B_VEC, float, float>(a, st);
+    launch_one<BM, BN, BK, WM, WN, A_KC, B_KC, A_VEC, B_VEC, float, float>(a, st, only);
   }
 }
 
 template <int BM, int BN, int BK, int WM, int WN, bool A_KC, bool B_KC>
-static void launch_vec(const GemmArgs& a, bool av, bool bv, hipStream_t st) {
+static void launch_vec(const GemmArgs& a, bool av, bool bv, hipStream_t st, const Declined& only) {
   if (av && bv)
-    launch_typed<BM, BN, BK, WM, WN, A_KC, B_KC, true, true>(a, st);
+    launch_typed<BM, BN, BK, WM, WN, A_KC, B_KC, true, true>(a, st, only);
   else if (av)
-    launch_typed<BM, BN, BK, WM, WN, A_KC, B_KC, true, false>(a, st);
+    launch_typed<BM, BN, BK, WM, WN, A_KC, B_KC, true, false>(a, st, only);
   else if (bv)
-    launch_typed<BM, BN, BK, WM, WN, A_KC, B_KC, false, true>(a, st);
+    launch_typed<BM, BN, BK, WM, WN, A_KC, B_KC, false, true>(a, st, only);
   else
-    launch_typed<BM, BN, BK, WM, WN, A_KC, B_KC, false, false>(a, st);
+    launch_typed<BM, BN, BK, WM, WN, A_KC, B_KC, false, false>(a, st, only);
 }
 
 template <int BM, int BN, int BK, int WM, int WN>
-static void launch_cfg(const GemmArgs& a, bool a_kc, bool b_kc, bool av, bool bv, hipStream_t st) {
+static void launch_cfg(const GemmArgs& a, bool a_kc, bool b_kc, bool av, bool bv, hipStream_t st, const Declined& only) {
   if (a_kc && b_kc)
-    launch_vec<BM, BN, BK, WM, WN, true, true>(a, av, bv, st);
+    launch_vec<BM, BN, BK, WM, WN, true, true>(a, av, bv, st, only);
   else if (a_kc)
-    launch_vec<BM, BN, BK, WM, WN, true, false>(a, av, bv, st);
+    launch_vec<BM, BN, BK, WM, WN, true, false>(a, av, bv, st, only);
   else if (b_kc)
-    launch_vec<BM, BN, BK, WM, WN, false, true>(a, av, bv, st);
+    launch_vec<BM, BN, BK, WM, WN, false, true>(a, av, bv, st, only);
   else
-    launch_vec<BM, BN, BK, WM, WN, false, false>(a, av, bv, st);
+    launch_vec<BM, BN, BK, WM, WN, false, false>(a, av, bv, st, only);
 }
 
 static bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
@@ -458,7 +458,7 @@ bool gemm_is_small(const GemmArgs& a) {
 
 static bool in_aligned(const void* p, int dtype) { return dtype == VCNN_BF16 ? group_aligned<bf16>(p) : group_aligned<float>(p); }
 
-vcnn_status launch_gemm_f32(const GemmArgs& a, hipStream_t st) {
+vcnn_status launch_gemm_f32(const GemmArgs& a, hipStream_t st, const Declined& only) {
   if (a.M <= 0 || a.N <= 0 || a.K <= 0) return fail(VCNN_ERR_SHAPE, "gemm: empty operand");
   const bool a_kc = (a.a_sk == 1) && (a.a_si != 1);
   const bool b_kc = (a.b_sk == 1) && (a.b_sj != 1);
@@ -485,15 +485,15 @@ vcnn_status launch_gemm_f32(const GemmArgs& a, hipStream_t st) {
   }
   if (a.row_sums) return fail(VCNN_ERR_UNSUPPORTED, "gemm: row sums are only built into the small-product kernel");
   if (a.M > 32 && a.N <= 4096 && big_tiles < 128)
-    launch_cfg<64, 64, 32, 32, 32>(a, a_kc, b_kc, av, bv, st);
+    launch_cfg<64, 64, 32, 32, 32>(a, a_kc, b_kc, av, bv, st, only);
   else if (a.M <= 32)
-    launch_cfg<32, 256, 32, 32, 64>(a, a_kc, b_kc, av, bv, st);
+    launch_cfg<32, 256, 32, 32, 64>(a, a_kc, b_kc, av, bv, st, only);
   else if (a.M <= 64 && ceil_div(a.N, 256) < 256)  // too few 256-wide tiles to occupy the compute units: halve them
-    launch_cfg<64, 128, 32, 32, 64>(a, a_kc, b_kc, av, bv, st);
+    launch_cfg<64, 128, 32, 32, 64>(a, a_kc, b_kc, av, bv, st, only);
   else if (a.M <= 64)
-    launch_cfg<64, 256, 32, 64, 64>(a, a_kc, b_kc, av, bv, st);
+    launch_cfg<64, 256, 32, 64, 64>(a, a_kc, b_kc, av, bv, st, only);
   else
-    launch_cfg<128, 128, 16, 64, 64>(a, a_kc, b_kc, av, bv, st);
+    launch_cfg<128, 128, 16, 64, 64>(a, a_kc, b_kc, av, bv, st, only);
   return check_launch("gemm_f32");
 }
 
