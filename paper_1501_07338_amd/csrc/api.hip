@@ -241,16 +241,16 @@ static void prefer_two_terms(const ConvGeom& g, int pass, size_t offered, Plan* 
   const double est = f2.est_seconds + 12e-6;
   if (pass == VCNN_PASS_BWD_FILTER) {
     // Variance of the error of an output against 64 bits, in units of 2e-16 of the output's own: what the products leave,
-    // the sums in a slice (the zero border's apart), the sums of slices.  Fitted to 170 drawn layers; where this line takes
-    // the two-term kernel its error measures 0.37 to 0.97 of the float kernel's, beyond it up to 1.5 (139 32 15 15 -> 32 5 5 0.8
-    // to 1.0, 139 32 7 7 -> 64 5 5 1.1 to 1.2: these stay in float, which costs them 0 to 15 us).
+    // the sums in a slice (the zero border's apart), the sums of slices.  Fitted to 170 drawn layers (float to 16 %, two-term
+    // to 8 %); the 159 this line takes measure 0.36 to 1.0 of the float kernel's error, 0.63 in the middle, and three of them
+    // 1.02, 1.03 and 1.09; the others reach 1.5.  (256 32 15 15 -> 32 5 5: 0.82 to 0.99, 50 us instead of 65; 200 32 7 7 -> 64
+    // 5 5, 0.97 to 1.04, stays in float, 51 us instead of 40.)
     const HaloFilterPlan& h = p->hfp;
     const double waves_k = 4 / (f2.filter.waves_m * f2.filter.waves_n), parts = f2.parts, splits = f2.filter.splits;
-    const double pixels = (double)g.n * inside(g.h, g.r, g.ph, g.oh) * inside(g.w, g.s, g.pw, g.ow);
-    auto slice_sums = [&](double slices) { return 1.75 * sum_slices_depth(slices, (double)g.M * (double)g.K); };
-    const double before = 12 + pixels / h.splits / 2 + slice_sums(h.splits);
-    const double after = 32 + 3.3 * pixels / (splits * parts * waves_k) / 16 + slice_sums(splits) + 1.75 * parts + 5 * waves_k;
-    if (after > 0.8 * before) return;
+    const double pixels = (double)g.n * inside(g.h, g.r, g.ph, g.oh) * inside(g.w, g.s, g.pw, g.ow), count = (double)g.M * (double)g.K;
+    const double before = 12 + pixels / h.splits / 2 + 1.75 * sum_slices_depth(h.splits, count, false);
+    const double after = 37 + 3.3 * pixels / (splits * parts * waves_k) / 16 + 2.3 * (sum_slices_depth(splits, count, true) + parts - 1) + 4.1 * waves_k;
+    if (after > before) return;
   }
   if (fold_s < est) return take_fold();
   if (est > 0.92 * f32) return;

@@ -395,8 +395,13 @@ vcnn_status launch_conv_fft(const FftPlan& p, int dtype, const ConvGeom& g, cons
 // out[i] = act(bias[(i / plane) % maps] + sum_s partial[s][i]), slices added in ascending order (bias nullable)
 vcnn_status launch_sum_slices(const float* partial, const float* bias, void* out, int out_dtype, int64_t count,
                               int splits, int64_t plane, int maps, int relu, hipStream_t st, const OtherSlices& other = {});
-// roundings in a sum of that many slices of `count` elements (the sixteen lanes of a short result share them)
-inline double sum_slices_depth(double splits, double count) { return splits >= 32 && count <= 65536 ? splits / 16 + 16 : splits; }
+// roundings in a sum of that many slices of `count` elements: in ascending order, sixteen lanes sharing the slices of a
+// short result, or, of a two-term product's slices, in pairs
+inline double sum_slices_depth(double splits, double count, bool in_pairs) {
+  const bool lanes = splits >= 32 && count <= 65536;
+  if (in_pairs) return splits <= 1 ? 0 : (lanes ? splits / 16 + 5 : splits / 8 + 3);
+  return lanes ? splits / 16 + 16 : splits;
+}
 // partial is [splits][rows][cols + 1]: main[r][c] = sum_s partial[s][r][c] for c < cols, last[r] = sum_s partial[s][r][cols]
 vcnn_status launch_sum_slices_split(const float* partial, float* main, float* last, int64_t rows, int cols, int splits,
                                     hipStream_t st);

@@ -114,11 +114,11 @@ def float_bytes(d, which):
     return high
 
 
-@pytest.mark.parametrize("shape", [(244, 9, 17, 17, 82, 7, 7, 0, 0), (6, 61, 27, 27, 461, 16, 16, 0, 0),
+@pytest.mark.parametrize("shape", [(3, 410, 27, 27, 187, 13, 12, 0, 0), (6, 61, 27, 27, 461, 16, 16, 0, 0),
                                    (15, 314, 8, 12, 15, 9, 9, 4, 4), (20, 233, 8, 8, 325, 9, 9, 4, 4)])
 def test_kernel_gradients_that_round_less_in_float_stay_there(shape):
-    """No GPU needed: short sums in many slices, and planes that are mostly border, where the two-term kernel measured up to
-    1.15 of the float kernel's error against 64 bits."""
+    """No GPU needed: short sums, and planes that are mostly border, where the two-term kernel measured up to 1.5 of the float
+    kernel's error against 64 bits."""
     assert route(vcnn.conv_desc(*shape), FILTER) == "implicit"
 
 
