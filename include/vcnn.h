@@ -68,8 +68,8 @@ enum { VCNN_PASS_FWD = 0, VCNN_PASS_BWD_FILTER = 1, VCNN_PASS_BWD_DATA = 2 };
  * the four term products, float accumulation.  IMPLICIT keeps to the float instruction; on operands of ordinary range the
  * two measure alike against the exact sums.  Activations, and dy in an input gradient, are scaled image by image, so that
  * an image's result does not depend on the others.  The terms carry elements down to 2^-29 of the largest one under the
- * same scale; an image (or kernel matrix, or operand of a kernel gradient) with more than one in 8192 of its elements
- * below that, zeros aside, or with an infinity or NaN, is computed by the float kernel instead, in its own time and that of
+ * same scale; an image (or kernel matrix, or operand of a kernel gradient) with more than one in 8192 of its elements, or
+ * 1024 of them, below that, zeros aside, or with an infinity or NaN, is computed by the float kernel instead, in its own time and that of
  * the scan.  Nothing of this decision reaches the host. */
 enum { VCNN_ALGO_AUTO = 0, VCNN_ALGO_EXPLICIT = 1, VCNN_ALGO_IMPLICIT = 2, VCNN_ALGO_FOLD = 3, VCNN_ALGO_FFT = 4,
        VCNN_ALGO_SPLIT = 5 };

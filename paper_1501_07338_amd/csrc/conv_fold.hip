@@ -278,7 +278,8 @@ __global__ __launch_bounds__(kThreads, 4) void bwd_data_fold_kernel(FoldArgs a) 
 // TERMS = 2: float operands as two f16 terms each (split_f16.h), three products per step; TERMS = 1: bfloat16 operands.
 // Both operands are re-laid once into fragment order (rows of the kernel matrix's transpose, pixels of a sample's dy), and
 // the tile's product is frag_product's.  Two blocks per CU: one block's fold runs under the other's products.  16 38 64 64
-// -> 512 16 16: 3.17 (float kernel) -> 1.39 ms, matrix pipe 48 % busy at the 1.8 GHz the chip holds under it.
+// -> 512 16 16: 3.17 (float kernel) -> 1.27 to 1.35 ms, the float kernel behind each part included (25 us); matrix pipe 48 %
+// busy at the 1.8 GHz the chip holds under it.
 struct FoldFragArgs {
   FoldArgs f;
   const uint4* wf;   // [4 tiles_i][steps][64]
@@ -327,7 +328,7 @@ __global__ __launch_bounds__(kThreads) void fragments_kernel(const void* __restr
     if (blockIdx.x == 0 && blockIdx.y == 0 && (int)blockIdx.z == image && threadIdx.x == 0) note_scale(sc, operand, image, largest);
   }
   const int lane = threadIdx.x & 63, step = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
-  if (step >= steps) return;
+  const bool inside = step < steps;
   const int row = blockIdx.y * 32 + (lane & 31), k0 = step * 16 + (lane >> 5) * 8;
   const int64_t from = blockIdx.z * s_z + min(row, rows - 1) * s_row;
   const int64_t to = (((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * steps + step) * 64 + lane;
@@ -351,8 +352,7 @@ __global__ __launch_bounds__(kThreads) void fragments_kernel(const void* __restr
     }
     uint4 hi, lo;
     pack_terms(v, &hi, &lo);
-    dst[to] = hi;
-    dst[to + term] = lo;
+    if (inside) dst[to] = hi, dst[to + term] = lo;
     note_small(sc, operand, image, small.count(f));
   } else {
     const bf16* const p = static_cast<const bf16*>(src) + from;
@@ -361,7 +361,7 @@ __global__ __launch_bounds__(kThreads) void fragments_kernel(const void* __restr
       const uint32_t b = p[min(k0 + j, depth - 1) * s_k].bits;
       v[j] = row < rows && k0 + j < depth ? b : 0u;
     }
-    dst[to] = make_uint4(v[0] | v[1] << 16, v[2] | v[3] << 16, v[4] | v[5] << 16, v[6] | v[7] << 16);
+    if (inside) dst[to] = make_uint4(v[0] | v[1] << 16, v[2] | v[3] << 16, v[4] | v[5] << 16, v[6] | v[7] << 16);
   }
 }
 

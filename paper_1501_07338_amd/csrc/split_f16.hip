@@ -91,7 +91,8 @@ SplitScales split_scales(void* workspace, int images, int images_at_once, int64_
   sc.exponent[0] = (int32_t*)take(images), sc.small[0] = take(images), sc.image = take(images);
   sc.partial[1] = take(kAbsMaxBlocks), sc.partial[0] = take((size_t)images + kAbsMaxBlocks);
   sc.blocks = scan_blocks(images_at_once);
-  auto limit = [](int64_t count) { return (uint32_t)std::min<int64_t>(count >> 13, 1 << 30); };
+  // (at most half of a block's elements: a block of small ones then says so by itself, see note_small)
+  auto limit = [](int64_t count) { return (uint32_t)std::min<int64_t>(count >> 13, 1024); };
   sc.limit[0] = limit(per_image), sc.limit[1] = limit(others);
   return sc;
 }
