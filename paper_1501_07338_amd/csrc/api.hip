@@ -127,7 +127,8 @@ struct Plan {
   int split;        // channel slices (few-out), output-map group size (few-in) or batch slices (filter gradient)
   size_t partial_bytes;
   size_t workspace_bytes;
-  size_t bias_offset;  // filter-gradient pass: where the bias-gradient partial sums live in the workspace
+  size_t bias_offset;  // filter-gradient pass: where the bias-gradient partial sums live in the workspace (and, until the
+                       // product is complete, the scales of a two-term product)
 };
 
 // Scratch memory of the allocation-free kernel gradient (vcnn_conv_bwd_filter_noalloc), per GPU.
@@ -151,6 +152,12 @@ static constexpr size_t kAsk = ~(size_t)0;  // make_plan: plan for the workspace
 // times this, the kernel gradient 0.8 to 1.2 times (1.3 to 1.5 with 32-row tiles); the factors below sit inside.
 static double f32_seconds(double blocks, double tiles, double depth) {
   return std::max(std::ceil(blocks / 256.0), 1.6) * depth * 32.0 * tiles * 1.2 / 2.4e9;
+}
+
+// Bytes behind a kernel gradient's product: the partial sums of the bias gradient, and before them the two-term scales.
+static size_t bias_room(const ConvGeom& g, int pass, bool two_terms) {
+  if (pass != VCNN_PASS_BWD_FILTER) return 0;
+  return std::max(align256(bias_grad_partial_bytes(g)), two_terms ? split_scales_bytes(1) : 0);
 }
 
 // Output rows whose tap lies inside an image of h rows, on average over r taps (likewise columns).
@@ -178,8 +185,8 @@ static double inside(int h, int r, int pad, int oh) {
 // sums runs that route, as it always has.
 static void prefer_two_terms(const ConvGeom& g, int pass, size_t offered, Plan* p) {
   if (g.c <= 4 || g.k <= 4) return;  // channel groups of eight, most of them padding
-  const size_t bias = pass == VCNN_PASS_BWD_FILTER ? align256(bias_grad_partial_bytes(g)) : 0;
-  const size_t own = p->workspace_bytes + bias;  // what the float route needs
+  const size_t own = p->workspace_bytes + bias_room(g, pass, false);  // what the float route needs
+  const size_t bias = bias_room(g, pass, true);
   double f32 = 12e-6;
   if (p->path == PATH_HALO) {
     const bool fwd = pass == VCNN_PASS_FWD;
@@ -230,11 +237,11 @@ static void prefer_two_terms(const ConvGeom& g, int pass, size_t offered, Plan* 
   if (ask < bias + beside || !conv_f16x2_plan(g, pass, ask - bias - beside, &f2)) return take_fold();
   const bool whole = f2.parts == 1;
   if (!whole && pass == VCNN_PASS_BWD_FILTER) {
-    if (!conv_f16x2_plan(g, pass, own - bias, &f2)) return;
+    if (!conv_f16x2_plan(g, pass, p->workspace_bytes, &f2)) return;
   } else if (!whole) {
     if (offered == kAsk || offered < beside || !conv_f16x2_plan(g, pass, offered - beside, &f2)) return take_fold();
   }
-  const size_t behind_at = pass == VCNN_PASS_BWD_FILTER ? split_scales_bytes(1) : align256(f2.workspace_bytes);
+  const size_t behind_at = pass == VCNN_PASS_BWD_FILTER ? 0 : align256(f2.workspace_bytes);
   const size_t need = std::max(align256(f2.workspace_bytes), behind_at + p->workspace_bytes) + bias;
   if (pass == VCNN_PASS_BWD_FILTER && need > ask) return;
   if (offered != kAsk && need > offered) return take_fold();
@@ -274,14 +281,14 @@ static void prefer_pointwise_f16(const ConvGeom& g, int pass, size_t offered, Pl
   else f32 += 1.3 * f32_seconds(std::ceil(rows / 64) * std::ceil(cols / 128) * g.n, 2, depth);
   const double operands = filter ? (rows + cols) * depth : depth * cols * g.n;
   if (0.92 * f32 < 12e-6 + 12.0 * operands / 4.5e12) return;  // not worth planning for
-  const size_t bias = filter ? align256(bias_grad_partial_bytes(g)) : 0, own = p->workspace_bytes + bias;
+  const size_t bias = bias_room(g, pass, true), own = p->workspace_bytes + bias_room(g, pass, false);
   PointwiseF16Plan q{};
   if (!pointwise_f16_plan(g, pass, &q)) return;
-  const size_t behind_at = split_scales_bytes(filter ? 1 : g.n);
-  const size_t need = std::max(align256(q.workspace_bytes), behind_at + p->workspace_bytes) + bias;
+  // (the float kernel's slices of a kernel gradient in the product's place; the others need no workspace)
+  const size_t need = std::max(align256(q.workspace_bytes), p->workspace_bytes) + bias;
   if (need > std::max(own, pointwise_allowance(pass, own)) || (offered != kAsk && need > offered)) return;
   if (1.05 * q.est_seconds > 0.92 * f32) return;
-  p->behind = p->path, p->behind_at = behind_at;
+  p->behind = p->path, p->behind_at = 0;
   p->path = PATH_POINTWISE_F16;
   p->pw16 = q;
   p->workspace_bytes = need - bias;
@@ -465,10 +472,8 @@ static Plan make_plan(const ConvGeom& g, int pass, int dtype, size_t offered) {
     prefer_pointwise_f16(g, pass, offered, &p);
     prefer_two_terms(g, pass, offered, &p);
   }
-  if (pass == VCNN_PASS_BWD_FILTER) {
-    p.bias_offset = p.workspace_bytes;
-    p.workspace_bytes += align256(bias_grad_partial_bytes(g));
-  }
+  p.bias_offset = p.workspace_bytes;
+  p.workspace_bytes += bias_room(g, pass, p.path == PATH_F16X2 || p.path == PATH_POINTWISE_F16);
   return p;
 }
 
@@ -658,8 +663,8 @@ vcnn_status vcnn_conv_bwd_filter(const vcnn_conv_desc* d, const void* x, const v
   } else if (plan.path == PATH_POINTWISE_F16 || plan.path == PATH_F16X2) {
     const FilterBehind behind{&g, (const float*)x, (const float*)dy, plan.behind == PATH_HALO_FILTER ? &plan.hfp : nullptr,
                               (float*)((char*)workspace + plan.behind_at)};
-    const vcnn_status s = plan.path == PATH_F16X2 ? launch_conv_f16x2_filter(plan.f2, g, behind.x, behind.dy, dw, workspace, behind, st)
-                                                  : launch_pointwise_f16_filter(plan.pw16, g, behind.x, behind.dy, dw, workspace, behind, st);
+    const vcnn_status s = plan.path == PATH_F16X2 ? launch_conv_f16x2_filter(plan.f2, g, behind.x, behind.dy, dw, workspace, bias_partial, behind, st)
+                                                  : launch_pointwise_f16_filter(plan.pw16, g, behind.x, behind.dy, dw, workspace, bias_partial, behind, st);
     if (s != VCNN_OK) return s;
   } else if (plan.path == PATH_SPLIT) {
     if (vcnn_status s = launch_conv_split_filter(plan.sp, g, (const float*)x, (const float*)dy, dw, workspace, st)) return s;

@@ -311,14 +311,14 @@ bool pointwise_f16_plan(const ConvGeom& g, int pass, PointwiseF16Plan* p);
 vcnn_status launch_pointwise_f16(const PointwiseF16Plan& p, const ConvGeom& g, int pass, const float* w, const float* x,
                                  const float* bias, float* y, int relu, void* workspace, hipStream_t st);
 vcnn_status launch_pointwise_f16_filter(const PointwiseF16Plan& p, const ConvGeom& g, const float* x, const float* dy, float* dw,
-                                        void* workspace, const FilterBehind& behind, hipStream_t st);
+                                        void* workspace, void* scales, const FilterBehind& behind, hipStream_t st);
 
 struct F16x2Plan {
   HaloBf16Plan fwd;           // forward pass, and the input gradient as a correlation, of `images` images
   FilterGradBf16Plan filter;  // kernel gradient of `images` images
   int parts, images;          // the batch is worked through in parts of at most `images` images
   int max_splits;             // bound on the kernel gradient's slices (0: none)
-  size_t workspace_bytes;     // scales, re-laid terms, slices
+  size_t workspace_bytes;     // scales (not a kernel gradient's), re-laid terms, slices
   double est_seconds;         // of the whole pass, re-laying included
 };
 // The fastest plan whose workspace holds in `budget` bytes: the batch in as few parts as that allows, and fewer slices of a
@@ -329,7 +329,7 @@ vcnn_status launch_conv_f16x2_fwd(const F16x2Plan& p, const ConvGeom& g, const f
 vcnn_status launch_conv_f16x2_bwd_data(const F16x2Plan& p, const ConvGeom& g, const float* w, const float* dy, float* dx,
                                        float* flipped, void* workspace, hipStream_t st);
 vcnn_status launch_conv_f16x2_filter(const F16x2Plan& p, const ConvGeom& g, const float* x, const float* dy, float* dw,
-                                     void* workspace, const FilterBehind& behind, hipStream_t st);
+                                     void* workspace, void* scales, const FilterBehind& behind, hipStream_t st);
 
 // ---- split_bf16.hip: fp32 products of large layers as sums of bf16 products (on request only) ------------------------
 struct SplitPlan {

@@ -136,7 +136,7 @@ bool pointwise_f16_plan(const ConvGeom& g, int pass, PointwiseF16Plan* p) {
     if (p->splits > 1) p->partial_bytes = align256((size_t)p->splits * g.M * g.K * sizeof(float));
     blocks = (double)tiles * p->splits, steps = (double)p->slabs_per_split * kSteps;
   }
-  p->workspace_bytes = split_scales_bytes(filter ? 1 : g.n) + 2 * (p->a_bytes + p->b_bytes) + p->partial_bytes;
+  p->workspace_bytes = (filter ? 0 : split_scales_bytes(g.n)) + 2 * (p->a_bytes + p->b_bytes) + p->partial_bytes;
   // products at half the nominal rate on the busiest CU; the scan, the re-laying and the slices at 4.5 TB/s
   const double floats = 4.0 * (filter ? (double)g.M * g.N + (double)g.K * g.N : (double)g.M * g.K + (double)depth * g.N);
   p->est_seconds = std::max(std::ceil(blocks / 256.0), 1.5) * (steps * 12 * 32 * 1.9 / 2.4e9 + 1.5e-6) +
@@ -167,10 +167,10 @@ vcnn_status launch_pointwise_f16(const PointwiseF16Plan& p, const ConvGeom& g, i
 }
 
 vcnn_status launch_pointwise_f16_filter(const PointwiseF16Plan& p, const ConvGeom& g, const float* x, const float* dy, float* dw,
-                                        void* workspace, const FilterBehind& behind, hipStream_t st) {
+                                        void* workspace, void* scales, const FilterBehind& behind, hipStream_t st) {
   const int P = (int)g.P;
-  const SplitScales sc = split_scales(workspace, 1, 1, g.K * g.N, g.M * g.N);
-  char* const fa = (char*)workspace + split_scales_bytes(1);
+  const SplitScales sc = split_scales(scales, 1, 1, g.K * g.N, g.M * g.N);
+  char* const fa = (char*)workspace;
   char* const fb = fa + 2 * p.a_bytes;
   float* const partial = (float*)(fb + 2 * p.b_bytes);
   PointwiseF16Args a{};

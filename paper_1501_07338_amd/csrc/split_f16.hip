@@ -126,7 +126,7 @@ static bool part_plan(const ConvGeom& whole, int pass, int n, int max_splits, F1
     const size_t terms = 2 * (p->filter.x8n_bytes + p->filter.dyf_bytes);
     // (later parts add to dw through the slice sum, which then needs one slice at least)
     const size_t slices = std::max(p->filter.partial_bytes, n < whole.n ? (size_t)g.M * g.K * sizeof(float) : (size_t)0);
-    p->workspace_bytes = split_scales_bytes(1) + terms + align256(slices);
+    p->workspace_bytes = terms + align256(slices);  // (the scales have a place of their own)
     p->est_seconds = p->filter.est_seconds + relay_seconds(x_bytes + y_bytes, (double)terms);
     return true;
   }
@@ -220,11 +220,11 @@ vcnn_status launch_conv_f16x2_bwd_data(const F16x2Plan& plan, const ConvGeom& wh
 }
 
 vcnn_status launch_conv_f16x2_filter(const F16x2Plan& plan, const ConvGeom& whole, const float* x, const float* dy, float* dw,
-                                     void* workspace, const FilterBehind& behind, hipStream_t st) {
+                                     void* workspace, void* scales, const FilterBehind& behind, hipStream_t st) {
   const int64_t chw = (int64_t)whole.c * whole.h * whole.w, mp = whole.M * whole.P;
-  char* const x8n = (char*)workspace + split_scales_bytes(1);
+  char* const x8n = (char*)workspace;
   return each_part(plan, whole, VCNN_PASS_BWD_FILTER, [&](int n0, const ConvGeom& g, const F16x2Plan& p) {
-    const SplitScales sc = split_scales(workspace, 1, 1, g.n * chw, g.n * mp);
+    const SplitScales sc = split_scales(scales, 1, 1, g.n * chw, g.n * mp);
     char* const dyf = x8n + 2 * p.filter.x8n_bytes;
     if (vcnn_status e = launch_absmax(x + n0 * chw, 1, g.n * chw, dy + n0 * mp, g.n * mp, sc, n0 == 0, st)) return e;
     return launch_filter_grad_f16x2(p.filter, g, x + n0 * chw, dy + n0 * mp, dw, sc, x8n, dyf,
