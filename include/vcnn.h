@@ -58,7 +58,7 @@ enum { VCNN_PASS_FWD = 0, VCNN_PASS_BWD_FILTER = 1, VCNN_PASS_BWD_DATA = 2 };
  * patch-matrix gradient on chip (AUTO uses that route only where it is the fastest).  FFT is AUTO except that the
  * forward pass of layers with one-dimensional kernels (r x 1 or 1 x s, at least 8 taps, no padding across the
  * kernel) goes through the Fourier domain - the alternative the paper's related-work paragraph names ("FFT
- * speedup"), kept as a comparison: AUTO never takes it.  SPLIT is AUTO except that the forward pass and the kernel
+ * speedup"), kept as a comparison: AUTO never takes this one.  SPLIT is AUTO except that the forward pass and the kernel
  * gradient of fp32 layers with more than 4 maps and channels compute their products (Eq. 1 / Eq. 2) as sums of
  * bfloat16 products: every float operand is, exactly, a sum of three bfloat16 terms, and the six largest of the nine
  * term products, accumulated in float, carry the product to within float rounding.  The result stays within the
@@ -70,7 +70,12 @@ enum { VCNN_PASS_FWD = 0, VCNN_PASS_BWD_FILTER = 1, VCNN_PASS_BWD_DATA = 2 };
  * an image's result does not depend on the others.  The terms carry elements down to 2^-29 of the largest one under the
  * same scale; an image (or kernel matrix, or operand of a kernel gradient) with more than one in 8192 of its elements, or
  * 1024 of them, below that, zeros aside, or with an infinity or NaN, is computed by the float kernel instead, in its own time and that of
- * the scan.  Nothing of this decision reaches the host. */
+ * the scan.  Nothing of this decision reaches the host.
+ * AUTO takes layers with large kernels (7 x 7 to 16 x 16 taps, more than 4 maps and channels, either dtype) through the
+ * Fourier domain where that is faster: transforms in double, spectra and their products in float; nearer the exact sums
+ * than the direct routes as measured over whole results.  Its error is spread over the plane, though, so an image with a
+ * window (all channels) below 2^-10 of its largest element - black areas of a kernel's size among them -, with an infinity
+ * or NaN, or with magnitudes whose products leave the float range is computed by the float kernel, in its own time. */
 enum { VCNN_ALGO_AUTO = 0, VCNN_ALGO_EXPLICIT = 1, VCNN_ALGO_IMPLICIT = 2, VCNN_ALGO_FOLD = 3, VCNN_ALGO_FFT = 4,
        VCNN_ALGO_SPLIT = 5 };
 
@@ -104,12 +109,13 @@ vcnn_status vcnn_conv_out_shape(const vcnn_conv_desc* d, int32_t* oh, int32_t* o
  * slower route that needs less.  Where the re-laid operands of an fp32 forward pass or input gradient exceed 64 MiB the
  * query asks for the float kernel's workspace only (often 0), and a call that brings just that runs it; one that brings
  * more (64 MiB will do) takes the two-term kernels and works through the batch in parts:
- * vcnn_conv_route tells what a size buys. */
+ * vcnn_conv_route tells what a size buys.  The passes through the Fourier domain ask for their spectra: up to 1 GiB, a
+ * forward pass 64 MiB (it works through its maps in parts; more workspace, fewer parts). */
 vcnn_status vcnn_conv_workspace_bytes(const vcnn_conv_desc* d, int32_t pass, size_t* bytes);
 /* The route the given pass takes with that many bytes of aligned workspace, under the present VCNN_ALGO_* choice, as a
  * short static string (for diagnostics and tests): "two_term", "two_term_fold" and "two_term_pointwise" are the fp32
- * products from two half-precision terms, the others the names of their kernels.  VCNN_ERR_WORKSPACE if the pass cannot
- * run with so little. */
+ * products from two half-precision terms, "spectral" a pass through the Fourier domain, the others the names of their
+ * kernels.  VCNN_ERR_WORKSPACE if the pass cannot run with so little. */
 vcnn_status vcnn_conv_route(const vcnn_conv_desc* d, int32_t pass, size_t workspace_bytes, const char** name);
 
 /* phi_c (Eq. 2; mini-batch form Eq. 4): col[(c*R+r)*S+s][(n*OH+oh)*OW+ow] = xpad[n][c][oh+r-pad_h][ow+s-pad_w].

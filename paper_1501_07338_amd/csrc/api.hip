@@ -8,6 +8,7 @@
 #include <cstring>
 
 #include "common.h"
+#include "spectral.h"
 
 namespace vcnn {
 
@@ -104,7 +105,7 @@ static bool fold_beats_halo(const ConvGeom& g, const HaloPlan& hp, const FoldPla
 
 // Which realisation a pass uses for a given shape.  The same decision drives the workspace query and
 // the launch, so the two always agree.
-enum Path { PATH_EXPLICIT, PATH_POINTWISE, PATH_FEW_OUT, PATH_FEW_IN, PATH_DIRECT_FILTER, PATH_HALO, PATH_HALO_FILTER, PATH_HALO_BF16, PATH_FILTER_BF16, PATH_HALO_FILTER_BF16, PATH_FEW_COLS_FILTER, PATH_SMALL, PATH_SMALL_BWD, PATH_FOLD, PATH_FFT, PATH_TAPS, PATH_POINTWISE_BF16, PATH_SPLIT, PATH_F16X2, PATH_FOLD_FRAG, PATH_POINTWISE_F16 };
+enum Path { PATH_EXPLICIT, PATH_POINTWISE, PATH_FEW_OUT, PATH_FEW_IN, PATH_DIRECT_FILTER, PATH_HALO, PATH_HALO_FILTER, PATH_HALO_BF16, PATH_FILTER_BF16, PATH_HALO_FILTER_BF16, PATH_FEW_COLS_FILTER, PATH_SMALL, PATH_SMALL_BWD, PATH_FOLD, PATH_FFT, PATH_TAPS, PATH_POINTWISE_BF16, PATH_SPLIT, PATH_F16X2, PATH_FOLD_FRAG, PATH_POINTWISE_F16, PATH_SPECTRAL };
 struct Plan {
   Path path;
   DirectGeom dg;
@@ -122,7 +123,8 @@ struct Plan {
   F16x2Plan f2;
   FoldFragPlan ff;
   PointwiseF16Plan pw16;
-  Path behind;       // PATH_F16X2, PATH_POINTWISE_F16: the float path enqueued behind for what the terms do not carry ...
+  SpectralPlan spec;
+  Path behind;       // PATH_F16X2, PATH_POINTWISE_F16, PATH_SPECTRAL: the float path enqueued behind for what the terms do not carry ...
   size_t behind_at;  // ... and the offset of its workspace
   int split;        // channel slices (few-out), output-map group size (few-in) or batch slices (filter gradient)
   size_t partial_bytes;
@@ -144,6 +146,8 @@ static size_t two_term_allowance(int pass, size_t own) {
 static size_t pointwise_allowance(int pass, size_t own) {
   return pass == VCNN_PASS_BWD_FILTER && own <= kScratchBytes ? kScratchBytes : (size_t)384 << 20;
 }
+// A pass through the Fourier domain: its spectra (the forward pass works through its maps in parts that fit what it is given).
+static constexpr size_t kSpectralAllowance = (size_t)1 << 30, kSpectralForward = (size_t)64 << 20;
 static constexpr size_t kAsk = ~(size_t)0;  // make_plan: plan for the workspace query, not for a given workspace
 
 // Estimated time of a float matrix-core kernel, in seconds: `blocks` blocks of four waves, each wave `tiles` accumulator
@@ -294,7 +298,7 @@ static void prefer_pointwise_f16(const ConvGeom& g, int pass, size_t offered, Pl
   p->workspace_bytes = need - bias;
 }
 
-static Plan make_plan(const ConvGeom& g, int pass, int dtype, size_t offered) {
+static Plan direct_plan(const ConvGeom& g, int pass, int dtype, size_t offered) {
   Plan p{};
   p.path = PATH_EXPLICIT;
   const int algo = g_conv_algo.load();
@@ -477,6 +481,63 @@ static Plan make_plan(const ConvGeom& g, int pass, int dtype, size_t offered) {
   return p;
 }
 
+// Takes a pass through the Fourier domain (spectral.h) where that is faster than `direct`, the plan it replaces.  That one's
+// time is taken from below: on the half-precision matrix cores 1.1 times the flops at their best rate (three products each in
+// float) and 45 us of scan, re-laying and launches in float, 25 in bfloat16; on the float instruction its flops at 130 TFLOP/s.
+// (40 drawn layers, 110 passes; n c h w -> k r s, direct / through the Fourier domain: 16 38 64 64 -> 512 16 16, three passes,
+// 3.33 / 0.70 ms, in bfloat16 1.25 / 0.68 ms; 3 354 64 64 -> 69 8 14 kernel gradient 813 / 126 us; 32 17 64 64 -> 90 11 11 forward
+// 210 / 65 us; 16 13 64 64 -> 57 9 9 forward 64 / 44 us; 57 39 34 34 -> 276 11 11, 342 / 326 us, stays, and so does bfloat16 in 18
+// 207 56 24 -> 101 13 9, 181 / 372 us.)
+static bool prefer_spectral(const ConvGeom& g, int pass, int dtype, size_t offered, const Plan& direct, Plan* p) {
+  if (g.r * g.s < 49 || g.c <= 4 || g.k <= 4) return false;
+  const double flops = 2.0 * (double)g.M * (double)g.K * (double)g.N;
+  const bool on_float = direct.path == PATH_HALO || direct.path == PATH_HALO_FILTER || direct.path == PATH_FOLD || direct.path == PATH_EXPLICIT;
+  const double direct_s = on_float ? flops / 1.3e14 : (dtype == VCNN_BF16 ? flops / 1e15 + 25e-6 : 3 * flops / 1.05e15 + 45e-6);
+  if (flops < 4e9) return false;  // (not worth planning for)
+  const bool filter = pass == VCNN_PASS_BWD_FILTER, data = pass == VCNN_PASS_BWD_DATA;
+  // (the kernel gradient's route depends on the shape alone, and stays inside the scratch memory where it was)
+  const bool small = filter && direct.workspace_bytes <= kScratchBytes;
+  size_t budget = filter ? (small ? kScratchBytes : kSpectralAllowance) : (offered != kAsk ? offered : (data ? kSpectralAllowance : kSpectralForward));
+  SpectralPlan q{};
+  if (!spectral_plan(g, pass, budget, &q)) return false;
+  // the float kernel behind, for declined images: its workspace in the place of the spectra
+  size_t behind = 0;
+  HaloPlan hp{};
+  HaloFilterPlan hfp{};
+  if (filter) {
+    if (!conv_halo_filter_plan(g, &hfp)) return false;
+    behind = hfp.partial_bytes;
+  } else if (data) {
+    if (g.r - 1 - g.ph < 0 || g.s - 1 - g.pw < 0 ||
+        !conv_halo_plan(g.n, g.k, g.oh, g.ow, g.c, g.r, g.s, g.r - 1 - g.ph, g.s - 1 - g.pw, &hp)) return false;
+    behind = (size_t)g.M * g.K * (dtype == VCNN_BF16 ? 2 : 4);
+  } else if (!conv_halo_plan(g.n, g.c, g.h, g.w, g.k, g.r, g.s, g.ph, g.pw, &hp)) {
+    return false;
+  }
+  const size_t spectra = q.workspace_bytes - q.words_bytes;
+  if (behind > spectra) q.map_bytes += align256(behind - spectra), q.workspace_bytes += align256(behind - spectra);
+  size_t need = align256(q.workspace_bytes);
+  if (filter && !small) need = std::max(need, kScratchBytes + 256);  // refused by the allocation-free entry point as before
+  if (need > budget || (offered != kAsk && need > offered)) return false;
+  if (1.1 * q.est_seconds > direct_s) return false;
+  *p = Plan{};
+  p->path = PATH_SPECTRAL, p->spec = q, p->hp = hp, p->hfp = hfp;
+  p->behind = filter ? PATH_HALO_FILTER : PATH_HALO;
+  p->workspace_bytes = p->bias_offset = need;
+  return true;
+}
+
+static Plan make_plan(const ConvGeom& g, int pass, int dtype, size_t offered) {
+  const Plan direct = direct_plan(g, pass, dtype, offered);
+  const int algo = g_conv_algo.load();
+  Plan p{};
+  if ((algo == VCNN_ALGO_AUTO || (algo == VCNN_ALGO_FOLD && pass != VCNN_PASS_BWD_DATA) || (algo == VCNN_ALGO_FFT && direct.path != PATH_FFT) ||
+       (algo == VCNN_ALGO_SPLIT && direct.path != PATH_SPLIT)) &&
+      prefer_spectral(g, pass, dtype, offered, direct, &p))
+    return p;
+  return direct;
+}
+
 static size_t workspace_need(const ConvGeom& g, int pass, int dtype) { return make_plan(g, pass, dtype, kAsk).workspace_bytes; }
 // the workspace a call brings, as far as it can be used
 static size_t usable(const void* workspace, size_t bytes) {
@@ -556,6 +617,7 @@ vcnn_status vcnn_conv_route(const vcnn_conv_desc* d, int32_t pass, size_t worksp
     case PATH_F16X2: *name = "two_term"; break;
     case PATH_FOLD_FRAG: *name = p.ff.terms == 2 ? "two_term_fold" : "fold_bf16"; break;
     case PATH_POINTWISE_F16: *name = "two_term_pointwise"; break;
+    case PATH_SPECTRAL: *name = "spectral"; break;
   }
   return VCNN_OK;
 }
@@ -606,6 +668,10 @@ static vcnn_status conv_fwd_linear(const vcnn_conv_desc* d, const ConvGeom& g, c
     return launch_conv_halo(plan.hp, dt, g.n, g.c, g.h, g.w, g.k, g.r, g.s, g.ph, g.pw, x, w, bias, y, relu, st, only);
   };
   if (plan.path == PATH_HALO) return float_halo({});
+  if (plan.path == PATH_SPECTRAL) {
+    if (vcnn_status s = launch_spectral_fwd(plan.spec, dt, g, x, w, bias, y, relu, workspace, st)) return s;
+    return float_halo(spectral_declined(g, VCNN_PASS_FWD, plan.spec, workspace));
+  }
   if (plan.path == PATH_HALO_BF16) {
     return launch_conv_halo_bf16(plan.hb, g.n, g.c, g.h, g.w, g.k, g.r, g.s, g.ph, g.pw, x, w, g.K, (int64_t)g.r * g.s, 0,
                                  bias, y, relu, workspace, st);
@@ -666,6 +732,13 @@ vcnn_status vcnn_conv_bwd_filter(const vcnn_conv_desc* d, const void* x, const v
     const vcnn_status s = plan.path == PATH_F16X2 ? launch_conv_f16x2_filter(plan.f2, g, behind.x, behind.dy, dw, workspace, bias_partial, behind, st)
                                                   : launch_pointwise_f16_filter(plan.pw16, g, behind.x, behind.dy, dw, workspace, bias_partial, behind, st);
     if (s != VCNN_OK) return s;
+  } else if (plan.path == PATH_SPECTRAL) {
+    if (vcnn_status s = launch_spectral_filter(plan.spec, dt, g, x, dy, dw, dbias, workspace, st)) return s;
+    const Declined declined = spectral_declined(g, VCNN_PASS_BWD_FILTER, plan.spec, workspace);
+    if (vcnn_status s = launch_conv_halo_filter(plan.hfp, dt, g, x, dy, dw, nullptr, (float*)workspace, st, declined)) return s;
+    if (plan.hfp.splits == 1) return VCNN_OK;
+    const OtherSlices slices{declined.any, (const float*)workspace, plan.hfp.splits};
+    return launch_sum_slices(nullptr, nullptr, dw, VCNN_F32, g.M * g.K, 0, 1, 1, 0, st, slices);
   } else if (plan.path == PATH_SPLIT) {
     if (vcnn_status s = launch_conv_split_filter(plan.sp, g, (const float*)x, (const float*)dy, dw, workspace, st)) return s;
   } else if (plan.path == PATH_POINTWISE_BF16) {
@@ -721,6 +794,12 @@ static vcnn_status conv_bwd_data_impl(const vcnn_conv_desc* d, int act_below, co
     return launch_conv_halo(plan.hp, dt, g.n, g.k, g.oh, g.ow, g.c, g.r, g.s, g.r - 1 - g.ph, g.s - 1 - g.pw, dy, flipped,
                             nullptr, dx, 0, st, only);
   };
+  if (plan.path == PATH_SPECTRAL) {
+    if (vcnn_status s = launch_spectral_bwd_data(plan.spec, dt, g, w, dy, dx, workspace, st)) return s;
+    const Declined declined = spectral_declined(g, VCNN_PASS_BWD_DATA, plan.spec, workspace);
+    if (vcnn_status s = launch_flip_transpose(dt, w, workspace, g.k, g.c, g.r * g.s, st, declined)) return s;
+    return then_act(float_halo(workspace, declined));
+  }
   if (plan.path == PATH_F16X2) {
     float* const flipped = (float*)((char*)workspace + plan.behind_at);
     if (vcnn_status s = launch_conv_f16x2_bwd_data(plan.f2, g, (const float*)w, (const float*)dy, (float*)dx, flipped, workspace, st)) return s;

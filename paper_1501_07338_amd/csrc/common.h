@@ -167,7 +167,8 @@ bool filter_grad_few_cols_plan(const ConvGeom& g, FewColsPlan* p);
 // dbias nullable; when the plan has a bias column and dbias is given, dbias is produced here as well
 vcnn_status launch_filter_grad_few_cols(const FewColsPlan& p, int dtype, const ConvGeom& g, const void* x, const void* dy,
                                         float* dw, float* dbias, float* partial, hipStream_t st);
-vcnn_status launch_flip_transpose(int dtype, const void* w, void* w2, int M, int C, int RS, hipStream_t st);
+// only: if anything was left to the kernel that reads w2
+vcnn_status launch_flip_transpose(int dtype, const void* w, void* w2, int M, int C, int RS, hipStream_t st, const Declined& only = {});
 
 // ---- bf16_conv.hip (implicit bf16 kernels) / bf16_mfma.hip (explicit-route bf16 product) ------------
 struct HaloBf16Plan {

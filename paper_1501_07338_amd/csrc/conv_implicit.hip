@@ -387,7 +387,8 @@ __global__ __launch_bounds__(kThreads) void conv_halo16_kernel(HaloArgs a) {
 // w2[c][m][r'][s'] = w[m][c][R-1-r'][S-1-s']: the kernel matrix of the input-gradient correlation.
 template <typename T>
 __global__ __launch_bounds__(kThreads) void flip_transpose_kernel(const T* __restrict__ w, T* __restrict__ w2, int M,
-                                                                  int C, int RS) {
+                                                                  int C, int RS, Declined only) {
+  if (leave_all(only)) return;
   const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   if (i >= (int64_t)M * C * RS) return;
   const int q = (int)(i % RS);
@@ -397,13 +398,14 @@ __global__ __launch_bounds__(kThreads) void flip_transpose_kernel(const T* __res
   w2[i] = w[((int64_t)m * C + c) * RS + (RS - 1 - q)];
 }
 
-vcnn_status launch_flip_transpose(int dtype, const void* w, void* w2, int M, int C, int RS, hipStream_t st) {
+vcnn_status launch_flip_transpose(int dtype, const void* w, void* w2, int M, int C, int RS, hipStream_t st,
+                                  const Declined& only) {
   const int64_t count = (int64_t)M * C * RS;
   const dim3 grid((unsigned)ceil_div(count, kThreads)), block(kThreads);
   if (dtype == VCNN_BF16)
-    hipLaunchKernelGGL(flip_transpose_kernel<bf16>, grid, block, 0, st, (const bf16*)w, (bf16*)w2, M, C, RS);
+    hipLaunchKernelGGL(flip_transpose_kernel<bf16>, grid, block, 0, st, (const bf16*)w, (bf16*)w2, M, C, RS, only);
   else
-    hipLaunchKernelGGL(flip_transpose_kernel<float>, grid, block, 0, st, (const float*)w, (float*)w2, M, C, RS);
+    hipLaunchKernelGGL(flip_transpose_kernel<float>, grid, block, 0, st, (const float*)w, (float*)w2, M, C, RS, only);
   return check_launch("flip_transpose");
 }
 

@@ -1,0 +1,79 @@
+// Convolutions through the Fourier domain (planes of 64 x 64 pixels): what the transforms (spectral_fft.hip) and the
+// products (spectral.hip) share.
+//
+// With xt a plane of at most 64 x 64 pixels and wt a kernel, both zero-extended to 64 x 64 and transformed,
+//   forward         Y(u,v)  = sum_c X_c(u,v) conj(W_kc(u,v))    valid where the kernel lies inside the plane
+//   input gradient  dX(u,v) = sum_k dY_k(u,v) W_kc(u,v)
+//   kernel gradient dW(u,v) = sum_n X_nc(u,v) conj(dY_nk(u,v))  the first R x S elements
+// so a pass costs 64 * 33 complex products per pair of planes where the direct sum costs R S oh ow real ones (16 x 16 taps
+// on 64 x 64 pixels: 73 times fewer operations).  Larger planes are cut into tiles of 64 x 64 whose valid parts join.
+//
+// Precision.  The transforms run in double (the vector units do a double as fast as a float), spectra are stored as float,
+// and the products add in float on the matrix cores over the channels (maps, images) only.  What is rounded to float is
+// each spectrum once (rows of a kernel once more) and the short sums, so the result lies nearer the 64-bit one than that of
+// the direct kernels, whose sums run over channels times taps.  The error is spread over a whole plane, though: an output
+// whose window holds only elements far below the plane's largest would lose what the direct sum keeps.  Images with such a
+// window, with magnitudes whose products leave the range of a float, or with an infinity or NaN are DECLINED on the device
+// and computed by the direct float kernel enqueued behind (which otherwise leaves at once).
+#pragma once
+#include "common.h"
+
+namespace vcnn {
+
+static constexpr int kFL = 64;        // transform length
+static constexpr int kFV = 33;        // columns of a real plane's spectrum
+static constexpr int kFTaps = 16;     // most kernel rows / columns
+// A plane's spectrum is stored as columns v = 0..32, each of 64 complex floats in four residues rho = u mod 4 (one wave of
+// the product each) of the 16 frequencies u = 4 a + rho in order.
+
+static constexpr int kFCells = 32;    // cells of 8 x 16 pixels of a plane
+// A window (in whole cells) darker than this share of its tile's largest element declines the image.
+static constexpr float kDarkWindow = 1.f / 1024;
+
+struct SpectralPlan {
+  int tiles_y, tiles_x;    // tiles of a plane
+  int step_y, step_x;      // distance of the tiles' valid parts
+  int part;                // forward: output maps worked on at once (else all)
+  int splits, per_split;   // slices of the contraction, summed by the inverse transform
+  size_t image_bytes;      // spectra over the input channels (input gradient: one slice per split)
+  size_t map_bytes;        // spectra over the output maps (of a part)
+  size_t taps_bytes;       // row spectra of the kernels (of a part; kernel gradient: one slice per split)
+  size_t words_bytes;      // maxima, sums and Declined
+  size_t workspace_bytes;
+  double est_seconds;
+};
+bool spectral_plan(const ConvGeom& g, int pass, size_t budget, SpectralPlan* p);
+vcnn_status launch_spectral_fwd(const SpectralPlan& p, int dtype, const ConvGeom& g, const void* x, const void* w, const float* bias,
+                                void* y, int relu, void* workspace, hipStream_t st);
+vcnn_status launch_spectral_bwd_data(const SpectralPlan& p, int dtype, const ConvGeom& g, const void* w, const void* dy, void* dx,
+                                     void* workspace, hipStream_t st);
+vcnn_status launch_spectral_filter(const SpectralPlan& p, int dtype, const ConvGeom& g, const void* x, const void* dy, float* dw,
+                                   float* db, void* workspace, hipStream_t st);
+// The images these passes leave to the float kernel behind them.
+Declined spectral_declined(const ConvGeom& g, int pass, const SpectralPlan& p, const void* workspace);
+
+// ---- spectral_fft.hip -----------------------------------------------------------------------------------------------
+// Planes of a tensor [images][channels][h][w], tile by tile: tile (ty, tx) starts at pixel (ty step_y + y0, tx step_x + x0)
+// (what lies outside the plane is zero) and holds lim_y x lim_x pixels.  Spectra of plane (image, ty, tx, channel) in order.
+struct SpectralTiles {
+  int images, channels, first, count;  // channels first .. first + count - 1 of each image
+  int h, w;
+  int tiles_y, tiles_x, step_y, step_x, y0, x0, lim_y, lim_x;
+  int64_t planes() const { return (int64_t)images * tiles_y * tiles_x * count; }
+};
+// Also leaves each plane's largest magnitude per cell of 8 x 16 pixels (cells, float bits), its sum (sums, nullable), and
+// zeros in words[0..1] (nullable).
+vcnn_status launch_plane_spectra(const SpectralTiles& t, int dtype, const void* src, float2* spectra, uint32_t* cells,
+                                 double* sums, uint32_t* words, hipStream_t st);
+// The spectra of planes back to pixels: pixel (y, x) of tile (ty, tx) is (ty step_y + y, tx step_x + x) of the plane and lies
+// at (y + y0, x + x0) of the transform; `slices` spectra of a plane, `slice` complex values apart, are added first; bias per channel, nullable.
+vcnn_status launch_plane_inverse(const SpectralTiles& t, int dtype, const float2* spectra, int64_t slice, int slices, void* dst,
+                                 const float* bias, int relu, hipStream_t st);
+// Row spectra of kernels of r x s taps: [v][kernel][16 rows]; largest magnitude of each four kernels.
+vcnn_status launch_taps_spectra(int dtype, const void* w, int64_t kernels, int r, int s, float2* spectra, uint32_t* largest,
+                                hipStream_t st);
+// And back; also db[m] = sums[0][m] + sums[1][m] + ... (planes of `maps` maps; nullable).
+vcnn_status launch_taps_inverse(const float2* spectra, int64_t slice, int slices, int64_t kernels, int r, int s, float* dw,
+                                const double* sums, int sum_planes, int maps, float* db, hipStream_t st);
+
+}  // namespace vcnn

@@ -1,0 +1,599 @@
+// Convolutions through the Fourier domain: products of spectra, the passes and their plans (spectral.h).
+#include <algorithm>
+#include <cmath>
+
+#include "bf16_core.h"
+#include "spectral.h"
+
+namespace vcnn {
+
+static constexpr int kThreads = 256;
+
+struct cf {
+  float x, y;
+};
+__device__ __forceinline__ cf operator+(cf a, cf b) { return {a.x + b.x, a.y + b.y}; }
+__device__ __forceinline__ cf operator-(cf a, cf b) { return {a.x - b.x, a.y - b.y}; }
+__device__ __forceinline__ cf operator*(cf a, cf b) { return {fmaf(a.x, b.x, -a.y * b.y), fmaf(a.x, b.y, a.y * b.x)}; }
+template <bool INV>
+__device__ __forceinline__ void dft4(cf& a, cf& b, cf& c, cf& d) {
+  const cf s = a + c, t = a - c, u = b + d, e = b - d;
+  const cf q = INV ? cf{-e.y, e.x} : cf{e.y, -e.x};
+  a = s + u, b = t + q, c = s - u, d = t - q;
+}
+// v[4 k + i], i < 4, hold what first(v, i) makes of v[i + 4 n]; second(v, k) then leaves point k + 4 n of
+// sum_m v[m] e^(-+ 2 pi i m p / 16) in v[4 k + n]
+template <bool INV>
+__device__ __forceinline__ void dft16_first(cf (&v)[16], int i) {
+  constexpr float c1 = 0.92387953251128675613f, s1 = 0.38268343236508977173f, h = 0.70710678118654752440f;
+  constexpr float c[10] = {1, c1, h, s1, 0, 0, -h, 0, 0, -c1}, s[10] = {0, s1, h, c1, 1, 0, h, 0, 0, -s1};
+  dft4<INV>(v[i], v[4 + i], v[8 + i], v[12 + i]);
+  if (i > 0) {
+#pragma unroll
+    for (int k = 1; k < 4; ++k) v[4 * k + i] = v[4 * k + i] * cf{c[i * k], INV ? s[i * k] : -s[i * k]};
+  }
+}
+template <bool INV>
+__device__ __forceinline__ void dft16_second(cf (&v)[16], int k) { dft4<INV>(v[4 * k], v[4 * k + 1], v[4 * k + 2], v[4 * k + 3]); }
+__device__ __forceinline__ constexpr int dft16_at(int p) { return 4 * (p & 3) + (p >> 2); }  // where point p is
+// e^(-2 pi i q / 64), q = rho * r for the residues rho < 4 and kernel rows r < 16
+__constant__ const float kRoots[4][16][2] = {
+#define R0 {1.f, 0.f}
+#define ROOT(c, s) {c, -(s)}
+    {R0, R0, R0, R0, R0, R0, R0, R0, R0, R0, R0, R0, R0, R0, R0, R0},
+    {R0, ROOT(0.99518472667219688624f, 0.09801714032956060199f), ROOT(0.98078528040323044913f, 0.19509032201612826785f),
+     ROOT(0.95694033573220886494f, 0.29028467725446236764f), ROOT(0.92387953251128675613f, 0.38268343236508977173f),
+     ROOT(0.88192126434835502971f, 0.47139673682599764856f), ROOT(0.83146961230254523708f, 0.55557023301960222474f),
+     ROOT(0.77301045336273696081f, 0.63439328416364549822f), ROOT(0.70710678118654752440f, 0.70710678118654752440f),
+     ROOT(0.63439328416364549822f, 0.77301045336273696081f), ROOT(0.55557023301960222474f, 0.83146961230254523708f),
+     ROOT(0.47139673682599764856f, 0.88192126434835502971f), ROOT(0.38268343236508977173f, 0.92387953251128675613f),
+     ROOT(0.29028467725446236764f, 0.95694033573220886494f), ROOT(0.19509032201612826785f, 0.98078528040323044913f),
+     ROOT(0.09801714032956060199f, 0.99518472667219688624f)},
+    {R0, ROOT(0.98078528040323044913f, 0.19509032201612826785f), ROOT(0.92387953251128675613f, 0.38268343236508977173f),
+     ROOT(0.83146961230254523708f, 0.55557023301960222474f), ROOT(0.70710678118654752440f, 0.70710678118654752440f),
+     ROOT(0.55557023301960222474f, 0.83146961230254523708f), ROOT(0.38268343236508977173f, 0.92387953251128675613f),
+     ROOT(0.19509032201612826785f, 0.98078528040323044913f), ROOT(0.0f, 1.0f),
+     ROOT(-0.19509032201612826785f, 0.98078528040323044913f), ROOT(-0.38268343236508977173f, 0.92387953251128675613f),
+     ROOT(-0.55557023301960222474f, 0.83146961230254523708f), ROOT(-0.70710678118654752440f, 0.70710678118654752440f),
+     ROOT(-0.83146961230254523708f, 0.55557023301960222474f), ROOT(-0.92387953251128675613f, 0.38268343236508977173f),
+     ROOT(-0.98078528040323044913f, 0.19509032201612826785f)},
+    {R0, ROOT(0.95694033573220886494f, 0.29028467725446236764f), ROOT(0.83146961230254523708f, 0.55557023301960222474f),
+     ROOT(0.63439328416364549822f, 0.77301045336273696081f), ROOT(0.38268343236508977173f, 0.92387953251128675613f),
+     ROOT(0.09801714032956060199f, 0.99518472667219688624f), ROOT(-0.19509032201612826785f, 0.98078528040323044913f),
+     ROOT(-0.47139673682599764856f, 0.88192126434835502971f), ROOT(-0.70710678118654752440f, 0.70710678118654752440f),
+     ROOT(-0.88192126434835502971f, 0.47139673682599764856f), ROOT(-0.98078528040323044913f, 0.19509032201612826785f),
+     ROOT(-0.99518472667219688624f, -0.09801714032956060199f), ROOT(-0.92387953251128675613f, -0.38268343236508977173f),
+     ROOT(-0.77301045336273696081f, -0.63439328416364549822f), ROOT(-0.55557023301960222474f, -0.83146961230254523708f),
+     ROOT(-0.29028467725446236764f, -0.95694033573220886494f)}};
+#undef ROOT
+#undef R0
+
+__device__ const float4 kZeros[8] = {};
+
+// ---- what declines an image --------------------------------------------------------------------------------------
+struct GuardArgs {
+  const uint32_t* cells[2];  // [image][tile][plane][kFCells]: of the operand with windows, and of another (nullable)
+  int planes[2], tiles_y, tiles_x, images;
+  int step_y, step_x, y0, x0, h, w, lim_y, lim_x;  // of the first operand's tiles
+  int win_y, win_x;          // cells a window covers
+  const uint32_t* largest;   // of the kernels (nullable)
+  int64_t largest_count;
+  int grow;                  // bits a sum of products may gain
+  uint32_t* any;
+  uint32_t* image;
+};
+__device__ void guard_image(const GuardArgs& g, int n, uint32_t* lds) {
+  const int tid = threadIdx.x, tiles = g.tiles_y * g.tiles_x;
+  uint32_t most = 0, other = 0;
+  bool bad = false;
+  for (int t = 0; t < tiles; ++t) {
+    uint32_t m = 0;
+    const uint32_t* c = g.cells[0] + ((int64_t)n * tiles + t) * g.planes[0] * kFCells;
+    for (int i = tid; i < g.planes[0] * kFCells; i += kThreads) m = max(m, c[i]);
+    __syncthreads();
+    lds[tid] = m;
+    __syncthreads();
+    uint32_t top = 0;
+    for (int i = 0; i < 256; ++i) top = max(top, lds[i]);
+    most = max(most, top);
+    const int cy = tid >> 2, cx = tid & 3, ty = t / g.tiles_x, tx = t % g.tiles_x;
+    const int ys = ty * g.step_y + g.y0, xs = tx * g.step_x + g.x0;  // the tile's first pixel in the plane
+    bool inside = cy + g.win_y <= 8 && cx + g.win_x <= 4;
+    inside = inside && ys + cy * 8 >= 0 && xs + cx * 16 >= 0;
+    inside = inside && (cy + g.win_y) * 8 <= min(g.lim_y, g.h - ys) && (cx + g.win_x) * 16 <= min(g.lim_x, g.w - xs);
+    if (inside) {
+      uint32_t win = 0;
+      for (int y = cy; y < cy + g.win_y; ++y)
+        for (int x = cx; x < cx + g.win_x; ++x)
+          for (int b = 0; b < 8; ++b) win = max(win, lds[b * kFCells + y * 4 + x]);
+      bad |= __uint_as_float(win) < kDarkWindow * __uint_as_float(top);
+    }
+  }
+  if (g.cells[1]) {
+    const uint32_t* c = g.cells[1] + (int64_t)n * tiles * g.planes[1] * kFCells;
+    for (int i = tid; i < tiles * g.planes[1] * kFCells; i += kThreads) other = max(other, c[i]);
+  } else {
+    for (int64_t i = tid; i < g.largest_count; i += kThreads) other = max(other, g.largest[i]);
+  }
+  __syncthreads();
+  lds[tid] = other;
+  __syncthreads();
+  for (int i = 0; i < 256; ++i) other = max(other, lds[i]);
+  // exponents: sums of a transform gain 12 bits, and products of spectra have to stay 24 bits clear of the least float
+  const int ea = (int)(most >> 23) - 127, eb = (int)(other >> 23) - 127;
+  bad |= ea == 128 || eb == 128;  // infinity or NaN
+  if (most && other) bad |= ea + eb + 24 + g.grow > 126 || ea > 110 || eb > 110 || ea + eb < -80 || ea < -90 || eb < -90;
+  const int flag = __syncthreads_or(bad);
+  if (tid == 0) {
+    g.image[n] = flag ? 1 : 0;
+    if (flag) atomicOr(g.any, 1u);
+  }
+}
+
+// ---- products of spectra -------------------------------------------------------------------------------------------
+// C(row, col) = sum_z A(row, z) B(z, col) at every frequency, A conjugated or not.  A block does 16 x 16 pairs at one column
+// v of the spectrum, its wave rho the frequencies u = 4 a + rho: 16 complex products per step of four z on
+// v_mfma_f32_16x16x4_f32, whose operands are one float per lane - lane (row, z) needs the 16 values of ITS plane, which lie
+// together (128 bytes), and nothing another lane has.  They go through a swizzled LDS buffer of the wave's own, so that eight
+// lanes fetch one plane's line together (by themselves every lane would touch 64 lines per load), straight from global memory
+// and one step ahead; there is no barrier in the loop.
+// TAPS operands are the row spectra of kernels: the lane transforms the 16 rows in registers (double) to its wave's 16
+// frequencies, so that the kernels' spectra, four times as large, never reach memory; TAPS results are transformed back the
+// same way, each wave's share of the rows, added over the four waves in LDS.
+struct ProductArgs {
+  const float2* A;
+  const float2* B;
+  float2* C;
+  int rows, cols, depth;
+  int64_t a_row, a_z, b_col, b_z, c_row, c_col;  // in planes (kernels)
+  int64_t a_planes, b_planes, c_planes;          // per column v
+  int64_t c_slice;                               // complex values
+  int tiles_r, tiles_c, splits, per_split;
+  int flush;                                     // (spectra as results) so many products are added in a row, then to C
+  int rows_inner;                                // tiles of rows follow each other (the columns' operand is the larger one)
+  int blocks;                                    // of products; further blocks look for what is declined
+  GuardArgs guard;
+};
+
+__device__ __forceinline__ float4 add4(float4 a, float4 b) { return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w); }
+
+template <bool TAPS_A, bool CONJ_A, bool TAPS_C>
+__global__ __launch_bounds__(kThreads, 2) void spectral_product_kernel(ProductArgs a) {
+  __shared__ __attribute__((aligned(128))) uint4 lds[4][1024];
+  if ((int)blockIdx.x >= a.blocks) return guard_image(a.guard, blockIdx.x - a.blocks, reinterpret_cast<uint32_t*>(&lds[0][0]));
+  const int tid = threadIdx.x, lane = tid & 63, rho = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // blocks that share the larger operand's planes one after the other on the same XCD (blocks are dealt to the eight in turn)
+  int id = blockIdx.x;
+  {
+    const int whole = a.blocks / 8, rest = a.blocks % 8, xcd = id % 8;
+    id = xcd * whole + min(xcd, rest) + id / 8;
+  }
+  const int inner = a.rows_inner ? a.tiles_r : a.tiles_c, outer = a.rows_inner ? a.tiles_c : a.tiles_r;
+  const int ti = id % inner, to = id / inner % outer;
+  const int tr = a.rows_inner ? ti : to, tc = a.rows_inner ? to : ti;
+  id /= inner * outer;
+  const int split = id % a.splits, v = id / a.splits;
+  const int z_begin = split * a.per_split, z_end = min(a.depth, z_begin + a.per_split);
+  uint4* const la = lds[rho];
+  uint4* const lb = lds[rho] + 512;
+
+  // load j of a step: lane i fetches 16 bytes of plane 8 j + i / 8, that is of row 8 (j & 1) + i / 8 and z = j / 2
+  const int piece = (lane & 7) ^ (lane >> 3);
+  const uint4 *pa[2], *pb[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int row = min(tr * 16 + 8 * h + (lane >> 3), a.rows - 1), col = min(tc * 16 + 8 * h + (lane >> 3), a.cols - 1);
+    if (TAPS_A) pa[h] = reinterpret_cast<const uint4*>(a.A + ((int64_t)v * a.a_planes + row * a.a_row) * 16) + piece;
+    else pa[h] = reinterpret_cast<const uint4*>(a.A + ((int64_t)v * a.a_planes + row * a.a_row) * 64 + rho * 16) + piece;
+    pb[h] = reinterpret_cast<const uint4*>(a.B + ((int64_t)v * a.b_planes + col * a.b_col) * 64 + rho * 16) + piece;
+  }
+  const int64_t za = a.a_z * (TAPS_A ? 8 : 32), zb = a.b_z * 32;
+  auto fetch_a = [&](int z0) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int z = z0 + (j >> 1);
+      load_to_lds16(z < z_end ? pa[j & 1] + z * za : reinterpret_cast<const uint4*>(kZeros) + piece, la + 64 * j);
+    }
+  };
+  auto fetch_b = [&](int z0) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) load_to_lds16(pb[j & 1] + min(z0 + (j >> 1), z_end - 1) * zb, lb + 64 * j);
+  };
+  f32x4 re[16], im[16];
+  auto clear = [&]() {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) re[i] = f32x4{0, 0, 0, 0}, im[i] = f32x4{0, 0, 0, 0};
+  };
+  const float(&root)[16][2] = kRoots[rho];
+
+  // what a lane holds: column lane % 16, rows 4 (lane / 16) + e; `more`: C holds the sums before (never those of TAPS results)
+  auto put = [&](bool more) {
+    const int64_t slice = (int64_t)split * a.c_slice;
+    if (!TAPS_C) {
+      // eight lanes a line, through the LDS of the second operand
+      float4* const turn = reinterpret_cast<float4*>(lb);
+      int ln = lane;
+      asm volatile("" : "+v"(ln));  // (or the addresses below are kept in registers throughout the loop: 62 spilled)
+      const int which = ln >> 3, unit = ln & 7;
+      char* const out = reinterpret_cast<char*>(a.C + slice + (int64_t)v * a.c_planes * 64 + rho * 16);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+          turn[ln * 8 + (q ^ unit)] = make_float4(re[2 * q][e], im[2 * q][e], re[2 * q + 1][e], im[2 * q + 1][e]);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {  // the values of lane 8 j + which
+          const int row = tr * 16 + 4 * (j >> 1) + e, col = tc * 16 + 8 * (j & 1) + which;
+          float4 f = turn[(8 * j + which) * 8 + (unit ^ which)];
+          if (row >= a.rows || col >= a.cols) continue;
+          float4* const to = reinterpret_cast<float4*>(out + (unsigned)((row * (int)a.c_row + col * (int)a.c_col) * 512 + unit * 16));
+          if (more) f = add4(f, *to);
+          *to = f;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+      }
+    } else {
+      float4* const share = reinterpret_cast<float4*>(&lds[0][0]);
+#pragma unroll
+      for (int round = 0; round < 2; ++round) {
+        __syncthreads();
+#pragma unroll
+        for (int e2 = 0; e2 < 2; ++e2) {
+          cf t[16];
+#pragma unroll
+          for (int i = 0; i < 16; ++i) t[i] = {re[i][2 * round + e2], im[i][2 * round + e2]};
+#pragma unroll
+          for (int i = 0; i < 4; ++i) dft16_first<true>(t, i);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) dft16_second<true>(t, i);
+#pragma unroll
+          for (int q = 0; q < 8; ++q) {
+            const cf f = t[dft16_at(2 * q)] * cf{root[2 * q][0], -root[2 * q][1]};
+            const cf g = t[dft16_at(2 * q + 1)] * cf{root[2 * q + 1][0], -root[2 * q + 1][1]};
+            share[rho * 1024 + (e2 * 64 + lane) * 8 + (q ^ (lane & 7))] = make_float4(f.x, f.y, g.x, g.y);
+          }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+          const int i = tid + 256 * m, q = i & 7, ln = (i >> 3) & 63, e2 = i >> 9;
+          const int row = tr * 16 + 4 * (ln >> 4) + 2 * round + e2, col = tc * 16 + (ln & 15);
+          const int at = (e2 * 64 + ln) * 8 + (q ^ (ln & 7));
+          const float4 s0 = share[at], s1 = share[1024 + at], s2 = share[2048 + at], s3 = share[3072 + at];
+          if (row >= a.rows || col >= a.cols) continue;
+          float4* const out = reinterpret_cast<float4*>(a.C + slice + ((int64_t)v * a.c_planes + row * a.c_row + col * a.c_col) * 16) + q;
+          *out = add4(add4(s0, s1), add4(s2, s3));
+        }
+      }
+    }
+  };
+
+  // an operand's 16 values out of LDS (the next step's loads land in the same place)
+  auto take = [&](const uint4* from, cf (&f)[16]) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const float4 t = __builtin_bit_cast(float4, from[lane * 8 + (q ^ (lane & 7))]);
+      f[2 * q] = {t.x, t.y}, f[2 * q + 1] = {t.z, t.w};
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  };
+  auto multiply = [&](cf x, cf y, int i) {
+    re[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.x, y.x, re[i], 0, 0, 0);
+    im[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.x, y.y, im[i], 0, 0, 0);
+    re[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(CONJ_A ? x.y : -x.y, y.y, re[i], 0, 0, 0);
+    im[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(CONJ_A ? -x.y : x.y, y.x, im[i], 0, 0, 0);
+  };
+  // a part in eight of a lane's transform of 16 kernel rows to the wave's frequencies
+  auto transform = [&](cf (&t)[16], int part) {
+    if (part < 4) {
+#pragma unroll
+      for (int r = part; r < 16; r += 4) t[r] = t[r] * cf{root[r][0], root[r][1]};
+      dft16_first<false>(t, part);
+    } else {
+      dft16_second<false>(t, part - 4);
+    }
+  };
+
+  // Loads complete in order, eight per operand and step: with eight still out, all but the last operand fetched are there.
+  fetch_a(z_begin);
+  fetch_b(z_begin);
+  cf fa[16], fb[16];
+  if (TAPS_A) {
+    // The next step's transform runs between this step's products: waves that did one after the other did the same thing at
+    // the same time.
+    cf ga[16];
+    asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+    take(la, fa);
+    fetch_a(z_begin + 4);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) transform(fa, q);
+    asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+    take(lb, fb);
+    fetch_b(z_begin + 4);
+    auto step = [&](int z0, cf (&xa)[16], cf (&ya)[16], bool last) {
+      asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+      take(la, ya);
+      fetch_a(z0 + 8);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        multiply(xa[dft16_at(2 * q)], fb[2 * q], 2 * q);
+        multiply(xa[dft16_at(2 * q + 1)], fb[2 * q + 1], 2 * q + 1);
+        transform(ya, q);
+#pragma unroll
+        for (int m = 0; m < 8; ++m) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one matrix instruction,
+          __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);  // four of the vector units
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+      take(lb, fb);
+      if (!last) fetch_b(z0 + 8);  // (the sums leave through its place)
+    };
+    for (int z_put = z_begin; z_put < z_end; z_put += a.flush) {
+      const int z_next = min(z_put + a.flush, z_end);
+      clear();
+      for (int z0 = z_put;;) {
+        step(z0, fa, ga, z0 + 4 >= z_next);
+        z0 += 4;
+        if (z0 >= z_next) {
+#pragma unroll
+          for (int i = 0; i < 16; ++i) fa[i] = ga[i];
+          break;
+        }
+        step(z0, ga, fa, z0 + 4 >= z_next);
+        z0 += 4;
+        if (z0 >= z_next) break;
+      }
+      put(z_put > z_begin);
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      if (z_next < z_end) fetch_b(z_next + 4);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (the last fetch)
+  } else {
+    clear();
+    for (int z0 = z_begin; z0 < z_end; z0 += 4) {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      take(la, fa);
+      take(lb, fb);
+      if (z0 + 4 < z_end) fetch_a(z0 + 4), fetch_b(z0 + 4);
+#pragma unroll
+      for (int i = 0; i < 16; ++i) multiply(fa[i], fb[i], i);
+    }
+    put(false);
+  }
+}
+
+// ---- plans ---------------------------------------------------------------------------------------------------------
+static size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
+
+namespace {
+struct Layout {  // of the workspace
+  size_t image, map, taps, words;          // offsets
+  size_t cells_image, cells_map, largest, sums;  // inside words
+};
+}  // namespace
+
+static bool one_tile(const ConvGeom& g) { return g.h + 2 * g.ph <= kFL && g.w + 2 * g.pw <= kFL; }
+static int64_t tiles_of(const ConvGeom& g, const SpectralPlan& p) { return (int64_t)g.n * p.tiles_y * p.tiles_x; }
+
+static Layout layout(const ConvGeom& g, int pass, const SpectralPlan& p) {
+  Layout l{};
+  const int64_t tiles = tiles_of(g, p);
+  l.image = 0;
+  l.map = l.image + p.image_bytes;
+  l.taps = l.map + p.map_bytes;
+  l.words = l.taps + p.taps_bytes;
+  size_t at = l.words + align256(256 + 4 * (size_t)g.n);
+  l.cells_image = at;
+  if (pass != VCNN_PASS_BWD_DATA) at += align256((size_t)tiles * g.c * kFCells * 4);
+  l.cells_map = at;
+  if (pass != VCNN_PASS_FWD) at += align256((size_t)tiles * g.k * kFCells * 4);
+  l.largest = at;
+  if (pass != VCNN_PASS_BWD_FILTER) at += align256((size_t)ceil_div((int64_t)g.k * g.c, 4) * 4);
+  l.sums = at;
+  if (pass == VCNN_PASS_BWD_FILTER) at += align256((size_t)tiles * g.k * 8);
+  (void)at;
+  return l;
+}
+static size_t words_bytes(const ConvGeom& g, int pass, const SpectralPlan& p) {
+  SpectralPlan q = p;
+  q.image_bytes = q.map_bytes = q.taps_bytes = 0;
+  const Layout l = layout(g, pass, q);
+  return l.sums + (pass == VCNN_PASS_BWD_FILTER ? align256((size_t)tiles_of(g, p) * g.k * 8) : 0);
+}
+
+bool spectral_plan(const ConvGeom& g, int pass, size_t budget, SpectralPlan* p) {
+  if (g.r > kFTaps || g.s > kFTaps || g.c <= 4 || g.k <= 4) return false;
+  const bool data = pass == VCNN_PASS_BWD_DATA, filter = pass == VCNN_PASS_BWD_FILTER;
+  SpectralPlan q{};
+  if (one_tile(g)) {
+    q.tiles_y = q.tiles_x = 1;
+    q.step_y = q.step_x = kFL;
+  } else {
+    q.step_y = kFL - g.r + 1, q.step_x = kFL - g.s + 1;
+    q.tiles_y = (int)ceil_div(data ? g.h : g.oh, q.step_y), q.tiles_x = (int)ceil_div(data ? g.w : g.ow, q.step_x);
+  }
+  const int64_t tiles = tiles_of(g, q), spectrum = (int64_t)kFV * kFL * 8, taps = (int64_t)kFV * kFTaps * 8;
+  if (tiles * std::max(g.c, g.k) > (1 << 20)) return false;
+  const size_t image = align256((size_t)(tiles * g.c * spectrum));
+  const double rows = data ? g.c : g.k, cols = filter ? (double)g.c : (double)tiles, depth = filter ? (double)tiles : (data ? g.k : g.c);
+  // No sum over maps or images is longer than 32 complex products, 64 roundings of the float instruction: the input
+  // gradient's blocks take two of them (as one, 16 38 64 64 -> 512 16 16 has an error of
+  // 2.1e-7, the two-term product 1.9e-7),
+  // the slices are added in double.  (Those over channels stay whole: a slice of a forward pass is as large as its result.)
+  const int most = data ? 64 : (filter ? 32 : 1 << 30);
+  q.per_split = (int)std::min<double>(depth, most);
+  q.splits = (int)std::ceil(depth / q.per_split);
+  q.part = g.k;
+  q.image_bytes = image * (data ? q.splits : 1);
+  q.taps_bytes = align256((size_t)((int64_t)g.k * g.c * taps)) * (filter ? q.splits : 1);
+  q.map_bytes = align256((size_t)(tiles * g.k * spectrum));
+  q.words_bytes = words_bytes(g, pass, q);
+  if (pass == VCNN_PASS_FWD && q.image_bytes + q.map_bytes + q.taps_bytes + q.words_bytes > budget) {
+    // as many maps at once as the budget holds, in whole tiles of 16
+    int64_t maps = ceil_div(g.k, 16) * 16;
+    do {
+      maps -= 16;
+      if (maps < 16) return false;
+      q.part = (int)(ceil_div(ceil_div(g.k, 16), ceil_div(g.k, maps)) * 16);
+      q.map_bytes = align256((size_t)(tiles * q.part * spectrum));
+      q.taps_bytes = align256((size_t)((int64_t)q.part * g.c * taps));
+    } while (q.image_bytes + q.map_bytes + q.taps_bytes + q.words_bytes > budget);
+  }
+  q.workspace_bytes = q.image_bytes + q.map_bytes + q.taps_bytes + q.words_bytes;
+  if (q.workspace_bytes > budget) return false;
+  // What the transforms read and write at 4.4 TB/s, and the products: blocks of so many steps of four, two of them resident on
+  // each of 256 CUs at 2.7 us a step (3.4 where the larger operand is read by every block; one alone 2.2 us), four steps' worth
+  // to begin and to end with.  (110 passes of 40 drawn layers, 44 to 861 us, take 0.75 to 1.2 times this.)
+  const double parts = (double)ceil_div(g.k, q.part), e = 4, pixels = (double)g.n * ((double)g.c * g.h * g.w + (double)g.k * g.P);
+  const double bytes = pixels * e + 2.0 * (double)(q.image_bytes + (size_t)(tiles * g.k * spectrum)) +
+                       2.0 * (double)g.k * g.c * taps * (filter ? q.splits : 1) + (double)g.M * g.K * e;
+  const double blocks = kFV * std::ceil(rows / 16) * std::ceil(cols / 16) * q.splits, steps = std::ceil(q.per_split / 4.0) + 4;
+  q.est_seconds = bytes / 4.4e12 + (blocks <= 256 ? 2.2e-6 : std::ceil(blocks / 512) * (data ? 3.4e-6 : 2.7e-6)) * steps + 5e-6 * (1 + 3 * parts);
+  *p = q;
+  return true;
+}
+
+// ---- passes --------------------------------------------------------------------------------------------------------
+template <bool TAPS_A, bool CONJ_A, bool TAPS_C>
+static vcnn_status launch_product(ProductArgs a, int guard_blocks, hipStream_t st) {
+  a.tiles_r = (int)ceil_div(a.rows, 16), a.tiles_c = (int)ceil_div(a.cols, 16);
+  a.blocks = kFV * a.tiles_r * a.tiles_c * a.splits;
+  hipLaunchKernelGGL((spectral_product_kernel<TAPS_A, CONJ_A, TAPS_C>), dim3((unsigned)(a.blocks + guard_blocks)), dim3(kThreads), 0, st, a);
+  return check_launch("spectral_product");
+}
+
+static SpectralTiles tiles_for(const ConvGeom& g, const SpectralPlan& p, int channels, int h, int w) {
+  SpectralTiles t{};
+  t.images = g.n, t.channels = channels, t.first = 0, t.count = channels;
+  t.h = h, t.w = w;
+  t.tiles_y = p.tiles_y, t.tiles_x = p.tiles_x, t.step_y = p.step_y, t.step_x = p.step_x;
+  t.lim_y = t.lim_x = kFL;
+  return t;
+}
+static GuardArgs guard_for(const SpectralTiles& t, const uint32_t* cells, int win_h, int win_w, char* words) {
+  GuardArgs g{};
+  g.cells[0] = cells, g.planes[0] = t.channels;
+  g.tiles_y = t.tiles_y, g.tiles_x = t.tiles_x, g.images = t.images;
+  g.step_y = t.step_y, g.step_x = t.step_x, g.y0 = t.y0, g.x0 = t.x0, g.h = t.h, g.w = t.w, g.lim_y = t.lim_y, g.lim_x = t.lim_x;
+  g.win_y = std::max(1, (win_h + 7) / 8), g.win_x = std::max(1, (win_w + 15) / 16);
+  g.any = reinterpret_cast<uint32_t*>(words), g.image = reinterpret_cast<uint32_t*>(words + 256);
+  return g;
+}
+static int bits_of(int64_t n) { return (int)std::ceil(std::log2((double)std::max<int64_t>(n, 1))); }
+
+vcnn_status launch_spectral_fwd(const SpectralPlan& p, int dtype, const ConvGeom& g, const void* x, const void* w, const float* bias,
+                                void* y, int relu, void* workspace, hipStream_t st) {
+  const Layout l = layout(g, VCNN_PASS_FWD, p);
+  char* const ws = (char*)workspace;
+  float2* const xs = (float2*)(ws + l.image);
+  float2* const ys = (float2*)(ws + l.map);
+  float2* const taps = (float2*)(ws + l.taps);
+  uint32_t* const cells = (uint32_t*)(ws + l.cells_image);
+  uint32_t* const largest = (uint32_t*)(ws + l.largest);
+  const int64_t tiles = tiles_of(g, p);
+  const int esize = dtype == VCNN_BF16 ? 2 : 4;
+  SpectralTiles tx = tiles_for(g, p, g.c, g.h, g.w);
+  tx.y0 = -g.ph, tx.x0 = -g.pw;
+  if (vcnn_status s = launch_plane_spectra(tx, dtype, x, xs, cells, nullptr, (uint32_t*)(ws + l.words), st)) return s;
+  SpectralTiles ty = tiles_for(g, p, g.k, g.oh, g.ow);
+  ty.lim_y = std::min(p.step_y, g.oh), ty.lim_x = std::min(p.step_x, g.ow);
+  for (int k0 = 0; k0 < g.k; k0 += p.part) {
+    const int maps = std::min(p.part, g.k - k0);
+    const bool last = k0 + maps == g.k;
+    if (vcnn_status s = launch_taps_spectra(dtype, (const char*)w + (int64_t)k0 * g.K * esize, (int64_t)maps * g.c, g.r, g.s, taps,
+                                            largest + (int64_t)k0 * g.c / 4, st)) return s;
+    ProductArgs a{};
+    a.A = taps, a.B = xs, a.C = ys;
+    a.rows = maps, a.cols = (int)tiles, a.depth = g.c;
+    a.a_row = g.c, a.a_z = 1, a.a_planes = (int64_t)maps * g.c;
+    a.b_col = g.c, a.b_z = 1, a.b_planes = tiles * g.c;
+    a.c_row = 1, a.c_col = maps, a.c_planes = tiles * maps;
+    a.splits = p.splits, a.per_split = p.per_split, a.flush = g.c;
+    if (last) {
+      a.guard = guard_for(tx, cells, g.r, g.s, ws + l.words);
+      a.guard.largest = largest, a.guard.largest_count = ceil_div((int64_t)g.k * g.c, 4);
+      a.guard.grow = bits_of((int64_t)g.c * g.r * g.s);
+    }
+    if (vcnn_status s = launch_product<true, true, false>(a, last ? g.n : 0, st)) return s;
+    ty.first = k0, ty.count = maps;
+    if (vcnn_status s = launch_plane_inverse(ty, dtype, ys, 0, 1, y, bias, relu, st)) return s;
+  }
+  return VCNN_OK;
+}
+
+vcnn_status launch_spectral_bwd_data(const SpectralPlan& p, int dtype, const ConvGeom& g, const void* w, const void* dy, void* dx,
+                                     void* workspace, hipStream_t st) {
+  const Layout l = layout(g, VCNN_PASS_BWD_DATA, p);
+  char* const ws = (char*)workspace;
+  float2* const xs = (float2*)(ws + l.image);
+  float2* const ys = (float2*)(ws + l.map);
+  float2* const taps = (float2*)(ws + l.taps);
+  uint32_t* const cells = (uint32_t*)(ws + l.cells_map);
+  uint32_t* const largest = (uint32_t*)(ws + l.largest);
+  const int64_t tiles = tiles_of(g, p);
+  const bool one = one_tile(g);
+  // Pixel i of the padded plane gets dy[i - q] w[q].  A whole plane starts at dy's first pixel; a tile of a larger one starts
+  // r - 1 pixels before its results, of which the transform wraps that many.
+  SpectralTiles tdy = tiles_for(g, p, g.k, g.oh, g.ow);
+  tdy.y0 = one ? 0 : g.ph - (g.r - 1), tdy.x0 = one ? 0 : g.pw - (g.s - 1);
+  SpectralTiles tdx = tiles_for(g, p, g.c, g.h, g.w);
+  tdx.y0 = one ? g.ph : g.r - 1, tdx.x0 = one ? g.pw : g.s - 1;
+  tdx.lim_y = std::min(p.step_y, g.h), tdx.lim_x = std::min(p.step_x, g.w);
+  if (vcnn_status s = launch_plane_spectra(tdy, dtype, dy, ys, cells, nullptr, (uint32_t*)(ws + l.words), st)) return s;
+  if (vcnn_status s = launch_taps_spectra(dtype, w, (int64_t)g.k * g.c, g.r, g.s, taps, largest, st)) return s;
+  ProductArgs a{};
+  a.A = taps, a.B = ys, a.C = xs;
+  a.rows = g.c, a.cols = (int)tiles, a.depth = g.k, a.rows_inner = 1;
+  a.a_row = 1, a.a_z = g.c, a.a_planes = (int64_t)g.k * g.c;
+  a.b_col = g.k, a.b_z = 1, a.b_planes = tiles * g.k;
+  a.c_row = 1, a.c_col = g.c, a.c_planes = tiles * g.c;
+  a.splits = p.splits, a.per_split = p.per_split, a.flush = 32, a.c_slice = (int64_t)(p.image_bytes / p.splits / 8);
+  a.guard = guard_for(tdy, cells, g.r, g.s, ws + l.words);
+  a.guard.largest = largest, a.guard.largest_count = ceil_div((int64_t)g.k * g.c, 4);
+  a.guard.grow = bits_of((int64_t)g.k * g.r * g.s);
+  if (vcnn_status s = launch_product<true, false, false>(a, g.n, st)) return s;
+  return launch_plane_inverse(tdx, dtype, xs, a.c_slice, p.splits, dx, nullptr, 0, st);
+}
+
+vcnn_status launch_spectral_filter(const SpectralPlan& p, int dtype, const ConvGeom& g, const void* x, const void* dy, float* dw,
+                                   float* db, void* workspace, hipStream_t st) {
+  const Layout l = layout(g, VCNN_PASS_BWD_FILTER, p);
+  char* const ws = (char*)workspace;
+  float2* const xs = (float2*)(ws + l.image);
+  float2* const ys = (float2*)(ws + l.map);
+  float2* const taps = (float2*)(ws + l.taps);
+  uint32_t* const cells_x = (uint32_t*)(ws + l.cells_image);
+  uint32_t* const cells_dy = (uint32_t*)(ws + l.cells_map);
+  double* const sums = (double*)(ws + l.sums);
+  const int64_t tiles = tiles_of(g, p);
+  SpectralTiles tx = tiles_for(g, p, g.c, g.h, g.w);
+  tx.y0 = -g.ph, tx.x0 = -g.pw;
+  SpectralTiles tdy = tiles_for(g, p, g.k, g.oh, g.ow);
+  tdy.lim_y = std::min(p.step_y, g.oh), tdy.lim_x = std::min(p.step_x, g.ow);  // every output pixel in one tile
+  if (vcnn_status s = launch_plane_spectra(tx, dtype, x, xs, cells_x, nullptr, (uint32_t*)(ws + l.words), st)) return s;
+  if (vcnn_status s = launch_plane_spectra(tdy, dtype, dy, ys, cells_dy, db ? sums : nullptr, nullptr, st)) return s;
+  ProductArgs a{};
+  a.A = ys, a.B = xs, a.C = taps;
+  a.rows = g.k, a.cols = g.c, a.depth = (int)tiles;
+  a.a_row = 1, a.a_z = g.k, a.a_planes = tiles * g.k;
+  a.b_col = 1, a.b_z = g.c, a.b_planes = tiles * g.c;
+  a.c_row = g.c, a.c_col = 1, a.c_planes = (int64_t)g.k * g.c;
+  a.splits = p.splits, a.per_split = p.per_split, a.flush = 32, a.c_slice = (int64_t)(p.taps_bytes / p.splits / 8);
+  a.guard = guard_for(tx, cells_x, tdy.lim_y, tdy.lim_x, ws + l.words);
+  a.guard.cells[1] = cells_dy, a.guard.planes[1] = g.k;
+  a.guard.grow = bits_of(g.N);
+  if (vcnn_status s = launch_product<false, true, true>(a, g.n, st)) return s;
+  return launch_taps_inverse(taps, a.c_slice, p.splits, (int64_t)g.k * g.c, g.r, g.s, dw, sums, (int)tiles, g.k, db, st);
+}
+
+Declined spectral_declined(const ConvGeom& g, int pass, const SpectralPlan& p, const void* workspace) {
+  const uint32_t* const words = (const uint32_t*)((const char*)workspace + layout(g, pass, p).words);
+  return Declined{words, words + 1, words + 64};
+}
+
+}  // namespace vcnn

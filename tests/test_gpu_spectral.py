@@ -1,0 +1,289 @@
+"""Passes through the Fourier domain (the AUTO route of layers with large kernels): parity with the oracle at the edges of
+tiles, planes and slices, what is left to the float kernel on the device, parts, and the direct route where the workspace is
+too small."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from paper_1501_07338_amd import vcnn
+from paper_1501_07338_amd.workloads import bf16_round, random_tensor
+from util import assert_close, to_np
+
+DEV = "cuda:0"
+FWD, FILTER, DATA = vcnn.PASS_FWD, vcnn.PASS_BWD_FILTER, vcnn.PASS_BWD_DATA
+# the spectra are rounded to float (2^-24 of each, twice the kernels') and added over channels, maps or images: measured
+# below 2e-6 of the largest element
+TOL = 4e-6
+
+# (n, c, h, w, k, r, s, pad_h, pad_w), the passes, bfloat16
+SHAPES = [
+    ((27, 28, 64, 64, 29, 16, 16, 0, 0), {FWD, FILTER, DATA}, False),   # one whole tile; the largest kernel; ragged maps, images
+    ((12, 41, 39, 31, 33, 12, 12, 11, 8), {FILTER, DATA}, False),       # padded by as much as the kernel; ragged channels
+    ((11, 11, 69, 64, 60, 11, 15, 0, 0), {FWD, FILTER}, False),         # tiles along one axis, the second a few rows
+    ((14, 13, 103, 100, 13, 13, 12, 0, 0), {FWD, DATA}, False),         # 2 x 2 tiles, more than 32 of them
+    ((17, 24, 58, 60, 50, 8, 9, 0, 0), {FILTER}, False),                # odd kernel columns
+    ((41, 13, 95, 41, 12, 14, 13, 1, 1), {DATA}, False),                # padded tiles
+    ((5, 12, 60, 38, 98, 8, 16, 5, 11), {FWD, FILTER}, False),          # more than 64 maps; pads on one side of a tile
+    ((20, 40, 64, 64, 139, 16, 16, 0, 0), {FWD, DATA}, False),          # maps in slices, the last one short
+    ((40, 11, 64, 64, 150, 16, 16, 0, 0), {FILTER}, False),             # images in two slices, the second short
+    ((4, 36, 98, 41, 67, 10, 15, 0, 0), {FILTER}, True),
+    ((30, 29, 64, 62, 180, 16, 16, 0, 0), {FWD, FILTER, DATA}, True),
+]
+ONE_EACH = [((9, 22, 70, 70, 49, 16, 16, 0, 0), FWD), ((27, 28, 64, 64, 29, 16, 16, 0, 0), DATA), ((11, 11, 69, 64, 60, 11, 15, 0, 0), FILTER)]
+
+
+def desc(shape, bf16=False):
+    return vcnn.conv_desc(*shape, dtype=vcnn.BF16 if bf16 else vcnn.F32)
+
+
+def route(d, which):
+    return vcnn.conv_route(d, which, vcnn.conv_workspace_bytes(d, which))
+
+
+def tensors(shape, seed, bf16=False):
+    n, c, h, w, k, r, s, ph, pw = shape
+    d = desc(shape, bf16)
+    oh, ow = vcnn.conv_out_shape(d)
+    t = (np.maximum(random_tensor(seed, (n, c, h, w)), 0), random_tensor(seed + 1, (k, c, r, s), scale=(2.0 / (c * r * s)) ** 0.5),
+         random_tensor(seed + 3, (n, k, oh, ow)))
+    x, wt, dy = (bf16_round(a) for a in t) if bf16 else t
+    return d, x, wt, random_tensor(seed + 2, (k,), scale=0.1), dy
+
+
+def run_pass(d, which, x, wt, b, dy, nbytes=None, act=None):
+    bf16 = d.dtype == vcnn.BF16
+    up = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(DEV).to(torch.bfloat16 if bf16 else torch.float32)
+    xd, wd, dyd, bd = up(x), up(wt), up(dy), torch.from_numpy(b).to(DEV)
+    nbytes = vcnn.conv_workspace_bytes(d, which) if nbytes is None else nbytes
+    ws = torch.full((nbytes,), 255, dtype=torch.uint8, device=DEV) if nbytes else None
+    if which == FILTER:
+        dw, db = torch.full(wt.shape, float("nan"), device=DEV), torch.full(b.shape, float("nan"), device=DEV)
+        vcnn.conv_bwd_filter(d, xd, dyd, dw, db, ws)
+        return to_np(dw), to_np(db)
+    out = torch.full((dy if which == FWD else x).shape, float("nan"), device=DEV).to(xd.dtype)
+    if which == FWD:
+        vcnn.conv_fwd(d, xd, wd, bd, out, ws)
+    elif act is None:
+        vcnn.conv_bwd_data(d, wd, dyd, out, ws)
+    else:
+        vcnn.conv_bwd_data_act(d, act, xd, wd, dyd, out, ws)
+    return to_np(out.float())
+
+
+def expected(d, which, x, wt, b, dy, images):
+    pad = (d.pad_h, d.pad_w)
+    if which == FWD:
+        return O.conv_fwd(x[images], wt, b, pad=pad)
+    return O.conv_bwd_data(wt, dy[images], (d.h, d.w), pad=pad)
+
+
+def probes(d, x, dy, seed, count=300):
+    """Elements of the kernel gradient, corners of it among them, and what they are."""
+    rng = np.random.default_rng(seed)
+    idx = np.stack([rng.integers(0, m, count) for m in (d.k, d.c, d.r, d.s)], 1)
+    idx[:4] = [(0, 0, 0, 0), (d.k - 1, d.c - 1, d.r - 1, d.s - 1), (0, d.c - 1, 0, d.s - 1), (d.k - 1, 0, d.r - 1, 0)]
+    return idx, O.conv_bwd_filter_at(x, dy, (d.r, d.s), (d.pad_h, d.pad_w), idx)
+
+
+def check(d, which, x, wt, b, dy, got, tol, seed=0):
+    if which == FILTER:
+        idx, want = probes(d, x, dy, seed)
+        scale = np.max(np.abs(got[0].astype(np.float64)))
+        assert np.all(np.isfinite(got[0])) and np.max(np.abs(got[0][tuple(idx.T)] - want)) <= tol * scale
+        assert_close(got[1], dy.astype(np.float64).sum((0, 2, 3)), tol, "db")
+    else:
+        assert np.all(np.isfinite(got))
+        images = [0, d.n - 1]
+        assert_close(got[images], expected(d, which, x, wt, b, dy, images), tol)
+
+
+@pytest.mark.parametrize("shape,passes,bf16", SHAPES)
+def test_routes_of_the_tested_layers(shape, passes, bf16):
+    for which in passes:
+        assert route(desc(shape, bf16), which) == "spectral", which
+
+
+def test_small_kernels_and_few_maps_stay():
+    """No GPU needed: kernels the transforms do not take, and layers they do not pay for."""
+    for shape in ((27, 28, 64, 64, 29, 17, 16, 0, 0), (27, 28, 64, 64, 29, 6, 6, 0, 0), (27, 28, 64, 64, 4, 16, 16, 0, 0),
+                  (27, 4, 64, 64, 29, 16, 16, 0, 0), (1, 8, 30, 30, 8, 9, 9, 0, 0)):
+        assert all(route(desc(shape), which) != "spectral" for which in (FWD, FILTER, DATA)), shape
+
+
+def test_queries_and_routes_agree():
+    """No GPU needed: over drawn layers a pass runs with exactly what its query asks for and with more; the kernel gradient
+    by the same route, and the allocation-free entry point takes no layer that it refused."""
+    rng, seen = np.random.default_rng(3), set()
+    log = lambda lo, hi: int(round(np.exp(rng.uniform(np.log(lo), np.log(hi)))))
+    for _ in range(600):
+        r, s = int(rng.integers(7, 17)), int(rng.integers(7, 17))
+        bf16 = bool(rng.random() < 0.3)
+        d = desc((log(1, 100), log(5, 100), log(r, 130), log(s, 130), log(5, 300), r, s, int(rng.integers(0, r)), int(rng.integers(0, s))), bf16)
+        for which in (FWD, FILTER, DATA):
+            need = vcnn.conv_workspace_bytes(d, which)
+            name = vcnn.conv_route(d, which, need)
+            for more in (need + 256, need + (64 << 20)):
+                assert vcnn.conv_route(d, which, more) == name or which != FILTER
+            if name == "spectral":
+                seen.add((which, bf16))
+                assert which != FWD or need <= 64 << 20
+                if which == FILTER:  # (what it takes without the transforms)
+                    direct = vcnn.conv_workspace_bytes(vcnn.conv_desc(d.n, d.c, d.h, d.w, d.k, d.r, d.s, d.pad_h, d.pad_w, dtype=d.dtype), which)
+                    assert direct == need
+    assert {(FWD, False), (FILTER, False), (DATA, False), (FILTER, True)} <= seen
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,passes,bf16", SHAPES)
+def test_against_the_oracle(shape, passes, bf16):
+    d, x, wt, b, dy = tensors(shape, 5100, bf16)
+    for which in sorted(passes):
+        assert route(d, which) == "spectral"
+        got = run_pass(d, which, x, wt, b, dy)
+        check(d, which, x, wt, b, dy, got, 4e-3 if bf16 and which != FILTER else TOL)  # (one rounding to eight bits)
+        again = run_pass(d, which, x, wt, b, dy)
+        assert all(np.array_equal(p, q) for p, q in zip(got, again))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,which", [t for t in ONE_EACH if t[1] != FILTER])
+def test_an_image_does_not_depend_on_its_neighbours(shape, which):
+    """Bit for bit, whatever the magnitudes of the other images, also where one of those is not finite."""
+    d, x, wt, b, dy = tensors(shape, 5200)
+    base = run_pass(d, which, x, wt, b, dy)
+    for big in (np.float32(2.0 ** 60), np.float32(np.inf)):
+        x2, dy2 = x.copy(), dy.copy()
+        x2[1] *= big
+        dy2[1] *= big
+        with np.errstate(invalid="ignore"):
+            got = run_pass(d, which, x2, wt, b, dy2)
+        others = np.arange(d.n) != 1
+        assert np.array_equal(got[others], base[others])
+        assert np.isfinite(big) or not np.all(np.isfinite(got[1]))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,which", ONE_EACH)
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("case", ["outlier", "dark", "inf", "nan", "weight", "range"])
+def test_what_the_transforms_do_not_carry(shape, which, bf16, case):
+    """An element or a window far from the rest of its plane, infinities and NaN, magnitudes whose products leave a float's
+    range on the way: the pass gives what the float kernel gives, every output to that kernel's own accuracy."""
+    shape = (30, 29, 64, 62, 180, 16, 16, 0, 0) if bf16 else shape
+    d, x, wt, b, dy = tensors(shape, 5300, bf16)
+    assert route(d, which) == "spectral"
+    b = np.zeros_like(b)
+    t = dy if which == DATA else x
+    if case == "outlier":    # meets zeros only
+        t[0, 2, 5, 5] = 2.0 ** 45
+        if which == FWD:
+            wt[:, 2] = 0
+        elif which == DATA:
+            wt[2] = 0
+        else:
+            dy[0] = 0
+    elif case == "dark":
+        t[0, :, :40, :40] *= np.float32(2.0 ** -16)
+    elif case == "weight":
+        if which == FILTER:
+            dy[1, 1, 1, 1] = np.inf
+        else:
+            wt[1, 1, 1, 1] = np.inf
+    elif case == "range":
+        t *= np.float32(2.0 ** 62)
+        (dy if which == FILTER else wt)[...] *= np.float32(2.0 ** 40)
+    else:
+        t[0, 1, 3, 3] = np.inf if case == "inf" else np.nan
+    with np.errstate(all="ignore"):
+        got = run_pass(d, which, x, wt, b, dy)
+        vcnn.set_conv_algo(vcnn.ALGO_IMPLICIT)
+        try:
+            want = run_pass(d, which, x, wt, b, dy)
+        finally:
+            vcnn.set_conv_algo(vcnn.ALGO_AUTO)
+    got, want = (got[0], want[0]) if which == FILTER else (got, want)
+    # what has to be the float kernel's: the image, or all of it
+    image = (0,) if which != FILTER and case not in ("weight", "range") else (slice(None),)
+    g, e = got[image].astype(np.float64), want[image].astype(np.float64)
+    assert np.array_equal(np.isnan(g), np.isnan(e)) and np.array_equal(np.isposinf(g), np.isposinf(e))
+    fine = np.isfinite(e)
+    if which == FILTER:  # (its slices are added in another order there)
+        assert np.max(np.abs(g - e)[fine], initial=0) <= TOL * np.max(np.abs(e[fine]), initial=0)
+    else:
+        assert np.array_equal(g[fine], e[fine])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("act", [vcnn.ACT_RELU, vcnn.ACT_TANH, vcnn.ACT_SIGMOID])
+def test_activation_derivative(act):
+    """Applied once, to the images the float kernel computes as to the others."""
+    d, x, wt, b, dy = tensors(ONE_EACH[1][0], 5400)
+    assert route(d, DATA) == "spectral"
+    dy[1, 0, 0, 0] = 2.0 ** 45
+    wt[0] = 0
+    y = (np.tanh(x) * np.float32(0.7)).astype(np.float32)
+    ref = {vcnn.ACT_RELU: y > 0, vcnn.ACT_TANH: 1 - y.astype(np.float64) ** 2, vcnn.ACT_SIGMOID: y * (1 - y.astype(np.float64))}[act]
+    got = run_pass(d, DATA, y, wt, b, dy, act=act)
+    for i in (0, 1, d.n - 1):
+        assert_close(got[i], expected(d, DATA, x, wt, b, dy, [i])[0] * ref[i], TOL, f"image {i}")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,which", ONE_EACH)
+def test_recorded_call_decides_anew_on_every_replay(shape, which):
+    d, x, wt, b, dy = tensors(shape, 5500)
+    xd, wd, bd, dyd = (torch.from_numpy(a).to(DEV) for a in (x, wt, b, dy))
+    ws = torch.empty(vcnn.conv_workspace_bytes(d, which), dtype=torch.uint8, device=DEV)
+    out = torch.empty({FWD: dy, FILTER: wt, DATA: x}[which].shape, device=DEV)
+    db = torch.empty(b.shape, device=DEV)
+    call = {FWD: lambda: vcnn.conv_fwd(d, xd, wd, bd, out, ws), DATA: lambda: vcnn.conv_bwd_data(d, wd, dyd, out, ws),
+            FILTER: lambda: vcnn.conv_bwd_filter(d, xd, dyd, out, db, ws)}[which]
+    call()
+    torch.cuda.synchronize()
+    stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        call()
+    moved = {FWD: xd, FILTER: xd, DATA: dyd}[which]
+    first = moved.clone()
+    for value in (None, 2.0 ** 45, None, np.inf, np.nan, None):
+        moved.copy_(first)
+        if value is not None:
+            moved[-1, -1, -1, -1] = value
+        ws.fill_(255)
+        graph.replay()
+        torch.cuda.synchronize()
+        got = out.clone()
+        assert np.isfinite(torch.randn(1 << 16, device=DEV).sum().item())  # unrelated eager work between replays
+        call()
+        torch.cuda.synchronize()
+        assert torch.equal(torch.nan_to_num(got, 7.0, 8.0, 9.0), torch.nan_to_num(out, 7.0, 8.0, 9.0))
+
+
+@pytest.mark.gpu
+def test_parts_and_smaller_workspaces():
+    """The forward pass in parts of its maps gives the same bits; with less workspace than that a direct route runs."""
+    shape = (16, 38, 64, 64, 512, 16, 16, 0, 0)
+    d, x, wt, b, dy = tensors(shape, 5600)
+    need = vcnn.conv_workspace_bytes(d, FWD)
+    whole, parts = (run_pass(d, FWD, x, wt, b, dy, z) for z in (300 << 20, need))
+    assert np.array_equal(whole, parts)
+    x[3, :, :40, :40] = 0  # declined: in every part
+    whole, parts = (run_pass(d, FWD, x, wt, b, dy, z) for z in (300 << 20, need))
+    assert np.array_equal(whole, parts)
+    assert np.array_equal(whole[3][:, :25, :25], np.broadcast_to(b[:, None, None], whole[3][:, :25, :25].shape))
+    for which in (FWD, FILTER, DATA):
+        d, x, wt, b, dy = tensors(ONE_EACH[1][0], 5700)
+        need = vcnn.conv_workspace_bytes(d, which)
+        low, high = -1, need
+        while high - low > 1:  # the least the pass runs with
+            mid = (low + high) // 2
+            try:
+                vcnn.conv_route(d, which, mid)
+                high = mid
+            except vcnn.VcnnError:
+                low = mid
+        assert vcnn.conv_route(d, which, high) != "spectral"
+        got, want = (run_pass(d, which, x, wt, b, dy, z) for z in (high, need))
+        got, want = (got[0], want[0]) if which == FILTER else (got, want)
+        assert_close(got, want, 2 * TOL)
