@@ -488,12 +488,15 @@ static Plan direct_plan(const ConvGeom& g, int pass, int dtype, size_t offered) 
 // 3.33 / 0.70 ms, in bfloat16 1.25 / 0.68 ms; 3 354 64 64 -> 69 8 14 kernel gradient 813 / 126 us; 32 17 64 64 -> 90 11 11 forward
 // 210 / 65 us; 16 13 64 64 -> 57 9 9 forward 64 / 44 us; 57 39 34 34 -> 276 11 11, 342 / 326 us, stays, and so does bfloat16 in 18
 // 207 56 24 -> 101 13 9, 181 / 372 us.)
+//
+// `direct`: the plan for the query, whatever the call offers, so that a workspace of the size asked for takes the route asked for.
+static bool spectral_worth_planning(const ConvGeom& g) {
+  return g.r * g.s >= (g.r == 1 || g.s == 1 ? 8 : 49) && g.c > 4 && g.k > 4 && 2.0 * (double)g.M * (double)g.K * (double)g.N >= 4e9;
+}
 static bool prefer_spectral(const ConvGeom& g, int pass, int dtype, size_t offered, const Plan& direct, Plan* p) {
-  if (g.r * g.s < 49 || g.c <= 4 || g.k <= 4) return false;
   const double flops = 2.0 * (double)g.M * (double)g.K * (double)g.N;
   const bool on_float = direct.path == PATH_HALO || direct.path == PATH_HALO_FILTER || direct.path == PATH_FOLD || direct.path == PATH_EXPLICIT;
   const double direct_s = on_float ? flops / 1.3e14 : (dtype == VCNN_BF16 ? flops / 1e15 + 25e-6 : 3 * flops / 1.05e15 + 45e-6);
-  if (flops < 4e9) return false;  // (not worth planning for)
   const bool filter = pass == VCNN_PASS_BWD_FILTER, data = pass == VCNN_PASS_BWD_DATA;
   // (the kernel gradient's route depends on the shape alone, and stays inside the scratch memory where it was)
   const bool small = filter && direct.workspace_bytes <= kScratchBytes;
@@ -519,7 +522,7 @@ static bool prefer_spectral(const ConvGeom& g, int pass, int dtype, size_t offer
   size_t need = align256(q.workspace_bytes);
   if (filter && !small) need = std::max(need, kScratchBytes + 256);  // refused by the allocation-free entry point as before
   if (need > budget || (offered != kAsk && need > offered)) return false;
-  if (1.1 * q.est_seconds > direct_s) return false;
+  if ((q.along ? 1.05 : 1.1) * q.est_seconds > direct_s) return false;
   *p = Plan{};
   p->path = PATH_SPECTRAL, p->spec = q, p->hp = hp, p->hfp = hfp;
   p->behind = filter ? PATH_HALO_FILTER : PATH_HALO;
@@ -528,14 +531,13 @@ static bool prefer_spectral(const ConvGeom& g, int pass, int dtype, size_t offer
 }
 
 static Plan make_plan(const ConvGeom& g, int pass, int dtype, size_t offered) {
-  const Plan direct = direct_plan(g, pass, dtype, offered);
   const int algo = g_conv_algo.load();
+  const bool automatic = algo == VCNN_ALGO_AUTO || algo == VCNN_ALGO_FFT || algo == VCNN_ALGO_SPLIT || (algo == VCNN_ALGO_FOLD && pass != VCNN_PASS_BWD_DATA);
+  if (!automatic || !spectral_worth_planning(g)) return direct_plan(g, pass, dtype, offered);
+  const Plan asked = direct_plan(g, pass, dtype, kAsk);
   Plan p{};
-  if ((algo == VCNN_ALGO_AUTO || (algo == VCNN_ALGO_FOLD && pass != VCNN_PASS_BWD_DATA) || (algo == VCNN_ALGO_FFT && direct.path != PATH_FFT) ||
-       (algo == VCNN_ALGO_SPLIT && direct.path != PATH_SPLIT)) &&
-      prefer_spectral(g, pass, dtype, offered, direct, &p))
-    return p;
-  return direct;
+  if (asked.path != PATH_FFT && asked.path != PATH_SPLIT && prefer_spectral(g, pass, dtype, offered, asked, &p)) return p;
+  return offered == kAsk ? asked : direct_plan(g, pass, dtype, offered);
 }
 
 static size_t workspace_need(const ConvGeom& g, int pass, int dtype) { return make_plan(g, pass, dtype, kAsk).workspace_bytes; }

@@ -25,16 +25,21 @@ static constexpr int kFV = 33;        // columns of a real plane's spectrum
 static constexpr int kFTaps = 16;     // most kernel rows / columns
 // A plane's spectrum is stored as columns v = 0..32, each of 64 complex floats in four residues rho = u mod 4 (one wave of
 // the product each) of the 16 frequencies u = 4 a + rho in order.
+// Layers whose kernels are one row (column) do the same with lines of 256 samples along it; a line's spectrum is two such
+// columns of 64 values, frequencies 0..127, the first with those of 0 and 128 (both real) as its two parts.
 
+static constexpr int kLL = 256, kLV = 2, kLineTaps = 128;  // lines: length, columns of 64 values, most taps
 static constexpr int kFCells = 32;    // cells of 8 x 16 pixels of a plane
 // A window (in whole cells) darker than this share of its tile's largest element declines the image.
 static constexpr float kDarkWindow = 1.f / 1024;
 
 struct SpectralPlan {
+  int along;               // 0: planes; kernels of one row (1) or one column (2): lines along the width or the height
   int tiles_y, tiles_x;    // tiles of a plane
   int step_y, step_x;      // distance of the tiles' valid parts
   int part;                // forward: output maps worked on at once (else all)
   int splits, per_split;   // slices of the contraction, summed by the inverse transform
+  int flush;               // products in one sum
   size_t image_bytes;      // spectra over the input channels (input gradient: one slice per split)
   size_t map_bytes;        // spectra over the output maps (of a part)
   size_t taps_bytes;       // row spectra of the kernels (of a part; kernel gradient: one slice per split)
@@ -62,9 +67,9 @@ struct SpectralTiles {
   int64_t planes() const { return (int64_t)images * tiles_y * tiles_x * count; }
 };
 // Also leaves each plane's largest magnitude per cell of 8 x 16 pixels (cells, float bits), its sum (sums, nullable), and
-// zeros in words[0..1] (nullable).
+// zeros in `cleared` words.
 vcnn_status launch_plane_spectra(const SpectralTiles& t, int dtype, const void* src, float2* spectra, uint32_t* cells,
-                                 double* sums, uint32_t* words, hipStream_t st);
+                                 double* sums, uint32_t* words, int cleared, hipStream_t st);
 // The spectra of planes back to pixels: pixel (y, x) of tile (ty, tx) is (ty step_y + y, tx step_x + x) of the plane and lies
 // at (y + y0, x + x0) of the transform; `slices` spectra of a plane, `slice` complex values apart, are added first; bias per channel, nullable.
 vcnn_status launch_plane_inverse(const SpectralTiles& t, int dtype, const float2* spectra, int64_t slice, int slices, void* dst,
@@ -72,8 +77,33 @@ vcnn_status launch_plane_inverse(const SpectralTiles& t, int dtype, const float2
 // Row spectra of kernels of r x s taps: [v][kernel][16 rows]; largest magnitude of each four kernels.
 vcnn_status launch_taps_spectra(int dtype, const void* w, int64_t kernels, int r, int s, float2* spectra, uint32_t* largest,
                                 hipStream_t st);
-// And back; also db[m] = sums[0][m] + sums[1][m] + ... (planes of `maps` maps; nullable).
+// And back; also, in blocks of their own, db[m] = sums[0][m] + sums[1][m] + ... (planes of `maps` maps; nullable).
 vcnn_status launch_taps_inverse(const float2* spectra, int64_t slice, int slices, int64_t kernels, int r, int s, float* dw,
                                 const double* sums, int sum_planes, int maps, float* db, hipStream_t st);
+
+// Lines of a tensor [images][channels][...]: sample x of line (image, channel, o) lies at o s_other + x s_along of the channel;
+// tiles as above, in one dimension.  The spectrum of line (image, channel, o, tile) is number
+// image p_image + channel p_channel + o tiles + tile.
+struct SpectralLines {
+  int images, channels, first, count;
+  int len, others, tiles, step, x0, lim;
+  int64_t s_channel, s_other, s_along;
+  int64_t p_image, p_channel;
+  __host__ __device__ int64_t lines() const { return (int64_t)images * count * others * tiles; }
+};
+struct LineJob {
+  SpectralLines t;
+  int64_t planes;    // spectra per column
+  const void* src;
+  float2* spectra;
+  uint32_t* cells;   // the largest magnitude of each 16 samples: [image][o][tile][channel][16], or one of ...
+  int whole;         // ... each line
+  double* sums;      // sums of the lines, nullable: [image][o][tile][channel]
+};
+// The lines of two tensors (the second may have none: all zero); leaves zeros in `cleared` words.
+vcnn_status launch_line_spectra(int dtype, const LineJob& first, const LineJob& second, uint32_t* words, int cleared, hipStream_t st);
+vcnn_status launch_line_inverse(const SpectralLines& t, int64_t planes, int dtype, const float2* spectra, int64_t slice, int slices,
+                                void* dst, const float* bias, int relu, const double* sums, int sum_planes, int maps, float* db,
+                                hipStream_t st);
 
 }  // namespace vcnn

@@ -4,38 +4,12 @@
 
 #include "bf16_core.h"
 #include "spectral.h"
+#include "spectral_math.h"
 
 namespace vcnn {
 
 static constexpr int kThreads = 256;
 
-struct cf {
-  float x, y;
-};
-__device__ __forceinline__ cf operator+(cf a, cf b) { return {a.x + b.x, a.y + b.y}; }
-__device__ __forceinline__ cf operator-(cf a, cf b) { return {a.x - b.x, a.y - b.y}; }
-__device__ __forceinline__ cf operator*(cf a, cf b) { return {fmaf(a.x, b.x, -a.y * b.y), fmaf(a.x, b.y, a.y * b.x)}; }
-template <bool INV>
-__device__ __forceinline__ void dft4(cf& a, cf& b, cf& c, cf& d) {
-  const cf s = a + c, t = a - c, u = b + d, e = b - d;
-  const cf q = INV ? cf{-e.y, e.x} : cf{e.y, -e.x};
-  a = s + u, b = t + q, c = s - u, d = t - q;
-}
-// v[4 k + i], i < 4, hold what first(v, i) makes of v[i + 4 n]; second(v, k) then leaves point k + 4 n of
-// sum_m v[m] e^(-+ 2 pi i m p / 16) in v[4 k + n]
-template <bool INV>
-__device__ __forceinline__ void dft16_first(cf (&v)[16], int i) {
-  constexpr float c1 = 0.92387953251128675613f, s1 = 0.38268343236508977173f, h = 0.70710678118654752440f;
-  constexpr float c[10] = {1, c1, h, s1, 0, 0, -h, 0, 0, -c1}, s[10] = {0, s1, h, c1, 1, 0, h, 0, 0, -s1};
-  dft4<INV>(v[i], v[4 + i], v[8 + i], v[12 + i]);
-  if (i > 0) {
-#pragma unroll
-    for (int k = 1; k < 4; ++k) v[4 * k + i] = v[4 * k + i] * cf{c[i * k], INV ? s[i * k] : -s[i * k]};
-  }
-}
-template <bool INV>
-__device__ __forceinline__ void dft16_second(cf (&v)[16], int k) { dft4<INV>(v[4 * k], v[4 * k + 1], v[4 * k + 2], v[4 * k + 3]); }
-__device__ __forceinline__ constexpr int dft16_at(int p) { return 4 * (p & 3) + (p >> 2); }  // where point p is
 // e^(-2 pi i q / 64), q = rho * r for the residues rho < 4 and kernel rows r < 16
 __constant__ const float kRoots[4][16][2] = {
 #define R0 {1.f, 0.f}
@@ -81,53 +55,93 @@ struct GuardArgs {
   int grow;                  // bits a sum of products may gain
   uint32_t* any;
   uint32_t* image;
+  int line_groups;           // > 0: lines, so many groups of one line per channel in an image; tiles_x of them along a line;
+                             // cells[.]: [image][group][line of it][16]
 };
-__device__ void guard_image(const GuardArgs& g, int n, uint32_t* lds) {
-  const int tid = threadIdx.x, tiles = g.tiles_y * g.tiles_x;
+static constexpr int kGuardLines = 16;  // groups of lines a block looks at
+// The largest element of some groups of lines, and whether a window of one (win_x cells of 16 samples, all channels) is dark.
+__device__ bool dark_line(const GuardArgs& g, int n, int first, uint32_t* most) {
+  const int tid = threadIdx.x, lane = tid & 63, cell = lane & 15;
+  bool bad = false;
+  for (int i = first + (tid >> 6); i < min(first + kGuardLines, g.line_groups); i += 4) {
+    const uint32_t* c = g.cells[0] + ((int64_t)n * g.line_groups + i) * g.planes[0] * 16;
+    uint32_t m = 0;
+#pragma unroll 8
+    for (int p = lane >> 4; p < g.planes[0]; p += 4) m = max(m, c[p * 16 + cell]);
+    m = max(m, (uint32_t)__shfl_xor((int)m, 16));
+    m = max(m, (uint32_t)__shfl_xor((int)m, 32));
+    uint32_t top = m, win = m;
+#pragma unroll
+    for (int d = 8; d > 0; d >>= 1) top = max(top, (uint32_t)__shfl_xor((int)top, d));
+    for (int d = 1; d < g.win_x; ++d) win = max(win, (uint32_t)__shfl((int)m, (cell + d) & 15));
+    const int xs = i % g.tiles_x * g.step_x + g.x0;
+    const bool inside = cell + g.win_x <= 16 && xs + cell * 16 >= 0 && (cell + g.win_x) * 16 <= min(g.lim_x, g.w - xs);
+    bad |= inside && __uint_as_float(win) < kDarkWindow * __uint_as_float(top);
+    *most = max(*most, top);
+  }
+  return bad;
+}
+// By all 256 threads.
+__device__ __forceinline__ uint32_t block_max(uint32_t m, uint32_t* lds) {
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, d));
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = m;
+  __syncthreads();
+  return max(max(lds[0], lds[1]), max(lds[2], lds[3]));
+}
+__device__ void guard_image(const GuardArgs& g, int block, uint32_t* lds) {
+  const int tid = threadIdx.x;
   uint32_t most = 0, other = 0;
   bool bad = false;
-  for (int t = 0; t < tiles; ++t) {
-    uint32_t m = 0;
-    const uint32_t* c = g.cells[0] + ((int64_t)n * tiles + t) * g.planes[0] * kFCells;
-    for (int i = tid; i < g.planes[0] * kFCells; i += kThreads) m = max(m, c[i]);
-    __syncthreads();
-    lds[tid] = m;
-    __syncthreads();
-    uint32_t top = 0;
-    for (int i = 0; i < 256; ++i) top = max(top, lds[i]);
-    most = max(most, top);
-    const int cy = tid >> 2, cx = tid & 3, ty = t / g.tiles_x, tx = t % g.tiles_x;
-    const int ys = ty * g.step_y + g.y0, xs = tx * g.step_x + g.x0;  // the tile's first pixel in the plane
-    bool inside = cy + g.win_y <= 8 && cx + g.win_x <= 4;
-    inside = inside && ys + cy * 8 >= 0 && xs + cx * 16 >= 0;
-    inside = inside && (cy + g.win_y) * 8 <= min(g.lim_y, g.h - ys) && (cx + g.win_x) * 16 <= min(g.lim_x, g.w - xs);
-    if (inside) {
-      uint32_t win = 0;
-      for (int y = cy; y < cy + g.win_y; ++y)
-        for (int x = cx; x < cx + g.win_x; ++x)
-          for (int b = 0; b < 8; ++b) win = max(win, lds[b * kFCells + y * 4 + x]);
-      bad |= __uint_as_float(win) < kDarkWindow * __uint_as_float(top);
+  int n = block, share = g.tiles_y * g.tiles_x * g.planes[1] * kFCells, first = 0;  // of the other operand's cells
+  if (g.line_groups) {
+    const int chunks = (g.line_groups + kGuardLines - 1) / kGuardLines;
+    n = block / chunks;
+    const int group = block % chunks * kGuardLines;
+    bad = dark_line(g, n, group, &most);
+    first = group * g.planes[1] * 16, share = min(kGuardLines, g.line_groups - group) * g.planes[1] * 16;
+  } else {
+    for (int t = 0; t < g.tiles_y * g.tiles_x; ++t) {
+      uint32_t m = 0;
+      const uint32_t* c = g.cells[0] + ((int64_t)n * g.tiles_y * g.tiles_x + t) * g.planes[0] * kFCells;
+#pragma unroll 8
+      for (int i = tid; i < g.planes[0] * kFCells; i += kThreads) m = max(m, c[i]);
+      const uint32_t top = block_max(m, lds + 256);
+      lds[tid] = m;
+      __syncthreads();
+      most = max(most, top);
+      const int cy = tid >> 2, cx = tid & 3, ty = t / g.tiles_x, tx = t % g.tiles_x;
+      const int ys = ty * g.step_y + g.y0, xs = tx * g.step_x + g.x0;  // the tile's first pixel in the plane
+      bool inside = cy + g.win_y <= 8 && cx + g.win_x <= 4;
+      inside = inside && ys + cy * 8 >= 0 && xs + cx * 16 >= 0;
+      inside = inside && (cy + g.win_y) * 8 <= min(g.lim_y, g.h - ys) && (cx + g.win_x) * 16 <= min(g.lim_x, g.w - xs);
+      if (inside) {
+        uint32_t win = 0;
+        for (int y = cy; y < cy + g.win_y; ++y)
+          for (int x = cx; x < cx + g.win_x; ++x)
+            for (int b = 0; b < 8; ++b) win = max(win, lds[b * kFCells + y * 4 + x]);
+        bad |= __uint_as_float(win) < kDarkWindow * __uint_as_float(top);
+      }
+      __syncthreads();
     }
   }
   if (g.cells[1]) {
-    const uint32_t* c = g.cells[1] + (int64_t)n * tiles * g.planes[1] * kFCells;
-    for (int i = tid; i < tiles * g.planes[1] * kFCells; i += kThreads) other = max(other, c[i]);
+    const int tiles = g.line_groups ? g.line_groups * 16 : g.tiles_y * g.tiles_x * kFCells;
+    const uint32_t* c = g.cells[1] + (int64_t)n * tiles * g.planes[1] + first;
+#pragma unroll 8
+    for (int i = tid; i < share; i += kThreads) other = max(other, c[i]);
   } else {
-    for (int64_t i = tid; i < g.largest_count; i += kThreads) other = max(other, g.largest[i]);
+#pragma unroll 8
+    for (int i = tid; i < (int)g.largest_count; i += kThreads) other = max(other, g.largest[i]);
   }
-  __syncthreads();
-  lds[tid] = other;
-  __syncthreads();
-  for (int i = 0; i < 256; ++i) other = max(other, lds[i]);
+  most = block_max(most, lds);
+  other = block_max(other, lds);
   // exponents: sums of a transform gain 12 bits, and products of spectra have to stay 24 bits clear of the least float
   const int ea = (int)(most >> 23) - 127, eb = (int)(other >> 23) - 127;
   bad |= ea == 128 || eb == 128;  // infinity or NaN
   if (most && other) bad |= ea + eb + 24 + g.grow > 126 || ea > 110 || eb > 110 || ea + eb < -80 || ea < -90 || eb < -90;
-  const int flag = __syncthreads_or(bad);
-  if (tid == 0) {
-    g.image[n] = flag ? 1 : 0;
-    if (flag) atomicOr(g.any, 1u);
-  }
+  if (__syncthreads_or(bad) && tid == 0) atomicOr(g.image + n, 1u), atomicOr(g.any, 1u);
 }
 
 // ---- products of spectra -------------------------------------------------------------------------------------------
@@ -148,7 +162,7 @@ struct ProductArgs {
   int64_t a_row, a_z, b_col, b_z, c_row, c_col;  // in planes (kernels)
   int64_t a_planes, b_planes, c_planes;          // per column v
   int64_t c_slice;                               // complex values
-  int tiles_r, tiles_c, splits, per_split;
+  int columns, tiles_r, tiles_c, splits, per_split;
   int flush;                                     // (spectra as results) so many products are added in a row, then to C
   int rows_inner;                                // tiles of rows follow each other (the columns' operand is the larger one)
   int blocks;                                    // of products; further blocks look for what is declined
@@ -157,7 +171,7 @@ struct ProductArgs {
 
 __device__ __forceinline__ float4 add4(float4 a, float4 b) { return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w); }
 
-template <bool TAPS_A, bool CONJ_A, bool TAPS_C>
+template <bool TAPS_A, bool CONJ_A, bool TAPS_C, bool LINES>
 __global__ __launch_bounds__(kThreads, 2) void spectral_product_kernel(ProductArgs a) {
   __shared__ __attribute__((aligned(128))) uint4 lds[4][1024];
   if ((int)blockIdx.x >= a.blocks) return guard_image(a.guard, blockIdx.x - a.blocks, reinterpret_cast<uint32_t*>(&lds[0][0]));
@@ -280,11 +294,14 @@ __global__ __launch_bounds__(kThreads, 2) void spectral_product_kernel(ProductAr
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   };
+  const bool pair = LINES && v == 0 && rho == 0;  // a line's first value: two real ones
   auto multiply = [&](cf x, cf y, int i) {
+    float xi = CONJ_A ? -x.y : x.y, yr = y.x, yi = y.y;
     re[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.x, y.x, re[i], 0, 0, 0);
-    im[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.x, y.y, im[i], 0, 0, 0);
-    re[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(CONJ_A ? x.y : -x.y, y.y, re[i], 0, 0, 0);
-    im[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(CONJ_A ? -x.y : x.y, y.x, im[i], 0, 0, 0);
+    if (LINES && i == 0 && pair) yr = y.y, yi = 0, xi = x.y;
+    im[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.x, yi, im[i], 0, 0, 0);
+    re[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(-xi, yi, re[i], 0, 0, 0);
+    im[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(xi, yr, im[i], 0, 0, 0);
   };
   // a part in eight of a lane's transform of 16 kernel rows to the wave's frequencies
   auto transform = [&](cf (&t)[16], int part) {
@@ -355,15 +372,25 @@ __global__ __launch_bounds__(kThreads, 2) void spectral_product_kernel(ProductAr
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (the last fetch)
   } else {
     clear();
+    int z_put = z_begin;
     for (int z0 = z_begin; z0 < z_end; z0 += 4) {
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       take(la, fa);
       take(lb, fb);
-      if (z0 + 4 < z_end) fetch_a(z0 + 4), fetch_b(z0 + 4);
+      const bool another = z0 + 4 < z_end, last = !another || z0 + 4 - z_put >= a.flush;
+      if (another) fetch_a(z0 + 4);
+      if (!last) fetch_b(z0 + 4);
 #pragma unroll
       for (int i = 0; i < 16; ++i) multiply(fa[i], fb[i], i);
+      if (last) {
+        put(z_put > z_begin);
+        if (TAPS_C || !another) break;
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        fetch_b(z0 + 4);
+        clear();
+        z_put = z0 + 4;
+      }
     }
-    put(false);
   }
 }
 
@@ -378,61 +405,84 @@ struct Layout {  // of the workspace
 }  // namespace
 
 static bool one_tile(const ConvGeom& g) { return g.h + 2 * g.ph <= kFL && g.w + 2 * g.pw <= kFL; }
-static int64_t tiles_of(const ConvGeom& g, const SpectralPlan& p) { return (int64_t)g.n * p.tiles_y * p.tiles_x; }
+// Tiles (lines: tiles of lines) of one channel of the whole batch.
+static int64_t tiles_of(const ConvGeom& g, const SpectralPlan& p, int pass) {
+  if (p.along == 0) return (int64_t)g.n * p.tiles_y * p.tiles_x;
+  const bool data = pass == VCNN_PASS_BWD_DATA;
+  return (int64_t)g.n * p.tiles_x * (p.along == 1 ? (data ? g.h : g.oh) : (data ? g.w : g.ow));
+}
 
+static size_t lay_out(const ConvGeom& g, int pass, const SpectralPlan& p, Layout* l) {
+  const int64_t tiles = tiles_of(g, p, pass);
+  const size_t cells = p.along ? 64 : kFCells * 4;
+  l->image = 0;
+  l->map = l->image + p.image_bytes;
+  l->taps = l->map + p.map_bytes;
+  l->words = l->taps + p.taps_bytes;
+  size_t at = l->words + align256(256 + 4 * (size_t)g.n);
+  l->cells_image = at;
+  if (pass != VCNN_PASS_BWD_DATA) at += align256((size_t)tiles * g.c * cells);
+  l->cells_map = at;
+  if (pass != VCNN_PASS_FWD) at += align256((size_t)tiles * g.k * cells);
+  l->largest = at;
+  if (pass != VCNN_PASS_BWD_FILTER) at += align256(p.along ? (size_t)g.k * g.c * 4 : (size_t)ceil_div((int64_t)g.k * g.c, 4) * 4);
+  l->sums = at;
+  if (pass == VCNN_PASS_BWD_FILTER) at += align256((size_t)tiles * g.k * 8);
+  return at;
+}
 static Layout layout(const ConvGeom& g, int pass, const SpectralPlan& p) {
   Layout l{};
-  const int64_t tiles = tiles_of(g, p);
-  l.image = 0;
-  l.map = l.image + p.image_bytes;
-  l.taps = l.map + p.map_bytes;
-  l.words = l.taps + p.taps_bytes;
-  size_t at = l.words + align256(256 + 4 * (size_t)g.n);
-  l.cells_image = at;
-  if (pass != VCNN_PASS_BWD_DATA) at += align256((size_t)tiles * g.c * kFCells * 4);
-  l.cells_map = at;
-  if (pass != VCNN_PASS_FWD) at += align256((size_t)tiles * g.k * kFCells * 4);
-  l.largest = at;
-  if (pass != VCNN_PASS_BWD_FILTER) at += align256((size_t)ceil_div((int64_t)g.k * g.c, 4) * 4);
-  l.sums = at;
-  if (pass == VCNN_PASS_BWD_FILTER) at += align256((size_t)tiles * g.k * 8);
-  (void)at;
+  lay_out(g, pass, p, &l);
   return l;
-}
-static size_t words_bytes(const ConvGeom& g, int pass, const SpectralPlan& p) {
-  SpectralPlan q = p;
-  q.image_bytes = q.map_bytes = q.taps_bytes = 0;
-  const Layout l = layout(g, pass, q);
-  return l.sums + (pass == VCNN_PASS_BWD_FILTER ? align256((size_t)tiles_of(g, p) * g.k * 8) : 0);
 }
 
 bool spectral_plan(const ConvGeom& g, int pass, size_t budget, SpectralPlan* p) {
-  if (g.r > kFTaps || g.s > kFTaps || g.c <= 4 || g.k <= 4) return false;
+  if (g.c <= 4 || g.k <= 4) return false;
   const bool data = pass == VCNN_PASS_BWD_DATA, filter = pass == VCNN_PASS_BWD_FILTER;
   SpectralPlan q{};
-  if (one_tile(g)) {
-    q.tiles_y = q.tiles_x = 1;
-    q.step_y = q.step_x = kFL;
+  int64_t spectrum, taps;  // bytes of a tile's spectrum, of a kernel's
+  if (g.r == 1 || g.s == 1) {
+    q.along = g.r == 1 ? 1 : 2;
+    const int len = q.along == 1 ? g.w : g.h, pad = q.along == 1 ? g.pw : g.ph, size = g.r * g.s, out = q.along == 1 ? g.ow : g.oh;
+    if (size > kLineTaps || (q.along == 1 ? g.ph : g.pw) != 0) return false;
+    const bool one = len + 2 * pad <= kLL;
+    q.tiles_y = 1, q.step_y = 1;
+    q.step_x = one ? kLL : kLL - size + 1;
+    q.tiles_x = one ? 1 : (int)ceil_div(data ? len : out, q.step_x);
+    spectrum = taps = kLV * kFL * 8;
   } else {
-    q.step_y = kFL - g.r + 1, q.step_x = kFL - g.s + 1;
-    q.tiles_y = (int)ceil_div(data ? g.h : g.oh, q.step_y), q.tiles_x = (int)ceil_div(data ? g.w : g.ow, q.step_x);
+    if (g.r > kFTaps || g.s > kFTaps) return false;
+    if (one_tile(g)) {
+      q.tiles_y = q.tiles_x = 1;
+      q.step_y = q.step_x = kFL;
+    } else {
+      q.step_y = kFL - g.r + 1, q.step_x = kFL - g.s + 1;
+      q.tiles_y = (int)ceil_div(data ? g.h : g.oh, q.step_y), q.tiles_x = (int)ceil_div(data ? g.w : g.ow, q.step_x);
+    }
+    spectrum = (int64_t)kFV * kFL * 8, taps = (int64_t)kFV * kFTaps * 8;
   }
-  const int64_t tiles = tiles_of(g, q), spectrum = (int64_t)kFV * kFL * 8, taps = (int64_t)kFV * kFTaps * 8;
-  if (tiles * std::max(g.c, g.k) > (1 << 20)) return false;
+  const int columns = q.along ? kLV : kFV;
+  const int64_t tiles = tiles_of(g, q, pass);
+  if (tiles * std::max(g.c, g.k) > (1 << 21) || (int64_t)g.c * g.k > (1 << 21)) return false;
   const size_t image = align256((size_t)(tiles * g.c * spectrum));
   const double rows = data ? g.c : g.k, cols = filter ? (double)g.c : (double)tiles, depth = filter ? (double)tiles : (data ? g.k : g.c);
-  // No sum over maps or images is longer than 32 complex products, 64 roundings of the float instruction: the input
-  // gradient's blocks take two of them (as one, 16 38 64 64 -> 512 16 16 has an error of
-  // 2.1e-7, the two-term product 1.9e-7),
-  // the slices are added in double.  (Those over channels stay whole: a slice of a forward pass is as large as its result.)
-  const int most = data ? 64 : (filter ? 32 : 1 << 30);
+  // No sum is longer than 32 complex products, 64 roundings of the float instruction (as one of 512, an input gradient over
+  // 512 maps has an error of 4.6e-7, over 64 of 2.1e-7, the two-term product 1.9e-7): a block of an input gradient takes two
+  // of them, a kernel gradient's sums are cut into slices, which the inverse transform adds in double.  A forward pass's
+  // slices would be as large as its result; its blocks take every channel, and up to 64 in one sum.
+  const int most = data || (filter && q.along) ? 64 : (filter ? 32 : 1 << 30);
   q.per_split = (int)std::min<double>(depth, most);
   q.splits = (int)std::ceil(depth / q.per_split);
+  const int longest = q.along == 0 && pass == VCNN_PASS_FWD && g.c <= 64 ? 64 : 32;
+  q.flush = (int)(ceil_div(ceil_div(q.per_split, ceil_div(q.per_split, longest)), 4) * 4);  // in chunks of about the same size
   q.part = g.k;
   q.image_bytes = image * (data ? q.splits : 1);
   q.taps_bytes = align256((size_t)((int64_t)g.k * g.c * taps)) * (filter ? q.splits : 1);
   q.map_bytes = align256((size_t)(tiles * g.k * spectrum));
-  q.words_bytes = words_bytes(g, pass, q);
+  SpectralPlan none = q;
+  none.image_bytes = none.map_bytes = none.taps_bytes = 0;
+  Layout l{};
+  q.words_bytes = lay_out(g, pass, none, &l);
   if (pass == VCNN_PASS_FWD && q.image_bytes + q.map_bytes + q.taps_bytes + q.words_bytes > budget) {
     // as many maps at once as the budget holds, in whole tiles of 16
     int64_t maps = ceil_div(g.k, 16) * 16;
@@ -450,20 +500,24 @@ bool spectral_plan(const ConvGeom& g, int pass, size_t budget, SpectralPlan* p) 
   // each of 256 CUs at 2.7 us a step (3.4 where the larger operand is read by every block; one alone 2.2 us), four steps' worth
   // to begin and to end with.  (110 passes of 40 drawn layers, 44 to 861 us, take 0.75 to 1.2 times this.)
   const double parts = (double)ceil_div(g.k, q.part), e = 4, pixels = (double)g.n * ((double)g.c * g.h * g.w + (double)g.k * g.P);
-  const double bytes = pixels * e + 2.0 * (double)(q.image_bytes + (size_t)(tiles * g.k * spectrum)) +
+  const double result = data ? (double)image : (filter ? (double)g.k * g.c * taps : (double)tiles * g.k * spectrum), flushes = std::ceil(q.per_split / (double)q.flush) - 1;
+  const double bytes = pixels * e + 2.0 * (double)(q.image_bytes + (size_t)(tiles * g.k * spectrum)) + 2.0 * flushes * result * q.splits +
                        2.0 * (double)g.k * g.c * taps * (filter ? q.splits : 1) + (double)g.M * g.K * e;
-  const double blocks = kFV * std::ceil(rows / 16) * std::ceil(cols / 16) * q.splits, steps = std::ceil(q.per_split / 4.0) + 4;
-  q.est_seconds = bytes / 4.4e12 + (blocks <= 256 ? 2.2e-6 : std::ceil(blocks / 512) * (data ? 3.4e-6 : 2.7e-6)) * steps + 5e-6 * (1 + 3 * parts);
+  const double blocks = columns * std::ceil(rows / 16) * std::ceil(cols / 16) * q.splits, steps = std::ceil(q.per_split / 4.0) + 4;
+  q.est_seconds = bytes / 4.4e12 + (blocks <= 256 ? 2.2e-6 : std::ceil(blocks / 512) * (data ? 3.4e-6 : 2.7e-6)) * steps + 5e-6 * (1 + (q.along ? 2 : 3) * parts);
+  if (q.along) q.est_seconds *= filter ? 1.0 : 0.87;  // (measured against 100 passes of lines: 0.75 to 1.15 times the above)
   *p = q;
   return true;
 }
 
 // ---- passes --------------------------------------------------------------------------------------------------------
-template <bool TAPS_A, bool CONJ_A, bool TAPS_C>
-static vcnn_status launch_product(ProductArgs a, int guard_blocks, hipStream_t st) {
+template <bool TAPS_A, bool CONJ_A, bool TAPS_C, bool LINES>
+static vcnn_status launch_product(ProductArgs a, int images, hipStream_t st) {
+  a.columns = LINES ? kLV : kFV;
   a.tiles_r = (int)ceil_div(a.rows, 16), a.tiles_c = (int)ceil_div(a.cols, 16);
-  a.blocks = kFV * a.tiles_r * a.tiles_c * a.splits;
-  hipLaunchKernelGGL((spectral_product_kernel<TAPS_A, CONJ_A, TAPS_C>), dim3((unsigned)(a.blocks + guard_blocks)), dim3(kThreads), 0, st, a);
+  a.blocks = a.columns * a.tiles_r * a.tiles_c * a.splits;
+  const int guard_blocks = images * (LINES ? (int)ceil_div(a.guard.line_groups, kGuardLines) : 1);
+  hipLaunchKernelGGL((spectral_product_kernel<TAPS_A, CONJ_A, TAPS_C, LINES>), dim3((unsigned)(a.blocks + guard_blocks)), dim3(kThreads), 0, st, a);
   return check_launch("spectral_product");
 }
 
@@ -486,8 +540,135 @@ static GuardArgs guard_for(const SpectralTiles& t, const uint32_t* cells, int wi
 }
 static int bits_of(int64_t n) { return (int)std::ceil(std::log2((double)std::max<int64_t>(n, 1))); }
 
+// The lines of a tensor of `channels` channels of h x w, and of the kernels (one line each).
+static SpectralLines lines_for(const ConvGeom& g, const SpectralPlan& p, int channels, int h, int w) {
+  SpectralLines t{};
+  t.images = g.n, t.channels = channels, t.first = 0, t.count = channels;
+  t.len = p.along == 1 ? w : h, t.others = p.along == 1 ? h : w;
+  t.tiles = p.tiles_x, t.step = p.step_x, t.lim = kLL;
+  t.s_channel = (int64_t)h * w, t.s_other = p.along == 1 ? w : 1, t.s_along = p.along == 1 ? 1 : w;
+  t.p_image = (int64_t)t.others * t.tiles, t.p_channel = g.n * t.p_image;  // the lines of a channel of all images together
+  return t;
+}
+static SpectralLines kernel_lines(const ConvGeom& g, int maps) {
+  SpectralLines t{};
+  t.images = maps, t.channels = t.count = g.c;
+  t.len = t.lim = g.r * g.s, t.others = t.tiles = t.step = 1;
+  t.s_channel = g.r * g.s, t.s_other = 0, t.s_along = 1;
+  t.p_image = g.c, t.p_channel = 1;
+  return t;
+}
+static GuardArgs guard_for(const SpectralLines& t, const uint32_t* cells, int win, char* words) {
+  GuardArgs g{};
+  g.cells[0] = cells, g.planes[0] = t.channels, g.images = t.images;
+  g.line_groups = t.others * t.tiles, g.tiles_x = t.tiles;
+  g.step_x = t.step, g.x0 = t.x0, g.w = t.len, g.lim_x = t.lim;
+  g.win_x = std::max(1, (win + 15) / 16);
+  g.any = reinterpret_cast<uint32_t*>(words), g.image = reinterpret_cast<uint32_t*>(words + 256);
+  return g;
+}
+// Tile offsets of the three tensors: x starts a tile `pad` before it.  In an input gradient pixel i of the padded line gets
+// dy[i - q] w[q]: a whole line starts at dy's first pixel; a tile of a longer one starts `size` - 1 pixels before its results,
+// of which the transform wraps that many.
+static void place_dx(bool one, int size, int pad, int* dy0, int* dx0) { *dy0 = one ? 0 : pad - (size - 1), *dx0 = one ? pad : size - 1; }
+
+static vcnn_status lines_fwd(const SpectralPlan& p, int dtype, const ConvGeom& g, const void* x, const void* w, const float* bias,
+                             void* y, int relu, void* workspace, hipStream_t st) {
+  const Layout l = layout(g, VCNN_PASS_FWD, p);
+  char* const ws = (char*)workspace;
+  float2 *const xs = (float2*)(ws + l.image), *const ys = (float2*)(ws + l.map), *const taps = (float2*)(ws + l.taps);
+  uint32_t *const cells = (uint32_t*)(ws + l.cells_image), *const largest = (uint32_t*)(ws + l.largest);
+  const int64_t tiles = tiles_of(g, p, VCNN_PASS_FWD);
+  const int esize = dtype == VCNN_BF16 ? 2 : 4;
+  SpectralLines tx = lines_for(g, p, g.c, g.h, g.w);
+  tx.x0 = -(p.along == 1 ? g.pw : g.ph);
+  SpectralLines ty = lines_for(g, p, g.k, g.oh, g.ow);
+  ty.lim = std::min(p.step_x, ty.len);
+  for (int k0 = 0; k0 < g.k; k0 += p.part) {
+    const int maps = std::min(p.part, g.k - k0);
+    const bool last = k0 + maps == g.k;
+    LineJob image{tx, tiles * g.c, x, xs, cells, 0, nullptr};
+    if (k0 > 0) image.t.count = 0;  // (they stay)
+    const LineJob kernels{kernel_lines(g, maps), (int64_t)maps * g.c, (const char*)w + (int64_t)k0 * g.K * esize, taps, largest + (int64_t)k0 * g.c, 1, nullptr};
+    if (vcnn_status s = launch_line_spectra(dtype, image, kernels, (uint32_t*)(ws + l.words), k0 == 0 ? 64 + g.n : 0, st)) return s;
+    ProductArgs a{};
+    a.A = taps, a.B = xs, a.C = ys;
+    a.rows = maps, a.cols = (int)tiles, a.depth = g.c;
+    a.a_row = g.c, a.a_z = 1, a.a_planes = (int64_t)maps * g.c;
+    a.b_col = 1, a.b_z = tiles, a.b_planes = tiles * g.c;
+    a.c_row = tiles, a.c_col = 1, a.c_planes = tiles * maps;
+    a.splits = p.splits, a.per_split = p.per_split, a.flush = p.flush, a.rows_inner = 1;
+    if (last) {
+      a.guard = guard_for(tx, cells, g.r * g.s, ws + l.words);
+      a.guard.largest = largest, a.guard.largest_count = (int64_t)g.k * g.c;
+      a.guard.grow = bits_of(g.K);
+    }
+    if (vcnn_status s = launch_product<false, true, false, true>(a, last ? g.n : 0, st)) return s;
+    ty.first = k0, ty.count = maps;
+    if (vcnn_status s = launch_line_inverse(ty, tiles * maps, dtype, ys, 0, 1, y, bias, relu, nullptr, 0, 0, nullptr, st)) return s;
+  }
+  return VCNN_OK;
+}
+
+static vcnn_status lines_bwd_data(const SpectralPlan& p, int dtype, const ConvGeom& g, const void* w, const void* dy, void* dx,
+                                  void* workspace, hipStream_t st) {
+  const Layout l = layout(g, VCNN_PASS_BWD_DATA, p);
+  char* const ws = (char*)workspace;
+  float2 *const xs = (float2*)(ws + l.image), *const ys = (float2*)(ws + l.map), *const taps = (float2*)(ws + l.taps);
+  uint32_t *const cells = (uint32_t*)(ws + l.cells_map), *const largest = (uint32_t*)(ws + l.largest);
+  const int64_t tiles = tiles_of(g, p, VCNN_PASS_BWD_DATA);
+  const int pad = p.along == 1 ? g.pw : g.ph;
+  SpectralLines tdy = lines_for(g, p, g.k, g.oh, g.ow), tdx = lines_for(g, p, g.c, g.h, g.w);
+  place_dx(tdx.len + 2 * pad <= kLL, g.r * g.s, pad, &tdy.x0, &tdx.x0);
+  tdx.lim = std::min(p.step_x, tdx.len);
+  const LineJob image{tdy, tiles * g.k, dy, ys, cells, 0, nullptr};
+  const LineJob kernels{kernel_lines(g, g.k), (int64_t)g.k * g.c, w, taps, largest, 1, nullptr};
+  if (vcnn_status s = launch_line_spectra(dtype, image, kernels, (uint32_t*)(ws + l.words), 64 + g.n, st)) return s;
+  ProductArgs a{};
+  a.A = taps, a.B = ys, a.C = xs;
+  a.rows = g.c, a.cols = (int)tiles, a.depth = g.k;
+  a.a_row = 1, a.a_z = g.c, a.a_planes = (int64_t)g.k * g.c;
+  a.b_col = 1, a.b_z = tiles, a.b_planes = tiles * g.k;
+  a.c_row = tiles, a.c_col = 1, a.c_planes = tiles * g.c;
+  a.splits = p.splits, a.per_split = p.per_split, a.flush = p.flush, a.rows_inner = 1, a.c_slice = (int64_t)(p.image_bytes / p.splits / 8);
+  a.guard = guard_for(tdy, cells, g.r * g.s, ws + l.words);
+  a.guard.largest = largest, a.guard.largest_count = (int64_t)g.k * g.c;
+  a.guard.grow = bits_of((int64_t)g.k * g.r * g.s);
+  if (vcnn_status s = launch_product<false, false, false, true>(a, g.n, st)) return s;
+  return launch_line_inverse(tdx, tiles * g.c, dtype, xs, a.c_slice, p.splits, dx, nullptr, 0, nullptr, 0, 0, nullptr, st);
+}
+
+static vcnn_status lines_filter(const SpectralPlan& p, int dtype, const ConvGeom& g, const void* x, const void* dy, float* dw,
+                                float* db, void* workspace, hipStream_t st) {
+  const Layout l = layout(g, VCNN_PASS_BWD_FILTER, p);
+  char* const ws = (char*)workspace;
+  float2 *const xs = (float2*)(ws + l.image), *const ys = (float2*)(ws + l.map), *const taps = (float2*)(ws + l.taps);
+  uint32_t *const cells_x = (uint32_t*)(ws + l.cells_image), *const cells_dy = (uint32_t*)(ws + l.cells_map);
+  double* const sums = (double*)(ws + l.sums);
+  const int64_t tiles = tiles_of(g, p, VCNN_PASS_BWD_FILTER);
+  SpectralLines tx = lines_for(g, p, g.c, g.h, g.w), tdy = lines_for(g, p, g.k, g.oh, g.ow);
+  tx.x0 = -(p.along == 1 ? g.pw : g.ph);
+  tdy.lim = std::min(p.step_x, tdy.len);  // every output pixel in one tile
+  const LineJob image{tx, tiles * g.c, x, xs, cells_x, 0, nullptr}, map{tdy, tiles * g.k, dy, ys, cells_dy, 0, db ? sums : nullptr};
+  if (vcnn_status s = launch_line_spectra(dtype, image, map, (uint32_t*)(ws + l.words), 64 + g.n, st)) return s;
+  ProductArgs a{};
+  a.A = ys, a.B = xs, a.C = taps;
+  a.rows = g.k, a.cols = g.c, a.depth = (int)tiles;
+  a.a_row = tiles, a.a_z = 1, a.a_planes = tiles * g.k;
+  a.b_col = tiles, a.b_z = 1, a.b_planes = tiles * g.c;
+  a.c_row = g.c, a.c_col = 1, a.c_planes = (int64_t)g.k * g.c;
+  a.splits = p.splits, a.per_split = p.per_split, a.flush = p.flush, a.c_slice = (int64_t)(p.taps_bytes / p.splits / 8);
+  a.guard = guard_for(tx, cells_x, tdy.lim, ws + l.words);
+  a.guard.cells[1] = cells_dy, a.guard.planes[1] = g.k;
+  a.guard.grow = bits_of(g.N);
+  if (vcnn_status s = launch_product<false, true, false, true>(a, g.n, st)) return s;
+  return launch_line_inverse(kernel_lines(g, g.k), (int64_t)g.k * g.c, VCNN_F32, taps, a.c_slice, p.splits, dw, nullptr, 0, sums,
+                             (int)tiles, g.k, db, st);
+}
+
 vcnn_status launch_spectral_fwd(const SpectralPlan& p, int dtype, const ConvGeom& g, const void* x, const void* w, const float* bias,
                                 void* y, int relu, void* workspace, hipStream_t st) {
+  if (p.along) return lines_fwd(p, dtype, g, x, w, bias, y, relu, workspace, st);
   const Layout l = layout(g, VCNN_PASS_FWD, p);
   char* const ws = (char*)workspace;
   float2* const xs = (float2*)(ws + l.image);
@@ -495,11 +676,11 @@ vcnn_status launch_spectral_fwd(const SpectralPlan& p, int dtype, const ConvGeom
   float2* const taps = (float2*)(ws + l.taps);
   uint32_t* const cells = (uint32_t*)(ws + l.cells_image);
   uint32_t* const largest = (uint32_t*)(ws + l.largest);
-  const int64_t tiles = tiles_of(g, p);
+  const int64_t tiles = tiles_of(g, p, VCNN_PASS_FWD);
   const int esize = dtype == VCNN_BF16 ? 2 : 4;
   SpectralTiles tx = tiles_for(g, p, g.c, g.h, g.w);
   tx.y0 = -g.ph, tx.x0 = -g.pw;
-  if (vcnn_status s = launch_plane_spectra(tx, dtype, x, xs, cells, nullptr, (uint32_t*)(ws + l.words), st)) return s;
+  if (vcnn_status s = launch_plane_spectra(tx, dtype, x, xs, cells, nullptr, (uint32_t*)(ws + l.words), 64 + g.n, st)) return s;
   SpectralTiles ty = tiles_for(g, p, g.k, g.oh, g.ow);
   ty.lim_y = std::min(p.step_y, g.oh), ty.lim_x = std::min(p.step_x, g.ow);
   for (int k0 = 0; k0 < g.k; k0 += p.part) {
@@ -513,13 +694,13 @@ vcnn_status launch_spectral_fwd(const SpectralPlan& p, int dtype, const ConvGeom
     a.a_row = g.c, a.a_z = 1, a.a_planes = (int64_t)maps * g.c;
     a.b_col = g.c, a.b_z = 1, a.b_planes = tiles * g.c;
     a.c_row = 1, a.c_col = maps, a.c_planes = tiles * maps;
-    a.splits = p.splits, a.per_split = p.per_split, a.flush = g.c;
+    a.splits = p.splits, a.per_split = p.per_split, a.flush = p.flush;
     if (last) {
       a.guard = guard_for(tx, cells, g.r, g.s, ws + l.words);
       a.guard.largest = largest, a.guard.largest_count = ceil_div((int64_t)g.k * g.c, 4);
       a.guard.grow = bits_of((int64_t)g.c * g.r * g.s);
     }
-    if (vcnn_status s = launch_product<true, true, false>(a, last ? g.n : 0, st)) return s;
+    if (vcnn_status s = launch_product<true, true, false, false>(a, last ? g.n : 0, st)) return s;
     ty.first = k0, ty.count = maps;
     if (vcnn_status s = launch_plane_inverse(ty, dtype, ys, 0, 1, y, bias, relu, st)) return s;
   }
@@ -528,6 +709,7 @@ vcnn_status launch_spectral_fwd(const SpectralPlan& p, int dtype, const ConvGeom
 
 vcnn_status launch_spectral_bwd_data(const SpectralPlan& p, int dtype, const ConvGeom& g, const void* w, const void* dy, void* dx,
                                      void* workspace, hipStream_t st) {
+  if (p.along) return lines_bwd_data(p, dtype, g, w, dy, dx, workspace, st);
   const Layout l = layout(g, VCNN_PASS_BWD_DATA, p);
   char* const ws = (char*)workspace;
   float2* const xs = (float2*)(ws + l.image);
@@ -535,16 +717,14 @@ vcnn_status launch_spectral_bwd_data(const SpectralPlan& p, int dtype, const Con
   float2* const taps = (float2*)(ws + l.taps);
   uint32_t* const cells = (uint32_t*)(ws + l.cells_map);
   uint32_t* const largest = (uint32_t*)(ws + l.largest);
-  const int64_t tiles = tiles_of(g, p);
+  const int64_t tiles = tiles_of(g, p, VCNN_PASS_BWD_DATA);
   const bool one = one_tile(g);
-  // Pixel i of the padded plane gets dy[i - q] w[q].  A whole plane starts at dy's first pixel; a tile of a larger one starts
-  // r - 1 pixels before its results, of which the transform wraps that many.
   SpectralTiles tdy = tiles_for(g, p, g.k, g.oh, g.ow);
-  tdy.y0 = one ? 0 : g.ph - (g.r - 1), tdy.x0 = one ? 0 : g.pw - (g.s - 1);
   SpectralTiles tdx = tiles_for(g, p, g.c, g.h, g.w);
-  tdx.y0 = one ? g.ph : g.r - 1, tdx.x0 = one ? g.pw : g.s - 1;
+  place_dx(one, g.r, g.ph, &tdy.y0, &tdx.y0);
+  place_dx(one, g.s, g.pw, &tdy.x0, &tdx.x0);
   tdx.lim_y = std::min(p.step_y, g.h), tdx.lim_x = std::min(p.step_x, g.w);
-  if (vcnn_status s = launch_plane_spectra(tdy, dtype, dy, ys, cells, nullptr, (uint32_t*)(ws + l.words), st)) return s;
+  if (vcnn_status s = launch_plane_spectra(tdy, dtype, dy, ys, cells, nullptr, (uint32_t*)(ws + l.words), 64 + g.n, st)) return s;
   if (vcnn_status s = launch_taps_spectra(dtype, w, (int64_t)g.k * g.c, g.r, g.s, taps, largest, st)) return s;
   ProductArgs a{};
   a.A = taps, a.B = ys, a.C = xs;
@@ -552,16 +732,17 @@ vcnn_status launch_spectral_bwd_data(const SpectralPlan& p, int dtype, const Con
   a.a_row = 1, a.a_z = g.c, a.a_planes = (int64_t)g.k * g.c;
   a.b_col = g.k, a.b_z = 1, a.b_planes = tiles * g.k;
   a.c_row = 1, a.c_col = g.c, a.c_planes = tiles * g.c;
-  a.splits = p.splits, a.per_split = p.per_split, a.flush = 32, a.c_slice = (int64_t)(p.image_bytes / p.splits / 8);
+  a.splits = p.splits, a.per_split = p.per_split, a.flush = p.flush, a.c_slice = (int64_t)(p.image_bytes / p.splits / 8);
   a.guard = guard_for(tdy, cells, g.r, g.s, ws + l.words);
   a.guard.largest = largest, a.guard.largest_count = ceil_div((int64_t)g.k * g.c, 4);
   a.guard.grow = bits_of((int64_t)g.k * g.r * g.s);
-  if (vcnn_status s = launch_product<true, false, false>(a, g.n, st)) return s;
+  if (vcnn_status s = launch_product<true, false, false, false>(a, g.n, st)) return s;
   return launch_plane_inverse(tdx, dtype, xs, a.c_slice, p.splits, dx, nullptr, 0, st);
 }
 
 vcnn_status launch_spectral_filter(const SpectralPlan& p, int dtype, const ConvGeom& g, const void* x, const void* dy, float* dw,
                                    float* db, void* workspace, hipStream_t st) {
+  if (p.along) return lines_filter(p, dtype, g, x, dy, dw, db, workspace, st);
   const Layout l = layout(g, VCNN_PASS_BWD_FILTER, p);
   char* const ws = (char*)workspace;
   float2* const xs = (float2*)(ws + l.image);
@@ -570,24 +751,24 @@ vcnn_status launch_spectral_filter(const SpectralPlan& p, int dtype, const ConvG
   uint32_t* const cells_x = (uint32_t*)(ws + l.cells_image);
   uint32_t* const cells_dy = (uint32_t*)(ws + l.cells_map);
   double* const sums = (double*)(ws + l.sums);
-  const int64_t tiles = tiles_of(g, p);
+  const int64_t tiles = tiles_of(g, p, VCNN_PASS_BWD_FILTER);
   SpectralTiles tx = tiles_for(g, p, g.c, g.h, g.w);
   tx.y0 = -g.ph, tx.x0 = -g.pw;
   SpectralTiles tdy = tiles_for(g, p, g.k, g.oh, g.ow);
   tdy.lim_y = std::min(p.step_y, g.oh), tdy.lim_x = std::min(p.step_x, g.ow);  // every output pixel in one tile
-  if (vcnn_status s = launch_plane_spectra(tx, dtype, x, xs, cells_x, nullptr, (uint32_t*)(ws + l.words), st)) return s;
-  if (vcnn_status s = launch_plane_spectra(tdy, dtype, dy, ys, cells_dy, db ? sums : nullptr, nullptr, st)) return s;
+  if (vcnn_status s = launch_plane_spectra(tx, dtype, x, xs, cells_x, nullptr, (uint32_t*)(ws + l.words), 64 + g.n, st)) return s;
+  if (vcnn_status s = launch_plane_spectra(tdy, dtype, dy, ys, cells_dy, db ? sums : nullptr, nullptr, 0, st)) return s;
   ProductArgs a{};
   a.A = ys, a.B = xs, a.C = taps;
   a.rows = g.k, a.cols = g.c, a.depth = (int)tiles;
   a.a_row = 1, a.a_z = g.k, a.a_planes = tiles * g.k;
   a.b_col = 1, a.b_z = g.c, a.b_planes = tiles * g.c;
   a.c_row = g.c, a.c_col = 1, a.c_planes = (int64_t)g.k * g.c;
-  a.splits = p.splits, a.per_split = p.per_split, a.flush = 32, a.c_slice = (int64_t)(p.taps_bytes / p.splits / 8);
+  a.splits = p.splits, a.per_split = p.per_split, a.flush = p.flush, a.c_slice = (int64_t)(p.taps_bytes / p.splits / 8);
   a.guard = guard_for(tx, cells_x, tdy.lim_y, tdy.lim_x, ws + l.words);
   a.guard.cells[1] = cells_dy, a.guard.planes[1] = g.k;
   a.guard.grow = bits_of(g.N);
-  if (vcnn_status s = launch_product<false, true, true>(a, g.n, st)) return s;
+  if (vcnn_status s = launch_product<false, true, true, false>(a, g.n, st)) return s;
   return launch_taps_inverse(taps, a.c_slice, p.splits, (int64_t)g.k * g.c, g.r, g.s, dw, sums, (int)tiles, g.k, db, st);
 }
 

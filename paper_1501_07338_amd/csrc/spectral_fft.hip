@@ -8,44 +8,12 @@
 // the memory the spectra take.
 #include "elem.h"
 #include "spectral.h"
+#include "spectral_math.h"
 
 namespace vcnn {
 
 static constexpr int kThreads = 256;
 static constexpr int kPitch = 65;  // of a row of 64 complex doubles in LDS: eight rows 16 bytes apart in their banks
-
-struct cd {
-  double x, y;
-};
-__device__ __forceinline__ cd operator+(cd a, cd b) { return {a.x + b.x, a.y + b.y}; }
-__device__ __forceinline__ cd operator-(cd a, cd b) { return {a.x - b.x, a.y - b.y}; }
-__device__ __forceinline__ cd operator*(cd a, cd b) { return {fma(a.x, b.x, -a.y * b.y), fma(a.x, b.y, a.y * b.x)}; }
-__device__ __forceinline__ cd conj(cd a) { return {a.x, -a.y}; }
-// a * (-i) forward, a * i inverse
-template <bool INV>
-__device__ __forceinline__ cd turn(cd a) { return INV ? cd{-a.y, a.x} : cd{a.y, -a.x}; }
-
-template <bool INV>
-__device__ __forceinline__ void dft4(cd& a, cd& b, cd& c, cd& d) {
-  const cd s = a + c, t = a - c, u = b + d, q = turn<INV>(b - d);
-  a = s + u, b = t + q, c = s - u, d = t - q;
-}
-// v[k] = sum_n v[n] e^(-+ 2 pi i n k / 8)
-template <bool INV>
-__device__ __forceinline__ void dft8(cd (&v)[8]) {
-  constexpr double h = 0.70710678118654752440;
-  cd a[4], b[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) a[i] = v[i] + v[i + 4], b[i] = v[i] - v[i + 4];
-  const cd t1 = turn<INV>(b[1]), t3 = turn<INV>(b[3]);
-  b[1] = {h * (b[1].x + t1.x), h * (b[1].y + t1.y)};
-  b[2] = turn<INV>(b[2]);
-  b[3] = {h * (t3.x - b[3].x), h * (t3.y - b[3].y)};
-  dft4<INV>(a[0], a[1], a[2], a[3]);
-  dft4<INV>(b[0], b[1], b[2], b[3]);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) v[2 * i] = a[i], v[2 * i + 1] = b[i];
-}
 
 // e^(-2 pi i j / 64), j < 8
 __device__ const cd kRoot64[8] = {{1.0, -0.0},
@@ -61,11 +29,6 @@ __device__ __forceinline__ void twiddle(cd (&v)[8], cd w) {
   const cd w2 = w * w, w3 = w2 * w, w4 = w2 * w2;
   v[1] = v[1] * w, v[2] = v[2] * w2, v[3] = v[3] * w3, v[4] = v[4] * w4;
   v[5] = v[5] * (w4 * w), v[6] = v[6] * (w3 * w3), v[7] = v[7] * (w4 * w3);
-}
-// Orders a wave's LDS accesses among its lanes (they execute in program order).
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
 }
 // Between the two halves of a transform: thread j has v[k] and gets the v[j] of the eight threads, through its row of LDS.
 __device__ __forceinline__ void exchange(cd (&v)[8], cd* row, int j) {
@@ -110,28 +73,18 @@ struct PlaneArgs {
   uint32_t* cells;
   double* sums;
   uint32_t* words;
+  int cleared;
   int64_t planes;
 };
 
-// The largest of v[0..7] over a wave: lane l gets that of v[((l >> 3) & 1) * 4 + (l >> 1 & 3)].  (Moves within 16 lanes cost the
-// vector units one instruction; by general shuffles, of 16 values, this took 45 of 106 us on 8192 planes.)
-template <int CTRL>
-__device__ __forceinline__ uint32_t moved(uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, true); }
+// The largest of v[0..7] over a wave: lane l gets that of v[((l >> 3) & 1) * 4 + (l >> 1 & 3)].  (By general shuffles, of 16
+// values, this took 45 of 106 us on 8192 planes.)
 __device__ __forceinline__ uint32_t max_scatter(const uint32_t (&v)[8], int lane) {
   uint32_t a[4], b[2], c;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {  // row_mirror: lane ^ 15
-    const uint32_t keep = lane & 8 ? v[i + 4] : v[i], give = lane & 8 ? v[i] : v[i + 4];
-    a[i] = max(keep, moved<0x140>(give));
-  }
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {  // row_half_mirror: lane ^ 7
-    const uint32_t keep = lane & 4 ? a[i + 2] : a[i], give = lane & 4 ? a[i] : a[i + 2];
-    b[i] = max(keep, moved<0x141>(give));
-  }
-  const uint32_t keep = lane & 2 ? b[1] : b[0], give = lane & 2 ? b[0] : b[1];
-  c = max(keep, moved<0x4e>(give));  // lane ^ 2
-  c = max(c, moved<0xb1>(c));        // lane ^ 1
+  keep_half<kMirror16, 4>(v, lane & 8, a);
+  keep_half<kMirror8, 2>(a, lane & 4, b);
+  keep_half<kSwap2, 1>(b, lane & 2, &c);
+  c = max(c, moved<kSwap1>(c));
   c = max(c, (uint32_t)__shfl_xor((int)c, 16));
   return max(c, (uint32_t)__shfl_xor((int)c, 32));
 }
@@ -165,7 +118,8 @@ __global__ __launch_bounds__(kThreads) void plane_spectra_kernel(PlaneArgs a) {
       const int ly = q + 32 * half, lx = j + 8 * i;
       if (!(ly >= top && ly < bottom && lx >= left && lx < right)) (half ? hi : lo)[i] = 0.f;
     }
-  if (a.words && p == 0 && tid < 2) a.words[tid] = 0;
+  if (p == 0)
+    for (int i = tid; i < a.cleared; i += kThreads) a.words[i] = 0;
   const cd w = kRoot64[j];
   cd v[8];
 #pragma unroll
@@ -364,6 +318,16 @@ __global__ __launch_bounds__(kThreads) void taps_spectra_kernel(const T* __restr
   if (tid == 0) largest[blockIdx.x] = max(max(wave_max[0], wave_max[1]), max(wave_max[2], wave_max[3]));
 }
 
+// db[m] = sums[m] + sums[maps + m] + ..., by a wave
+__device__ __forceinline__ void add_sums(const double* sums, int count, int maps, int m, float* db) {
+  if (m >= maps) return;
+  double sum = 0;
+  for (int i = threadIdx.x & 63; i < count; i += 64) sum += sums[(int64_t)i * maps + m];
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) sum += __shfl_xor(sum, d);
+  if ((threadIdx.x & 63) == 0) db[m] = (float)sum;
+}
+
 __global__ __launch_bounds__(kThreads) void taps_inverse_kernel(const float2* __restrict__ spectra, int64_t slice, int slices,
                                                                 int64_t kernels, int r, int s, float* __restrict__ dw,
                                                                 const double* __restrict__ sums, int sum_planes, int maps,
@@ -371,11 +335,7 @@ __global__ __launch_bounds__(kThreads) void taps_inverse_kernel(const float2* __
   __shared__ cd z[32 * kPitch];
   const int tid = threadIdx.x, j = tid & 7, q = tid >> 3;
   if ((int)blockIdx.x >= blocks) {  // the bias gradient
-    const int m = ((int)blockIdx.x - blocks) * kThreads + tid;
-    if (m >= maps) return;
-    double sum = 0;
-    for (int i = 0; i < sum_planes; ++i) sum += sums[(int64_t)i * maps + m];
-    db[m] = (float)sum;
+    add_sums(sums, sum_planes, maps, ((int)blockIdx.x - blocks) * 4 + (tid >> 6), db);
     return;
   }
   const int64_t first = (int64_t)blockIdx.x * 4;
@@ -414,10 +374,223 @@ __global__ __launch_bounds__(kThreads) void taps_inverse_kernel(const float2* __
     }
 }
 
+// ---- lines -------------------------------------------------------------------------------------------------------
+// 256 points as 16 x 16: sixteen threads a transform, two real lines each; 32 lines a block.
+// e^(-2 pi i j / 256), j < 16
+__device__ const cd kRoot256[16] = {{1.0, -0.0},
+                                    {0.99969881869620422012, -0.02454122852291228803},
+                                    {0.99879545620517239271, -0.04906767432741801426},
+                                    {0.99729045667869021614, -0.07356456359966742352},
+                                    {0.99518472667219688624, -0.09801714032956060199},
+                                    {0.99247953459870999816, -0.12241067519921619849},
+                                    {0.98917650996478097345, -0.14673047445536175166},
+                                    {0.98527764238894124477, -0.17096188876030122636},
+                                    {0.98078528040323044913, -0.19509032201612826785},
+                                    {0.97570213003852854446, -0.21910124015686979722},
+                                    {0.97003125319454399260, -0.24298017990326388994},
+                                    {0.96377606579543986669, -0.26671275747489838633},
+                                    {0.95694033573220886494, -0.29028467725446236764},
+                                    {0.94952818059303666720, -0.31368174039889147666},
+                                    {0.94154406518302077841, -0.33688985339222005069},
+                                    {0.93299279883473888771, -0.35989503653498814878}};
+__device__ __forceinline__ void twiddle(cd (&v)[16], cd w) {
+  cd p[16];
+  p[1] = w;
+#pragma unroll
+  for (int k = 2; k < 16; ++k) p[k] = p[k / 2] * p[k - k / 2];
+#pragma unroll
+  for (int k = 1; k < 16; ++k) v[k] = v[k] * p[k];
+}
+__device__ __forceinline__ void exchange(cd (&v)[16], cd* row, int j) {
+  wave_sync();
+#pragma unroll
+  for (int k = 0; k < 16; ++k) row[k * 16 + (j ^ k)] = v[k];
+  wave_sync();
+#pragma unroll
+  for (int i = 0; i < 16; ++i) v[i] = row[j * 16 + (i ^ j)];
+  wave_sync();
+}
+
+// Where a line comes from and where its spectrum goes.
+struct Line {
+  int64_t at;      // of its first sample (before the tile's offset) in the tensor
+  int64_t plane;   // index of its spectrum
+  int64_t cell;    // index of its cells
+  int channel, start;
+};
+__device__ __forceinline__ Line line_of(const SpectralLines& t, unsigned id) {
+  Line l;
+  const unsigned rows = id / t.tiles, maps = rows / t.others;
+  const int tile = id % t.tiles, o = rows % t.others, c = maps % t.count;
+  const int64_t n = maps / t.count;
+  l.at = (n * t.channels + t.first + c) * t.s_channel + o * t.s_other;
+  l.plane = n * t.p_image + c * t.p_channel + (int64_t)o * t.tiles + tile;
+  l.cell = ((n * t.others + o) * t.tiles + tile) * t.count + c;
+  l.channel = t.first + c, l.start = tile * t.step;
+  return l;
+}
+
+struct LineArgs {
+  LineJob job[2];
+  int first_blocks;  // blocks of the first job
+  uint32_t* words;
+  int cleared;
+};
+
+template <typename T>
+__global__ __launch_bounds__(kThreads) void line_spectra_kernel(LineArgs args) {
+  __shared__ cd z[16 * 256];
+  __shared__ int plane_of[32];
+  const int tid = threadIdx.x, j = tid & 15, q = tid >> 4;
+  if (blockIdx.x == 0)
+    for (int i = tid; i < args.cleared; i += kThreads) args.words[i] = 0;
+  const bool second = (int)blockIdx.x >= args.first_blocks;
+  const LineJob& a = args.job[second];
+  const SpectralLines& t = a.t;
+  const int block = blockIdx.x - (second ? args.first_blocks : 0), first = block * 32 + 2 * q, lines = (int)t.lines();
+  cd v[16];
+  float f[2][16];
+  Line l[2];
+#pragma unroll
+  for (int half = 0; half < 2; ++half) {
+    l[half] = line_of(t, min(first + half, lines - 1));
+    if (j == half) plane_of[2 * q + half] = (int)l[half].plane;
+    const int x0 = l[half].start + t.x0;
+    const T* const src = (const T*)a.src + l[half].at;
+    const int left = max(0, -x0), right = first + half < lines ? min(t.lim, t.len - x0) : 0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int x = j + 16 * i;
+      f[half][i] = ld(src + (x >= left && x < right ? (int64_t)(x0 + x) * t.s_along : 0));
+    }
+  }
+#pragma unroll
+  for (int half = 0; half < 2; ++half) {
+    const int x0 = l[half].start + t.x0, left = max(0, -x0), right = first + half < lines ? min(t.lim, t.len - x0) : 0;
+    uint32_t m[16], b[8], c[4], e[2], largest;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int x = j + 16 * i;
+      if (!(x >= left && x < right)) f[half][i] = 0.f;
+      m[i] = __float_as_uint(f[half][i]) & 0x7fffffffu;
+    }
+    if (a.cells) {  // cell i: samples 16 i to 16 i + 15
+      keep_half<kMirror16, 8>(m, j & 8, b);
+      keep_half<kMirror8, 4>(b, j & 4, c);
+      keep_half<kSwap2, 2>(c, j & 2, e);
+      keep_half<kSwap1, 1>(e, j & 1, &largest);
+      if (a.whole) {
+        largest = max(largest, moved<kMirror16>(largest));
+        largest = max(largest, moved<kMirror8>(largest));
+        largest = max(largest, moved<kSwap2>(largest));
+        largest = max(largest, moved<kSwap1>(largest));
+        if (first + half < lines && j == 0) a.cells[l[half].cell] = largest;
+      } else if (first + half < lines) {
+        a.cells[l[half].cell * 16 + j] = largest;
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 16; ++i) v[i] = {(double)f[0][i], (double)f[1][i]};
+  cd* const row = z + q * 256;
+  dft16<false>(v);
+  twiddle(v, kRoot256[j]);
+  exchange(v, row, j);
+  dft16<false>(v);
+#pragma unroll
+  for (int k = 0; k < 16; ++k) row[j + 16 * k] = v[k];
+  if (a.sums && j == 0) {  // (additions only, also where an element is not finite)
+    if (first < lines) a.sums[l[0].cell] = v[0].x;
+    if (first + 1 < lines) a.sums[l[1].cell] = v[0].y;
+  }
+  __syncthreads();
+  const int slot = tid & 127;
+#pragma unroll 2
+  for (int m = 0; m < 8; ++m) {
+    const int tr = (tid >> 7) + 2 * m;
+    const cd A = z[tr * 256 + slot], B = z[tr * 256 + (slot == 0 ? 128 : 256 - slot)];
+    const float2 lower = slot == 0 ? make_float2((float)A.x, (float)B.x) : make_float2((float)(0.5 * (A.x + B.x)), (float)(0.5 * (A.y - B.y)));
+    const float2 upper = slot == 0 ? make_float2((float)A.y, (float)B.y) : make_float2((float)(0.5 * (A.y + B.y)), (float)(0.5 * (B.x - A.x)));
+    const int id = block * 32 + 2 * tr;
+    if (id < lines) a.spectra[((slot >> 6) * a.planes + plane_of[2 * tr]) * 64 + (slot & 63)] = lower;
+    if (id + 1 < lines) a.spectra[((slot >> 6) * a.planes + plane_of[2 * tr + 1]) * 64 + (slot & 63)] = upper;
+  }
+}
+
+struct LineInverseArgs {
+  SpectralLines t;
+  const float2* spectra;
+  int64_t slice, lines, planes;
+  int slices, blocks;
+  void* dst;
+  const float* bias;
+  int relu;
+  const double* sums;
+  int sum_planes, maps;
+  float* db;
+};
+
+template <typename T>
+__global__ __launch_bounds__(kThreads) void line_inverse_kernel(LineInverseArgs a) {
+  __shared__ cd z[16 * 256];
+  const int tid = threadIdx.x, j = tid & 15, q = tid >> 4;
+  const SpectralLines& t = a.t;
+  if ((int)blockIdx.x >= a.blocks) return add_sums(a.sums, a.sum_planes, a.maps, ((int)blockIdx.x - a.blocks) * 4 + (tid >> 6), a.db);
+  __shared__ int plane_of[32];
+  const int lines = (int)a.lines;
+  if (tid < 32) plane_of[tid] = (int)line_of(t, min((int)blockIdx.x * 32 + tid, lines - 1)).plane;
+  __syncthreads();
+  const int slot = tid & 127;
+#pragma unroll 4
+  for (int m = 0; m < 8; ++m) {
+    const int tr = (tid >> 7) + 2 * m;
+    const float2* in[2];
+#pragma unroll
+    for (int half = 0; half < 2; ++half) in[half] = a.spectra + ((slot >> 6) * a.planes + plane_of[2 * tr + half]) * 64 + (slot & 63);
+    cd A{0, 0}, B{0, 0};
+    for (int s = 0; s < a.slices; ++s) {
+      const float2 f = in[0][s * a.slice], g = in[1][s * a.slice];
+      A = A + cd{(double)f.x, (double)f.y}, B = B + cd{(double)g.x, (double)g.y};
+    }
+    cd* const row = z + tr * 256;
+    if (slot == 0) {
+      row[0] = {A.x, B.x}, row[128] = {A.y, B.y};
+    } else {
+      row[slot] = {A.x - B.y, A.y + B.x};
+      row[256 - slot] = {A.x + B.y, B.x - A.y};
+    }
+  }
+  __syncthreads();
+  cd* const row = z + q * 256;
+  cd v[16];
+#pragma unroll
+  for (int k = 0; k < 16; ++k) v[k] = row[j + 16 * k];
+  dft16<true>(v);
+  twiddle(v, conj(kRoot256[j]));
+  exchange(v, row, j);
+  dft16<true>(v);
+#pragma unroll
+  for (int half = 0; half < 2; ++half) {
+    const int id = blockIdx.x * 32 + 2 * q + half;
+    if (id >= lines) continue;
+    const Line l = line_of(t, id);
+    T* const dst = (T*)a.dst + l.at;
+    const float bias = a.bias ? a.bias[l.channel] : 0.f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int lx = j + 16 * i - t.x0, x = l.start + lx;
+      if (lx < 0 || lx >= t.lim || x >= t.len) continue;
+      float r = (float)((half ? v[i].y : v[i].x) * (1.0 / 256) + (double)bias);
+      if (a.relu) r = fmaxf(r, 0.f);
+      st(dst + (int64_t)x * t.s_along, r);
+    }
+  }
+}
+
 // ---- launches ----------------------------------------------------------------------------------------------------
 vcnn_status launch_plane_spectra(const SpectralTiles& t, int dtype, const void* src, float2* spectra, uint32_t* cells, double* sums,
-                                 uint32_t* words, hipStream_t st) {
-  PlaneArgs a{t, src, spectra, cells, sums, words, t.planes()};
+                                 uint32_t* words, int cleared, hipStream_t st) {
+  PlaneArgs a{t, src, spectra, cells, sums, words, cleared, t.planes()};
   if (dtype == VCNN_BF16) hipLaunchKernelGGL(plane_spectra_kernel<bf16>, dim3((unsigned)a.planes), dim3(kThreads), 0, st, a);
   else hipLaunchKernelGGL(plane_spectra_kernel<float>, dim3((unsigned)a.planes), dim3(kThreads), 0, st, a);
   return check_launch("plane_spectra");
@@ -440,9 +613,26 @@ vcnn_status launch_taps_spectra(int dtype, const void* w, int64_t kernels, int r
 vcnn_status launch_taps_inverse(const float2* spectra, int64_t slice, int slices, int64_t kernels, int r, int s, float* dw,
                                 const double* sums, int sum_planes, int maps, float* db, hipStream_t st) {
   const int blocks = (int)ceil_div(kernels, 4);
-  hipLaunchKernelGGL(taps_inverse_kernel, dim3((unsigned)(blocks + (db ? ceil_div(maps, kThreads) : 0))), dim3(kThreads), 0, st,
+  hipLaunchKernelGGL(taps_inverse_kernel, dim3((unsigned)(blocks + (db ? ceil_div(maps, 4) : 0))), dim3(kThreads), 0, st,
                      spectra, slice, slices, kernels, r, s, dw, sums, sum_planes, maps, db, blocks);
   return check_launch("taps_inverse");
+}
+
+vcnn_status launch_line_spectra(int dtype, const LineJob& first, const LineJob& second, uint32_t* words, int cleared, hipStream_t st) {
+  LineArgs a{{first, second}, (int)ceil_div(first.t.lines(), 32), words, cleared};
+  const dim3 grid((unsigned)(a.first_blocks + ceil_div(second.t.lines(), 32)));
+  if (dtype == VCNN_BF16) hipLaunchKernelGGL(line_spectra_kernel<bf16>, grid, dim3(kThreads), 0, st, a);
+  else hipLaunchKernelGGL(line_spectra_kernel<float>, grid, dim3(kThreads), 0, st, a);
+  return check_launch("line_spectra");
+}
+vcnn_status launch_line_inverse(const SpectralLines& t, int64_t planes, int dtype, const float2* spectra, int64_t slice, int slices,
+                                void* dst, const float* bias, int relu, const double* sums, int sum_planes, int maps, float* db,
+                                hipStream_t st) {
+  LineInverseArgs a{t, spectra, slice, t.lines(), planes, slices, (int)ceil_div(t.lines(), 32), dst, bias, relu, sums, sum_planes, maps, db};
+  const dim3 grid((unsigned)(a.blocks + (db ? ceil_div(maps, 4) : 0)));
+  if (dtype == VCNN_BF16) hipLaunchKernelGGL(line_inverse_kernel<bf16>, grid, dim3(kThreads), 0, st, a);
+  else hipLaunchKernelGGL(line_inverse_kernel<float>, grid, dim3(kThreads), 0, st, a);
+  return check_launch("line_inverse");
 }
 
 }  // namespace vcnn

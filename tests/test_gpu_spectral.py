@@ -19,18 +19,34 @@ TOL = 4e-6
 # (n, c, h, w, k, r, s, pad_h, pad_w), the passes, bfloat16
 SHAPES = [
     ((27, 28, 64, 64, 29, 16, 16, 0, 0), {FWD, FILTER, DATA}, False),   # one whole tile; the largest kernel; ragged maps, images
-    ((12, 41, 39, 31, 33, 12, 12, 11, 8), {FILTER, DATA}, False),       # padded by as much as the kernel; ragged channels
+    ((12, 41, 39, 31, 33, 12, 12, 11, 8), {FILTER}, False),             # padded by as much as the kernel; ragged channels
     ((11, 11, 69, 64, 60, 11, 15, 0, 0), {FWD, FILTER}, False),         # tiles along one axis, the second a few rows
     ((14, 13, 103, 100, 13, 13, 12, 0, 0), {FWD, DATA}, False),         # 2 x 2 tiles, more than 32 of them
     ((17, 24, 58, 60, 50, 8, 9, 0, 0), {FILTER}, False),                # odd kernel columns
     ((41, 13, 95, 41, 12, 14, 13, 1, 1), {DATA}, False),                # padded tiles
     ((5, 12, 60, 38, 98, 8, 16, 5, 11), {FWD, FILTER}, False),          # more than 64 maps; pads on one side of a tile
-    ((20, 40, 64, 64, 139, 16, 16, 0, 0), {FWD, DATA}, False),          # maps in slices, the last one short
+    ((14, 40, 64, 64, 139, 16, 16, 0, 0), {FWD, DATA}, False),          # maps in slices, the last one short
     ((40, 11, 64, 64, 150, 16, 16, 0, 0), {FILTER}, False),             # images in two slices, the second short
     ((4, 36, 98, 41, 67, 10, 15, 0, 0), {FILTER}, True),
-    ((30, 29, 64, 62, 180, 16, 16, 0, 0), {FWD, FILTER, DATA}, True),
+    ((30, 29, 64, 62, 180, 16, 16, 0, 0), {FWD, FILTER}, True),
+    ((16, 38, 64, 64, 512, 16, 16, 0, 0), {DATA}, True),
+    ((18, 14, 51, 48, 31, 10, 13, 9, 5), {DATA}, False),                # pads that differ
+    # lines: along the width and the height, whole and in tiles, padded, a last pair and a last block that are not full
+    ((7, 20, 42, 214, 36, 1, 100, 0, 0), {FWD, DATA}, False),
+    ((1, 51, 219, 228, 48, 72, 1, 0, 0), {FWD, DATA}, False),
+    ((49, 10, 8, 149, 23, 1, 128, 0, 117), {FWD, DATA}, False),         # the longest kernel
+    ((6, 55, 261, 9, 58, 95, 1, 86, 0), {DATA}, False),
+    ((1, 78, 32, 205, 130, 1, 58, 0, 23), {FILTER}, False),
+    ((4, 70, 217, 8, 189, 100, 1, 0, 0), {FILTER}, False),
+    ((7, 38, 227, 28, 43, 100, 1, 60, 0), {FWD, DATA}, True),
+    ((5, 80, 11, 278, 77, 1, 92, 0, 0), {FILTER}, True),
 ]
-ONE_EACH = [((9, 22, 70, 70, 49, 16, 16, 0, 0), FWD), ((27, 28, 64, 64, 29, 16, 16, 0, 0), DATA), ((11, 11, 69, 64, 60, 11, 15, 0, 0), FILTER)]
+# one of every pair of pass and transform, and of the two types
+ONE_EACH = [((9, 22, 70, 70, 49, 16, 16, 0, 0), FWD, False), ((27, 28, 64, 64, 29, 16, 16, 0, 0), DATA, False),
+            ((11, 11, 69, 64, 60, 11, 15, 0, 0), FILTER, False), ((7, 20, 42, 214, 36, 1, 100, 0, 0), FWD, False),
+            ((50, 55, 10, 128, 12, 1, 97, 0, 84), DATA, False), ((4, 70, 217, 8, 189, 100, 1, 0, 0), FILTER, False),
+            ((30, 29, 64, 62, 180, 16, 16, 0, 0), FWD, True), ((16, 38, 64, 64, 512, 16, 16, 0, 0), DATA, True),
+            ((30, 29, 64, 62, 180, 16, 16, 0, 0), FILTER, True), ((7, 38, 227, 28, 43, 100, 1, 60, 0), FWD, True)]
 
 
 def desc(shape, bf16=False):
@@ -106,7 +122,7 @@ def test_routes_of_the_tested_layers(shape, passes, bf16):
 
 def test_small_kernels_and_few_maps_stay():
     """No GPU needed: kernels the transforms do not take, and layers they do not pay for."""
-    for shape in ((27, 28, 64, 64, 29, 17, 16, 0, 0), (27, 28, 64, 64, 29, 6, 6, 0, 0), (27, 28, 64, 64, 4, 16, 16, 0, 0),
+    for shape in ((27, 28, 64, 64, 29, 17, 16, 0, 0), (16, 38, 64, 200, 38, 1, 129, 0, 0), (16, 38, 64, 184, 38, 1, 121, 1, 0), (27, 28, 64, 64, 29, 6, 6, 0, 0), (27, 28, 64, 64, 4, 16, 16, 0, 0),
                   (27, 4, 64, 64, 29, 16, 16, 0, 0), (1, 8, 30, 30, 8, 9, 9, 0, 0)):
         assert all(route(desc(shape), which) != "spectral" for which in (FWD, FILTER, DATA)), shape
 
@@ -118,8 +134,10 @@ def test_queries_and_routes_agree():
     log = lambda lo, hi: int(round(np.exp(rng.uniform(np.log(lo), np.log(hi)))))
     for _ in range(600):
         r, s = int(rng.integers(7, 17)), int(rng.integers(7, 17))
+        if rng.random() < 0.4:
+            r, s = (1, int(rng.integers(8, 129))) if rng.random() < 0.5 else (int(rng.integers(8, 129)), 1)
         bf16 = bool(rng.random() < 0.3)
-        d = desc((log(1, 100), log(5, 100), log(r, 130), log(s, 130), log(5, 300), r, s, int(rng.integers(0, r)), int(rng.integers(0, s))), bf16)
+        d = desc((log(1, 100), log(5, 100), log(r, 250), log(s, 250), log(5, 300), r, s, int(rng.integers(0, r)), int(rng.integers(0, s))), bf16)
         for which in (FWD, FILTER, DATA):
             need = vcnn.conv_workspace_bytes(d, which)
             name = vcnn.conv_route(d, which, need)
@@ -147,7 +165,7 @@ def test_against_the_oracle(shape, passes, bf16):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("shape,which", [t for t in ONE_EACH if t[1] != FILTER])
+@pytest.mark.parametrize("shape,which", [t[:2] for t in ONE_EACH if t[1] != FILTER and not t[2]])
 def test_an_image_does_not_depend_on_its_neighbours(shape, which):
     """Bit for bit, whatever the magnitudes of the other images, also where one of those is not finite."""
     d, x, wt, b, dy = tensors(shape, 5200)
@@ -164,13 +182,11 @@ def test_an_image_does_not_depend_on_its_neighbours(shape, which):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("shape,which", ONE_EACH)
-@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("shape,which,bf16", ONE_EACH)
 @pytest.mark.parametrize("case", ["outlier", "dark", "inf", "nan", "weight", "range"])
 def test_what_the_transforms_do_not_carry(shape, which, bf16, case):
     """An element or a window far from the rest of its plane, infinities and NaN, magnitudes whose products leave a float's
     range on the way: the pass gives what the float kernel gives, every output to that kernel's own accuracy."""
-    shape = (30, 29, 64, 62, 180, 16, 16, 0, 0) if bf16 else shape
     d, x, wt, b, dy = tensors(shape, 5300, bf16)
     assert route(d, which) == "spectral"
     b = np.zeros_like(b)
@@ -184,12 +200,12 @@ def test_what_the_transforms_do_not_carry(shape, which, bf16, case):
         else:
             dy[0] = 0
     elif case == "dark":
-        t[0, :, :40, :40] *= np.float32(2.0 ** -16)
+        t[0, :, :d.r + (40 if d.s == 1 else 24), :d.s + (40 if d.r == 1 else 24)] *= np.float32(2.0 ** -16)  # (some whole cells)
     elif case == "weight":
         if which == FILTER:
             dy[1, 1, 1, 1] = np.inf
         else:
-            wt[1, 1, 1, 1] = np.inf
+            wt[1, 1, -1, -1] = np.inf
     elif case == "range":
         t *= np.float32(2.0 ** 62)
         (dy if which == FILTER else wt)[...] *= np.float32(2.0 ** 40)
@@ -216,9 +232,10 @@ def test_what_the_transforms_do_not_carry(shape, which, bf16, case):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("act", [vcnn.ACT_RELU, vcnn.ACT_TANH, vcnn.ACT_SIGMOID])
-def test_activation_derivative(act):
+@pytest.mark.parametrize("shape", [t[0] for t in ONE_EACH if t[1] == DATA and not t[2]])
+def test_activation_derivative(shape, act):
     """Applied once, to the images the float kernel computes as to the others."""
-    d, x, wt, b, dy = tensors(ONE_EACH[1][0], 5400)
+    d, x, wt, b, dy = tensors(shape, 5400)
     assert route(d, DATA) == "spectral"
     dy[1, 0, 0, 0] = 2.0 ** 45
     wt[0] = 0
@@ -230,7 +247,7 @@ def test_activation_derivative(act):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("shape,which", ONE_EACH)
+@pytest.mark.parametrize("shape,which", [t[:2] for t in ONE_EACH if not t[2]])
 def test_recorded_call_decides_anew_on_every_replay(shape, which):
     d, x, wt, b, dy = tensors(shape, 5500)
     xd, wd, bd, dyd = (torch.from_numpy(a).to(DEV) for a in (x, wt, b, dy))
@@ -272,8 +289,8 @@ def test_parts_and_smaller_workspaces():
     whole, parts = (run_pass(d, FWD, x, wt, b, dy, z) for z in (300 << 20, need))
     assert np.array_equal(whole, parts)
     assert np.array_equal(whole[3][:, :25, :25], np.broadcast_to(b[:, None, None], whole[3][:, :25, :25].shape))
-    for which in (FWD, FILTER, DATA):
-        d, x, wt, b, dy = tensors(ONE_EACH[1][0], 5700)
+    for which, shape in ((FWD, SHAPES[0][0]), (FILTER, SHAPES[0][0]), (DATA, SHAPES[0][0]), (FWD, ONE_EACH[3][0]), (DATA, ONE_EACH[4][0])):
+        d, x, wt, b, dy = tensors(shape, 5700)
         need = vcnn.conv_workspace_bytes(d, which)
         low, high = -1, need
         while high - low > 1:  # the least the pass runs with
