@@ -105,7 +105,7 @@ static bool fold_beats_halo(const ConvGeom& g, const HaloPlan& hp, const FoldPla
 
 // Which realisation a pass uses for a given shape.  The same decision drives the workspace query and
 // the launch, so the two always agree.
-enum Path { PATH_EXPLICIT, PATH_POINTWISE, PATH_FEW_OUT, PATH_FEW_IN, PATH_DIRECT_FILTER, PATH_HALO, PATH_HALO_FILTER, PATH_HALO_BF16, PATH_FILTER_BF16, PATH_HALO_FILTER_BF16, PATH_FEW_COLS_FILTER, PATH_SMALL, PATH_SMALL_BWD, PATH_FOLD, PATH_FFT, PATH_TAPS, PATH_POINTWISE_BF16, PATH_SPLIT, PATH_F16X2, PATH_FOLD_FRAG, PATH_POINTWISE_F16, PATH_SPECTRAL };
+enum Path { PATH_EXPLICIT, PATH_POINTWISE, PATH_FEW_OUT, PATH_FEW_IN, PATH_DIRECT_FILTER, PATH_HALO, PATH_HALO_FILTER, PATH_HALO_BF16, PATH_FILTER_BF16, PATH_HALO_FILTER_BF16, PATH_FEW_COLS_FILTER, PATH_SMALL, PATH_SMALL_BWD, PATH_FOLD, PATH_FFT, PATH_TAPS, PATH_POINTWISE_BF16, PATH_SPLIT, PATH_F16X2, PATH_FOLD_FRAG, PATH_POINTWISE_F16, PATH_SPECTRAL, PATH_FIRST };
 struct Plan {
   Path path;
   DirectGeom dg;
@@ -124,6 +124,7 @@ struct Plan {
   FoldFragPlan ff;
   PointwiseF16Plan pw16;
   SpectralPlan spec;
+  FirstPlan first;
   Path behind;       // PATH_F16X2, PATH_POINTWISE_F16, PATH_SPECTRAL: the float path enqueued behind for what the terms do not carry ...
   size_t behind_at;  // ... and the offset of its workspace
   int split;        // channel slices (few-out), output-map group size (few-in) or batch slices (filter gradient)
@@ -341,7 +342,13 @@ static Plan direct_plan(const ConvGeom& g, int pass, int dtype, size_t offered) 
     }
   }
   // (other 1x1 layers included: they are a plain bf16 product through the same kernel)
-  // (a single map over many channels is faster as the taps-as-rows product below, in bf16 storage as well)
+  // (a single map over many channels is faster as the taps-as-rows product below, in bf16 storage as well; and so are at most
+  // four channels, half or more of a channel group of eight padding, by the kernel that holds the kernel matrix in registers:
+  // 64 1 64 64 -> 64 9 9 102 -> 49 us, 128 3 32 32 -> 32 5 5 30 -> 17 us)
+  if (bf16_mfma && pass == VCNN_PASS_FWD && g.k > 4 && conv_first_plan(g, &p.first)) {
+    p.path = PATH_FIRST;
+    return p;
+  }
   if (bf16_mfma && pass == VCNN_PASS_FWD && (g.k > 4 || g.c >= 64) && !conv_taps_applies(g) &&
       conv_halo_bf16_plan(g.n, g.c, g.h, g.w, g.k, g.r, g.s, g.ph, g.pw, &p.hb)) {
     p.path = PATH_HALO_BF16;
@@ -398,6 +405,8 @@ static Plan direct_plan(const ConvGeom& g, int pass, int dtype, size_t offered) 
       p.workspace_bytes = align256(p.partial_bytes);
     } else if (is_pointwise(g)) {
       p.path = PATH_POINTWISE;
+    } else if (automatic && g.k > 4 && conv_first_plan(g, &p.first)) {
+      p.path = PATH_FIRST;  // at most four channels: the kernel matrix in registers
     } else if (automatic && g.k > 4 && conv_small_applies(g.n, g.c, g.h, g.w, g.k, g.r, g.s, g.ph, g.pw)) {
       p.path = PATH_SMALL;  // a few hundred MFLOP: latency-bound, one tile per block and the contraction over its waves
     } else if (allow_direct && (g.c > 4 || g.k >= 32 || algo == VCNN_ALGO_IMPLICIT) &&
@@ -619,6 +628,7 @@ vcnn_status vcnn_conv_route(const vcnn_conv_desc* d, int32_t pass, size_t worksp
     case PATH_F16X2: *name = "two_term"; break;
     case PATH_FOLD_FRAG: *name = p.ff.terms == 2 ? "two_term_fold" : "fold_bf16"; break;
     case PATH_POINTWISE_F16: *name = "two_term_pointwise"; break;
+    case PATH_FIRST: *name = "first"; break;
     case PATH_SPECTRAL: *name = "spectral"; break;
   }
   return VCNN_OK;
@@ -664,6 +674,7 @@ static vcnn_status conv_fwd_linear(const vcnn_conv_desc* d, const ConvGeom& g, c
   if (plan.path == PATH_FEW_OUT)
     return launch_direct_few_out(plan.dg, dt, plan.split, x, w, bias, y, (float*)workspace, relu, st);
   if (plan.path == PATH_FEW_IN) return launch_direct_few_in(plan.dg, dt, plan.split, x, w, bias, y, relu, st);
+  if (plan.path == PATH_FIRST) return launch_conv_first(plan.first, dt, g, x, w, bias, y, relu, st);
   if (plan.path == PATH_SMALL)
     return launch_conv_small(dt, g.n, g.c, g.h, g.w, g.k, g.r, g.s, g.ph, g.pw, x, w, bias, y, relu, st);
   auto float_halo = [&](const Declined& only) {

@@ -170,6 +170,19 @@ vcnn_status launch_filter_grad_few_cols(const FewColsPlan& p, int dtype, const C
 // only: if anything was left to the kernel that reads w2
 vcnn_status launch_flip_transpose(int dtype, const void* w, void* w2, int M, int C, int RS, hipStream_t st, const Declined& only = {});
 
+// ---- conv_first.hip -------------------------------------------------------------------------------------
+// Forward pass of layers with at most four input channels, the kernel matrix held in registers.
+struct FirstPlan {
+  int tm, steps;       // 32-row tiles; steps of two contraction indices compiled for
+  int groups;          // of 32 tm output maps
+  int tiles_per_img, tiles_per_wave, blocks_per_img;  // tiles of 32 pixels
+  int nr, wp;
+  size_t lds_bytes;
+};
+bool conv_first_plan(const ConvGeom& g, FirstPlan* p);
+vcnn_status launch_conv_first(const FirstPlan& p, int dtype, const ConvGeom& g, const void* x, const void* w, const float* bias, void* y,
+                              int relu, hipStream_t st);
+
 // ---- bf16_conv.hip (implicit bf16 kernels) / bf16_mfma.hip (explicit-route bf16 product) ------------
 struct HaloBf16Plan {
   int waves_m;       // waves of a block along the output maps

@@ -1134,17 +1134,23 @@ __global__ __launch_bounds__(kThreads, 2) void filter_grad_few_cols_kernel(FewCo
 
   const int run0 = blockIdx.x * a.runs_per_block;
   const int run1 = min(a.total_runs, run0 + a.runs_per_block);
-  for (int run = run0; run < run1; ++run) {
+  // A run's loads - the dY rows, zero beyond the maps and the sample's pixels, and the input rows where eight per thread
+  // hold them - are in flight while the run before is multiplied (64 1 64 64 -> 64 9 9, four runs a block: 55 -> 51 us with the sum of the
+  // slices, 64 1 64 64 -> 64 3 3 33 -> 29 us; one run a block: the same).
+  constexpr int MSTEP = kThreads / BP, PER = ROWS * BP / kThreads, HPER = 4;
+  const int pk = tid % BP, tile_elems = a.c * plane;
+  const bool halo_ahead = TM * TN <= 6 && tile_elems <= HPER * kThreads;
+  float dyv[PER], hv[HPER];
+  int tile_at = 0;
+  unsigned inside = 0;  // bit u: hv[u] lies in the image; bit 31: the run's pixel pk exists
+  auto load_run = [&](int run) {
     const int n = run / a.runs_per_img;
     const int tq = run - n * a.runs_per_img;
     const int p0 = a.tw ? 0 : tq * BP;
     const int oh_first = a.tw ? tq / a.tiles_x * (BP / a.tw) : p0 / a.ow;  // first output row and column of the run
     const int ow_first = a.tw ? tq % a.tiles_x * a.tw : 0;
-    __syncthreads();  // the previous run's MFMAs are done with the tiles
-    // pixel pk = tid % BP of the run: where it lies in the sample's output plane (-1: outside) and in the halo tile
-    constexpr int MSTEP = kThreads / BP;
-    const int pk = tid % BP;
-    int pix, tile_at;
+    // pixel pk of the run: where it lies in the sample's output plane (-1: outside) and in the halo tile
+    int pix;
     if (a.tw) {
       const int ty = pk / a.tw, tx = pk - ty * a.tw;
       const int oh = oh_first + ty, ow = ow_first + tx;
@@ -1156,24 +1162,42 @@ __global__ __launch_bounds__(kThreads, 2) void filter_grad_few_cols_kernel(FewCo
       pix = p0 + pk < a.P ? p : -1;
       tile_at = (oh - oh_first) * a.wp + (p - oh * a.ow);
     }
-    if (tid < BP) pixoff[tid] = tile_at;
-    // dY rows of this run, zero beyond the maps / the sample's pixels.  All of a thread's loads are issued before the
-    // halo tile is staged and stored only after it: the run costs one memory round trip, not one per eight loads
-    const T* dyn = static_cast<const T*>(a.dy) + (int64_t)n * a.m * a.P + max(pix, 0);
-    constexpr int PER = ROWS * BP / kThreads;
-    float dyv[PER];
+    inside = pix >= 0 ? 1u << 31 : 0;
+    const T* const dyn = static_cast<const T*>(a.dy) + (int64_t)n * a.m * a.P;
 #pragma unroll
-    for (int u = 0; u < PER; ++u) {
-      const int m = u * MSTEP + tid / BP;
-      const bool ok = m < a.m && pix >= 0;
-      const float t = ld(dyn + (ok ? (int64_t)m * a.P : 0));
-      dyv[u] = ok ? t : 0.f;
+    for (int u = 0; u < PER; ++u) dyv[u] = ld(dyn + ((unsigned)min(u * MSTEP + tid / BP, a.m - 1) * (unsigned)a.P + (unsigned)max(pix, 0)));
+    if (halo_ahead) {
+      const T* const xin = static_cast<const T*>(a.x) + (int64_t)n * a.c * a.h * a.w;
+#pragma unroll
+      for (int u = 0; u < HPER; ++u) {
+        const int e = tid + u * kThreads, row = e / a.wp, cl = row / a.nr;
+        const int ih = oh_first - a.ph + row - cl * a.nr, iw = e - row * a.wp - a.pw + ow_first;
+        const bool ok = e < tile_elems && (unsigned)ih < (unsigned)a.h && (unsigned)iw < (unsigned)a.w;
+        hv[u] = ld(xin + (unsigned)(ok ? (cl * a.h + ih) * a.w + iw : 0));
+        inside |= ok ? 1u << u : 0;
+      }
     }
-    stage_halo<8>(halo, static_cast<const T*>(a.x) + (int64_t)n * a.c * a.h * a.w, a.c, a.c, a.nr, a.wp, a.h, a.w,
-                  oh_first - a.ph, a.pw - ow_first, tid);
+  };
+  if (TM * TN <= 6) load_run(run0);
+  for (int run = run0; run < run1; ++run) {
+    if (TM * TN > 6) load_run(run);  // (eight accumulator tiles leave no registers for more)
+    __syncthreads();  // the previous run's MFMAs are done with the tiles
+    if (tid < BP) pixoff[tid] = tile_at;
+    if (halo_ahead) {
 #pragma unroll
-    for (int u = 0; u < PER; ++u) dyt[(u * MSTEP + tid / BP) * PITCH + pk] = dyv[u];
+      for (int u = 0; u < HPER; ++u)
+        if (tid + u * kThreads < tile_elems) halo[tid + u * kThreads] = inside >> u & 1 ? hv[u] : 0.f;
+    } else {
+      const int n = run / a.runs_per_img, tq = run - n * a.runs_per_img;
+      const int oh_first = a.tw ? tq / a.tiles_x * (BP / a.tw) : tq * BP / a.ow, ow_first = a.tw ? tq % a.tiles_x * a.tw : 0;
+      stage_halo<8>(halo, static_cast<const T*>(a.x) + (int64_t)n * a.c * a.h * a.w, a.c, a.c, a.nr, a.wp, a.h, a.w,
+                    oh_first - a.ph, a.pw - ow_first, tid);
+    }
+#pragma unroll
+    for (int u = 0; u < PER; ++u)
+      dyt[(u * MSTEP + tid / BP) * PITCH + pk] = inside >> 31 && u * MSTEP + tid / BP < a.m ? dyv[u] : 0.f;
     __syncthreads();
+    if (TM * TN <= 6 && run + 1 < run1) load_run(run + 1);
 
 #pragma unroll
     for (int g = 0; g < 4; ++g) {  // this wave's 32 pixels in groups of 8 = four MFMA steps
@@ -1242,7 +1266,7 @@ __global__ __launch_bounds__(kThreads, 2) void filter_grad_few_cols_kernel(FewCo
 }
 
 bool filter_grad_few_cols_plan(const ConvGeom& g, FewColsPlan* p) {
-  if (g.K > 128 || g.M > 64 || (int64_t)g.c * g.h * g.w > 0x7fffffffLL || g.P > 0x7fffffffLL) return false;
+  if (g.K > 128 || g.M > 64 || (int64_t)g.c * g.h * g.w > 0x7fffffffLL || g.P > (1 << 26)) return false;
   p->tm = g.M <= 32 ? 1 : 2;
   p->tn = (int)ceil_div(g.K, 32);
   int rows = (kRunPixels + g.ow - 2) / g.ow + 1;  // rows a run of consecutive pixels can touch

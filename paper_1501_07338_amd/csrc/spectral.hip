@@ -469,11 +469,20 @@ bool spectral_plan(const ConvGeom& g, int pass, size_t budget, SpectralPlan* p) 
   // No sum is longer than 32 complex products, 64 roundings of the float instruction (as one of 512, an input gradient over
   // 512 maps has an error of 4.6e-7, over 64 of 2.1e-7, the two-term product 1.9e-7): a block of an input gradient takes two
   // of them, a kernel gradient's sums are cut into slices, which the inverse transform adds in double.  A forward pass's
-  // slices would be as large as its result; its blocks take every channel, and up to 64 in one sum.
+  // slices would be as large as its result; its blocks take every channel, and up to 64 in one sum.  An input gradient over fewer
+  // maps competes with a transposed product whose own sums are shorter, and takes 16: 64 20 64 64 -> 80 16 16 1.62e-7 -> 1.37e-7, that
+  // product 1.36e-7 (200 maps 1.37e-7 against 1.53e-7; 512 maps 1.69e-7 with 32 and 683 us a layer, 1.38e-7 with 16 and 741 us).
   const int most = data || (filter && q.along) ? 64 : (filter ? 32 : 1 << 30);
   q.per_split = (int)std::min<double>(depth, most);
+  if (data) {
+    // where slices of 64 are more blocks than two for each CU, as few slices as fill those (16 38 64 64 -> 512 16 16: 792 blocks
+    // in two rounds 165 us, 495 in one 105 us)
+    const double blocks = columns * std::ceil(rows / 16) * std::ceil(cols / 16);
+    if (blocks * std::ceil(depth / 64) > 512) q.per_split = (int)(std::ceil(depth / std::max(1.0, std::floor(512 / blocks)) / 4) * 4);
+    q.per_split = (int)std::min<double>(depth, q.per_split);
+  }
   q.splits = (int)std::ceil(depth / q.per_split);
-  const int longest = q.along == 0 && pass == VCNN_PASS_FWD && g.c <= 64 ? 64 : 32;
+  const int longest = q.along == 0 && pass == VCNN_PASS_FWD && g.c <= 64 ? 64 : (q.along == 0 && data && g.k < 320 ? 16 : 32);
   q.flush = (int)(ceil_div(ceil_div(q.per_split, ceil_div(q.per_split, longest)), 4) * 4);  // in chunks of about the same size
   q.part = g.k;
   q.image_bytes = image * (data ? q.splits : 1);
@@ -501,7 +510,7 @@ bool spectral_plan(const ConvGeom& g, int pass, size_t budget, SpectralPlan* p) 
   // to begin and to end with.  (110 passes of 40 drawn layers, 44 to 861 us, take 0.75 to 1.2 times this.)
   const double parts = (double)ceil_div(g.k, q.part), e = 4, pixels = (double)g.n * ((double)g.c * g.h * g.w + (double)g.k * g.P);
   const double result = data ? (double)image : (filter ? (double)g.k * g.c * taps : (double)tiles * g.k * spectrum), flushes = std::ceil(q.per_split / (double)q.flush) - 1;
-  const double bytes = pixels * e + 2.0 * (double)(q.image_bytes + (size_t)(tiles * g.k * spectrum)) + 2.0 * flushes * result * q.splits +
+  const double bytes = pixels * e + 2.0 * (double)(q.image_bytes + (size_t)(tiles * g.k * spectrum)) + 2.0 * flushes * result * q.splits * 0.75 +
                        2.0 * (double)g.k * g.c * taps * (filter ? q.splits : 1) + (double)g.M * g.K * e;
   const double blocks = columns * std::ceil(rows / 16) * std::ceil(cols / 16) * q.splits, steps = std::ceil(q.per_split / 4.0) + 4;
   q.est_seconds = bytes / 4.4e12 + (blocks <= 256 ? 2.2e-6 : std::ceil(blocks / 512) * (data ? 3.4e-6 : 2.7e-6)) * steps + 5e-6 * (1 + (q.along ? 2 : 3) * parts);

@@ -1,0 +1,55 @@
+"""Forward pass of layers with at most four input channels, whose kernel matrix stays in registers: both types at the edges of
+its row groups, steps, pixel tiles and blocks, against the oracle, and sums that an infinity next to a window must not reach."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from paper_1501_07338_amd import vcnn
+from paper_1501_07338_amd.workloads import bf16_round, random_tensor
+from util import assert_close, to_np
+
+DEV = "cuda:0"
+# (n, c, h, w, k, r, s, pad_h, pad_w): 1..3 row groups, ragged ones, each number of steps compiled, odd and even kernel columns,
+# planes that end inside a tile, several tiles a wave and blocks an image
+SHAPES = [(1, 1, 5, 6, 5, 2, 2, 0, 0), (8, 1, 28, 28, 6, 5, 5, 0, 0), (3, 3, 17, 19, 32, 3, 3, 1, 1), (2, 4, 20, 31, 33, 4, 6, 0, 2),
+          (64, 1, 64, 64, 64, 9, 9, 4, 4), (5, 2, 40, 33, 100, 7, 5, 3, 0), (130, 1, 28, 28, 20, 5, 5, 0, 0), (1, 3, 184, 90, 31, 5, 7, 2, 3),
+          (300, 4, 12, 12, 65, 2, 3, 1, 0), (2, 1, 9, 40, 7, 9, 14, 0, 0)]
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("dtype", [vcnn.F32, vcnn.BF16])
+def test_routes(shape, dtype):
+    assert vcnn.conv_route(vcnn.conv_desc(*shape, dtype=dtype), vcnn.PASS_FWD, 0) == "first"
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("dtype", [vcnn.F32, vcnn.BF16])
+@pytest.mark.parametrize("relu", [False, True])
+def test_against_the_oracle(shape, dtype, relu):
+    n, c, h, w, k, r, s, ph, pw = shape
+    bf16 = dtype == vcnn.BF16
+    t = (random_tensor(6100, (n, c, h, w)), random_tensor(6101, (k, c, r, s), scale=(2.0 / (c * r * s)) ** 0.5))
+    x, wt = (bf16_round(a) for a in t) if bf16 else t
+    b = random_tensor(6102, (k,), scale=0.1)
+    d = vcnn.conv_desc(*shape, dtype=dtype, act=vcnn.ACT_RELU if relu else vcnn.ACT_NONE)
+    oh, ow = vcnn.conv_out_shape(d)
+    tt = torch.bfloat16 if bf16 else torch.float32
+    xd, wd = (torch.from_numpy(a).to(DEV).to(tt) for a in (x, wt))
+    y = torch.full((n, k, oh, ow), float("nan"), device=DEV).to(tt)
+    vcnn.conv_fwd(d, xd, wd, torch.from_numpy(b).to(DEV), y, None)
+    # float sums of at most 128 terms; one rounding to eight bits
+    assert_close(to_np(y.float()), O.conv_fwd(x, wt, b, pad=(ph, pw), relu=relu), 4e-3 if bf16 else 2e-6)
+    if relu:
+        return
+    at = (0, c - 1, h // 2, w // 2)
+    spoilt = x.copy()
+    spoilt[at] = np.inf
+    mark = np.zeros_like(x)
+    mark[at] = 1
+    touched = np.broadcast_to((O.conv_fwd(mark, np.ones_like(wt)[:1], np.zeros(1, np.float32), pad=(ph, pw)) != 0), y.shape)
+    got = torch.full_like(y, float("nan"))
+    vcnn.conv_fwd(d, torch.from_numpy(spoilt).to(DEV).to(tt), wd, torch.from_numpy(b).to(DEV), got, None)
+    got, base = to_np(got.float()), to_np(y.float())
+    assert np.array_equal(got[~touched], base[~touched]) and not np.any(np.isfinite(got[touched]))

@@ -25,12 +25,12 @@ SHAPES = [
     ((17, 24, 58, 60, 50, 8, 9, 0, 0), {FILTER}, False),                # odd kernel columns
     ((41, 13, 95, 41, 12, 14, 13, 1, 1), {DATA}, False),                # padded tiles
     ((5, 12, 60, 38, 98, 8, 16, 5, 11), {FWD, FILTER}, False),          # more than 64 maps; pads on one side of a tile
-    ((14, 40, 64, 64, 139, 16, 16, 0, 0), {FWD, DATA}, False),          # maps in slices, the last one short
+    ((64, 20, 64, 64, 80, 16, 16, 0, 0), {FWD, DATA}, False),           # maps in two slices, the second short
     ((40, 11, 64, 64, 150, 16, 16, 0, 0), {FILTER}, False),             # images in two slices, the second short
     ((4, 36, 98, 41, 67, 10, 15, 0, 0), {FILTER}, True),
     ((30, 29, 64, 62, 180, 16, 16, 0, 0), {FWD, FILTER}, True),
     ((16, 38, 64, 64, 512, 16, 16, 0, 0), {DATA}, True),
-    ((18, 14, 51, 48, 31, 10, 13, 9, 5), {DATA}, False),                # pads that differ
+    ((24, 29, 56, 46, 26, 16, 15, 3, 9), {DATA}, False),                # pads that differ
     # lines: along the width and the height, whole and in tiles, padded, a last pair and a last block that are not full
     ((7, 20, 42, 214, 36, 1, 100, 0, 0), {FWD, DATA}, False),
     ((1, 51, 219, 228, 48, 72, 1, 0, 0), {FWD, DATA}, False),
