@@ -109,11 +109,17 @@ def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
-def _stream(stream):
-    if stream is None:
-        import torch
+def _current_stream():
+    """The handle of torch's current stream on the current device.  Building torch's stream object takes 2.8 us, half of a
+    small call; its handle alone 0.2 us."""
+    import torch
+    if not torch.cuda.is_initialized():
         return torch.cuda.current_stream().cuda_stream
-    return getattr(stream, "cuda_stream", stream)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+
+
+def _stream(stream):
+    return _current_stream() if stream is None else getattr(stream, "cuda_stream", stream)
 
 
 def conv_desc(n, c, h, w, k, r, s, pad_h=0, pad_w=0, stride_h=1, stride_w=1, dtype=F32, act=ACT_NONE) -> ConvDesc:
