@@ -1226,42 +1226,27 @@ __global__ __launch_bounds__(kThreads, 2) void filter_grad_few_cols_kernel(FewCo
     }
   }
 
-  // add the four waves' tiles in wave order
-  float* red = reinterpret_cast<float*>(smem4);  // [TM*TN*16][64 lanes]
-#pragma unroll 1
-  for (int k = 1; k < 4; ++k) {
-    __syncthreads();
-    if (wave == k) {
-#pragma unroll
-      for (int mi = 0; mi < TM; ++mi)
-#pragma unroll
-        for (int ni = 0; ni < TN; ++ni)
-#pragma unroll
-          for (int q = 0; q < 16; ++q) red[((mi * TN + ni) * 16 + q) * 64 + lane] = acc[mi][ni][q];
-    }
-    __syncthreads();
-    if (wave == 0) {
-#pragma unroll
-      for (int mi = 0; mi < TM; ++mi)
-#pragma unroll
-        for (int ni = 0; ni < TN; ++ni)
-#pragma unroll
-          for (int q = 0; q < 16; ++q) acc[mi][ni][q] += red[((mi * TN + ni) * 16 + q) * 64 + lane];
-    }
-  }
-  if (wave != 0) return;
+  // add the four waves' tiles in wave order, tile by tile, every wave finishing and storing a quarter of the registers
+  // (one wave finishing all of them: 1 -> 64 maps 9x9 on 64x64, batch 64, forward and gradients 92.1 -> 90.9 us)
+  float* red = reinterpret_cast<float*>(smem4);  // [4 waves][16][64 lanes]
   float* dst = a.out + (int64_t)blockIdx.x * a.m * a.Kp;
 #pragma unroll
   for (int ni = 0; ni < TN; ++ni) {
     const int col = ni * 32 + l32;
-    if (col >= a.Kp) continue;
 #pragma unroll
-    for (int mi = 0; mi < TM; ++mi)
+    for (int mi = 0; mi < TM; ++mi) {
+      __syncthreads();
 #pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const int m = mi * 32 + acc_row(q, lane);
-        if (m < a.m) dst[(int64_t)m * a.Kp + col] = acc[mi][ni][q];
+      for (int q = 0; q < 16; ++q) red[(wave * 16 + q) * 64 + lane] = acc[mi][ni][q];
+      __syncthreads();
+      if (col >= a.Kp) continue;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int q = 4 * wave + u, m = mi * 32 + acc_row(q, lane);
+        const float v = ((red[q * 64 + lane] + red[(16 + q) * 64 + lane]) + red[(32 + q) * 64 + lane]) + red[(48 + q) * 64 + lane];
+        if (m < a.m) dst[(int64_t)m * a.Kp + col] = v;
       }
+    }
   }
 }
 
@@ -1282,8 +1267,7 @@ bool filter_grad_few_cols_plan(const ConvGeom& g, FewColsPlan* p) {
     if (g.s == 1) p->wp |= 1;
     p->lds_bytes = tile + kRunPixels * 4 + (size_t)g.c * p->nr * p->wp * 4;
   }
-  const size_t red = (size_t)p->tm * p->tn * 16 * 64 * 4;
-  if (red > tile || p->lds_bytes > 64 * 1024) return false;
+  if (p->lds_bytes > 64 * 1024) return false;
   p->runs_per_img = p->tw ? (int)(ceil_div(g.oh, kRunPixels / p->tw) * ceil_div(g.ow, p->tw)) : (int)ceil_div(g.P, kRunPixels);
   const int64_t total = (int64_t)g.n * p->runs_per_img;
   if (total > 0x7fffffffLL) return false;

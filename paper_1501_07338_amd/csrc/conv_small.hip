@@ -37,7 +37,7 @@ __global__ __launch_bounds__(512) void conv_small_kernel(SmallConvArgs a) {
   int* const tapoff = small_lds;                                         // [Kp]
   float* const halo = reinterpret_cast<float*>(small_lds + a.Kp);        // [c][nr][wp]
   const int plane = a.nr * a.wp;
-  float* const red = reinterpret_cast<float*>(small_lds);                // [waves - 1][16][64], reuses table + tile
+  float* const red = reinterpret_cast<float*>(small_lds);                // [waves][16][64], reuses table + tile
   const int waves = blockDim.x >> 6;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l32 = lane & 31, half = lane >> 5;
@@ -135,33 +135,26 @@ __global__ __launch_bounds__(512) void conv_small_kernel(SmallConvArgs a) {
       for (int u = 0; u < 4; ++u) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[g][u], bv[g][u], acc, 0, 0, 0);
   }
 
+  // the waves' tiles are added in wave order, every wave finishing some of the 16 accumulator registers
+  // (20 -> 50 maps 5x5 on 12x12, batch 128: 15.4 -> 15.0 us against one wave finishing them all)
+  float bq[4];  // (at least four waves)
+#pragma unroll
+  for (int u = 0; u < 4; ++u) bq[u] = a.bias ? a.bias[min(i0 + acc_row(min(wave + u * waves, 15), lane), a.m - 1)] : 0.f;
   __syncthreads();  // every wave is done with the table and the tile: their memory now takes the partial tiles
-  if (wave > 0) {
 #pragma unroll
-    for (int q = 0; q < 16; ++q) red[((wave - 1) * 16 + q) * 64 + lane] = acc[q];
-  }
+  for (int q = 0; q < 16; ++q) red[(wave * 16 + q) * 64 + lane] = acc[q];
   __syncthreads();
-  if (wave > 0) return;
-  for (int w = 0; w < waves - 1; ++w)
-#pragma unroll
-    for (int q = 0; q < 16; ++q) acc[q] += red[(w * 16 + q) * 64 + lane];
   if (p0 + l32 >= a.P) return;
   T* y = static_cast<T*>(a.y);
-  float bq[16];  // the bias of all 16 rows requested at once (clamped rows), not one wait per row
 #pragma unroll
-  for (int q = 0; q < 16; ++q) bq[q] = 0.f;
-  if (a.bias) {
-#pragma unroll
-    for (int q = 0; q < 16; ++q) bq[q] = a.bias[min(i0 + acc_row(q, lane), a.m - 1)];
-  }
-#pragma unroll
-  for (int q = 0; q < 16; ++q) {
-    const int row = i0 + acc_row(q, lane);
-    if (row < a.m) {
-      float v = acc[q] + bq[q];
-      if (a.relu) v = fmaxf(v, 0.f);
-      st(y + ((int64_t)n * a.m + row) * a.P + p, v);
-    }
+  for (int u = 0; u < 4; ++u) {
+    const int q = wave + u * waves, row = i0 + acc_row(q, lane);
+    if (q >= 16 || row >= a.m) continue;
+    float v = red[q * 64 + lane];
+    for (int w = 1; w < waves; ++w) v += red[(w * 16 + q) * 64 + lane];
+    v += bq[u];
+    if (a.relu) v = fmaxf(v, 0.f);
+    st(y + ((int64_t)n * a.m + row) * a.P + p, v);
   }
 }
 
@@ -177,7 +170,7 @@ static size_t small_lds_bytes(int c, int w, int r, int s, int ph, int pw, int64_
   *nr_out = nr, *wp_out = wp;
   const int64_t Kp = (K + 3) & ~(int64_t)3;
   const int64_t tile = ((int64_t)c * nr * wp + 3) & ~(int64_t)3;
-  return std::max((size_t)(Kp + tile) * 4, (size_t)(small_waves(K) - 1) * 16 * 64 * sizeof(float));
+  return std::max((size_t)(Kp + tile) * 4, (size_t)small_waves(K) * 16 * 64 * sizeof(float));
 }
 
 // Small enough that latency, not arithmetic, is the cost: at most 768 tiles and 2^29 multiply-adds; the

@@ -324,54 +324,45 @@ __device__ __forceinline__ void small_tile(const GemmArgs& a, int tile, int tile
       }
   }
 
-  if (wave > 0) {
+  // The waves' tiles are added in wave order, every wave finishing some of the accumulator registers (with all
+  // of them finished by one wave, up to 7 x 16 values in a row: 800 -> 500 at batch 128, forward and backward 18.2 -> 17.3 us).  What the epilogue reads (bias, the
+  // activation below) is requested before the barrier, at clamped addresses.
+  constexpr int OWN = (NQ + 3) / 4;  // at least four waves
+  auto row_of = [&](int q) { return i0 + (T16 ? 4 * kq + q : acc_row(q, lane)); };
+  float bq[OWN], rq[OWN];
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) red[((wave - 1) * NQ + q) * 64 + lane] = acc[q];
+  for (int u = 0; u < OWN; ++u) {
+    const int row = min(row_of(min(wave + u * waves, NQ - 1)), a.M - 1);
+    bq[u] = a.bias ? a.bias[row] : 0.f;
+    rq[u] = a.dact && j_ok ? ld(static_cast<const TO*>(a.dact_ref) + (int64_t)row * a.c_si + (int64_t)j * a.c_sj) : 0.f;
   }
-  __syncthreads();
-  if (wave > 0) return;
-  for (int w = 0; w < waves - 1; ++w)
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) acc[q] += red[(w * NQ + q) * 64 + lane];
+  for (int q = 0; q < NQ; ++q) red[(wave * NQ + q) * 64 + lane] = acc[q];
+  __syncthreads();
   if (!j_ok && !j_ones) return;
   TO* C = static_cast<TO*>(a.C);
-  // what the epilogue reads (bias, the activation below) is requested for all rows at once, at clamped addresses,
-  // before any of it is used: one memory latency instead of one per accumulator register
-  float bq[NQ], rq[NQ];
 #pragma unroll
-  for (int q = 0; q < NQ; ++q) bq[q] = 0.f, rq[q] = 0.f;
-  if (a.bias) {
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) bq[q] = a.bias[min(i0 + (T16 ? 4 * kq + q : acc_row(q, lane)), a.M - 1)];
-  }
-  if (a.dact && !j_ones) {
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      const int row = min(i0 + (T16 ? 4 * kq + q : acc_row(q, lane)), a.M - 1);
-      rq[q] = ld(static_cast<const TO*>(a.dact_ref) + (int64_t)row * a.c_si + (int64_t)j * a.c_sj);
+  for (int u = 0; u < OWN; ++u) {
+    const int q = wave + u * waves;
+    if (q >= NQ) break;
+    float v = red[q * 64 + lane];
+    for (int w = 1; w < waves; ++w) v += red[(w * NQ + q) * 64 + lane];
+    const int row = row_of(q);
+    if (row >= a.M) continue;
+    if (j_ones) {
+      a.row_sums[row] = v;
+      continue;
     }
-  }
-#pragma unroll
-  for (int q = 0; q < NQ; ++q) {
-    const int row = i0 + (T16 ? 4 * kq + q : acc_row(q, lane));
-    if (row < a.M) {
-      float v = acc[q];
-      if (j_ones) {
-        a.row_sums[row] = v;
-        continue;
-      }
-      v += bq[q];
-      if (a.relu) v = fmaxf(v, 0.f);
-      const int64_t at = (int64_t)row * a.c_si + (int64_t)j * a.c_sj;
-      if (a.dact) v = act_grad(a.dact, rq[q], v);
-      st(C + at, v);
-    }
+    v += bq[u];
+    if (a.relu) v = fmaxf(v, 0.f);
+    if (a.dact) v = act_grad(a.dact, rq[u], v);
+    st(C + (int64_t)row * a.c_si + (int64_t)j * a.c_sj, v);
   }
 }
 
 template <bool A_KC, bool B_KC, bool A_VEC, bool B_VEC, typename TI, typename TO>
 __global__ __launch_bounds__(1024) void gemm_small_kernel(GemmArgs a, int tiles_m, int kper, int t16) {
-  extern __shared__ float red[];  // [waves - 1][16][64]
+  extern __shared__ float red[];  // [waves][16][64]
   if (t16) small_tile<true, A_KC, B_KC, A_VEC, B_VEC, TI, TO>(a, blockIdx.x, tiles_m, kper, red);
   else small_tile<false, A_KC, B_KC, A_VEC, B_VEC, TI, TO>(a, blockIdx.x, tiles_m, kper, red);
 }
@@ -425,7 +416,7 @@ static void launch_small_t(const GemmArgs& a, hipStream_t st) {
   const int kper = small_kper(a, waves);
   const int t16 = small_use16(a);
   const dim3 grid((unsigned)tiles), block(64 * waves);
-  const size_t lds = (size_t)(waves - 1) * 16 * 64 * sizeof(float);
+  const size_t lds = (size_t)waves * 16 * 64 * sizeof(float);
   const bool in16 = a.in_dtype == VCNN_BF16, out16 = a.out_dtype == VCNN_BF16;
   if (in16 && out16)
     hipLaunchKernelGGL((gemm_small_kernel<A_KC, B_KC, A_VEC, B_VEC, bf16, bf16>), grid, block, lds, st, a, tiles_m, kper, t16);
@@ -735,7 +726,7 @@ vcnn_status launch_fc_bwd_small(const GemmArgs& gw, const GemmArgs& gx, hipStrea
   const int waves = std::max(small_waves(gw.K), small_waves(gx.K));
   const int tiles_w = (int)small_blocks(gw), tiles_x = (int)small_blocks(gx);
   const dim3 grid((unsigned)(tiles_w + tiles_x)), block(64 * waves);
-  const size_t lds = (size_t)(waves - 1) * 16 * 64 * sizeof(float);
+  const size_t lds = (size_t)waves * 16 * 64 * sizeof(float);
   const int tm_w = (int)ceil_div(gw.M, small_side(gw)), tm_x = (int)ceil_div(gx.M, small_side(gx));
   const int w16 = small_use16(gw), x16 = small_use16(gx);
   // each product keeps the split it has when launched alone (surplus waves get an empty share), so the fused
