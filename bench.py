@@ -39,6 +39,7 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0  # dense bf16 -> fp32 accumulate
 # A float product costs one multiply-add of the float instruction or three of the f16 one (two f16 terms per operand, the
 # route of the larger layers): the ceiling of the matrix cores for float products is the better of the two.
 MFMA_FLOAT_PRODUCT_PEAK_TFLOPS = max(MFMA_F32_PEAK_TFLOPS, MFMA_BF16_PEAK_TFLOPS / 3)
+SPECTRAL_TILE, SPECTRAL_LINE = 64, 256  # samples a side of a transform: planes; lines of one-row and one-column kernels
 WORKLOAD_TEXT = {
     "cfg1": "cfg1: single conv block 8x1x28x28 -> conv5x5x6 -> ReLU -> maxpool2, fwd + bwd from an upstream gradient",
     "cfg2": "cfg2: small recognition CNN, batch 128x1x28x28, conv5x5x20-pool-conv5x5x50-pool-fc500-fc10, "
@@ -204,12 +205,13 @@ def run_workload(name, steps, warmup, layer_iters=10, algos=None, phase_prefix=N
             mark(f"{phase_prefix or name}.conv{li}.{pname}")
             t = time_calls(fn, layer_iters, stream)
             mark("-")
-            peak = MFMA_BF16_PEAK_TFLOPS if bf16 else MFMA_FLOAT_PRODUCT_PEAK_TFLOPS
+            route = routed(lambda p=pname: vcnn.conv_route(d, ("fwd", "bwd_filter", "bwd_data").index(p), ts.workspace.numel()))
+            mflops, peak, spectra = matrix_work(L, g, pname, route, bf16)
             layers.append({"layer": f"conv{li}", "pass": pname, "M": g["M"], "K": g["K"], "N": g["N"], "ms": t,
+                           "route": route, "matrix_flops": mflops, "matrix_peak": peak,
                            "gflops": flops / (t * 1e6),
-                           # the bf16 variant contracts on the bf16 matrix-core instructions: priced against their peak
-                           "pct_mfma_peak": 100.0 * flops / (t * 1e9) / peak,
-                           "algorithmic_bytes": in_b + out_b + w_b, "gbs": (in_b + out_b + w_b) / (t * 1e6),
+                           "pct_mfma_peak": 100.0 * mflops / (t * 1e9) / peak,
+                           "algorithmic_bytes": in_b + out_b + w_b + spectra, "gbs": (in_b + out_b + w_b + spectra) / (t * 1e6),
                            "in_step": not (li == 0 and pname == "bwd_data")})
             if not (li == 0 and pname == "bwd_data"):
                 conv_flops += flops
@@ -217,12 +219,37 @@ def run_workload(name, steps, warmup, layer_iters=10, algos=None, phase_prefix=N
         del y_buf, dx_buf
     res["conv_layers"] = layers
     res["conv_gflops_fwd_bwd"] = conv_flops / (conv_ms * 1e6) if conv_ms else None
-    peak = MFMA_BF16_PEAK_TFLOPS if bf16 else MFMA_FLOAT_PRODUCT_PEAK_TFLOPS
-    res["conv_pct_mfma_peak"] = 100.0 * res["conv_gflops_fwd_bwd"] / (peak * 1e3) if conv_ms else None
+    # each pass's share of the peak of the instructions it contracts on, weighted by its time
+    res["conv_pct_mfma_peak"] = (sum(l["pct_mfma_peak"] * l["ms"] for l in layers if l["in_step"]) / conv_ms) if conv_ms else None
     res["roofline"] = dominant_roofline(res)
     del graph, ts
     torch.cuda.empty_cache()
     return res
+
+
+def matrix_work(L, g, pname, route, bf16):
+    """Flops a pass contracts on the matrix cores, the peak they are priced against (TFLOP/s) and the bytes of what it hands
+    from launch to launch: 2 M K N in float (two f16 terms) or bf16, nothing; through the Fourier domain one complex
+    multiply-add (8 flops) per frequency, tile and pair of channel and map, on the float instruction in either storage type,
+    and the spectra of input, output (64 x 33 values a tile, 128 a line) and kernels (16 x 33, 128), written and read."""
+    if route != "spectral":
+        return 2.0 * g["M"] * g["K"] * g["N"], MFMA_BF16_PEAK_TFLOPS if bf16 else MFMA_FLOAT_PRODUCT_PEAK_TFLOPS, 0.0
+    data = pname == "bwd_data"
+
+    def steps(size, taps, out, length):  # outputs (samples of an input gradient) a transform leaves whole
+        return math.ceil((size if data else out) / (length - taps + 1))
+
+    if L.kh == 1:  # one transform if the padded samples fit
+        count, freqs = g["oh"] * (1 if g["w"] + 2 * L.pad_w <= SPECTRAL_LINE else steps(g["w"], L.kw, g["ow"], SPECTRAL_LINE)), SPECTRAL_LINE // 2
+    elif L.kw == 1:
+        count, freqs = g["ow"] * (1 if g["h"] + 2 * L.pad_h <= SPECTRAL_LINE else steps(g["h"], L.kh, g["oh"], SPECTRAL_LINE)), SPECTRAL_LINE // 2
+    else:
+        whole = max(g["h"] + 2 * L.pad_h, g["w"] + 2 * L.pad_w) <= SPECTRAL_TILE
+        count = 1 if whole else steps(g["h"], L.kh, g["oh"], SPECTRAL_TILE) * steps(g["w"], L.kw, g["ow"], SPECTRAL_TILE)
+        freqs = SPECTRAL_TILE * (SPECTRAL_TILE // 2 + 1)
+    tap_values = freqs if min(L.kh, L.kw) == 1 else 16 * (SPECTRAL_TILE // 2 + 1)
+    spectra = 8.0 * (freqs * g["n"] * count * (g["c"] + g["M"]) + tap_values * g["c"] * g["M"])
+    return 8.0 * freqs * g["n"] * count * g["c"] * g["M"], MFMA_F32_PEAK_TFLOPS, 2.0 * spectra
 
 
 def measured_traffic(name):
@@ -242,22 +269,23 @@ def dominant_roofline(res):
     """Roofline record of the convolution pass that takes the most time inside the step.  A pass whose
     arithmetic intensity (flops over input + output + kernel bytes) is above the machine balance
     (matrix-core peak over 8 TB/s) is priced against the matrix-core peak of the instructions it contracts
-    on (float products: 833 TFLOP/s, three f16 products each at 2.5 PFLOP/s; bf16 variant: 2.5 PFLOP/s), else against HBM."""
+    on (float products: 833 TFLOP/s, three f16 products each at 2.5 PFLOP/s; bf16 variant: 2.5 PFLOP/s), else against HBM.
+    A pass through the Fourier domain does a small part of those flops: its products of spectra are priced, on the float
+    instruction they run on (157.3 TFLOP/s), and the spectra count as bytes."""
     layers = [l for l in res.get("conv_layers") or [] if l["in_step"]]
     if not layers:
         return None
     top = max(layers, key=lambda r: r["ms"])
-    flops = 2.0 * top["M"] * top["K"] * top["N"]
+    flops, peak = top["matrix_flops"], top["matrix_peak"]
     name = f"{res['workload']}.{top['layer']}.{top['pass']}"
-    peak = MFMA_BF16_PEAK_TFLOPS if res.get("storage_dtype") == "bf16" else MFMA_FLOAT_PRODUCT_PEAK_TFLOPS
     if flops / top["algorithmic_bytes"] >= peak * 1e3 / HBM_PEAK_GBS:
         ach = flops / (top["ms"] * 1e9)
         return {"kernel": name, "bound": "mfma", "achieved": ach, "peak": peak, "unit": "TFLOP/s",
-                "frac": ach / peak, "traffic": measured_traffic(name), "ms": top["ms"], "flops": flops}
+                "frac": ach / peak, "traffic": measured_traffic(name), "ms": top["ms"], "flops": flops, "route": top["route"]}
     ach = top["algorithmic_bytes"] / (top["ms"] * 1e6)
     return {"kernel": name, "bound": "hbm", "achieved": ach, "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": ach / HBM_PEAK_GBS, "traffic": measured_traffic(name), "ms": top["ms"],
-            "bytes": top["algorithmic_bytes"]}
+            "bytes": top["algorithmic_bytes"], "route": top["route"]}
 
 
 def hbm_kernels(stream):
@@ -538,7 +566,7 @@ def main():
                    "ms_per_step_median": main_res["ms_per_step_median"],
                    "timing": "each step between its own event pair on the launch stream, mean of the K steps; the seeded "
                              "parameters are restored before every step outside the pair",
-                   "float_products": "larger layers: three f16 matrix-core products per float product (each operand two f16 terms "
+                   "float_products": "large kernels: products of spectra on the float instruction (transforms in double, spectra in float); other larger layers: three f16 matrix-core products per float product (each operand two f16 terms "
                                      "scaled by powers of two, 23 bits, fp32 accumulation); others: the float instruction",
                    "loss_first_step": main_res["loss_first_step"]},
         "conv_gflops_fwd_bwd": main_res["conv_gflops_fwd_bwd"],

@@ -71,8 +71,9 @@ enum { VCNN_PASS_FWD = 0, VCNN_PASS_BWD_FILTER = 1, VCNN_PASS_BWD_DATA = 2 };
  * same scale; an image (or kernel matrix, or operand of a kernel gradient) with more than one in 8192 of its elements, or
  * 1024 of them, below that, zeros aside, or with an infinity or NaN, is computed by the float kernel instead, in its own time and that of
  * the scan.  Nothing of this decision reaches the host.
- * AUTO takes layers with large kernels (7 x 7 to 16 x 16 taps, more than 4 maps and channels, either dtype) through the
- * Fourier domain where that is faster: transforms in double, spectra and their products in float; nearer the exact sums
+ * AUTO takes layers with large kernels (49 taps or more, at most 16 a side, or 8 to 128 taps in one row or one column; more
+ * than 4 maps and channels, either dtype) through the Fourier domain where that is faster: transforms in double, spectra and
+ * their products in float; nearer the exact sums
  * than the direct routes as measured over whole results.  Its error is spread over the plane, though, so an image with a
  * window (all channels) below 2^-10 of its largest element - black areas of a kernel's size among them -, with an infinity
  * or NaN, or with magnitudes whose products leave the float range is computed by the float kernel, in its own time. */

@@ -7,7 +7,9 @@
 // l holds rows l % 32 and the contraction index 2 t + l / 32 of each step t), the input rows under the block's pixels are
 // staged once, and the waves walk their tiles of 32 pixels of one sample with no barrier: a step reads one float per lane
 // from the halo tile at lane_base(pixel) + offset(t) for TM matrix instructions, and a tile's stores leave while the next
-// tile's products run.  64 1 64 64 -> 64 9 9: 61 -> 31 us (18 us of matrix instructions, 67 MB written).
+// tile's products run.  64 1 64 64 -> 64 9 9: 61 -> 44 us (28 of them products: 18 of matrix instructions at two waves a SIMD,
+// then the stores of 67 MB and the staging of a block); 128 1 28 28 -> 20 5 5: 8 us, as before.  Halo reads a further group
+// ahead: no change; 1024 blocks: slower.
 //
 // The contraction runs over (channel, kernel row, column pairs); where the kernel has an odd number of columns the lanes of
 // the second half repeat the first half's entry in the last pair with a zero weight, so that no pixel outside an output's

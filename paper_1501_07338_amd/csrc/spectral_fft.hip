@@ -5,7 +5,8 @@
 // result.  Two real rows share one complex transform, as its real and imaginary part.  One block of 256 threads does a
 // plane: 32 pairs of rows, a transposition through LDS (one barrier on either side), 32 columns (the real columns 0 and 32
 // share one).  Double costs the vector units no more than float and the LDS traffic twice as much; the kernels are bound by
-// the memory the spectra take.
+// the memory the spectra take: 16.9 KB written (read) a plane, 8192 planes of 49 x 49 pixels (dY of 512 maps, batch 16) 67 us
+// forward and 62 back, 608 planes 11 us, 19456 kernels of 16 x 16 (row spectra, 4.2 KB each) 28 us either way.
 #include "elem.h"
 #include "spectral.h"
 #include "spectral_math.h"
