@@ -154,9 +154,10 @@ __device__ void guard_image(const GuardArgs& g, int block, uint32_t* lds) {
 // TAPS operands are the row spectra of kernels: the lane transforms the 16 rows in registers (double) to its wave's 16
 // frequencies, so that the kernels' spectra, four times as large, never reach memory; TAPS results are transformed back the
 // same way, each wave's share of the rows, added over the four waves in LDS.
-// 16 38 64 64 -> 512 16 16 does 5.3 GFLOP a pass (33 us of matrix instructions) in 107 us forward, 105 input gradient, 137
-// kernel gradient: bound by a step's chain of loads, LDS reads and the kernels' transforms at two waves a SIMD, by a block's
-// beginning and end (10 steps of four between them) and, with 1056 blocks on 512 slots, by a last round that is nearly empty.  Stored
+// 16 38 64 64 -> 512 16 16 does 5.3 GFLOP a pass (33 us of matrix instructions) in 105 us forward, 112 kernel gradient and
+// 153 input gradient (matrix cores busy 45, 43, 32 % of the cycles): bound by a step's chain of loads, LDS reads and the kernels' transforms at two waves a SIMD, by a block's
+// beginning and end (10 steps of four between them) and, with 1056 blocks on 512 slots, by a last round that is nearly empty; the
+// input gradient by 0.67 GB between the L2s and memory, half of it the sums put away and fetched again every 32 products.  Stored
 // by every lane for itself instead of through LDS, results cost 34 us more; the kernels' transform in front of the products
 // instead of between them 13.
 struct ProductArgs {
