@@ -58,7 +58,8 @@ __global__ __launch_bounds__(kThreads) void conv_first_kernel(FirstArgs a) {
   // columns -pw + [0, wp), zero outside the image.  Loads in batches: one round trip each, not one per element
   const T* const wgt = (const T*)a.wgt;
   const T* const x = (const T*)a.x + (int64_t)n * a.c * a.h * a.w;
-  constexpr int WU = 32 * TM * 2 * STEPS / kThreads, WB = WU < 12 ? WU : 12, HU = 8;
+  constexpr int WU = 32 * TM * 2 * STEPS / kThreads, WB = WU <= 12 ? WU : (WU % 12 == 0 ? 12 : 8), HU = 8;
+  static_assert(WU % WB == 0, "a batch that ran over would write rows past the matrix into the halo tile");
   const int total = a.c * a.nr * a.wp;
   auto halo_batch = [&](int e0, float (&v)[HU], unsigned& inside) {
     inside = 0;

@@ -11,10 +11,11 @@ from util import assert_close, to_np
 
 DEV = "cuda:0"
 # (n, c, h, w, k, r, s, pad_h, pad_w): 1..3 row groups, ragged ones, each number of steps compiled, odd and even kernel columns,
-# planes that end inside a tile, several tiles a wave and blocks an image
-SHAPES = [(1, 1, 5, 6, 5, 2, 2, 0, 0), (8, 1, 28, 28, 6, 5, 5, 0, 0), (3, 3, 17, 19, 32, 3, 3, 1, 1), (2, 4, 20, 31, 33, 4, 6, 0, 2),
+# planes that end inside a tile, several tiles a wave and blocks an image, more blocks than compute units
+SHAPES = [(1, 1, 5, 6, 5, 2, 2, 0, 0), (8, 1, 28, 28, 6, 5, 5, 0, 0), (3, 3, 17, 19, 32, 3, 3, 1, 1), (12, 4, 20, 31, 33, 4, 6, 0, 2),
           (64, 1, 64, 64, 64, 9, 9, 4, 4), (5, 2, 40, 33, 100, 7, 5, 3, 0), (130, 1, 28, 28, 20, 5, 5, 0, 0), (1, 3, 184, 90, 31, 5, 7, 2, 3),
-          (300, 4, 12, 12, 65, 2, 3, 1, 0), (2, 1, 9, 40, 7, 9, 14, 0, 0)]
+          (300, 4, 12, 12, 65, 2, 3, 1, 0), (260, 1, 9, 40, 7, 9, 14, 0, 0),
+          (300, 2, 17, 15, 40, 5, 5, 0, 0)]
 
 
 @pytest.mark.parametrize("shape", SHAPES)
