@@ -405,8 +405,12 @@ static Plan direct_plan(const ConvGeom& g, int pass, int dtype, size_t offered) 
       p.workspace_bytes = align256(p.partial_bytes);
     } else if (is_pointwise(g)) {
       p.path = PATH_POINTWISE;
-    } else if (automatic && g.k > 4 && conv_first_plan(g, &p.first)) {
-      p.path = PATH_FIRST;  // at most four channels: the kernel matrix in registers
+    } else if (automatic && g.k > 4 && conv_first_plan(g, &p.first) &&
+               !(p.first.steps > 32 && (int64_t)g.n * p.first.tiles_per_img * p.first.groups < 256 &&
+                 conv_small_applies(g.n, g.c, g.h, g.w, g.k, g.r, g.s, g.ph, g.pw))) {
+      // at most four channels: the kernel matrix in registers (a long contraction over few tiles is faster split over a
+      // block's waves: 3 3 15 67 -> 5 9 4 6.3 against 9.2 us, 3 3 43 16 -> 29 6 6 6.8 against 8.6)
+      p.path = PATH_FIRST;
     } else if (automatic && g.k > 4 && conv_small_applies(g.n, g.c, g.h, g.w, g.k, g.r, g.s, g.ph, g.pw)) {
       p.path = PATH_SMALL;  // a few hundred MFLOP: latency-bound, one tile per block and the contraction over its waves
     } else if (allow_direct && (g.c > 4 || g.k >= 32 || algo == VCNN_ALGO_IMPLICIT) &&

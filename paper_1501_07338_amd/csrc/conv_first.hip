@@ -168,6 +168,8 @@ bool conv_first_plan(const ConvGeom& g, FirstPlan* p) {
   const int s2 = (g.s + 1) / 2 * 2, steps = g.c * g.r * s2 / 2;
   p->tm = g.k <= 32 ? 1 : 2;
   if (steps > (p->tm == 2 ? 48 : kMaxSteps)) return false;
+  // with few tiles, 32 rows a wave and twice the waves: a wave's chain of products is half as long
+  if ((int64_t)g.n * ceil_div(g.P, 32) * ceil_div(g.k, 32) <= 1024) p->tm = 1;
   p->steps = steps <= 16 ? 16 : (steps <= 32 ? 32 : (steps <= 48 ? 48 : 64));
   p->groups = (int)ceil_div(g.k, 32 * p->tm);
   p->tiles_per_img = (int)ceil_div(g.P, 32);
@@ -176,6 +178,7 @@ bool conv_first_plan(const ConvGeom& g, FirstPlan* p) {
   // two blocks for each of 256 CUs where there is that much to do: what a block stages serves several tiles of each wave
   p->tiles_per_wave = (int)std::min<int64_t>(ceil_div(tiles, 4 * 512), 16);
   p->blocks_per_img = (int)ceil_div(p->tiles_per_img, 4 * p->tiles_per_wave);
+  p->tiles_per_wave = (int)ceil_div(p->tiles_per_img, 4 * p->blocks_per_img);  // (an image's blocks alike)
   const int pixels = 128 * p->tiles_per_wave;
   p->nr = std::min(g.oh, (pixels + g.ow - 2) / g.ow + 1) + g.r - 1, p->wp = g.w + 2 * g.pw;
   const int64_t halo = (int64_t)g.c * p->nr * p->wp;

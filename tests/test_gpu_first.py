@@ -24,6 +24,12 @@ def test_routes(shape, dtype):
     assert vcnn.conv_route(vcnn.conv_desc(*shape, dtype=dtype), vcnn.PASS_FWD, 0) == "first"
 
 
+@pytest.mark.parametrize("n,route", [(3, "small"), (18, "small"), (19, "first")])
+def test_long_contractions_over_few_tiles_stay(n, route):
+    # 54 pairs of taps; 14 tiles an image
+    assert vcnn.conv_route(vcnn.conv_desc(n, 3, 15, 67, 5, 9, 4, 0, 0), vcnn.PASS_FWD, 0) == route
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("shape", SHAPES)
 @pytest.mark.parametrize("dtype", [vcnn.F32, vcnn.BF16])
