@@ -377,6 +377,11 @@ __global__ __launch_bounds__(kThreads) void taps_inverse_kernel(const float2* __
 
 // ---- lines -------------------------------------------------------------------------------------------------------
 // 256 points as 16 x 16: sixteen threads a transform, two real lines each; 32 lines a block.
+//
+// The two lines of a transform may belong to two images, channels or maps of any magnitudes, and double keeps 53 bits of
+// the larger one: each is scaled by a power of two to its own largest value first (exactly, and back as exactly), so that
+// nothing of one shows in the other's spectrum; a line with an infinity or NaN takes part as zeros (its image, or the whole
+// kernel gradient, is declined).
 // e^(-2 pi i j / 256), j < 16
 __device__ const cd kRoot256[16] = {{1.0, -0.0},
                                     {0.99969881869620422012, -0.02454122852291228803},
@@ -442,6 +447,7 @@ template <typename T>
 __global__ __launch_bounds__(kThreads) void line_spectra_kernel(LineArgs args) {
   __shared__ cd z[16 * 256];
   __shared__ int plane_of[32];
+  __shared__ double unscale_of[32];
   const int tid = threadIdx.x, j = tid & 15, q = tid >> 4;
   if (blockIdx.x == 0)
     for (int i = tid; i < args.cleared; i += kThreads) args.words[i] = 0;
@@ -452,6 +458,8 @@ __global__ __launch_bounds__(kThreads) void line_spectra_kernel(LineArgs args) {
   cd v[16];
   float f[2][16];
   Line l[2];
+  double scale[2], spoilt_sum[2] = {0, 0};
+  bool spoilt[2];
 #pragma unroll
   for (int half = 0; half < 2; ++half) {
     l[half] = line_of(t, min(first + half, lines - 1));
@@ -475,24 +483,41 @@ __global__ __launch_bounds__(kThreads) void line_spectra_kernel(LineArgs args) {
       if (!(x >= left && x < right)) f[half][i] = 0.f;
       m[i] = __float_as_uint(f[half][i]) & 0x7fffffffu;
     }
-    if (a.cells) {  // cell i: samples 16 i to 16 i + 15
-      keep_half<kMirror16, 8>(m, j & 8, b);
-      keep_half<kMirror8, 4>(b, j & 4, c);
-      keep_half<kSwap2, 2>(c, j & 2, e);
-      keep_half<kSwap1, 1>(e, j & 1, &largest);
+    // cell i: samples 16 i to 16 i + 15
+    keep_half<kMirror16, 8>(m, j & 8, b);
+    keep_half<kMirror8, 4>(b, j & 4, c);
+    keep_half<kSwap2, 2>(c, j & 2, e);
+    keep_half<kSwap1, 1>(e, j & 1, &largest);
+    uint32_t top = largest;  // of the line
+    top = max(top, moved<kMirror16>(top));
+    top = max(top, moved<kMirror8>(top));
+    top = max(top, moved<kSwap2>(top));
+    top = max(top, moved<kSwap1>(top));
+    if (a.cells) {
       if (a.whole) {
-        largest = max(largest, moved<kMirror16>(largest));
-        largest = max(largest, moved<kMirror8>(largest));
-        largest = max(largest, moved<kSwap2>(largest));
-        largest = max(largest, moved<kSwap1>(largest));
-        if (first + half < lines && j == 0) a.cells[l[half].cell] = largest;
+        if (first + half < lines && j == 0) a.cells[l[half].cell] = top;
       } else if (first + half < lines) {
         a.cells[l[half].cell * 16 + j] = largest;
       }
     }
+    const bool finite = top < 0x7f800000u;
+    spoilt[half] = !finite;
+    if (a.sums && __any(!finite)) {  // the sum of such a line as it is
+      double sum = 0;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) sum += (double)f[half][i];
+#pragma unroll
+      for (int d = 8; d > 0; d >>= 1) sum += __shfl_xor(sum, d);
+      spoilt_sum[half] = sum;
+    }
+    const int exponent = max((int)(top >> 23), 1) - 127;
+    scale[half] = ldexp(1.0, -exponent);
+    if (j == half) unscale_of[2 * q + half] = top == 0 || !finite ? 0.0 : ldexp(1.0, exponent);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) f[half][i] = finite ? f[half][i] : 0.f;
   }
 #pragma unroll
-  for (int i = 0; i < 16; ++i) v[i] = {(double)f[0][i], (double)f[1][i]};
+  for (int i = 0; i < 16; ++i) v[i] = {(double)f[0][i] * scale[0], (double)f[1][i] * scale[1]};
   cd* const row = z + q * 256;
   dft16<false>(v);
   twiddle(v, kRoot256[j]);
@@ -500,18 +525,19 @@ __global__ __launch_bounds__(kThreads) void line_spectra_kernel(LineArgs args) {
   dft16<false>(v);
 #pragma unroll
   for (int k = 0; k < 16; ++k) row[j + 16 * k] = v[k];
-  if (a.sums && j == 0) {  // (additions only, also where an element is not finite)
-    if (first < lines) a.sums[l[0].cell] = v[0].x;
-    if (first + 1 < lines) a.sums[l[1].cell] = v[0].y;
-  }
   __syncthreads();
+  if (a.sums && j == 0) {
+    if (first < lines) a.sums[l[0].cell] = spoilt[0] ? spoilt_sum[0] : v[0].x * unscale_of[2 * q];
+    if (first + 1 < lines) a.sums[l[1].cell] = spoilt[1] ? spoilt_sum[1] : v[0].y * unscale_of[2 * q + 1];
+  }
   const int slot = tid & 127;
 #pragma unroll 2
   for (int m = 0; m < 8; ++m) {
     const int tr = (tid >> 7) + 2 * m;
     const cd A = z[tr * 256 + slot], B = z[tr * 256 + (slot == 0 ? 128 : 256 - slot)];
-    const float2 lower = slot == 0 ? make_float2((float)A.x, (float)B.x) : make_float2((float)(0.5 * (A.x + B.x)), (float)(0.5 * (A.y - B.y)));
-    const float2 upper = slot == 0 ? make_float2((float)A.y, (float)B.y) : make_float2((float)(0.5 * (A.y + B.y)), (float)(0.5 * (B.x - A.x)));
+    const double ua = unscale_of[2 * tr], ub = unscale_of[2 * tr + 1], ha = 0.5 * ua, hb = 0.5 * ub;
+    const float2 lower = slot == 0 ? make_float2((float)(ua * A.x), (float)(ua * B.x)) : make_float2((float)(ha * (A.x + B.x)), (float)(ha * (A.y - B.y)));
+    const float2 upper = slot == 0 ? make_float2((float)(ub * A.y), (float)(ub * B.y)) : make_float2((float)(hb * (A.y + B.y)), (float)(hb * (B.x - A.x)));
     const int id = block * 32 + 2 * tr;
     if (id < lines) a.spectra[((slot >> 6) * a.planes + plane_of[2 * tr]) * 64 + (slot & 63)] = lower;
     if (id + 1 < lines) a.spectra[((slot >> 6) * a.planes + plane_of[2 * tr + 1]) * 64 + (slot & 63)] = upper;
@@ -538,27 +564,51 @@ __global__ __launch_bounds__(kThreads) void line_inverse_kernel(LineInverseArgs 
   const SpectralLines& t = a.t;
   if ((int)blockIdx.x >= a.blocks) return add_sums(a.sums, a.sum_planes, a.maps, ((int)blockIdx.x - a.blocks) * 4 + (tid >> 6), a.db);
   __shared__ int plane_of[32];
+  __shared__ uint32_t top_of[4][16];
   const int lines = (int)a.lines;
   if (tid < 32) plane_of[tid] = (int)line_of(t, min((int)blockIdx.x * 32 + tid, lines - 1)).plane;
   __syncthreads();
   const int slot = tid & 127;
-#pragma unroll 4
+  cd A[8], B[8];  // of the lines 2 tr and 2 tr + 1, tr = tid / 128 + 2 m
+#pragma unroll
+  for (int m = 0; m < 8; ++m) A[m] = B[m] = {0, 0};
+  for (int s = 0; s < a.slices; ++s)
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+      const int tr = (tid >> 7) + 2 * m;
+      const float2* const in = a.spectra + s * a.slice + (slot >> 6) * a.planes * 64 + (slot & 63);
+      const float2 f = in[(int64_t)plane_of[2 * tr] * 64], g = in[(int64_t)plane_of[2 * tr + 1] * 64];
+      A[m] = A[m] + cd{(double)f.x, (double)f.y}, B[m] = B[m] + cd{(double)g.x, (double)g.y};
+    }
+  {  // the largest value of each line, as the upper half of a double: half a line a wave, lane 2 m + half has that one's
+    auto high = [](cd f) { return max((uint32_t)__double2hiint(f.x) & 0x7fffffffu, (uint32_t)__double2hiint(f.y) & 0x7fffffffu); };
+    uint32_t t[16], b[8], c[4], e[2], top;
+#pragma unroll
+    for (int m = 0; m < 8; ++m) t[2 * m] = high(A[m]), t[2 * m + 1] = high(B[m]);
+    keep_half<kMirror16, 8>(t, tid & 8, b);
+    keep_half<kMirror8, 4>(b, tid & 4, c);
+    keep_half<kSwap2, 2>(c, tid & 2, e);
+    keep_half<kSwap1, 1>(e, tid & 1, &top);
+    top = max(top, (uint32_t)__shfl_xor((int)top, 16));
+    top = max(top, (uint32_t)__shfl_xor((int)top, 32));
+    if ((tid & 63) < 16) top_of[tid >> 6][tid & 15] = top;
+  }
+  __syncthreads();
+  auto top = [&](int tr, int half) { return max(top_of[2 * (tr & 1)][(tr & ~1) + half], top_of[2 * (tr & 1) + 1][(tr & ~1) + half]); };
+  auto finite = [&](uint32_t high) { return high < 0x7ff00000u; };
+  auto exponent = [&](uint32_t high) { return (int)(high >> 20) - 1023; };  // (sums of floats: never that of a denormal double)
+#pragma unroll
   for (int m = 0; m < 8; ++m) {
     const int tr = (tid >> 7) + 2 * m;
-    const float2* in[2];
-#pragma unroll
-    for (int half = 0; half < 2; ++half) in[half] = a.spectra + ((slot >> 6) * a.planes + plane_of[2 * tr + half]) * 64 + (slot & 63);
-    cd A{0, 0}, B{0, 0};
-    for (int s = 0; s < a.slices; ++s) {
-      const float2 f = in[0][s * a.slice], g = in[1][s * a.slice];
-      A = A + cd{(double)f.x, (double)f.y}, B = B + cd{(double)g.x, (double)g.y};
-    }
+    const uint32_t ta = top(tr, 0), tb = top(tr, 1);
+    const double sa = ta ? ldexp(1.0, -exponent(ta)) : 0.0, sb = tb ? ldexp(1.0, -exponent(tb)) : 0.0;
+    const cd lower = finite(ta) ? cd{sa * A[m].x, sa * A[m].y} : cd{0, 0}, upper = finite(tb) ? cd{sb * B[m].x, sb * B[m].y} : cd{0, 0};
     cd* const row = z + tr * 256;
     if (slot == 0) {
-      row[0] = {A.x, B.x}, row[128] = {A.y, B.y};
+      row[0] = {lower.x, upper.x}, row[128] = {lower.y, upper.y};
     } else {
-      row[slot] = {A.x - B.y, A.y + B.x};
-      row[256 - slot] = {A.x + B.y, B.x - A.y};
+      row[slot] = {lower.x - upper.y, lower.y + upper.x};
+      row[256 - slot] = {lower.x + upper.y, upper.x - lower.y};
     }
   }
   __syncthreads();
@@ -577,11 +627,13 @@ __global__ __launch_bounds__(kThreads) void line_inverse_kernel(LineInverseArgs 
     const Line l = line_of(t, id);
     T* const dst = (T*)a.dst + l.at;
     const float bias = a.bias ? a.bias[l.channel] : 0.f;
+    const uint32_t high = top(q, half);
+    const double unscale = high && finite(high) ? ldexp(1.0 / 256, exponent(high)) : 0.0;
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       const int lx = j + 16 * i - t.x0, x = l.start + lx;
       if (lx < 0 || lx >= t.lim || x >= t.len) continue;
-      float r = (float)((half ? v[i].y : v[i].x) * (1.0 / 256) + (double)bias);
+      float r = (float)((half ? v[i].y : v[i].x) * unscale + (double)bias);
       if (a.relu) r = fmaxf(r, 0.f);
       st(dst + (int64_t)x * t.s_along, r);
     }

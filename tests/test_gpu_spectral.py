@@ -47,6 +47,8 @@ ONE_EACH = [((9, 22, 70, 70, 49, 16, 16, 0, 0), FWD, False), ((27, 28, 64, 64, 2
             ((50, 55, 10, 128, 12, 1, 97, 0, 84), DATA, False), ((4, 70, 217, 8, 189, 100, 1, 0, 0), FILTER, False),
             ((30, 29, 64, 62, 180, 16, 16, 0, 0), FWD, True), ((16, 38, 64, 64, 512, 16, 16, 0, 0), DATA, True),
             ((30, 29, 64, 62, 180, 16, 16, 0, 0), FILTER, True), ((7, 38, 227, 28, 43, 100, 1, 60, 0), FWD, True)]
+# lines in odd numbers an image (channels times rows, and maps times rows): a transform's two lines belong to two images
+ODD_LINES = [((7, 21, 43, 214, 37, 1, 100, 0, 0), FWD), ((7, 21, 43, 214, 37, 1, 100, 0, 0), DATA), ((6, 55, 261, 9, 59, 95, 1, 86, 0), DATA)]
 
 
 def desc(shape, bf16=False):
@@ -165,7 +167,7 @@ def test_against_the_oracle(shape, passes, bf16):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("shape,which", [t[:2] for t in ONE_EACH if t[1] != FILTER and not t[2]])
+@pytest.mark.parametrize("shape,which", [t[:2] for t in ONE_EACH if t[1] != FILTER and not t[2]] + ODD_LINES)
 def test_an_image_does_not_depend_on_its_neighbours(shape, which):
     """Bit for bit, whatever the magnitudes of the other images, also where one of those is not finite."""
     d, x, wt, b, dy = tensors(shape, 5200)
@@ -179,6 +181,32 @@ def test_an_image_does_not_depend_on_its_neighbours(shape, which):
         others = np.arange(d.n) != 1
         assert np.array_equal(got[others], base[others])
         assert np.isfinite(big) or not np.all(np.isfinite(got[1]))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,which", ODD_LINES + [((5, 71, 217, 9, 189, 100, 1, 0, 0), FILTER), ((11, 11, 69, 64, 60, 11, 15, 0, 0), FILTER),
+                                                     ((9, 22, 70, 70, 49, 16, 16, 0, 0), FWD)])
+def test_magnitudes_do_not_mix(shape, which):
+    """Powers of two on lines, channels and maps pass through unrounded, whatever the magnitudes beside them: twice a line is
+    twice its result, and a channel scaled against its kernels changes nothing."""
+    d, x, wt, b, dy = tensors(shape, 5250)
+    assert route(d, which) == "spectral"
+    b = np.zeros_like(b)
+    base = run_pass(d, which, x, wt, b, dy)
+    rng = np.random.default_rng(7)
+    power = lambda *size: np.float32(2.0) ** rng.integers(-12, 13, size).astype(np.float32)
+    c, k = power(1, d.c, 1, 1), power(d.k, 1, 1, 1)
+    if which == FILTER:
+        got = run_pass(d, which, x * c, wt, b, dy * k.reshape(1, -1, 1, 1))
+        assert np.array_equal(got[0], base[0] * c * k) and np.array_equal(got[1], base[1] * k.ravel())
+        return
+    lines = power(d.n, 1, d.h if d.r == 1 else 1, d.w if d.s == 1 else 1)  # (planes: one of each image)
+    if which == FWD:
+        got = run_pass(d, which, x * c * lines, wt / c * k, b, dy)
+        assert np.array_equal(got, base * lines * k.reshape(1, -1, 1, 1))
+    else:
+        got = run_pass(d, which, x, wt / k * c, b, dy * lines * k.reshape(1, -1, 1, 1))
+        assert np.array_equal(got, base * lines * c)
 
 
 @pytest.mark.gpu
