@@ -73,10 +73,13 @@ enum { VCNN_PASS_FWD = 0, VCNN_PASS_BWD_FILTER = 1, VCNN_PASS_BWD_DATA = 2 };
  * the scan.  Nothing of this decision reaches the host.
  * AUTO takes layers with large kernels (49 taps or more, at most 16 a side, or 8 to 128 taps in one row or one column; more
  * than 4 maps and channels, either dtype) through the Fourier domain where that is faster: transforms in double, spectra and
- * their products in float; nearer the exact sums
- * than the direct routes as measured over whole results.  Its error is spread over the plane, though, so an image with a
- * window (all channels) below 2^-10 of its largest element - black areas of a kernel's size among them -, with an infinity
- * or NaN, or with magnitudes whose products leave the float range is computed by the float kernel, in its own time. */
+ * their products in float; nearer the exact sums than the direct routes as measured over whole results.  Its error is spread
+ * evenly over a transform (a tile of 64 x 64 pixels, or 256 of a line), though.  So an output of a forward pass or input
+ * gradient whose window holds only zeros is exactly zero (plus its bias), and an image with an output whose window - its own,
+ * clipped at the border - has less than 1/16 of the root mean square of its transform (over all channels; or in all less
+ * than a quarter of the norm of one average pixel; in bfloat16 1/32 of either), with an infinity or NaN, or with magnitudes
+ * whose products leave the float range is computed by the float kernel, in its own time.  The error of an output is then a few
+ * 1e-7 times the norm of what its window holds times that of its kernel (4e-6 at most). */
 enum { VCNN_ALGO_AUTO = 0, VCNN_ALGO_EXPLICIT = 1, VCNN_ALGO_IMPLICIT = 2, VCNN_ALGO_FOLD = 3, VCNN_ALGO_FFT = 4,
        VCNN_ALGO_SPLIT = 5 };
 

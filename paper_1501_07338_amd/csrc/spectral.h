@@ -11,10 +11,11 @@
 // Precision.  The transforms run in double (the vector units do a double as fast as a float), spectra are stored as float,
 // and the products add in float on the matrix cores over the channels (maps, images) only.  What is rounded to float is
 // each spectrum once (rows of a kernel once more) and the short sums, so the result lies nearer the 64-bit one than that of
-// the direct kernels, whose sums run over channels times taps.  The error is spread over a whole plane, though: an output
-// whose window holds only elements far below the plane's largest would lose what the direct sum keeps.  Images with such a
-// window, with magnitudes whose products leave the range of a float, or with an infinity or NaN are DECLINED on the device
-// and computed by the direct float kernel enqueued behind (which otherwise leaves at once).
+// the direct kernels, whose sums run over channels times taps.  The error is spread evenly over a transform, though, whatever
+// the samples under an output's window: outputs whose window holds nothing but zeros are put to zero exactly, and an image with
+// an output that sums too little of its transform's energy for that error (kDark...), with magnitudes whose products leave
+// the range of a float, or with an infinity or NaN is DECLINED on the device (spectral_guard.hip) and computed by the
+// direct route enqueued behind, which otherwise leaves at once.
 #pragma once
 #include "common.h"
 
@@ -32,6 +33,12 @@ static constexpr int kLL = 256, kLV = 2, kLineTaps = 128;  // lines: length, col
 static constexpr int kFCells = 32;    // cells of 8 x 16 pixels of a plane
 // A window (in whole cells) darker than this share of its tile's largest element declines the image.
 static constexpr float kDarkWindow = 1.f / 1024;
+// A forward pass or input gradient declines an image where an output's window has, per sample of it, less energy (sum of squares
+// over the channels) than this share of the mean over its transform, or in all less than that share of one mean sample: an
+// error of some 1e-7 of the transform's mean output is then at most 16 times that of the output's own scale (short windows at
+// the border of an input gradient: 4 sqrt(taps) times).
+static constexpr double kDarkMean = 1.0 / 256, kDarkLeast = 1.0 / 16;
+static constexpr double kDarkBf16 = 1.0 / 1024;  // of those, where the result is rounded to eight bits: 32 times the error
 
 struct SpectralPlan {
   int along;               // 0: planes; kernels of one row (1) or one column (2): lines along the width or the height
@@ -43,7 +50,7 @@ struct SpectralPlan {
   size_t image_bytes;      // spectra over the input channels (input gradient: one slice per split)
   size_t map_bytes;        // spectra over the output maps (of a part)
   size_t taps_bytes;       // row spectra of the kernels (of a part; kernel gradient: one slice per split)
-  size_t words_bytes;      // maxima, sums and Declined
+  size_t words_bytes;      // energies, masks, maxima, sums and Declined
   size_t workspace_bytes;
   double est_seconds;
 };
@@ -66,14 +73,20 @@ struct SpectralTiles {
   int tiles_y, tiles_x, step_y, step_x, y0, x0, lim_y, lim_x;
   int64_t planes() const { return (int64_t)images * tiles_y * tiles_x * count; }
 };
-// Also leaves each plane's largest magnitude per cell of 8 x 16 pixels (cells, float bits), its sum (sums, nullable), and
-// zeros in `cleared` words.
+// Also leaves each plane's largest magnitude per cell of 8 x 16 pixels (cells, float bits, nullable), its sum (sums, nullable),
+// and zeros in `cleared` words.  Images declined (nullable) are left out.
 vcnn_status launch_plane_spectra(const SpectralTiles& t, int dtype, const void* src, float2* spectra, uint32_t* cells,
-                                 double* sums, uint32_t* words, int cleared, hipStream_t st);
+                                 double* sums, uint32_t* words, int cleared, const uint32_t* declined, hipStream_t st);
+// What an inverse transform does not write, and what it writes as zero (both nullable).
+struct SpectralExcept {
+  const uint32_t* declined;  // [image]
+  const uint64_t* zero;      // a bit for each sample of a transform: [tile][64 rows], [line][4] ...
+  const uint32_t* zeros;     // ... where this is set
+};
 // The spectra of planes back to pixels: pixel (y, x) of tile (ty, tx) is (ty step_y + y, tx step_x + x) of the plane and lies
 // at (y + y0, x + x0) of the transform; `slices` spectra of a plane, `slice` complex values apart, are added first; bias per channel, nullable.
 vcnn_status launch_plane_inverse(const SpectralTiles& t, int dtype, const float2* spectra, int64_t slice, int slices, void* dst,
-                                 const float* bias, int relu, hipStream_t st);
+                                 const float* bias, int relu, const SpectralExcept& except, hipStream_t st);
 // Row spectra of kernels of r x s taps: [v][kernel][16 rows]; largest magnitude of each four kernels.
 vcnn_status launch_taps_spectra(int dtype, const void* w, int64_t kernels, int r, int s, float2* spectra, uint32_t* largest,
                                 hipStream_t st);
@@ -104,6 +117,33 @@ struct LineJob {
 vcnn_status launch_line_spectra(int dtype, const LineJob& first, const LineJob& second, uint32_t* words, int cleared, hipStream_t st);
 vcnn_status launch_line_inverse(const SpectralLines& t, int64_t planes, int dtype, const float2* spectra, int64_t slice, int slices,
                                 void* dst, const float* bias, int relu, const double* sums, int sum_planes, int maps, float* db,
-                                hipStream_t st);
+                                const SpectralExcept& except, hipStream_t st);
+
+// ---- spectral_guard.hip ---------------------------------------------------------------------------------------------
+struct SpectralWords {  // cleared by launch_energies: 64 words and one for each image
+  uint32_t* any;
+  uint32_t* zeros;  // an output's window holds only zeros
+  uint32_t* image;
+};
+struct EnergyJob {
+  const void* src;  // [image][channels][pixels]
+  int channels;
+  int64_t pixels;
+  double* energy;   // [image][pixels]: the sum of the squares over the channels
+};
+// (the second may have no pixels)
+vcnn_status launch_energies(int dtype, int images, const EnergyJob& first, const EnergyJob& second, uint32_t* words, int cleared,
+                            hipStream_t st);
+struct WindowGuard {
+  const double* energy;
+  int back;            // the window of transform sample i: samples i and on (0), i and before (1)
+  double mean, least;  // the least an output may sum, of its transform's energy: for each sample of its window, in all
+  uint64_t* zero;      // left for the inverse transform
+  double* totals;      // left for the guard of magnitudes: the energy of each transform
+  SpectralWords words;
+};
+// in: the transforms of the operand with the energies; out: the outputs that the inverse transform keeps of them.
+vcnn_status launch_guard_planes(const WindowGuard& g, const SpectralTiles& in, const SpectralTiles& out, int r, int s, hipStream_t st);
+vcnn_status launch_guard_lines(const WindowGuard& g, const SpectralLines& in, const SpectralLines& out, int taps, hipStream_t st);
 
 }  // namespace vcnn

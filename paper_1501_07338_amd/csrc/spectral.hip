@@ -50,8 +50,6 @@ struct GuardArgs {
   int planes[2], tiles_y, tiles_x, images;
   int step_y, step_x, y0, x0, h, w, lim_y, lim_x;  // of the first operand's tiles
   int win_y, win_x;          // cells a window covers
-  const uint32_t* largest;   // of the kernels (nullable)
-  int64_t largest_count;
   int grow;                  // bits a sum of products may gain
   uint32_t* any;
   uint32_t* image;
@@ -126,14 +124,11 @@ __device__ void guard_image(const GuardArgs& g, int block, uint32_t* lds) {
       __syncthreads();
     }
   }
-  if (g.cells[1]) {
+  {
     const int tiles = g.line_groups ? g.line_groups * 16 : g.tiles_y * g.tiles_x * kFCells;
     const uint32_t* c = g.cells[1] + (int64_t)n * tiles * g.planes[1] + first;
 #pragma unroll 8
     for (int i = tid; i < share; i += kThreads) other = max(other, c[i]);
-  } else {
-#pragma unroll 8
-    for (int i = tid; i < (int)g.largest_count; i += kThreads) other = max(other, g.largest[i]);
   }
   most = block_max(most, lds);
   other = block_max(other, lds);
@@ -142,6 +137,40 @@ __device__ void guard_image(const GuardArgs& g, int block, uint32_t* lds) {
   bad |= ea == 128 || eb == 128;  // infinity or NaN
   if (most && other) bad |= ea + eb + 24 + g.grow > 126 || ea > 110 || eb > 110 || ea + eb < -80 || ea < -90 || eb < -90;
   if (__syncthreads_or(bad) && tid == 0) atomicOr(g.image + n, 1u), atomicOr(g.any, 1u);
+}
+
+// What the magnitudes of a forward pass's or input gradient's operands decline, an image each block: of the image the energies that
+// the guard of windows left, of the kernels the largest element of each few.
+struct RangeArgs {
+  SpectralWords words;
+  const double* totals;     // [image][transform]
+  int transforms;
+  const uint32_t* largest;
+  int largest_count;
+  int grow;   // bits a sum of products may gain
+  int depth;  // bits of the root of the number of channels (maps) added
+};
+__device__ void guard_range(const RangeArgs& g, int n, uint32_t* lds) {
+  // (upper halves of doubles, none negative: ordered as integers)
+  uint32_t most = 0, high = 0, low = 0;
+#pragma unroll 8
+  for (int i = threadIdx.x; i < g.largest_count; i += kThreads) most = max(most, g.largest[i]);
+#pragma unroll 4
+  for (int i = threadIdx.x; i < g.transforms; i += kThreads) {
+    const uint32_t t = (uint32_t)__double2hiint(g.totals[(int64_t)n * g.transforms + i]);
+    high = max(high, t), low = max(low, t ? ~t : 0u);
+  }
+  most = block_max(most, lds), high = block_max(high, lds), low = ~block_max(low, lds);
+  const int eb = (int)(most >> 23) - 127;
+  bool bad = eb == 128;  // infinity or NaN
+  if (most && high) {
+    // Norms of transforms (the root of the energy): below 2^top, 2^bottom or more.  A transform of 4096 samples gains 12 bits over
+    // its largest, one of a kernel as many; a channel of them all alike has to stay far from the least float, and its product too.
+    const int top = (((int)(high >> 20) - 1023) >> 1) + 1, bottom = ((int)(low >> 20) - 1023) >> 1;
+    bad |= top + eb + 24 + g.grow > 126 || top > 110 || eb > 110;
+    bad |= bottom - g.depth + eb < -80 || bottom - g.depth < -90 || eb < -90;
+  }
+  if (bad && threadIdx.x == 0) g.words.image[n] = 1, *g.words.any = 1;
 }
 
 // ---- products of spectra -------------------------------------------------------------------------------------------
@@ -172,15 +201,26 @@ struct ProductArgs {
   int flush;                                     // (spectra as results) so many products are added in a row, then to C
   int rows_inner;                                // tiles of rows follow each other (the columns' operand is the larger one)
   int blocks;                                    // of products; further blocks look for what is declined
-  GuardArgs guard;
+  GuardArgs guard;                               // (kernel gradient)
+  RangeArgs range;                               // (the others)
+  int col_images;                                // (the others) columns of one image
 };
+// Whether all images of a block's 16 columns are declined.
+__device__ __forceinline__ bool leave_columns(const ProductArgs& a, int tc) {
+  if (!a.range.words.any || !*a.range.words.any) return false;
+  const int col = min(tc * 16 + ((int)threadIdx.x & 15), a.cols - 1);
+  return __all(a.range.words.image[col / a.col_images] != 0);
+}
 
 __device__ __forceinline__ float4 add4(float4 a, float4 b) { return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w); }
 
 template <bool TAPS_A, bool CONJ_A, bool TAPS_C, bool LINES>
 __global__ __launch_bounds__(kThreads, 2) void spectral_product_kernel(ProductArgs a) {
   __shared__ __attribute__((aligned(128))) uint4 lds[4][1024];
-  if ((int)blockIdx.x >= a.blocks) return guard_image(a.guard, blockIdx.x - a.blocks, reinterpret_cast<uint32_t*>(&lds[0][0]));
+  if ((int)blockIdx.x >= a.blocks) {
+    uint32_t* const words = reinterpret_cast<uint32_t*>(&lds[0][0]);
+    return a.range.words.any ? guard_range(a.range, blockIdx.x - a.blocks, words) : guard_image(a.guard, blockIdx.x - a.blocks, words);
+  }
   const int tid = threadIdx.x, lane = tid & 63, rho = __builtin_amdgcn_readfirstlane(tid >> 6);
   // blocks that share the larger operand's planes one after the other on the same XCD (blocks are dealt to the eight in turn)
   int id = blockIdx.x;
@@ -191,6 +231,7 @@ __global__ __launch_bounds__(kThreads, 2) void spectral_product_kernel(ProductAr
   const int inner = a.rows_inner ? a.tiles_r : a.tiles_c, outer = a.rows_inner ? a.tiles_c : a.tiles_r;
   const int ti = id % inner, to = id / inner % outer;
   const int tr = a.rows_inner ? ti : to, tc = a.rows_inner ? to : ti;
+  if (leave_columns(a, tc)) return;
   id /= inner * outer;
   const int split = id % a.splits, v = id / a.splits;
   const int z_begin = split * a.per_split, z_end = min(a.depth, z_begin + a.per_split);
@@ -405,8 +446,8 @@ static size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 namespace {
 struct Layout {  // of the workspace
-  size_t image, map, taps, words;          // offsets
-  size_t cells_image, cells_map, largest, sums;  // inside words
+  size_t image, map, taps, words, energy;  // offsets
+  size_t zero, totals, cells_image, cells_map, largest, sums;  // inside words
 };
 }  // namespace
 
@@ -426,12 +467,22 @@ static size_t lay_out(const ConvGeom& g, int pass, const SpectralPlan& p, Layout
   l->taps = l->map + p.map_bytes;
   l->words = l->taps + p.taps_bytes;
   size_t at = l->words + align256(256 + 4 * (size_t)g.n);
-  l->cells_image = at;
-  if (pass != VCNN_PASS_BWD_DATA) at += align256((size_t)tiles * g.c * cells);
-  l->cells_map = at;
-  if (pass != VCNN_PASS_FWD) at += align256((size_t)tiles * g.k * cells);
-  l->largest = at;
-  if (pass != VCNN_PASS_BWD_FILTER) at += align256(p.along ? (size_t)g.k * g.c * 4 : (size_t)ceil_div((int64_t)g.k * g.c, 4) * 4);
+  l->zero = l->totals = l->cells_image = l->cells_map = l->largest = at;
+  // (in the place of the result's spectra: at most 32 KB for a tile, which takes 16.5 KB of them for each of more than four
+  // channels or maps, lines 2 and 1 KB)
+  l->energy = pass == VCNN_PASS_FWD ? l->map : l->image;
+  if (pass != VCNN_PASS_BWD_FILTER) {
+    at += align256((size_t)tiles * (p.along ? 32 : 8 * kFL));
+    l->totals = at;
+    at += align256((size_t)tiles * 8);
+    l->largest = at;
+    at += align256(p.along ? (size_t)g.k * g.c * 4 : (size_t)ceil_div((int64_t)g.k * g.c, 4) * 4);
+  } else {
+    l->cells_image = at;
+    at += align256((size_t)tiles * g.c * cells);
+    l->cells_map = at;
+    at += align256((size_t)tiles * g.k * cells);
+  }
   l->sums = at;
   if (pass == VCNN_PASS_BWD_FILTER) at += align256((size_t)tiles * g.k * 8);
   return at;
@@ -531,10 +582,12 @@ static vcnn_status launch_product(ProductArgs a, int images, hipStream_t st) {
   a.columns = LINES ? kLV : kFV;
   a.tiles_r = (int)ceil_div(a.rows, 16), a.tiles_c = (int)ceil_div(a.cols, 16);
   a.blocks = a.columns * a.tiles_r * a.tiles_c * a.splits;
-  const int guard_blocks = images * (LINES ? (int)ceil_div(a.guard.line_groups, kGuardLines) : 1);
+  const int guard_blocks = images * (a.guard.line_groups ? (int)ceil_div(a.guard.line_groups, kGuardLines) : 1);
   hipLaunchKernelGGL((spectral_product_kernel<TAPS_A, CONJ_A, TAPS_C, LINES>), dim3((unsigned)(a.blocks + guard_blocks)), dim3(kThreads), 0, st, a);
   return check_launch("spectral_product");
 }
+
+static int bits_of(int64_t n) { return (int)std::ceil(std::log2((double)std::max<int64_t>(n, 1))); }
 
 static SpectralTiles tiles_for(const ConvGeom& g, const SpectralPlan& p, int channels, int h, int w) {
   SpectralTiles t{};
@@ -553,7 +606,31 @@ static GuardArgs guard_for(const SpectralTiles& t, const uint32_t* cells, int wi
   g.any = reinterpret_cast<uint32_t*>(words), g.image = reinterpret_cast<uint32_t*>(words + 256);
   return g;
 }
-static int bits_of(int64_t n) { return (int)std::ceil(std::log2((double)std::max<int64_t>(n, 1))); }
+static SpectralWords words_at(void* workspace, const Layout& l) {
+  uint32_t* const w = (uint32_t*)((char*)workspace + l.words);
+  return {w, w + 2, w + 64};
+}
+// The guard of a forward pass's or input gradient's windows, and that of the magnitudes.
+static WindowGuard window_guard(const ConvGeom& g, int pass, int dtype, const Layout& l, int samples, void* workspace) {
+  const double share = (dtype == VCNN_BF16 ? kDarkBf16 : 1.0) / samples;
+  return {(const double*)((char*)workspace + l.energy), pass == VCNN_PASS_BWD_DATA, kDarkMean * share, kDarkLeast * share,
+          (uint64_t*)((char*)workspace + l.zero), (double*)((char*)workspace + l.totals), words_at(workspace, l)};
+}
+static RangeArgs range_guard(const ConvGeom& g, int pass, const SpectralPlan& p, const Layout& l, const void* workspace) {
+  RangeArgs r{};
+  r.words = words_at(const_cast<void*>(workspace), l);
+  r.totals = (const double*)((const char*)workspace + l.totals), r.transforms = (int)(tiles_of(g, p, pass) / g.n);
+  r.largest = (const uint32_t*)((const char*)workspace + l.largest);
+  r.largest_count = (int)(p.along ? (int64_t)g.k * g.c : ceil_div((int64_t)g.k * g.c, 4));
+  const int64_t depth = pass == VCNN_PASS_FWD ? g.c : g.k;
+  r.grow = bits_of(depth * g.r * g.s), r.depth = (bits_of(depth) + 1) / 2;
+  return r;
+}
+static vcnn_status scan_energies(const ConvGeom& g, int pass, int dtype, const Layout& l, const void* src, void* workspace, hipStream_t st) {
+  const bool fwd = pass == VCNN_PASS_FWD;
+  const EnergyJob job{src, fwd ? g.c : g.k, fwd ? (int64_t)g.h * g.w : g.P, (double*)((char*)workspace + l.energy)};
+  return launch_energies(dtype, g.n, job, {}, (uint32_t*)((char*)workspace + l.words), 64 + g.n, st);
+}
 
 // The lines of a tensor of `channels` channels of h x w, and of the kernels (one line each).
 static SpectralLines lines_for(const ConvGeom& g, const SpectralPlan& p, int channels, int h, int w) {
@@ -592,20 +669,24 @@ static vcnn_status lines_fwd(const SpectralPlan& p, int dtype, const ConvGeom& g
   const Layout l = layout(g, VCNN_PASS_FWD, p);
   char* const ws = (char*)workspace;
   float2 *const xs = (float2*)(ws + l.image), *const ys = (float2*)(ws + l.map), *const taps = (float2*)(ws + l.taps);
-  uint32_t *const cells = (uint32_t*)(ws + l.cells_image), *const largest = (uint32_t*)(ws + l.largest);
+  uint32_t* const largest = (uint32_t*)(ws + l.largest);
+  const WindowGuard guard = window_guard(g, VCNN_PASS_FWD, dtype, l, kLL, workspace);
+  const SpectralExcept except{guard.words.image, guard.zero, guard.words.zeros};
   const int64_t tiles = tiles_of(g, p, VCNN_PASS_FWD);
   const int esize = dtype == VCNN_BF16 ? 2 : 4;
   SpectralLines tx = lines_for(g, p, g.c, g.h, g.w);
   tx.x0 = -(p.along == 1 ? g.pw : g.ph);
   SpectralLines ty = lines_for(g, p, g.k, g.oh, g.ow);
   ty.lim = std::min(p.step_x, ty.len);
+  if (vcnn_status s = scan_energies(g, VCNN_PASS_FWD, dtype, l, x, workspace, st)) return s;
+  if (vcnn_status s = launch_guard_lines(guard, tx, ty, g.r * g.s, st)) return s;
   for (int k0 = 0; k0 < g.k; k0 += p.part) {
     const int maps = std::min(p.part, g.k - k0);
     const bool last = k0 + maps == g.k;
-    LineJob image{tx, tiles * g.c, x, xs, cells, 0, nullptr};
+    LineJob image{tx, tiles * g.c, x, xs, nullptr, 0, nullptr};
     if (k0 > 0) image.t.count = 0;  // (they stay)
     const LineJob kernels{kernel_lines(g, maps), (int64_t)maps * g.c, (const char*)w + (int64_t)k0 * g.K * esize, taps, largest + (int64_t)k0 * g.c, 1, nullptr};
-    if (vcnn_status s = launch_line_spectra(dtype, image, kernels, (uint32_t*)(ws + l.words), k0 == 0 ? 64 + g.n : 0, st)) return s;
+    if (vcnn_status s = launch_line_spectra(dtype, image, kernels, nullptr, 0, st)) return s;
     ProductArgs a{};
     a.A = taps, a.B = xs, a.C = ys;
     a.rows = maps, a.cols = (int)tiles, a.depth = g.c;
@@ -613,14 +694,10 @@ static vcnn_status lines_fwd(const SpectralPlan& p, int dtype, const ConvGeom& g
     a.b_col = 1, a.b_z = tiles, a.b_planes = tiles * g.c;
     a.c_row = tiles, a.c_col = 1, a.c_planes = tiles * maps;
     a.splits = p.splits, a.per_split = p.per_split, a.flush = p.flush, a.rows_inner = 1;
-    if (last) {
-      a.guard = guard_for(tx, cells, g.r * g.s, ws + l.words);
-      a.guard.largest = largest, a.guard.largest_count = (int64_t)g.k * g.c;
-      a.guard.grow = bits_of(g.K);
-    }
+    a.range = range_guard(g, VCNN_PASS_FWD, p, l, workspace), a.col_images = (int)(tiles / g.n);
     if (vcnn_status s = launch_product<false, true, false, true>(a, last ? g.n : 0, st)) return s;
     ty.first = k0, ty.count = maps;
-    if (vcnn_status s = launch_line_inverse(ty, tiles * maps, dtype, ys, 0, 1, y, bias, relu, nullptr, 0, 0, nullptr, st)) return s;
+    if (vcnn_status s = launch_line_inverse(ty, tiles * maps, dtype, ys, 0, 1, y, bias, relu, nullptr, 0, 0, nullptr, except, st)) return s;
   }
   return VCNN_OK;
 }
@@ -630,15 +707,18 @@ static vcnn_status lines_bwd_data(const SpectralPlan& p, int dtype, const ConvGe
   const Layout l = layout(g, VCNN_PASS_BWD_DATA, p);
   char* const ws = (char*)workspace;
   float2 *const xs = (float2*)(ws + l.image), *const ys = (float2*)(ws + l.map), *const taps = (float2*)(ws + l.taps);
-  uint32_t *const cells = (uint32_t*)(ws + l.cells_map), *const largest = (uint32_t*)(ws + l.largest);
+  uint32_t* const largest = (uint32_t*)(ws + l.largest);
+  const WindowGuard guard = window_guard(g, VCNN_PASS_BWD_DATA, dtype, l, kLL, workspace);
   const int64_t tiles = tiles_of(g, p, VCNN_PASS_BWD_DATA);
   const int pad = p.along == 1 ? g.pw : g.ph;
   SpectralLines tdy = lines_for(g, p, g.k, g.oh, g.ow), tdx = lines_for(g, p, g.c, g.h, g.w);
   place_dx(tdx.len + 2 * pad <= kLL, g.r * g.s, pad, &tdy.x0, &tdx.x0);
   tdx.lim = std::min(p.step_x, tdx.len);
-  const LineJob image{tdy, tiles * g.k, dy, ys, cells, 0, nullptr};
+  const LineJob image{tdy, tiles * g.k, dy, ys, nullptr, 0, nullptr};
   const LineJob kernels{kernel_lines(g, g.k), (int64_t)g.k * g.c, w, taps, largest, 1, nullptr};
-  if (vcnn_status s = launch_line_spectra(dtype, image, kernels, (uint32_t*)(ws + l.words), 64 + g.n, st)) return s;
+  if (vcnn_status s = scan_energies(g, VCNN_PASS_BWD_DATA, dtype, l, dy, workspace, st)) return s;
+  if (vcnn_status s = launch_guard_lines(guard, tdy, tdx, g.r * g.s, st)) return s;
+  if (vcnn_status s = launch_line_spectra(dtype, image, kernels, nullptr, 0, st)) return s;
   ProductArgs a{};
   a.A = taps, a.B = ys, a.C = xs;
   a.rows = g.c, a.cols = (int)tiles, a.depth = g.k;
@@ -646,11 +726,10 @@ static vcnn_status lines_bwd_data(const SpectralPlan& p, int dtype, const ConvGe
   a.b_col = 1, a.b_z = tiles, a.b_planes = tiles * g.k;
   a.c_row = tiles, a.c_col = 1, a.c_planes = tiles * g.c;
   a.splits = p.splits, a.per_split = p.per_split, a.flush = p.flush, a.rows_inner = 1, a.c_slice = (int64_t)(p.image_bytes / p.splits / 8);
-  a.guard = guard_for(tdy, cells, g.r * g.s, ws + l.words);
-  a.guard.largest = largest, a.guard.largest_count = (int64_t)g.k * g.c;
-  a.guard.grow = bits_of((int64_t)g.k * g.r * g.s);
+  a.range = range_guard(g, VCNN_PASS_BWD_DATA, p, l, workspace), a.col_images = (int)(tiles / g.n);
   if (vcnn_status s = launch_product<false, false, false, true>(a, g.n, st)) return s;
-  return launch_line_inverse(tdx, tiles * g.c, dtype, xs, a.c_slice, p.splits, dx, nullptr, 0, nullptr, 0, 0, nullptr, st);
+  return launch_line_inverse(tdx, tiles * g.c, dtype, xs, a.c_slice, p.splits, dx, nullptr, 0, nullptr, 0, 0, nullptr,
+                             {guard.words.image, guard.zero, guard.words.zeros}, st);
 }
 
 static vcnn_status lines_filter(const SpectralPlan& p, int dtype, const ConvGeom& g, const void* x, const void* dy, float* dw,
@@ -678,7 +757,7 @@ static vcnn_status lines_filter(const SpectralPlan& p, int dtype, const ConvGeom
   a.guard.grow = bits_of(g.N);
   if (vcnn_status s = launch_product<false, true, false, true>(a, g.n, st)) return s;
   return launch_line_inverse(kernel_lines(g, g.k), (int64_t)g.k * g.c, VCNN_F32, taps, a.c_slice, p.splits, dw, nullptr, 0, sums,
-                             (int)tiles, g.k, db, st);
+                             (int)tiles, g.k, db, {}, st);
 }
 
 vcnn_status launch_spectral_fwd(const SpectralPlan& p, int dtype, const ConvGeom& g, const void* x, const void* w, const float* bias,
@@ -689,15 +768,18 @@ vcnn_status launch_spectral_fwd(const SpectralPlan& p, int dtype, const ConvGeom
   float2* const xs = (float2*)(ws + l.image);
   float2* const ys = (float2*)(ws + l.map);
   float2* const taps = (float2*)(ws + l.taps);
-  uint32_t* const cells = (uint32_t*)(ws + l.cells_image);
   uint32_t* const largest = (uint32_t*)(ws + l.largest);
+  const WindowGuard guard = window_guard(g, VCNN_PASS_FWD, dtype, l, kFL * kFL, workspace);
+  const SpectralExcept except{guard.words.image, guard.zero, guard.words.zeros};
   const int64_t tiles = tiles_of(g, p, VCNN_PASS_FWD);
   const int esize = dtype == VCNN_BF16 ? 2 : 4;
   SpectralTiles tx = tiles_for(g, p, g.c, g.h, g.w);
   tx.y0 = -g.ph, tx.x0 = -g.pw;
-  if (vcnn_status s = launch_plane_spectra(tx, dtype, x, xs, cells, nullptr, (uint32_t*)(ws + l.words), 64 + g.n, st)) return s;
   SpectralTiles ty = tiles_for(g, p, g.k, g.oh, g.ow);
   ty.lim_y = std::min(p.step_y, g.oh), ty.lim_x = std::min(p.step_x, g.ow);
+  if (vcnn_status s = scan_energies(g, VCNN_PASS_FWD, dtype, l, x, workspace, st)) return s;
+  if (vcnn_status s = launch_guard_planes(guard, tx, ty, g.r, g.s, st)) return s;
+  if (vcnn_status s = launch_plane_spectra(tx, dtype, x, xs, nullptr, nullptr, nullptr, 0, guard.words.image, st)) return s;
   for (int k0 = 0; k0 < g.k; k0 += p.part) {
     const int maps = std::min(p.part, g.k - k0);
     const bool last = k0 + maps == g.k;
@@ -710,14 +792,10 @@ vcnn_status launch_spectral_fwd(const SpectralPlan& p, int dtype, const ConvGeom
     a.b_col = g.c, a.b_z = 1, a.b_planes = tiles * g.c;
     a.c_row = 1, a.c_col = maps, a.c_planes = tiles * maps;
     a.splits = p.splits, a.per_split = p.per_split, a.flush = p.flush;
-    if (last) {
-      a.guard = guard_for(tx, cells, g.r, g.s, ws + l.words);
-      a.guard.largest = largest, a.guard.largest_count = ceil_div((int64_t)g.k * g.c, 4);
-      a.guard.grow = bits_of((int64_t)g.c * g.r * g.s);
-    }
+    a.range = range_guard(g, VCNN_PASS_FWD, p, l, workspace), a.col_images = (int)(tiles / g.n);
     if (vcnn_status s = launch_product<true, true, false, false>(a, last ? g.n : 0, st)) return s;
     ty.first = k0, ty.count = maps;
-    if (vcnn_status s = launch_plane_inverse(ty, dtype, ys, 0, 1, y, bias, relu, st)) return s;
+    if (vcnn_status s = launch_plane_inverse(ty, dtype, ys, 0, 1, y, bias, relu, except, st)) return s;
   }
   return VCNN_OK;
 }
@@ -730,8 +808,8 @@ vcnn_status launch_spectral_bwd_data(const SpectralPlan& p, int dtype, const Con
   float2* const xs = (float2*)(ws + l.image);
   float2* const ys = (float2*)(ws + l.map);
   float2* const taps = (float2*)(ws + l.taps);
-  uint32_t* const cells = (uint32_t*)(ws + l.cells_map);
   uint32_t* const largest = (uint32_t*)(ws + l.largest);
+  const WindowGuard guard = window_guard(g, VCNN_PASS_BWD_DATA, dtype, l, kFL * kFL, workspace);
   const int64_t tiles = tiles_of(g, p, VCNN_PASS_BWD_DATA);
   const bool one = one_tile(g);
   SpectralTiles tdy = tiles_for(g, p, g.k, g.oh, g.ow);
@@ -739,7 +817,9 @@ vcnn_status launch_spectral_bwd_data(const SpectralPlan& p, int dtype, const Con
   place_dx(one, g.r, g.ph, &tdy.y0, &tdx.y0);
   place_dx(one, g.s, g.pw, &tdy.x0, &tdx.x0);
   tdx.lim_y = std::min(p.step_y, g.h), tdx.lim_x = std::min(p.step_x, g.w);
-  if (vcnn_status s = launch_plane_spectra(tdy, dtype, dy, ys, cells, nullptr, (uint32_t*)(ws + l.words), 64 + g.n, st)) return s;
+  if (vcnn_status s = scan_energies(g, VCNN_PASS_BWD_DATA, dtype, l, dy, workspace, st)) return s;
+  if (vcnn_status s = launch_guard_planes(guard, tdy, tdx, g.r, g.s, st)) return s;
+  if (vcnn_status s = launch_plane_spectra(tdy, dtype, dy, ys, nullptr, nullptr, nullptr, 0, guard.words.image, st)) return s;
   if (vcnn_status s = launch_taps_spectra(dtype, w, (int64_t)g.k * g.c, g.r, g.s, taps, largest, st)) return s;
   ProductArgs a{};
   a.A = taps, a.B = ys, a.C = xs;
@@ -748,11 +828,9 @@ vcnn_status launch_spectral_bwd_data(const SpectralPlan& p, int dtype, const Con
   a.b_col = g.k, a.b_z = 1, a.b_planes = tiles * g.k;
   a.c_row = 1, a.c_col = g.c, a.c_planes = tiles * g.c;
   a.splits = p.splits, a.per_split = p.per_split, a.flush = p.flush, a.c_slice = (int64_t)(p.image_bytes / p.splits / 8);
-  a.guard = guard_for(tdy, cells, g.r, g.s, ws + l.words);
-  a.guard.largest = largest, a.guard.largest_count = ceil_div((int64_t)g.k * g.c, 4);
-  a.guard.grow = bits_of((int64_t)g.k * g.r * g.s);
+  a.range = range_guard(g, VCNN_PASS_BWD_DATA, p, l, workspace), a.col_images = (int)(tiles / g.n);
   if (vcnn_status s = launch_product<true, false, false, false>(a, g.n, st)) return s;
-  return launch_plane_inverse(tdx, dtype, xs, a.c_slice, p.splits, dx, nullptr, 0, st);
+  return launch_plane_inverse(tdx, dtype, xs, a.c_slice, p.splits, dx, nullptr, 0, {guard.words.image, guard.zero, guard.words.zeros}, st);
 }
 
 vcnn_status launch_spectral_filter(const SpectralPlan& p, int dtype, const ConvGeom& g, const void* x, const void* dy, float* dw,
@@ -771,8 +849,8 @@ vcnn_status launch_spectral_filter(const SpectralPlan& p, int dtype, const ConvG
   tx.y0 = -g.ph, tx.x0 = -g.pw;
   SpectralTiles tdy = tiles_for(g, p, g.k, g.oh, g.ow);
   tdy.lim_y = std::min(p.step_y, g.oh), tdy.lim_x = std::min(p.step_x, g.ow);  // every output pixel in one tile
-  if (vcnn_status s = launch_plane_spectra(tx, dtype, x, xs, cells_x, nullptr, (uint32_t*)(ws + l.words), 64 + g.n, st)) return s;
-  if (vcnn_status s = launch_plane_spectra(tdy, dtype, dy, ys, cells_dy, db ? sums : nullptr, nullptr, 0, st)) return s;
+  if (vcnn_status s = launch_plane_spectra(tx, dtype, x, xs, cells_x, nullptr, (uint32_t*)(ws + l.words), 64 + g.n, nullptr, st)) return s;
+  if (vcnn_status s = launch_plane_spectra(tdy, dtype, dy, ys, cells_dy, db ? sums : nullptr, nullptr, 0, nullptr, st)) return s;
   ProductArgs a{};
   a.A = ys, a.B = xs, a.C = taps;
   a.rows = g.k, a.cols = g.c, a.depth = (int)tiles;

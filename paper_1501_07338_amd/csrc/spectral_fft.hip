@@ -75,6 +75,7 @@ struct PlaneArgs {
   double* sums;
   uint32_t* words;
   int cleared;
+  const uint32_t* declined;
   int64_t planes;
 };
 
@@ -98,6 +99,7 @@ __global__ __launch_bounds__(kThreads) void plane_spectra_kernel(PlaneArgs a) {
   const SpectralTiles& t = a.t;
   const int c = (int)(p % t.count), tx = (int)(p / t.count % t.tiles_x), ty = (int)(p / t.count / t.tiles_x % t.tiles_y);
   const int64_t n = p / t.count / t.tiles_x / t.tiles_y;
+  const bool leaves = a.declined && a.declined[n];
   const T* const src = (const T*)a.src + (n * t.channels + t.first + c) * ((int64_t)t.h * t.w);
   const int y0 = ty * t.step_y + t.y0, x0 = tx * t.step_x + t.x0;
   // the pixels of the transform that lie in the tile and in the plane
@@ -112,6 +114,7 @@ __global__ __launch_bounds__(kThreads) void plane_spectra_kernel(PlaneArgs a) {
       const bool in = ly >= top && ly < bottom && lx >= left && lx < right;
       (half ? hi : lo)[i] = ld(src + (unsigned)(in ? at + 32 * half * t.w + 8 * i : 0));
     }
+  if (leaves) return;  // (here, and not in front of the loads, the word's latency costs nothing)
 #pragma unroll
   for (int half = 0; half < 2; ++half)  // (all loads in flight before the first is looked at)
 #pragma unroll
@@ -125,7 +128,7 @@ __global__ __launch_bounds__(kThreads) void plane_spectra_kernel(PlaneArgs a) {
   cd v[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) v[i] = {(double)lo[i], (double)hi[i]};
-  {  // wave b holds the rows of cells b (lo) and b + 4 (hi); the columns j + 16 i and j + 8 + 16 i are those of a cell
+  if (a.cells) {  // wave b holds the rows of cells b (lo) and b + 4 (hi); the columns j + 16 i and j + 8 + 16 i are those of a cell
     uint32_t m[8];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -184,6 +187,7 @@ __global__ __launch_bounds__(kThreads) void plane_spectra_kernel(PlaneArgs a) {
 
 struct InverseArgs {
   SpectralTiles t;
+  SpectralExcept except;
   const float2* spectra;
   int64_t slice, planes;
   int slices;
@@ -197,6 +201,9 @@ __global__ __launch_bounds__(kThreads) void plane_inverse_kernel(InverseArgs a) 
   __shared__ cd z[32 * kPitch];
   const int tid = threadIdx.x, j = tid & 7, q = tid >> 3;
   const int64_t p = blockIdx.x;
+  const SpectralTiles& t = a.t;
+  const int64_t tile = p / t.count, n = tile / t.tiles_x / t.tiles_y;
+  const bool leaves = a.except.declined && a.except.declined[n], zeros = a.except.zero && *a.except.zeros;
   const cd w = kRoot64[j];
   const int col = q;
   cd v[8];
@@ -233,6 +240,7 @@ __global__ __launch_bounds__(kThreads) void plane_inverse_kernel(InverseArgs a) 
     for (int k = 0; k < 8; ++k) v[k] = {v[k].x - r[k].y, v[k].y + r[k].x};
   }
   ifft64(v, z + col * kPitch, j, w);
+  if (leaves) return;  // (here the word's latency costs nothing)
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
@@ -249,9 +257,7 @@ __global__ __launch_bounds__(kThreads) void plane_inverse_kernel(InverseArgs a) 
 #pragma unroll
   for (int k = 0; k < 8; ++k) v[k] = z[q * kPitch + j + 8 * k];
   ifft64(v, z + q * kPitch, j, w);
-  const SpectralTiles& t = a.t;
-  const int c = (int)(p % t.count), tx = (int)(p / t.count % t.tiles_x), ty = (int)(p / t.count / t.tiles_x % t.tiles_y);
-  const int64_t n = p / t.count / t.tiles_x / t.tiles_y;
+  const int c = (int)(p % t.count), tx = (int)(tile % t.tiles_x), ty = (int)(tile / t.tiles_x % t.tiles_y);
   const int64_t plane = (n * t.channels + t.first + c) * ((int64_t)t.h * t.w);
   T* const dst = (T*)a.dst + plane;
   const float bias = a.bias ? a.bias[t.first + c] : 0.f;
@@ -259,11 +265,12 @@ __global__ __launch_bounds__(kThreads) void plane_inverse_kernel(InverseArgs a) 
   for (int half = 0; half < 2; ++half) {
     const int ly = q + 32 * half - t.y0, y = ty * t.step_y + ly;
     if (ly < 0 || ly >= t.lim_y || y >= t.h) continue;
+    const uint64_t zero = zeros ? a.except.zero[tile * kFL + q + 32 * half] >> j : 0;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const int lx = j + 8 * i - t.x0, x = tx * t.step_x + lx;
       if (lx < 0 || lx >= t.lim_x || x >= t.w) continue;
-      float r = (float)((half ? v[i].y : v[i].x) * (1.0 / 4096) + (double)bias);
+      float r = zero >> 8 * i & 1 ? bias : (float)((half ? v[i].y : v[i].x) * (1.0 / 4096) + (double)bias);
       if (a.relu) r = fmaxf(r, 0.f);
       st(dst + (int64_t)y * t.w + x, r);
     }
@@ -422,7 +429,8 @@ struct Line {
   int64_t at;      // of its first sample (before the tile's offset) in the tensor
   int64_t plane;   // index of its spectrum
   int64_t cell;    // index of its cells
-  int channel, start;
+  int64_t group;   // index of the lines of all channels it is one of
+  int channel, start, image;
 };
 __device__ __forceinline__ Line line_of(const SpectralLines& t, unsigned id) {
   Line l;
@@ -431,8 +439,9 @@ __device__ __forceinline__ Line line_of(const SpectralLines& t, unsigned id) {
   const int64_t n = maps / t.count;
   l.at = (n * t.channels + t.first + c) * t.s_channel + o * t.s_other;
   l.plane = n * t.p_image + c * t.p_channel + (int64_t)o * t.tiles + tile;
-  l.cell = ((n * t.others + o) * t.tiles + tile) * t.count + c;
-  l.channel = t.first + c, l.start = tile * t.step;
+  l.group = (n * t.others + o) * t.tiles + tile;
+  l.cell = l.group * t.count + c;
+  l.channel = t.first + c, l.start = tile * t.step, l.image = (int)n;
   return l;
 }
 
@@ -555,6 +564,7 @@ struct LineInverseArgs {
   const double* sums;
   int sum_planes, maps;
   float* db;
+  SpectralExcept except;
 };
 
 template <typename T>
@@ -565,6 +575,7 @@ __global__ __launch_bounds__(kThreads) void line_inverse_kernel(LineInverseArgs 
   if ((int)blockIdx.x >= a.blocks) return add_sums(a.sums, a.sum_planes, a.maps, ((int)blockIdx.x - a.blocks) * 4 + (tid >> 6), a.db);
   __shared__ int plane_of[32];
   __shared__ uint32_t top_of[4][16];
+  const bool zeros = a.except.zero && *a.except.zeros;
   const int lines = (int)a.lines;
   if (tid < 32) plane_of[tid] = (int)line_of(t, min((int)blockIdx.x * 32 + tid, lines - 1)).plane;
   __syncthreads();
@@ -625,15 +636,19 @@ __global__ __launch_bounds__(kThreads) void line_inverse_kernel(LineInverseArgs 
     const int id = blockIdx.x * 32 + 2 * q + half;
     if (id >= lines) continue;
     const Line l = line_of(t, id);
+    if (a.except.declined && a.except.declined[l.image]) continue;
     T* const dst = (T*)a.dst + l.at;
     const float bias = a.bias ? a.bias[l.channel] : 0.f;
     const uint32_t high = top(q, half);
     const double unscale = high && finite(high) ? ldexp(1.0 / 256, exponent(high)) : 0.0;
+    uint64_t zero[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) zero[k] = zeros ? a.except.zero[l.group * 4 + k] >> j : 0;
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       const int lx = j + 16 * i - t.x0, x = l.start + lx;
       if (lx < 0 || lx >= t.lim || x >= t.len) continue;
-      float r = (float)((half ? v[i].y : v[i].x) * unscale + (double)bias);
+      float r = zero[i >> 2] >> 16 * (i & 3) & 1 ? bias : (float)((half ? v[i].y : v[i].x) * unscale + (double)bias);
       if (a.relu) r = fmaxf(r, 0.f);
       st(dst + (int64_t)x * t.s_along, r);
     }
@@ -642,15 +657,15 @@ __global__ __launch_bounds__(kThreads) void line_inverse_kernel(LineInverseArgs 
 
 // ---- launches ----------------------------------------------------------------------------------------------------
 vcnn_status launch_plane_spectra(const SpectralTiles& t, int dtype, const void* src, float2* spectra, uint32_t* cells, double* sums,
-                                 uint32_t* words, int cleared, hipStream_t st) {
-  PlaneArgs a{t, src, spectra, cells, sums, words, cleared, t.planes()};
+                                 uint32_t* words, int cleared, const uint32_t* declined, hipStream_t st) {
+  PlaneArgs a{t, src, spectra, cells, sums, words, cleared, declined, t.planes()};
   if (dtype == VCNN_BF16) hipLaunchKernelGGL(plane_spectra_kernel<bf16>, dim3((unsigned)a.planes), dim3(kThreads), 0, st, a);
   else hipLaunchKernelGGL(plane_spectra_kernel<float>, dim3((unsigned)a.planes), dim3(kThreads), 0, st, a);
   return check_launch("plane_spectra");
 }
 vcnn_status launch_plane_inverse(const SpectralTiles& t, int dtype, const float2* spectra, int64_t slice, int slices, void* dst,
-                                 const float* bias, int relu, hipStream_t st) {
-  InverseArgs a{t, spectra, slice, t.planes(), slices, dst, bias, relu};
+                                 const float* bias, int relu, const SpectralExcept& except, hipStream_t st) {
+  InverseArgs a{t, except, spectra, slice, t.planes(), slices, dst, bias, relu};
   if (dtype == VCNN_BF16) hipLaunchKernelGGL(plane_inverse_kernel<bf16>, dim3((unsigned)a.planes), dim3(kThreads), 0, st, a);
   else hipLaunchKernelGGL(plane_inverse_kernel<float>, dim3((unsigned)a.planes), dim3(kThreads), 0, st, a);
   return check_launch("plane_inverse");
@@ -680,8 +695,8 @@ vcnn_status launch_line_spectra(int dtype, const LineJob& first, const LineJob& 
 }
 vcnn_status launch_line_inverse(const SpectralLines& t, int64_t planes, int dtype, const float2* spectra, int64_t slice, int slices,
                                 void* dst, const float* bias, int relu, const double* sums, int sum_planes, int maps, float* db,
-                                hipStream_t st) {
-  LineInverseArgs a{t, spectra, slice, t.lines(), planes, slices, (int)ceil_div(t.lines(), 32), dst, bias, relu, sums, sum_planes, maps, db};
+                                const SpectralExcept& except, hipStream_t st) {
+  LineInverseArgs a{t, spectra, slice, t.lines(), planes, slices, (int)ceil_div(t.lines(), 32), dst, bias, relu, sums, sum_planes, maps, db, except};
   const dim3 grid((unsigned)(a.blocks + (db ? ceil_div(maps, 4) : 0)));
   if (dtype == VCNN_BF16) hipLaunchKernelGGL(line_inverse_kernel<bf16>, grid, dim3(kThreads), 0, st, a);
   else hipLaunchKernelGGL(line_inverse_kernel<float>, grid, dim3(kThreads), 0, st, a);

@@ -4,6 +4,7 @@ too small."""
 import numpy as np
 import pytest
 import torch
+import torch.nn.functional as F
 
 import oracle as O
 from paper_1501_07338_amd import vcnn
@@ -240,12 +241,7 @@ def test_what_the_transforms_do_not_carry(shape, which, bf16, case):
     else:
         t[0, 1, 3, 3] = np.inf if case == "inf" else np.nan
     with np.errstate(all="ignore"):
-        got = run_pass(d, which, x, wt, b, dy)
-        vcnn.set_conv_algo(vcnn.ALGO_IMPLICIT)
-        try:
-            want = run_pass(d, which, x, wt, b, dy)
-        finally:
-            vcnn.set_conv_algo(vcnn.ALGO_AUTO)
+        got, want = run_pass(d, which, x, wt, b, dy), implicit(d, which, x, wt, b, dy)
     got, want = (got[0], want[0]) if which == FILTER else (got, want)
     # what has to be the float kernel's: the image, or all of it
     image = (0,) if which != FILTER and case not in ("weight", "range") else (slice(None),)
@@ -256,6 +252,72 @@ def test_what_the_transforms_do_not_carry(shape, which, bf16, case):
         assert np.max(np.abs(g - e)[fine], initial=0) <= TOL * np.max(np.abs(e[fine]), initial=0)
     else:
         assert np.array_equal(g[fine], e[fine])
+
+
+def implicit(d, which, x, wt, b, dy):
+    """The same pass by the direct float kernels."""
+    vcnn.set_conv_algo(vcnn.ALGO_IMPLICIT)
+    try:
+        return run_pass(d, which, x, wt, b, dy)
+    finally:
+        vcnn.set_conv_algo(vcnn.ALGO_AUTO)
+
+
+def window_norms(d, which, x, wt, dy):
+    """For every output the norm of what it sums times that of its kernel: 0 where only zeros meet."""
+    ones = torch.ones((1, 1, d.r, d.s), dtype=torch.float64)
+    t = torch.from_numpy(((x if which == FWD else dy).astype(np.float64) ** 2).sum(1, keepdims=True))
+    w2 = wt.astype(np.float64) ** 2
+    if which == FWD:
+        e = F.conv2d(t, ones, padding=(d.pad_h, d.pad_w))
+        return np.sqrt(e.numpy() * w2.sum((1, 2, 3))[None, :, None, None])
+    e = F.conv_transpose2d(t, ones, padding=(d.pad_h, d.pad_w))
+    return np.sqrt(e.numpy() * w2.sum((0, 2, 3))[None, :, None, None])
+
+
+def paint(t, shape, case):
+    """Every image its own place: areas of a kernel's size and a little more, elements, borders."""
+    n, _, h, w = t.shape
+    r, s = shape[5:7]
+    for i in range(n):
+        if case in ("dark", "black"):
+            dh, dw = min(h, r + i % 3), min(w, s + i % 4)
+            oy, ox = i * 5 % (h - dh + 1), i * 7 % (w - dw + 1)
+            t[i, :, oy:oy + dh, ox:ox + dw] *= 0 if case == "black" else np.float32(2.0 ** -16)
+        elif case == "outlier":
+            t[i, 2, i * 11 % h, (60 + i * 13) % w] = 2.0 ** (20 if i % 2 else 45)
+        else:
+            by = 0 if case == "black border" else np.float32(2.0 ** -16)
+            if r > 1:
+                t[i, :, :1 + i % r] *= by
+            if s > 1:
+                t[i, :, :, w - 1 - i % s:] *= by
+    return t
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,which,bf16", [((27, 28, 64, 64, 29, 16, 16, 0, 0), FWD, False), ((27, 28, 64, 64, 29, 16, 16, 0, 0), DATA, False),
+                                              ((9, 22, 70, 70, 49, 16, 16, 0, 0), FWD, False), ((24, 29, 56, 46, 26, 16, 15, 3, 9), DATA, False),
+                                              ((5, 12, 60, 38, 98, 8, 16, 5, 11), FWD, False), ((14, 13, 103, 100, 13, 13, 12, 0, 0), DATA, False),
+                                              ((7, 20, 42, 214, 36, 1, 100, 0, 0), FWD, False), ((16, 38, 64, 184, 38, 1, 121, 0, 0), DATA, False),
+                                              ((1, 51, 219, 228, 48, 72, 1, 0, 0), FWD, False), ((6, 55, 261, 9, 58, 95, 1, 86, 0), DATA, False),
+                                              ((30, 29, 64, 62, 180, 16, 16, 0, 0), FWD, True), ((16, 38, 64, 64, 512, 16, 16, 0, 0), DATA, True)])
+@pytest.mark.parametrize("case", ["dark", "black", "outlier", "border", "black border"])
+def test_every_window_counts(shape, which, bf16, case):
+    """Whatever the rest of a plane holds, an output is exact relative to what it sums itself, wherever its window lies, and an
+    output that sums zeros is zero.  The spectra are rounded to float and their error is spread evenly: 1.2e-7 of the root mean square
+    of a transform's outputs; the guard holds that to four times the norm of a window and its kernel, 32 times that in
+    bfloat16 (beside its own rounding, 2^-9), and the largest of 10^6 errors is five times their root mean square."""
+    d, x, wt, b, dy = tensors(shape, 5900, bf16)
+    assert route(d, which) == "spectral"
+    b = np.zeros_like(b)
+    t = paint(x if which == FWD else dy, shape, case)
+    if bf16:
+        t[...] = bf16_round(t)
+    got, want = run_pass(d, which, x, wt, b, dy).astype(np.float64), implicit(d, which, x, wt, b, dy).astype(np.float64)
+    norms = window_norms(d, which, x, wt, dy)
+    limit = norms * (4e-6 * (32 if bf16 else 1)) + np.abs(want) * (2.0 ** -7 if bf16 else 0)  # (both results are rounded there)
+    assert np.all(np.abs(got - want) <= limit), float(np.max(np.abs(got - want) / np.maximum(norms, 1e-300)))
 
 
 @pytest.mark.gpu
