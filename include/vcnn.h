@@ -79,7 +79,9 @@ enum { VCNN_PASS_FWD = 0, VCNN_PASS_BWD_FILTER = 1, VCNN_PASS_BWD_DATA = 2 };
  * clipped at the border - has less than 1/16 of the root mean square of its transform (over all channels; or in all less
  * than a quarter of the norm of one average pixel; in bfloat16 1/32 of either), with an infinity or NaN, or with magnitudes
  * whose products leave the float range is computed by the float kernel, in its own time.  The error of an output is then a few
- * 1e-7 times the norm of what its window holds times that of its kernel (4e-6 at most). */
+ * 1e-7 times the norm of what its window holds times that of its kernel (4e-6 at most).  A kernel gradient is left to the float
+ * kernel, all of it, where at some tap the energies that meet come to less than 1/16 of their mean over all shifts (so that its
+ * error stays below 1e-6 of what the tap sums); a tap at which nothing meets is exactly zero. */
 enum { VCNN_ALGO_AUTO = 0, VCNN_ALGO_EXPLICIT = 1, VCNN_ALGO_IMPLICIT = 2, VCNN_ALGO_FOLD = 3, VCNN_ALGO_FFT = 4,
        VCNN_ALGO_SPLIT = 5 };
 

@@ -30,15 +30,15 @@ static constexpr int kFTaps = 16;     // most kernel rows / columns
 // columns of 64 values, frequencies 0..127, the first with those of 0 and 128 (both real) as its two parts.
 
 static constexpr int kLL = 256, kLV = 2, kLineTaps = 128;  // lines: length, columns of 64 values, most taps
-static constexpr int kFCells = 32;    // cells of 8 x 16 pixels of a plane
-// A window (in whole cells) darker than this share of its tile's largest element declines the image.
-static constexpr float kDarkWindow = 1.f / 1024;
 // A forward pass or input gradient declines an image where an output's window has, per sample of it, less energy (sum of squares
 // over the channels) than this share of the mean over its transform, or in all less than that share of one mean sample: an
 // error of some 1e-7 of the transform's mean output is then at most 16 times that of the output's own scale (short windows at
 // the border of an input gradient: 4 sqrt(taps) times).
 static constexpr double kDarkMean = 1.0 / 256, kDarkLeast = 1.0 / 16;
 static constexpr double kDarkBf16 = 1.0 / 1024;  // of those, where the result is rounded to eight bits: 32 times the error
+// A kernel gradient declines, all of it, where at a tap what meets - the energies of the two operands multiplied pixel by pixel -
+// is less than this share of the mean over all shifts: an error of 6e-8 of the mean result at most four times that of the tap's own.
+static constexpr double kDarkMeet = 1.0 / 16;
 
 struct SpectralPlan {
   int along;               // 0: planes; kernels of one row (1) or one column (2): lines along the width or the height
@@ -47,6 +47,7 @@ struct SpectralPlan {
   int part;                // forward: output maps worked on at once (else all)
   int splits, per_split;   // slices of the contraction, summed by the inverse transform
   int flush;               // products in one sum
+  int energy_in_taps;      // kernel gradient: the energies of the operands in the place of the result's spectra
   size_t image_bytes;      // spectra over the input channels (input gradient: one slice per split)
   size_t map_bytes;        // spectra over the output maps (of a part)
   size_t taps_bytes;       // row spectra of the kernels (of a part; kernel gradient: one slice per split)
@@ -73,12 +74,28 @@ struct SpectralTiles {
   int tiles_y, tiles_x, step_y, step_x, y0, x0, lim_y, lim_x;
   int64_t planes() const { return (int64_t)images * tiles_y * tiles_x * count; }
 };
-// Also leaves each plane's largest magnitude per cell of 8 x 16 pixels (cells, float bits, nullable), its sum (sums, nullable),
-// and zeros in `cleared` words.  Images declined (nullable) are left out.
-vcnn_status launch_plane_spectra(const SpectralTiles& t, int dtype, const void* src, float2* spectra, uint32_t* cells,
-                                 double* sums, uint32_t* words, int cleared, const uint32_t* declined, hipStream_t st);
+struct SpectralWords {  // cleared by launch_energies: 64 words and one for each image
+  uint32_t* any;
+  uint32_t* zeros;  // an output's window holds only zeros
+  uint32_t* image;
+};
+// The decision about a kernel gradient from what meets at its taps (launch_meet_..), by one block of the transforms that follow: the
+// word that declines, and a bit for each tap at which nothing meets (zero[16]: the rows of a kernel, of one row 64 taps each).
+struct MeetDecision {
+  const double* partial;  // null: nothing to decide
+  int chunks, r, s;
+  double share;
+  int grow;
+  uint64_t* zero;
+  SpectralWords words;
+};
+// Also leaves each plane's sum (sums, nullable).  What is declined (nullable: a word for each image, or one) may be left out, where
+// no sums are asked for; `decide` is done on the way.
+vcnn_status launch_plane_spectra(const SpectralTiles& t, int dtype, const void* src, float2* spectra, double* sums,
+                                 const uint32_t* declined, int per_image, const MeetDecision& decide, hipStream_t st);
 // What an inverse transform does not write, and what it writes as zero (both nullable).
 struct SpectralExcept {
+  int per_image;             // the words are each image's, each transform's, or (0) one for all
   const uint32_t* declined;  // [image]
   const uint64_t* zero;      // a bit for each sample of a transform: [tile][64 rows], [line][4] ...
   const uint32_t* zeros;     // ... where this is set
@@ -92,7 +109,7 @@ vcnn_status launch_taps_spectra(int dtype, const void* w, int64_t kernels, int r
                                 hipStream_t st);
 // And back; also, in blocks of their own, db[m] = sums[0][m] + sums[1][m] + ... (planes of `maps` maps; nullable).
 vcnn_status launch_taps_inverse(const float2* spectra, int64_t slice, int slices, int64_t kernels, int r, int s, float* dw,
-                                const double* sums, int sum_planes, int maps, float* db, hipStream_t st);
+                                const double* sums, int sum_planes, int maps, float* db, const SpectralExcept& except, hipStream_t st);
 
 // Lines of a tensor [images][channels][...]: sample x of line (image, channel, o) lies at o s_other + x s_along of the channel;
 // tiles as above, in one dimension.  The spectrum of line (image, channel, o, tile) is number
@@ -109,22 +126,16 @@ struct LineJob {
   int64_t planes;    // spectra per column
   const void* src;
   float2* spectra;
-  uint32_t* cells;   // the largest magnitude of each 16 samples: [image][o][tile][channel][16], or one of ...
-  int whole;         // ... each line
+  uint32_t* largest; // magnitude of each line, nullable
   double* sums;      // sums of the lines, nullable: [image][o][tile][channel]
 };
-// The lines of two tensors (the second may have none: all zero); leaves zeros in `cleared` words.
-vcnn_status launch_line_spectra(int dtype, const LineJob& first, const LineJob& second, uint32_t* words, int cleared, hipStream_t st);
+// The lines of two tensors (the second may have none: all zero).
+vcnn_status launch_line_spectra(int dtype, const LineJob& first, const LineJob& second, const MeetDecision& decide, hipStream_t st);
 vcnn_status launch_line_inverse(const SpectralLines& t, int64_t planes, int dtype, const float2* spectra, int64_t slice, int slices,
                                 void* dst, const float* bias, int relu, const double* sums, int sum_planes, int maps, float* db,
                                 const SpectralExcept& except, hipStream_t st);
 
 // ---- spectral_guard.hip ---------------------------------------------------------------------------------------------
-struct SpectralWords {  // cleared by launch_energies: 64 words and one for each image
-  uint32_t* any;
-  uint32_t* zeros;  // an output's window holds only zeros
-  uint32_t* image;
-};
 struct EnergyJob {
   const void* src;  // [image][channels][pixels]
   int channels;
@@ -145,5 +156,16 @@ struct WindowGuard {
 // in: the transforms of the operand with the energies; out: the outputs that the inverse transform keeps of them.
 vcnn_status launch_guard_planes(const WindowGuard& g, const SpectralTiles& in, const SpectralTiles& out, int r, int s, hipStream_t st);
 vcnn_status launch_guard_lines(const WindowGuard& g, const SpectralLines& in, const SpectralLines& out, int taps, hipStream_t st);
+// What meets at each tap of a kernel gradient: partial[chunk][taps + 1] = the sums over some transforms of the products of the
+// operands' energies, and of those of their totals.
+struct MeetGuard {
+  const double *x, *dy;  // energies [image][pixel]
+  int chunks, per_chunk; // transforms
+  double* partial;
+  int depth_x, depth_dy; // bits of the root of the numbers of channels, of maps
+  SpectralWords words;
+};
+vcnn_status launch_meet_planes(const MeetGuard& m, const SpectralTiles& x, const SpectralTiles& dy, int r, int s, hipStream_t st);
+vcnn_status launch_meet_lines(const MeetGuard& m, const SpectralLines& x, const SpectralLines& dy, int taps, hipStream_t st);
 
 }  // namespace vcnn

@@ -44,41 +44,7 @@ __constant__ const float kRoots[4][16][2] = {
 
 __device__ const float4 kZeros[8] = {};
 
-// ---- what declines an image --------------------------------------------------------------------------------------
-struct GuardArgs {
-  const uint32_t* cells[2];  // [image][tile][plane][kFCells]: of the operand with windows, and of another (nullable)
-  int planes[2], tiles_y, tiles_x, images;
-  int step_y, step_x, y0, x0, h, w, lim_y, lim_x;  // of the first operand's tiles
-  int win_y, win_x;          // cells a window covers
-  int grow;                  // bits a sum of products may gain
-  uint32_t* any;
-  uint32_t* image;
-  int line_groups;           // > 0: lines, so many groups of one line per channel in an image; tiles_x of them along a line;
-                             // cells[.]: [image][group][line of it][16]
-};
-static constexpr int kGuardLines = 16;  // groups of lines a block looks at
-// The largest element of some groups of lines, and whether a window of one (win_x cells of 16 samples, all channels) is dark.
-__device__ bool dark_line(const GuardArgs& g, int n, int first, uint32_t* most) {
-  const int tid = threadIdx.x, lane = tid & 63, cell = lane & 15;
-  bool bad = false;
-  for (int i = first + (tid >> 6); i < min(first + kGuardLines, g.line_groups); i += 4) {
-    const uint32_t* c = g.cells[0] + ((int64_t)n * g.line_groups + i) * g.planes[0] * 16;
-    uint32_t m = 0;
-#pragma unroll 8
-    for (int p = lane >> 4; p < g.planes[0]; p += 4) m = max(m, c[p * 16 + cell]);
-    m = max(m, (uint32_t)__shfl_xor((int)m, 16));
-    m = max(m, (uint32_t)__shfl_xor((int)m, 32));
-    uint32_t top = m, win = m;
-#pragma unroll
-    for (int d = 8; d > 0; d >>= 1) top = max(top, (uint32_t)__shfl_xor((int)top, d));
-    for (int d = 1; d < g.win_x; ++d) win = max(win, (uint32_t)__shfl((int)m, (cell + d) & 15));
-    const int xs = i % g.tiles_x * g.step_x + g.x0;
-    const bool inside = cell + g.win_x <= 16 && xs + cell * 16 >= 0 && (cell + g.win_x) * 16 <= min(g.lim_x, g.w - xs);
-    bad |= inside && __uint_as_float(win) < kDarkWindow * __uint_as_float(top);
-    *most = max(*most, top);
-  }
-  return bad;
-}
+// ---- what the magnitudes decline ---------------------------------------------------------------------------------
 // By all 256 threads.
 __device__ __forceinline__ uint32_t block_max(uint32_t m, uint32_t* lds) {
 #pragma unroll
@@ -88,57 +54,6 @@ __device__ __forceinline__ uint32_t block_max(uint32_t m, uint32_t* lds) {
   __syncthreads();
   return max(max(lds[0], lds[1]), max(lds[2], lds[3]));
 }
-__device__ void guard_image(const GuardArgs& g, int block, uint32_t* lds) {
-  const int tid = threadIdx.x;
-  uint32_t most = 0, other = 0;
-  bool bad = false;
-  int n = block, share = g.tiles_y * g.tiles_x * g.planes[1] * kFCells, first = 0;  // of the other operand's cells
-  if (g.line_groups) {
-    const int chunks = (g.line_groups + kGuardLines - 1) / kGuardLines;
-    n = block / chunks;
-    const int group = block % chunks * kGuardLines;
-    bad = dark_line(g, n, group, &most);
-    first = group * g.planes[1] * 16, share = min(kGuardLines, g.line_groups - group) * g.planes[1] * 16;
-  } else {
-    for (int t = 0; t < g.tiles_y * g.tiles_x; ++t) {
-      uint32_t m = 0;
-      const uint32_t* c = g.cells[0] + ((int64_t)n * g.tiles_y * g.tiles_x + t) * g.planes[0] * kFCells;
-#pragma unroll 8
-      for (int i = tid; i < g.planes[0] * kFCells; i += kThreads) m = max(m, c[i]);
-      const uint32_t top = block_max(m, lds + 256);
-      lds[tid] = m;
-      __syncthreads();
-      most = max(most, top);
-      const int cy = tid >> 2, cx = tid & 3, ty = t / g.tiles_x, tx = t % g.tiles_x;
-      const int ys = ty * g.step_y + g.y0, xs = tx * g.step_x + g.x0;  // the tile's first pixel in the plane
-      bool inside = cy + g.win_y <= 8 && cx + g.win_x <= 4;
-      inside = inside && ys + cy * 8 >= 0 && xs + cx * 16 >= 0;
-      inside = inside && (cy + g.win_y) * 8 <= min(g.lim_y, g.h - ys) && (cx + g.win_x) * 16 <= min(g.lim_x, g.w - xs);
-      if (inside) {
-        uint32_t win = 0;
-        for (int y = cy; y < cy + g.win_y; ++y)
-          for (int x = cx; x < cx + g.win_x; ++x)
-            for (int b = 0; b < 8; ++b) win = max(win, lds[b * kFCells + y * 4 + x]);
-        bad |= __uint_as_float(win) < kDarkWindow * __uint_as_float(top);
-      }
-      __syncthreads();
-    }
-  }
-  {
-    const int tiles = g.line_groups ? g.line_groups * 16 : g.tiles_y * g.tiles_x * kFCells;
-    const uint32_t* c = g.cells[1] + (int64_t)n * tiles * g.planes[1] + first;
-#pragma unroll 8
-    for (int i = tid; i < share; i += kThreads) other = max(other, c[i]);
-  }
-  most = block_max(most, lds);
-  other = block_max(other, lds);
-  // exponents: sums of a transform gain 12 bits, and products of spectra have to stay 24 bits clear of the least float
-  const int ea = (int)(most >> 23) - 127, eb = (int)(other >> 23) - 127;
-  bad |= ea == 128 || eb == 128;  // infinity or NaN
-  if (most && other) bad |= ea + eb + 24 + g.grow > 126 || ea > 110 || eb > 110 || ea + eb < -80 || ea < -90 || eb < -90;
-  if (__syncthreads_or(bad) && tid == 0) atomicOr(g.image + n, 1u), atomicOr(g.any, 1u);
-}
-
 // What the magnitudes of a forward pass's or input gradient's operands decline, an image each block: of the image the energies that
 // the guard of windows left, of the kernels the largest element of each few.
 struct RangeArgs {
@@ -200,14 +115,14 @@ struct ProductArgs {
   int columns, tiles_r, tiles_c, splits, per_split;
   int flush;                                     // (spectra as results) so many products are added in a row, then to C
   int rows_inner;                                // tiles of rows follow each other (the columns' operand is the larger one)
-  int blocks;                                    // of products; further blocks look for what is declined
-  GuardArgs guard;                               // (kernel gradient)
-  RangeArgs range;                               // (the others)
-  int col_images;                                // (the others) columns of one image
+  int blocks;                                    // of products; further blocks look at the magnitudes (range)
+  const uint32_t* declined;                      // something is ...
+  int col_images;                                // ... columns of one image (0, kernel gradient: then all is)
+  RangeArgs range;
 };
 // Whether all images of a block's 16 columns are declined.
 __device__ __forceinline__ bool leave_columns(const ProductArgs& a, int tc) {
-  if (!a.range.words.any || !*a.range.words.any) return false;
+  if (!*a.declined || a.col_images == 0) return *a.declined != 0;
   const int col = min(tc * 16 + ((int)threadIdx.x & 15), a.cols - 1);
   return __all(a.range.words.image[col / a.col_images] != 0);
 }
@@ -217,10 +132,7 @@ __device__ __forceinline__ float4 add4(float4 a, float4 b) { return make_float4(
 template <bool TAPS_A, bool CONJ_A, bool TAPS_C, bool LINES>
 __global__ __launch_bounds__(kThreads, 2) void spectral_product_kernel(ProductArgs a) {
   __shared__ __attribute__((aligned(128))) uint4 lds[4][1024];
-  if ((int)blockIdx.x >= a.blocks) {
-    uint32_t* const words = reinterpret_cast<uint32_t*>(&lds[0][0]);
-    return a.range.words.any ? guard_range(a.range, blockIdx.x - a.blocks, words) : guard_image(a.guard, blockIdx.x - a.blocks, words);
-  }
+  if ((int)blockIdx.x >= a.blocks) return guard_range(a.range, blockIdx.x - a.blocks, reinterpret_cast<uint32_t*>(&lds[0][0]));
   const int tid = threadIdx.x, lane = tid & 63, rho = __builtin_amdgcn_readfirstlane(tid >> 6);
   // blocks that share the larger operand's planes one after the other on the same XCD (blocks are dealt to the eight in turn)
   int id = blockIdx.x;
@@ -446,8 +358,8 @@ static size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 namespace {
 struct Layout {  // of the workspace
-  size_t image, map, taps, words, energy;  // offsets
-  size_t zero, totals, cells_image, cells_map, largest, sums;  // inside words
+  size_t image, map, taps, words, energy, energy_dy;        // offsets
+  size_t zero, totals, largest, meet, sums;                 // inside words
 };
 }  // namespace
 
@@ -459,32 +371,33 @@ static int64_t tiles_of(const ConvGeom& g, const SpectralPlan& p, int pass) {
   return (int64_t)g.n * p.tiles_x * (p.along == 1 ? (data ? g.h : g.oh) : (data ? g.w : g.ow));
 }
 
+// Of both operands of a kernel gradient.
+static size_t energy_bytes(const ConvGeom& g) { return 8 * ((size_t)g.n * g.h * g.w + (size_t)g.N); }
+// Chunks of its transforms whose energies are multiplied at each tap.
+static int meet_chunks(const SpectralPlan& p, int64_t tiles) { return (int)ceil_div(tiles, ceil_div(tiles, p.along ? 256 : 64)); }
+
 static size_t lay_out(const ConvGeom& g, int pass, const SpectralPlan& p, Layout* l) {
   const int64_t tiles = tiles_of(g, p, pass);
-  const size_t cells = p.along ? 64 : kFCells * 4;
   l->image = 0;
   l->map = l->image + p.image_bytes;
   l->taps = l->map + p.map_bytes;
   l->words = l->taps + p.taps_bytes;
   size_t at = l->words + align256(256 + 4 * (size_t)g.n);
-  l->zero = l->totals = l->cells_image = l->cells_map = l->largest = at;
-  // (in the place of the result's spectra: at most 32 KB for a tile, which takes 16.5 KB of them for each of more than four
-  // channels or maps, lines 2 and 1 KB)
-  l->energy = pass == VCNN_PASS_FWD ? l->map : l->image;
+  auto take = [&](size_t bytes) { const size_t from = at; at += align256(bytes); return from; };
+  // (energies in the place of the result's spectra: at most 32 KB for a tile, which takes 16.5 KB of them for each of more than four
+  // channels or maps, lines 2 and 1 KB; a kernel gradient's are as many as its kernels)
+  l->energy = l->energy_dy = pass == VCNN_PASS_FWD ? l->map : l->image;
   if (pass != VCNN_PASS_BWD_FILTER) {
-    at += align256((size_t)tiles * (p.along ? 32 : 8 * kFL));
-    l->totals = at;
-    at += align256((size_t)tiles * 8);
-    l->largest = at;
-    at += align256(p.along ? (size_t)g.k * g.c * 4 : (size_t)ceil_div((int64_t)g.k * g.c, 4) * 4);
+    l->zero = take((size_t)tiles * (p.along ? 32 : 8 * kFL));
+    l->totals = take((size_t)tiles * 8);
+    l->largest = take(p.along ? (size_t)g.k * g.c * 4 : (size_t)ceil_div((int64_t)g.k * g.c, 4) * 4);
   } else {
-    l->cells_image = at;
-    at += align256((size_t)tiles * g.c * cells);
-    l->cells_map = at;
-    at += align256((size_t)tiles * g.k * cells);
+    l->energy = p.energy_in_taps ? l->taps : take(energy_bytes(g));
+    l->energy_dy = l->energy + 8 * (size_t)g.n * g.h * g.w;
+    l->zero = take(16 * 8);
+    l->meet = take((size_t)meet_chunks(p, tiles) * (g.r * g.s + 1) * 8);
+    l->sums = take((size_t)tiles * g.k * 8);
   }
-  l->sums = at;
-  if (pass == VCNN_PASS_BWD_FILTER) at += align256((size_t)tiles * g.k * 8);
   return at;
 }
 static Layout layout(const ConvGeom& g, int pass, const SpectralPlan& p) {
@@ -545,6 +458,7 @@ bool spectral_plan(const ConvGeom& g, int pass, size_t budget, SpectralPlan* p) 
   q.image_bytes = image * (data ? q.splits : 1);
   q.taps_bytes = align256((size_t)((int64_t)g.k * g.c * taps)) * (filter ? q.splits : 1);
   q.map_bytes = align256((size_t)(tiles * g.k * spectrum));
+  q.energy_in_taps = filter && energy_bytes(g) <= q.taps_bytes;
   SpectralPlan none = q;
   none.image_bytes = none.map_bytes = none.taps_bytes = 0;
   Layout l{};
@@ -578,12 +492,11 @@ bool spectral_plan(const ConvGeom& g, int pass, size_t budget, SpectralPlan* p) 
 
 // ---- passes --------------------------------------------------------------------------------------------------------
 template <bool TAPS_A, bool CONJ_A, bool TAPS_C, bool LINES>
-static vcnn_status launch_product(ProductArgs a, int images, hipStream_t st) {
+static vcnn_status launch_product(ProductArgs a, int images, hipStream_t st) {  // (images: whose magnitudes are looked at)
   a.columns = LINES ? kLV : kFV;
   a.tiles_r = (int)ceil_div(a.rows, 16), a.tiles_c = (int)ceil_div(a.cols, 16);
   a.blocks = a.columns * a.tiles_r * a.tiles_c * a.splits;
-  const int guard_blocks = images * (a.guard.line_groups ? (int)ceil_div(a.guard.line_groups, kGuardLines) : 1);
-  hipLaunchKernelGGL((spectral_product_kernel<TAPS_A, CONJ_A, TAPS_C, LINES>), dim3((unsigned)(a.blocks + guard_blocks)), dim3(kThreads), 0, st, a);
+  hipLaunchKernelGGL((spectral_product_kernel<TAPS_A, CONJ_A, TAPS_C, LINES>), dim3((unsigned)(a.blocks + images)), dim3(kThreads), 0, st, a);
   return check_launch("spectral_product");
 }
 
@@ -596,15 +509,6 @@ static SpectralTiles tiles_for(const ConvGeom& g, const SpectralPlan& p, int cha
   t.tiles_y = p.tiles_y, t.tiles_x = p.tiles_x, t.step_y = p.step_y, t.step_x = p.step_x;
   t.lim_y = t.lim_x = kFL;
   return t;
-}
-static GuardArgs guard_for(const SpectralTiles& t, const uint32_t* cells, int win_h, int win_w, char* words) {
-  GuardArgs g{};
-  g.cells[0] = cells, g.planes[0] = t.channels;
-  g.tiles_y = t.tiles_y, g.tiles_x = t.tiles_x, g.images = t.images;
-  g.step_y = t.step_y, g.step_x = t.step_x, g.y0 = t.y0, g.x0 = t.x0, g.h = t.h, g.w = t.w, g.lim_y = t.lim_y, g.lim_x = t.lim_x;
-  g.win_y = std::max(1, (win_h + 7) / 8), g.win_x = std::max(1, (win_w + 15) / 16);
-  g.any = reinterpret_cast<uint32_t*>(words), g.image = reinterpret_cast<uint32_t*>(words + 256);
-  return g;
 }
 static SpectralWords words_at(void* workspace, const Layout& l) {
   uint32_t* const w = (uint32_t*)((char*)workspace + l.words);
@@ -625,6 +529,24 @@ static RangeArgs range_guard(const ConvGeom& g, int pass, const SpectralPlan& p,
   const int64_t depth = pass == VCNN_PASS_FWD ? g.c : g.k;
   r.grow = bits_of(depth * g.r * g.s), r.depth = (bits_of(depth) + 1) / 2;
   return r;
+}
+static MeetGuard meet_guard(const ConvGeom& g, const SpectralPlan& p, const Layout& l, void* workspace) {
+  char* const ws = (char*)workspace;
+  const int64_t tiles = tiles_of(g, p, VCNN_PASS_BWD_FILTER);
+  MeetGuard m{};
+  m.x = (const double*)(ws + l.energy), m.dy = (const double*)(ws + l.energy_dy);
+  m.chunks = meet_chunks(p, tiles), m.per_chunk = (int)ceil_div(tiles, m.chunks), m.partial = (double*)(ws + l.meet);
+  m.depth_x = (bits_of(g.c) + 1) / 2, m.depth_dy = (bits_of(g.k) + 1) / 2;
+  m.words = words_at(workspace, l);
+  return m;
+}
+static MeetDecision meet_decision(const ConvGeom& g, const SpectralPlan& p, const Layout& l, const MeetGuard& m, void* workspace) {
+  return {m.partial, m.chunks, g.r, g.s, kDarkMeet / (p.along ? kLL : kFL * kFL), bits_of(g.N), (uint64_t*)((char*)workspace + l.zero), m.words};
+}
+static vcnn_status scan_both(const ConvGeom& g, int dtype, const Layout& l, const void* x, const void* dy, void* workspace, hipStream_t st) {
+  char* const ws = (char*)workspace;
+  return launch_energies(dtype, g.n, {x, g.c, (int64_t)g.h * g.w, (double*)(ws + l.energy)}, {dy, g.k, g.P, (double*)(ws + l.energy_dy)},
+                         (uint32_t*)(ws + l.words), 64 + g.n, st);
 }
 static vcnn_status scan_energies(const ConvGeom& g, int pass, int dtype, const Layout& l, const void* src, void* workspace, hipStream_t st) {
   const bool fwd = pass == VCNN_PASS_FWD;
@@ -650,15 +572,6 @@ static SpectralLines kernel_lines(const ConvGeom& g, int maps) {
   t.p_image = g.c, t.p_channel = 1;
   return t;
 }
-static GuardArgs guard_for(const SpectralLines& t, const uint32_t* cells, int win, char* words) {
-  GuardArgs g{};
-  g.cells[0] = cells, g.planes[0] = t.channels, g.images = t.images;
-  g.line_groups = t.others * t.tiles, g.tiles_x = t.tiles;
-  g.step_x = t.step, g.x0 = t.x0, g.w = t.len, g.lim_x = t.lim;
-  g.win_x = std::max(1, (win + 15) / 16);
-  g.any = reinterpret_cast<uint32_t*>(words), g.image = reinterpret_cast<uint32_t*>(words + 256);
-  return g;
-}
 // Tile offsets of the three tensors: x starts a tile `pad` before it.  In an input gradient pixel i of the padded line gets
 // dy[i - q] w[q]: a whole line starts at dy's first pixel; a tile of a longer one starts `size` - 1 pixels before its results,
 // of which the transform wraps that many.
@@ -671,7 +584,7 @@ static vcnn_status lines_fwd(const SpectralPlan& p, int dtype, const ConvGeom& g
   float2 *const xs = (float2*)(ws + l.image), *const ys = (float2*)(ws + l.map), *const taps = (float2*)(ws + l.taps);
   uint32_t* const largest = (uint32_t*)(ws + l.largest);
   const WindowGuard guard = window_guard(g, VCNN_PASS_FWD, dtype, l, kLL, workspace);
-  const SpectralExcept except{guard.words.image, guard.zero, guard.words.zeros};
+  const SpectralExcept except{1, guard.words.image, guard.zero, guard.words.zeros};
   const int64_t tiles = tiles_of(g, p, VCNN_PASS_FWD);
   const int esize = dtype == VCNN_BF16 ? 2 : 4;
   SpectralLines tx = lines_for(g, p, g.c, g.h, g.w);
@@ -683,10 +596,10 @@ static vcnn_status lines_fwd(const SpectralPlan& p, int dtype, const ConvGeom& g
   for (int k0 = 0; k0 < g.k; k0 += p.part) {
     const int maps = std::min(p.part, g.k - k0);
     const bool last = k0 + maps == g.k;
-    LineJob image{tx, tiles * g.c, x, xs, nullptr, 0, nullptr};
+    LineJob image{tx, tiles * g.c, x, xs, nullptr, nullptr};
     if (k0 > 0) image.t.count = 0;  // (they stay)
-    const LineJob kernels{kernel_lines(g, maps), (int64_t)maps * g.c, (const char*)w + (int64_t)k0 * g.K * esize, taps, largest + (int64_t)k0 * g.c, 1, nullptr};
-    if (vcnn_status s = launch_line_spectra(dtype, image, kernels, nullptr, 0, st)) return s;
+    const LineJob kernels{kernel_lines(g, maps), (int64_t)maps * g.c, (const char*)w + (int64_t)k0 * g.K * esize, taps, largest + (int64_t)k0 * g.c, nullptr};
+    if (vcnn_status s = launch_line_spectra(dtype, image, kernels, {}, st)) return s;
     ProductArgs a{};
     a.A = taps, a.B = xs, a.C = ys;
     a.rows = maps, a.cols = (int)tiles, a.depth = g.c;
@@ -694,7 +607,7 @@ static vcnn_status lines_fwd(const SpectralPlan& p, int dtype, const ConvGeom& g
     a.b_col = 1, a.b_z = tiles, a.b_planes = tiles * g.c;
     a.c_row = tiles, a.c_col = 1, a.c_planes = tiles * maps;
     a.splits = p.splits, a.per_split = p.per_split, a.flush = p.flush, a.rows_inner = 1;
-    a.range = range_guard(g, VCNN_PASS_FWD, p, l, workspace), a.col_images = (int)(tiles / g.n);
+    a.range = range_guard(g, VCNN_PASS_FWD, p, l, workspace), a.declined = guard.words.any, a.col_images = (int)(tiles / g.n);
     if (vcnn_status s = launch_product<false, true, false, true>(a, last ? g.n : 0, st)) return s;
     ty.first = k0, ty.count = maps;
     if (vcnn_status s = launch_line_inverse(ty, tiles * maps, dtype, ys, 0, 1, y, bias, relu, nullptr, 0, 0, nullptr, except, st)) return s;
@@ -714,11 +627,11 @@ static vcnn_status lines_bwd_data(const SpectralPlan& p, int dtype, const ConvGe
   SpectralLines tdy = lines_for(g, p, g.k, g.oh, g.ow), tdx = lines_for(g, p, g.c, g.h, g.w);
   place_dx(tdx.len + 2 * pad <= kLL, g.r * g.s, pad, &tdy.x0, &tdx.x0);
   tdx.lim = std::min(p.step_x, tdx.len);
-  const LineJob image{tdy, tiles * g.k, dy, ys, nullptr, 0, nullptr};
-  const LineJob kernels{kernel_lines(g, g.k), (int64_t)g.k * g.c, w, taps, largest, 1, nullptr};
+  const LineJob image{tdy, tiles * g.k, dy, ys, nullptr, nullptr};
+  const LineJob kernels{kernel_lines(g, g.k), (int64_t)g.k * g.c, w, taps, largest, nullptr};
   if (vcnn_status s = scan_energies(g, VCNN_PASS_BWD_DATA, dtype, l, dy, workspace, st)) return s;
   if (vcnn_status s = launch_guard_lines(guard, tdy, tdx, g.r * g.s, st)) return s;
-  if (vcnn_status s = launch_line_spectra(dtype, image, kernels, nullptr, 0, st)) return s;
+  if (vcnn_status s = launch_line_spectra(dtype, image, kernels, {}, st)) return s;
   ProductArgs a{};
   a.A = taps, a.B = ys, a.C = xs;
   a.rows = g.c, a.cols = (int)tiles, a.depth = g.k;
@@ -726,10 +639,10 @@ static vcnn_status lines_bwd_data(const SpectralPlan& p, int dtype, const ConvGe
   a.b_col = 1, a.b_z = tiles, a.b_planes = tiles * g.k;
   a.c_row = tiles, a.c_col = 1, a.c_planes = tiles * g.c;
   a.splits = p.splits, a.per_split = p.per_split, a.flush = p.flush, a.rows_inner = 1, a.c_slice = (int64_t)(p.image_bytes / p.splits / 8);
-  a.range = range_guard(g, VCNN_PASS_BWD_DATA, p, l, workspace), a.col_images = (int)(tiles / g.n);
+  a.range = range_guard(g, VCNN_PASS_BWD_DATA, p, l, workspace), a.declined = guard.words.any, a.col_images = (int)(tiles / g.n);
   if (vcnn_status s = launch_product<false, false, false, true>(a, g.n, st)) return s;
   return launch_line_inverse(tdx, tiles * g.c, dtype, xs, a.c_slice, p.splits, dx, nullptr, 0, nullptr, 0, 0, nullptr,
-                             {guard.words.image, guard.zero, guard.words.zeros}, st);
+                             {1, guard.words.image, guard.zero, guard.words.zeros}, st);
 }
 
 static vcnn_status lines_filter(const SpectralPlan& p, int dtype, const ConvGeom& g, const void* x, const void* dy, float* dw,
@@ -737,14 +650,17 @@ static vcnn_status lines_filter(const SpectralPlan& p, int dtype, const ConvGeom
   const Layout l = layout(g, VCNN_PASS_BWD_FILTER, p);
   char* const ws = (char*)workspace;
   float2 *const xs = (float2*)(ws + l.image), *const ys = (float2*)(ws + l.map), *const taps = (float2*)(ws + l.taps);
-  uint32_t *const cells_x = (uint32_t*)(ws + l.cells_image), *const cells_dy = (uint32_t*)(ws + l.cells_map);
   double* const sums = (double*)(ws + l.sums);
+  const MeetGuard meet = meet_guard(g, p, l, workspace);
+  const MeetDecision decision = meet_decision(g, p, l, meet, workspace);
   const int64_t tiles = tiles_of(g, p, VCNN_PASS_BWD_FILTER);
   SpectralLines tx = lines_for(g, p, g.c, g.h, g.w), tdy = lines_for(g, p, g.k, g.oh, g.ow);
   tx.x0 = -(p.along == 1 ? g.pw : g.ph);
   tdy.lim = std::min(p.step_x, tdy.len);  // every output pixel in one tile
-  const LineJob image{tx, tiles * g.c, x, xs, cells_x, 0, nullptr}, map{tdy, tiles * g.k, dy, ys, cells_dy, 0, db ? sums : nullptr};
-  if (vcnn_status s = launch_line_spectra(dtype, image, map, (uint32_t*)(ws + l.words), 64 + g.n, st)) return s;
+  const LineJob image{tx, tiles * g.c, x, xs, nullptr, nullptr}, map{tdy, tiles * g.k, dy, ys, nullptr, db ? sums : nullptr};
+  if (vcnn_status s = scan_both(g, dtype, l, x, dy, workspace, st)) return s;
+  if (vcnn_status s = launch_meet_lines(meet, tx, tdy, g.r * g.s, st)) return s;
+  if (vcnn_status s = launch_line_spectra(dtype, image, map, decision, st)) return s;
   ProductArgs a{};
   a.A = ys, a.B = xs, a.C = taps;
   a.rows = g.k, a.cols = g.c, a.depth = (int)tiles;
@@ -752,12 +668,10 @@ static vcnn_status lines_filter(const SpectralPlan& p, int dtype, const ConvGeom
   a.b_col = tiles, a.b_z = 1, a.b_planes = tiles * g.c;
   a.c_row = g.c, a.c_col = 1, a.c_planes = (int64_t)g.k * g.c;
   a.splits = p.splits, a.per_split = p.per_split, a.flush = p.flush, a.c_slice = (int64_t)(p.taps_bytes / p.splits / 8);
-  a.guard = guard_for(tx, cells_x, tdy.lim, ws + l.words);
-  a.guard.cells[1] = cells_dy, a.guard.planes[1] = g.k;
-  a.guard.grow = bits_of(g.N);
-  if (vcnn_status s = launch_product<false, true, false, true>(a, g.n, st)) return s;
+  a.declined = meet.words.any;
+  if (vcnn_status s = launch_product<false, true, false, true>(a, 0, st)) return s;
   return launch_line_inverse(kernel_lines(g, g.k), (int64_t)g.k * g.c, VCNN_F32, taps, a.c_slice, p.splits, dw, nullptr, 0, sums,
-                             (int)tiles, g.k, db, {}, st);
+                             (int)tiles, g.k, db, {0, meet.words.any, decision.zero, meet.words.zeros}, st);
 }
 
 vcnn_status launch_spectral_fwd(const SpectralPlan& p, int dtype, const ConvGeom& g, const void* x, const void* w, const float* bias,
@@ -770,7 +684,7 @@ vcnn_status launch_spectral_fwd(const SpectralPlan& p, int dtype, const ConvGeom
   float2* const taps = (float2*)(ws + l.taps);
   uint32_t* const largest = (uint32_t*)(ws + l.largest);
   const WindowGuard guard = window_guard(g, VCNN_PASS_FWD, dtype, l, kFL * kFL, workspace);
-  const SpectralExcept except{guard.words.image, guard.zero, guard.words.zeros};
+  const SpectralExcept except{1, guard.words.image, guard.zero, guard.words.zeros};
   const int64_t tiles = tiles_of(g, p, VCNN_PASS_FWD);
   const int esize = dtype == VCNN_BF16 ? 2 : 4;
   SpectralTiles tx = tiles_for(g, p, g.c, g.h, g.w);
@@ -779,7 +693,7 @@ vcnn_status launch_spectral_fwd(const SpectralPlan& p, int dtype, const ConvGeom
   ty.lim_y = std::min(p.step_y, g.oh), ty.lim_x = std::min(p.step_x, g.ow);
   if (vcnn_status s = scan_energies(g, VCNN_PASS_FWD, dtype, l, x, workspace, st)) return s;
   if (vcnn_status s = launch_guard_planes(guard, tx, ty, g.r, g.s, st)) return s;
-  if (vcnn_status s = launch_plane_spectra(tx, dtype, x, xs, nullptr, nullptr, nullptr, 0, guard.words.image, st)) return s;
+  if (vcnn_status s = launch_plane_spectra(tx, dtype, x, xs, nullptr, guard.words.image, 1, {}, st)) return s;
   for (int k0 = 0; k0 < g.k; k0 += p.part) {
     const int maps = std::min(p.part, g.k - k0);
     const bool last = k0 + maps == g.k;
@@ -792,7 +706,7 @@ vcnn_status launch_spectral_fwd(const SpectralPlan& p, int dtype, const ConvGeom
     a.b_col = g.c, a.b_z = 1, a.b_planes = tiles * g.c;
     a.c_row = 1, a.c_col = maps, a.c_planes = tiles * maps;
     a.splits = p.splits, a.per_split = p.per_split, a.flush = p.flush;
-    a.range = range_guard(g, VCNN_PASS_FWD, p, l, workspace), a.col_images = (int)(tiles / g.n);
+    a.range = range_guard(g, VCNN_PASS_FWD, p, l, workspace), a.declined = guard.words.any, a.col_images = (int)(tiles / g.n);
     if (vcnn_status s = launch_product<true, true, false, false>(a, last ? g.n : 0, st)) return s;
     ty.first = k0, ty.count = maps;
     if (vcnn_status s = launch_plane_inverse(ty, dtype, ys, 0, 1, y, bias, relu, except, st)) return s;
@@ -819,7 +733,7 @@ vcnn_status launch_spectral_bwd_data(const SpectralPlan& p, int dtype, const Con
   tdx.lim_y = std::min(p.step_y, g.h), tdx.lim_x = std::min(p.step_x, g.w);
   if (vcnn_status s = scan_energies(g, VCNN_PASS_BWD_DATA, dtype, l, dy, workspace, st)) return s;
   if (vcnn_status s = launch_guard_planes(guard, tdy, tdx, g.r, g.s, st)) return s;
-  if (vcnn_status s = launch_plane_spectra(tdy, dtype, dy, ys, nullptr, nullptr, nullptr, 0, guard.words.image, st)) return s;
+  if (vcnn_status s = launch_plane_spectra(tdy, dtype, dy, ys, nullptr, guard.words.image, 1, {}, st)) return s;
   if (vcnn_status s = launch_taps_spectra(dtype, w, (int64_t)g.k * g.c, g.r, g.s, taps, largest, st)) return s;
   ProductArgs a{};
   a.A = taps, a.B = ys, a.C = xs;
@@ -828,9 +742,9 @@ vcnn_status launch_spectral_bwd_data(const SpectralPlan& p, int dtype, const Con
   a.b_col = g.k, a.b_z = 1, a.b_planes = tiles * g.k;
   a.c_row = 1, a.c_col = g.c, a.c_planes = tiles * g.c;
   a.splits = p.splits, a.per_split = p.per_split, a.flush = p.flush, a.c_slice = (int64_t)(p.image_bytes / p.splits / 8);
-  a.range = range_guard(g, VCNN_PASS_BWD_DATA, p, l, workspace), a.col_images = (int)(tiles / g.n);
+  a.range = range_guard(g, VCNN_PASS_BWD_DATA, p, l, workspace), a.declined = guard.words.any, a.col_images = (int)(tiles / g.n);
   if (vcnn_status s = launch_product<true, false, false, false>(a, g.n, st)) return s;
-  return launch_plane_inverse(tdx, dtype, xs, a.c_slice, p.splits, dx, nullptr, 0, {guard.words.image, guard.zero, guard.words.zeros}, st);
+  return launch_plane_inverse(tdx, dtype, xs, a.c_slice, p.splits, dx, nullptr, 0, {1, guard.words.image, guard.zero, guard.words.zeros}, st);
 }
 
 vcnn_status launch_spectral_filter(const SpectralPlan& p, int dtype, const ConvGeom& g, const void* x, const void* dy, float* dw,
@@ -841,16 +755,18 @@ vcnn_status launch_spectral_filter(const SpectralPlan& p, int dtype, const ConvG
   float2* const xs = (float2*)(ws + l.image);
   float2* const ys = (float2*)(ws + l.map);
   float2* const taps = (float2*)(ws + l.taps);
-  uint32_t* const cells_x = (uint32_t*)(ws + l.cells_image);
-  uint32_t* const cells_dy = (uint32_t*)(ws + l.cells_map);
+  const MeetGuard meet = meet_guard(g, p, l, workspace);
+  const MeetDecision decision = meet_decision(g, p, l, meet, workspace);
   double* const sums = (double*)(ws + l.sums);
   const int64_t tiles = tiles_of(g, p, VCNN_PASS_BWD_FILTER);
   SpectralTiles tx = tiles_for(g, p, g.c, g.h, g.w);
   tx.y0 = -g.ph, tx.x0 = -g.pw;
   SpectralTiles tdy = tiles_for(g, p, g.k, g.oh, g.ow);
   tdy.lim_y = std::min(p.step_y, g.oh), tdy.lim_x = std::min(p.step_x, g.ow);  // every output pixel in one tile
-  if (vcnn_status s = launch_plane_spectra(tx, dtype, x, xs, cells_x, nullptr, (uint32_t*)(ws + l.words), 64 + g.n, nullptr, st)) return s;
-  if (vcnn_status s = launch_plane_spectra(tdy, dtype, dy, ys, cells_dy, db ? sums : nullptr, nullptr, 0, nullptr, st)) return s;
+  if (vcnn_status s = scan_both(g, dtype, l, x, dy, workspace, st)) return s;
+  if (vcnn_status s = launch_meet_planes(meet, tx, tdy, g.r, g.s, st)) return s;
+  if (vcnn_status s = launch_plane_spectra(tx, dtype, x, xs, nullptr, nullptr, 0, decision, st)) return s;
+  if (vcnn_status s = launch_plane_spectra(tdy, dtype, dy, ys, db ? sums : nullptr, meet.words.any, 0, {}, st)) return s;
   ProductArgs a{};
   a.A = ys, a.B = xs, a.C = taps;
   a.rows = g.k, a.cols = g.c, a.depth = (int)tiles;
@@ -858,11 +774,10 @@ vcnn_status launch_spectral_filter(const SpectralPlan& p, int dtype, const ConvG
   a.b_col = 1, a.b_z = g.c, a.b_planes = tiles * g.c;
   a.c_row = g.c, a.c_col = 1, a.c_planes = (int64_t)g.k * g.c;
   a.splits = p.splits, a.per_split = p.per_split, a.flush = p.flush, a.c_slice = (int64_t)(p.taps_bytes / p.splits / 8);
-  a.guard = guard_for(tx, cells_x, tdy.lim_y, tdy.lim_x, ws + l.words);
-  a.guard.cells[1] = cells_dy, a.guard.planes[1] = g.k;
-  a.guard.grow = bits_of(g.N);
-  if (vcnn_status s = launch_product<false, true, true, false>(a, g.n, st)) return s;
-  return launch_taps_inverse(taps, a.c_slice, p.splits, (int64_t)g.k * g.c, g.r, g.s, dw, sums, (int)tiles, g.k, db, st);
+  a.declined = meet.words.any;
+  if (vcnn_status s = launch_product<false, true, true, false>(a, 0, st)) return s;
+  return launch_taps_inverse(taps, a.c_slice, p.splits, (int64_t)g.k * g.c, g.r, g.s, dw, sums, (int)tiles, g.k, db,
+                             {0, meet.words.any, decision.zero, meet.words.zeros}, st);
 }
 
 Declined spectral_declined(const ConvGeom& g, int pass, const SpectralPlan& p, const void* workspace) {

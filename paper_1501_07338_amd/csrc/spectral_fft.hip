@@ -66,40 +66,53 @@ __device__ __forceinline__ void ifft64(cd (&v)[8], cd* row, int j, cd w) {
   dft8<true>(v);
 }
 
+// By one block of 256 threads (spectral.h).
+__device__ void decide_meeting(const MeetDecision& m, uint64_t* zero) {
+  const int tid = threadIdx.x, taps = m.r * m.s;
+  if (tid < 16) zero[tid] = 0;
+  __syncthreads();
+  if (tid < taps) {
+    double meets = 0, total = 0;
+#pragma unroll 8
+    for (int c = 0; c < m.chunks; ++c) meets += m.partial[(int64_t)c * (taps + 1) + tid], total += m.partial[(int64_t)c * (taps + 1) + taps];
+    bool bad = !(total < __builtin_inf());
+    if (total > 0) {
+      const int norms = ((__double2hiint(total) >> 20) - 1023) >> 1;  // of the product of two of them
+      bad |= norms + 1 + 24 + m.grow > 126 || norms < -80 || (meets != 0 && !(meets >= total * m.share));
+    }
+    if (bad) *m.words.any = 1;
+    if (meets == 0) {
+      const int row = m.r == 1 || m.s == 1 ? tid >> 6 : tid / m.s, bit = m.r == 1 || m.s == 1 ? tid & 63 : tid % m.s;
+      atomicOr((unsigned long long*)zero + row, 1ull << bit);
+      *m.words.zeros = 1;
+    }
+  }
+  __syncthreads();
+  if (tid < 16) m.zero[tid] = zero[tid];
+}
+
 // ---- planes ------------------------------------------------------------------------------------------------------
 struct PlaneArgs {
   SpectralTiles t;
   const void* src;
   float2* spectra;
-  uint32_t* cells;
   double* sums;
-  uint32_t* words;
-  int cleared;
   const uint32_t* declined;
+  int per_image;
   int64_t planes;
+  MeetDecision decide;
 };
-
-// The largest of v[0..7] over a wave: lane l gets that of v[((l >> 3) & 1) * 4 + (l >> 1 & 3)].  (By general shuffles, of 16
-// values, this took 45 of 106 us on 8192 planes.)
-__device__ __forceinline__ uint32_t max_scatter(const uint32_t (&v)[8], int lane) {
-  uint32_t a[4], b[2], c;
-  keep_half<kMirror16, 4>(v, lane & 8, a);
-  keep_half<kMirror8, 2>(a, lane & 4, b);
-  keep_half<kSwap2, 1>(b, lane & 2, &c);
-  c = max(c, moved<kSwap1>(c));
-  c = max(c, (uint32_t)__shfl_xor((int)c, 16));
-  return max(c, (uint32_t)__shfl_xor((int)c, 32));
-}
 
 template <typename T>
 __global__ __launch_bounds__(kThreads) void plane_spectra_kernel(PlaneArgs a) {
   __shared__ cd z[32 * kPitch];
   const int tid = threadIdx.x, j = tid & 7, q = tid >> 3;
   const int64_t p = blockIdx.x;
+  if (p == a.planes) return decide_meeting(a.decide, reinterpret_cast<uint64_t*>(z));
   const SpectralTiles& t = a.t;
   const int c = (int)(p % t.count), tx = (int)(p / t.count % t.tiles_x), ty = (int)(p / t.count / t.tiles_x % t.tiles_y);
   const int64_t n = p / t.count / t.tiles_x / t.tiles_y;
-  const bool leaves = a.declined && a.declined[n];
+  const uint32_t leaves = a.declined && !a.sums ? a.declined[a.per_image ? n : 0] : 0;  // (looked at where its latency is over)
   const T* const src = (const T*)a.src + (n * t.channels + t.first + c) * ((int64_t)t.h * t.w);
   const int y0 = ty * t.step_y + t.y0, x0 = tx * t.step_x + t.x0;
   // the pixels of the transform that lie in the tile and in the plane
@@ -114,7 +127,7 @@ __global__ __launch_bounds__(kThreads) void plane_spectra_kernel(PlaneArgs a) {
       const bool in = ly >= top && ly < bottom && lx >= left && lx < right;
       (half ? hi : lo)[i] = ld(src + (unsigned)(in ? at + 32 * half * t.w + 8 * i : 0));
     }
-  if (leaves) return;  // (here, and not in front of the loads, the word's latency costs nothing)
+  if (leaves) return;
 #pragma unroll
   for (int half = 0; half < 2; ++half)  // (all loads in flight before the first is looked at)
 #pragma unroll
@@ -122,23 +135,10 @@ __global__ __launch_bounds__(kThreads) void plane_spectra_kernel(PlaneArgs a) {
       const int ly = q + 32 * half, lx = j + 8 * i;
       if (!(ly >= top && ly < bottom && lx >= left && lx < right)) (half ? hi : lo)[i] = 0.f;
     }
-  if (p == 0)
-    for (int i = tid; i < a.cleared; i += kThreads) a.words[i] = 0;
   const cd w = kRoot64[j];
   cd v[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) v[i] = {(double)lo[i], (double)hi[i]};
-  if (a.cells) {  // wave b holds the rows of cells b (lo) and b + 4 (hi); the columns j + 16 i and j + 8 + 16 i are those of a cell
-    uint32_t m[8];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      m[i] = max(__float_as_uint(lo[2 * i]) & 0x7fffffffu, __float_as_uint(lo[2 * i + 1]) & 0x7fffffffu);
-      m[i + 4] = max(__float_as_uint(hi[2 * i]) & 0x7fffffffu, __float_as_uint(hi[2 * i + 1]) & 0x7fffffffu);
-    }
-    const int lane = tid & 63;
-    const uint32_t largest = max_scatter(m, lane);
-    if (lane < 16 && (lane & 1) == 0) a.cells[p * kFCells + ((tid >> 6) + 4 * (lane >> 3)) * 4 + (lane >> 1 & 3)] = largest;
-  }
   fft64(v, z + q * kPitch, j, w);  // rows q and q + 32
 #pragma unroll
   for (int k = 0; k < 8; ++k) z[q * kPitch + j + 8 * k] = v[k];
@@ -203,7 +203,8 @@ __global__ __launch_bounds__(kThreads) void plane_inverse_kernel(InverseArgs a) 
   const int64_t p = blockIdx.x;
   const SpectralTiles& t = a.t;
   const int64_t tile = p / t.count, n = tile / t.tiles_x / t.tiles_y;
-  const bool leaves = a.except.declined && a.except.declined[n], zeros = a.except.zero && *a.except.zeros;
+  // (looked at where their latency is over)
+  const uint32_t leaves = a.except.declined ? a.except.declined[a.except.per_image ? n : 0] : 0, zeros = a.except.zero ? *a.except.zeros : 0;
   const cd w = kRoot64[j];
   const int col = q;
   cd v[8];
@@ -240,7 +241,7 @@ __global__ __launch_bounds__(kThreads) void plane_inverse_kernel(InverseArgs a) 
     for (int k = 0; k < 8; ++k) v[k] = {v[k].x - r[k].y, v[k].y + r[k].x};
   }
   ifft64(v, z + col * kPitch, j, w);
-  if (leaves) return;  // (here the word's latency costs nothing)
+  if (leaves) return;
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
@@ -339,13 +340,14 @@ __device__ __forceinline__ void add_sums(const double* sums, int count, int maps
 __global__ __launch_bounds__(kThreads) void taps_inverse_kernel(const float2* __restrict__ spectra, int64_t slice, int slices,
                                                                 int64_t kernels, int r, int s, float* __restrict__ dw,
                                                                 const double* __restrict__ sums, int sum_planes, int maps,
-                                                                float* __restrict__ db, int blocks) {
+                                                                float* __restrict__ db, int blocks, SpectralExcept except) {
   __shared__ cd z[32 * kPitch];
   const int tid = threadIdx.x, j = tid & 7, q = tid >> 3;
   if ((int)blockIdx.x >= blocks) {  // the bias gradient
     add_sums(sums, sum_planes, maps, ((int)blockIdx.x - blocks) * 4 + (tid >> 6), db);
     return;
   }
+  const uint32_t leaves = *except.declined, zeros = *except.zeros;  // (looked at where their latency is over)
   const int64_t first = (int64_t)blockIdx.x * 4;
   for (int i = tid; i < kFV * 32; i += kThreads) {
     const int col = i >> 5, tr = i & 31;
@@ -365,6 +367,7 @@ __global__ __launch_bounds__(kThreads) void taps_inverse_kernel(const float2* __
       row[64 - col] = {lower.x + upper.y, upper.x - lower.y};
     }
   }
+  if (leaves) return;
   __syncthreads();
   const cd w = kRoot64[j];
   cd v[8];
@@ -374,12 +377,15 @@ __global__ __launch_bounds__(kThreads) void taps_inverse_kernel(const float2* __
   const int64_t kernel = first + (q >> 3);
   if (kernel >= kernels) return;
 #pragma unroll
-  for (int half = 0; half < 2; ++half)
+  for (int half = 0; half < 2; ++half) {
+    const int y = (q & 7) + 8 * half;
+    const uint64_t zero = zeros ? except.zero[y] : 0;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      const int y = (q & 7) + 8 * half, x = j + 8 * i;
-      if (y < r && x < s) dw[(kernel * r + y) * s + x] = (float)((half ? v[i].y : v[i].x) * (1.0 / 4096));
+      const int x = j + 8 * i;
+      if (y < r && x < s) dw[(kernel * r + y) * s + x] = zero >> x & 1 ? 0.f : (float)((half ? v[i].y : v[i].x) * (1.0 / 4096));
     }
+  }
 }
 
 // ---- lines -------------------------------------------------------------------------------------------------------
@@ -428,8 +434,8 @@ __device__ __forceinline__ void exchange(cd (&v)[16], cd* row, int j) {
 struct Line {
   int64_t at;      // of its first sample (before the tile's offset) in the tensor
   int64_t plane;   // index of its spectrum
-  int64_t cell;    // index of its cells
   int64_t group;   // index of the lines of all channels it is one of
+  int64_t cell;    // group by group
   int channel, start, image;
 };
 __device__ __forceinline__ Line line_of(const SpectralLines& t, unsigned id) {
@@ -448,8 +454,8 @@ __device__ __forceinline__ Line line_of(const SpectralLines& t, unsigned id) {
 struct LineArgs {
   LineJob job[2];
   int first_blocks;  // blocks of the first job
-  uint32_t* words;
-  int cleared;
+  int blocks;        // of both; another one decides
+  MeetDecision decide;
 };
 
 template <typename T>
@@ -458,8 +464,7 @@ __global__ __launch_bounds__(kThreads) void line_spectra_kernel(LineArgs args) {
   __shared__ int plane_of[32];
   __shared__ double unscale_of[32];
   const int tid = threadIdx.x, j = tid & 15, q = tid >> 4;
-  if (blockIdx.x == 0)
-    for (int i = tid; i < args.cleared; i += kThreads) args.words[i] = 0;
+  if ((int)blockIdx.x >= args.blocks) return decide_meeting(args.decide, reinterpret_cast<uint64_t*>(z));
   const bool second = (int)blockIdx.x >= args.first_blocks;
   const LineJob& a = args.job[second];
   const SpectralLines& t = a.t;
@@ -485,30 +490,21 @@ __global__ __launch_bounds__(kThreads) void line_spectra_kernel(LineArgs args) {
 #pragma unroll
   for (int half = 0; half < 2; ++half) {
     const int x0 = l[half].start + t.x0, left = max(0, -x0), right = first + half < lines ? min(t.lim, t.len - x0) : 0;
-    uint32_t m[16], b[8], c[4], e[2], largest;
+    uint32_t m[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       const int x = j + 16 * i;
       if (!(x >= left && x < right)) f[half][i] = 0.f;
       m[i] = __float_as_uint(f[half][i]) & 0x7fffffffu;
     }
-    // cell i: samples 16 i to 16 i + 15
-    keep_half<kMirror16, 8>(m, j & 8, b);
-    keep_half<kMirror8, 4>(b, j & 4, c);
-    keep_half<kSwap2, 2>(c, j & 2, e);
-    keep_half<kSwap1, 1>(e, j & 1, &largest);
-    uint32_t top = largest;  // of the line
+    uint32_t top = 0;  // the line's largest
+#pragma unroll
+    for (int i = 0; i < 16; ++i) top = max(top, m[i]);
     top = max(top, moved<kMirror16>(top));
     top = max(top, moved<kMirror8>(top));
     top = max(top, moved<kSwap2>(top));
     top = max(top, moved<kSwap1>(top));
-    if (a.cells) {
-      if (a.whole) {
-        if (first + half < lines && j == 0) a.cells[l[half].cell] = top;
-      } else if (first + half < lines) {
-        a.cells[l[half].cell * 16 + j] = largest;
-      }
-    }
+    if (a.largest && first + half < lines && j == 0) a.largest[l[half].cell] = top;
     const bool finite = top < 0x7f800000u;
     spoilt[half] = !finite;
     if (a.sums && __any(!finite)) {  // the sum of such a line as it is
@@ -575,7 +571,7 @@ __global__ __launch_bounds__(kThreads) void line_inverse_kernel(LineInverseArgs 
   if ((int)blockIdx.x >= a.blocks) return add_sums(a.sums, a.sum_planes, a.maps, ((int)blockIdx.x - a.blocks) * 4 + (tid >> 6), a.db);
   __shared__ int plane_of[32];
   __shared__ uint32_t top_of[4][16];
-  const bool zeros = a.except.zero && *a.except.zeros;
+  const uint32_t zeros = a.except.zero ? *a.except.zeros : 0;
   const int lines = (int)a.lines;
   if (tid < 32) plane_of[tid] = (int)line_of(t, min((int)blockIdx.x * 32 + tid, lines - 1)).plane;
   __syncthreads();
@@ -636,14 +632,14 @@ __global__ __launch_bounds__(kThreads) void line_inverse_kernel(LineInverseArgs 
     const int id = blockIdx.x * 32 + 2 * q + half;
     if (id >= lines) continue;
     const Line l = line_of(t, id);
-    if (a.except.declined && a.except.declined[l.image]) continue;
+    if (a.except.declined && a.except.declined[a.except.per_image ? l.image : 0]) continue;
     T* const dst = (T*)a.dst + l.at;
     const float bias = a.bias ? a.bias[l.channel] : 0.f;
     const uint32_t high = top(q, half);
     const double unscale = high && finite(high) ? ldexp(1.0 / 256, exponent(high)) : 0.0;
     uint64_t zero[4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) zero[k] = zeros ? a.except.zero[l.group * 4 + k] >> j : 0;
+    for (int k = 0; k < 4; ++k) zero[k] = zeros ? a.except.zero[(a.except.per_image ? l.group * 4 : 0) + k] >> j : 0;
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       const int lx = j + 16 * i - t.x0, x = l.start + lx;
@@ -656,11 +652,12 @@ __global__ __launch_bounds__(kThreads) void line_inverse_kernel(LineInverseArgs 
 }
 
 // ---- launches ----------------------------------------------------------------------------------------------------
-vcnn_status launch_plane_spectra(const SpectralTiles& t, int dtype, const void* src, float2* spectra, uint32_t* cells, double* sums,
-                                 uint32_t* words, int cleared, const uint32_t* declined, hipStream_t st) {
-  PlaneArgs a{t, src, spectra, cells, sums, words, cleared, declined, t.planes()};
-  if (dtype == VCNN_BF16) hipLaunchKernelGGL(plane_spectra_kernel<bf16>, dim3((unsigned)a.planes), dim3(kThreads), 0, st, a);
-  else hipLaunchKernelGGL(plane_spectra_kernel<float>, dim3((unsigned)a.planes), dim3(kThreads), 0, st, a);
+vcnn_status launch_plane_spectra(const SpectralTiles& t, int dtype, const void* src, float2* spectra, double* sums,
+                                 const uint32_t* declined, int per_image, const MeetDecision& decide, hipStream_t st) {
+  PlaneArgs a{t, src, spectra, sums, declined, per_image, t.planes(), decide};
+  const dim3 grid((unsigned)(a.planes + (decide.partial ? 1 : 0)));
+  if (dtype == VCNN_BF16) hipLaunchKernelGGL(plane_spectra_kernel<bf16>, grid, dim3(kThreads), 0, st, a);
+  else hipLaunchKernelGGL(plane_spectra_kernel<float>, grid, dim3(kThreads), 0, st, a);
   return check_launch("plane_spectra");
 }
 vcnn_status launch_plane_inverse(const SpectralTiles& t, int dtype, const float2* spectra, int64_t slice, int slices, void* dst,
@@ -679,16 +676,17 @@ vcnn_status launch_taps_spectra(int dtype, const void* w, int64_t kernels, int r
   return check_launch("taps_spectra");
 }
 vcnn_status launch_taps_inverse(const float2* spectra, int64_t slice, int slices, int64_t kernels, int r, int s, float* dw,
-                                const double* sums, int sum_planes, int maps, float* db, hipStream_t st) {
+                                const double* sums, int sum_planes, int maps, float* db, const SpectralExcept& except, hipStream_t st) {
   const int blocks = (int)ceil_div(kernels, 4);
   hipLaunchKernelGGL(taps_inverse_kernel, dim3((unsigned)(blocks + (db ? ceil_div(maps, 4) : 0))), dim3(kThreads), 0, st,
-                     spectra, slice, slices, kernels, r, s, dw, sums, sum_planes, maps, db, blocks);
+                     spectra, slice, slices, kernels, r, s, dw, sums, sum_planes, maps, db, blocks, except);
   return check_launch("taps_inverse");
 }
 
-vcnn_status launch_line_spectra(int dtype, const LineJob& first, const LineJob& second, uint32_t* words, int cleared, hipStream_t st) {
-  LineArgs a{{first, second}, (int)ceil_div(first.t.lines(), 32), words, cleared};
-  const dim3 grid((unsigned)(a.first_blocks + ceil_div(second.t.lines(), 32)));
+vcnn_status launch_line_spectra(int dtype, const LineJob& first, const LineJob& second, const MeetDecision& decide, hipStream_t st) {
+  LineArgs a{{first, second}, (int)ceil_div(first.t.lines(), 32), 0, decide};
+  a.blocks = (int)(a.first_blocks + ceil_div(second.t.lines(), 32));
+  const dim3 grid((unsigned)(a.blocks + (decide.partial ? 1 : 0)));
   if (dtype == VCNN_BF16) hipLaunchKernelGGL(line_spectra_kernel<bf16>, grid, dim3(kThreads), 0, st, a);
   else hipLaunchKernelGGL(line_spectra_kernel<float>, grid, dim3(kThreads), 0, st, a);
   return check_launch("line_spectra");

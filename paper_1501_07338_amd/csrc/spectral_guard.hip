@@ -5,7 +5,8 @@
 // root mean square over the WHOLE transform of what is summed there.  An output is exact to that relative to what it sums
 // itself only if its own samples are not much darker than the rest of the transform.  The windows looked at are the outputs'
 // own, pixel by pixel, with what lies outside the plane left out.  The scan and the guard take 15 us of a forward pass over 10 MB, 32 us
-// of an input gradient over 79 MB (16 38 64 64 -> 512 16 16: 671 -> 717 us in all).
+// of an input gradient over 79 MB and 32 us of a kernel gradient over both (16 38 64 64 -> 512 16 16: 672 -> 752 us in all, of which the
+// direct routes would take 3240).
 #include <algorithm>
 
 #include "elem.h"
@@ -22,34 +23,34 @@ struct EnergyArgs {
   int cleared;
 };
 
-// A block does 256 pixels of an image, four a lane (64 at a time, pieces of 128 and 256 bytes lie across cache lines that two
-// blocks then fetch: 16 512 49 49 in bfloat16 36 us), a wave a share of the channels, 32 loads in flight.
-static constexpr int kEnergyPixels = 256, kEnergyWaves = 16, kEnergyBatch = 8;
+// A block does 256 pixels of an image, four a lane, a wave a share of the channels, 32 loads in flight.  (Smaller pieces lie across
+// cache lines that two blocks then fetch: 16 512 49 49 takes 22 us, 24 with 128 pixels; in bfloat16 15, and 36 with 64.)
+static constexpr int kEnergyWaves = 16, kEnergyPixels = 256, kEnergyBatch = 8;
 template <typename T>
 __global__ __launch_bounds__(64 * kEnergyWaves) void energies_kernel(EnergyArgs a) {
-  __shared__ double part[kEnergyWaves][kEnergyPixels];
-  constexpr int PX = kEnergyPixels / 64;
+  constexpr int PX = kEnergyPixels / 64, PIXELS = kEnergyPixels, BATCH = kEnergyBatch;
+  __shared__ double part[kEnergyWaves][PIXELS];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, waves = blockDim.x >> 6;
   if (blockIdx.x == 0)
     for (int i = tid; i < a.cleared; i += blockDim.x) a.words[i] = 0;
   const bool second = (int)blockIdx.x >= a.first_blocks;
   const EnergyJob& job = a.job[second];
   const int id = (int)blockIdx.x - (second ? a.first_blocks : 0), blocks = a.blocks[second], image = id / blocks;
-  const int64_t first = (int64_t)(id - image * blocks) * kEnergyPixels + lane;
+  const int64_t first = (int64_t)(id - image * blocks) * PIXELS;
   const int each = (job.channels + waves - 1) / waves, begin = wave * each, end = min(begin + each, job.channels);
   const T* const src = (const T*)job.src + (int64_t)image * job.channels * job.pixels;
   int64_t at[PX];
   double sum[PX];
 #pragma unroll
-  for (int k = 0; k < PX; ++k) at[k] = min(first + 64 * k, job.pixels - 1), sum[k] = 0;
-  for (int c0 = begin; c0 < end; c0 += kEnergyBatch) {
-    T t[kEnergyBatch][PX];
+  for (int k = 0; k < PX; ++k) at[k] = min(first + lane + 64 * k, job.pixels - 1), sum[k] = 0;
+  for (int c0 = begin; c0 < end; c0 += BATCH) {
+    T t[BATCH][PX];
 #pragma unroll
-    for (int u = 0; u < kEnergyBatch; ++u)
+    for (int u = 0; u < BATCH; ++u)
 #pragma unroll
       for (int k = 0; k < PX; ++k) t[u][k] = src[min(c0 + u, end - 1) * job.pixels + at[k]];
 #pragma unroll
-    for (int u = 0; u < kEnergyBatch; ++u)
+    for (int u = 0; u < BATCH; ++u)
 #pragma unroll
       for (int k = 0; k < PX; ++k) {
         const double f = (double)ld(&t[u][k]);
@@ -59,17 +60,17 @@ __global__ __launch_bounds__(64 * kEnergyWaves) void energies_kernel(EnergyArgs 
 #pragma unroll
   for (int k = 0; k < PX; ++k) part[wave][lane + 64 * k] = sum[k];
   __syncthreads();
-  for (int i = tid; i < kEnergyPixels; i += blockDim.x) {
-    const int64_t pixel = first - lane + i;
-    if (pixel >= job.pixels) break;
+  for (int i = tid; i < PIXELS && first + i < job.pixels; i += blockDim.x) {
     double e = 0;
     for (int k = 0; k < waves; ++k) e += part[k][i];
-    job.energy[image * job.pixels + pixel] = e;
+    job.energy[image * job.pixels + first + i] = e;
   }
 }
 
-vcnn_status launch_energies(int dtype, int images, const EnergyJob& first, const EnergyJob& second, uint32_t* words, int cleared,
-                            hipStream_t st) {
+// (the larger operand's blocks in front)
+vcnn_status launch_energies(int dtype, int images, const EnergyJob& x, const EnergyJob& y, uint32_t* words, int cleared, hipStream_t st) {
+  const bool turn = x.channels * x.pixels < y.channels * y.pixels;
+  const EnergyJob &first = turn ? y : x, &second = turn ? x : y;
   EnergyArgs a{};
   a.job[0] = first, a.job[1] = second, a.words = words, a.cleared = cleared;
   a.blocks[0] = (int)ceil_div(first.pixels, kEnergyPixels), a.blocks[1] = (int)ceil_div(second.pixels, kEnergyPixels);
@@ -257,6 +258,110 @@ vcnn_status launch_guard_lines(const WindowGuard& g, const SpectralLines& in, co
   const int64_t lines = (int64_t)in.images * in.others * in.tiles;
   hipLaunchKernelGGL(guard_lines_kernel, dim3((unsigned)ceil_div(lines, kGuardLines)), dim3(kLL), 0, st, g, in, out, taps);
   return check_launch("guard_lines");
+}
+
+// ---- what meets at the taps of a kernel gradient ---------------------------------------------------------------------
+// dW(tap) adds x(p + tap) dy(p); over the channels and maps its variance is the sum of the energies' products, M(tap).  The error is
+// that of a correlation over the whole transform, sum over all shifts / samples = total(x) total(dy) / samples: the same for every
+// tap, however little meets at it (black areas under all that is large in dy, for one).
+//
+// A transform with nothing or with something that is not finite in either operand: 0 or not finite in the totals' product.
+__device__ __forceinline__ bool out_of_range(double energy, int depth) {
+  if (energy == 0) return false;
+  const int norm = ((__double2hiint(energy) >> 20) - 1023) >> 1;
+  return norm + 1 > 110 || norm - depth < -90;
+}
+
+static constexpr int kThreads = 256;
+// A block does a row of taps of some transforms, a thread four of them along one row of the plane.
+__global__ __launch_bounds__(kThreads) void meet_planes_kernel(MeetGuard m, SpectralTiles tx, SpectralTiles tdy, int r, int s) {
+  __shared__ double ex[kFL][kFL + 1], ey[kFL][kFL + 1];
+  __shared__ double red[4], part[4][16];
+  const int tid = threadIdx.x, q = blockIdx.x % r, chunk = blockIdx.x / r, tap = 4 * (tid & 3), row = tid >> 2;
+  const int tiles = tx.images * tx.tiles_y * tx.tiles_x, taps = r * s;
+  double acc[4] = {0, 0, 0, 0}, totals = 0;
+  for (int t = chunk * m.per_chunk; t < min(tiles, (chunk + 1) * m.per_chunk); ++t) {
+    const int ix = t % tx.tiles_x, iy = t / tx.tiles_x % tx.tiles_y;
+    const int64_t n = t / tx.tiles_x / tx.tiles_y;
+    const int x0 = ix * tx.step_x + tx.x0, y0 = iy * tx.step_y + tx.y0, dx0 = ix * tdy.step_x, dy0 = iy * tdy.step_y;
+    double e[16], f[16], sum_x = 0, sum_y = 0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      const int y = (tid >> 6) + 4 * k, x = tid & 63;
+      const bool in = (unsigned)(y0 + y) < (unsigned)tx.h && (unsigned)(x0 + x) < (unsigned)tx.w;
+      const bool out = y < tdy.lim_y && x < tdy.lim_x && dy0 + y < tdy.h && dx0 + x < tdy.w;
+      e[k] = in ? m.x[(n * tx.h + y0 + y) * tx.w + x0 + x] : 0.0;
+      f[k] = out ? m.dy[(n * tdy.h + dy0 + y) * tdy.w + dx0 + x] : 0.0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      const int y = (tid >> 6) + 4 * k, x = tid & 63;
+      ex[y][x] = e[k], ey[y][x] = f[k];
+      sum_x += e[k], sum_y += f[k];
+    }
+    if (q == 0) {
+      sum_x = block_sum(sum_x, red), sum_y = block_sum(sum_y, red);
+      totals += sum_x * sum_y;
+      if (tid == 0 && sum_x != 0 && sum_y != 0 && (out_of_range(sum_x, m.depth_x) || out_of_range(sum_y, m.depth_dy))) *m.words.any = 1;
+    }
+    __syncthreads();
+    if (row < tdy.lim_y) {  // (row + q and, of the taps there are, x + tap lie in the transform)
+      const double* const from = ex[(row + q) & 63];
+      double a = from[tap], b = from[tap + 1], c = from[tap + 2];
+      for (int x = 0; x < tdy.lim_x; ++x) {
+        const double g = ey[row][x], d = from[min(x + tap + 3, kFL - 1)];
+        acc[0] += g * a, acc[1] += g * b, acc[2] += g * c, acc[3] += g * d;
+        a = b, b = c, c = d;
+      }
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+#pragma unroll
+    for (int d = 4; d < 64; d <<= 1) acc[k] += __shfl_xor(acc[k], d);
+    if ((tid & 63) < 4) part[tid >> 6][tap + k] = acc[k];
+  }
+  __syncthreads();
+  if (tid < s) m.partial[(int64_t)chunk * (taps + 1) + q * s + tid] = (part[0][tid] + part[1][tid]) + (part[2][tid] + part[3][tid]);
+  if (tid == 0 && q == 0) m.partial[(int64_t)chunk * (taps + 1) + taps] = totals;
+}
+
+// Two threads a tap, each half of a line.
+__global__ __launch_bounds__(kThreads) void meet_lines_kernel(MeetGuard m, SpectralLines tx, SpectralLines tdy, int taps) {
+  __shared__ double ex[2 * kLL], ey[kLL];
+  __shared__ double red[4], other[kLineTaps];
+  const int tid = threadIdx.x, tap = tid & (kLineTaps - 1), from = (tid >> 7) * (kLL / 2);
+  const int lines = tx.images * tx.others * tx.tiles;
+  double acc = 0, totals = 0;
+  ex[kLL + tid] = 0;
+  for (int l = blockIdx.x * m.per_chunk; l < min(lines, ((int)blockIdx.x + 1) * m.per_chunk); ++l) {
+    const int tile = l % tx.tiles, o = l / tx.tiles % tx.others;
+    const int64_t n = l / tx.tiles / tx.others;
+    const int px = tile * tx.step + tx.x0 + tid, py = tile * tdy.step + tid;
+    const double e = (unsigned)px < (unsigned)tx.len ? m.x[n * tx.s_channel + o * tx.s_other + px * tx.s_along] : 0.0;
+    const double f = tid < tdy.lim && py < tdy.len ? m.dy[n * tdy.s_channel + o * tdy.s_other + py * tdy.s_along] : 0.0;
+    __syncthreads();
+    ex[tid] = e, ey[tid] = f;
+    const double sum_x = block_sum(e, red), sum_y = block_sum(f, red);
+    totals += sum_x * sum_y;
+    if (tid == 0 && sum_x != 0 && sum_y != 0 && (out_of_range(sum_x, m.depth_x) || out_of_range(sum_y, m.depth_dy))) *m.words.any = 1;
+#pragma unroll 8
+    for (int k = 0; k < kLL / 2; ++k) acc += ey[from + k] * ex[from + k + tap];
+  }
+  if (from) other[tap] = acc;
+  __syncthreads();
+  if (tid < taps) m.partial[(int64_t)blockIdx.x * (taps + 1) + tid] = acc + other[tid];
+  if (tid == 0) m.partial[(int64_t)blockIdx.x * (taps + 1) + taps] = totals;
+}
+
+vcnn_status launch_meet_planes(const MeetGuard& m, const SpectralTiles& x, const SpectralTiles& dy, int r, int s, hipStream_t st) {
+  hipLaunchKernelGGL(meet_planes_kernel, dim3((unsigned)(m.chunks * r)), dim3(kThreads), 0, st, m, x, dy, r, s);
+  return check_launch("meet_planes");
+}
+vcnn_status launch_meet_lines(const MeetGuard& m, const SpectralLines& x, const SpectralLines& dy, int taps, hipStream_t st) {
+  hipLaunchKernelGGL(meet_lines_kernel, dim3((unsigned)m.chunks), dim3(kThreads), 0, st, m, x, dy, taps);
+  return check_launch("meet_lines");
 }
 
 }  // namespace vcnn

@@ -321,6 +321,41 @@ def test_every_window_counts(shape, which, bf16, case):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("shape,bf16", [((11, 11, 69, 64, 60, 11, 15, 0, 0), False), ((40, 11, 64, 64, 150, 16, 16, 0, 0), False),
+                                        ((12, 41, 39, 31, 33, 12, 12, 11, 8), False), ((4, 36, 98, 41, 67, 10, 15, 0, 0), True),
+                                        ((5, 71, 217, 9, 189, 100, 1, 0, 0), False), ((5, 80, 11, 278, 77, 1, 92, 0, 0), True)])
+@pytest.mark.parametrize("case", ["1", "1e-1", "1e-2", "1e-3", "1e-5", "1e-7", "apart", "edge"])
+def test_what_meets_counts(shape, bf16, case):
+    """A kernel gradient is exact relative to what it sums, not to what the operands hold: x is black under all that is large in dy (by
+    the given ratio), an element of x far above the others is reached by nothing in dy, or some taps meet nothing at all."""
+    d, x, wt, b, dy = tensors(shape, 6100, bf16)
+    assert route(d, FILTER) == "spectral"
+    axis, size, taps, pad = (3, d.w, d.s, d.pad_w) if d.s > 1 else (2, d.h, d.r, d.pad_h)
+    at = lambda lo, hi: (slice(None),) * axis + (slice(lo, hi),)
+    half = size // 2
+    empty = []
+    if case == "apart":     # tap q meets x[p + q - pad]
+        x[at(half + taps, half + taps + 1)] *= np.float32(2.0 ** 20) if half + taps < size else 1
+        dy[at(half + pad - 1, None)] = 0
+    elif case == "edge":
+        x[at(20, None)] = 0
+        dy[at(0, 12 + pad)] = 0  # p >= 12 + pad: x[12 + q] and on
+        empty = range(8, taps)
+    else:
+        x[at(half, None)] = 0
+        dy[at(0, half + pad)] *= np.float32(float(case))
+    if bf16:
+        x, dy = bf16_round(x), bf16_round(dy)
+    got = run_pass(d, FILTER, x, wt, b, dy)
+    idx, want = probes(d, x, dy, 5)
+    have = got[0][tuple(idx.T)].astype(np.float64)
+    assert np.linalg.norm(have - want) <= 1e-6 * np.linalg.norm(want)
+    assert_close(got[1], dy.astype(np.float64).sum((0, 2, 3)), TOL, "db")
+    for q in empty:
+        assert not np.any(got[0][..., q] if d.s > 1 else got[0][..., q, :]), q
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("act", [vcnn.ACT_RELU, vcnn.ACT_TANH, vcnn.ACT_SIGMOID])
 @pytest.mark.parametrize("shape", [t[0] for t in ONE_EACH if t[1] == DATA and not t[2]])
 def test_activation_derivative(shape, act):
