@@ -78,9 +78,10 @@ enum { VCNN_PASS_FWD = 0, VCNN_PASS_BWD_FILTER = 1, VCNN_PASS_BWD_DATA = 2 };
  * gradient whose window holds only zeros is exactly zero (plus its bias), and an image with an output whose window - its own,
  * clipped at the border - has less than 1/16 of the root mean square of its transform (over all channels; or in all less
  * than a quarter of the norm of one average pixel; in bfloat16 1/32 of either), with an infinity or NaN, or with magnitudes
- * whose products leave the float range is computed by the float kernel, in its own time.  The error of an output is then a few
- * 1e-7 times the norm of what its window holds times that of its kernel (4e-6 at most).  A kernel gradient is left to the float
- * kernel, all of it, where at some tap the energies that meet come to less than 1/16 of their mean over all shifts (so that its
+ * whose products leave the float range is computed by a direct route enqueued behind (two terms or bfloat16 where that is
+ * faster than the float kernel), in its own time and that of the decision.  The error of an output is then a few
+ * 1e-7 times the norm of what its window holds times that of its kernel (4e-6 at most).  A kernel gradient is left to the
+ * direct route, all of it, where at some tap the energies that meet come to less than 1/16 of their mean over all shifts (so that its
  * error stays below 1e-6 of what the tap sums); a tap at which nothing meets is exactly zero. */
 enum { VCNN_ALGO_AUTO = 0, VCNN_ALGO_EXPLICIT = 1, VCNN_ALGO_IMPLICIT = 2, VCNN_ALGO_FOLD = 3, VCNN_ALGO_FFT = 4,
        VCNN_ALGO_SPLIT = 5 };
@@ -116,7 +117,8 @@ vcnn_status vcnn_conv_out_shape(const vcnn_conv_desc* d, int32_t* oh, int32_t* o
  * query asks for the float kernel's workspace only (often 0), and a call that brings just that runs it; one that brings
  * more (64 MiB will do) takes the two-term kernels and works through the batch in parts:
  * vcnn_conv_route tells what a size buys.  The passes through the Fourier domain ask for their spectra: up to 1 GiB, a
- * forward pass 64 MiB (it works through its maps in parts; more workspace, fewer parts). */
+ * forward pass 64 MiB (it works through its maps in parts; more workspace, fewer parts).  An input gradient that ran in
+ * a few MiB before then asks for hundreds: it still runs with less, down to what the direct routes need. */
 vcnn_status vcnn_conv_workspace_bytes(const vcnn_conv_desc* d, int32_t pass, size_t* bytes);
 /* The route the given pass takes with that many bytes of aligned workspace, under the present VCNN_ALGO_* choice, as a
  * short static string (for diagnostics and tests): "two_term", "two_term_fold" and "two_term_pointwise" are the fp32

@@ -105,7 +105,7 @@ static bool fold_beats_halo(const ConvGeom& g, const HaloPlan& hp, const FoldPla
 
 // Which realisation a pass uses for a given shape.  The same decision drives the workspace query and
 // the launch, so the two always agree.
-enum Path { PATH_EXPLICIT, PATH_POINTWISE, PATH_FEW_OUT, PATH_FEW_IN, PATH_DIRECT_FILTER, PATH_HALO, PATH_HALO_FILTER, PATH_HALO_BF16, PATH_FILTER_BF16, PATH_HALO_FILTER_BF16, PATH_FEW_COLS_FILTER, PATH_SMALL, PATH_SMALL_BWD, PATH_FOLD, PATH_FFT, PATH_TAPS, PATH_POINTWISE_BF16, PATH_SPLIT, PATH_F16X2, PATH_FOLD_FRAG, PATH_POINTWISE_F16, PATH_SPECTRAL, PATH_FIRST };
+enum Path { PATH_EXPLICIT, PATH_POINTWISE, PATH_FEW_OUT, PATH_FEW_IN, PATH_DIRECT_FILTER, PATH_HALO, PATH_HALO_FILTER, PATH_HALO_BF16, PATH_FILTER_BF16, PATH_HALO_FILTER_BF16, PATH_FEW_COLS_FILTER, PATH_SMALL, PATH_SMALL_BWD, PATH_FOLD, PATH_FFT, PATH_TAPS, PATH_POINTWISE_BF16, PATH_SPLIT, PATH_F16X2, PATH_FOLD_FRAG, PATH_POINTWISE_F16, PATH_FIRST };
 struct Plan {
   Path path;
   DirectGeom dg;
@@ -123,9 +123,10 @@ struct Plan {
   F16x2Plan f2;
   FoldFragPlan ff;
   PointwiseF16Plan pw16;
-  SpectralPlan spec;
+  bool spectral;     // through the Fourier domain first (spec); `path` is then enqueued behind for what that declines, its
+  SpectralPlan spec; // workspace in the place of the spectra
   FirstPlan first;
-  Path behind;       // PATH_F16X2, PATH_POINTWISE_F16, PATH_SPECTRAL: the float path enqueued behind for what the terms do not carry ...
+  Path behind;       // PATH_F16X2, PATH_POINTWISE_F16: the float path enqueued behind for what the terms do not carry ...
   size_t behind_at;  // ... and the offset of its workspace
   int split;        // channel slices (few-out), output-map group size (few-in) or batch slices (filter gradient)
   size_t partial_bytes;
@@ -139,8 +140,9 @@ static constexpr size_t kScratchBytes = (size_t)32 << 20;
 // What a two-term pass may ask for beyond its float route's own workspace.  Larger layers ask for the float route's and
 // work through the batch in parts that fit what they are given.  The kernel gradient keeps to the scratch memory above,
 // so that the allocation-free entry point takes every layer it took, by the same route as the ordinary one.
-static size_t two_term_allowance(int pass, size_t own) {
-  if (pass != VCNN_PASS_BWD_FILTER) return (size_t)64 << 20;
+// `room`: what there is anyway, behind a pass through the Fourier domain (0: of itself; see direct_plan).
+static size_t two_term_allowance(int pass, size_t own, size_t room) {
+  if (pass != VCNN_PASS_BWD_FILTER) return std::max((size_t)64 << 20, room);
   return own <= kScratchBytes ? kScratchBytes : (size_t)384 << 20;
 }
 // (1 x 1 layers are not cut into parts: their re-laid copies are as large as the activations)
@@ -188,7 +190,7 @@ static double inside(int h, int r, int pad, int oh) {
 //
 // `offered`: the workspace the call has (kAsk: the query).  A call whose workspace only holds the float route's partial
 // sums runs that route, as it always has.
-static void prefer_two_terms(const ConvGeom& g, int pass, size_t offered, Plan* p) {
+static void prefer_two_terms(const ConvGeom& g, int pass, size_t offered, size_t room, Plan* p) {
   if (g.c <= 4 || g.k <= 4) return;  // channel groups of eight, most of them padding
   const size_t own = p->workspace_bytes + bias_room(g, pass, false);  // what the float route needs
   const size_t bias = bias_room(g, pass, true);
@@ -222,7 +224,7 @@ static void prefer_two_terms(const ConvGeom& g, int pass, size_t offered, Plan* 
   // fewer than a correlation's.  It also serves layers whose correlation contracts for long over few tiles.
   FoldFragPlan ff{};
   double fold_s = 1e9;
-  if (pass == VCNN_PASS_BWD_DATA && bwd_data_fold_frag_plan(g, 2, std::max(own, two_term_allowance(pass, own)), &ff) &&
+  if (pass == VCNN_PASS_BWD_DATA && !room && bwd_data_fold_frag_plan(g, 2, std::max(own, two_term_allowance(pass, own, room)), &ff) &&
       (offered == kAsk || ff.workspace_bytes <= offered))
     fold_s = 1.05 * ff.est_seconds + 3e-6;
   auto take_fold = [&] {
@@ -235,7 +237,7 @@ static void prefer_two_terms(const ConvGeom& g, int pass, size_t offered, Plan* 
   F16x2Plan f2{};
   // (the kernel gradient's parts add up to one sum: its budget, and with it the order of that sum, depends on the
   // shape alone, not on how much more a caller has)
-  const size_t ask = std::max(own, two_term_allowance(pass, own));
+  const size_t ask = std::max(own, two_term_allowance(pass, own, room));
   // (the float kernel's workspace: a kernel gradient's slices in the product's place, an input gradient's flipped kernel
   // matrix beside it, where the product writes it)
   const size_t beside = pass == VCNN_PASS_BWD_DATA ? p->workspace_bytes : 0;
@@ -299,7 +301,9 @@ static void prefer_pointwise_f16(const ConvGeom& g, int pass, size_t offered, Pl
   p->workspace_bytes = need - bias;
 }
 
-static Plan direct_plan(const ConvGeom& g, int pass, int dtype, size_t offered) {
+// room: not 0: a plan that stays behind a pass through the Fourier domain, with that much workspace: no transposed product (its
+// blocks take longer to leave: 16 38 64 64 -> 512 16 16 in two terms 46 us, 7 launches, against 18 for the correlation).
+static Plan direct_plan(const ConvGeom& g, int pass, int dtype, size_t offered, size_t room = 0) {
   Plan p{};
   p.path = PATH_EXPLICIT;
   const int algo = g_conv_algo.load();
@@ -369,7 +373,7 @@ static Plan direct_plan(const ConvGeom& g, int pass, int dtype, size_t offered) 
     const double corr = 1.2 * skip * halo_bf16_seconds(p.hb, g.n, g.c, g.r, g.s, (int64_t)g.h * g.w) + 14e-6;
     FoldFragPlan ff{};
     const size_t own = p.workspace_bytes;
-    if (algo == VCNN_ALGO_AUTO && bwd_data_fold_frag_plan(g, 1, std::max(own, two_term_allowance(pass, own)), &ff) &&
+    if (algo == VCNN_ALGO_AUTO && !room && bwd_data_fold_frag_plan(g, 1, std::max(own, two_term_allowance(pass, own, room)), &ff) &&
         (offered == kAsk || ff.workspace_bytes <= offered) && 1.05 * ff.est_seconds + 3e-6 < 0.9 * corr) {
       p.path = PATH_FOLD_FRAG;
       p.ff = ff;
@@ -448,7 +452,7 @@ static Plan direct_plan(const ConvGeom& g, int pass, int dtype, size_t offered) 
       p.workspace_bytes = align256((size_t)g.M * g.K * sizeof(float));
     } else if (allow_direct && g.r - 1 - g.ph >= 0 && g.s - 1 - g.pw >= 0 &&
                conv_halo_plan(g.n, g.k, g.oh, g.ow, g.c, g.r, g.s, g.r - 1 - g.ph, g.s - 1 - g.pw, &p.hp) &&
-               (algo == VCNN_ALGO_IMPLICIT ||
+               (algo == VCNN_ALGO_IMPLICIT || room ||
                 (halo_bwd_data_pays(g, p.hp) && !(automatic && bwd_data_fold_plan(g, &p.fold) && fold_beats_halo(g, p.hp, p.fold))))) {
       // correlation of dy (k channels) with the flipped kernels; the flipped matrix lives in the workspace
       p.path = PATH_HALO;
@@ -487,7 +491,7 @@ static Plan direct_plan(const ConvGeom& g, int pass, int dtype, size_t offered) 
   }
   if (automatic && dtype == VCNN_F32) {
     prefer_pointwise_f16(g, pass, offered, &p);
-    prefer_two_terms(g, pass, offered, &p);
+    prefer_two_terms(g, pass, offered, room, &p);
   }
   p.bias_offset = p.workspace_bytes;
   p.workspace_bytes += bias_room(g, pass, p.path == PATH_F16X2 || p.path == PATH_POINTWISE_F16);
@@ -495,51 +499,90 @@ static Plan direct_plan(const ConvGeom& g, int pass, int dtype, size_t offered) 
 }
 
 // Takes a pass through the Fourier domain (spectral.h) where that is faster than `direct`, the plan it replaces.  That one's
-// time is taken from below: on the half-precision matrix cores 1.1 times the flops at their best rate (three products each in
-// float) and 45 us of scan, re-laying and launches in float, 25 in bfloat16; on the float instruction its flops at 130 TFLOP/s.
-// (40 drawn layers, 110 passes; n c h w -> k r s, direct / through the Fourier domain: 16 38 64 64 -> 512 16 16, three passes,
-// 3.33 / 0.70 ms, in bfloat16 1.25 / 0.68 ms; 3 354 64 64 -> 69 8 14 kernel gradient 813 / 126 us; 32 17 64 64 -> 90 11 11 forward
-// 210 / 65 us; 16 13 64 64 -> 57 9 9 forward 64 / 44 us; 57 39 34 34 -> 276 11 11, 342 / 326 us, stays, and so does bfloat16 in 18
-// 207 56 24 -> 101 13 9, 181 / 372 us.)
+// time, of 400 drawn passes: two terms 0.9 to 1.2 times its own estimate (kernel gradient 0.85 to 1.2), folded 0.95 to 1.2 times; the
+// others from below by their flops, in bfloat16 1.1 to 2.6 times that, on the float instruction 1.0 to 10 times.  (Of 480
+// passes that could go either way 1 of those taken through the Fourier domain is slower there by more than 3 %; all of them are nearer the exact
+// sums, 0.1 to 1.01 times the direct route's error.)
+// (n c h w -> k r s, direct / through the Fourier domain: 16 38 64 64 -> 512 16 16, three passes, 3.35 / 0.78 ms, in bfloat16 1.25 /
+// 0.74 ms; 32 17 64 64 -> 90 11 11 forward 218 / 90 us; 7 57 64 43 -> 235 15 11 forward 214 / 166 us, stays; 3 200 89 214 -> 202 1 79
+// forward 0.83 / 1.83 ms in thirteen parts, stays.)
 //
 // `direct`: the plan for the query, whatever the call offers, so that a workspace of the size asked for takes the route asked for.
 static bool spectral_worth_planning(const ConvGeom& g) {
   return g.r * g.s >= (g.r == 1 || g.s == 1 ? 8 : 49) && g.c > 4 && g.k > 4 && 2.0 * (double)g.M * (double)g.K * (double)g.N >= 4e9;
 }
+// The float kernels as a plan of their own.
+static bool float_behind(const ConvGeom& g, int pass, int dtype, Plan* p) {
+  *p = Plan{};
+  if (pass == VCNN_PASS_BWD_FILTER) {
+    p->path = PATH_HALO_FILTER;
+    if (!conv_halo_filter_plan(g, &p->hfp)) return false;
+    p->workspace_bytes = align256(p->hfp.partial_bytes);
+    return true;
+  }
+  p->path = PATH_HALO;
+  if (pass == VCNN_PASS_FWD) return conv_halo_plan(g.n, g.c, g.h, g.w, g.k, g.r, g.s, g.ph, g.pw, &p->hp);
+  p->workspace_bytes = align256((size_t)g.M * g.K * (dtype == VCNN_BF16 ? 2 : 4));  // the flipped kernels
+  return g.r - 1 - g.ph >= 0 && g.s - 1 - g.pw >= 0 &&
+         conv_halo_plan(g.n, g.k, g.oh, g.ow, g.c, g.r, g.s, g.r - 1 - g.ph, g.s - 1 - g.pw, &p->hp);
+}
+// What a route takes behind another that has declined nothing: its launches, 4.6 us each.
+static double idle_seconds(const Plan& p, int pass) {
+  const bool filter = pass == VCNN_PASS_BWD_FILTER;
+  int launches;
+  switch (p.path) {
+    case PATH_F16X2: launches = filter ? 5 * p.f2.parts + 1 : 3 * p.f2.parts + 1; break;
+    case PATH_HALO_BF16: launches = 3; break;
+    case PATH_HALO_FILTER_BF16: launches = 4; break;
+    default: launches = pass == VCNN_PASS_FWD ? 1 : 2;
+  }
+  return 4.6e-6 * launches;
+}
 static bool prefer_spectral(const ConvGeom& g, int pass, int dtype, size_t offered, const Plan& direct, Plan* p) {
   const double flops = 2.0 * (double)g.M * (double)g.K * (double)g.N;
-  const bool on_float = direct.path == PATH_HALO || direct.path == PATH_HALO_FILTER || direct.path == PATH_FOLD || direct.path == PATH_EXPLICIT;
-  const double direct_s = on_float ? flops / 1.3e14 : (dtype == VCNN_BF16 ? flops / 1e15 + 25e-6 : 3 * flops / 1.05e15 + 45e-6);
   const bool filter = pass == VCNN_PASS_BWD_FILTER, data = pass == VCNN_PASS_BWD_DATA;
+  double direct_s;
+  switch (direct.path) {
+    case PATH_F16X2: direct_s = (filter ? 0.9 : 0.97) * direct.f2.est_seconds; break;
+    case PATH_FOLD_FRAG: direct_s = 1.05 * direct.ff.est_seconds; break;
+    case PATH_FOLD: direct_s = flops / 6e13; break;
+    case PATH_HALO: case PATH_HALO_FILTER: case PATH_EXPLICIT: direct_s = flops / 9.5e13; break;
+    default: direct_s = flops / 1.15e15 + 25e-6;
+  }
   // (the kernel gradient's route depends on the shape alone, and stays inside the scratch memory where it was)
   const bool small = filter && direct.workspace_bytes <= kScratchBytes;
   size_t budget = filter ? (small ? kScratchBytes : kSpectralAllowance) : (offered != kAsk ? offered : (data ? kSpectralAllowance : kSpectralForward));
   SpectralPlan q{};
   if (!spectral_plan(g, pass, budget, &q)) return false;
-  // the float kernel behind, for declined images: its workspace in the place of the spectra
-  size_t behind = 0;
-  HaloPlan hp{};
-  HaloFilterPlan hfp{};
-  if (filter) {
-    if (!conv_halo_filter_plan(g, &hfp)) return false;
-    behind = hfp.partial_bytes;
-  } else if (data) {
-    if (g.r - 1 - g.ph < 0 || g.s - 1 - g.pw < 0 ||
-        !conv_halo_plan(g.n, g.k, g.oh, g.ow, g.c, g.r, g.s, g.r - 1 - g.ph, g.s - 1 - g.pw, &hp)) return false;
-    behind = (size_t)g.M * g.K * (dtype == VCNN_BF16 ? 2 : 4);
-  } else if (!conv_halo_plan(g.n, g.c, g.h, g.w, g.k, g.r, g.s, g.ph, g.pw, &hp)) {
-    return false;
-  }
+  // A direct route stays enqueued behind, for what is declined, its workspace in the place of the spectra (16 38 64 64 -> 512 16 16 with an
+  // area of 20 x 20 at 2^-8 in every image: three passes 3.24 ms against 3.65 by the direct routes alone and 11.1 with the float kernel
+  // behind, in bfloat16 1.20, 1.34 and 11.3).  Each of its launches takes 4.6 us where nothing is declined: so in as few parts of the batch as the spectra
+  // leave room for.
   const size_t spectra = q.workspace_bytes - q.words_bytes;
-  if (behind > spectra) q.map_bytes += align256(behind - spectra), q.workspace_bytes += align256(behind - spectra);
+  Plan behind = direct;
+  auto fits = [&] {
+    switch (behind.path) {  // what can be held to some images
+      case PATH_HALO: case PATH_HALO_FILTER: case PATH_HALO_BF16: case PATH_HALO_FILTER_BF16: case PATH_F16X2: break;
+      default: return false;
+    }
+    return q.words_bytes + std::max(spectra, align256(behind.workspace_bytes)) <= budget;
+  };
+  if (!filter) {
+    behind = direct_plan(g, pass, dtype, spectra, spectra);
+    if (behind.path == PATH_HALO || !fits()) behind = direct;
+  }
+  if (!fits() && (!float_behind(g, pass, dtype, &behind) || !fits())) return false;
+  if (align256(behind.workspace_bytes) > spectra) {
+    const size_t more = align256(behind.workspace_bytes) - spectra;
+    q.map_bytes += more, q.workspace_bytes += more;
+  }
   size_t need = align256(q.workspace_bytes);
   if (filter && !small) need = std::max(need, kScratchBytes + 256);  // refused by the allocation-free entry point as before
   if (need > budget || (offered != kAsk && need > offered)) return false;
-  if ((q.along ? 1.05 : 1.1) * q.est_seconds > direct_s) return false;
-  *p = Plan{};
-  p->path = PATH_SPECTRAL, p->spec = q, p->hp = hp, p->hfp = hfp;
-  p->behind = filter ? PATH_HALO_FILTER : PATH_HALO;
-  p->workspace_bytes = p->bias_offset = need;
+  if (1.04 * (q.est_seconds + idle_seconds(behind, pass)) > direct_s) return false;
+  *p = behind;
+  p->spectral = true, p->spec = q;
+  p->workspace_bytes = need;
   return true;
 }
 
@@ -613,6 +656,10 @@ vcnn_status vcnn_conv_route(const vcnn_conv_desc* d, int32_t pass, size_t worksp
   const Plan p = make_plan(g, pass, d->dtype, workspace_bytes);
   if (p.workspace_bytes > workspace_bytes)
     return fail(VCNN_ERR_WORKSPACE, "conv_route: %zu bytes of workspace, %zu needed", workspace_bytes, p.workspace_bytes);
+  if (p.spectral) {
+    *name = "spectral";
+    return VCNN_OK;
+  }
   switch (p.path) {
     case PATH_EXPLICIT: *name = "explicit"; break;
     case PATH_POINTWISE: *name = "pointwise"; break;
@@ -633,7 +680,6 @@ vcnn_status vcnn_conv_route(const vcnn_conv_desc* d, int32_t pass, size_t worksp
     case PATH_FOLD_FRAG: *name = p.ff.terms == 2 ? "two_term_fold" : "fold_bf16"; break;
     case PATH_POINTWISE_F16: *name = "two_term_pointwise"; break;
     case PATH_FIRST: *name = "first"; break;
-    case PATH_SPECTRAL: *name = "spectral"; break;
   }
   return VCNN_OK;
 }
@@ -674,6 +720,11 @@ static vcnn_status conv_fwd_linear(const vcnn_conv_desc* d, const ConvGeom& g, c
   hipStream_t st = (hipStream_t)stream;
   const int relu = d->act == VCNN_ACT_RELU;
   const int dt = d->dtype;
+  Declined only{};
+  if (plan.spectral) {
+    if (vcnn_status s = launch_spectral_fwd(plan.spec, dt, g, x, w, bias, y, relu, workspace, st)) return s;
+    only = spectral_declined(g, VCNN_PASS_FWD, plan.spec, workspace);
+  }
   if (plan.path == PATH_TAPS) return launch_conv_taps_fwd(g, dt, x, w, bias, y, relu, (float*)workspace, st);
   if (plan.path == PATH_FEW_OUT)
     return launch_direct_few_out(plan.dg, dt, plan.split, x, w, bias, y, (float*)workspace, relu, st);
@@ -681,22 +732,18 @@ static vcnn_status conv_fwd_linear(const vcnn_conv_desc* d, const ConvGeom& g, c
   if (plan.path == PATH_FIRST) return launch_conv_first(plan.first, dt, g, x, w, bias, y, relu, st);
   if (plan.path == PATH_SMALL)
     return launch_conv_small(dt, g.n, g.c, g.h, g.w, g.k, g.r, g.s, g.ph, g.pw, x, w, bias, y, relu, st);
-  auto float_halo = [&](const Declined& only) {
-    return launch_conv_halo(plan.hp, dt, g.n, g.c, g.h, g.w, g.k, g.r, g.s, g.ph, g.pw, x, w, bias, y, relu, st, only);
+  auto float_halo = [&](const Declined& declined) {
+    return launch_conv_halo(plan.hp, dt, g.n, g.c, g.h, g.w, g.k, g.r, g.s, g.ph, g.pw, x, w, bias, y, relu, st, declined);
   };
-  if (plan.path == PATH_HALO) return float_halo({});
-  if (plan.path == PATH_SPECTRAL) {
-    if (vcnn_status s = launch_spectral_fwd(plan.spec, dt, g, x, w, bias, y, relu, workspace, st)) return s;
-    return float_halo(spectral_declined(g, VCNN_PASS_FWD, plan.spec, workspace));
-  }
+  if (plan.path == PATH_HALO) return float_halo(only);
   if (plan.path == PATH_HALO_BF16) {
     return launch_conv_halo_bf16(plan.hb, g.n, g.c, g.h, g.w, g.k, g.r, g.s, g.ph, g.pw, x, w, g.K, (int64_t)g.r * g.s, 0,
-                                 bias, y, relu, workspace, st);
+                                 bias, y, relu, workspace, st, nullptr, 0, only);
   }
   if (plan.path == PATH_FFT) return launch_conv_fft(plan.fft, dt, g, x, w, bias, y, relu, workspace, st);
   if (plan.path == PATH_F16X2) {
-    if (vcnn_status s = launch_conv_f16x2_fwd(plan.f2, g, (const float*)x, (const float*)w, bias, (float*)y, relu, workspace, st)) return s;
-    return float_halo(split_declined(workspace, g.n));
+    if (vcnn_status s = launch_conv_f16x2_fwd(plan.f2, g, (const float*)x, (const float*)w, bias, (float*)y, relu, workspace, st, only)) return s;
+    return float_halo(split_declined(workspace, g.n, only));
   }
   if (plan.path == PATH_SPLIT)
     return launch_conv_split_fwd(plan.sp, g, (const float*)x, (const float*)w, bias, (float*)y, relu, workspace, st);
@@ -736,6 +783,12 @@ vcnn_status vcnn_conv_bwd_filter(const vcnn_conv_desc* d, const void* x, const v
   hipStream_t st = (hipStream_t)stream;
   const int dt = d->dtype;
   float* bias_partial = (float*)((char*)workspace + plan.bias_offset);
+  Declined only{};
+  if (plan.spectral) {
+    if (vcnn_status s = launch_spectral_filter(plan.spec, dt, g, x, dy, dw, dbias, workspace, st)) return s;
+    only = spectral_declined(g, VCNN_PASS_BWD_FILTER, plan.spec, workspace);
+    dbias = nullptr;  // (from sums of the samples, whatever is declined)
+  }
   if (plan.path == PATH_TAPS) {
     if (vcnn_status s = launch_conv_taps_filter(g, dt, x, dy, dw, workspace, st)) return s;
   } else if (plan.path == PATH_DIRECT_FILTER) {
@@ -746,26 +799,19 @@ vcnn_status vcnn_conv_bwd_filter(const vcnn_conv_desc* d, const void* x, const v
   } else if (plan.path == PATH_POINTWISE_F16 || plan.path == PATH_F16X2) {
     const FilterBehind behind{&g, (const float*)x, (const float*)dy, plan.behind == PATH_HALO_FILTER ? &plan.hfp : nullptr,
                               (float*)((char*)workspace + plan.behind_at)};
-    const vcnn_status s = plan.path == PATH_F16X2 ? launch_conv_f16x2_filter(plan.f2, g, behind.x, behind.dy, dw, workspace, bias_partial, behind, st)
+    const vcnn_status s = plan.path == PATH_F16X2 ? launch_conv_f16x2_filter(plan.f2, g, behind.x, behind.dy, dw, workspace, bias_partial, behind, st, only)
                                                   : launch_pointwise_f16_filter(plan.pw16, g, behind.x, behind.dy, dw, workspace, bias_partial, behind, st);
     if (s != VCNN_OK) return s;
-  } else if (plan.path == PATH_SPECTRAL) {
-    if (vcnn_status s = launch_spectral_filter(plan.spec, dt, g, x, dy, dw, dbias, workspace, st)) return s;
-    const Declined declined = spectral_declined(g, VCNN_PASS_BWD_FILTER, plan.spec, workspace);
-    if (vcnn_status s = launch_conv_halo_filter(plan.hfp, dt, g, x, dy, dw, nullptr, (float*)workspace, st, declined)) return s;
-    if (plan.hfp.splits == 1) return VCNN_OK;
-    const OtherSlices slices{declined.any, (const float*)workspace, plan.hfp.splits};
-    return launch_sum_slices(nullptr, nullptr, dw, VCNN_F32, g.M * g.K, 0, 1, 1, 0, st, slices);
   } else if (plan.path == PATH_SPLIT) {
     if (vcnn_status s = launch_conv_split_filter(plan.sp, g, (const float*)x, (const float*)dy, dw, workspace, st)) return s;
   } else if (plan.path == PATH_POINTWISE_BF16) {
     if (vcnn_status s = launch_pointwise_filter_bf16(plan.pwf, g, x, dy, dw, (float*)workspace, st)) return s;
   } else if (plan.path == PATH_HALO_FILTER_BF16) {
-    if (vcnn_status s = launch_filter_grad_bf16(plan.hfb, g, x, dy, dw, workspace, st)) return s;
+    if (vcnn_status s = launch_filter_grad_bf16(plan.hfb, g, x, dy, dw, workspace, st, 0, only)) return s;
   } else if (plan.path == PATH_FILTER_BF16) {
     if (vcnn_status s = launch_bwd_filter_bf16(plan.fb, g, x, dy, dw, workspace, st)) return s;
   } else if (plan.path == PATH_HALO_FILTER) {
-    if (vcnn_status s = launch_conv_halo_filter(plan.hfp, dt, g, x, dy, dw, dbias, (float*)workspace, st)) return s;
+    if (vcnn_status s = launch_conv_halo_filter(plan.hfp, dt, g, x, dy, dw, dbias, (float*)workspace, st, only)) return s;
     if (plan.hfp.bias_column) return VCNN_OK;  // the bias gradient came out of the same product
   } else if (plan.path == PATH_POINTWISE) {
     if (vcnn_status s = launch_bwd_filter_gemm_f32(g, dt, dy, nullptr, x, dw, (float*)workspace, st)) return s;
@@ -799,28 +845,27 @@ static vcnn_status conv_bwd_data_impl(const vcnn_conv_desc* d, int act_below, co
     if (s != VCNN_OK || da == VCNN_ACT_NONE) return s;
     return vcnn_act_bwd(da, dt, (size_t)g.n * g.c * g.h * g.w, x, dx, dx, stream);
   };
+  Declined only{};
+  if (plan.spectral) {
+    if (vcnn_status s = launch_spectral_bwd_data(plan.spec, dt, g, w, dy, dx, workspace, st)) return s;
+    only = spectral_declined(g, VCNN_PASS_BWD_DATA, plan.spec, workspace);
+  }
   if (plan.path == PATH_FEW_OUT)
     return then_act(launch_direct_few_out(plan.dg, dt, plan.split, dy, w, nullptr, dx, (float*)workspace, 0, st));
   if (plan.path == PATH_FEW_IN) return launch_direct_few_in(plan.dg, dt, plan.split, dy, w, nullptr, dx, 0, st, da, ref);
   if (plan.path == PATH_HALO_BF16) {
     // correlation of dy (k channels) with the flipped kernels into c maps: the re-ordering pass flips and transposes
     return then_act(launch_conv_halo_bf16(plan.hb, g.n, g.k, g.oh, g.ow, g.c, g.r, g.s, g.r - 1 - g.ph, g.s - 1 - g.pw, dy,
-                                          w, (int64_t)g.r * g.s, g.K, 1, nullptr, dx, 0, workspace, st));
+                                          w, (int64_t)g.r * g.s, g.K, 1, nullptr, dx, 0, workspace, st, nullptr, 0, only));
   }
-  auto float_halo = [&](void* flipped, const Declined& only) {
+  auto float_halo = [&](void* flipped, const Declined& declined) {
     return launch_conv_halo(plan.hp, dt, g.n, g.k, g.oh, g.ow, g.c, g.r, g.s, g.r - 1 - g.ph, g.s - 1 - g.pw, dy, flipped,
-                            nullptr, dx, 0, st, only);
+                            nullptr, dx, 0, st, declined);
   };
-  if (plan.path == PATH_SPECTRAL) {
-    if (vcnn_status s = launch_spectral_bwd_data(plan.spec, dt, g, w, dy, dx, workspace, st)) return s;
-    const Declined declined = spectral_declined(g, VCNN_PASS_BWD_DATA, plan.spec, workspace);
-    if (vcnn_status s = launch_flip_transpose(dt, w, workspace, g.k, g.c, g.r * g.s, st, declined)) return s;
-    return then_act(float_halo(workspace, declined));
-  }
   if (plan.path == PATH_F16X2) {
     float* const flipped = (float*)((char*)workspace + plan.behind_at);
-    if (vcnn_status s = launch_conv_f16x2_bwd_data(plan.f2, g, (const float*)w, (const float*)dy, (float*)dx, flipped, workspace, st)) return s;
-    return then_act(float_halo(flipped, split_declined(workspace, g.n)));
+    if (vcnn_status s = launch_conv_f16x2_bwd_data(plan.f2, g, (const float*)w, (const float*)dy, (float*)dx, flipped, workspace, st, only)) return s;
+    return then_act(float_halo(flipped, split_declined(workspace, g.n, only)));
   }
   if (plan.path == PATH_POINTWISE_BF16) {
     // dx[n][c][p] = sum_m w[m][c] * dy[n][m][p]: the forward product on the transposed kernel matrix
@@ -835,8 +880,8 @@ static vcnn_status conv_bwd_data_impl(const vcnn_conv_desc* d, int act_below, co
                                       nullptr, dx, 0, st));
   }
   if (plan.path == PATH_HALO) {
-    if (vcnn_status s = launch_flip_transpose(dt, w, workspace, g.k, g.c, g.r * g.s, st)) return s;
-    return then_act(float_halo(workspace, {}));
+    if (vcnn_status s = launch_flip_transpose(dt, w, workspace, g.k, g.c, g.r * g.s, st, only)) return s;
+    return then_act(float_halo(workspace, only));
   }
   if (plan.path == PATH_FOLD_FRAG) return launch_bwd_data_fold_frag(plan.ff, g, w, dy, dx, workspace, st, da, ref);
   if (plan.path == PATH_FOLD) return launch_bwd_data_fold(plan.fold, dt, g, w, dy, dx, (float*)workspace, st, da, ref);

@@ -38,8 +38,11 @@ static constexpr int kThreads = 256;
 static constexpr size_t kLdsBudget = 78 * 1024;  // two blocks per CU
 
 // x8[n][g][pos][c8] = x[n][8g + c8][pos], zero for channels >= C; x8[total] = 0 (the padding source)
+// (BEHIND, here and below: an instance of its own for calls behind another pass, for what that declined: `only`)
+template <bool BEHIND>
 __global__ __launch_bounds__(kThreads) void interleave_channels_kernel(const bf16* __restrict__ x, uint4* __restrict__ x8,
-                                                                       int C, int CG, int HW, int64_t total) {
+                                                                       int C, int CG, int HW, int64_t total, Declined only) {
+  if (BEHIND && looks_at_none(only)) return;
   const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   if (i == 0) x8[total] = make_uint4(0u, 0u, 0u, 0u);
   if (i >= total) return;
@@ -47,6 +50,7 @@ __global__ __launch_bounds__(kThreads) void interleave_channels_kernel(const bf1
   const int64_t t = i / HW;
   const int g = (int)(t % CG);
   const int64_t n = t / CG;
+  if (BEHIND && !looks_at(only, (int)n)) return;
   const bf16* src = x + (n * C + g * 8) * HW + pos;
   uint32_t v[8];
 #pragma unroll
@@ -62,10 +66,12 @@ __global__ __launch_bounds__(kThreads) void interleave_channels_kernel(const bf1
 // (gl, q) = divmod(2 jl + lane / 32, RS); zero outside the matrix or the chunk.  With m16: row = 16 mt + lane % 16
 // and (gl, q) = divmod(4 jl + lane / 16, RS).
 // w(row, channel, q) = in[row*so + channel*si + (flip ? RS-1-q : q)].
+template <bool BEHIND>
 __global__ __launch_bounds__(kThreads) void reorder_weights_frag_kernel(const bf16* __restrict__ in, bf16* __restrict__ out,
                                                                         int CO, int CI, int RS, int64_t so, int64_t si,
                                                                         int flip, int cgc, int nchunks, int steps,
-                                                                        int m16, int64_t total) {
+                                                                        int m16, int64_t total, Declined only) {
+  if (BEHIND && looks_at_none(only)) return;
   const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   if (i >= total) return;
   const int c8 = (int)(i & 7);
@@ -90,10 +96,12 @@ __global__ __launch_bounds__(kThreads) void reorder_weights_frag_kernel(const bf
 // element-wise form reads 2 bytes per thread at strides of a kernel's size - and stores them to the 8 (group, tap) pairs
 // they belong to.  Threads are ordered (channel in group, row in tile) fastest, so that the 2-byte stores of one tap
 // fill 128 contiguous bytes per 8 rows.  Entries outside the matrix or the chunk are written as zeros, as above.
+template <bool BEHIND>
 __global__ __launch_bounds__(kThreads) void reorder_weights_frag8_kernel(const bf16* __restrict__ in, bf16* __restrict__ out,
                                                                          int CO, int CI, int RS, int64_t so, int64_t si,
                                                                          int flip, int cgc, int nchunks, int uch, int m16,
-                                                                         int64_t total) {
+                                                                         int64_t total, Declined only) {
+  if (BEHIND && looks_at_none(only)) return;
   const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   if (i >= total) return;
   const int T = m16 ? 16 : 32;
@@ -201,10 +209,15 @@ __device__ __forceinline__ int reorder_weights_split(const HaloSplitArgs& a, int
   return small.count(f);
 }
 
+template <bool BEHIND>
 __global__ __launch_bounds__(kThreads) void halo_split_kernel(HaloSplitArgs a) {
   const int op = (int)blockIdx.x >= a.x_blocks;
   const int image = op ? 0 : (int)blockIdx.x / a.image_blocks;
   const int block = op ? (int)blockIdx.x - a.x_blocks : (int)blockIdx.x - image * a.image_blocks;
+  if (BEHIND && (op ? looks_at_none(a.sc.only) : !looks_at(a.sc.only, image))) {
+    if (op == 0 && image == 0 && block == 0 && threadIdx.x == 0) a.x8[a.x_total] = make_uint4(0u, 0u, 0u, 0u);  // (the other images' too)
+    return;
+  }
   const uint32_t largest = op ? split_max(a.sc.partial[1], kAbsMaxBlocks)
                               : split_max(a.sc.partial[0] + (int64_t)image * a.sc.blocks, a.sc.blocks);
   if (block == 0 && threadIdx.x == 0) note_scale(a.sc, op, image, largest);
@@ -220,7 +233,7 @@ struct HaloBf16Args {
   int64_t wf_term;
   const int32_t* image_exponent;  // TERMS = 2: the scales of the input's images ...
   const int32_t* exponent;        // ... and of the kernel matrix (result times 2^-(image_exponent[n] + *exponent))
-  Declined declined;              // TERMS = 2: images left to the float kernel, which wants, for an input gradient, ...
+  Declined declined;              // BEHIND: the images looked at; TERMS = 2: those left to the float kernel, which wants, for an input gradient, ...
   const float* flip_w;            // ... this matrix [flip_m][m][r*s] ...
   float* flipped;                 // ... flipped and transposed here
   int flip_m;
@@ -279,7 +292,7 @@ __device__ __forceinline__ Acc mfma_term(uint4 a, uint4 b, Acc c) {
 // of their own.  TERMS = 3: both operands are given as three bfloat16 terms each (a float split exactly into three), and a step
 // multiplies the six largest of the nine term pairs - smallest first - into the same accumulators: the float product
 // to within float rounding, with every staged word and every fragment used for two or three MFMAs instead of one.
-template <int WAVES_M, int WAVES_K, int TM, int TN, bool M16 = false, int WAVES_N = 1, int TERMS = 1>
+template <int WAVES_M, int WAVES_K, int TM, int TN, bool M16 = false, int WAVES_N = 1, int TERMS = 1, bool BEHIND = false>
 __global__ __launch_bounds__(kThreads, 2) void conv_halo_bf16_kernel(HaloBf16Args a) {
   static_assert(TERMS >= 1 && TERMS <= 3, "plain bfloat16 operands, or floats as two f16 or three bfloat16 terms");
   using Split = SplitTerms<TERMS>;
@@ -303,9 +316,13 @@ __global__ __launch_bounds__(kThreads, 2) void conv_halo_bf16_kernel(HaloBf16Arg
   const int tm = blockIdx.x % a.tiles_m;
   const int tj = blockIdx.x / a.tiles_m;
   const int n = tj / a.tiles_per_img;
-  if (TERMS == 2 && *a.declined.any) {
-    if (a.flipped) flip_share(a);
-    if (is_declined(a.declined, n)) return;
+  if (BEHIND && !looks_at(a.declined, n)) return;
+  if (TERMS == 2) {
+    const uint32_t any = *a.declined.any;
+    if (any != 0) {
+      if (a.flipped && any != kNotLookedAt) flip_share(a);
+      if (is_declined(a.declined, n)) return;
+    }
   }
   const int p0 = (tj - n * a.tiles_per_img) * BN;
   const int i0 = tm * BM + wave_m * TILE * TM;  // first output map of this wave
@@ -789,14 +806,18 @@ bool conv_halo_bf16_plan(int n, int c, int h, int w, int m, int r, int s, int ph
 template <int WAVES_M, int WAVES_K, int TM, int TN, bool M16 = false, int WAVES_N = 1, int TERMS = 1>
 static void launch_one(const HaloBf16Args& a, size_t lds, hipStream_t st) {
   const dim3 grid((unsigned)((int64_t)a.tiles_m * a.n * a.tiles_per_img)), block(kThreads);
-  auto kernel = conv_halo_bf16_kernel<WAVES_M, WAVES_K, TM, TN, M16, WAVES_N, TERMS>;
-  static bool opted = false;  // one flag per instantiation, i.e. per kernel
-  if (!opted) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)kLdsBudget);
-    opted = true;
-  }
-  hipLaunchKernelGGL(kernel, grid, block, lds, st, a);
+  auto go = [&](auto kernel, bool& opted) {
+    if (!opted) {
+      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)kLdsBudget);
+      opted = true;
+    }
+    hipLaunchKernelGGL(kernel, grid, block, lds, st, a);
+  };
+  static bool opted[2] = {};  // one flag per instantiation, i.e. per kernel
+  if constexpr (TERMS == 1)
+    if (a.declined.of_any) return go(conv_halo_bf16_kernel<WAVES_M, WAVES_K, TM, TN, M16, WAVES_N, 1, true>, opted[1]);
+  go(conv_halo_bf16_kernel<WAVES_M, WAVES_K, TM, TN, M16, WAVES_N, TERMS>, opted[0]);
 }
 
 template <int TN>
@@ -825,23 +846,17 @@ static void launch_tn(const HaloBf16Args& a, int waves_m, int waves_n, int tm, i
   else launch_one<1, 4, 1, TN>(a, lds, st);
 }
 
-vcnn_status launch_conv_halo_bf16(const HaloBf16Plan& p, int n, int c, int h, int w, int m, int r, int s, int ph, int pw,
-                                  const void* x, const void* wgt, int64_t w_so, int64_t w_si, int flip, const float* bias,
-                                  void* y, int relu, void* workspace, hipStream_t st, float* y32, int accumulate) {
-  return launch_conv_halo_bf16_prepared(p, n, c, h, w, m, r, s, ph, pw, x, wgt, w_so, w_si, flip, bias, y, relu, workspace,
-                                        (char*)workspace + p.x8_bytes, st, y32, accumulate);
-}
-
 // the two re-laying passes of one operand each, and the product on re-laid operands
-static vcnn_status relay_input(const HaloBf16Plan& p, int n, int c, int h, int w, const void* x, void* x8_buf, hipStream_t st) {
+static vcnn_status relay_input(const HaloBf16Plan& p, int n, int c, int h, int w, const void* x, void* x8_buf, hipStream_t st,
+                               const Declined& only = {}) {
   const int64_t total = (int64_t)n * p.cg * h * w;
-  hipLaunchKernelGGL(interleave_channels_kernel, dim3((unsigned)ceil_div(total, kThreads)), dim3(kThreads), 0, st,
-                     (const bf16*)x, (uint4*)x8_buf, c, p.cg, h * w, total);
+  hipLaunchKernelGGL(only.of_any ? interleave_channels_kernel<true> : interleave_channels_kernel<false>, dim3((unsigned)ceil_div(total, kThreads)), dim3(kThreads), 0, st,
+                     (const bf16*)x, (uint4*)x8_buf, c, p.cg, h * w, total, only);
   return check_launch("interleave_channels");
 }
 
 static vcnn_status relay_kernels(const HaloBf16Plan& p, int c, int m, int rs, const void* wgt, int64_t w_so, int64_t w_si,
-                                 int flip, void* wf_buf, hipStream_t st) {
+                                 int flip, void* wf_buf, hipStream_t st, const Declined& only = {}) {
   const int tile = p.m16 ? 16 : 32;
   const int bm = tile * p.tm * p.waves_m;
   const int tiles_m = (int)ceil_div(m, bm);
@@ -849,19 +864,20 @@ static vcnn_status relay_kernels(const HaloBf16Plan& p, int c, int m, int rs, co
   const int64_t total = (int64_t)tiles_m * (bm / tile) * p.nchunks * steps * 512;
   if (rs % 8 == 0 && w_so % 8 == 0 && w_si % 8 == 0 && (reinterpret_cast<uintptr_t>(wgt) & 15) == 0) {
     const int64_t threads = (int64_t)tiles_m * (bm / tile) * p.nchunks * (p.uch / 8) * tile * 8;
-    hipLaunchKernelGGL(reorder_weights_frag8_kernel, dim3((unsigned)ceil_div(threads, kThreads)), dim3(kThreads), 0, st,
-                       (const bf16*)wgt, (bf16*)wf_buf, m, c, rs, w_so, w_si, flip, p.cgc, p.nchunks, p.uch, p.m16, threads);
+    hipLaunchKernelGGL(only.of_any ? reorder_weights_frag8_kernel<true> : reorder_weights_frag8_kernel<false>, dim3((unsigned)ceil_div(threads, kThreads)), dim3(kThreads), 0, st,
+                       (const bf16*)wgt, (bf16*)wf_buf, m, c, rs, w_so, w_si, flip, p.cgc, p.nchunks, p.uch, p.m16, threads, only);
     return check_launch("reorder_weights_frag8");
   }
-  hipLaunchKernelGGL(reorder_weights_frag_kernel, dim3((unsigned)ceil_div(total, kThreads)), dim3(kThreads), 0, st,
-                     (const bf16*)wgt, (bf16*)wf_buf, m, c, rs, w_so, w_si, flip, p.cgc, p.nchunks, steps, p.m16, total);
+  hipLaunchKernelGGL(only.of_any ? reorder_weights_frag_kernel<true> : reorder_weights_frag_kernel<false>, dim3((unsigned)ceil_div(total, kThreads)), dim3(kThreads), 0, st,
+                     (const bf16*)wgt, (bf16*)wf_buf, m, c, rs, w_so, w_si, flip, p.cgc, p.nchunks, steps, p.m16, total, only);
   return check_launch("reorder_weights_frag");
 }
 
 static vcnn_status launch_product(const HaloBf16Plan& p, int n, int h, int w, int m, int r, int s, int ph, int pw,
                                   const float* bias, void* y, int relu, const void* x8_buf, const void* wf_buf,
                                   hipStream_t st, float* y32, int accumulate, const SplitScales* sc = nullptr,
-                                  const float* flip_w = nullptr, float* flipped = nullptr, int flip_m = 0) {
+                                  const float* flip_w = nullptr, float* flipped = nullptr, int flip_m = 0,
+                                  const Declined& only = {}) {
   const uint4* x8 = (const uint4*)x8_buf;
   const int tile = p.m16 ? 16 : 32;
   const int bm = tile * p.tm * p.waves_m;
@@ -869,7 +885,8 @@ static vcnn_status launch_product(const HaloBf16Plan& p, int n, int h, int w, in
   a.x8 = x8, a.zero = x8 + (int64_t)n * p.cg * h * w, a.wf = (const uint4*)wf_buf, a.bias = bias, a.y = (bf16*)y;
   a.x8_term = (int64_t)(p.x8_bytes / 16), a.wf_term = (int64_t)(p.wf_bytes / 16);  // (read by the split forms only)
   a.y32 = y32, a.accumulate = accumulate;
-  if (sc) a.image_exponent = sc->exponent[0], a.exponent = sc->exponent[1], a.declined = sc->declined();
+  a.declined = sc ? sc->declined() : only;
+  if (sc) a.image_exponent = sc->exponent[0], a.exponent = sc->exponent[1];
   a.flip_w = flip_w, a.flipped = flipped, a.flip_m = flip_m;
   a.n = n, a.h = h, a.w = w, a.m = m, a.r = r, a.s = s, a.ph = ph, a.pw = pw;
   a.oh = h + 2 * ph - r + 1, a.ow = w + 2 * pw - s + 1;
@@ -889,6 +906,15 @@ static vcnn_status launch_product(const HaloBf16Plan& p, int n, int h, int w, in
   else if (p.tn == 4) launch_tn<4>(a, p.waves_m, p.waves_n, p.tm, p.terms, p.lds_bytes, st);
   else launch_tn<5>(a, p.waves_m, p.waves_n, p.tm, p.terms, p.lds_bytes, st);
   return check_launch("conv_halo_bf16");
+}
+
+vcnn_status launch_conv_halo_bf16(const HaloBf16Plan& p, int n, int c, int h, int w, int m, int r, int s, int ph, int pw,
+                                  const void* x, const void* wgt, int64_t w_so, int64_t w_si, int flip, const float* bias,
+                                  void* y, int relu, void* workspace, hipStream_t st, float* y32, int accumulate, const Declined& only) {
+  char* const wf = (char*)workspace + p.x8_bytes;
+  if (vcnn_status e = relay_input(p, n, c, h, w, x, workspace, st, only)) return e;
+  if (vcnn_status e = relay_kernels(p, c, m, r * s, wgt, w_so, w_si, flip, wf, st, only)) return e;
+  return launch_product(p, n, h, w, m, r, s, ph, pw, bias, y, relu, workspace, wf, st, y32, accumulate, nullptr, nullptr, nullptr, 0, only);
 }
 
 vcnn_status launch_conv_halo_bf16_prepared(const HaloBf16Plan& p, int n, int c, int h, int w, int m, int r, int s, int ph,
@@ -938,7 +964,7 @@ vcnn_status launch_conv_halo_f16x2(const HaloBf16Plan& p, int n, int c, int h, i
   a.so = w_so, a.si = w_si, a.CO = m, a.RS = r * s, a.flip = flip, a.cgc = p.cgc, a.nchunks = p.nchunks, a.m16 = p.m16;
   a.image_blocks = (int)ceil_div((int64_t)p.cg * h * w, kThreads);
   a.x_blocks = n * a.image_blocks, a.sc = sc;
-  hipLaunchKernelGGL(halo_split_kernel, dim3((unsigned)(a.x_blocks + ceil_div(a.w_total, kThreads))), dim3(kThreads), 0, st, a);
+  hipLaunchKernelGGL(sc.only.of_any ? halo_split_kernel<true> : halo_split_kernel<false>, dim3((unsigned)(a.x_blocks + ceil_div(a.w_total, kThreads))), dim3(kThreads), 0, st, a);
   if (vcnn_status e = check_launch("halo_split")) return e;
   return launch_product(p, n, h, w, m, r, s, ph, pw, bias, nullptr, relu, x8_bufs, wf_bufs, st, y32, 0, &sc, wgt, flipped, c);
 }
@@ -955,8 +981,10 @@ vcnn_status launch_conv_halo_f16x2(const HaloBf16Plan& p, int n, int c, int h, i
 // =========================================================================================================
 
 // x8n[ng][pos][i8] = x[8 ng + i8][pos] (pos runs over c, h, w), zero for images >= N; x8n[total] = 0
+template <bool BEHIND>
 __global__ __launch_bounds__(kThreads) void interleave_images_kernel(const bf16* __restrict__ x, uint4* __restrict__ x8n,
-                                                                     int N, int64_t CHW, int64_t total) {
+                                                                     int N, int64_t CHW, int64_t total, Declined only) {
+  if (BEHIND && looks_at_none(only)) return;
   const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   if (i == 0) x8n[total] = make_uint4(0u, 0u, 0u, 0u);
   if (i >= total) return;
@@ -977,9 +1005,11 @@ __global__ __launch_bounds__(kThreads) void interleave_images_kernel(const bf16*
 // the run and the image, zero otherwise.  A thread owns one (map, pixel) and gathers its 8 images; consecutive
 // lanes take consecutive pixels, so the reads are coalesced; the 16-byte writes of neighbouring maps fill
 // whole cache lines between them.
+template <bool BEHIND>
 __global__ __launch_bounds__(kThreads) void dy_fragments_kernel(const bf16* __restrict__ dy, uint4* __restrict__ dyf, int N,
                                                                 int M, int P, int MT, int runs, int bp, int uch,
-                                                                int64_t total) {
+                                                                int64_t total, Declined only) {
+  if (BEHIND && looks_at_none(only)) return;
   const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   if (i >= total) return;
   const int u = (int)(i % uch);
@@ -1011,9 +1041,11 @@ __global__ __launch_bounds__(kThreads) void dy_fragments_kernel(const bf16* __re
 // one map each, then read 32 different banks.
 static constexpr int kFragPixels = 64, kFragPitch = 66;
 
+template <bool BEHIND>
 __global__ __launch_bounds__(kThreads) void dy_fragments_tile_kernel(const bf16* __restrict__ dy, uint4* __restrict__ dyf,
                                                                      int N, int M, int P, int MT, int runs, int bp, int uch,
-                                                                     int uchunks) {
+                                                                     int uchunks, Declined only) {
+  if (BEHIND && looks_at_none(only)) return;
   __shared__ uint16_t tile[8 * 32 * kFragPitch];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int b = blockIdx.x;
@@ -1059,10 +1091,12 @@ __global__ __launch_bounds__(kThreads) void dy_fragments_tile_kernel(const bf16*
 
 // The two re-laying passes of the kernel gradient for float operands as two f16 terms each (split_f16.h), in the layouts
 // above, one plane per term; block 0 leaves the operand's scale for the product kernel.
+template <bool BEHIND>
 __global__ __launch_bounds__(kThreads) void interleave_images_split_kernel(const float* __restrict__ x,
                                                                            uint4* __restrict__ x8n, int64_t term, int N,
                                                                            int64_t CHW, int64_t total,
                                                                            SplitScales sc) {
+  if (BEHIND && looks_at_none(sc.only)) return;
   const uint32_t largest = split_max(sc.partial[0], sc.blocks);
   const int e = split_exponent(largest);
   const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
@@ -1097,10 +1131,12 @@ __global__ __launch_bounds__(kThreads) void interleave_images_split_kernel(const
 // (as dy_fragments_tile_kernel, 32 pixels at a time: an element takes four bytes of the tile, its two terms.  The pitch
 // of 33 words keeps both sides on different banks: reads of one pixel column step a row per lane.)
 static constexpr int kSplitFragPixels = 32, kSplitFragPitch = 33;
+template <bool BEHIND>
 __global__ __launch_bounds__(kThreads) void dy_fragments_split_kernel(const float* __restrict__ dy, uint4* __restrict__ dyf,
                                                                       int64_t term, int N, int M, int P, int MT, int runs,
                                                                       int bp, int uch, int uchunks,
                                                                       SplitScales sc) {
+  if (BEHIND && looks_at_none(sc.only)) return;
   __shared__ uint32_t tile[8 * 32 * kSplitFragPitch];
   const uint32_t largest = split_max(sc.partial[1], kAbsMaxBlocks);
   const int e = split_exponent(largest);
@@ -1159,7 +1195,7 @@ struct FilterBf16Args {
   int64_t x8n_term;   // TERMS > 1: distance between the terms of x8n, and of dyf, in 16-byte words
   int64_t dyf_term;
   const int32_t* exponent[2];  // TERMS = 2: the two operands' scales
-  const uint32_t* declined;    // TERMS = 2: nonzero: left to the float kernel
+  const uint32_t* declined;    // TERMS = 2: nonzero: none of this kernel's; BEHIND: zero
   float* out;         // [splits][m][K]
   int c, h, w, m, r, s, ph, pw, oh, ow;
   int K;              // c*r*s
@@ -1174,7 +1210,7 @@ struct FilterBf16Args {
 // fragments at about the same time, all but one from the first-level cache).  TERMS = 3: both operands as three
 // bfloat16 terms each, the six largest term products per step - smallest first - into the same accumulators, with the
 // operands of a step requested one step ahead, in order of first use, between the MFMAs (as in the forward kernel).
-template <int WAVES_M, int WAVES_K, int TM, int TN, int WAVES_N = 1, int TERMS = 1>
+template <int WAVES_M, int WAVES_K, int TM, int TN, int WAVES_N = 1, int TERMS = 1, bool BEHIND = false>
 __global__ __launch_bounds__(kThreads, 2) void filter_grad_bf16_kernel(FilterBf16Args a) {
   static_assert(WAVES_M * WAVES_K * WAVES_N * 64 == kThreads, "four waves per block");
   static_assert(TERMS >= 1 && TERMS <= 3, "plain bfloat16 operands, or floats as two f16 or three bfloat16 terms");
@@ -1182,6 +1218,7 @@ __global__ __launch_bounds__(kThreads, 2) void filter_grad_bf16_kernel(FilterBf1
   constexpr int PAIRS = Split::PAIRS;
   constexpr int BM = 32 * TM * WAVES_M, WN = 32 * TN, BN = WN * WAVES_N;
   if (TERMS == 2 && *a.declined) return;
+  if (BEHIND && *a.declined == 0) return;
   extern __shared__ uint4 smem16[];
   int* const tbl = reinterpret_cast<int*>(smem16);  // [uch], per slab of 8 pixels: [half][4]
   uint4* const hbuf = smem16 + a.uch / 4;           // nbuf x TERMS x [ccs][nr][wp], each padded to hpos positions
@@ -1577,14 +1614,18 @@ bool filter_grad_bf16_plan(const ConvGeom& g, FilterGradBf16Plan* p, int terms, 
 
 template <int WAVES_M, int WAVES_K, int TM, int TN, int WAVES_N = 1, int TERMS = 1>
 static void launch_filter_one(const FilterBf16Args& a, unsigned tiles, unsigned splits, size_t lds, hipStream_t st) {
-  auto kernel = filter_grad_bf16_kernel<WAVES_M, WAVES_K, TM, TN, WAVES_N, TERMS>;
-  static bool opted = false;
-  if (!opted) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)kLdsBudget);
-    opted = true;
-  }
-  hipLaunchKernelGGL(kernel, dim3(tiles, splits), dim3(kThreads), lds, st, a);
+  auto go = [&](auto kernel, bool& opted) {
+    if (!opted) {
+      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)kLdsBudget);
+      opted = true;
+    }
+    hipLaunchKernelGGL(kernel, dim3(tiles, splits), dim3(kThreads), lds, st, a);
+  };
+  static bool opted[2] = {};
+  if constexpr (TERMS == 1)
+    if (a.declined) return go(filter_grad_bf16_kernel<WAVES_M, WAVES_K, TM, TN, WAVES_N, 1, true>, opted[1]);
+  go(filter_grad_bf16_kernel<WAVES_M, WAVES_K, TM, TN, WAVES_N, TERMS>, opted[0]);
 }
 
 template <int TN>
@@ -1597,44 +1638,48 @@ static void launch_filter_tn(const FilterBf16Args& a, int waves_m, int tm, unsig
 }
 
 vcnn_status launch_filter_grad_bf16(const FilterGradBf16Plan& p, const ConvGeom& g0, const void* x, const void* dy,
-                                    float* dw, void* workspace, hipStream_t st, int accumulate) {
+                                    float* dw, void* workspace, hipStream_t st, int accumulate, const Declined& only) {
   return launch_filter_grad_bf16_prepared(p, g0, x, dy, dw, workspace, (char*)workspace + p.x8n_bytes,
-                                          (float*)((char*)workspace + p.x8n_bytes + p.dyf_bytes), st, accumulate);
+                                          (float*)((char*)workspace + p.x8n_bytes + p.dyf_bytes), st, accumulate, only);
 }
 
-static vcnn_status relay_images(const FilterGradBf16Plan& p, const ConvGeom& g, const void* x, void* x8n_buf, hipStream_t st) {
+static vcnn_status relay_images(const FilterGradBf16Plan& p, const ConvGeom& g, const void* x, void* x8n_buf, hipStream_t st,
+                                const Declined& only = {}) {
   const int64_t chw = (int64_t)g.c * g.h * g.w;
   const int64_t total = (int64_t)p.ngroups * chw;
-  hipLaunchKernelGGL(interleave_images_kernel, dim3((unsigned)ceil_div(total, kThreads)), dim3(kThreads), 0, st,
-                     (const bf16*)x, (uint4*)x8n_buf, g.n, chw, total);
+  hipLaunchKernelGGL(only.of_any ? interleave_images_kernel<true> : interleave_images_kernel<false>, dim3((unsigned)ceil_div(total, kThreads)), dim3(kThreads), 0, st,
+                     (const bf16*)x, (uint4*)x8n_buf, g.n, chw, total, only);
   return check_launch("interleave_images");
 }
 
-static vcnn_status relay_dy(const FilterGradBf16Plan& p, const ConvGeom& g, const void* dy, void* dyf_buf, hipStream_t st) {
+static vcnn_status relay_dy(const FilterGradBf16Plan& p, const ConvGeom& g, const void* dy, void* dyf_buf, hipStream_t st,
+                            const Declined& only = {}) {
   const int uchunks = (int)ceil_div(p.uch, kFragPixels);
   const int64_t blocks = (int64_t)p.ngroups * p.mt_total * p.runs * uchunks;
   if (blocks <= 0x7fffffffLL && p.uch >= kFragPixels / 2) {  // (short runs would leave most of a block's pixels empty)
-    hipLaunchKernelGGL(dy_fragments_tile_kernel, dim3((unsigned)blocks), dim3(kThreads), 0, st, (const bf16*)dy,
-                       (uint4*)dyf_buf, g.n, (int)g.M, (int)g.P, p.mt_total, p.runs, p.bp, p.uch, uchunks);
+    hipLaunchKernelGGL(only.of_any ? dy_fragments_tile_kernel<true> : dy_fragments_tile_kernel<false>, dim3((unsigned)blocks), dim3(kThreads), 0, st, (const bf16*)dy,
+                       (uint4*)dyf_buf, g.n, (int)g.M, (int)g.P, p.mt_total, p.runs, p.bp, p.uch, uchunks, only);
     return check_launch("dy_fragments_tile");
   }
   const int64_t total = (int64_t)p.ngroups * p.mt_total * 32 * p.runs * p.uch;
-  hipLaunchKernelGGL(dy_fragments_kernel, dim3((unsigned)ceil_div(total, kThreads)), dim3(kThreads), 0, st,
-                     (const bf16*)dy, (uint4*)dyf_buf, g.n, (int)g.M, (int)g.P, p.mt_total, p.runs, p.bp, p.uch, total);
+  hipLaunchKernelGGL(only.of_any ? dy_fragments_kernel<true> : dy_fragments_kernel<false>, dim3((unsigned)ceil_div(total, kThreads)), dim3(kThreads), 0, st,
+                     (const bf16*)dy, (uint4*)dyf_buf, g.n, (int)g.M, (int)g.P, p.mt_total, p.runs, p.bp, p.uch, total, only);
   return check_launch("dy_fragments");
 }
 
 // the product on re-laid operands (g flattened), slices summed into dw (added to its contents when `accumulate`)
 static vcnn_status launch_filter_product(const FilterGradBf16Plan& p, const ConvGeom& g, float* dw, const void* x8n_buf,
                                          const void* dyf_buf, float* partial, hipStream_t st, int accumulate,
-                                         const SplitScales* sc = nullptr, const OtherSlices& other = {}) {
+                                         const SplitScales* sc = nullptr, OtherSlices other = {}, const Declined& only = {}) {
   const uint4* x8n = (const uint4*)x8n_buf;
   const int64_t chw = (int64_t)g.c * g.h * g.w;
   FilterBf16Args a{};
   // accumulate: dw += the product (the slice sum takes dw as its addend); the workspace then holds at least one slice
   a.x8n = x8n, a.zero = x8n + (int64_t)p.ngroups * chw, a.dyf = (const uint4*)dyf_buf;
   a.x8n_term = (int64_t)(p.x8n_bytes / 16), a.dyf_term = (int64_t)(p.dyf_bytes / 16);  // (read by the split forms only)
-  if (sc) a.exponent[0] = sc->exponent[0], a.exponent[1] = sc->exponent[1], a.declined = sc->any;
+  if (sc) a.exponent[0] = sc->exponent[0], a.exponent[1] = sc->exponent[1];
+  a.declined = sc ? sc->any : only.of_any;
+  other.of_any = sc ? sc->only.of_any : only.of_any;
   a.out = (p.splits > 1 || accumulate) ? partial : dw;
   a.c = g.c, a.h = g.h, a.w = g.w, a.m = g.k, a.r = g.r, a.s = g.s, a.ph = g.ph, a.pw = g.pw, a.oh = g.oh, a.ow = g.ow;
   a.K = (int)g.K;
@@ -1664,13 +1709,13 @@ static vcnn_status launch_filter_product(const FilterGradBf16Plan& p, const Conv
 
 vcnn_status launch_filter_grad_bf16_prepared(const FilterGradBf16Plan& p, const ConvGeom& g0, const void* x, const void* dy,
                                              float* dw, void* x8n_buf, void* dyf_buf, float* partial, hipStream_t st,
-                                             int accumulate) {
+                                             int accumulate, const Declined& only) {
   const ConvGeom g = flatten_pointwise(g0);
   if (x)
-    if (vcnn_status e = relay_images(p, g, x, x8n_buf, st)) return e;
+    if (vcnn_status e = relay_images(p, g, x, x8n_buf, st, only)) return e;
   if (dy)
-    if (vcnn_status e = relay_dy(p, g, dy, dyf_buf, st)) return e;
-  return launch_filter_product(p, g, dw, x8n_buf, dyf_buf, partial, st, accumulate);
+    if (vcnn_status e = relay_dy(p, g, dy, dyf_buf, st, only)) return e;
+  return launch_filter_product(p, g, dw, x8n_buf, dyf_buf, partial, st, accumulate, nullptr, {}, only);
 }
 
 // Three-term form (p planned with terms = 3): x_terms / dy_terms hold the three bfloat16 terms of the float input and
@@ -1697,12 +1742,12 @@ vcnn_status launch_filter_grad_f16x2(const FilterGradBf16Plan& p, const ConvGeom
   const ConvGeom g = flatten_pointwise(g0);
   const int64_t chw = (int64_t)g.c * g.h * g.w;
   const int64_t total = (int64_t)p.ngroups * chw;
-  hipLaunchKernelGGL(interleave_images_split_kernel, dim3((unsigned)ceil_div(total, kThreads)), dim3(kThreads), 0, st, x,
+  hipLaunchKernelGGL(sc.only.of_any ? interleave_images_split_kernel<true> : interleave_images_split_kernel<false>, dim3((unsigned)ceil_div(total, kThreads)), dim3(kThreads), 0, st, x,
                      (uint4*)x8n_bufs, (int64_t)(p.x8n_bytes / 16), g.n, chw, total, sc);
   if (vcnn_status e = check_launch("interleave_images_split")) return e;
   const int uchunks = (int)ceil_div(p.uch, kSplitFragPixels);
   const int64_t blocks = (int64_t)p.ngroups * p.mt_total * p.runs * uchunks;
-  hipLaunchKernelGGL(dy_fragments_split_kernel, dim3((unsigned)blocks), dim3(kThreads), 0, st, dy, (uint4*)dyf_bufs,
+  hipLaunchKernelGGL(sc.only.of_any ? dy_fragments_split_kernel<true> : dy_fragments_split_kernel<false>, dim3((unsigned)blocks), dim3(kThreads), 0, st, dy, (uint4*)dyf_bufs,
                      (int64_t)(p.dyf_bytes / 16), g.n, (int)g.M, (int)g.P, p.mt_total, p.runs, p.bp, p.uch, uchunks, sc);
   if (vcnn_status e = check_launch("dy_fragments_split")) return e;
   OtherSlices other{};

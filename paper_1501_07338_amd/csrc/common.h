@@ -24,22 +24,38 @@ struct ConvGeom {
   int64_t M, K, N;
 };
 
-// The images a two-term product leaves to the float kernel behind it (split_f16.h): words the re-laying passes write on
-// the device.  A float kernel that is given them (any != null) computes only those images.
+// The images that one pass leaves to another behind it, words on the device.  Two may follow one another: a pass through the
+// Fourier domain (spectral.h) declines images, a direct route computes those alone (`of`), and where that is a
+// two-term product (split_f16.h) its re-laying passes decline some of them in turn, for the float kernel.
 struct Declined {
-  const uint32_t* any;    // nonzero: at least one image
-  const uint32_t* all;    // nonzero: every image
-  const uint32_t* image;  // [image] nonzero: that one
+  const uint32_t* any;     // given: of a two-term product: nonzero: at least one image ...
+  const uint32_t* all;     // ... every image
+  const uint32_t* image;   // ... [image] that one
+  const uint32_t* of_any;  // given: only images that a pass before has declined are looked at: nonzero: there are any ...
+  const uint32_t* of;      // ... [image] that one (null: all or none)
+
+  Declined from(int n0) const {  // for images n0 and on
+    Declined d = *this;
+    if (d.image) d.image += n0;
+    if (d.of) d.of += n0;
+    return d;
+  }
 };
 __device__ __forceinline__ bool is_declined(const Declined& d, int n) { return (*d.all | d.image[n]) != 0; }
-__device__ __forceinline__ bool leave_image(const Declined& only, int n) { return only.any && !is_declined(only, n); }
-__device__ __forceinline__ bool leave_all(const Declined& only) { return only.any && *only.any == 0; }
+__device__ __forceinline__ bool looks_at_none(const Declined& d) { return d.of_any && *d.of_any == 0; }
+__device__ __forceinline__ bool looks_at(const Declined& d, int n) { return !d.of_any || (d.of ? d.of[n] != 0 : *d.of_any != 0); }
+// For the kernel behind (only: given any, or of_any): whether image n, whether everything is none of its own.
+__device__ __forceinline__ bool leave_image(const Declined& only, int n) {
+  return !looks_at(only, n) || (only.any && !is_declined(only, n));
+}
+__device__ __forceinline__ bool leave_all(const Declined& only) { return looks_at_none(only) || (only.any && *only.any == 0); }
 
 // Slices a sum takes in place of its own if a product was declined (splits = 0: there is nothing left to add then).
 struct OtherSlices {
   const uint32_t* declined;  // given: the word of Declined that decides
   const float* partial;
   int splits;
+  const uint32_t* of_any;    // given: zero: no sum at all
 };
 
 // ---- unroll.hip ---------------------------------------------------------------------------------
@@ -231,7 +247,7 @@ double halo_bf16_seconds(const HaloBf16Plan& p, int n, int m, int r, int s, int6
 vcnn_status launch_conv_halo_bf16(const HaloBf16Plan& p, int n, int c, int h, int w, int m, int r, int s, int ph, int pw,
                                   const void* x, const void* wgt, int64_t w_so, int64_t w_si, int flip, const float* bias,
                                   void* y, int relu, void* workspace, hipStream_t st, float* y32 = nullptr,
-                                  int accumulate = 0);  // y32: float result (added to its contents when accumulate) instead of y
+                                  int accumulate = 0, const Declined& only = {});  // y32: float result (added to its contents when accumulate) instead of y
 // The same with the two re-laid operands in buffers of the caller (x8_bytes, wf_bytes); a null x or wgt means that its
 // buffer already holds that operand from an earlier call.
 vcnn_status launch_conv_halo_bf16_prepared(const HaloBf16Plan& p, int n, int c, int h, int w, int m, int r, int s, int ph,
@@ -261,12 +277,12 @@ bool filter_grad_bf16_plan(const ConvGeom& g, FilterGradBf16Plan* p, int terms =
 // workspace: x8n_bytes + dyf_bytes + partial_bytes
 // accumulate: dw += the product; the workspace then needs max(partial_bytes, one slice of M*K floats) behind dyf
 vcnn_status launch_filter_grad_bf16(const FilterGradBf16Plan& p, const ConvGeom& g, const void* x, const void* dy,
-                                    float* dw, void* workspace, hipStream_t st, int accumulate = 0);
+                                    float* dw, void* workspace, hipStream_t st, int accumulate = 0, const Declined& only = {});
 // The same with the re-laid operands in buffers of the caller (x8n_bytes, dyf_bytes; null x or dy: already there) and
 // the slices in `partial`.
 vcnn_status launch_filter_grad_bf16_prepared(const FilterGradBf16Plan& p, const ConvGeom& g, const void* x, const void* dy,
                                              float* dw, void* x8n_buf, void* dyf_buf, float* partial, hipStream_t st,
-                                             int accumulate);
+                                             int accumulate, const Declined& only = {});
 vcnn_status launch_filter_grad_bf16_terms(const FilterGradBf16Plan& p, const ConvGeom& g, const void* x_terms,
                                           size_t x_term_bytes, const void* dy_terms, size_t dy_term_bytes, float* dw,
                                           void* x8n_bufs, void* dyf_bufs, float* partial, hipStream_t st);
@@ -286,8 +302,8 @@ vcnn_status launch_filter_behind(const FilterBehind& b, float* dw, const Decline
 // Bytes of the scales of a product of `images` images, and their layout in the workspace for `images_at_once` of them (a
 // part of the batch); operand 0 has `per_image` floats per image and scale, operand 1 `others`.
 size_t split_scales_bytes(int images);
-SplitScales split_scales(void* workspace, int images, int images_at_once, int64_t per_image, int64_t others);
-Declined split_declined(const void* workspace, int images);
+SplitScales split_scales(void* workspace, int images, int images_at_once, int64_t per_image, int64_t others, const Declined& only = {});
+Declined split_declined(const void* workspace, int images, const Declined& only = {});
 // partial maxima of the images of a and of b (nb = 0: b's scale and words are left as they are); `first`: of the call
 vcnn_status launch_absmax(const float* a, int images, int64_t per_image, const float* b, int64_t nb, const SplitScales& sc,
                           bool first, hipStream_t st);
@@ -339,11 +355,11 @@ struct F16x2Plan {
 // kernel gradient where they leave room for larger parts; false if there is none (or the layer does not fit the kernels).
 bool conv_f16x2_plan(const ConvGeom& g, int pass, size_t budget, F16x2Plan* p);
 vcnn_status launch_conv_f16x2_fwd(const F16x2Plan& p, const ConvGeom& g, const float* x, const float* w, const float* bias,
-                                  float* y, int relu, void* workspace, hipStream_t st);
+                                  float* y, int relu, void* workspace, hipStream_t st, const Declined& only = {});
 vcnn_status launch_conv_f16x2_bwd_data(const F16x2Plan& p, const ConvGeom& g, const float* w, const float* dy, float* dx,
-                                       float* flipped, void* workspace, hipStream_t st);
+                                       float* flipped, void* workspace, hipStream_t st, const Declined& only = {});
 vcnn_status launch_conv_f16x2_filter(const F16x2Plan& p, const ConvGeom& g, const float* x, const float* dy, float* dw,
-                                     void* workspace, void* scales, const FilterBehind& behind, hipStream_t st);
+                                     void* workspace, void* scales, const FilterBehind& behind, hipStream_t st, const Declined& only = {});
 
 // ---- split_bf16.hip: fp32 products of large layers as sums of bf16 products (on request only) ------------------------
 struct SplitPlan {

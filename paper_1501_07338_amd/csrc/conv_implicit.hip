@@ -36,7 +36,7 @@ struct HaloArgs {
   int kch;            // taps per full chunk, padded to a multiple of BK
   int relu;
   int tw, tiles_x;    // tw > 0: a tile is a strip of BN / tw output rows x tw output columns (tiles_x strips side by side)
-  Declined only;      // given: only the images a two-term product left to this kernel
+  Declined only;      // given: only the images that the pass before left to this kernel
 };
 
 // Pixel q of a block's tile as a flat index into the sample's output plane (-1: outside it), and its position inside
@@ -631,7 +631,7 @@ struct HaloFilterArgs {
   int runs_per_split;
   int ccs;           // channels a block's column range can span
   int nr, wp;
-  Declined only;     // given: only if a two-term product left anything to this kernel
+  Declined only;     // given: only if the pass before left anything to this kernel
 };
 
 template <int BM, int BNK, int WM, int WN, int BK, bool VEC, typename T>
@@ -1079,7 +1079,7 @@ vcnn_status launch_conv_halo_filter(const HaloFilterPlan& p, int dtype, const Co
   if (vcnn_status s = check_launch("conv_halo_filter")) return s;
   if (with_bias) return launch_sum_slices_split(partial, dw, dbias, g.M, (int)g.K, p.splits, st);
   if (p.splits == 1 || only.any) return VCNN_OK;
-  return launch_sum_slices(partial, nullptr, dw, VCNN_F32, g.M * g.K, p.splits, 1, 1, 0, st);
+  return launch_sum_slices(partial, nullptr, dw, VCNN_F32, g.M * g.K, p.splits, 1, 1, 0, st, {nullptr, nullptr, 0, only.of_any});
 }
 
 // =========================================================================================================

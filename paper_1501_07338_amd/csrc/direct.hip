@@ -263,6 +263,7 @@ __global__ __launch_bounds__(kThreads) void direct_few_out_kernel(DirectGeom g, 
 // *in_pairs: the slices are a two-term product's, whose errors leave less room for the sum's own (see sum_eight).
 __device__ __forceinline__ bool choose_slices(const OtherSlices& other, const float** partial, int* splits, const float** bias,
                                               bool* in_pairs) {
+  if (other.of_any && *other.of_any == 0) return false;
   *in_pairs = other.declined != nullptr;
   if (other.declined && *other.declined) *partial = other.partial, *splits = other.splits, *bias = nullptr, *in_pairs = false;
   return *splits > 0;

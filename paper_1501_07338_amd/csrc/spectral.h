@@ -51,7 +51,7 @@ struct SpectralPlan {
   size_t image_bytes;      // spectra over the input channels (input gradient: one slice per split)
   size_t map_bytes;        // spectra over the output maps (of a part)
   size_t taps_bytes;       // row spectra of the kernels (of a part; kernel gradient: one slice per split)
-  size_t words_bytes;      // energies, masks, maxima, sums and Declined
+  size_t words_bytes;      // energies, masks, maxima, sums and the words of Declined: behind everything else
   size_t workspace_bytes;
   double est_seconds;
 };
@@ -62,7 +62,7 @@ vcnn_status launch_spectral_bwd_data(const SpectralPlan& p, int dtype, const Con
                                      void* workspace, hipStream_t st);
 vcnn_status launch_spectral_filter(const SpectralPlan& p, int dtype, const ConvGeom& g, const void* x, const void* dy, float* dw,
                                    float* db, void* workspace, hipStream_t st);
-// The images these passes leave to the float kernel behind them.
+// The images these passes leave to the route behind them.
 Declined spectral_declined(const ConvGeom& g, int pass, const SpectralPlan& p, const void* workspace);
 
 // ---- spectral_fft.hip -----------------------------------------------------------------------------------------------

@@ -476,16 +476,20 @@ bool spectral_plan(const ConvGeom& g, int pass, size_t budget, SpectralPlan* p) 
   }
   q.workspace_bytes = q.image_bytes + q.map_bytes + q.taps_bytes + q.words_bytes;
   if (q.workspace_bytes > budget) return false;
-  // What the transforms read and write at 4.4 TB/s, and the products: blocks of so many steps of four, two of them resident on
-  // each of 256 CUs at 2.7 us a step (3.4 where the larger operand is read by every block; one alone 2.2 us), four steps' worth
-  // to begin and to end with.  (110 passes of 40 drawn layers, 44 to 861 us, take 0.75 to 1.2 times this.)
-  const double parts = (double)ceil_div(g.k, q.part), e = 4, pixels = (double)g.n * ((double)g.c * g.h * g.w + (double)g.k * g.P);
+  // What the transforms read and write at 4.4 TB/s (the image spectra again for each part of a forward pass), and the products: blocks
+  // of so many steps of four, two of them resident on each of 256 CUs at 2.7 us a step (3.4 where the larger operand is read
+  // by every block; one alone 2.2 us), four steps' worth to begin and to end with; of that a share as fitted below; the scan of the energies, and 9 us for the guard
+  // and for the launches of each part.  (229 passes of drawn layers, 40 us to 1.8 ms, with the launches behind: 0.9 to 1.1 times this in eight
+  // of ten.)
+  const double parts = (double)ceil_div(g.k, q.part), e = 4, x_pixels = (double)g.n * g.c * g.h * g.w, y_pixels = (double)g.n * g.k * g.P;
   const double result = data ? (double)image : (filter ? (double)g.k * g.c * taps : (double)tiles * g.k * spectrum), flushes = std::ceil(q.per_split / (double)q.flush) - 1;
-  const double bytes = pixels * e + 2.0 * (double)(q.image_bytes + (size_t)(tiles * g.k * spectrum)) + 2.0 * flushes * result * q.splits * 0.75 +
-                       2.0 * (double)g.k * g.c * taps * (filter ? q.splits : 1) + (double)g.M * g.K * e;
-  const double blocks = columns * std::ceil(rows / 16) * std::ceil(cols / 16) * q.splits, steps = std::ceil(q.per_split / 4.0) + 4;
-  q.est_seconds = bytes / 4.4e12 + (blocks <= 256 ? 2.2e-6 : std::ceil(blocks / 512) * (data ? 3.4e-6 : 2.7e-6)) * steps + 5e-6 * (1 + (q.along ? 2 : 3) * parts);
-  if (q.along) q.est_seconds *= filter ? 1.0 : 0.87;  // (measured against 100 passes of lines: 0.75 to 1.15 times the above)
+  const double bytes = (x_pixels + y_pixels) * e + 2.0 * (double)(q.image_bytes + (size_t)(tiles * g.k * spectrum)) + 2.0 * flushes * result * q.splits * 0.75 +
+                       2.0 * (double)g.k * g.c * taps * (filter ? q.splits : 1) + (double)g.M * g.K * e + (parts - 1) * (double)image;
+  const double blocks = columns * std::ceil((data ? rows : (double)std::min<int64_t>(q.part, g.k)) / 16) * std::ceil(cols / 16) * q.splits, steps = std::ceil(q.per_split / 4.0) + 4;
+  const double product = parts * (blocks <= 256 ? 2.2e-6 : std::ceil(blocks / 512) * (data ? 3.4e-6 : 2.7e-6)) * steps;
+  const double share = filter ? (q.along ? 0.85 : 0.7) : (data ? (q.along ? 0.9 : 0.82) : (q.along ? 0.92 : 0.87));
+  const double scanned = (filter ? x_pixels + y_pixels : (data ? y_pixels : x_pixels)) * e;
+  q.est_seconds = share * (bytes / 4.4e12 + product) + scanned / 4e12 + 9e-6 * (1 + parts);
   *p = q;
   return true;
 }
@@ -781,8 +785,8 @@ vcnn_status launch_spectral_filter(const SpectralPlan& p, int dtype, const ConvG
 }
 
 Declined spectral_declined(const ConvGeom& g, int pass, const SpectralPlan& p, const void* workspace) {
-  const uint32_t* const words = (const uint32_t*)((const char*)workspace + layout(g, pass, p).words);
-  return Declined{words, words + 1, words + 64};
+  const SpectralWords words = words_at(const_cast<void*>(workspace), layout(g, pass, p));
+  return {nullptr, nullptr, nullptr, words.any, pass == VCNN_PASS_BWD_FILTER ? nullptr : words.image};
 }
 
 }  // namespace vcnn

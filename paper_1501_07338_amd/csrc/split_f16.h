@@ -28,6 +28,7 @@
 
 namespace vcnn {
 
+static constexpr uint32_t kNotLookedAt = 2;
 static constexpr int kAbsMaxBlocks = 512;  // partial maxima of an operand with one scale
 
 // What a two-term product keeps about its two operands in the workspace (device pointers; the host lays them out).
@@ -35,17 +36,18 @@ struct SplitScales {
   uint32_t* partial[2];  // largest magnitude (float bits) of each scanning block's share
   int32_t* exponent[2];  // scaled by 2^exponent: one per image, one
   uint32_t* small[2];    // elements below 2^-15 when scaled: per image, one
-  uint32_t* any;         // the words of Declined
-  uint32_t* all;
+  uint32_t* any;         // the words of Declined: kNotLookedAt in `any` and `image` keeps the product from images that `only`
+  uint32_t* all;         // leaves out, so that its kernels need to look at nothing more
   uint32_t* image;
   uint32_t limit[2];     // more small elements than this decline
   int blocks;            // scanning blocks per image of operand 0
+  Declined only;         // (of_any, of) the images that the product is for
 
-  Declined declined() const { return {any, all, image}; }
+  Declined declined() const { return {any, all, image, only.of_any, only.of}; }
   // The same for images n0 and on (a part of the batch).
   SplitScales from(int n0) const {
     SplitScales s = *this;
-    s.exponent[0] += n0, s.small[0] += n0, s.image += n0;
+    s.exponent[0] += n0, s.small[0] += n0, s.image += n0, s.only = s.only.from(n0);
     return s;
   }
 };

@@ -1,5 +1,5 @@
 """Passes through the Fourier domain (the AUTO route of layers with large kernels): parity with the oracle at the edges of
-tiles, planes and slices, what is left to the float kernel on the device, parts, and the direct route where the workspace is
+tiles, planes and slices, what is left to the direct route on the device, parts, and the direct route where the workspace is
 too small."""
 import numpy as np
 import pytest
@@ -21,35 +21,35 @@ TOL = 4e-6
 SHAPES = [
     ((27, 28, 64, 64, 29, 16, 16, 0, 0), {FWD, FILTER, DATA}, False),   # one whole tile; the largest kernel; ragged maps, images
     ((12, 41, 39, 31, 33, 12, 12, 11, 8), {FILTER}, False),             # padded by as much as the kernel; ragged channels
-    ((11, 11, 69, 64, 60, 11, 15, 0, 0), {FWD, FILTER}, False),         # tiles along one axis, the second a few rows
-    ((14, 13, 103, 100, 13, 13, 12, 0, 0), {FWD, DATA}, False),         # 2 x 2 tiles, more than 32 of them
-    ((17, 24, 58, 60, 50, 8, 9, 0, 0), {FILTER}, False),                # odd kernel columns
+    ((11, 11, 69, 64, 97, 11, 15, 0, 0), {FWD, FILTER}, False),         # tiles along one axis, the second a few rows
+    ((19, 13, 103, 100, 13, 13, 12, 0, 0), {FWD, DATA}, False),         # 2 x 2 tiles, more than 32 of them
+    ((17, 36, 58, 60, 82, 8, 9, 0, 0), {FILTER}, False),                # odd kernel columns
     ((41, 13, 95, 41, 12, 14, 13, 1, 1), {DATA}, False),                # padded tiles
-    ((5, 12, 60, 38, 98, 8, 16, 5, 11), {FWD, FILTER}, False),          # more than 64 maps; pads on one side of a tile
+    ((13, 19, 60, 38, 98, 8, 16, 5, 11), {FWD, FILTER}, False),          # more than 64 maps; pads on one side of a tile
     ((64, 20, 64, 64, 80, 16, 16, 0, 0), {FWD, DATA}, False),           # maps in two slices, the second short
     ((40, 11, 64, 64, 150, 16, 16, 0, 0), {FILTER}, False),             # images in two slices, the second short
     ((4, 36, 98, 41, 67, 10, 15, 0, 0), {FILTER}, True),
-    ((30, 29, 64, 62, 180, 16, 16, 0, 0), {FWD, FILTER}, True),
+    ((30, 29, 64, 62, 237, 16, 16, 0, 0), {FWD, FILTER}, True),
     ((16, 38, 64, 64, 512, 16, 16, 0, 0), {DATA}, True),
     ((24, 29, 56, 46, 26, 16, 15, 3, 9), {DATA}, False),                # pads that differ
     # lines: along the width and the height, whole and in tiles, padded, a last pair and a last block that are not full
-    ((7, 20, 42, 214, 36, 1, 100, 0, 0), {FWD, DATA}, False),
+    ((9, 20, 42, 214, 73, 1, 100, 0, 0), {FWD, DATA}, False),
     ((1, 51, 219, 228, 48, 72, 1, 0, 0), {FWD, DATA}, False),
-    ((49, 10, 8, 149, 23, 1, 128, 0, 117), {FWD, DATA}, False),         # the longest kernel
-    ((6, 55, 261, 9, 58, 95, 1, 86, 0), {DATA}, False),
+    ((79, 10, 8, 149, 37, 1, 128, 0, 117), {FWD, DATA}, False),         # the longest kernel
+    ((7, 55, 261, 9, 93, 95, 1, 86, 0), {DATA}, False),
     ((1, 78, 32, 205, 130, 1, 58, 0, 23), {FILTER}, False),
     ((4, 70, 217, 8, 189, 100, 1, 0, 0), {FILTER}, False),
     ((7, 38, 227, 28, 43, 100, 1, 60, 0), {FWD, DATA}, True),
     ((5, 80, 11, 278, 77, 1, 92, 0, 0), {FILTER}, True),
 ]
 # one of every pair of pass and transform, and of the two types
-ONE_EACH = [((9, 22, 70, 70, 49, 16, 16, 0, 0), FWD, False), ((27, 28, 64, 64, 29, 16, 16, 0, 0), DATA, False),
-            ((11, 11, 69, 64, 60, 11, 15, 0, 0), FILTER, False), ((7, 20, 42, 214, 36, 1, 100, 0, 0), FWD, False),
-            ((50, 55, 10, 128, 12, 1, 97, 0, 84), DATA, False), ((4, 70, 217, 8, 189, 100, 1, 0, 0), FILTER, False),
-            ((30, 29, 64, 62, 180, 16, 16, 0, 0), FWD, True), ((16, 38, 64, 64, 512, 16, 16, 0, 0), DATA, True),
-            ((30, 29, 64, 62, 180, 16, 16, 0, 0), FILTER, True), ((7, 38, 227, 28, 43, 100, 1, 60, 0), FWD, True)]
+ONE_EACH = [((11, 22, 70, 70, 51, 16, 16, 0, 0), FWD, False), ((27, 28, 64, 64, 29, 16, 16, 0, 0), DATA, False),
+            ((11, 11, 69, 64, 97, 11, 15, 0, 0), FILTER, False), ((9, 20, 42, 214, 73, 1, 100, 0, 0), FWD, False),
+            ((65, 55, 10, 128, 20, 1, 97, 0, 84), DATA, False), ((4, 70, 217, 8, 189, 100, 1, 0, 0), FILTER, False),
+            ((30, 29, 64, 62, 237, 16, 16, 0, 0), FWD, True), ((16, 38, 64, 64, 512, 16, 16, 0, 0), DATA, True),
+            ((30, 29, 64, 62, 237, 16, 16, 0, 0), FILTER, True), ((7, 38, 227, 28, 43, 100, 1, 60, 0), FWD, True)]
 # lines in odd numbers an image (channels times rows, and maps times rows): a transform's two lines belong to two images
-ODD_LINES = [((7, 21, 43, 214, 37, 1, 100, 0, 0), FWD), ((7, 21, 43, 214, 37, 1, 100, 0, 0), DATA), ((6, 55, 261, 9, 59, 95, 1, 86, 0), DATA)]
+ODD_LINES = [((9, 21, 43, 214, 75, 1, 100, 0, 0), FWD), ((9, 21, 43, 214, 75, 1, 100, 0, 0), DATA), ((7, 55, 261, 9, 95, 95, 1, 86, 0), DATA)]
 
 
 def desc(shape, bf16=False):
@@ -185,8 +185,8 @@ def test_an_image_does_not_depend_on_its_neighbours(shape, which):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("shape,which", ODD_LINES + [((5, 71, 217, 9, 189, 100, 1, 0, 0), FILTER), ((11, 11, 69, 64, 60, 11, 15, 0, 0), FILTER),
-                                                     ((9, 22, 70, 70, 49, 16, 16, 0, 0), FWD)])
+@pytest.mark.parametrize("shape,which", ODD_LINES + [((5, 71, 217, 9, 189, 100, 1, 0, 0), FILTER), ((11, 11, 69, 64, 97, 11, 15, 0, 0), FILTER),
+                                                     ((11, 22, 70, 70, 51, 16, 16, 0, 0), FWD)])
 def test_magnitudes_do_not_mix(shape, which):
     """Powers of two on lines, channels and maps pass through unrounded, whatever the magnitudes beside them: twice a line is
     twice its result, and a channel scaled against its kernels changes nothing."""
@@ -215,7 +215,7 @@ def test_magnitudes_do_not_mix(shape, which):
 @pytest.mark.parametrize("case", ["outlier", "dark", "inf", "nan", "weight", "range"])
 def test_what_the_transforms_do_not_carry(shape, which, bf16, case):
     """An element or a window far from the rest of its plane, infinities and NaN, magnitudes whose products leave a float's
-    range on the way: the pass gives what the float kernel gives, every output to that kernel's own accuracy."""
+    range on the way: the pass gives what the route gives that it replaces, to the bit."""
     d, x, wt, b, dy = tensors(shape, 5300, bf16)
     assert route(d, which) == "spectral"
     b = np.zeros_like(b)
@@ -241,17 +241,42 @@ def test_what_the_transforms_do_not_carry(shape, which, bf16, case):
     else:
         t[0, 1, 3, 3] = np.inf if case == "inf" else np.nan
     with np.errstate(all="ignore"):
-        got, want = run_pass(d, which, x, wt, b, dy), implicit(d, which, x, wt, b, dy)
+        got, want = run_pass(d, which, x, wt, b, dy), replaced(d, which, x, wt, b, dy)
     got, want = (got[0], want[0]) if which == FILTER else (got, want)
-    # what has to be the float kernel's: the image, or all of it
+    # what has to be that route's: the image, or all of it
     image = (0,) if which != FILTER and case not in ("weight", "range") else (slice(None),)
-    g, e = got[image].astype(np.float64), want[image].astype(np.float64)
-    assert np.array_equal(np.isnan(g), np.isnan(e)) and np.array_equal(np.isposinf(g), np.isposinf(e))
-    fine = np.isfinite(e)
-    if which == FILTER:  # (its slices are added in another order there)
-        assert np.max(np.abs(g - e)[fine], initial=0) <= TOL * np.max(np.abs(e[fine]), initial=0)
+    if which == FILTER and case in ("outlier", "dark"):  # (enough meets at every tap: not declined)
+        assert np.max(np.abs(got.astype(np.float64) - want)) <= TOL * np.max(np.abs(want))
     else:
-        assert np.array_equal(g[fine], e[fine])
+        assert np.array_equal(got[image], want[image], equal_nan=True)
+
+
+def replaced_bytes(d, which):
+    """The most workspace with which the pass runs by the route that it replaces."""
+    nbytes = vcnn.conv_workspace_bytes(d, which)
+    while vcnn.conv_route(d, which, nbytes) == "spectral":  # (a forward pass in more and more parts)
+        nbytes -= max(256, nbytes // 256 // 64 * 256) if which == FWD else 256
+    return nbytes
+
+
+def replaced(d, which, x, wt, b, dy):
+    return run_pass(d, which, x, wt, b, dy, replaced_bytes(d, which))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,which,bf16", [t for t in ONE_EACH if t[1] != FILTER] + [(t[0], t[1], False) for t in ODD_LINES])
+def test_only_what_is_declined_changes_hands(shape, which, bf16):
+    """One dim image, and kernels that two half-precision terms do not carry: that image is the direct route's (by the float
+    kernel in its turn), all others stay as they were, to the bit."""
+    d, x, wt, b, dy = tensors(shape, 5350, bf16)
+    assert route(d, which) == "spectral"
+    wt.reshape(d.k, d.c, -1)[..., ::3] *= np.float32(2.0 ** -40)
+    base = run_pass(d, which, x, wt, b, dy)
+    t = x if which == FWD else dy
+    t[-1, :, :d.r + 3, :d.s + 3] *= np.float32(2.0 ** -12)
+    got = run_pass(d, which, x, wt, b, dy)
+    assert np.array_equal(got[:-1], base[:-1])
+    assert np.array_equal(got[-1], replaced(d, which, x, wt, b, dy)[-1]) and not np.array_equal(got[-1], base[-1])
 
 
 def implicit(d, which, x, wt, b, dy):
@@ -297,11 +322,11 @@ def paint(t, shape, case):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("shape,which,bf16", [((27, 28, 64, 64, 29, 16, 16, 0, 0), FWD, False), ((27, 28, 64, 64, 29, 16, 16, 0, 0), DATA, False),
-                                              ((9, 22, 70, 70, 49, 16, 16, 0, 0), FWD, False), ((24, 29, 56, 46, 26, 16, 15, 3, 9), DATA, False),
-                                              ((5, 12, 60, 38, 98, 8, 16, 5, 11), FWD, False), ((14, 13, 103, 100, 13, 13, 12, 0, 0), DATA, False),
-                                              ((7, 20, 42, 214, 36, 1, 100, 0, 0), FWD, False), ((16, 38, 64, 184, 38, 1, 121, 0, 0), DATA, False),
-                                              ((1, 51, 219, 228, 48, 72, 1, 0, 0), FWD, False), ((6, 55, 261, 9, 58, 95, 1, 86, 0), DATA, False),
-                                              ((30, 29, 64, 62, 180, 16, 16, 0, 0), FWD, True), ((16, 38, 64, 64, 512, 16, 16, 0, 0), DATA, True)])
+                                              ((11, 22, 70, 70, 51, 16, 16, 0, 0), FWD, False), ((24, 29, 56, 46, 26, 16, 15, 3, 9), DATA, False),
+                                              ((13, 19, 60, 38, 98, 8, 16, 5, 11), FWD, False), ((19, 13, 103, 100, 13, 13, 12, 0, 0), DATA, False),
+                                              ((9, 20, 42, 214, 73, 1, 100, 0, 0), FWD, False), ((16, 38, 64, 184, 38, 1, 121, 0, 0), DATA, False),
+                                              ((1, 51, 219, 228, 48, 72, 1, 0, 0), FWD, False), ((7, 55, 261, 9, 93, 95, 1, 86, 0), DATA, False),
+                                              ((30, 29, 64, 62, 237, 16, 16, 0, 0), FWD, True), ((16, 38, 64, 64, 512, 16, 16, 0, 0), DATA, True)])
 @pytest.mark.parametrize("case", ["dark", "black", "outlier", "border", "black border"])
 def test_every_window_counts(shape, which, bf16, case):
     """Whatever the rest of a plane holds, an output is exact relative to what it sums itself, wherever its window lies, and an
@@ -321,7 +346,7 @@ def test_every_window_counts(shape, which, bf16, case):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("shape,bf16", [((11, 11, 69, 64, 60, 11, 15, 0, 0), False), ((40, 11, 64, 64, 150, 16, 16, 0, 0), False),
+@pytest.mark.parametrize("shape,bf16", [((11, 11, 69, 64, 97, 11, 15, 0, 0), False), ((40, 11, 64, 64, 150, 16, 16, 0, 0), False),
                                         ((12, 41, 39, 31, 33, 12, 12, 11, 8), False), ((4, 36, 98, 41, 67, 10, 15, 0, 0), True),
                                         ((5, 71, 217, 9, 189, 100, 1, 0, 0), False), ((5, 80, 11, 278, 77, 1, 92, 0, 0), True)])
 @pytest.mark.parametrize("case", ["1", "1e-1", "1e-2", "1e-3", "1e-5", "1e-7", "apart", "edge"])
