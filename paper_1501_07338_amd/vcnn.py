@@ -111,11 +111,14 @@ def _ptr(t):
 
 def _current_stream():
     """The handle of torch's current stream on the current device.  Building torch's stream object takes 2.8 us, half of a
-    small call; its handle alone 0.2 us."""
+    small call; its handle alone 0.2 us, by two functions that torch keeps private: without them, the object."""
     import torch
-    if not torch.cuda.is_initialized():
-        return torch.cuda.current_stream().cuda_stream
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    if torch.cuda.is_initialized():
+        try:
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        except (AttributeError, TypeError):  # (absent, or no longer taking one device number)
+            pass
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _stream(stream):

@@ -136,3 +136,18 @@ def test_workspace_queries_of_every_workload_layer(name):
                         assert 0 <= need <= 3 * patch_matrix + (1 << 29), (name, li, dtype, algo, p, need)
     finally:
         vcnn.set_conv_algo(vcnn.ALGO_AUTO)
+
+
+@pytest.mark.parametrize("raw", ["present", "absent", "other arguments"])
+def test_current_stream_does_not_depend_on_private_functions(monkeypatch, raw):
+    import types
+    import torch
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 3, raising=False)
+    if raw == "absent":
+        monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    else:
+        one, none = (lambda device: 70 + device), (lambda: 0)
+        monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", one if raw == "present" else none, raising=False)
+    assert vcnn._current_stream() == (73 if raw == "present" else 77)
