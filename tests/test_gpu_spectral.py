@@ -133,7 +133,7 @@ def test_small_kernels_and_few_maps_stay():
 def test_queries_and_routes_agree():
     """No GPU needed: over drawn layers a pass runs with exactly what its query asks for and with more; the kernel gradient
     by the same route, and the allocation-free entry point takes no layer that it refused."""
-    rng, seen = np.random.default_rng(3), set()
+    rng, seen, sides = np.random.default_rng(3), set(), set()
     log = lambda lo, hi: int(round(np.exp(rng.uniform(np.log(lo), np.log(hi)))))
     for _ in range(600):
         r, s = int(rng.integers(7, 17)), int(rng.integers(7, 17))
@@ -149,10 +149,33 @@ def test_queries_and_routes_agree():
             if name == "spectral":
                 seen.add((which, bf16))
                 assert which != FWD or need <= 64 << 20
-                if which == FILTER:  # (what it takes without the transforms)
-                    direct = vcnn.conv_workspace_bytes(vcnn.conv_desc(d.n, d.c, d.h, d.w, d.k, d.r, d.s, d.pad_h, d.pad_w, dtype=d.dtype), which)
-                    assert direct == need
-    assert {(FWD, False), (FILTER, False), (DATA, False), (FILTER, True)} <= seen
+                if which == FILTER:
+                    limit = vcnn.conv_bwd_filter_noalloc_limit()
+                    assert (need <= limit) == (direct_filter_bytes(d) <= limit)
+                    sides.add(need <= limit)
+    assert {(FWD, False), (FILTER, False), (DATA, False), (FILTER, True)} <= seen and len(sides) == 2
+
+
+def direct_filter_bytes(d):
+    """What a kernel gradient needs without the transforms: in bfloat16 the least it runs with (one plan, whatever is offered), in
+    float what the float kernel needs (the two terms stay in the scratch memory exactly where that does)."""
+    if d.dtype == vcnn.F32:
+        vcnn.set_conv_algo(vcnn.ALGO_IMPLICIT)
+        try:
+            assert route(d, FILTER) == "implicit"
+            return vcnn.conv_workspace_bytes(d, FILTER)
+        finally:
+            vcnn.set_conv_algo(vcnn.ALGO_AUTO)
+    low, high = -1, vcnn.conv_workspace_bytes(d, FILTER)
+    while high - low > 1:
+        mid = (low + high) // 2
+        try:
+            vcnn.conv_route(d, FILTER, mid)
+            high = mid
+        except vcnn.VcnnError:
+            low = mid
+    assert vcnn.conv_route(d, FILTER, high) != "spectral"
+    return high
 
 
 @pytest.mark.gpu
