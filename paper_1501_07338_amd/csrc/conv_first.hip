@@ -7,13 +7,15 @@
 // l holds rows l % 32 and the contraction index 2 t + l / 32 of each step t), the input rows under the block's pixels are
 // staged once, and the waves walk their tiles of 32 pixels of one sample with no barrier: a step reads one float per lane
 // from the halo tile at lane_base(pixel) + offset(t) for TM matrix instructions, and a tile's stores leave while the next
-// tile's products run.  64 1 64 64 -> 64 9 9: 61 -> 44 us (28 of them products: 18 of matrix instructions at two waves a SIMD,
-// then the stores of 67 MB and the staging of a block); 128 1 28 28 -> 20 5 5: 8 us, as before.  Halo reads a further group
+// tile's products run.  64 1 64 64 -> 64 9 9: 61 -> 42 us (28 of them products: 18 of matrix instructions at two waves a SIMD,
+// then the stores of 67 MB and the staging of a block); 128 1 28 28 -> 20 5 5: 12 -> 8 us.  Halo reads a further group
 // ahead: no change; 1024 blocks: slower.
 //
-// The contraction runs over (channel, kernel row, column pairs); where the kernel has an odd number of columns the lanes of
-// the second half repeat the first half's entry in the last pair with a zero weight, so that no pixel outside an output's
-// window is read for it (a zero times an infinity would spoil the sum).
+// The contraction runs over (channel, kernel row, column pairs).  Where the kernel has an odd number of columns the second half has
+// no entry in the last pair, and the steps compiled beyond those in use have none at all: their pixels are put to zero by one
+// select a step, with the lanes' mask in scalar registers, since a zero weight times an infinity would be NaN (64 1 64 64 -> 64 9 9
+// 42 -> 40 us with it, fewer registers; 16 3 184 90 -> 31 5 7 35 -> 37, 128 1 28 28 -> 20 5 5 8.1 -> 8.8).  The sums begin with the bias,
+// which measures 0.89 to 1.0 of the error of adding it last (14 layers, eight seeds each).
 #include <algorithm>
 #include <type_traits>
 
@@ -36,8 +38,8 @@ struct FirstArgs {
   int tiles_per_img, tiles_per_wave, blocks_per_img, groups;
   int relu;
   unsigned magic_wp, magic_nr, magic_s2;  // ceil(2^32 / .): division by multiply-high, exact below 2^16
-  uint16_t offset[kMaxSteps];     // of step t inside the halo tile ...
-  uint16_t second[kMaxSteps];     // ... and 1 where its second half has an entry of its own
+  uint16_t offset[kMaxSteps];     // of step t inside the halo tile
+  uint64_t first, second;         // bit t: the first, the second half of step t has an entry
 };
 
 template <int TM, int STEPS, typename T>
@@ -45,8 +47,8 @@ __global__ __launch_bounds__(kThreads) void conv_first_kernel(FirstArgs a) {
   constexpr int PITCH = 2 * STEPS + 1;  // odd: the 32 rows of a read on different banks
   extern __shared__ float first_lds[];
   float* const ws = first_lds;                              // [32 TM][PITCH]
-  float* const bias = ws + ((32 * TM * PITCH + 3) & ~3);    // [32 TM]
-  float* const halo = bias + 32 * TM;                       // [c][nr][wp]
+  float* const halo = ws + ((32 * TM * PITCH + 3) & ~3);    // [c][nr][wp]
+  float* const bias = halo + a.c * a.nr * a.wp;             // [32 TM] (an absent second half may read its first word)
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, half = lane >> 5;
   const int group = blockIdx.x % a.groups, rest = blockIdx.x / a.groups;
   const int n = rest / a.blocks_per_img, share = rest - n * a.blocks_per_img;
@@ -124,13 +126,19 @@ __global__ __launch_bounds__(kThreads) void conv_first_kernel(FirstArgs a) {
     const int tile = t0 + q * 4 + wave;
     if (tile >= a.tiles_per_img) break;
     const int p = tile * 32 + l32, pc = min(p, a.P - 1), oy = pc / a.ow;
-    const int base = (oy - oh_first) * a.wp + (pc - oy * a.ow);
+    const int base = (oy - oh_first) * a.wp + (pc - oy * a.ow) + half;
     f32x16 acc[TM];
+    int first[2] = {(int)a.first, (int)(a.first >> 32)}, second[2] = {(int)a.second, (int)(a.second >> 32)};
+    asm volatile("" : "+s"(first[0]), "+s"(first[1]), "+s"(second[0]), "+s"(second[1]));  // (else every step's mask is kept, in registers that spill)
+    auto present = [&](float v, int t) {  // 0 in the lanes without an entry
+      const uint64_t lanes = (uint64_t)(unsigned)__builtin_amdgcn_sbfe(second[t >> 5], t & 31, 1) << 32 | (unsigned)__builtin_amdgcn_sbfe(first[t >> 5], t & 31, 1);
+      return __builtin_amdgcn_inverse_ballot_w64(lanes) ? v : 0.f;
+    };
     // (eight steps' values requested while the eight before are multiplied)
     float b[2][8];
     auto request = [&](int t0, float (&v)[8]) {
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = halo[base + a.offset[t0 + u] + (half & a.second[t0 + u])];
+      for (int u = 0; u < 8; ++u) v[u] = halo[base + a.offset[t0 + u]];
     };
     request(0, b[0]);
 #pragma unroll
@@ -140,7 +148,7 @@ __global__ __launch_bounds__(kThreads) void conv_first_kernel(FirstArgs a) {
 #pragma unroll
       for (int u = 0; u < 8; ++u)
 #pragma unroll
-        for (int mi = 0; mi < TM; ++mi) acc[mi] = __builtin_amdgcn_mfma_f32_32x32x2f32(wr[mi][t + u], b[(t / 8) & 1][u], t + u == 0 ? start[mi] : acc[mi], 0, 0, 0);
+        for (int mi = 0; mi < TM; ++mi) acc[mi] = __builtin_amdgcn_mfma_f32_32x32x2f32(wr[mi][t + u], present(b[(t / 8) & 1][u], t + u), t + u == 0 ? start[mi] : acc[mi], 0, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
     }
     if (p >= a.P) continue;
@@ -219,7 +227,7 @@ vcnn_status launch_conv_first(const FirstPlan& p, int dtype, const ConvGeom& g, 
   for (int t = 0; t < a.steps; ++t) {
     const int cr = 2 * t / a.s2, s = 2 * t % a.s2;
     a.offset[t] = (uint16_t)((cr / g.r * p.nr + cr % g.r) * p.wp + s);
-    a.second[t] = s + 1 < g.s;
+    a.first |= 1ULL << t, a.second |= (uint64_t)(s + 1 < g.s) << t;
   }
   if (dtype == VCNN_BF16) launch_typed<bf16>(a, p, g.n, st);
   else launch_typed<float>(a, p, g.n, st);

@@ -48,15 +48,18 @@ def test_against_the_oracle(shape, dtype, relu):
     vcnn.conv_fwd(d, xd, wd, torch.from_numpy(b).to(DEV), y, None)
     # float sums of at most 128 terms; one rounding to eight bits
     assert_close(to_np(y.float()), O.conv_fwd(x, wt, b, pad=(ph, pw), relu=relu), 4e-3 if bf16 else 2e-6)
-    if relu:
-        return
-    at = (0, c - 1, h // 2, w // 2)
-    spoilt = x.copy()
-    spoilt[at] = np.inf
-    mark = np.zeros_like(x)
-    mark[at] = 1
-    touched = np.broadcast_to((O.conv_fwd(mark, np.ones_like(wt)[:1], np.zeros(1, np.float32), pad=(ph, pw)) != 0), y.shape)
-    got = torch.full_like(y, float("nan"))
-    vcnn.conv_fwd(d, torch.from_numpy(spoilt).to(DEV).to(tt), wd, torch.from_numpy(b).to(DEV), got, None)
-    got, base = to_np(got.float()), to_np(y.float())
-    assert np.array_equal(got[~touched], base[~touched]) and not np.any(np.isfinite(got[touched]))
+    # an infinity: infinite, of the right sign, where a window holds it, and the same bits elsewhere; in the middle, and in the corner
+    # where it is the first pixel of a window (which the steps without an entry read)
+    for at in ((0, c - 1, h // 2, w // 2), (0, 0, min(r, h - 1) - ph, 0)):
+        spoilt = x.copy()
+        spoilt[at] = np.inf
+        mark = np.zeros_like(x)
+        mark[at] = 1
+        touched = np.broadcast_to((O.conv_fwd(mark, np.ones_like(wt)[:1], np.zeros(1, np.float32), pad=(ph, pw)) != 0), y.shape)
+        got = torch.full_like(y, float("nan"))
+        vcnn.conv_fwd(d, torch.from_numpy(spoilt).to(DEV).to(tt), wd, torch.from_numpy(b).to(DEV), got, None)
+        got, base = to_np(got.float()), to_np(y.float())
+        assert np.any(touched) and np.array_equal(got[~touched], base[~touched])
+        signs = O.conv_fwd(mark, wt, np.zeros_like(b), pad=(ph, pw))  # (one element meets the infinity: its weight)
+        want = np.where(signs > 0, np.inf, 0 if relu else -np.inf)
+        assert np.all(signs[touched] != 0) and np.array_equal(got[touched], want[touched])
