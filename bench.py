@@ -570,6 +570,7 @@ def main():
                                      "scaled by powers of two, 23 bits, fp32 accumulation); others: the float instruction",
                    "loss_first_step": main_res["loss_first_step"]},
         "conv_gflops_fwd_bwd": main_res["conv_gflops_fwd_bwd"],
+        "conv_gflops_counted": "the direct sum's flops, whatever the route: a pass through the Fourier domain does a fraction of them",
         "conv_pct_mfma_peak": main_res["conv_pct_mfma_peak"],
         "roofline": {k: main_res["roofline"][k] for k in ("kernel", "bound", "achieved", "peak", "unit", "frac", "traffic")},
         # [layer, pass, ms, TFLOP/s, % of the matrix-core peak]

@@ -117,8 +117,9 @@ vcnn_status vcnn_conv_out_shape(const vcnn_conv_desc* d, int32_t* oh, int32_t* o
  * query asks for the float kernel's workspace only (often 0), and a call that brings just that runs it; one that brings
  * more (64 MiB will do) takes the two-term kernels and works through the batch in parts:
  * vcnn_conv_route tells what a size buys.  The passes through the Fourier domain ask for their spectra: up to 1 GiB, a
- * forward pass 64 MiB (it works through its maps in parts; more workspace, fewer parts).  An input gradient that ran in
- * a few MiB before then asks for hundreds: it still runs with less, down to what the direct routes need. */
+ * forward pass 64 MiB (it works through its maps in parts; more workspace, fewer parts).  An input gradient that runs in
+ * a few MiB by a direct route then asks for hundreds (64 64 96 96 -> 64 maps of 9 x 9: 545 MiB; 64 32 128 128 -> 64 of 7 x 7: 900): it
+ * still runs with less, down to what the direct routes need. */
 vcnn_status vcnn_conv_workspace_bytes(const vcnn_conv_desc* d, int32_t pass, size_t* bytes);
 /* The route the given pass takes with that many bytes of aligned workspace, under the present VCNN_ALGO_* choice, as a
  * short static string (for diagnostics and tests): "two_term", "two_term_fold" and "two_term_pointwise" are the fp32

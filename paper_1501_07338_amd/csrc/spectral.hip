@@ -440,8 +440,10 @@ bool spectral_plan(const ConvGeom& g, int pass, size_t budget, SpectralPlan* p) 
   // 512 maps has an error of 4.6e-7, over 64 of 2.1e-7, the two-term product 1.9e-7): a block of an input gradient takes two
   // of them, a kernel gradient's sums are cut into slices, which the inverse transform adds in double.  A forward pass's
   // slices would be as large as its result; its blocks take every channel, and up to 64 in one sum.  An input gradient over fewer
-  // maps competes with a transposed product whose own sums are shorter, and takes 16: 64 20 64 64 -> 80 16 16 1.62e-7 -> 1.37e-7, that
-  // product 1.36e-7 (200 maps 1.37e-7 against 1.53e-7; 512 maps 1.69e-7 with 32 and 683 us a layer, 1.38e-7 with 16 and 741 us).
+  // maps competes with a transposed product whose own sums are shorter, and takes 16: the line lies where the two errors meet.
+  // 16 38 64 64 -> k 16 16, error of that product / of sums of 32 (time of the pass) / of 16, in 1e-7: 96 maps 1.38 / 1.69 (112 us) / 1.38 (126),
+  // 200 1.52 / 1.67 (156) / 1.37 (172), 300 1.66 / 1.67 (175) / 1.38 (199), 340 1.71 / 1.52 (202) / 1.39 (227), 400 1.77 / 1.60 (230)
+  // / 1.40 (265), 512 1.89 / 1.61 (296) / 1.41 (348).  (Four more shapes, whose other routes have 2.8e-7 and more: 1.4 to 1.8 with 32, 1.2 to 1.6 with 16.)
   const int most = data || (filter && q.along) ? 64 : (filter ? 32 : 1 << 30);
   q.per_split = (int)std::min<double>(depth, most);
   if (data) {
